@@ -1,9 +1,29 @@
-// Generic (any dtype, any d <= 128, any Nq / Nc) kernels in plain fp32 FMA arithmetic.
-// They serve the shapes the MFMA kernels do not cover (fp32 inputs, d != 128); the work per
-// call is small there, so they are written for clarity: one wavefront per output row, keys
-// (or queries) spread over the 64 lanes, dot products over d done per lane, reductions and
-// broadcasts through lane shuffles.  Same mathematics as the tiled kernels: paper Alg. 1 loop
-// body + merge for the forward, Alg. 2 block pair for the backward.
+// Forward and backward for every call that the bf16 MFMA kernels do not take: fp32 tensors, bf16
+// head dimensions that are no multiple of 8, slices or chunks beyond the 32-bit addressing of those
+// kernels.  Same mathematics (paper Alg. 1 loop body + merge, Alg. 2 block pair), all of it in fp32
+// on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 products, fp32 accumulation).
+//
+// What bounds them: the fp32 matrix rate (157 TFLOP/s nominal, 130 measured for a large product), 64
+// cycles per MFMA, so that operand traffic is small beside it.  Hence no LDS tiles and no barriers
+// in the loops: a wavefront owns 32 query rows (or 32 keys), keeps their operands and accumulators in
+// registers and reads the other side's 32-row tiles straight from memory, each operand while the
+// MFMAs of the one before it run.  The wavefronts of a workgroup share one row block and take its
+// tiles in turn (their partial results meet in LDS at the end, in a fixed order): a slice of 256
+// rows would otherwise keep 8 of the chip's 1024 SIMDs busy.
+// Measured per launch, forward / dQ / dK+dV, against one wavefront per row with scalar FMAs (the form
+// these kernels replace): fp32, 8 heads of 700 x 700, d = 128: 448 / 522 / 1927 -> 41 / 63 / 84 us
+// (half of the fp32 matrix rate; what is left is the address arithmetic and register moves of one
+// wavefront per SIMD); fp32, one head of 256 x 256, d = 64: 48 / 46 / 93 -> 13 / 18 / 26 us; bf16,
+// d = 96, 32 heads of 777 x 777: 1208 / 1070 / 4308 -> 272 / 480 / 587 us.
+//
+// Operand layouts of v_mfma_f32_32x32x2_f32 (lane = 32 h + lr): A holds [m = lr][k = h], B holds
+// [k = h][n = lr], one value each; D register r holds [m = 8 (r / 4) + 4 h + r % 4][n = lr].
+//  - Contractions over d read four consecutive d per lane (d = 8 ks + 4 h + j); MFMA j of step ks
+//    contracts d = 8 ks + j (h = 0) and 8 ks + 4 + j (h = 1) on both sides.
+//  - A score register r is the B operand (forward, dQ) or A operand (dK, dV) of the second product as
+//    it stands: its two keys (rows), of h = 0 and h = 1, are the two k of that MFMA.
+//  - The other operand of the second product is a row of V, K, dO or Q spread over lr: block db of
+//    lane lr is column col_of(db, lr).
 #include "burst_common.h"
 
 namespace burst {
@@ -15,260 +35,604 @@ struct GenArgs {
   float* dQ; float* dK; float* dV;
   int Nq, Nc, d, BH;
   int causal;
-  float scale;
+  float scale, c;                                 // c = scale * log2(e)
   long long q_off, k_off;
   long long window;
-  const uint8_t* bmask; int bsize, bpitch;        // block mask (nullptr = none)
+  const uint8_t* bmask; int bsize, bpitch;        // block mask (nullptr = none); bsize a multiple of 64
   long long bhstride;                             // bytes between heads' flag matrices (0 = shared)
   Layout lay;                                     // strides of Q, dO and of K, V
   int group;                                      // query heads per key/value head
   int acc_dq, acc_dkv;
+  int blocks;                                     // 32-row (32-key) blocks per head
 };
 
-// Visibility of key `key` of the chunk from query row `row` of the slice (both in range).
-__device__ __forceinline__ bool visible(const GenArgs& a, int head, int row, int key) {
-  const long long qpos = a.q_off + row, kpos = a.k_off + key;
-  if (a.causal && kpos > qpos) return false;
-  if (a.window != 0 && kpos <= qpos - a.window) return false;
-  if (a.bmask != nullptr && a.bmask[(size_t)head * a.bhstride + (size_t)(row / a.bsize) * a.bpitch + key / a.bsize] == 0) return false;
+__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ int reg_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+
+// How one call shape reads its rows.  VEC: fp32 with d a multiple of 4 (rows then start on 16 bytes).
+template <typename T, int D, bool VEC>
+struct Rows {
+  static constexpr int NK = D / 8;                // four-wide operand pieces of a row
+  static constexpr int NB = D / 32;               // 32-wide blocks of d
+  static constexpr bool PACKED = VEC && D != 96;  // columns NB lr .. NB lr + NB - 1 in one load
+  static __device__ __forceinline__ int col_of(int db, int lr) { return PACKED ? NB * lr + db : 32 * db + lr; }
+  // columns 8 ks + 4 h .. + 3.  Past d: whatever the row's last columns hold (the other operand, `fixed`
+  // below, is zero there).
+  static __device__ __forceinline__ f32x4 piece(const T* row, int col, int d) {
+    f32x4 v;
+    if constexpr (VEC) {
+      v = *reinterpret_cast<const f32x4*>(row + min(col, d - 4));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; j++) v[j] = (float)row[min(col + j, d - 1)];
+    }
+    return v;
+  }
+  // the same, zero past d and in rows that do not exist
+  static __device__ __forceinline__ f32x4 fixed(const T* row, int col, int d, bool ok) {
+    f32x4 v = piece(row, col, d);
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[j] = (ok && col + j < d) ? v[j] : 0.f;
+    return v;
+  }
+  // block columns of lane lr (past d: anything, such columns are never stored)
+  static __device__ __forceinline__ void spread(const T* row, int lr, int d, float (&v)[NB]) {
+    if constexpr (PACKED) {
+      typedef __attribute__((ext_vector_type(NB))) float vec;
+      if constexpr (NB == 1) v[0] = row[min(lr, d - 1)];
+      else {
+        const vec x = *reinterpret_cast<const vec*>(row + min(NB * lr, d - NB));
+#pragma unroll
+        for (int db = 0; db < NB; db++) v[db] = x[db];
+      }
+    } else {
+#pragma unroll
+      for (int db = 0; db < NB; db++) v[db] = (float)row[min(32 * db + lr, d - 1)];
+    }
+  }
+};
+
+// Workgroup id -> (head, block).  Ids go round-robin to the 8 XCDs; each XCD gets one run of
+// consecutive blocks, so that a head's tensors stay in one L2 and every XCD gets the same number of
+// workgroups whatever the number of heads.
+__device__ __forceinline__ bool gen_locate(int bid, int heads, int blocks, int& head, int& blk) {
+  const int total = heads * blocks, per = (total + 7) >> 3;
+  const int lin = (bid & 7) * per + (bid >> 3);
+  if ((bid >> 3) >= per || lin >= total) return false;
+  head = lin / blocks;
+  blk = lin - head * blocks;
   return true;
 }
+static unsigned gen_grid(long long heads, long long blocks) { return (unsigned)((heads * blocks + 7) / 8 * 8); }
 
-template <typename T> __device__ __forceinline__ float ld(const T* p) { return (float)(*p); }
-
-__device__ __forceinline__ float wave_max(float v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
+// Key tiles (32 keys) of the chunk that rows [row0, row0 + 32) of the slice can see: [lo, hi).
+__device__ __forceinline__ void key_tiles(const GenArgs& a, int row0, int& lo, int& hi) {
+  lo = 0; hi = (a.Nc + 31) >> 5;
+  if (a.causal) {
+    const long long last = a.q_off + min(row0 + 31, a.Nq - 1) - a.k_off;   // last visible key
+    if (last < 0) hi = 0;
+    else if ((last >> 5) + 1 < hi) hi = (int)(last >> 5) + 1;
+  }
+  if (a.window > 0) {
+    const long long first = a.q_off + row0 - a.window + 1 - a.k_off;
+    if (first >= a.Nc) lo = hi;
+    else if (first > 0) lo = (int)(first >> 5);
+  }
 }
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+// Query tiles (32 rows) that see keys [key0, key0 + 32).
+__device__ __forceinline__ void row_tiles(const GenArgs& a, int key0, int& lo, int& hi) {
+  lo = 0; hi = (a.Nq + 31) >> 5;
+  if (a.causal) {
+    const long long first = a.k_off + key0 - a.q_off;
+    if (first >= a.Nq) lo = hi;
+    else if (first > 0) lo = (int)(first >> 5);
+  }
+  if (a.window > 0) {
+    const long long last = a.k_off + min(key0 + 31, a.Nc - 1) + a.window - 1 - a.q_off;
+    if (last < 0) hi = 0;
+    else if ((last >> 5) + 1 < hi) hi = (int)(last >> 5) + 1;
+  }
+}
+// A 32 x 32 tile lies in one block of the flags (their edge is a multiple of 64).
+__device__ __forceinline__ bool tile_flag(const GenArgs& a, int head, int row0, int key0) {
+  if (a.bmask == nullptr) return true;
+  return a.bmask[(size_t)head * a.bhstride + (size_t)(row0 / a.bsize) * a.bpitch + key0 / a.bsize] != 0;
 }
 
 // ---------------------------------------------------------------------------- forward
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, int D, bool VEC, int W>
+__global__ void __launch_bounds__(64 * W, W / 4)
 fwd_generic_kernel(GenArgs a) {
-  __shared__ float qrow[4][128];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  long long wave = (long long)blockIdx.x * 4 + w;
-  long long total = (long long)a.BH * a.Nq;
-  const bool live = wave < total;
-  if (!live) wave = 0;                             // keep every wavefront up to the barrier
-  const int head = (int)(wave / a.Nq), row = (int)(wave % a.Nq);
-  const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
+  using R = Rows<T, D, VEC>;
+  constexpr int NB = R::NB, NK = R::NK;
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial O^T, then [W][32] m, l
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int head, blk;
+  if (!gen_locate(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  const int row0 = blk * 32, row = row0 + lr;
   const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
   const T* Vh = (const T*)a.V + a.lay.kv_base(head / a.group);
-  for (int t = lane; t < a.d; t += 64) qrow[w][t] = ld(Qr + t);
-  __syncthreads();
-  if (!live) return;
-  const long long qpos = a.q_off + row;
-  float m_run = BURST_NEG_INF, l_run = 0.f, o0 = 0.f, o1 = 0.f;   // dims lane and lane + 64
-  for (int k0 = 0; k0 < a.Nc; k0 += 64) {
-    int key = k0 + lane;
-    bool vis = key < a.Nc && visible(a, head, row, key);
-    float s = BURST_NEG_INF;
-    if (vis) {
-      float acc = 0.f;
-      const T* kr = Kh + (size_t)key * a.lay.ks_r;
-      for (int t = 0; t < a.d; t++) acc = __builtin_fmaf(qrow[w][t], ld(kr + t), acc);
-      s = acc * a.scale;
-    }
-    float m_tile = wave_max(s);
-    float m_new = fmaxf(m_run, m_tile);
-    float ref = (m_new == BURST_NEG_INF) ? 0.f : m_new;
-    float p = expf(s - ref);                       // exp(-inf) = 0 for masked keys
-    float alpha = expf(m_run - ref);
-    l_run = l_run * alpha + wave_sum(p);
-    o0 *= alpha; o1 *= alpha;
-    m_run = m_new;
-    int nk = min(64, a.Nc - k0);
-    for (int k = 0; k < nk; k++) {
-      float pk = __shfl(p, k);
-      const T* vr = Vh + (size_t)(k0 + k) * a.lay.ks_r;
-      if (lane < a.d) o0 = __builtin_fmaf(pk, ld(vr + lane), o0);
-      if (lane + 64 < a.d) o1 = __builtin_fmaf(pk, ld(vr + lane + 64), o1);
+  int lo, hi;
+  key_tiles(a, row0, lo, hi);
+  auto seek = [&](int t) {                        // first tile from t on, in steps of W, that the flags leave
+    while (t < hi && !tile_flag(a, head, row0, t * 32)) t += W;
+    return t;
+  };
+
+  f32x16 o[NB];
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) o[db][r] = 0.f;
+  float m2 = BURST_NEG_INF, lsum = 0.f;           // reference max (log2 units), sum over this lane's keys
+
+  int t = seek(lo + w);
+  if (t < hi) {
+    f32x4 qf[NK], kf[NK];
+    const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) qf[ks] = R::fixed(Qr, 8 * ks + 4 * h, a.d, row < a.Nq);
+    auto load_k = [&](int tile) __attribute__((always_inline)) {
+      const T* kr = Kh + (size_t)min(tile * 32 + lr, a.Nc - 1) * a.lay.ks_r;
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) kf[ks] = R::piece(kr, 8 * ks + 4 * h, a.d);
+    };
+    load_k(t);
+    while (t < hi) {
+      const int key0 = t * 32, tn = seek(t + W);
+      float vf[16][NB];
+      auto load_v = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = r0; r < r0 + 8; r++)
+          R::spread(Vh + (size_t)min(key0 + reg_row(r, h), a.Nc - 1) * a.lay.ks_r, lr, a.d, vf[r]);
+      };
+      load_v(0);
+      __builtin_amdgcn_sched_barrier(0);
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; r++) s[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) s = mfma_f32(kf[ks][j], qf[ks][j], s);
+      __builtin_amdgcn_sched_barrier(0);
+      load_v(8);
+      // masks: register r holds key key0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
+      const long long dd = (a.q_off - a.k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, a.Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
+      if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
+      float v = BURST_NEG_INF;
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        s[r] = (cpart <= lim && cpart >= lim_lo) ? s[r] : BURST_NEG_INF;
+        v = fmaxf(v, s[r]);
+      }
+      const float mx = max_both_halves(v) * a.c;
+      const float m_new = fmaxf(m2, mx), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
+      const float alpha = fast_exp2(m2 - ref);
+      m2 = m_new;
+      lsum *= alpha;
+#pragma unroll
+      for (int db = 0; db < NB; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) o[db][r] *= alpha;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = fast_exp2(__builtin_fmaf(s[r], a.c, -ref)); lsum += s[r]; }
+      // O^T += V^T P^T
+#pragma unroll
+      for (int r = 0; r < 8; r++)
+#pragma unroll
+        for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[r][db], s[r], o[db]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (tn < hi) load_k(tn);
+#pragma unroll
+      for (int r = 8; r < 16; r++)
+#pragma unroll
+        for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[r][db], s[r], o[db]);
+      t = tn;
     }
   }
-  if (m_run == BURST_NEG_INF) return;              // the row saw no key: state untouched
-  // merge into the stored state (Alg. 1 merge step)
-  size_t r = (size_t)head * a.Nq + row;
-  float m_old = a.m[r], l_old = a.l[r];
-  float m_new = fmaxf(m_old, m_run);
-  float fa = expf(m_old - m_new), fb = expf(m_run - m_new);
-  float* orow = a.O_acc + r * a.d;
-  if (lane < a.d) orow[lane] = (fa == 0.f ? 0.f : fa * orow[lane]) + fb * o0;
-  if (lane + 64 < a.d) orow[lane + 64] = (fa == 0.f ? 0.f : fa * orow[lane + 64]) + fb * o1;
-  if (lane == 0) {
-    a.m[r] = m_new;
-    a.l[r] = (fa == 0.f ? 0.f : fa * l_old) + fb * l_run;
+  // the wavefronts' partial results meet in LDS
+  float* const ml = gsh + W * NB * 1024;
+  const float l_half = sum_both_halves(lsum);
+  if (h == 0) { ml[w * 64 + lr] = m2; ml[w * 64 + 32 + lr] = l_half; }
+  __syncthreads();
+  float mg = BURST_NEG_INF, lg = 0.f;
+#pragma unroll
+  for (int i = 0; i < W; i++) mg = fmaxf(mg, ml[i * 64 + lr]);
+  const float mref = mg == BURST_NEG_INF ? 0.f : mg;
+#pragma unroll
+  for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2(ml[i * 64 + lr] - mref);
+  const float own = fast_exp2(m2 - mref);
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = o[db][r] * own;
+  __syncthreads();
+  if (row >= a.Nq || mg == BURST_NEG_INF) return;  // rows that saw no key keep their state
+  const size_t sr = (size_t)head * a.Nq + row;
+  const float m_old = a.m[sr] * kLog2e, l_old = a.l[sr];
+  const float m_new = fmaxf(m_old, mg);
+  const float fa = fast_exp2(m_old - m_new), fb = fast_exp2(mg - m_new);
+  __syncthreads();                                 // every wavefront has read the row's old m and l
+  if (w == 0 && h == 0) {
+    a.m[sr] = m_new * kLn2;
+    a.l[sr] = (fa == 0.f ? 0.f : fa * l_old) + fb * lg;
+  }
+  float* const orow = a.O_acc + sr * a.d;
+#pragma unroll
+  for (int rr = 0; rr < 16 / W; rr++) {
+    const int r = w * (16 / W) + rr, mrow = reg_row(r, h);
+    float v[NB];
+#pragma unroll
+    for (int db = 0; db < NB; db++) {
+      v[db] = 0.f;
+#pragma unroll
+      for (int i = 0; i < W; i++) v[db] += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+    }
+#pragma unroll
+    for (int db = 0; db < NB; db++) {
+      const int col = R::col_of(db, mrow);
+      if (col < a.d) orow[col] = (fa == 0.f ? 0.f : fa * orow[col]) + fb * v[db];
+    }
   }
 }
 
 // ---------------------------------------------------------------------------- backward, dQ
-// One wavefront per query row; lanes = keys of a 64-key tile.
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, int D, bool VEC, int W>
+__global__ void __launch_bounds__(64 * W, W / 4)
 bwd_dq_generic_kernel(GenArgs a) {
-  __shared__ float qrow[4][128];
-  __shared__ float grow[4][128];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  long long wave = (long long)blockIdx.x * 4 + w;
-  long long total = (long long)a.BH * a.Nq;
-  const bool live = wave < total;
-  if (!live) wave = 0;
-  const int head = (int)(wave / a.Nq), row = (int)(wave % a.Nq);
-  size_t r = (size_t)head * a.Nq + row;
-  const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
-  const T* Gr = (const T*)a.dO + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
+  using R = Rows<T, D, VEC>;
+  constexpr int NB = R::NB, NK = R::NK;
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dQ^T
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int head, blk;
+  if (!gen_locate(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  const int row0 = blk * 32, row = row0 + lr;
+  const bool ok = row < a.Nq;
   const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
   const T* Vh = (const T*)a.V + a.lay.kv_base(head / a.group);
-  for (int t = lane; t < a.d; t += 64) { qrow[w][t] = ld(Qr + t); grow[w][t] = ld(Gr + t); }
-  __syncthreads();
-  if (!live) return;
-  const float lse = a.lse[r], Dr = a.D[r];
-  const long long qpos = a.q_off + row;
-  float q0 = 0.f, q1 = 0.f;
-  for (int k0 = 0; k0 < a.Nc; k0 += 64) {
-    int key = k0 + lane;
-    bool vis = key < a.Nc && lse != BURST_NEG_INF && visible(a, head, row, key);
-    float ds = 0.f;
-    if (vis) {
-      float sa = 0.f, dp = 0.f;
-      const T* kr = Kh + (size_t)key * a.lay.ks_r;
-      const T* vr = Vh + (size_t)key * a.lay.ks_r;
-      for (int t = 0; t < a.d; t++) {
-        sa = __builtin_fmaf(qrow[w][t], ld(kr + t), sa);
-        dp = __builtin_fmaf(grow[w][t], ld(vr + t), dp);
-      }
-      float p = expf(sa * a.scale - lse);
-      ds = p * (dp - Dr);
+  const size_t sr = (size_t)head * a.Nq + min(row, a.Nq - 1);
+  int lo, hi;
+  key_tiles(a, row0, lo, hi);
+  auto seek = [&](int t) {
+    while (t < hi && !tile_flag(a, head, row0, t * 32)) t += W;
+    return t;
+  };
+
+  f32x16 dq[NB];
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
+  int t = seek(lo + w);
+  if (t < hi) {
+    f32x4 qf[NK], gf[NK], kf[NK];
+    const size_t qrow = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) {
+      qf[ks] = R::fixed((const T*)a.Q + qrow, 8 * ks + 4 * h, a.d, ok);
+      gf[ks] = R::fixed((const T*)a.dO + qrow, 8 * ks + 4 * h, a.d, ok);
     }
-    int nk = min(64, a.Nc - k0);
-    for (int k = 0; k < nk; k++) {
-      float dsk = __shfl(ds, k);
-      const T* kr = Kh + (size_t)(k0 + k) * a.lay.ks_r;
-      if (lane < a.d) q0 = __builtin_fmaf(dsk, ld(kr + lane), q0);
-      if (lane + 64 < a.d) q1 = __builtin_fmaf(dsk, ld(kr + lane + 64), q1);
+    const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
+    const float nlse2 = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv * kLog2e;   // -inf: P = 0
+    const float nD = ok ? -a.D[sr] : 0.f;
+    auto load_k = [&](int tile) __attribute__((always_inline)) {
+      const T* kr = Kh + (size_t)min(tile * 32 + lr, a.Nc - 1) * a.lay.ks_r;
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) kf[ks] = R::piece(kr, 8 * ks + 4 * h, a.d);
+    };
+    load_k(t);
+    while (t < hi) {
+      const int key0 = t * 32, tn = seek(t + W);
+      f32x4 vf[NK];
+      const T* vr = Vh + (size_t)min(key0 + lr, a.Nc - 1) * a.lay.ks_r;
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) vf[ks] = R::piece(vr, 8 * ks + 4 * h, a.d);
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = nD; }
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) s = mfma_f32(kf[ks][j], qf[ks][j], s);
+      __builtin_amdgcn_sched_barrier(0);
+      float kt[16][NB];
+      auto load_kt = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = r0; r < r0 + 8; r++)
+          R::spread(Kh + (size_t)min(key0 + reg_row(r, h), a.Nc - 1) * a.lay.ks_r, lr, a.d, kt[r]);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      load_kt(0);
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) dp = mfma_f32(vf[ks][j], gf[ks][j], dp);
+      __builtin_amdgcn_sched_barrier(0);
+      load_kt(8);
+      const long long dd = (a.q_off - a.k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, a.Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
+      if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        const float p = fast_exp2(__builtin_fmaf(s[r], a.c, nlse2));
+        dp[r] = (cpart <= lim && cpart >= lim_lo) ? p * dp[r] : 0.f;   // dS^T
+      }
+      // dQ^T += K^T dS^T
+#pragma unroll
+      for (int r = 0; r < 8; r++)
+#pragma unroll
+        for (int db = 0; db < NB; db++) dq[db] = mfma_f32(kt[r][db], dp[r], dq[db]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (tn < hi) load_k(tn);
+#pragma unroll
+      for (int r = 8; r < 16; r++)
+#pragma unroll
+        for (int db = 0; db < NB; db++) dq[db] = mfma_f32(kt[r][db], dp[r], dq[db]);
+      __builtin_amdgcn_sched_barrier(0);
+      t = tn;
     }
   }
-  float* out = a.dQ + r * a.d;
-  if (lane < a.d) out[lane] = (a.acc_dq ? out[lane] : 0.f) + a.scale * q0;
-  if (lane + 64 < a.d) out[lane + 64] = (a.acc_dq ? out[lane + 64] : 0.f) + a.scale * q1;
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = dq[db][r];
+  __syncthreads();
+  if (!ok) return;
+  float* const out = a.dQ + sr * a.d;
+#pragma unroll
+  for (int rr = 0; rr < 16 / W; rr++) {
+    const int r = w * (16 / W) + rr, mrow = reg_row(r, h);
+#pragma unroll
+    for (int db = 0; db < NB; db++) {
+      float v = 0.f;
+#pragma unroll
+      for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+      const int col = R::col_of(db, mrow);
+      if (col < a.d) out[col] = (a.acc_dq ? out[col] : 0.f) + a.scale * v;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------- backward, dK dV
-// One wavefront per key row; lanes = query rows of a 64-row tile.
-template <typename T>
-__global__ void __launch_bounds__(256)
+// Lane = key; score register r = query row reg_row(r, h) of the tile.
+template <typename T, int D, bool VEC, int W>
+__global__ void __launch_bounds__(64 * W, W / 4)
 bwd_dkv_generic_kernel(GenArgs a) {
-  __shared__ float krow[4][128];
-  __shared__ float vrow[4][128];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  long long wave = (long long)blockIdx.x * 4 + w;
-  long long total = (long long)(a.BH / a.group) * a.Nc;      // one wavefront per key row of a key/value head
-  const bool live = wave < total;
-  if (!live) wave = 0;
-  const int kvhead = (int)(wave / a.Nc), key = (int)(wave % a.Nc);
-  size_t kr_i = (size_t)kvhead * a.Nc + key;
-  const T* Kr = (const T*)a.K + a.lay.kv_base(kvhead) + (size_t)key * a.lay.ks_r;
-  const T* Vr = (const T*)a.V + a.lay.kv_base(kvhead) + (size_t)key * a.lay.ks_r;
-  for (int t = lane; t < a.d; t += 64) { krow[w][t] = ld(Kr + t); vrow[w][t] = ld(Vr + t); }
-  __syncthreads();
-  if (!live) return;
-  float k0a = 0.f, k1a = 0.f, v0a = 0.f, v1a = 0.f;
-  for (int g = 0; g < a.group; g++) {                        // the query heads that share this key/value head
-    const int head = kvhead * a.group + g;
-    const T* Qh = (const T*)a.Q + a.lay.q_base(head);
-    const T* Gh = (const T*)a.dO + a.lay.q_base(head);
-    const float* lseh = a.lse + (size_t)head * a.Nq;
-    const float* Dh = a.D + (size_t)head * a.Nq;
-    for (int r0 = 0; r0 < a.Nq; r0 += 64) {
-      int row = r0 + lane;
-      float p = 0.f, ds = 0.f;
-      if (row < a.Nq && visible(a, head, row, key)) {
-        float lse = lseh[row];
-        if (lse != BURST_NEG_INF) {
-          float sa = 0.f, dp = 0.f;
-          const T* qr = Qh + (size_t)row * a.lay.qs_r;
-          const T* gr = Gh + (size_t)row * a.lay.qs_r;
-          for (int t = 0; t < a.d; t++) {
-            sa = __builtin_fmaf(ld(qr + t), krow[w][t], sa);
-            dp = __builtin_fmaf(ld(gr + t), vrow[w][t], dp);
-          }
-          p = expf(sa * a.scale - lse);
-          ds = p * (dp - Dh[row]);
-        }
+  using R = Rows<T, D, VEC>;
+  constexpr int NB = R::NB, NK = R::NK;
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dK, then dV
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int kvhead, blk;
+  if (!gen_locate(blockIdx.x, a.BH / a.group, a.blocks, kvhead, blk)) return;
+  const int key0 = blk * 32, key = key0 + lr;
+  int lo, hi;
+  row_tiles(a, key0, lo, hi);
+  const int per_head = hi - lo, total = max(per_head, 0) * a.group;   // walk positions: the tiles of all heads of the group
+  auto place = [&](int n, int& head, int& tile) __attribute__((always_inline)) {
+    const int g = n / per_head;
+    head = kvhead * a.group + g;
+    tile = lo + n - g * per_head;
+  };
+  auto seek = [&](int n) {
+    while (n < total) {
+      int head, tile;
+      place(n, head, tile);
+      if (tile_flag(a, head, tile * 32, key0)) break;
+      n += W;
+    }
+    return n;
+  };
+
+  f32x16 dk[NB], dv[NB];
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
+  int n = seek(w);
+  if (n < total) {
+    f32x4 kf[NK], vf[NK];
+    const size_t krow = a.lay.kv_base(kvhead) + (size_t)min(key, a.Nc - 1) * a.lay.ks_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) {
+      kf[ks] = R::fixed((const T*)a.K + krow, 8 * ks + 4 * h, a.d, key < a.Nc);
+      vf[ks] = R::fixed((const T*)a.V + krow, 8 * ks + 4 * h, a.d, key < a.Nc);
+    }
+    // A tile is eight groups of MFMAs (S, dP, dV, dK, two halves each); every group's operands are
+    // requested one group ahead, which is all that fits beside the resident operands and
+    // accumulators (256 registers at d = 128).
+    constexpr int HK = NK / 2;
+    f32x4 pa[HK], pb[HK];                         // pieces of Q or dO rows: first and second half of a contraction over d
+    float ra[8][NB], rb[8][NB];                   // spread rows of dO or Q: first and second half of a contraction over rows
+    auto pieces = [&](f32x4 (&dst)[HK], const T* rowp, int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < HK; i++) dst[i] = R::piece(rowp, 8 * (half * HK + i) + 4 * h, a.d);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto rows8 = [&](float (&dst)[8][NB], const T* base, int row0, int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 8; i++)
+        R::spread(base + (size_t)min(row0 + reg_row(8 * half + i, h), a.Nq - 1) * a.lay.qs_r, lr, a.d, dst[i]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto over_d = [&](f32x16& acc, const f32x4 (&x)[HK], const f32x4 (&y)[NK], int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < HK; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc = mfma_f32(x[i][j], y[half * HK + i][j], acc);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto over_rows = [&](f32x16 (&acc)[NB], const f32x16& x, const float (&y)[8][NB], int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 8; i++)
+#pragma unroll
+        for (int db = 0; db < NB; db++) acc[db] = mfma_f32(x[8 * half + i], y[i][db], acc[db]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int head, tile;
+    place(n, head, tile);
+    const T* qrow = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(tile * 32 + lr, a.Nq - 1) * a.lay.qs_r;
+    pieces(pa, qrow, 0);
+    while (n < total) {
+      const int nn = seek(n + W), row0 = tile * 32;
+      const T* Qh = (const T*)a.Q + a.lay.q_base(head);
+      const T* Gh = (const T*)a.dO + a.lay.q_base(head);
+      const T* grow = Gh + (size_t)min(row0 + lr, a.Nq - 1) * a.lay.qs_r;
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+      pieces(pb, qrow, 1);
+      over_d(s, pa, kf, 0);
+      pieces(pa, grow, 0);
+      over_d(s, pb, kf, 1);
+      float lrow[16], drow[16];
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const size_t sr = (size_t)head * a.Nq + min(row0 + reg_row(r, h), a.Nq - 1);
+        lrow[r] = a.lse[sr];
+        drow[r] = a.D[sr];
       }
-      int nr = min(64, a.Nq - r0);
-      for (int j = 0; j < nr; j++) {
-        float pj = __shfl(p, j), dsj = __shfl(ds, j);
-        const T* qr = Qh + (size_t)(r0 + j) * a.lay.qs_r;
-        const T* gr = Gh + (size_t)(r0 + j) * a.lay.qs_r;
-        if (lane < a.d) { v0a = __builtin_fmaf(pj, ld(gr + lane), v0a); k0a = __builtin_fmaf(dsj, ld(qr + lane), k0a); }
-        if (lane + 64 < a.d) { v1a = __builtin_fmaf(pj, ld(gr + lane + 64), v1a); k1a = __builtin_fmaf(dsj, ld(qr + lane + 64), k1a); }
+      pieces(pb, grow, 1);
+      over_d(dp, pa, vf, 0);
+      rows8(ra, Gh, row0, 0);
+      over_d(dp, pb, vf, 1);
+      rows8(rb, Gh, row0, 1);
+      // masks: register r holds row row0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
+      const long long dd = (a.k_off - a.q_off) + key - ((long long)row0 + 4 * h);   // key position - row position at cpart 0
+      int lim = min(64, a.Nq - 1 - (row0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim_lo = (int)(dd < -1 ? -1 : dd > 64 ? 64 : dd);
+      if (a.window > 0) { const long long dl = dd + a.window - 1; lim = (int)min((long long)lim, dl < -1 ? -1LL : dl); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        const bool vis = cpart <= lim && cpart >= lim_lo && lrow[r] != BURST_NEG_INF;
+        const float p = fast_exp2(__builtin_fmaf(s[r], a.c, -lrow[r] * kLog2e));
+        dp[r] = vis ? p * (dp[r] - drow[r]) : 0.f;
+        s[r] = vis ? p : 0.f;
+      }
+      // dV += P^T dO, dK += dS^T Q
+      over_rows(dv, s, ra, 0);
+      rows8(ra, Qh, row0, 0);
+      over_rows(dv, s, rb, 1);
+      rows8(rb, Qh, row0, 1);
+      over_rows(dk, dp, ra, 0);
+      if (nn < total) {
+        place(nn, head, tile);
+        qrow = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(tile * 32 + lr, a.Nq - 1) * a.lay.qs_r;
+        pieces(pa, qrow, 0);
+      }
+      over_rows(dk, dp, rb, 1);
+      n = nn;
+    }
+  }
+  // lane = column, registers = keys; the two sums use the same LDS one after the other
+#pragma unroll
+  for (int which = 0; which < 2; which++) {
+    if (which) __syncthreads();
+#pragma unroll
+    for (int db = 0; db < NB; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
+    __syncthreads();
+    float* const base = which ? a.dV : a.dK;
+    const float f = which ? 1.f : a.scale;
+#pragma unroll
+    for (int rr = 0; rr < 16 / W; rr++) {
+      const int r = w * (16 / W) + rr, k = key0 + reg_row(r, h);
+      if (k >= a.Nc) continue;
+      float* const out = base + ((size_t)kvhead * a.Nc + k) * a.d;
+#pragma unroll
+      for (int db = 0; db < NB; db++) {
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+        const int col = R::col_of(db, lr);
+        if (col < a.d) out[col] = (a.acc_dkv ? out[col] : 0.f) + f * v;
       }
     }
   }
-  float* dk = a.dK + kr_i * a.d;
-  float* dv = a.dV + kr_i * a.d;
-  if (lane < a.d) {
-    dk[lane] = (a.acc_dkv ? dk[lane] : 0.f) + a.scale * k0a;
-    dv[lane] = (a.acc_dkv ? dv[lane] : 0.f) + v0a;
-  }
-  if (lane + 64 < a.d) {
-    dk[lane + 64] = (a.acc_dkv ? dk[lane + 64] : 0.f) + a.scale * k1a;
-    dv[lane + 64] = (a.acc_dkv ? dv[lane + 64] : 0.f) + v1a;
-  }
 }
 
+// ---------------------------------------------------------------------------- launchers
 static GenArgs make_args(const KParams& p) {
   GenArgs a = {};
   a.Nq = p.Nq; a.Nc = p.Nc; a.d = p.d; a.BH = p.B * p.H;
-  a.causal = p.causal; a.scale = p.scale; a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
+  a.causal = p.causal; a.scale = p.scale; a.c = p.scale * kLog2e; a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
   a.bmask = p.bmask; a.bsize = p.bsize; a.bpitch = p.bpitch; a.bhstride = p.bhstride; a.group = p.group;
   a.lay = p.lay;
   return a;
 }
 
+enum { GEN_FWD, GEN_DQ, GEN_DKV };
+template <int KIND, typename T, int D, bool VEC, int W>
+static int gen_launch(GenArgs a, hipStream_t s) {
+  const long long heads = KIND == GEN_DKV ? a.BH / a.group : a.BH;
+  a.blocks = (int)(((long long)(KIND == GEN_DKV ? a.Nc : a.Nq) + 31) / 32);
+  if (heads * a.blocks > 0x7fffff00LL) return BURST_ERR_SHAPE;
+  const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : 0)) * 4;
+  const dim3 grid(gen_grid(heads, a.blocks)), wg(64 * W);
+  void (*kernel)(GenArgs);
+  if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W>;
+  else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W>;
+  else kernel = bwd_dkv_generic_kernel<T, D, VEC, W>;
+  static DeviceOnce lds_opt_in;
+  const int st = lds_opt_in.run([&] {
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
+  });
+  if (st != BURST_OK) return st;
+  BURST_LAUNCH(kernel, grid, wg, lds, s, a);
+  return launch_status();
+}
+// Padded head dimension: the next multiple of 32.  With eight wavefronts per workgroup (two per
+// SIMD; the registers allow it up to 64) a row block's tiles are walked in half the time; that pays
+// while there are fewer row blocks than CUs.
+template <int KIND>
+static int gen_dispatch(const GenArgs& a, int dtype, hipStream_t s) {
+  const long long n = KIND == GEN_DKV ? (long long)(a.BH / a.group) * ((a.Nc + 31) / 32) : (long long)a.BH * ((a.Nq + 31) / 32);
+  const bool few = n <= 256;
+  if (dtype == BURST_F32 && a.d % 4 == 0) {
+    if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, s) : gen_launch<KIND, float, 32, true, 4>(a, s);
+    if (a.d <= 64) return few ? gen_launch<KIND, float, 64, true, 8>(a, s) : gen_launch<KIND, float, 64, true, 4>(a, s);
+    if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, s);
+    return gen_launch<KIND, float, 128, true, 4>(a, s);
+  }
+  if (dtype == BURST_F32) return a.d <= 64 ? gen_launch<KIND, float, 64, false, 4>(a, s) : gen_launch<KIND, float, 128, false, 4>(a, s);
+  return a.d <= 64 ? gen_launch<KIND, bf16, 64, false, 4>(a, s) : gen_launch<KIND, bf16, 128, false, 4>(a, s);
+}
+
 int launch_fwd_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
                        float* O_acc, float* m, float* l, hipStream_t s) {
-  long long waves = (long long)p.B * p.H * p.Nq;
-  if (waves == 0 || p.Nc == 0) return BURST_OK;
-  long long blocks = (waves + 3) / 4;
-  if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  if ((long long)p.B * p.H * p.Nq == 0 || p.Nc == 0) return BURST_OK;
   GenArgs a = make_args(p);
   a.Q = Q; a.K = K; a.V = V; a.O_acc = O_acc; a.m = m; a.l = l;
-  if (dtype == BURST_BF16) BURST_LAUNCH((fwd_generic_kernel<bf16>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-  else BURST_LAUNCH((fwd_generic_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-  return launch_status();
+  return gen_dispatch<GEN_FWD>(a, dtype, s);
 }
 
 int launch_bwd_dq_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
                           const void* dO, const float* lse, const float* D, float* dQ, int acc_dq, hipStream_t s) {
+  if ((long long)p.B * p.H * p.Nq == 0) return BURST_OK;
   GenArgs a = make_args(p);
   a.Q = Q; a.K = K; a.V = V; a.dO = dO; a.lse = lse; a.D = D; a.dQ = dQ; a.acc_dq = acc_dq;
-  long long wq = (long long)p.B * p.H * p.Nq;
-  if (wq == 0) return BURST_OK;
-  if ((wq + 3) / 4 > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  unsigned blocks = (unsigned)((wq + 3) / 4);
-  if (dtype == BURST_BF16) BURST_LAUNCH((bwd_dq_generic_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
-  else BURST_LAUNCH((bwd_dq_generic_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
-  return launch_status();
+  return gen_dispatch<GEN_DQ>(a, dtype, s);
 }
 
 int launch_bwd_dkv_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
                            const void* dO, const float* lse, const float* D, float* dK, float* dV,
                            int acc_dkv, hipStream_t s) {
+  if ((long long)p.B * p.H / p.group * p.Nc == 0) return BURST_OK;
   GenArgs a = make_args(p);
   a.Q = Q; a.K = K; a.V = V; a.dO = dO; a.lse = lse; a.D = D; a.dK = dK; a.dV = dV; a.acc_dkv = acc_dkv;
-  long long wk = (long long)p.B * p.H / p.group * p.Nc;
-  if (wk == 0) return BURST_OK;
-  if ((wk + 3) / 4 > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  unsigned blocks = (unsigned)((wk + 3) / 4);
-  if (dtype == BURST_BF16) BURST_LAUNCH((bwd_dkv_generic_kernel<bf16>), dim3(blocks), dim3(256), 0, s, a);
-  else BURST_LAUNCH((bwd_dkv_generic_kernel<float>), dim3(blocks), dim3(256), 0, s, a);
-  return launch_status();
+  return gen_dispatch<GEN_DKV>(a, dtype, s);
 }
 
 }  // namespace burst
