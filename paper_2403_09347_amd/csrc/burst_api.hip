@@ -23,20 +23,22 @@ int launch_bwd_dq_generic(const KParams&, int, const void*, const void*, const v
                           const float*, float*, int, hipStream_t);
 int launch_bwd_dkv_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
                            const float*, float*, float*, int, hipStream_t);
-namespace d64 {
-int launch_fwd(const KParams&, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
-int launch_bwd_dq(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                  const float*, float*, int, hipStream_t);
-int launch_bwd_dkv(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                   const float*, float*, float*, int, hipStream_t);
-}  // namespace d64
-namespace d128p {
-int launch_fwd(const KParams&, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
-int launch_bwd_dq(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                  const float*, float*, int, hipStream_t);
-int launch_bwd_dkv(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                   const float*, float*, float*, int, hipStream_t);
-}  // namespace d128p
+// the plainly written kernels of burst_plain_mfma.h, one namespace per build
+#define BURST_DECLARE_PLAIN(ns)                                                                                        \
+  namespace ns {                                                                                                       \
+  int launch_fwd(const KParams&, const void*, const void*, const void*, float*, float*, float*, hipStream_t);          \
+  int launch_bwd_dq(const KParams&, const void*, const void*, const void*, const void*, const float*, const float*,    \
+                    float*, int, hipStream_t);                                                                         \
+  int launch_bwd_dkv(const KParams&, const void*, const void*, const void*, const void*, const float*, const float*,   \
+                     float*, float*, int, hipStream_t);                                                                \
+  }
+BURST_DECLARE_PLAIN(d64)
+BURST_DECLARE_PLAIN(d128p)
+BURST_DECLARE_PLAIN(d32x)
+BURST_DECLARE_PLAIN(d64x)
+BURST_DECLARE_PLAIN(d96x)
+BURST_DECLARE_PLAIN(d128x)
+#undef BURST_DECLARE_PLAIN
 size_t materialized_workspace_bytes(const KParams&, int);
 size_t materialized_bwd_workspace_bytes(const KParams&, int);
 int launch_bwd_materialized(const KParams&, int, bool, const void*, const void*, const void*, const void*, const float*,
@@ -177,14 +179,32 @@ constexpr int kMaxMaskedRows = 8192 * 64;
 bool use_mfma(const burst_params* p, const KParams& k) {
   return p->dtype == BURST_BF16 && p->d == 128 && p->Nq <= kMaxMfmaRows && p->Nc <= kMaxMfmaRows && spans_fit(p, k);
 }
-// bf16, d = 64 has MFMA kernels of its own.
-bool use_d64(const burst_params* p, const KParams& k) {
-  if (!(p->dtype == BURST_BF16 && p->d == 64 && p->Nq <= kMaxMfmaRows && p->Nc <= kMaxMfmaRows &&
-        spans_fit(p, k))) return false;
-  if (p->block_mask == nullptr) return true;
-  // with block flags: lists of at most 4096 tiles (32 keys or rows each; rows of all heads of a group)
-  const long long group = (p->kv_heads > 0) ? p->H / p->kv_heads : 1;
-  return p->Nc <= 4096 * 32 && group * ((p->Nq + 31) / 32) <= 4096;
+// bf16 with another head dimension than 128: the plainly written kernels, built for d = 64 and, for
+// every other multiple of 8, at the next of the padded widths 32, 64, 96, 128 (their DMA descriptors
+// must span less than 2 GiB, see s_dma_off).  Null where the generic kernels have to do it: rows that
+// do not start on 16 bytes, sizes beyond the 32-bit addressing.  (d = 96, 32 heads of 777 causal rows,
+// differentiable call with its gradients: 1375 us on the generic kernels, 262 us padded.)
+struct PlainFamily {
+  decltype(&burst::d64::launch_fwd) fwd;
+  decltype(&burst::d64::launch_bwd_dq) bwd_dq;
+  decltype(&burst::d64::launch_bwd_dkv) bwd_dkv;
+};
+#define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv}
+const PlainFamily kD64 = BURST_PLAIN(d64), kD32x = BURST_PLAIN(d32x), kD64x = BURST_PLAIN(d64x), kD96x = BURST_PLAIN(d96x),
+                  kD128x = BURST_PLAIN(d128x);
+#undef BURST_PLAIN
+const PlainFamily* plain_family(const burst_params* p, const KParams& k) {
+  if (p->dtype != BURST_BF16 || p->d == 128 || p->d % 8 != 0 || p->Nq > kMaxMfmaRows || p->Nc > kMaxMfmaRows ||
+      !spans_fit(p, k)) return nullptr;
+  if (p->block_mask != nullptr) {
+    // with block flags: lists of at most 4096 tiles (32 keys or rows each; rows of all heads of a group)
+    const long long group = (p->kv_heads > 0) ? p->H / p->kv_heads : 1;
+    if (p->Nc > 4096 * 32 || group * ((p->Nq + 31) / 32) > 4096) return nullptr;
+  }
+  if (p->d == 64) return &kD64;
+  if (((long long)p->Nq + 1024) * k.lay.qs_r * 2 > 0x7fffffffLL || ((long long)p->Nc + 1024) * k.lay.ks_r * 2 > 0x7fffffffLL)
+    return nullptr;
+  return p->d <= 32 ? &kD32x : p->d <= 64 ? &kD64x : p->d <= 96 ? &kD96x : &kD128x;
 }
 // The forward and dQ kernels for d = 128 run one 256-row workgroup per CU, so a call takes
 // ceil(workgroups / 256) rounds on the chip's 256 CUs.  When the last round is at most half full
@@ -288,7 +308,7 @@ int burst_local_fwd(const void* Q, const void* K_chunk, const void* V_chunk,
   REQUIRE_PTR(Q); REQUIRE_PTR(K_chunk); REQUIRE_PTR(V_chunk);
   REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l);
   if ((st = check_arch()) != BURST_OK) return st;
-  if (use_d64(p, k)) return burst::d64::launch_fwd(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
+  if (const PlainFamily* f = plain_family(p, k)) return f->fwd(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
   if (use_plain128(p, k)) return burst::d128p::launch_fwd(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
   if (use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows))
     return burst::launch_fwd_mfma(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
@@ -450,20 +470,21 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   // The kernels of this call: D (when it is not given), then the dQ half, then the dK/dV half.
   const bool mfma_dq = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
   const bool mfma_dkv = use_mfma(p, k) && dkv_mfma_ok(p, k);
-  const bool d64 = use_d64(p, k), plain128 = use_plain128(p, k), plain128_dkv = use_plain128_dkv(p, k);
+  const PlainFamily* const plain = plain_family(p, k);
+  const bool plain128 = use_plain128(p, k), plain128_dkv = use_plain128_dkv(p, k);
   const bool adq = accumulate_dq != 0, adkv = accumulate_dkv != 0;
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq) {
-      e = d64 ? burst::d64::launch_bwd_dq(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
+      e = plain ? plain->bwd_dq(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
         : plain128 ? burst::d128p::launch_bwd_dq(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
         : mfma_dq ? burst::launch_bwd_dq_mfma(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
                   : burst::launch_bwd_dq_generic(k, p->dtype, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s);
       if (e != BURST_OK) return e;
     }
     if (want_dkv) {
-      e = d64 ? burst::d64::launch_bwd_dkv(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s)
+      e = plain ? plain->bwd_dkv(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s)
         : plain128_dkv ? burst::d128p::launch_bwd_dkv(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s)
         : mfma_dkv ? burst::launch_bwd_dkv_mfma(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s,
                                                 dkv_key_waves(p, k))

@@ -6,6 +6,8 @@
 //   burst_d64_mfma.hip    d = 64, namespace burst::d64, all three kernels
 //   burst_d128_plain.hip  d = 128, namespace burst::d128p, all three kernels, the dK/dV one with
 //                         two wavefronts (64 keys) per workgroup (BURST_SMALL_DKV_WAVES = 2)
+//   burst_d{32,64,96,128}_pad.hip   every other multiple of 8 below 128, padded to the next of these
+//                         widths (BURST_SMALL_PAD), namespaces burst::d32x .. d128x
 //
 // Same mathematics, operand orientations and register layouts as the hand-scheduled d = 128
 // kernels (S^T = K Q^T with one query row per lane for the forward and dQ side, S = Q K^T with one
@@ -29,8 +31,18 @@
 namespace burst {
 namespace BURST_SMALL_NS {
 
+// BURST_SMALL_PAD: the call's head dimension is any multiple of 8 up to BURST_SMALL_D (a.d).  Columns
+// past it are zero in registers and in LDS (the DMA asks for them outside the buffer, which writes
+// zeros and moves nothing) and are never stored.  Rows then lie in LDS with the pitch of the next
+// layout there is, 64 or 128 columns.
+#ifdef BURST_SMALL_PAD
+constexpr bool S_PAD = true;
+#else
+constexpr bool S_PAD = false;
+#endif
 constexpr int S_D = BURST_SMALL_D;
-constexpr int S_ROWB = S_D * 2;                   // bytes per row
+constexpr int S_ROWB = S_D <= 64 ? 128 : 256;     // bytes per row in LDS
+static_assert(S_PAD || S_ROWB == 2 * S_D, "a head dimension without an LDS layout of its own needs BURST_SMALL_PAD");
 constexpr int S_KS = S_D / 16;                    // k-steps of a contraction over d
 constexpr int S_DB = S_D / 32;                    // 32-wide blocks of d
 constexpr int S_RPL = 1024 / S_ROWB;              // tile rows per wave-wide DMA load
@@ -47,23 +59,26 @@ struct FwdArgsLite {
   const uint8_t* bmask; int bsize, bpitch;       // block flags (nullptr = none)
   long long bhstride;                            // bytes between heads' flag matrices (0 = shared)
   int blocks_per_head;
+  int d;                                         // head dimension (S_D unless S_PAD)
   Layout lay;                                    // strides of Q and of K, V
 };
 
-__device__ __forceinline__ int s_swz(int row) { return S_D == 64 ? ((row >> 1) & 7) : row_code(row); }
+__device__ __forceinline__ int s_swz(int row) { return S_ROWB == 128 ? ((row >> 1) & 7) : row_code(row); }
 __device__ __forceinline__ int s_off(int row, int granule) {
   return row * S_ROWB + ((granule ^ s_swz(row)) << 4);
 }
 // DMA of `rows8` groups of 8 tile rows: one wave-wide load moves 8 rows (1024 bytes); lane i
 // fills LDS slot i & 7 of row i >> 3 of the group and asks for the granule that belongs there.
-// (pitch: bytes between rows of the tensor in HBM)
-__device__ __forceinline__ int s_dma_off(int group, int lane, unsigned pitch) {
-  const int row = group * S_RPL + lane / S_GPR;
-  return (int)(row * pitch + (((lane % S_GPR) ^ s_swz(row)) << 4));
+// (pitch: bytes between rows of the tensor in HBM; granules past the head dimension are asked for
+// 2 GiB further on, which no buffer of a padded call reaches: launchers check its span)
+__device__ __forceinline__ int s_dma_off(int group, int lane, unsigned pitch, int d) {
+  const int row = group * S_RPL + lane / S_GPR, granule = (lane % S_GPR) ^ s_swz(row);
+  if (S_PAD && granule * 8 >= d) return (int)0x80000000u;
+  return (int)(row * pitch + (granule << 4));
 }
 // bytes a buffer descriptor must cover for `rows` rows `pitch` bytes apart
-__device__ __forceinline__ unsigned s_span(int rows, unsigned pitch) {
-  return rows > 0 ? (unsigned)(rows - 1) * pitch + (unsigned)S_ROWB : 0u;
+__device__ __forceinline__ unsigned s_span(int rows, unsigned pitch, int d) {
+  return rows > 0 ? (unsigned)(rows - 1) * pitch + (unsigned)(2 * d) : 0u;
 }
 // addresses of the transposing reads of a 16-row group (see the d = 128 forward kernel): the
 // 16-lane group (h, dh) reads rows 8*sx + 4*h + (0..3), columns db*32 + dh*16 + (0..15)
@@ -127,6 +142,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SF_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
+  const int d = S_PAD ? a.d : S_D;
   int head, qb;
   s_head_block(blockIdx.x, a.blocks_per_head, head, qb);
   if (head >= a.H) return;
@@ -180,7 +196,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 
   bf16x8 qf[S_KS];
 #pragma unroll
-  for (int ks = 0; ks < S_KS; ks++) qf[ks] = s_load8(Qh + (size_t)(q0 + lr) * a.lay.qs_r + ks * 16 + h * 8, q0 + lr < a.Nq);
+  for (int ks = 0; ks < S_KS; ks++) qf[ks] = s_load8(Qh + (size_t)(q0 + lr) * a.lay.qs_r + ks * 16 + h * 8, q0 + lr < a.Nq && (!S_PAD || ks * 16 + h * 8 < d));
   f32x16 o[S_DB];
 #pragma unroll
   for (int db = 0; db < S_DB; db++)
@@ -192,14 +208,14 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 #pragma unroll
   for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
   s_taddr(lane, taddr);
-  const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch));
-  const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch));
+  const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch, d));
+  const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch, d));
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const unsigned lds0 = lds_addr(smem);
   constexpr int NL = SF_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
   int goff[NL];
 #pragma unroll
-  for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch);
+  for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
   auto dma_tile = [&](int t, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int il = 0; il < NL; il++) {
@@ -302,11 +318,12 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     const float m_old2 = a.m[srow] * kLog2e, l_old = a.l[srow];
     const float m_new = fmaxf(m_old2, m2);
     const float fa = fast_exp2(m_old2 - m_new), fb = fast_exp2(m2 - m_new);
-    float* orow = a.O_acc + srow * S_D;
+    float* orow = a.O_acc + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
         float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
         f32x4 old = *reinterpret_cast<f32x4*>(ptr), nw;
 #pragma unroll
@@ -331,6 +348,7 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SQ_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
+  const int d = S_PAD ? a.d : S_D;
   int head, qb;
   s_head_block(blockIdx.x, a.blocks_per_head, head, qb);
   if (head >= a.H) return;
@@ -394,8 +412,9 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) {
       const size_t qrow = a.lay.q_base(head) + (size_t)(ok ? row : 0) * a.lay.qs_r;
-      qf[ks] = s_load8(a.Q + qrow + ks * 16 + h * 8, ok);
-      gf[ks] = s_load8(a.dO + qrow + ks * 16 + h * 8, ok);
+      const bool there = ok && (!S_PAD || ks * 16 + h * 8 < d);
+      qf[ks] = s_load8(a.Q + qrow + ks * 16 + h * 8, there);
+      gf[ks] = s_load8(a.dO + qrow + ks * 16 + h * 8, there);
     }
     const float lv = ok ? a.lse[srow] : BURST_NEG_INF;
     const float nlse2 = (lv == BURST_NEG_INF) ? BURST_NEG_INF : -lv * kLog2e;   // -inf: P = 0
@@ -404,14 +423,14 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
     s_taddr(lane, taddr);
-    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch));
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch));
+    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch, d));
+    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch, d));
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const unsigned lds0 = lds_addr(smem);
     constexpr int NL = SQ_BC / S_RPL / 4;         // wave-wide loads per wavefront and tile
     int goff[NL];
 #pragma unroll
-    for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch);
+    for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
     auto dma_tile = [&](int t, int buf) __attribute__((always_inline)) {
 #pragma unroll
       for (int il = 0; il < NL; il++) {
@@ -477,11 +496,12 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   if (ok) {
-    float* orow = a.dQ + srow * S_D;
+    float* orow = a.dQ + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
         float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
         if (a.acc_dq) v = *reinterpret_cast<f32x4*>(ptr);
@@ -513,6 +533,7 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SK_TILE + 2 * 64 * 4];   // Q[2], dO[2], statistics[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
+  const int d = S_PAD ? a.d : S_D;
   int kvhead, kblk;
   s_head_block(blockIdx.x, a.blocks_per_head, kvhead, kblk);
   if (kvhead >= a.H) return;                       // a.H counts key/value heads here
@@ -575,8 +596,9 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
     bf16x8 kf[S_KS], vf[S_KS];
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) {
-      kf[ks] = s_load8(Kh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, key0 + lr < a.Nc);
-      vf[ks] = s_load8(Vh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, key0 + lr < a.Nc);
+      const bool there = key0 + lr < a.Nc && (!S_PAD || ks * 16 + h * 8 < d);
+      kf[ks] = s_load8(Kh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, there);
+      vf[ks] = s_load8(Vh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, there);
     }
     int qaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
@@ -588,7 +610,7 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
     static_assert(NL >= 1 && NL * SK_WAVES * S_RPL == SK_BR, "a tile's rows must divide evenly among the wavefronts");
     int goff[NL];
 #pragma unroll
-    for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, qpitch);
+    for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, qpitch, d);
     float* const stat = reinterpret_cast<float*>(smem + SK_STAT);
     // walk position n -> (query head, tile); every wavefront DMAs its 8 rows of Q and dO.  The
     // first wavefront also fetches the 32 rows' statistics with plain loads issued BEFORE the
@@ -605,8 +627,8 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
         else stat_x = r < a.Nq ? a.D[hrow + r] : 0.f;
       }
       const size_t hbase = a.lay.q_base(kvhead * a.group + g);
-      const __amdgpu_buffer_rsrc_t qrs = make_rsrc(a.Q + hbase, s_span(a.Nq, qpitch));
-      const __amdgpu_buffer_rsrc_t grs = make_rsrc(a.dO + hbase, s_span(a.Nq, qpitch));
+      const __amdgpu_buffer_rsrc_t qrs = make_rsrc(a.Q + hbase, s_span(a.Nq, qpitch, d));
+      const __amdgpu_buffer_rsrc_t grs = make_rsrc(a.dO + hbase, s_span(a.Nq, qpitch, d));
 #pragma unroll
       for (int il = 0; il < NL; il++) {
         dma_b128_to_lds(qrs, lds0 + buf * SK_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SK_BR * qpitch) + goff[il]);
@@ -659,9 +681,9 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
         if (need_mask) {
           // visible iff key position <= row position (constant part >= lim) and row position <
           // key position + window (constant part <= lim2)
-          const long long d = kpos - (tile_first_q + 4 * h);
-          const int lim = a.causal ? (int)(d < -1 ? -1 : (d > 64 ? 64 : d)) : -1;
-          const long long d2 = d + a.window - 1;
+          const long long dd = kpos - (tile_first_q + 4 * h);
+          const int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : -1;
+          const long long d2 = dd + a.window - 1;
           const int lim2 = a.window > 0 ? (int)(d2 < -1 ? -1 : (d2 > 64 ? 64 : d2)) : 64;
 #pragma unroll
           for (int r = 0; r < 16; r++) {
@@ -719,15 +741,16 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   // lane = d column, registers = keys
-  float* dKh = a.dK + (size_t)kvhead * a.Nc * S_D;
-  float* dVh = a.dV + (size_t)kvhead * a.Nc * S_D;
+  float* dKh = a.dK + (size_t)kvhead * a.Nc * d;
+  float* dVh = a.dV + (size_t)kvhead * a.Nc * d;
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
     if (key < a.Nc) {
 #pragma unroll
       for (int db = 0; db < S_DB; db++) {
-        const size_t off = (size_t)key * S_D + db * 32 + lr;
+        if (S_PAD && db * 32 + lr >= d) continue;
+        const size_t off = (size_t)key * d + db * 32 + lr;
         float k_old = 0.f, v_old = 0.f;
         if (a.acc_dkv) { k_old = dKh[off]; v_old = dVh[off]; }
         dKh[off] = k_old + a.scale * dk[db][r];
@@ -760,6 +783,7 @@ int launch_fwd(const KParams& p, const void* Q, const void* K, const void* V,
   a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
   a.bmask = p.bmask; a.bsize = p.bsize; a.bpitch = p.bpitch; a.bhstride = p.bhstride;
   a.lay = p.lay;
+  a.d = p.d;
   a.blocks_per_head = (p.Nq + SF_BR - 1) / SF_BR;
   const long long nb = (long long)((a.H + 7) / 8 * 8) * a.blocks_per_head;
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
