@@ -51,8 +51,8 @@ struct DkvShape {
 
 // SPARSE: the call carries block flags (paper Sec. 2.6) or several query heads share a key/value
 // head (a.group > 1: the tiles of all heads of the group are walked, `head` is then the key/value
-// head and Q, dO, lse, D of the group are addressed as one tensor of group * Nq rows, which needs
-// Nq to be a multiple of the tile).  The workgroup first writes the list of
+// head; an entry also names the head of its tile, whose rows have buffer descriptors of their own,
+// so that the rows past Nq of its last tile read as zeros).  The workgroup first writes the list of
 // query tiles that at least one of its wavefronts' keys are visible to (tile index plus one bit per
 // wavefront) into LDS and then walks that list instead of t_begin, t_begin + 1, ...; a wavefront
 // whose bit is clear hides the whole tile in the masking path.  Entries past the end name a tile
@@ -126,9 +126,8 @@ burst_bwd_dkv_kernel(BwdArgs a) {
   // SPARSE: the list of visible tiles, built by wavefront 0 (64 candidate tiles per round).
   // list[0] = number of entries, list[1 + j] = tile | (wavefront bits << 16), then 4 end entries.
   int* const list = reinterpret_cast<int*>(smem + DKV_LDS_BYTES);
-  const int tiles_per_head = (a.Nq + DKV_BR - 1) / DKV_BR;
   if constexpr (SPARSE) {
-    const int end_tile = (q_rows + DKV_BR - 1) / DKV_BR;        // a tile past the group's rows
+    const int end_tile = (a.Nq + DKV_BR - 1) / DKV_BR;          // a tile past the rows of the group's first head
     if (w == 0) {
       int n = 0;
       for (int g = 0; g < group; g++)
@@ -150,7 +149,7 @@ burst_bwd_dkv_kernel(BwdArgs a) {
           const unsigned long long bal = __builtin_amdgcn_ballot_w64(bits != 0);
           if (bits != 0) {
             const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-            list[1 + pos] = (g * tiles_per_head + t) | (bits << 16) | (g << 20);
+            list[1 + pos] = t | (bits << 16) | (g << 20);
           }
           n += __builtin_popcountll(bal);
         }
@@ -160,7 +159,7 @@ burst_bwd_dkv_kernel(BwdArgs a) {
     __syncthreads();
     nwalk = __builtin_amdgcn_readfirstlane(list[0]);
   }
-  // walk position j -> its entry: the tile index in the low 16 bits and, SPARSE, the wavefront
+  // walk position j -> its entry: the tile of its head in the low 16 bits and, SPARSE, the wavefront
   // bits (16..19) and the head of the group (20..27)
   auto entry_at = [&](int j) __attribute__((always_inline)) {
     if constexpr (SPARSE) return __builtin_amdgcn_readfirstlane(list[1 + j]);
@@ -186,13 +185,11 @@ burst_bwd_dkv_kernel(BwdArgs a) {
           taddr[db][sx] = tile_off(8 * sx + 4 * h + (j16 >> 2), db * 4 + 2 * dh + ((j16 & 3) >> 1)) + (j16 & 1) * 8;
     }
     // DMA: a 64-row tile is 16 wave-loads of 4 rows; wavefront w issues loads LPW*w .. LPW*w + LPW-1
-    // (the rows of the group's heads lie (head stride) apart: a tile of head g of the group starts
-    // g * gfix bytes away from where it would in one tensor of group * Nq rows)
-    const unsigned hbytes = (unsigned)a.lay.qs_h * 2u;
-    const unsigned gfix = hbytes - (unsigned)tiles_per_head * qtile;
-    const unsigned qbytes = a.Nq > 0 ? (unsigned)(group - 1) * hbytes + (unsigned)(a.Nq - 1) * qpitch + 256u : 0u;
-    const __amdgpu_buffer_rsrc_t qrs = make_rsrc(Qh, qbytes);
-    const __amdgpu_buffer_rsrc_t grs = make_rsrc(Gh, qbytes);
+    const unsigned qbytes = a.Nq > 0 ? (unsigned)(a.Nq - 1) * qpitch + 256u : 0u;
+    // (a descriptor per head of the group; without a list there is one head)
+    auto head_of = [&](int e) __attribute__((always_inline)) { return SPARSE ? (e >> 20) & 0xff : 0; };
+    auto q_rsrc = [&](int e) __attribute__((always_inline)) { return make_rsrc(Qh + (size_t)head_of(e) * a.lay.qs_h, qbytes); };
+    auto g_rsrc = [&](int e) __attribute__((always_inline)) { return make_rsrc(Gh + (size_t)head_of(e) * a.lay.qs_h, qbytes); };
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const unsigned lds0 = lds_addr(smem);
     int goff[LPW];
@@ -203,9 +200,7 @@ burst_bwd_dkv_kernel(BwdArgs a) {
     }
     // `e`: an entry (see entry_at)
     auto dma_tile = [&](__amdgpu_buffer_rsrc_t rs, unsigned lds_tile, int il, int e) __attribute__((always_inline)) {
-      unsigned tile = (unsigned)tile_of(e) * qtile;
-      if constexpr (SPARSE) tile += (unsigned)((e >> 20) & 0xff) * gfix;
-      dma_b128_to_lds(rs, lds_tile + (unsigned)(wu * LPW + il) * 1024u, (int)tile + goff[il]);
+      dma_b128_to_lds(rs, lds_tile + (unsigned)(wu * LPW + il) * 1024u, (int)((unsigned)tile_of(e) * qtile) + goff[il]);
     };
     // Per-row statistics of a tile travel like the tiles: wavefront 0 DMAs the 64 lse values,
     // wavefront 1 the 64 D values (rows past Nq read as 0; their Q and dO rows are 0 too, so they
@@ -216,14 +211,13 @@ burst_bwd_dkv_kernel(BwdArgs a) {
     // per-element vector work.  (Multiplying K by c beforehand would also remove the multiply,
     // but rounds c K to bf16 again; with few visible keys per row P is then visibly off.)  No
     // compiler-visible global load is left in the loop: its wait would drain the DMA queue.
-    const __amdgpu_buffer_rsrc_t lrs = make_rsrc(lseh, (unsigned)q_rows * 4u);
-    const __amdgpu_buffer_rsrc_t drs = make_rsrc(Dh, (unsigned)q_rows * 4u);
-    auto dma_rowstat = [&](int t, int slot) __attribute__((always_inline)) {
+    auto dma_rowstat = [&](int e, int slot) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t srs = make_rsrc((wu == 1 ? Dh : lseh) + (size_t)head_of(e) * a.Nq, (unsigned)a.Nq * 4u);
       // every wavefront issues exactly one such load per tile (the wait counts below rely on
       // it): 0 -> lse, 1 -> D, 2 and 3 -> a dummy copy of lse that nobody reads
       const unsigned dst = (wu == 0) ? lds0 + DKV_LDS_L + slot * DKV_BR * 4
                          : (wu == 1) ? lds0 + DKV_LDS_D + slot * DKV_BR * 4 : lds0 + DKV_LDS_DUMMY;
-      dma_b32_to_lds(wu == 1 ? drs : lrs, dst, (t * DKV_BR + lane) * 4);
+      dma_b32_to_lds(srs, dst, (tile_of(e) * DKV_BR + lane) * 4);
     };
     const float inv_scale = 1.0f / a.scale;
     // The same in two parts for the main loop, so that the LDS round trip hides behind MFMAs:
@@ -259,12 +253,12 @@ burst_bwd_dkv_kernel(BwdArgs a) {
       const int src = entry_at(t);
 #pragma unroll
       for (int il = 0; il < LPW; il++) {
-        dma_tile(qrs, lds0 + DKV_LDS_Q + t * DKV_TILE_BYTES, il, src);
-        dma_tile(grs, lds0 + DKV_LDS_G + t * DKV_TILE_BYTES, il, src);
+        dma_tile(q_rsrc(src), lds0 + DKV_LDS_Q + t * DKV_TILE_BYTES, il, src);
+        dma_tile(g_rsrc(src), lds0 + DKV_LDS_G + t * DKV_TILE_BYTES, il, src);
       }
     }
 #pragma unroll
-    for (int t = 0; t < 3; t++) dma_rowstat(tile_of(entry_at(t)), t);
+    for (int t = 0; t < 3; t++) dma_rowstat(entry_at(t), t);
     __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     scale_rowstat(0);
@@ -297,17 +291,17 @@ burst_bwd_dkv_kernel(BwdArgs a) {
 
     int slot = 0;
     for (int n = 0; n < nwalk; n++) {                  // n = walk position; statistic slot n & 3 holds its tile
-      // this tile, the entry of the tile whose rows are fetched now, the tile whose statistics are
-      int t = t_begin + n, t2 = t + DKV_SLOTS - 1, t3 = t + 3, t_in_head = t;
+      // this tile, the entries of the tile whose rows are fetched now and of the one whose statistics are
+      int t = t_begin + n, t2 = t + DKV_SLOTS - 1, t3 = t + 3;
       bool mine = true;                                // SPARSE: this wavefront's keys are visible to the tile
       if constexpr (SPARSE) {
         const int e = __builtin_amdgcn_readfirstlane(list[1 + n]);
         t = e & 0xffff;
-        t_in_head = t - ((e >> 20) & 0xff) * tiles_per_head;
         mine = ((e >> (16 + wu)) & 1) != 0;
         t2 = entry_at(n + DKV_SLOTS - 1);
-        t3 = tile_of(entry_at(n + 3));
+        t3 = entry_at(n + 3);
       }
+      const __amdgpu_buffer_rsrc_t qrs = q_rsrc(t2), grs = g_rsrc(t2);
       const int slot1 = (slot == DKV_SLOTS - 1) ? 0 : slot + 1;
       // where the tile fetched in this step goes: the slot after the next tile's, or (two slots) the next tile's
       const int slot2 = DKV_SLOTS == 2 ? slot1 : (slot1 == DKV_SLOTS - 1) ? 0 : slot1 + 1;
@@ -317,8 +311,7 @@ burst_bwd_dkv_kernel(BwdArgs a) {
       const float* dp_ = reinterpret_cast<const float*>(smem + DKV_LDS_D) + (n & 3) * DKV_BR;
       const float* lp_next = reinterpret_cast<const float*>(smem + DKV_LDS_L) + ((n + 1) & 3) * DKV_BR;
       const float* dp_next = reinterpret_cast<const float*>(smem + DKV_LDS_D) + ((n + 1) & 3) * DKV_BR;
-      // (t counts tiles over all heads of the group; the position restarts with every head)
-      const long long tile_first_q = a.q_off + (long long)t_in_head * DKV_BR;
+      const long long tile_first_q = a.q_off + (long long)t * DKV_BR;
       // (no branch around the MFMA phases: the AGPR-pinned accumulators must not become phi
       // values, the allocator would shuttle them through VGPRs every iteration)
       const bool need_mask = (a.causal && wave_last_k > tile_first_q) ||
@@ -499,7 +492,6 @@ int launch_bwd_dkv_mfma(const KParams& p, const void* Q, const void* K, const vo
   if (listed) {
     const int max_list = key_waves == 4 ? DkvShape<4>::MAX_LIST : DkvShape<2>::MAX_LIST;
     if ((long long)a.group * ((p.Nq + DKV_BR - 1) / DKV_BR) > max_list) return BURST_ERR_SHAPE;
-    if (a.group > 1 && p.Nq % DKV_BR != 0) return BURST_ERR_SHAPE;
     if (key_waves == 4)
       BURST_LAUNCH((burst_bwd_dkv_kernel<true, 4>), dim3((unsigned)nb), dim3(256),
                    DkvShape<4>::LDS_BYTES + DkvShape<4>::LIST_BYTES, stream, a);
