@@ -198,6 +198,38 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
                         float* dK_chunk, float* dV_chunk, int accumulate_dkv,
                         const burst_params* p, void* stream);
 
+/* A whole walk in one call, for chunks that are already resident (or have arrived together): the
+ * kernels go from one chunk to the next with the state in registers and the next tile in flight,
+ * instead of storing and reloading it between launches. */
+typedef struct burst_chunk {
+  const void* K; const void* V;      /* [B, kv_heads, Nc, d] of `dtype` */
+  float* dK; float* dV;              /* burst_walk_bwd: the same shapes, fp32; ignored by burst_walk_fwd */
+  const uint8_t* block_mask;         /* as in burst_params, for this chunk (edge: burst_params.block) */
+  int64_t block_mask_stride;
+  int64_t k_off;                     /* global position of row 0 */
+  int64_t kv_strides[3];             /* as in burst_params; all zero = contiguous */
+  int32_t Nc;                        /* rows, >= 0 */
+  int32_t reserved;                  /* 0 */
+} burst_chunk;
+/* burst_state_init, burst_local_fwd for each of the n_chunks chunks in order, burst_finalize: the same
+ * O, lse and final state.  `p` gives everything but Nc, k_off, block_mask, block_mask_stride and
+ * kv_strides, which are taken from the chunks.  workspace: device memory of at least
+ * burst_walk_workspace_bytes(...) bytes, 16-byte aligned, contents undefined before and after, or NULL;
+ * with it a slice of few rows is spread over the chip by splitting the keys into ranges whose partial
+ * states are merged at the end (the sums then come in another order). */
+int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
+                   void* O_out, float* lse, void* workspace, size_t workspace_bytes,
+                   const burst_params* p, void* stream);
+/* burst_bwd_prepare (when O is given; D is then written, else read), then burst_local_bwd for each
+ * chunk in order, with the dK and dV of the chunk.  accumulate_dq = 0: dQ is overwritten with the
+ * contribution of all chunks; accumulate_dkv applies to every chunk's dK and dV. */
+int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
+                   const float* lse, float* D, float* dQ, int accumulate_dq, int accumulate_dkv,
+                   void* workspace, size_t workspace_bytes, const burst_params* p, void* stream);
+/* Bytes of workspace either of the two can use for these arguments (0: none); an upper bound that
+ * depends on the shapes only.  Host logic, no device call. */
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p);
+
 /* Alg. 1, body of the loop for one chunk exactly as printed, WITHOUT the tiling of
  * Sec. 2.4 (the "w/o LAO" variant of the paper's ablation, Tables 2-3): the whole
  * S_ij = scale Q K_chunk^T and P_ij = exp(S_ij - m_ij) of the block pair are stored in

@@ -21,6 +21,7 @@ EXPORTS = [
     "burst_materialized_workspace_bytes", "burst_local_fwd_materialized", "burst_workspace_bytes",
     "burst_materialized_bwd_workspace_bytes", "burst_local_bwd_materialized", "burst_set_kernel_family",
     "burst_kernel_family_for", "burst_local_bwd_static", "burst_probe_mfma", "burst_probe_atomic_dq",
+    "burst_walk_fwd", "burst_walk_bwd", "burst_walk_workspace_bytes",
 ]
 
 
@@ -32,6 +33,14 @@ class BurstParams(ctypes.Structure):
         ("window", ctypes.c_int64), ("block_mask", ctypes.c_void_p), ("block", ctypes.c_int32),
         ("kv_heads", ctypes.c_int32), ("block_mask_stride", ctypes.c_int64),
         ("q_strides", ctypes.c_int64 * 3), ("kv_strides", ctypes.c_int64 * 3),
+    ]
+
+
+class BurstChunk(ctypes.Structure):
+    _fields_ = [
+        ("K", ctypes.c_void_p), ("V", ctypes.c_void_p), ("dK", ctypes.c_void_p), ("dV", ctypes.c_void_p),
+        ("block_mask", ctypes.c_void_p), ("block_mask_stride", ctypes.c_int64), ("k_off", ctypes.c_int64),
+        ("kv_strides", ctypes.c_int64 * 3), ("Nc", ctypes.c_int32), ("reserved", ctypes.c_int32),
     ]
 
 
@@ -78,6 +87,13 @@ def load():
     for name in ("burst_local_bwd_dq", "burst_local_bwd_dkv", "burst_state_init", "burst_local_fwd", "burst_finalize", "burst_merge_state",
                  "burst_bwd_prepare", "burst_local_bwd", "burst_event_record", "burst_version"):
         getattr(lib, name).restype = ctypes.c_int
+    cp, sz, ci = ctypes.POINTER(BurstChunk), ctypes.c_size_t, ctypes.c_int
+    lib.burst_walk_workspace_bytes.argtypes = [cp, ci, pp]
+    lib.burst_walk_workspace_bytes.restype = sz
+    lib.burst_walk_fwd.argtypes = [vp, cp, ci, fp, fp, fp, vp, fp, vp, sz, pp, vp]
+    lib.burst_walk_fwd.restype = ctypes.c_int
+    lib.burst_walk_bwd.argtypes = [vp, cp, ci, vp, vp, fp, fp, fp, ci, ci, vp, sz, pp, vp]
+    lib.burst_walk_bwd.restype = ctypes.c_int
     lib.burst_event_create.argtypes = []
     lib.burst_event_create.restype = vp
     lib.burst_event_record.argtypes = [vp, vp]
@@ -110,6 +126,20 @@ def strides_of(t):
     return tuple(int(t.stride(i)) if t.shape[i] > 1 else int(t.shape[3]) for i in range(3))
 
 
+def _mask(block_mask, block, B, H, Nq, Nc):
+    """(address, bytes between heads' matrices) of a chunk's block flags."""
+    if block_mask.dtype != torch.uint8 or not block_mask.is_cuda or not block_mask.is_contiguous():
+        raise ValueError("block_mask: contiguous uint8 device tensor expected")
+    if block <= 0:
+        raise ValueError("block_mask needs block > 0")
+    one = (-(-Nq // block), -(-Nc // block))
+    if tuple(block_mask.shape) == (B, H) + one:
+        return block_mask.data_ptr(), one[0] * one[1]
+    if tuple(block_mask.shape) != one:
+        raise ValueError("block_mask: shape must be [ceil(Nq/block), ceil(Nc/block)], alone or after [B, H]")
+    return block_mask.data_ptr(), 0
+
+
 def params(B, H, Nq, Nc, d, dtype, scale, causal=False, q_off=0, k_off=0, window=0, block_mask=None, block=0,
            kv_heads=0, q_strides=None, kv_strides=None):
     """block_mask: a contiguous uint8 device tensor [ceil(Nq/block), ceil(Nc/block)] shared by all
@@ -118,18 +148,7 @@ def params(B, H, Nq, Nc, d, dtype, scale, causal=False, q_off=0, k_off=0, window
     have run.  q_strides / kv_strides: (batch, head, row) element strides of Q, dO, O and of
     K, V (see strides_of); None = contiguous."""
     code = {torch.bfloat16: BURST_BF16, torch.float32: BURST_F32, "bf16": BURST_BF16, "f32": BURST_F32}.get(dtype, dtype)
-    ptr, stride = None, 0
-    if block_mask is not None:
-        if block_mask.dtype != torch.uint8 or not block_mask.is_cuda or not block_mask.is_contiguous():
-            raise ValueError("block_mask: contiguous uint8 device tensor expected")
-        if block <= 0:
-            raise ValueError("block_mask needs block > 0")
-        one = (-(-Nq // block), -(-Nc // block))
-        if tuple(block_mask.shape) == (B, H) + one:
-            stride = one[0] * one[1]
-        elif tuple(block_mask.shape) != one:
-            raise ValueError("block_mask: shape must be [ceil(Nq/block), ceil(Nc/block)], alone or after [B, H]")
-        ptr = block_mask.data_ptr()
+    ptr, stride = (None, 0) if block_mask is None else _mask(block_mask, block, B, H, Nq, Nc)
     return BurstParams(B, H, Nq, Nc, d, code, 1 if causal else 0, scale, q_off, k_off, window, ptr,
                        block if block_mask is not None else 0, kv_heads, stride,
                        (ctypes.c_int64 * 3)(*(q_strides or (0, 0, 0))), (ctypes.c_int64 * 3)(*(kv_strides or (0, 0, 0))))
@@ -307,6 +326,47 @@ def burst_local_bwd_dkv(Q, K_chunk, V_chunk, dO, lse, D, dK_chunk, dV_chunk, p, 
     _check(load().burst_local_bwd_dkv(_q(Q, p), _kv(K_chunk, p), _kv(V_chunk, p), _q(dO, p), _f32(lse), _f32(D),
                                       _f32(dK_chunk), _f32(dV_chunk), 1 if accumulate_dkv else 0,
                                       ctypes.byref(p), _stream()), "burst_local_bwd_dkv")
+
+
+def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None):
+    """The chunks of a walk as the C array burst_walk_fwd / burst_walk_bwd take.  `p`: the walk's parameter
+    block (its `block` is the edge of the masks' blocks)."""
+    arr = (BurstChunk * len(Ks))()
+    for j, (K, V) in enumerate(zip(Ks, Vs)):
+        c = arr[j]
+        if not K.is_cuda or not V.is_cuda:
+            raise ValueError("device tensor expected")
+        if not (K.is_contiguous() and V.is_contiguous()):
+            s = strides_of(K) or (0, 0, 0)
+            _strided(V, s)
+            c.kv_strides[:] = s
+        c.K, c.V, c.k_off, c.Nc = K.data_ptr(), V.data_ptr(), k_offs[j], K.shape[2]
+        if masks is not None and masks[j] is not None:
+            c.block_mask, c.block_mask_stride = _mask(masks[j], p.block, p.B, p.H, p.Nq, c.Nc)
+        if dKs is not None:
+            c.dK, c.dV = _f32(dKs[j]).value, _f32(dVs[j]).value
+    return arr
+
+
+def burst_walk_workspace_bytes(chunks, p):
+    return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p)))
+
+
+def _bytes(ws):
+    return ctypes.c_size_t(0 if ws is None else ws.numel() * ws.element_size())
+
+
+def burst_walk_fwd(Q, chunks, O_acc, m, l, O_out, lse, p, workspace=None):
+    """chunks: see chunk_array.  workspace: None or a contiguous device tensor."""
+    _check(load().burst_walk_fwd(_q(Q, p), chunks, len(chunks), _f32(O_acc), _f32(m), _f32(l), _q(O_out, p), _f32(lse),
+                                 _ptr(workspace), _bytes(workspace), ctypes.byref(p), _stream()), "burst_walk_fwd")
+
+
+def burst_walk_bwd(Q, chunks, O, dO, lse, D, dQ, p, accumulate_dq=True, accumulate_dkv=False, workspace=None):
+    """O given: D = rowsum(dO o O) is computed first and written; O = None: D is read."""
+    _check(load().burst_walk_bwd(_q(Q, p), chunks, len(chunks), _q(O, p), _q(dO, p), _f32(lse), _f32(D), _f32(dQ),
+                                 1 if accumulate_dq else 0, 1 if accumulate_dkv else 0,
+                                 _ptr(workspace), _bytes(workspace), ctypes.byref(p), _stream()), "burst_walk_bwd")
 
 
 class Event:

@@ -24,14 +24,14 @@ int launch_bwd_dq_generic(const KParams&, int, const void*, const void*, const v
 int launch_bwd_dkv_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
                            const float*, float*, float*, int, hipStream_t);
 // the plainly written kernels of burst_plain_mfma.h, one namespace per build
-#define BURST_DECLARE_PLAIN(ns)                                                                                        \
-  namespace ns {                                                                                                       \
-  int launch_fwd(const KParams&, const void*, const void*, const void*, float*, float*, float*, hipStream_t);          \
-  int launch_bwd_dq(const KParams&, const void*, const void*, const void*, const void*, const float*, const float*,    \
-                    float*, int, hipStream_t);                                                                         \
-  int launch_bwd_dkv(const KParams&, const void*, const void*, const void*, const void*, const float*, const float*,   \
-                     float*, float*, int, hipStream_t);                                                                \
+#define BURST_DECLARE_PLAIN(ns)                                                            \
+  namespace ns {                                                                           \
+  int launch_fwd(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);            \
+  int launch_bwd_dq(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);         \
+  int launch_bwd_dkv(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);        \
   }
+int launch_merge_splits(const KParams&, const FwdIo&, hipStream_t);
+int launch_sum_splits(const KParams&, const BwdIo&, hipStream_t);
 BURST_DECLARE_PLAIN(d64)
 BURST_DECLARE_PLAIN(d128p)
 BURST_DECLARE_PLAIN(d32x)
@@ -54,6 +54,9 @@ thread_local bool t_validate_only = false;
 namespace {
 
 using burst::KParams;
+using burst::Chunk;
+using burst::FwdIo;
+using burst::BwdIo;
 
 constexpr int kMaxDevices = 64;
 int g_arch_ok[kMaxDevices];                 // 0 = unknown, 1 = gfx950, -1 = other
@@ -190,7 +193,7 @@ struct PlainFamily {
   decltype(&burst::d64::launch_bwd_dkv) bwd_dkv;
 };
 #define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv}
-const PlainFamily kD64 = BURST_PLAIN(d64), kD32x = BURST_PLAIN(d32x), kD64x = BURST_PLAIN(d64x), kD96x = BURST_PLAIN(d96x),
+const PlainFamily kD64 = BURST_PLAIN(d64), kD128p = BURST_PLAIN(d128p), kD32x = BURST_PLAIN(d32x), kD64x = BURST_PLAIN(d64x), kD96x = BURST_PLAIN(d96x),
                   kD128x = BURST_PLAIN(d128x);
 #undef BURST_PLAIN
 const PlainFamily* plain_family(const burst_params* p, const KParams& k) {
@@ -264,6 +267,84 @@ bool use_plain128_dkv(const burst_params* p, const KParams& k) {
   return g_kernel_family.load(std::memory_order_relaxed) == 2;
 }
 
+// The kernels that serve one chunk's forward, dQ or dK/dV: one of the plainly written families
+// (which take several chunks in one launch), the hand-scheduled d = 128 kernels, or the generic ones.
+struct Kernels {
+  const PlainFamily* plain;
+  bool hand;
+  int key_waves;                                   // hand-scheduled dK/dV
+  bool fused() const { return plain != nullptr; }
+  bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves; }
+};
+Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the same choice
+  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0};
+  if (use_plain128(p, k)) return {&kD128p, false, 0};
+  return {nullptr, use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows), 0};
+}
+Kernels dkv_kernels(const burst_params* p, const KParams& k) {
+  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0};
+  if (use_plain128_dkv(p, k)) return {&kD128p, false, 0};
+  const bool hand = use_mfma(p, k) && dkv_mfma_ok(p, k);
+  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0};
+}
+int fwd_launch(const Kernels& f, const KParams& k, int dtype, const FwdIo& io, const Chunk* c, int n, hipStream_t s) {
+  if (f.plain != nullptr) return f.plain->fwd(k, io, c, n, s);
+  if (f.hand) return burst::launch_fwd_mfma(k, io.Q, c->K, c->V, io.O_acc, io.m, io.l, s);
+  return burst::launch_fwd_generic(k, dtype, io.Q, c->K, c->V, io.O_acc, io.m, io.l, s);
+}
+int dq_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
+  if (f.plain != nullptr) return f.plain->bwd_dq(k, io, c, n, s);
+  if (f.hand) return burst::launch_bwd_dq_mfma(k, io.Q, c->K, c->V, io.dO, io.lse, io.D, io.dQ, io.acc_dq, s);
+  return burst::launch_bwd_dq_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, io.dQ, io.acc_dq, s);
+}
+int dkv_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
+  if (f.plain != nullptr) return f.plain->bwd_dkv(k, io, c, n, s);
+  float* const dK = (float*)c->dK; float* const dV = (float*)c->dV;
+  if (f.hand) return burst::launch_bwd_dkv_mfma(k, io.Q, c->K, c->V, io.dO, io.lse, io.D, dK, dV, io.acc_dkv, s, f.key_waves);
+  return burst::launch_bwd_dkv_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, dK, dV, io.acc_dkv, s);
+}
+
+// A walk over several chunks: the chunks (without the empty ones), each with its own parameter block.
+struct WalkChunk { burst_params p; KParams k; Chunk c; };
+int walk_chunks(const burst_chunk* chunks, int n, const burst_params* p, bool backward, std::vector<WalkChunk>& out) {
+  if (n < 0) return BURST_ERR_SHAPE;
+  if (n > 0 && chunks == nullptr) return BURST_ERR_NULL;
+  if (p == nullptr) return BURST_ERR_NULL;
+  out.reserve((size_t)n);
+  for (int i = 0; i < n; i++) {
+    const burst_chunk& in = chunks[i];
+    WalkChunk w;
+    w.p = *p;
+    w.p.Nc = in.Nc; w.p.k_off = in.k_off; w.p.block_mask = in.block_mask; w.p.block_mask_stride = in.block_mask_stride;
+    std::memcpy(w.p.kv_strides, in.kv_strides, sizeof w.p.kv_strides);
+    const int st = check_params(&w.p, &w.k);
+    if (st != BURST_OK) return st;
+    if (in.Nc == 0) continue;
+    REQUIRE_PTR(in.K); REQUIRE_PTR(in.V);
+    if (backward) { REQUIRE_PTR(in.dK); REQUIRE_PTR(in.dV); }
+    w.c = burst::chunk_of(w.k, in.K, in.V, in.dK, in.dV);
+    out.push_back(w);
+  }
+  return BURST_OK;
+}
+// Calls launch(kernels, first chunk, chunks, is first, is last) for every run of chunks that one launch can take.
+template <typename Choose, typename Launch>
+int for_each_run(const std::vector<WalkChunk>& w, Choose choose, Launch launch) {
+  const size_t n = w.size();
+  for (size_t i = 0; i < n;) {
+    const Kernels f = choose(&w[i].p, w[i].k);
+    Chunk run[burst::kMaxChunks];
+    size_t m = 0;
+    do { run[m] = w[i + m].c; m++; }
+    while (f.fused() && m < (size_t)burst::kMaxChunks && i + m < n && (w[i + m].c.bmask == nullptr) == (run[0].bmask == nullptr) &&
+           choose(&w[i + m].p, w[i + m].k) == f);
+    const int st = launch(f, w[i].k, run, (int)m, i == 0, i + m == n);
+    if (st != BURST_OK) return st;
+    i += m;
+  }
+  return BURST_OK;
+}
+
 // Caller holds g_bwd_mutex.
 int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
   int dev = 0;
@@ -309,11 +390,9 @@ int burst_local_fwd(const void* Q, const void* K_chunk, const void* V_chunk,
   REQUIRE_PTR(Q); REQUIRE_PTR(K_chunk); REQUIRE_PTR(V_chunk);
   REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l);
   if ((st = check_arch()) != BURST_OK) return st;
-  if (const PlainFamily* f = plain_family(p, k)) return f->fwd(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
-  if (use_plain128(p, k)) return burst::d128p::launch_fwd(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
-  if (use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows))
-    return burst::launch_fwd_mfma(k, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
-  return burst::launch_fwd_generic(k, p->dtype, Q, K_chunk, V_chunk, O_acc, m, l, (hipStream_t)stream);
+  const FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, 0, nullptr, 1};
+  const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, nullptr, nullptr);
+  return fwd_launch(fwd_kernels(p, k), k, p->dtype, io, &c, 1, (hipStream_t)stream);
 }
 
 int burst_set_kernel_family(int family) {
@@ -469,30 +548,14 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
     return BURST_OK;
   }
   // The kernels of this call: D (when it is not given), then the dQ half, then the dK/dV half.
-  const bool mfma_dq = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
-  const bool mfma_dkv = use_mfma(p, k) && dkv_mfma_ok(p, k);
-  const PlainFamily* const plain = plain_family(p, k);
-  const bool plain128 = use_plain128(p, k), plain128_dkv = use_plain128_dkv(p, k);
-  const bool adq = accumulate_dq != 0, adkv = accumulate_dkv != 0;
+  const Kernels fq = fwd_kernels(p, k), fk = dkv_kernels(p, k);
+  const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, nullptr, 1};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
-    if (want_dq) {
-      e = plain ? plain->bwd_dq(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
-        : plain128 ? burst::d128p::launch_bwd_dq(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
-        : mfma_dq ? burst::launch_bwd_dq_mfma(k, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s)
-                  : burst::launch_bwd_dq_generic(k, p->dtype, Q, K_chunk, V_chunk, dO, lse, Duse, dQ, adq, s);
-      if (e != BURST_OK) return e;
-    }
-    if (want_dkv) {
-      e = plain ? plain->bwd_dkv(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s)
-        : plain128_dkv ? burst::d128p::launch_bwd_dkv(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s)
-        : mfma_dkv ? burst::launch_bwd_dkv_mfma(k, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk, dV_chunk, adkv, s,
-                                                dkv_key_waves(p, k))
-                   : burst::launch_bwd_dkv_generic(k, p->dtype, Q, K_chunk, V_chunk, dO, lse, Duse, dK_chunk,
-                                                   dV_chunk, adkv, s);
-      if (e != BURST_OK) return e;
-    }
+    if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
+    if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     return BURST_OK;
   };
   if (D != nullptr) return validated([&] { return enqueue(D, nullptr); });
@@ -537,6 +600,95 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
                         0, accumulate_dkv, p, stream);
 }
 
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p) {
+  return 0;
+}
+
+int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
+                   void* O_out, float* lse, void* workspace, size_t workspace_bytes,
+                   const burst_params* p, void* stream) {
+  KParams k;
+  burst_params base;
+  if (p == nullptr) return BURST_ERR_NULL;
+  base = *p;
+  base.Nc = 0; base.block_mask = nullptr;
+  std::memset(base.kv_strides, 0, sizeof base.kv_strides);
+  int st = check_params(&base, &k);
+  if (st != BURST_OK) return st;
+  std::vector<WalkChunk> w;
+  if ((st = walk_chunks(chunks, n_chunks, p, false, w)) != BURST_OK) return st;
+  if ((long long)k.B * k.H * k.Nq == 0) return BURST_OK;
+  REQUIRE_PTR(Q); REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l); REQUIRE_PTR(O_out); REQUIRE_PTR(lse);
+  if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
+  if ((st = check_arch()) != BURST_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  return validated([&] {
+    bool fresh = true, final = false;
+    const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
+      FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, fresh, nullptr, 1};
+      if (f.fused()) {
+        if (last) { io.O_out = O_out; io.lse = lse; final = true; }
+      } else if (fresh) {
+        io.fresh = 0;
+        if (const int i = burst::launch_state_init(k, O_acc, m, l, s); i != BURST_OK) return i;
+      }
+      fresh = false;
+      return fwd_launch(f, kc, p->dtype, io, c, n, s);
+    });
+    if (e != BURST_OK) return e;
+    if (fresh)
+      if (const int i = burst::launch_state_init(k, O_acc, m, l, s); i != BURST_OK) return i;
+    return final ? (int)BURST_OK : burst::launch_finalize(k, p->dtype, O_acc, m, l, O_out, lse, s);
+  });
+}
+
+int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
+                   const float* lse, float* D, float* dQ, int accumulate_dq, int accumulate_dkv,
+                   void* workspace, size_t workspace_bytes, const burst_params* p, void* stream) {
+  KParams k;
+  burst_params base;
+  if (p == nullptr) return BURST_ERR_NULL;
+  base = *p;
+  base.Nc = 0; base.block_mask = nullptr;
+  std::memset(base.kv_strides, 0, sizeof base.kv_strides);
+  int st = check_params(&base, &k);
+  if (st != BURST_OK) return st;
+  std::vector<WalkChunk> w;
+  if ((st = walk_chunks(chunks, n_chunks, p, true, w)) != BURST_OK) return st;
+  const long long bh = (long long)k.B * k.H;
+  const bool have_q = bh * k.Nq > 0;
+  if (!have_q && w.empty()) return BURST_OK;
+  if (have_q) {
+    REQUIRE_PTR(Q); REQUIRE_PTR(dO); REQUIRE_PTR(lse); REQUIRE_PTR(D); REQUIRE_PTR(dQ);
+    if (O != nullptr && !aligned16(O)) return BURST_ERR_ALIGN;
+  }
+  if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
+  if ((st = check_arch()) != BURST_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  return validated([&]() -> int {
+    int e = BURST_OK;
+    if (!have_q) {                                 // no rows: dK and dV are zero
+      for (const WalkChunk& x : w) {
+        if (accumulate_dkv) break;
+        if ((e = burst::launch_zero_fill((float*)x.c.dK, bh / k.group * x.c.Nc * k.d, s)) != BURST_OK) return e;
+        if ((e = burst::launch_zero_fill((float*)x.c.dV, bh / k.group * x.c.Nc * k.d, s)) != BURST_OK) return e;
+      }
+      return BURST_OK;
+    }
+    if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
+    if (w.empty()) return accumulate_dq ? (int)BURST_OK : burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s);
+    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, nullptr, 1};
+    e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
+      io.acc_dq = accumulate_dq != 0 || !first;
+      return dq_launch(f, kc, p->dtype, io, c, n, s);
+    });
+    if (e != BURST_OK) return e;
+    return for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
+      return dkv_launch(f, kc, p->dtype, io, c, n, s);
+    });
+  });
+}
+
 void* burst_event_create(void) {
   hipEvent_t e = nullptr;
   if (hipEventCreate(&e) != hipSuccess) return nullptr;
@@ -570,6 +722,6 @@ const char* burst_strerror(int status) {
   }
 }
 
-int burst_version(void) { return 111; }
+int burst_version(void) { return 112; }
 
 }  // extern "C"

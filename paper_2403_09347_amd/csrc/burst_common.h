@@ -69,6 +69,72 @@ struct KParams {
   }
 };
 
+// One key/value chunk of a call, as the kernels see it.  An entry point that is handed several chunks
+// passes them to one launch (at most kMaxChunks: they travel in the kernel arguments, which hold 4 KB).
+struct Chunk {
+  const void* K; const void* V;
+  void* dK; void* dV;                // backward only
+  const uint8_t* bmask;              // block flags of this chunk (nullptr = none), [ceil(Nq/bsize)][bpitch]
+  long long bhstride;                // bytes between the flag matrices of consecutive query heads (0 = shared)
+  long long k_off;                   // global position of key 0
+  long long ks_b, ks_h, ks_r;        // element strides of K and V: batch, head, row
+  int Nc, bpitch;
+  int first_block;                   // dK/dV kernels: workgroups of the chunks before this one
+  // element offset of row 0 of key/value head `kvhead`, which counts batch x heads
+  __host__ __device__ size_t kv_base(int kvhead, int kv_heads) const {
+    const int b = kvhead / kv_heads;
+    return (size_t)b * ks_b + (size_t)(kvhead - b * kv_heads) * ks_h;
+  }
+};
+constexpr int kMaxChunks = 32;
+inline Chunk chunk_of(const KParams& p, const void* K, const void* V, void* dK, void* dV) {
+  Chunk c = {};
+  c.K = K; c.V = V; c.dK = dK; c.dV = dV;
+  c.bmask = p.bmask; c.bhstride = p.bhstride; c.bpitch = p.bpitch;
+  c.k_off = p.k_off; c.Nc = p.Nc;
+  c.ks_b = p.lay.ks_b; c.ks_h = p.lay.ks_h; c.ks_r = p.lay.ks_r;
+  return c;
+}
+// What a forward (backward) launch reads and writes beside its chunks.
+struct FwdIo {
+  const void* Q;
+  float* O_acc; float* m; float* l;  // running state
+  void* O_out; float* lse;           // O_out != nullptr: the state is final after this launch, write these too
+  int fresh;                         // the state before the launch is the initial one, whatever the buffers hold
+  float* part; int splits;           // splits > 1: partial states of that many key ranges go to `part` instead
+};
+struct BwdIo {
+  const void* Q; const void* dO; const float* lse; const float* D;
+  float* dQ;
+  int acc_dq, acc_dkv;               // add to what the gradient buffers hold
+  float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
+};
+
+// The forward kernels choose their reference maximum (log2 units) on a grid of 16: rows of ordinary
+// inputs then get the same reference whatever the order of the chunks and however the keys are split,
+// and with it the same bf16 rounding of P.  (P is at most 2^16 smaller than with the maximum itself,
+// which changes the precision of nothing: bf16 and fp32 are floating point.)  A stored m (natural log)
+// of such a reference comes back exactly: r ln2 log2e differs from r by at most 4 x 2^-24 of it.  Any
+// other m is taken as it is.
+__device__ __forceinline__ float reference_for(float row_max) { return 16.f * __builtin_ceilf(row_max * 0.0625f); }
+__device__ __forceinline__ float reference_of(float m) {
+  const float x = m * kLog2e, r = __builtin_rintf(x);
+  return fabsf(x - r) <= 3e-7f * fabsf(r) ? r : x;
+}
+
+// Workgroup id -> (head, block of the head).  Ids go round-robin to the 8 XCDs; each XCD gets one
+// run of consecutive blocks, so that a head's tensors stay in one L2 and all XCDs get the same number
+// of workgroups whatever the number of heads.  False: nothing to do (the grid is rounded up to 8).
+__device__ __forceinline__ bool locate_block(int bid, int heads, int blocks, int& head, int& blk) {
+  const int total = heads * blocks, per = (total + 7) >> 3;
+  const int lin = (bid & 7) * per + (bid >> 3);
+  if ((bid >> 3) >= per || lin >= total) return false;
+  head = lin / blocks;
+  blk = lin - head * blocks;
+  return true;
+}
+inline long long grid_blocks(long long heads, long long blocks) { return (heads * blocks + 7) / 8 * 8; }
+
 // The opt-in to more than 64 KB of dynamic LDS is a per-device function attribute: launchers
 // set it once per device (index = current device, or -1 if it cannot be determined), whichever
 // host thread comes first.

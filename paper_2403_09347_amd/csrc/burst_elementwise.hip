@@ -178,6 +178,75 @@ zero_fill_kernel(float* __restrict__ p, long long n) {
   for (long long k = (n4 << 2) + (long long)blockIdx.x * 256 + threadIdx.x; k < n; k += stride) p[k] = 0.f;
 }
 
+// Partial states of `splits` key ranges (O [splits][rows][d], then m in log2 units and l, each
+// [splits][rows]) -> one, merged with the stored state unless that is the initial one; with O_out also
+// finalized (Alg. 1 merge step and last two steps).  HBM bound: every partial is read once.  d a
+// multiple of 8; d / 4 threads per row, whole rows per workgroup, so that a barrier separates the
+// reads of a row's old m and l from the write of the new ones.
+__global__ void __launch_bounds__(256)
+merge_splits_kernel(const float* __restrict__ part, int splits, float* __restrict__ O_acc, float* __restrict__ m,
+                    float* __restrict__ l, bf16* __restrict__ O_out, float* __restrict__ lse, int fresh,
+                    long long n_rows, int d, QRows qr) {
+  const int per_row = d >> 2;
+  const float* const pm = part + (size_t)splits * n_rows * d;
+  const float* const pl = pm + (size_t)splits * n_rows;
+  const int rows_here = 256 / per_row, r_in = threadIdx.x / per_row, c = threadIdx.x - r_in * per_row;
+  const bool live = r_in < rows_here && (long long)blockIdx.x * rows_here + r_in < n_rows;
+  const long long row = live ? (long long)blockIdx.x * rows_here + r_in : 0;
+  float mg = BURST_NEG_INF;
+  for (int i = 0; i < splits; i++) mg = fmaxf(mg, pm[i * n_rows + row]);
+  const float m_old = fresh ? BURST_NEG_INF : m[row], l_old = fresh ? 0.f : l[row];
+  float m_st = m_old, lsum = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  f32x4* const state = reinterpret_cast<f32x4*>(O_acc + row * d + c * 4);
+  if (mg != BURST_NEG_INF) {
+    const float m_old2 = m_old * kLog2e, mn = fmaxf(mg, m_old2);
+    const float fa = fast_exp2(m_old2 - mn);
+    if (fa != 0.f) {
+      const f32x4 old = *state;
+      for (int t = 0; t < 4; t++) o[t] = fa * old[t];
+      lsum = fa * l_old;
+    }
+    for (int i = 0; i < splits; i++) {
+      const float f = fast_exp2(pm[i * n_rows + row] - mn);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(part + ((size_t)i * n_rows + row) * d + c * 4);
+      for (int t = 0; t < 4; t++) o[t] += f * v[t];
+      lsum += f * pl[i * n_rows + row];
+    }
+    m_st = mn * kLn2;
+  } else if (m_old != BURST_NEG_INF) {             // no range saw a key: the state stays
+    o = *state;
+    lsum = l_old;
+  }
+  __syncthreads();
+  if (!live) return;
+  if (fresh || mg != BURST_NEG_INF) {
+    *state = o;
+    if (c == 0) { m[row] = m_st; l[row] = lsum; }
+  }
+  if (O_out != nullptr) {
+    const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    bf16x4 r;
+    for (int t = 0; t < 4; t++) r[t] = (bf16)(lsum > 0.f ? o[t] * inv : 0.f);
+    *reinterpret_cast<bf16x4*>(O_out + qr.off(row) + c * 4) = r;
+    if (c == 0) lse[row] = lsum > 0.f ? m_st + __logf(lsum) : BURST_NEG_INF;
+  }
+}
+
+// dQ = (acc ? dQ : 0) + the sum of `splits` partial dQ [splits][n], in that order.
+__global__ void __launch_bounds__(256)
+sum_splits_kernel(const float* __restrict__ part, int splits, float* __restrict__ dQ, int acc, long long n4) {
+  const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (k >= n4) return;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (acc) v = reinterpret_cast<const f32x4*>(dQ)[k];
+  for (int i = 0; i < splits; i++) {
+    const f32x4 x = reinterpret_cast<const f32x4*>(part)[(size_t)i * n4 + k];
+    for (int t = 0; t < 4; t++) v[t] += x[t];
+  }
+  reinterpret_cast<f32x4*>(dQ)[k] = v;
+}
+
 static inline unsigned grid_for(long long work_items, int per_block = 256, unsigned cap = 256 * 16) {
   long long b = (work_items + per_block - 1) / per_block;
   if (b < 1) b = 1;
@@ -212,6 +281,25 @@ int launch_finalize(const KParams& p, int dtype, const float* O_acc, const float
     if (vec) BURST_LAUNCH((finalize_kernel<float, 4>), dim3(g), dim3(256), 0, s, O_acc, m, l, (float*)O_out, lse, rows, p.d, p.q_rows());
     else BURST_LAUNCH((finalize_kernel<float, 1>), dim3(g), dim3(256), 0, s, O_acc, m, l, (float*)O_out, lse, rows, p.d, p.q_rows());
   }
+  return launch_status();
+}
+
+int launch_merge_splits(const KParams& p, const FwdIo& io, hipStream_t s) {
+  const long long rows = (long long)p.B * p.H * p.Nq;
+  const int here = 256 / (p.d / 4);
+  const long long blocks = (rows + here - 1) / here;
+  if (rows == 0) return BURST_OK;
+  if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  BURST_LAUNCH(merge_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.O_acc, io.m, io.l,
+               (bf16*)io.O_out, io.lse, io.fresh, rows, p.d, p.q_rows());
+  return launch_status();
+}
+
+int launch_sum_splits(const KParams& p, const BwdIo& io, hipStream_t s) {
+  const long long n4 = (long long)p.B * p.H * p.Nq * p.d / 4, blocks = (n4 + 255) / 256;
+  if (n4 == 0) return BURST_OK;
+  if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  BURST_LAUNCH(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.dQ, io.acc_dq, n4);
   return launch_status();
 }
 

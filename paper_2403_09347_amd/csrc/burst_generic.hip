@@ -94,19 +94,6 @@ struct Rows {
   }
 };
 
-// Workgroup id -> (head, block).  Ids go round-robin to the 8 XCDs; each XCD gets one run of
-// consecutive blocks, so that a head's tensors stay in one L2 and every XCD gets the same number of
-// workgroups whatever the number of heads.
-__device__ __forceinline__ bool gen_locate(int bid, int heads, int blocks, int& head, int& blk) {
-  const int total = heads * blocks, per = (total + 7) >> 3;
-  const int lin = (bid & 7) * per + (bid >> 3);
-  if ((bid >> 3) >= per || lin >= total) return false;
-  head = lin / blocks;
-  blk = lin - head * blocks;
-  return true;
-}
-static unsigned gen_grid(long long heads, long long blocks) { return (unsigned)((heads * blocks + 7) / 8 * 8); }
-
 // Key tiles (32 keys) of the chunk that rows [row0, row0 + 32) of the slice can see: [lo, hi).
 __device__ __forceinline__ void key_tiles(const GenArgs& a, int row0, int& lo, int& hi) {
   lo = 0; hi = (a.Nc + 31) >> 5;
@@ -151,7 +138,7 @@ fwd_generic_kernel(GenArgs a) {
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk;
-  if (!gen_locate(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
   const int row0 = blk * 32, row = row0 + lr;
   const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
   const T* Vh = (const T*)a.V + a.lay.kv_base(head / a.group);
@@ -293,7 +280,7 @@ bwd_dq_generic_kernel(GenArgs a) {
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk;
-  if (!gen_locate(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
   const int row0 = blk * 32, row = row0 + lr;
   const bool ok = row < a.Nq;
   const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
@@ -414,7 +401,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int kvhead, blk;
-  if (!gen_locate(blockIdx.x, a.BH / a.group, a.blocks, kvhead, blk)) return;
+  if (!locate_block(blockIdx.x, a.BH / a.group, a.blocks, kvhead, blk)) return;
   const int key0 = blk * 32, key = key0 + lr;
   int lo, hi;
   row_tiles(a, key0, lo, hi);
@@ -580,7 +567,7 @@ static int gen_launch(GenArgs a, hipStream_t s) {
   a.blocks = (int)(((long long)(KIND == GEN_DKV ? a.Nc : a.Nq) + 31) / 32);
   if (heads * a.blocks > 0x7fffff00LL) return BURST_ERR_SHAPE;
   const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : 0)) * 4;
-  const dim3 grid(gen_grid(heads, a.blocks)), wg(64 * W);
+  const dim3 grid((unsigned)grid_blocks(heads, a.blocks)), wg(64 * W);
   void (*kernel)(GenArgs);
   if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W>;
   else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W>;

@@ -26,6 +26,7 @@
 #if !defined(BURST_SMALL_D) || !defined(BURST_SMALL_NS)
 #error "define BURST_SMALL_D and BURST_SMALL_NS before including burst_plain_mfma.h"
 #endif
+#include <cmath>
 #include "burst_bwd_common.h"
 
 namespace burst {
@@ -50,17 +51,35 @@ constexpr int S_GPR = S_ROWB / 16;                // granules per row
 constexpr float S_LAZY = 8.0f;                    // log2 of the largest P allowed before the max is raised
 
 struct FwdArgsLite {
-  const bf16* Q; const bf16* K; const bf16* V;
+  const bf16* Q;
   float* O_acc; float* m; float* l;
-  int Nq, Nc, H, group;
-  int causal;
-  float c;               // scale * log2(e)
-  long long q_off, k_off, window;
-  const uint8_t* bmask; int bsize, bpitch;       // block flags (nullptr = none)
-  long long bhstride;                            // bytes between heads' flag matrices (0 = shared)
-  int blocks_per_head;
+  bf16* O_out; float* lse;                       // O_out != nullptr: final after this launch
+  float* part;                                   // partial states (splits > 1)
+  int Nq, H, group;                              // H counts batch x heads
+  int causal, fresh;
+  float c;                                       // scale * log2(e)
+  long long q_off, window;
+  int bsize;
+  int blocks_per_head, splits;
   int d;                                         // head dimension (S_D unless S_PAD)
-  Layout lay;                                    // strides of Q and of K, V
+  int n;                                         // chunks
+  Layout lay;                                    // strides of Q and O_out
+  Chunk ch[kMaxChunks];
+};
+struct BwdArgsLite {
+  const bf16* Q; const bf16* dO;
+  const float* lse; const float* D;
+  float* dQ;
+  float* part;                                   // partial dQ (splits > 1)
+  int Nq, H, group;                              // H counts batch x heads (dQ: query heads, dK/dV: key/value heads)
+  int causal, acc_dq, acc_dkv;
+  float c, scale, log2_scale;
+  long long q_off, window;
+  int bsize;
+  int blocks_per_head, splits;
+  int d, n;
+  Layout lay;
+  Chunk ch[kMaxChunks];
 };
 
 __device__ __forceinline__ int s_swz(int row) { return S_ROWB == 128 ? ((row >> 1) & 7) : row_code(row); }
@@ -96,21 +115,15 @@ __device__ __forceinline__ bf16x8 s_load8(const bf16* p, bool ok) {
   for (int t = 0; t < 8; t++) z[t] = (bf16)0.0f;
   return ok ? *reinterpret_cast<const bf16x8*>(p) : z;
 }
-__device__ __forceinline__ void s_head_block(int bid, int blocks_per_head, int& head, int& blk) {
-  // consecutive workgroup ids go round-robin to the 8 XCDs: all blocks of a head share an XCD
-  const int xcd = bid & 7, idx = bid >> 3;
-  const int hx = idx / blocks_per_head;
-  blk = idx - hx * blocks_per_head;
-  head = hx * 8 + xcd;
-}
-
 // Calls with block flags (paper Sec. 2.6) run the SPARSE instantiations: wavefront 0 first writes
 // the list of tiles that at least one wavefront of the workgroup can see into LDS (tile index plus
-// one bit per wavefront, list[0] = count, two end entries that name a tile past the data), the
-// loop then walks that list, and a wavefront whose bit is clear hides the whole tile.
+// one bit per wavefront, list[0] = count), the loop then walks that list, and a wavefront whose bit
+// is clear skips the tile.  A walk over several chunks writes a list per chunk when it gets there: all
+// wavefronts have then read the last entry of the one before.
 constexpr int S_MAX_LIST = 4096;                  // entries; longer masked calls take the generic kernels
 template <typename F>
-__device__ __forceinline__ int s_build_list(int* list, int w, int lane, int t_lo, int t_hi, int end_tile, F bits_of) {
+__device__ __forceinline__ int s_build_list(int* list, int w, int lane, int t_lo, int t_hi, F bits_of) {
+  __syncthreads();                                // (the count of the list before may still be on its way)
   if (w == 0) {
     int n = 0;
     for (int base = t_lo; base < t_hi; base += 64) {
@@ -124,7 +137,6 @@ __device__ __forceinline__ int s_build_list(int* list, int w, int lane, int t_lo
       }
       n += __builtin_popcountll(bal);
     }
-    if (lane < 2) list[1 + n + lane] = end_tile;
     if (lane == 0) list[0] = n;
   }
   __syncthreads();
@@ -143,101 +155,151 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
-  int head, qb;
-  s_head_block(blockIdx.x, a.blocks_per_head, head, qb);
-  if (head >= a.H) return;
+  int head, qb, split = 0;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb)) return;
+  if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
-  const int q0 = qb * SF_BR + w * 32;
-  const bf16* Qh = a.Q + a.lay.q_base(head);
-  const bf16* Kh = a.K + a.lay.kv_base(head / a.group);
-  const bf16* Vh = a.V + a.lay.kv_base(head / a.group);
-  const unsigned kpitch = (unsigned)a.lay.ks_r * 2u;             // bytes between key rows
+  const int q0 = qb * SF_BR + w * 32, row = q0 + lr;
+  const int kvhead = head / a.group;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const unsigned lds0 = lds_addr(smem);
 
-  int Nc = a.Nc;
-  long long k_off = a.k_off;
-  int t_lo = 0;
-  if (a.window > 0) {                              // skip whole tiles before the window of the first row
-    long long lo = a.q_off + (long long)qb * SF_BR - a.window + 1 - a.k_off;
-    if (lo >= a.Nc) return;
-    if (lo > 0) {
-      const int skip = (int)(lo / SF_BC) * SF_BC;
-      if constexpr (SPARSE) {
-        t_lo = skip / SF_BC;
-      } else {
-        Kh += (size_t)skip * a.lay.ks_r; Vh += (size_t)skip * a.lay.ks_r;
-        Nc -= skip; k_off += skip;
+  // The chunks' visible tiles (or list entries) form one sequence; this workgroup takes every
+  // `splits`-th of it, tile after tile, with the next one in flight across the chunk boundaries.
+  constexpr int NL = SF_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
+  int c = -1, ft = split, lo = 0, hi = 0;         // chunk, position in it, first and end position
+  int f_tile = 0, f_bits = 0xf, f_Nc = 0;         // the tile that was fetched last
+  long long f_koff = 0;
+  bool f_first = false;                           // ... is the first one of its chunk
+  unsigned ktile = 0;
+  int goff[NL];
+  __amdgpu_buffer_rsrc_t krs = make_rsrc(nullptr, 0), vrs = krs;
+  auto advance = [&](int step) __attribute__((always_inline)) {
+    ft += step;
+    f_first = false;
+    while (ft >= hi) {
+      const int past = ft - hi;
+      if (++c >= a.n) return false;
+      const Chunk& C = a.ch[c];
+      f_Nc = C.Nc; f_koff = C.k_off;
+      lo = 0; hi = (f_Nc + SF_BC - 1) / SF_BC;
+      if (a.window > 0) {                          // keys before the window of the first row
+        const long long first = a.q_off + (long long)qb * SF_BR - a.window + 1 - f_koff;
+        if (first >= f_Nc) lo = hi;
+        else if (first > 0) lo = (int)(first / SF_BC);
       }
-    }
-  }
-  int ntiles = (Nc + SF_BC - 1) / SF_BC;
-  if (a.causal) {                                  // stop after the last tile any row of the workgroup sees
-    long long lim = a.q_off + min(qb * SF_BR + SF_BR, a.Nq) - 1 - k_off;
-    if (lim < 0) return;
-    long long t = lim / SF_BC + 1;
-    if (t < ntiles) ntiles = (int)t;
-  }
-  if (ntiles <= 0) return;
-  if constexpr (SPARSE) {
-    ntiles = s_build_list(s_list, w, lane, t_lo, ntiles, (Nc + SF_BC - 1) / SF_BC, [&](int t) {
-      int bits = 0;
+      if (a.causal) {                              // keys after the last row
+        const long long last = a.q_off + min(qb * SF_BR + SF_BR, a.Nq) - 1 - f_koff;
+        if (last < 0) hi = lo;
+        else if (last / SF_BC + 1 < hi) hi = (int)(last / SF_BC) + 1;
+      }
+      if (hi > lo) {
+        const unsigned kpitch = (unsigned)C.ks_r * 2u;           // bytes between key rows
+        const size_t base = C.kv_base(kvhead, a.lay.kv_heads);
+        krs = make_rsrc((const bf16*)C.K + base, s_span(f_Nc, kpitch, d));
+        vrs = make_rsrc((const bf16*)C.V + base, s_span(f_Nc, kpitch, d));
+        ktile = kpitch * SF_BC;
 #pragma unroll
-      for (int ww = 0; ww < 4; ww++) {
-        const int row0 = qb * SF_BR + ww * 32;
-        if (row0 < a.Nq && (a.bmask + (size_t)head * a.bhstride)[(size_t)(row0 / a.bsize) * a.bpitch + (t * SF_BC) / a.bsize] != 0) bits |= 1 << ww;
+        for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
+        if constexpr (SPARSE) {
+          const uint8_t* const bm = C.bmask + (size_t)head * C.bhstride;
+          hi = s_build_list(s_list, w, lane, lo, hi, [&](int t) {
+            int bits = 0;
+#pragma unroll
+            for (int ww = 0; ww < 4; ww++) {
+              const int row0 = qb * SF_BR + ww * 32;
+              if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + (t * SF_BC) / a.bsize] != 0) bits |= 1 << ww;
+            }
+            return bits;
+          });
+          lo = 0;
+        }
       }
-      return bits;
-    });
-    if (ntiles == 0) return;
-  }
-  auto entry_at = [&](int j) __attribute__((always_inline)) {      // walk position -> tile | wavefront bits << 20
-    if constexpr (SPARSE) return __builtin_amdgcn_readfirstlane(s_list[1 + j]);
-    else return j | (0xf << 20);
+      hi = max(hi, lo);
+      ft = lo + past;
+      f_first = true;
+    }
+    f_tile = ft;
+    if constexpr (SPARSE) {
+      const int e = __builtin_amdgcn_readfirstlane(s_list[1 + ft]);
+      f_tile = e & 0xfffff;
+      f_bits = e >> 20;
+    }
+    return true;
   };
+  auto fetch = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int il = 0; il < NL; il++) {
+      dma_b128_to_lds(krs, lds0 + buf * SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)f_tile * ktile) + goff[il]);
+      dma_b128_to_lds(vrs, lds0 + (2 + buf) * SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)f_tile * ktile) + goff[il]);
+    }
+  };
+  bool have = advance(0);
+  // nothing visible: the state stays as it is, unless this launch has to produce it
+  if (!have && !a.fresh && a.O_out == nullptr) return;
+  if (have) fetch(0);
 
   bf16x8 qf[S_KS];
+  const bf16* Qh = a.Q + a.lay.q_base(head);
 #pragma unroll
-  for (int ks = 0; ks < S_KS; ks++) qf[ks] = s_load8(Qh + (size_t)(q0 + lr) * a.lay.qs_r + ks * 16 + h * 8, q0 + lr < a.Nq && (!S_PAD || ks * 16 + h * 8 < d));
+  for (int ks = 0; ks < S_KS; ks++) qf[ks] = s_load8(Qh + (size_t)row * a.lay.qs_r + ks * 16 + h * 8, row < a.Nq && (!S_PAD || ks * 16 + h * 8 < d));
+  // The state in registers: O^T accumulators, reference maximum m2 (log2 units, see reference_of), and
+  // the row sum over this lane's keys.  m_st is m as it is stored (natural log); a row whose reference
+  // has not moved keeps it bit for bit.
+  const size_t srow = (size_t)head * a.Nq + (row < a.Nq ? row : 0);
   f32x16 o[S_DB];
 #pragma unroll
   for (int db = 0; db < S_DB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) o[db][r] = 0.f;
-  float m2 = BURST_NEG_INF, lsum = 0.f;            // reference max (log2 units), sum over this lane's keys
+  float m_st = BURST_NEG_INF, lsum = 0.f;
+  if (!a.fresh && row < a.Nq) {
+    m_st = a.m[srow];
+    if (m_st != BURST_NEG_INF) {                   // (a row that has seen nothing may hold anything)
+      if (h == 0) lsum = a.l[srow];
+      const float* orow = a.O_acc + srow * d;
+#pragma unroll
+      for (int db = 0; db < S_DB; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          if (S_PAD && db * 32 + 8 * q4 >= d) continue;
+          const f32x4 v = *reinterpret_cast<const f32x4*>(orow + db * 32 + 8 * q4 + 4 * h);
+#pragma unroll
+          for (int b = 0; b < 4; b++) o[db][4 * q4 + b] = v[b];
+        }
+    }
+  }
+  float m2 = reference_of(m_st);
+  const float m_in = m2;
+  // What a store of the state and a load by the next launch do to it (to the row sum; m2 comes back as
+  // it was): a walk gives the same bits whether its chunks come in one launch or one by one.
+  auto settle = [&]() __attribute__((always_inline)) {
+    const float both = sum_both_halves(lsum);
+    lsum = h == 0 ? both : 0.f;
+  };
 
   int kaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
   for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
   s_taddr(lane, taddr);
-  const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch, d));
-  const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch, d));
-  const int wu = __builtin_amdgcn_readfirstlane(w);
-  const unsigned lds0 = lds_addr(smem);
-  constexpr int NL = SF_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
-  int goff[NL];
-#pragma unroll
-  for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
-  auto dma_tile = [&](int t, int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int il = 0; il < NL; il++) {
-      dma_b128_to_lds(krs, lds0 + buf * SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SF_BC * kpitch) + goff[il]);
-      dma_b128_to_lds(vrs, lds0 + (2 + buf) * SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SF_BC * kpitch) + goff[il]);
-    }
-  };
   const long long wave_first_q = a.q_off + q0, wave_last_q = wave_first_q + 31;
   bf16x2 ones;
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
 
-  dma_tile(entry_at(0) & 0xfffff, 0);
-  for (int j = 0; j < ntiles; j++) {               // j = walk position, kt = tile
-    const int e = entry_at(j);
-    const int kt = e & 0xfffff;
-    const bool mine = ((e >> (20 + wu)) & 1) != 0;
+  bool begun = false;
+  for (int buf = 0; have; buf ^= 1) {
+    const int kt = f_tile, Nc = f_Nc;
+    const long long k_off = f_koff;
+    const bool mine = ((f_bits >> wu) & 1) != 0, first = f_first;
     __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0): the tile landed, reads of the one before are done
     __builtin_amdgcn_s_barrier();
-    if (j + 1 < ntiles) dma_tile(entry_at(j + 1) & 0xfffff, (j + 1) & 1);
+    have = advance(a.splits);
+    if (have) fetch(buf ^ 1);
+    if (first && begun) settle();
+    begun = true;
     if (!mine) continue;                           // block flags hide the tile from this wavefront's rows
-    const char* kl = smem + (j & 1) * SF_TILE;
-    const char* vl = smem + (2 + (j & 1)) * SF_TILE;
+    const char* kl = smem + buf * SF_TILE;
+    const char* vl = smem + (2 + buf) * SF_TILE;
     // S^T = K Q^T: register r of key block kb = key kt*64 + kb*32 + 8*(r/4) + 4h + r%4
     f32x16 s[2];
 #pragma unroll
@@ -275,7 +337,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       for (int r = 0; r < 16; r++) v = fmaxf(v, s[kb][r]);
     const float mx = max_both_halves(v) * a.c;
     if (__builtin_amdgcn_ballot_w64(mx > m2 + S_LAZY) != 0) {   // raise the reference max (rare after the first tiles)
-      const float m_new = fmaxf(m2, mx);
+      const float m_new = mx > m2 ? reference_for(mx) : m2;
       const float ref = (m_new == BURST_NEG_INF) ? 0.f : m_new;
       const float alpha = fast_exp2(m2 - ref);
       m2 = m_new;
@@ -310,30 +372,59 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
-  // merge into the state (Alg. 1): lane (lr, h) holds row lr, columns db*32 + 8*q4 + 4h + (0..3)
-  const int row = q0 + lr;
-  const float l_chunk = sum_both_halves(lsum);
-  if (row < a.Nq && m2 != BURST_NEG_INF) {
-    const size_t srow = (size_t)head * a.Nq + row;
-    const float m_old2 = a.m[srow] * kLog2e, l_old = a.l[srow];
-    const float m_new = fmaxf(m_old2, m2);
-    const float fa = fast_exp2(m_old2 - m_new), fb = fast_exp2(m2 - m_new);
-    float* orow = a.O_acc + srow * d;
+  const float l_all = sum_both_halves(lsum);
+  if (m2 != m_in) m_st = m2 * kLn2;
+  asm volatile("" : "+v"(m_st));                   // (m as the next launch would load it)
+  if (row >= a.Nq) return;
+  // lane (lr, h) holds row lr, columns db*32 + 8*q4 + 4h + (0..3)
+  if (a.splits > 1) {                              // a partial state: [split][rows][d] O, then m (log2 units) and l
+    const size_t rows = (size_t)a.H * a.Nq, pr = (size_t)split * rows + srow;
+    float* const prow = a.part + pr * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
         if (S_PAD && db * 32 + 8 * q4 >= d) continue;
-        float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
-        f32x4 old = *reinterpret_cast<f32x4*>(ptr), nw;
+        f32x4 v;
 #pragma unroll
-        for (int b = 0; b < 4; b++) nw[b] = ((fa == 0.f) ? 0.f : old[b] * fa) + fb * o[db][4 * q4 + b];
-        *reinterpret_cast<f32x4*>(ptr) = nw;
+        for (int b = 0; b < 4; b++) v[b] = o[db][4 * q4 + b];
+        *reinterpret_cast<f32x4*>(prow + db * 32 + 8 * q4 + 4 * h) = v;
       }
     if (h == 0) {
-      a.m[srow] = m_new * kLn2;
-      a.l[srow] = ((fa == 0.f) ? 0.f : fa * l_old) + fb * l_chunk;
+      float* const ml = a.part + (size_t)a.splits * rows * d;
+      ml[pr] = m2;
+      ml[(size_t)a.splits * rows + pr] = l_all;
     }
+    return;
+  }
+  if (a.fresh || m2 != BURST_NEG_INF) {            // rows that never saw a key keep their state
+    float* const orow = a.O_acc + srow * d;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
+        f32x4 v;
+#pragma unroll
+        for (int b = 0; b < 4; b++) v[b] = o[db][4 * q4 + b];
+        *reinterpret_cast<f32x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
+      }
+    if (h == 0) { a.m[srow] = m_st; a.l[srow] = l_all; }
+  }
+  if (a.O_out != nullptr) {                        // Alg. 1, last two steps
+    const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
+    bf16* const out = a.O_out + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
+        bf16x4 v;
+#pragma unroll
+        for (int b = 0; b < 4; b++) v[b] = (bf16)(l_all > 0.f ? o[db][4 * q4 + b] * inv : 0.f);
+        *reinterpret_cast<bf16x4*>(out + db * 32 + 8 * q4 + 4 * h) = v;
+      }
+    if (h == 0) a.lse[srow] = l_all > 0.f ? m_st + __logf(l_all) : BURST_NEG_INF;
   }
 }
 
@@ -344,70 +435,115 @@ constexpr int SQ_TILE = SQ_BC * S_ROWB;
 
 template <bool SPARSE>
 __global__ void __launch_bounds__(256, 2)
-burst_bwd_dq_d64_kernel(BwdArgs a) {
+burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SQ_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
-  int head, qb;
-  s_head_block(blockIdx.x, a.blocks_per_head, head, qb);
-  if (head >= a.H) return;
+  int head, qb, split = 0;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb)) return;
+  if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
   const int q0 = qb * SQ_BR + w * 32;
   const int row = q0 + lr;
   const bool ok = row < a.Nq;
   const size_t srow = (size_t)head * a.Nq + (ok ? row : 0);
-  const bf16* Kh = a.K + a.lay.kv_base(head / a.group);
-  const bf16* Vh = a.V + a.lay.kv_base(head / a.group);
-  const unsigned kpitch = (unsigned)a.lay.ks_r * 2u;             // bytes between key rows
+  const int kvhead = head / a.group;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const unsigned lds0 = lds_addr(smem);
 
-  int Nc = a.Nc;
-  long long k_off = a.k_off;
-  bool nothing = false;
-  int t_lo = 0;
-  if (a.window > 0) {
-    long long lo = a.q_off + (long long)qb * SQ_BR - a.window + 1 - a.k_off;
-    if (lo >= a.Nc) nothing = true;
-    else if (lo > 0) {
-      const int skip = (int)(lo / SQ_BC) * SQ_BC;
-      if constexpr (SPARSE) {
-        t_lo = skip / SQ_BC;
-      } else {
-        Kh += (size_t)skip * a.lay.ks_r; Vh += (size_t)skip * a.lay.ks_r;
-        Nc -= skip; k_off += skip;
+  // The chunks' visible tiles (or list entries) form one sequence, as in the forward kernel.
+  constexpr int NL = SQ_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
+  int c = -1, ft = split, lo = 0, hi = 0;         // chunk, position in it, first and end position
+  int f_tile = 0, f_bits = 0xf, f_Nc = 0;         // the tile that was fetched last
+  long long f_koff = 0;
+  unsigned ktile = 0;
+  int goff[NL];
+  __amdgpu_buffer_rsrc_t krs = make_rsrc(nullptr, 0), vrs = krs;
+  auto advance = [&](int step) __attribute__((always_inline)) {
+    ft += step;
+    while (ft >= hi) {
+      const int past = ft - hi;
+      if (++c >= a.n) return false;
+      const Chunk& C = a.ch[c];
+      f_Nc = C.Nc; f_koff = C.k_off;
+      lo = 0; hi = (f_Nc + SQ_BC - 1) / SQ_BC;
+      if (a.window > 0) {
+        const long long first = a.q_off + (long long)qb * SQ_BR - a.window + 1 - f_koff;
+        if (first >= f_Nc) lo = hi;
+        else if (first > 0) lo = (int)(first / SQ_BC);
       }
-    }
-  }
-  int ntiles = nothing ? 0 : (Nc + SQ_BC - 1) / SQ_BC;
-  if (a.causal) {
-    long long lim = a.q_off + min(qb * SQ_BR + SQ_BR, a.Nq) - 1 - k_off;
-    long long t = lim < 0 ? 0 : lim / SQ_BC + 1;
-    if (t < ntiles) ntiles = (int)t;
-  }
-
-  if constexpr (SPARSE) {
-    ntiles = s_build_list(s_list, w, lane, t_lo, ntiles, (Nc + SQ_BC - 1) / SQ_BC, [&](int t) {
-      int bits = 0;
+      if (a.causal) {
+        const long long last = a.q_off + min(qb * SQ_BR + SQ_BR, a.Nq) - 1 - f_koff;
+        if (last < 0) hi = lo;
+        else if (last / SQ_BC + 1 < hi) hi = (int)(last / SQ_BC) + 1;
+      }
+      if (hi > lo) {
+        const unsigned kpitch = (unsigned)C.ks_r * 2u;           // bytes between key rows
+        const size_t base = C.kv_base(kvhead, a.lay.kv_heads);
+        krs = make_rsrc((const bf16*)C.K + base, s_span(f_Nc, kpitch, d));
+        vrs = make_rsrc((const bf16*)C.V + base, s_span(f_Nc, kpitch, d));
+        ktile = kpitch * SQ_BC;
 #pragma unroll
-      for (int ww = 0; ww < 4; ww++) {
-        const int row0 = qb * SQ_BR + ww * 32;
-        if (row0 < a.Nq && (a.bmask + (size_t)head * a.bhstride)[(size_t)(row0 / a.bsize) * a.bpitch + (t * SQ_BC) / a.bsize] != 0) bits |= 1 << ww;
+        for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
+        if constexpr (SPARSE) {
+          const uint8_t* const bm = C.bmask + (size_t)head * C.bhstride;
+          hi = s_build_list(s_list, w, lane, lo, hi, [&](int t) {
+            int bits = 0;
+#pragma unroll
+            for (int ww = 0; ww < 4; ww++) {
+              const int row0 = qb * SQ_BR + ww * 32;
+              if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + (t * SQ_BC) / a.bsize] != 0) bits |= 1 << ww;
+            }
+            return bits;
+          });
+          lo = 0;
+        }
       }
-      return bits;
-    });
-  }
-  auto entry_at = [&](int j) __attribute__((always_inline)) {
-    if constexpr (SPARSE) return __builtin_amdgcn_readfirstlane(s_list[1 + j]);
-    else return j | (0xf << 20);
+      hi = max(hi, lo);
+      ft = lo + past;
+    }
+    f_tile = ft;
+    if constexpr (SPARSE) {
+      const int e = __builtin_amdgcn_readfirstlane(s_list[1 + ft]);
+      f_tile = e & 0xfffff;
+      f_bits = e >> 20;
+    }
+    return true;
   };
+  auto fetch = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int il = 0; il < NL; il++) {
+      dma_b128_to_lds(krs, lds0 + buf * SQ_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)f_tile * ktile) + goff[il]);
+      dma_b128_to_lds(vrs, lds0 + (2 + buf) * SQ_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)f_tile * ktile) + goff[il]);
+    }
+  };
+  bool have = advance(0);
+  if (!have && a.acc_dq && a.splits == 1) return;  // nothing visible: nothing to add
+  if (have) fetch(0);
 
+  // The accumulators start at the dQ that is there: scale is folded into the exponent below
+  // (dS^T comes out as scale * dS^T), so they hold dQ itself and a walk gives the same bits whether its
+  // chunks come in one launch or one by one.
   f32x16 dq[S_DB];
 #pragma unroll
   for (int db = 0; db < S_DB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
+  if (a.acc_dq && a.splits == 1 && ok) {
+    const float* const orow = a.dQ + srow * d;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(orow + db * 32 + 8 * q4 + 4 * h);
+#pragma unroll
+        for (int b = 0; b < 4; b++) dq[db][4 * q4 + b] = v[b];
+      }
+  }
 
-  if (ntiles > 0) {                                // (uniform over the workgroup)
+  if (have) {                                      // (uniform over the workgroup)
     bf16x8 qf[S_KS], gf[S_KS];
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) {
@@ -417,40 +553,26 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
       gf[ks] = s_load8(a.dO + qrow + ks * 16 + h * 8, there);
     }
     const float lv = ok ? a.lse[srow] : BURST_NEG_INF;
-    const float nlse2 = (lv == BURST_NEG_INF) ? BURST_NEG_INF : -lv * kLog2e;   // -inf: P = 0
+    // exponent offset: P scaled by `scale`; -inf: P = 0
+    const float nlse2 = (lv == BURST_NEG_INF) ? BURST_NEG_INF : __builtin_fmaf(-lv, kLog2e, a.log2_scale);
     const float Dv = ok ? a.D[srow] : 0.f;
     int kaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
     s_taddr(lane, taddr);
-    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch, d));
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, s_span(Nc, kpitch, d));
-    const int wu = __builtin_amdgcn_readfirstlane(w);
-    const unsigned lds0 = lds_addr(smem);
-    constexpr int NL = SQ_BC / S_RPL / 4;         // wave-wide loads per wavefront and tile
-    int goff[NL];
-#pragma unroll
-    for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, kpitch, d);
-    auto dma_tile = [&](int t, int buf) __attribute__((always_inline)) {
-#pragma unroll
-      for (int il = 0; il < NL; il++) {
-        dma_b128_to_lds(krs, lds0 + buf * SQ_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SQ_BC * kpitch) + goff[il]);
-        dma_b128_to_lds(vrs, lds0 + (2 + buf) * SQ_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SQ_BC * kpitch) + goff[il]);
-      }
-    };
     const long long wave_first_q = a.q_off + q0;
 
-    dma_tile(entry_at(0) & 0xfffff, 0);
-    for (int j = 0; j < ntiles; j++) {             // j = walk position, kt = tile
-      const int e = entry_at(j);
-      const int kt = e & 0xfffff;
-      const bool mine = ((e >> (20 + wu)) & 1) != 0;
+    for (int buf = 0; have; buf ^= 1) {
+      const int kt = f_tile, Nc = f_Nc;
+      const long long k_off = f_koff;
+      const bool mine = ((f_bits >> wu) & 1) != 0;
       __builtin_amdgcn_s_waitcnt(0x0070);
       __builtin_amdgcn_s_barrier();
-      if (j + 1 < ntiles) dma_tile(entry_at(j + 1) & 0xfffff, (j + 1) & 1);
+      have = advance(a.splits);
+      if (have) fetch(buf ^ 1);
       if (!mine) continue;                         // block flags hide the tile from this wavefront's rows
-      const char* kl = smem + (j & 1) * SQ_TILE;
-      const char* vl = smem + (2 + (j & 1)) * SQ_TILE;
+      const char* kl = smem + buf * SQ_TILE;
+      const char* vl = smem + (2 + buf) * SQ_TILE;
       // S^T = K Q^T, dP^T = V dO^T: register r = key kt*32 + 8*(r/4) + 4h + r%4
       f32x16 s, dp;
 #pragma unroll
@@ -496,18 +618,16 @@ burst_bwd_dq_d64_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   if (ok) {
-    float* orow = a.dQ + srow * d;
+    float* const orow = a.splits > 1 ? a.part + ((size_t)split * a.H * a.Nq + srow) * d : a.dQ + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
         if (S_PAD && db * 32 + 8 * q4 >= d) continue;
-        float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (a.acc_dq) v = *reinterpret_cast<f32x4*>(ptr);
+        f32x4 v;
 #pragma unroll
-        for (int b = 0; b < 4; b++) v[b] += a.scale * dq[db][4 * q4 + b];
-        *reinterpret_cast<f32x4*>(ptr) = v;
+        for (int b = 0; b < 4; b++) v[b] = dq[db][4 * q4 + b];
+        *reinterpret_cast<f32x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
       }
   }
 }
@@ -529,42 +649,47 @@ constexpr int SK_STAT = 4 * SK_TILE;              // per buffer: 32 x (-lse log2
 
 template <bool SPARSE>
 __global__ void __launch_bounds__(64 * SK_WAVES, SK_WAVES == 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
-burst_bwd_dkv_d64_kernel(BwdArgs a) {
+burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SK_TILE + 2 * 64 * 4];   // Q[2], dO[2], statistics[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
+  // the workgroups of all chunks, chunk after chunk
+  int ci = 0;
+  while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
+  const Chunk& C = a.ch[ci];
   int kvhead, kblk;
-  s_head_block(blockIdx.x, a.blocks_per_head, kvhead, kblk);
-  if (kvhead >= a.H) return;                       // a.H counts key/value heads here
+  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + SK_BC - 1) / SK_BC, kvhead, kblk)) return;   // a.H counts key/value heads here
+  const int Nc = C.Nc;
+  const long long k_off = C.k_off;
   const int key_wg = kblk * SK_BC, key0 = key_wg + w * 32;
-  const bf16* Kh = a.K + a.lay.kv_base(kvhead);
-  const bf16* Vh = a.V + a.lay.kv_base(kvhead);
+  const bf16* Kh = (const bf16*)C.K + C.kv_base(kvhead, a.lay.kv_heads);
+  const bf16* Vh = (const bf16*)C.V + C.kv_base(kvhead, a.lay.kv_heads);
   const unsigned qpitch = (unsigned)a.lay.qs_r * 2u;             // bytes between query rows
 
   // query tiles of one head to visit (causal: rows before the first key see nothing; window:
   // rows too far behind the last key neither), then the same range for every head of the group
   int t_end = (a.Nq + SK_BR - 1) / SK_BR, t_begin = 0;
   if (a.causal) {
-    long long first_row = a.k_off + key_wg - a.q_off;
+    long long first_row = k_off + key_wg - a.q_off;
     if (first_row > 0) t_begin = (int)min((long long)t_end, first_row / SK_BR);
   }
   if (a.window > 0) {
-    long long last_row = a.k_off + min(key_wg + SK_BC, a.Nc) - 1 + a.window - 1 - a.q_off;
+    long long last_row = k_off + min(key_wg + SK_BC, Nc) - 1 + a.window - 1 - a.q_off;
     t_end = last_row < 0 ? 0 : (int)min((long long)t_end, last_row / SK_BR + 1);
   }
   const int per_head = t_end > t_begin ? t_end - t_begin : 0;
   int nwalk = per_head * a.group;
   if constexpr (SPARSE) {                          // entries count tiles over all heads of the group
-    nwalk = s_build_list(s_list, w, lane, 0, nwalk, 0, [&](int n) {
+    nwalk = s_build_list(s_list, w, lane, 0, nwalk, [&](int n) {
       const int g = n / (per_head > 0 ? per_head : 1);
       const int t = t_begin + n % (per_head > 0 ? per_head : 1);
-      const uint8_t* mrow = a.bmask + (size_t)(kvhead * a.group + g) * a.bhstride + (size_t)((t * SK_BR) / a.bsize) * a.bpitch;
+      const uint8_t* mrow = C.bmask + (size_t)(kvhead * a.group + g) * C.bhstride + (size_t)((t * SK_BR) / a.bsize) * C.bpitch;
       int bits = 0;
 #pragma unroll
       for (int ww = 0; ww < SK_WAVES; ww++) {
         const int k0 = key_wg + ww * 32;
-        if (k0 < a.Nc && mrow[k0 / a.bsize] != 0) bits |= 1 << ww;
+        if (k0 < Nc && mrow[k0 / a.bsize] != 0) bits |= 1 << ww;
       }
       return bits;
     });
@@ -596,9 +721,9 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
     bf16x8 kf[S_KS], vf[S_KS];
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) {
-      const bool there = key0 + lr < a.Nc && (!S_PAD || ks * 16 + h * 8 < d);
-      kf[ks] = s_load8(Kh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, there);
-      vf[ks] = s_load8(Vh + (size_t)(key0 + lr) * a.lay.ks_r + ks * 16 + h * 8, there);
+      const bool there = key0 + lr < Nc && (!S_PAD || ks * 16 + h * 8 < d);
+      kf[ks] = s_load8(Kh + (size_t)(key0 + lr) * C.ks_r + ks * 16 + h * 8, there);
+      vf[ks] = s_load8(Vh + (size_t)(key0 + lr) * C.ks_r + ks * 16 + h * 8, there);
     }
     int qaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
@@ -639,7 +764,7 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
       if (tid < 32) stat[buf * 64 + tid] = (stat_x == BURST_NEG_INF) ? BURST_NEG_INF : -stat_x * kLog2e;   // -inf: P = 0
       else if (tid < 64) stat[buf * 64 + tid] = stat_x;
     };
-    const long long wave_first_k = a.k_off + key0, wave_last_k = wave_first_k + 31;
+    const long long wave_first_k = k_off + key0, wave_last_k = wave_first_k + 31;
     const long long kpos = wave_first_k + lr;
 
     fetch(0, 0);
@@ -741,12 +866,12 @@ burst_bwd_dkv_d64_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   // lane = d column, registers = keys
-  float* dKh = a.dK + (size_t)kvhead * a.Nc * d;
-  float* dVh = a.dV + (size_t)kvhead * a.Nc * d;
+  float* dKh = (float*)C.dK + (size_t)kvhead * Nc * d;
+  float* dVh = (float*)C.dV + (size_t)kvhead * Nc * d;
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-    if (key < a.Nc) {
+    if (key < Nc) {
 #pragma unroll
       for (int db = 0; db < S_DB; db++) {
         if (S_PAD && db * 32 + lr >= d) continue;
@@ -772,72 +897,74 @@ static int allow_list(K kernel, DeviceOnce& once) {
                    hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
 }
+template <typename A, typename K>
+static int launch_plain(K dense, K sparse, DeviceOnce& once, A& a, long long nb, long long entries, int threads, hipStream_t stream) {
+  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  if (nb == 0) return BURST_OK;
+  if (a.ch[0].bmask != nullptr) {
+    if (entries > S_MAX_LIST) return BURST_ERR_SHAPE;
+    if (int st = allow_list(sparse, once); st != BURST_OK) return st;
+    BURST_LAUNCH(sparse, dim3((unsigned)nb), dim3(threads), ((unsigned)entries + 4) * 4, stream, a);
+  } else {
+    BURST_LAUNCH(dense, dim3((unsigned)nb), dim3(threads), 0, stream, a);
+  }
+  return launch_status();
+}
 
-int launch_fwd(const KParams& p, const void* Q, const void* K, const void* V,
-                   float* O_acc, float* m, float* l, hipStream_t stream) {
+// n <= kMaxChunks chunks, all of them with block flags or none.
+int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   FwdArgsLite a;
-  a.Q = (const bf16*)Q; a.K = (const bf16*)K; a.V = (const bf16*)V;
-  a.O_acc = O_acc; a.m = m; a.l = l;
-  a.Nq = p.Nq; a.Nc = p.Nc; a.H = p.B * p.H; a.group = p.group;
+  a.Q = (const bf16*)io.Q;
+  a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = (bf16*)io.O_out; a.lse = io.lse;
+  a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
+  a.fresh = io.fresh || a.splits > 1;
+  a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
   a.causal = p.causal; a.c = p.scale * kLog2e;
-  a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
-  a.bmask = p.bmask; a.bsize = p.bsize; a.bpitch = p.bpitch; a.bhstride = p.bhstride;
-  a.lay = p.lay;
-  a.d = p.d;
+  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
+  a.lay = p.lay; a.d = p.d; a.n = n;
   a.blocks_per_head = (p.Nq + SF_BR - 1) / SF_BR;
-  const long long nb = (long long)((a.H + 7) / 8 * 8) * a.blocks_per_head;
-  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  if (a.bmask != nullptr) {
-    const int entries = (p.Nc + SF_BC - 1) / SF_BC;
-    if (entries > S_MAX_LIST) return BURST_ERR_SHAPE;
-    static DeviceOnce done;
-    if (int st = allow_list(burst_fwd_d64_kernel<true>, done); st != BURST_OK) return st;
-    BURST_LAUNCH(burst_fwd_d64_kernel<true>, dim3((unsigned)nb), dim3(256), (entries + 4) * 4, stream, a);
-  } else {
-    BURST_LAUNCH(burst_fwd_d64_kernel<false>, dim3((unsigned)nb), dim3(256), 0, stream, a);
-  }
-  return launch_status();
+  int longest = 0;
+  for (int i = 0; i < n; i++) { a.ch[i] = ch[i]; if (ch[i].Nc > longest) longest = ch[i].Nc; }
+  static DeviceOnce done;
+  return launch_plain(burst_fwd_d64_kernel<false>, burst_fwd_d64_kernel<true>, done, a,
+                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SF_BC - 1) / SF_BC, 256, stream);
 }
 
-int launch_bwd_dq(const KParams& p, const void* Q, const void* K, const void* V,
-                      const void* dO, const float* lse, const float* D, float* dQ, int acc_dq,
-                      hipStream_t stream) {
-  if (p.Nq <= 0) return BURST_OK;
-  BwdArgs a = make_bwd_args(p, Q, K, V, dO, lse, D, dQ, nullptr, nullptr, acc_dq, 0);
+static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
+  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ;
+  a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
+  a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
+  a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale; a.log2_scale = log2f(p.scale);
+  a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
+  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
+  a.lay = p.lay; a.d = p.d; a.n = n;
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
+}
+
+int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
+  BwdArgsLite a;
+  bwd_args(a, p, io, ch, n);
   a.blocks_per_head = (p.Nq + SQ_BR - 1) / SQ_BR;
-  const long long nb = (long long)((a.H + 7) / 8 * 8) * a.blocks_per_head;
-  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  if (a.bmask != nullptr) {
-    const int entries = (p.Nc + SQ_BC - 1) / SQ_BC;
-    if (entries > S_MAX_LIST) return BURST_ERR_SHAPE;
-    static DeviceOnce done;
-    if (int st = allow_list(burst_bwd_dq_d64_kernel<true>, done); st != BURST_OK) return st;
-    BURST_LAUNCH(burst_bwd_dq_d64_kernel<true>, dim3((unsigned)nb), dim3(256), (entries + 4) * 4, stream, a);
-  } else {
-    BURST_LAUNCH(burst_bwd_dq_d64_kernel<false>, dim3((unsigned)nb), dim3(256), 0, stream, a);
-  }
-  return launch_status();
+  int longest = 0;
+  for (int i = 0; i < n; i++) if (ch[i].Nc > longest) longest = ch[i].Nc;
+  static DeviceOnce done;
+  return launch_plain(burst_bwd_dq_d64_kernel<false>, burst_bwd_dq_d64_kernel<true>, done, a,
+                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SQ_BC - 1) / SQ_BC, 256, stream);
 }
 
-int launch_bwd_dkv(const KParams& p, const void* Q, const void* K, const void* V,
-                       const void* dO, const float* lse, const float* D, float* dK, float* dV,
-                       int acc_dkv, hipStream_t stream) {
-  if (p.Nc <= 0) return BURST_OK;
-  BwdArgs a = make_bwd_args(p, Q, K, V, dO, lse, D, nullptr, dK, dV, 0, acc_dkv);
+int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
+  BwdArgsLite a;
+  bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
-  a.blocks_per_head = (p.Nc + SK_BC - 1) / SK_BC;
-  const long long nb = (long long)((a.H + 7) / 8 * 8) * a.blocks_per_head;
-  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  if (a.bmask != nullptr) {
-    const long long entries = (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR);
-    if (entries > S_MAX_LIST) return BURST_ERR_SHAPE;
-    static DeviceOnce done;
-    if (int st = allow_list(burst_bwd_dkv_d64_kernel<true>, done); st != BURST_OK) return st;
-    BURST_LAUNCH(burst_bwd_dkv_d64_kernel<true>, dim3((unsigned)nb), dim3(64 * SK_WAVES), ((int)entries + 4) * 4, stream, a);
-  } else {
-    BURST_LAUNCH(burst_bwd_dkv_d64_kernel<false>, dim3((unsigned)nb), dim3(64 * SK_WAVES), 0, stream, a);
+  long long nb = 0;
+  for (int i = 0; i < n; i++) {
+    a.ch[i].first_block = (int)nb;
+    nb += grid_blocks(a.H, (ch[i].Nc + SK_BC - 1) / SK_BC);
+    if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
   }
-  return launch_status();
+  static DeviceOnce done;
+  return launch_plain(burst_bwd_dkv_d64_kernel<false>, burst_bwd_dkv_d64_kernel<true>, done, a, nb,
+                      (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
 }
 
 }  // namespace BURST_SMALL_NS

@@ -26,6 +26,7 @@ class RingWalk:
         self.O = torch.empty_strided(Q.shape, Q.stride(), device=dev, dtype=Q.dtype)   # O and dO lie in memory like Q
         self.lse = torch.empty_like(self.m)
         self.D = torch.empty_like(self.m)
+        self._workspace = None
 
     def params(self, Nc, k_off, mask=None, K_c=None):
         """K_c: the chunk the call is about (its strides go into the parameter block; Q's always do)."""
@@ -46,29 +47,56 @@ class RingWalk:
 
     def forward(self, Ks, Vs, k_offs, order=None, masks=None):
         """masks: optional list of per-chunk block masks (uint8 device tensors, see binding.params)."""
-        self.init()
-        for j in (range(len(Ks)) if order is None else order):
-            self.step(Ks[j], Vs[j], k_offs[j], None if masks is None else masks[j])
-        return self.finalize()
+        if type(self).step is not RingWalk.step:     # a subclass with a chunk step of its own
+            self.init()
+            for j in (range(len(Ks)) if order is None else order):
+                self.step(Ks[j], Vs[j], k_offs[j], None if masks is None else masks[j])
+            return self.finalize()
+        if order is not None:
+            pick = lambda x: None if x is None else [x[j] for j in order]
+            Ks, Vs, k_offs, masks = pick(Ks), pick(Vs), pick(k_offs), pick(masks)
+        p = self._walk_params()
+        chunks = B.chunk_array(Ks, Vs, k_offs, masks, p)
+        B.burst_walk_fwd(self.Q, chunks, self.O_acc, self.m, self.l, self.O, self.lse, p, self._scratch(chunks, p))
+        return self.O, self.lse
+
+    def _walk_params(self):
+        p = self.params(0, 0)
+        p.block = self.block
+        return p
+
+    def _scratch(self, chunks, p):
+        """Workspace of a walk, kept by the walk (None: these sizes use none)."""
+        need = B.burst_walk_workspace_bytes(chunks, p)
+        if need == 0:
+            return None
+        if self._workspace is None or self._workspace.numel() < need:
+            self._workspace = torch.empty(need, device=self.Q.device, dtype=torch.uint8)
+        return self._workspace
 
     # ---- backward (Alg. 2), query slice pinned, chunks walked
     def prepare(self, dO):
         B.burst_bwd_prepare(self.O, dO, self.D, self.params(0, 0))
 
     def backward(self, Ks, Vs, k_offs, dO, dQ=None, dKs=None, dVs=None, use_D=True, masks=None):
+        """dQ given: the gradient is added to it.  use_D = False: every chunk's call computes D for itself."""
         dev = self.Q.device
+        accumulate = dQ is not None
         if dQ is None:
-            dQ = torch.zeros((self.Bt, self.H, self.Nq, self.d), device=dev, dtype=torch.float32)
+            dQ = (torch.empty if use_D else torch.zeros)((self.Bt, self.H, self.Nq, self.d), device=dev, dtype=torch.float32)
         if dKs is None:
             dKs = [torch.empty(K.shape, device=dev, dtype=torch.float32) for K in Ks]
             dVs = [torch.empty(V.shape, device=dev, dtype=torch.float32) for V in Vs]
         if dO.stride() != self.Q.stride():         # dO and O lie in memory like Q
             dO = torch.empty_strided(self.Q.shape, self.Q.stride(), device=dev, dtype=self.Q.dtype).copy_(dO)
         if use_D:
-            self.prepare(dO)
+            p = self._walk_params()
+            chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs)
+            B.burst_walk_bwd(self.Q, chunks, self.O, dO, self.lse, self.D, dQ, p, accumulate_dq=accumulate,
+                             accumulate_dkv=False, workspace=self._scratch(chunks, p))
+            return dQ, dKs, dVs
         for j in range(len(Ks)):
-            B.burst_local_bwd(self.Q, Ks[j], Vs[j], self.O, dO, self.lse, self.D if use_D else None,
-                              dQ, dKs[j], dVs[j],
+            B.burst_local_bwd(self.Q, Ks[j], Vs[j], self.O, dO, self.lse, None, dQ, dKs[j], dVs[j],
                               self.params(Ks[j].shape[2], k_offs[j], None if masks is None else masks[j], Ks[j]),
                               accumulate_dq=True, accumulate_dkv=False)
         return dQ, dKs, dVs

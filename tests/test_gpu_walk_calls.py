@@ -1,0 +1,85 @@
+"""The whole-walk entry points (one call for all chunks) against the same walk chunk by chunk: O, lse, the
+state and every gradient bit for bit where the kernels are the same, for each kernel family, with empty
+and invisible chunks in between, chunks of different pitch, and more chunks than one launch takes; and
+against the oracle."""
+import pytest
+import torch
+
+from paper_2403_09347_amd import binding as B
+from paper_2403_09347_amd import workloads
+from paper_2403_09347_amd.harness import RingWalk
+from gpu_util import compare_all_heads
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+CASES = [
+    ("bf16", dict(B=1, H=3, d=64, Nq=130, chunk_rows=[64, 1, 200, 33])),
+    ("bf16", dict(B=1, H=2, d=128, Nq=257, chunk_rows=[100, 64, 190], causal=True, q_off=90)),
+    ("bf16", dict(B=2, H=2, d=80, Nq=65, chunk_rows=[30] * 5, causal=True, q_off=60, window=50)),
+    ("bf16", dict(B=1, H=2, d=128, Nq=300, chunk_rows=[200, 128, 70], block=64, pattern="random", density=0.3)),
+    ("bf16", dict(B=1, H=4, kv_heads=2, d=64, Nq=100, chunk_rows=[90, 70], block=64, pattern="random", density=0.5,
+                  layout="seq")),
+    ("bf16", dict(B=1, H=4, kv_heads=2, d=128, Nq=100, chunk_rows=[90, 70], causal=True, q_off=60, layout="packed")),
+    ("bf16", dict(B=1, H=2, d=64, Nq=70, chunk_rows=[20] * 37, causal=True, q_off=700)),
+    ("f32", dict(B=1, H=2, d=64, Nq=70, chunk_rows=[40, 33, 64])),
+]
+
+
+def chunk_by_chunk(case, walk):
+    walk.init()
+    masks = case.get("masks") or [None] * len(case["K"])
+    for K, V, off, m in zip(case["K"], case["V"], case["k_offs"], masks):
+        walk.step(K, V, off, m)
+    O, lse = walk.finalize()
+    walk.prepare(case["dO"])
+    dQ = torch.zeros(walk.Q.shape, device=DEV)
+    dKs, dVs = [torch.empty(k.shape, device=DEV) for k in case["K"]], [torch.empty(k.shape, device=DEV) for k in case["K"]]
+    for j, (K, V) in enumerate(zip(case["K"], case["V"])):
+        B.burst_local_bwd(walk.Q, K, V, walk.O, case["dO"], lse, walk.D, dQ, dKs[j], dVs[j],
+                          walk.params(K.shape[2], case["k_offs"][j], masks[j], K), accumulate_dq=True, accumulate_dkv=False)
+    return [t.clone() for t in (O, lse, walk.O_acc, walk.m, walk.l, dQ)], dKs, dVs
+
+
+@pytest.mark.parametrize("family", [0, 1, 2])
+@pytest.mark.parametrize("dtype,spec", CASES, ids=lambda v: v if isinstance(v, str) else "-".join(f"{k}{x}" for k, x in v.items() if k != "chunk_rows"))
+def test_walk_calls_equal_the_walk_chunk_by_chunk(dtype, spec, family):
+    if family and spec["d"] != 128:
+        pytest.skip("the kernel families differ at d = 128 only")
+    B.burst_set_kernel_family(family)
+    try:
+        case = workloads.make_case(dtype=dtype, seed=97, device=DEV, **spec)
+        mk = lambda: RingWalk(case["Q"], case["scale"], case["causal"], case["q_off"], case["window"], case.get("block", 0),
+                              case.get("kv_heads", 0))
+        want, dKs0, dVs0 = chunk_by_chunk(case, mk())
+        walk = mk()
+        for t in (walk.O_acc, walk.m, walk.l, walk.O, walk.lse, walk.D):
+            t.fill_(float("nan"))                   # nothing of the buffers' contents may get into a fresh walk
+        O, lse = walk.forward(case["K"], case["V"], case["k_offs"], masks=case.get("masks"))
+        dQ, dKs, dVs = walk.backward(case["K"], case["V"], case["k_offs"], case["dO"], masks=case.get("masks"))
+        torch.cuda.synchronize()
+        if dtype == "bf16":
+            for name, a, b in zip(("O", "lse", "O_acc", "m", "l", "dQ"), (O, lse, walk.O_acc, walk.m, walk.l, dQ), want):
+                assert torch.equal(a, b), name
+            for a, b in zip(dKs + dVs, dKs0 + dVs0):
+                assert torch.equal(a, b)
+        compare_all_heads(case, dtype, O, lse, dQ, dKs, dVs)
+    finally:
+        B.burst_set_kernel_family(0)
+
+
+def test_walk_calls_without_a_visible_or_any_chunk():
+    case = workloads.make_case(B=1, H=2, d=64, Nq=70, chunk_rows=[40, 33], dtype="bf16", seed=3, device=DEV, causal=True,
+                               q_off=0, k_offs=[1000, 2000])
+    walk = RingWalk(case["Q"], case["scale"], True, 0)
+    for Ks, Vs, offs in ((case["K"], case["V"], case["k_offs"]), ([], [], [])):
+        for t in (walk.O_acc, walk.m, walk.l, walk.O, walk.lse):
+            t.fill_(3.0)
+        O, lse = walk.forward(Ks, Vs, offs)
+        dQ, dKs, dVs = walk.backward(Ks, Vs, offs, case["dO"])
+        kept = torch.full_like(dQ, 2.0)
+        walk.backward(Ks, Vs, offs, case["dO"], dQ=kept)
+        torch.cuda.synchronize()
+        assert torch.all(O == 0) and torch.all(torch.isneginf(lse)) and torch.all(walk.O_acc == 0)
+        assert torch.all(walk.l == 0) and torch.all(torch.isneginf(walk.m)) and torch.all(dQ == 0) and torch.all(kept == 2.0)
+        assert all(torch.all(g == 0) for g in dKs + dVs)
