@@ -1,5 +1,6 @@
 // C ABI (see include/burst.h): argument validation and dispatch to the kernels.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -367,6 +368,35 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
   return BURST_OK;
 }
 
+// Into how many key ranges a walk of the plain kernels is split (1: not at all).  Their workgroups hold
+// 128 rows and two share a CU: fewer than 512 leave the chip idle, fewer than 257 leave a second
+// workgroup's place on every CU.  Ranges shorter than 8 tiles would spend their time on the partial
+// states, and up to 20 tiles in all there is little to win (8 x 384 rows, forward: 512 keys 19.5 / 20.1 in
+// 2; 1024 keys 28 / 21; 1536 keys 36 / 22 in 3) and a walk keeps the bits it has chunk by chunk.  Forward, us, without / with the split this rule picks, in brackets one half or twice as many:
+// 32 heads x 40 rows x 32K keys 597 / 116 in 16 (8: 120, 24: 134); 32 x 512 x 8K causal 168 / 95 in 4
+// (2: 106, 8: 108); 8 x 100 x 4K, d = 64, 63 / 24 in 8 (4: 28, 16: 22); 8 x 1024 x 4K 85 / 38 in 8
+// (4: 39, 16: 52); backward (dQ) 32 x 512 x 8K 664 / 585, 8 x 1024 x 4K 257 / 191.
+int walk_splits(const std::vector<WalkChunk>& w) {
+  if (w.empty() || w.size() > (size_t)burst::kMaxChunks) return 1;
+  const Kernels f = fwd_kernels(&w[0].p, w[0].k);
+  if (!f.fused()) return 1;
+  const KParams& k = w[0].k;
+  const long long blocks = (long long)k.B * k.H * ((k.Nq + 127) / 128);
+  long long tiles = 0;                             // of 64 keys, that the last rows see
+  for (const WalkChunk& x : w) {
+    if (x.p.block_mask != nullptr || !(fwd_kernels(&x.p, x.k) == f)) return 1;
+    long long lo = 0, hi = x.c.Nc;
+    if (k.causal) hi = std::min(hi, k.q_off + k.Nq - x.c.k_off);
+    if (k.window > 0) lo = std::max(lo, k.q_off + k.Nq - 128 - k.window + 1 - x.c.k_off);
+    if (hi > lo) tiles += (hi - lo + 63) / 64;
+  }
+  const long long s = std::min(512 / blocks, tiles / 8);
+  return s < 2 || tiles < 20 ? 1 : (int)s;
+}
+size_t split_bytes(const KParams& k, int splits) {
+  return splits > 1 ? (size_t)splits * k.B * k.H * k.Nq * ((size_t)k.d + 2) * sizeof(float) : 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -601,7 +631,9 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
 }
 
 size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p) {
-  return 0;
+  std::vector<WalkChunk> w;
+  if (walk_chunks(chunks, n_chunks, p, false, w) != BURST_OK || w.empty()) return 0;
+  return split_bytes(w[0].k, walk_splits(w));
 }
 
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
@@ -622,6 +654,17 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
   if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  int splits = walk_splits(w);
+  if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
+  if (splits > 1) {
+    const FwdIo io = {Q, O_acc, m, l, O_out, lse, 1, (float*)workspace, splits};
+    return validated([&] {
+      const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
+        return fwd_launch(f, kc, p->dtype, io, c, n, s);
+      });
+      return e != BURST_OK ? e : burst::launch_merge_splits(k, io, s);
+    });
+  }
   return validated([&] {
     bool fresh = true, final = false;
     const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
@@ -665,6 +708,8 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  int splits = walk_splits(w);
+  if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
   return validated([&]() -> int {
     int e = BURST_OK;
     if (!have_q) {                                 // no rows: dK and dV are zero
@@ -677,12 +722,13 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     }
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s);
-    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, nullptr, 1};
+    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, (float*)workspace, splits};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       io.acc_dq = accumulate_dq != 0 || !first;
       return dq_launch(f, kc, p->dtype, io, c, n, s);
     });
     if (e != BURST_OK) return e;
+    if (splits > 1 && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
     return for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
       return dkv_launch(f, kc, p->dtype, io, c, n, s);
     });
