@@ -14,7 +14,7 @@ int launch_finalize(const KParams&, int, const float*, const float*, const float
 int launch_merge_state(const KParams&, float*, float*, float*, const float*, const float*, const float*, hipStream_t);
 int launch_bwd_prepare(const KParams&, int, const void*, const void*, float*, hipStream_t);
 int launch_zero_fill(float*, long long, hipStream_t);
-int launch_fwd_mfma(const KParams&, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
+int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_fwd_generic(const KParams&, int, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
 int launch_bwd_dq_mfma(const KParams&, const void*, const void*, const void*, const void*, const float*,
                        const float*, float*, int, hipStream_t);
@@ -274,23 +274,29 @@ struct Kernels {
   const PlainFamily* plain;
   bool hand;
   int key_waves;                                   // hand-scheduled dK/dV
-  bool fused() const { return plain != nullptr; }
-  bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves; }
+  int takes;                                       // most chunks of one launch
+  bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves && takes == o.takes; }
 };
-Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the same choice
-  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0};
-  if (use_plain128(p, k)) return {&kD128p, false, 0};
-  return {nullptr, use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows), 0};
+Kernels fwd_kernels(const burst_params* p, const KParams& k) {
+  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
+  if (use_plain128(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
+  const bool hand = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
+  return {nullptr, hand, 0, hand && p->block_mask == nullptr ? burst::kMaxChunks : 1};
+}
+Kernels dq_kernels(const burst_params* p, const KParams& k) {
+  Kernels f = fwd_kernels(p, k);
+  if (f.hand) f.takes = 1;
+  return f;
 }
 Kernels dkv_kernels(const burst_params* p, const KParams& k) {
-  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0};
-  if (use_plain128_dkv(p, k)) return {&kD128p, false, 0};
+  if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
+  if (use_plain128_dkv(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && dkv_mfma_ok(p, k);
-  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0};
+  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, 1};
 }
 int fwd_launch(const Kernels& f, const KParams& k, int dtype, const FwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->fwd(k, io, c, n, s);
-  if (f.hand) return burst::launch_fwd_mfma(k, io.Q, c->K, c->V, io.O_acc, io.m, io.l, s);
+  if (f.hand) return burst::launch_fwd_mfma(k, io, c, n, s);
   return burst::launch_fwd_generic(k, dtype, io.Q, c->K, c->V, io.O_acc, io.m, io.l, s);
 }
 int dq_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
@@ -337,8 +343,8 @@ int for_each_run(const std::vector<WalkChunk>& w, Choose choose, Launch launch) 
     Chunk run[burst::kMaxChunks];
     size_t m = 0;
     do { run[m] = w[i + m].c; m++; }
-    while (f.fused() && m < (size_t)burst::kMaxChunks && i + m < n && (w[i + m].c.bmask == nullptr) == (run[0].bmask == nullptr) &&
-           choose(&w[i + m].p, w[i + m].k) == f);
+    while (m < (size_t)f.takes && i + m < n && (w[i + m].c.bmask == nullptr) == (run[0].bmask == nullptr) &&
+           (!f.hand || w[i + m].c.ks_r == run[0].ks_r) && choose(&w[i + m].p, w[i + m].k) == f);
     const int st = launch(f, w[i].k, run, (int)m, i == 0, i + m == n);
     if (st != BURST_OK) return st;
     i += m;
@@ -379,7 +385,7 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
 int walk_splits(const std::vector<WalkChunk>& w) {
   if (w.empty() || w.size() > (size_t)burst::kMaxChunks) return 1;
   const Kernels f = fwd_kernels(&w[0].p, w[0].k);
-  if (!f.fused()) return 1;
+  if (f.plain == nullptr) return 1;
   const KParams& k = w[0].k;
   const long long blocks = (long long)k.B * k.H * ((k.Nq + 127) / 128);
   long long tiles = 0;                             // of 64 keys, that the last rows see
@@ -578,7 +584,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
     return BURST_OK;
   }
   // The kernels of this call: D (when it is not given), then the dQ half, then the dK/dV half.
-  const Kernels fq = fwd_kernels(p, k), fk = dkv_kernels(p, k);
+  const Kernels fq = dq_kernels(p, k), fk = dkv_kernels(p, k);
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
@@ -669,7 +675,7 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
     bool fresh = true, final = false;
     const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
       FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, fresh, nullptr, 1};
-      if (f.fused()) {
+      if (f.plain != nullptr || f.hand) {          // (the generic kernels want the state and leave it in memory)
         if (last) { io.O_out = O_out; io.lse = lse; final = true; }
       } else if (fresh) {
         io.fresh = 0;
@@ -723,7 +729,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, (float*)workspace, splits};
-    e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
+    e = for_each_run(w, dq_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       io.acc_dq = accumulate_dq != 0 || !first;
       return dq_launch(f, kc, p->dtype, io, c, n, s);
     });

@@ -16,8 +16,14 @@
 // registers) into two rings of three tiles each, two tiles ahead of their use (one barrier per
 // tile).  The running max is only raised when a row's new maximum exceeds it by more than 2^8
 // (P stays <= 2^8, exact in fp32/bf16 range), so the O rescale is rare.
-// The chunk-local (O_ij, m_ij, l_ij) is merged into the state in HBM in the epilogue
-// (Alg. 1: m_new = max, rescale, add).  No S or P tile ever leaves registers.
+// A launch takes several chunks: the state (O, m, l) is loaded once, stays in registers from chunk to
+// chunk and is stored once, and at the end of a walk the output is written with it.  With a launch per
+// chunk every workgroup drained its pipeline and moved its 128 KB of state both ways each time, all of
+// them at the same moment: 8 chunks of 4096 keys, 32 heads x 4096 rows: 2.18 ms; in one launch 1.84 ms
+// (1.20 PFLOP/s; what bounds it is the serial issue of matrix and vector instructions of the one wavefront
+// per SIMD, 64 MFMAs beside about 250 vector instructions a tile).  The test for masked tiles is two
+// comparisons of scalars set once per chunk: written out per tile it cost 3 %.
+// No S or P tile ever leaves registers.
 #include "burst_common.h"
 
 namespace burst {
@@ -31,19 +37,19 @@ constexpr int FWD_MAX_LIST = 8192;  // block-sparse calls: most key tiles of one
 constexpr int FWD_LIST_BYTES = (FWD_MAX_LIST + 8) * 4;
 
 struct FwdArgs {
-  const bf16* Q; const bf16* K; const bf16* V;
+  const bf16* Q;
   float* O_acc; float* m; float* l;
-  int Nq, Nc, H;
-  int causal;
+  bf16* O_out; float* lse;   // O_out != nullptr: final after this launch
+  int Nq, H, group;      // H counts batch x heads; query heads per key/value head
+  int causal, fresh;     // fresh: the state before the launch is the initial one
   float c;               // scale * log2(e)
-  long long q_off, k_off;
+  long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
   int q_blocks;          // ceil(Nq / FWD_BR)
-  const uint8_t* bmask;  // block flags [ceil(Nq / bsize)][bpitch], nullptr = none (paper Sec. 2.6)
-  int bsize, bpitch;     // bsize: a multiple of 64, so a wavefront's 64 rows and a key tile lie in one block
-  long long bhstride;    // bytes between the flag matrices of consecutive heads (0 = shared)
-  int group;             // query heads per key/value head (grouped-query attention; 1 = none)
-  Layout lay;            // strides of Q and of K, V
+  int bsize;             // block flags: edge, a multiple of 64, so a wavefront's 64 rows and a key tile lie in one block
+  int n;                 // chunks (with block flags: one)
+  Layout lay;            // strides of Q and O_out
+  Chunk ch[kMaxChunks];  // with one row pitch
 };
 
 
@@ -101,10 +107,17 @@ __device__ __forceinline__ void qk_tile(const char* kl, const int (&kaddr)[8], c
   }
 }
 
-// SPARSE: the call carries block flags.  The workgroup first writes the list of key tiles that at
-// least one of its wavefronts can see (tile index plus one bit per wavefront) into LDS and then
-// walks that list instead of 0, 1, 2, ...; a wavefront whose bit is clear hides the whole tile
-// in the masking path.  Entries past the end name a tile beyond the chunk: its DMA reads zeros
+// The visible key tiles of all chunks of the launch form one sequence.  Three positions in it are kept:
+// the tile being computed (its chunk's masks), the tile whose V and the one whose K are fetched, two and
+// three further on; the pipeline never drains between chunks.
+struct Pos {
+  int chunk, tile, left;                           // left: tiles of the chunk from this one on
+};
+
+// SPARSE: the call carries block flags (one chunk per launch).  The workgroup first writes the list of
+// key tiles that at least one of its wavefronts can see (tile index plus one bit per wavefront) into
+// LDS and then walks that list instead of 0, 1, 2, ...; a wavefront whose bit is clear hides the whole
+// tile in the masking path.  Entries past the end name a tile beyond the chunk: its DMA reads zeros
 // and the ragged-tail mask hides it.
 template <bool SPARSE>
 __global__ void __launch_bounds__(256, 1)
@@ -114,97 +127,91 @@ burst_fwd_mfma_kernel(FwdArgs a) {
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
 
-  // XCD-aware mapping: consecutive workgroup ids go round-robin to the 8 XCDs, so all
-  // query blocks of one head are given ids that are congruent mod 8 (same XCD, same L2).
-  // (a.H counts batch x heads; the id space is padded to a multiple of 8 heads.)
   int head, qb;
-  {
-    int bid = blockIdx.x;
-    int xcd = bid & 7, idx = bid >> 3;
-    int hx = idx / a.q_blocks;
-    qb = idx - hx * a.q_blocks;
-    // causal: the later a query block, the more key tiles it sees; the blocks of a head start
-    // in descending order so that the long ones do not end up in the last round
-    if (a.causal) qb = a.q_blocks - 1 - qb;
-    head = hx * 8 + xcd;
-    if (head >= a.H) return;                       // whole workgroup exits together
-  }
+  if (!locate_block(blockIdx.x, a.H, a.q_blocks, head, qb)) return;   // whole workgroup exits together
+  // causal: the later a query block, the more key tiles it sees; the blocks of a head start
+  // in descending order so that the long ones do not end up in the last round
+  if (a.causal) qb = a.q_blocks - 1 - qb;
+  const int kvhead = head / a.group;
 
   const int q0 = qb * FWD_BR + w * 64;             // first query row of this wave
   const bf16* Qh = a.Q + a.lay.q_base(head);
-  const bf16* Kh = a.K + a.lay.kv_base(head / a.group);
-  const bf16* Vh = a.V + a.lay.kv_base(head / a.group);
-  const unsigned kpitch = (unsigned)a.lay.ks_r * 2u;             // bytes between key rows
+  const unsigned kpitch = (unsigned)a.ch[0].ks_r * 2u;           // bytes between key rows
   const unsigned ktile = kpitch * FWD_BC;                        // ... between key tiles
 
-  // Sliding window: key tiles before the first one that the workgroup's first row can see are
-  // skipped by moving the start of the chunk (pointers, length, global offset) forward by whole
-  // tiles; everything below works on that shortened chunk.
-  int Nc = a.Nc;
-  long long k_off = a.k_off;
-  int t_lo = 0;                                    // SPARSE: first tile of the list (the chunk is not shifted)
-  if (a.window > 0) {
-    long long lo = a.q_off + (long long)qb * FWD_BR - a.window + 1 - a.k_off;   // first visible key index
-    if (lo >= a.Nc) return;                        // nothing visible: state unchanged
-    if (lo > 0) {
-      const int skip = (int)(lo / FWD_BC) * FWD_BC;
-      if constexpr (SPARSE) {
-        t_lo = skip / FWD_BC;
-      } else {
-        Kh += (size_t)skip * a.lay.ks_r; Vh += (size_t)skip * a.lay.ks_r;
-        Nc -= skip; k_off += skip;
-      }
+  // Key tiles of chunk c that some row of the workgroup sees: [lo, hi) (causal: up to the last one that
+  // the last row sees; window: from the first one that the first row sees).
+  auto tiles_of = [&](int c, int& lo, int& hi) {
+    const int Nc = a.ch[c].Nc;
+    const long long k_off = a.ch[c].k_off;
+    lo = 0; hi = (Nc + FWD_BC - 1) / FWD_BC;
+    if (a.window > 0) {
+      const long long first = a.q_off + (long long)qb * FWD_BR - a.window + 1 - k_off;
+      if (first >= Nc) lo = hi;
+      else if (first > 0) lo = (int)(first / FWD_BC);
     }
-  }
+    if (a.causal) {
+      const long long last = a.q_off + min(qb * FWD_BR + FWD_BR, a.Nq) - 1 - k_off;
+      if (last < 0) hi = lo;
+      else if (last / FWD_BC + 1 < hi) hi = (int)(last / FWD_BC) + 1;
+    }
+    if (hi < lo) hi = lo;
+  };
+  auto next_chunk = [&](Pos& p) {                  // to the first tile of the next chunk that has one
+    int lo = 0, hi = 0;
+    while (lo == hi && ++p.chunk < a.n) tiles_of(p.chunk, lo, hi);
+    p.tile = lo;
+    p.left = hi > lo ? hi - lo : 0x7fffffff;       // past the last chunk: stays there
+  };
+  auto kv_rsrc = [&](const Pos& p, bool v) {       // past the last chunk: everything reads as zero
+    if (p.chunk >= a.n) return make_rsrc(nullptr, 0);
+    const Chunk& C = a.ch[p.chunk];
+    return make_rsrc((const bf16*)(v ? C.V : C.K) + C.kv_base(kvhead, a.lay.kv_heads), (unsigned)(C.Nc - 1) * kpitch + 256u);
+  };
 
-  // Number of key tiles this workgroup must visit (causal: stop after the last tile that
-  // any of its rows can see).
-  int ntiles = (Nc + FWD_BC - 1) / FWD_BC;
-  const long long wg_last_q = a.q_off + min(qb * FWD_BR + FWD_BR, a.Nq) - 1;
-  if (a.causal) {
-    long long lim = wg_last_q - k_off;             // last visible key index in this chunk
-    if (lim < 0) return;                           // nothing visible: state unchanged
-    long long t = lim / FWD_BC + 1;
-    if (t < ntiles) ntiles = (int)t;
-  }
-  if (ntiles <= 0) return;
-
+  Pos at = {-1, 0, 0};
+  next_chunk(at);
   // SPARSE: the list of visible tiles, built by wavefront 0 (64 candidate tiles per round).
   // list[0] = number of entries, list[1 + j] = tile | (wavefront bits << 16), then 4 end entries.
   int* const list = reinterpret_cast<int*>(smem + 2 * FWD_NBUF * FWD_TILE_BYTES);
+  int entries = 0;
   if constexpr (SPARSE) {
-    const int end_tile = (Nc + FWD_BC - 1) / FWD_BC;             // a tile past the chunk
-    if (w == 0) {
-      const uint8_t* const bm = a.bmask + (size_t)head * a.bhstride;
-      int n = 0;
-      for (int base = t_lo; base < ntiles; base += 64) {
-        const int kt = base + lane;
-        int bits = 0;
-        if (kt < ntiles) {
-          const int col = (kt * FWD_BC) / a.bsize;
+    if (at.chunk < a.n) {
+      const Chunk& C = a.ch[0];
+      const int end_tile = (C.Nc + FWD_BC - 1) / FWD_BC;         // a tile past the chunk
+      if (w == 0) {
+        const uint8_t* const bm = C.bmask + (size_t)head * C.bhstride;
+        int n = 0;
+        for (int base = at.tile; base < at.tile + at.left; base += 64) {
+          const int kt = base + lane;
+          int bits = 0;
+          if (kt < at.tile + at.left) {
+            const int col = (kt * FWD_BC) / a.bsize;
 #pragma unroll
-          for (int ww = 0; ww < 4; ww++) {
-            const int row0 = qb * FWD_BR + ww * 64;
-            if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * a.bpitch + col] != 0) bits |= 1 << ww;
+            for (int ww = 0; ww < 4; ww++) {
+              const int row0 = qb * FWD_BR + ww * 64;
+              if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + col] != 0) bits |= 1 << ww;
+            }
           }
+          const unsigned long long bal = __builtin_amdgcn_ballot_w64(bits != 0);
+          if (bits != 0) {
+            const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+            list[1 + pos] = kt | (bits << 16);
+          }
+          n += __builtin_popcountll(bal);
         }
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(bits != 0);
-        if (bits != 0) {
-          const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-          list[1 + pos] = kt | (bits << 16);
-        }
-        n += __builtin_popcountll(bal);
+        if (lane < 4) list[1 + n + lane] = end_tile;
+        if (lane == 0) list[0] = n;
       }
-      if (lane < 4) list[1 + n + lane] = end_tile;
-      if (lane == 0) list[0] = n;
+      __syncthreads();
+      entries = __builtin_amdgcn_readfirstlane(list[0]);
     }
-    __syncthreads();
-    ntiles = __builtin_amdgcn_readfirstlane(list[0]);            // from here on: number of list entries
-    if (ntiles == 0) return;
   }
-  auto tile_at = [&](int j) __attribute__((always_inline)) {      // tile index of list entry j
-    if constexpr (SPARSE) return __builtin_amdgcn_readfirstlane(list[1 + j]) & 0xffff;
-    else return j;
+  const bool any = SPARSE ? entries > 0 : at.chunk < a.n;
+  // nothing visible: the state stays as it is, unless this launch has to produce it
+  if (!any && !a.fresh && a.O_out == nullptr) return;
+  auto tile_at = [&](int j) __attribute__((always_inline)) {      // SPARSE: tile index of list entry j
+    return __builtin_amdgcn_readfirstlane(list[1 + j]) & 0xffff;
   };
 
   // Q fragments (B operand): lane holds row lr of each 32-row block, 8 consecutive d.
@@ -222,15 +229,35 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     }
   }
 
-  f32x16 o[2][4];          // O^T accumulators: [row block][32-wide d block]
+  // The state: O^T accumulators [row block][32-wide d block], reference maximum (log2 units, see
+  // reference_of) and row sum over this lane's keys.
+  f32x16 o[2][4];
+  float m2[2] = {BURST_NEG_INF, BURST_NEG_INF};
+  float lsum[2] = {0.f, 0.f};
 #pragma unroll
   for (int rb = 0; rb < 2; rb++)
 #pragma unroll
     for (int db = 0; db < 4; db++)
 #pragma unroll
       for (int r = 0; r < 16; r++) o[rb][db][r] = 0.f;
-  float m2[2] = {BURST_NEG_INF, BURST_NEG_INF};   // reference max, log2 units, per row block
-  float lsum[2] = {0.f, 0.f};                     // running sum over this lane's keys only
+  if (!a.fresh) {
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++) {
+      const int row = q0 + rb * 32 + lr;
+      const size_t srow = (size_t)head * a.Nq + row;
+      if (row < a.Nq && (m2[rb] = reference_of(a.m[srow])) != BURST_NEG_INF) {   // (a row that has seen nothing may hold anything)
+        if (h == 0) lsum[rb] = a.l[srow];
+#pragma unroll
+        for (int db = 0; db < 4; db++)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; q4++) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(a.O_acc + srow * 128 + db * 32 + 8 * q4 + 4 * h);
+#pragma unroll
+            for (int b = 0; b < 4; b++) o[rb][db][4 * q4 + b] = v[b];
+          }
+      }
+    }
+  }
 
   // per-lane LDS byte offsets; tile-relative constants are added at the use site
   // K reads (128-bit): row = kb*32 + lr, granule = 2*ks + h
@@ -251,21 +278,28 @@ burst_fwd_mfma_kernel(FwdArgs a) {
 
   // ---- prologue: K tiles 0..2 and V tiles 0..1 into LDS, S of tile 0.
   // LDS: K ring = tiles 0..2 of the buffer, V ring = tiles 3..5; tile t lives in slot t % 3.
-  // Tiles past the end of the chunk read as zeros (buffer range check) and are never used.
-  const unsigned kbytes = Nc > 0 ? (unsigned)(Nc - 1) * kpitch + 256u : 0u;   // up to the end of the last row
-  const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, kbytes);
-  const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, kbytes);
+  // Tiles past the end of a chunk read as zeros (buffer range check) and are never used.
+  Pos kf = at, vf = at;                            // next K, V tile to fetch
+  __amdgpu_buffer_rsrc_t krs = kv_rsrc(kf, false), vrs = kv_rsrc(vf, true);
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const unsigned lds0 = lds_addr(smem);
   int goff[4];
   tile_dma_offsets(w, lane, kpitch, goff);
 #pragma unroll
   for (int t = 0; t < 3; t++) {
-    const int src = tile_at(t);
+    if constexpr (SPARSE) { if (any) kf.tile = vf.tile = tile_at(t); }
 #pragma unroll
     for (int il = 0; il < 4; il++) {
-      tile_dma(krs, lds0 + t * FWD_TILE_BYTES, wu, il, (int)(src * ktile) + goff[il]);
-      if (t < 2) tile_dma(vrs, lds0 + (3 + t) * FWD_TILE_BYTES, wu, il, (int)(src * ktile) + goff[il]);
+      tile_dma(krs, lds0 + t * FWD_TILE_BYTES, wu, il, (int)(kf.tile * ktile) + goff[il]);
+      if (t < 2) tile_dma(vrs, lds0 + (3 + t) * FWD_TILE_BYTES, wu, il, (int)(vf.tile * ktile) + goff[il]);
+    }
+    if constexpr (!SPARSE) {
+      kf.tile++;
+      if (--kf.left == 0) { next_chunk(kf); krs = kv_rsrc(kf, false); }
+      if (t < 2) {
+        vf.tile++;
+        if (--vf.left == 0) { next_chunk(vf); vrs = kv_rsrc(vf, true); }
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's DMA has landed
@@ -289,23 +323,40 @@ burst_fwd_mfma_kernel(FwdArgs a) {
   }
   __builtin_amdgcn_s_barrier();   // K tile 0 is consumed by every wavefront before its slot is refilled
 
-  const long long wave_first_q = a.q_off + q0;
-  const long long wave_last_q = wave_first_q + 63;
+  const long long wave_first_q = a.q_off + qb * FWD_BR + wu * 64;    // (scalar, as everything the masks' test needs)
   bf16x2 ones;
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
   constexpr int PF = 4;          // operand fragments are fetched PF MFMA pairs ahead
 
   // One tile: `sc` holds S^T of tile kt (unmasked), `sx` receives S^T of the next tile.
-  // jt = position of the tile in the walk (dense: jt = kt), slot = jt % 3 its LDS ring slot.
+  // SPARSE: jt = position of the tile in the list; slot: its LDS ring slot.
+  // Of the chunk being computed: length, offset, and the tiles without any mask, [plain_lo, plain_hi)
+  // (before the diagonal and the ragged tail, behind the far edge of the window).
+  int Nc = 0, plain_lo = 0, plain_hi = 0;
+  long long k_off = 0;
+  auto enter_chunk = [&]() {
+    Nc = a.ch[at.chunk].Nc; k_off = a.ch[at.chunk].k_off;
+    plain_lo = 0; plain_hi = Nc / FWD_BC;
+    if (a.causal) {                                // last key of the tile <= first row of the wavefront
+      const long long t = (wave_first_q - k_off + 1) >> 6;
+      if (t < plain_hi) plain_hi = t < 0 ? 0 : (int)t;
+    }
+    if (a.window > 0) {                            // first key of the tile > last row of the wavefront - window
+      const long long t = (wave_first_q + 63 - a.window + 1 - k_off + 63) >> 6;
+      if (t > 0) plain_lo = t > 0x7fffffff ? 0x7fffffff : (int)t;
+    }
+  };
+  static_assert(FWD_BC == 64, "the shifts above");
+  if (at.chunk < a.n) enter_chunk();
   auto step = [&](f32x16 (&sc)[2][2], f32x16 (&sx)[2][2], int jt, int slot) __attribute__((always_inline)) {
-    int kt = jt, kt2 = jt + 2, kt3 = jt + 3;       // this tile, and the tiles whose V / K are fetched now
+    int kt = at.tile;
     bool mine = true;                              // SPARSE: this wavefront's rows can see the tile
     if constexpr (SPARSE) {
       const int e = __builtin_amdgcn_readfirstlane(list[1 + jt]);
       kt = e & 0xffff;
       mine = ((e >> (16 + wu)) & 1) != 0;
-      kt2 = tile_at(jt + 2);
-      kt3 = tile_at(jt + 3);
+      vf.tile = tile_at(jt + 2);
+      kf.tile = tile_at(jt + 3);
     }
     const int slot1 = (slot == FWD_NBUF - 1) ? 0 : slot + 1;     // tile kt + 1
     const int slot2 = (slot1 == FWD_NBUF - 1) ? 0 : slot1 + 1;   // tile kt + 2
@@ -317,11 +368,8 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     bf16x8 kfq[PF + 1];
 #pragma unroll
     for (int pn = 0; pn < PF; pn++) kfq[pn] = lds_read_b128(kl_next, (pn & 1) * 32 * 256 + kaddr[pn >> 1]);
-    const long long tile_first_k = k_off + (long long)kt * FWD_BC;
     // ---- masking (diagonal tiles, ragged key tail): rare; redo the row maxima afterwards
-    const bool need_mask = (a.causal && tile_first_k + FWD_BC - 1 > wave_first_q) ||
-                           (a.window > 0 && tile_first_k < wave_last_q - a.window + 1) ||
-                           ((kt + 1) * FWD_BC > Nc) || !mine;
+    const bool need_mask = kt >= plain_hi || kt < plain_lo || !mine;
     if (need_mask) {
       raise = false;
 #pragma unroll
@@ -358,7 +406,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
       mfma_acc_fence(o);
 #pragma unroll
       for (int rb = 0; rb < 2; rb++) {
-        float m_new = fmaxf(m2[rb], mx[rb]);
+        float m_new = mx[rb] > m2[rb] ? reference_for(mx[rb]) : m2[rb];
         float ref = (m_new == BURST_NEG_INF) ? 0.f : m_new;
         float alpha = fast_exp2(m2[rb] - ref);                 // exp2(-inf) = 0 for a fresh row
         m2[rb] = m_new;
@@ -451,8 +499,8 @@ burst_fwd_mfma_kernel(FwdArgs a) {
       }
       if ((i & 3) == 1) {                          // 8 slots: one DMA of 4 tile rows each
         const int j = i >> 2;                      // 0..3 -> K of tile kt + 3, 4..7 -> V of tile kt + 2
-        if (j < 4) tile_dma(krs, k_dst, wu, j, (int)(kt3 * ktile) + goff[j]);
-        else tile_dma(vrs, v_dst, wu, j - 4, (int)(kt2 * ktile) + goff[j - 4]);
+        if (j < 4) tile_dma(krs, k_dst, wu, j, (int)(kf.tile * ktile) + goff[j]);
+        else tile_dma(vrs, v_dst, wu, j - 4, (int)(vf.tile * ktile) + goff[j - 4]);
       }
       {
         bf16x8 vf;
@@ -489,68 +537,100 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     __builtin_amdgcn_s_barrier();
   };
 
-  int slot = 0;
-  for (int kt = 0; kt < ntiles; kt += 2) {
-    step(sA, sB, kt, slot);
-    slot = (slot == FWD_NBUF - 1) ? 0 : slot + 1;
-    if (kt + 1 >= ntiles) break;
-    step(sB, sA, kt + 1, slot);
-    slot = (slot == FWD_NBUF - 1) ? 0 : slot + 1;
+  // After each tile: the three positions move on.  At a chunk's end the row sum is settled as a store of
+  // the state and a load by the next launch would do it, so that a walk gives the same bits whether its
+  // chunks come in one launch or one by one.  False: that was the last tile.
+  int jt = 0;
+  int run = min(at.left, min(kf.left, vf.left));   // tiles until one of the three reaches its chunk's end
+  auto moved_on = [&]() __attribute__((always_inline)) {
+    jt++;
+    if constexpr (SPARSE) return jt < entries;
+    at.tile++; kf.tile++; vf.tile++;
+    if (--run != 0) return true;
+    const int gone = min(at.left, min(kf.left, vf.left));
+    at.left -= gone; kf.left -= gone; vf.left -= gone;
+    if (kf.left == 0) { next_chunk(kf); krs = kv_rsrc(kf, false); }
+    if (vf.left == 0) { next_chunk(vf); vrs = kv_rsrc(vf, true); }
+    if (at.left == 0) {
+      next_chunk(at);
+      if (at.chunk >= a.n) return false;
+      enter_chunk();
+#pragma unroll
+      for (int rb = 0; rb < 2; rb++) {
+        const float both = sum_both_halves(lsum[rb]);
+        lsum[rb] = h == 0 ? both : 0.f;
+      }
+    }
+    run = min(at.left, min(kf.left, vf.left));
+    return true;
+  };
+  if (any) {
+    int slot = 0;
+    for (;;) {
+      step(sA, sB, jt, slot);
+      slot = (slot == FWD_NBUF - 1) ? 0 : slot + 1;
+      if (!moved_on()) break;
+      step(sB, sA, jt, slot);
+      slot = (slot == FWD_NBUF - 1) ? 0 : slot + 1;
+      if (!moved_on()) break;
+    }
+    mfma_acc_fence(o);       // (inside the block: behind the join the compiler may already move the accumulators)
   }
-
   __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): no DMA may outlive the loop
-  mfma_acc_fence(o);
-  // ---- epilogue: merge the chunk result into the state in HBM (Alg. 1 merge step)
-  float* Oh = a.O_acc + (size_t)head * a.Nq * 128;
-  float* mh = a.m + (size_t)head * a.Nq;
-  float* lh = a.l + (size_t)head * a.Nq;
+  // ---- epilogue: the state, and what is made of it at the end of a walk (Alg. 1, last two steps)
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {
-    int row = q0 + rb * 32 + lr;
-    float l_chunk = sum_both_halves(lsum[rb]);
-    if (row < a.Nq && m2[rb] != BURST_NEG_INF) {   // rows that saw no key keep their state bit for bit
-      float m_old2 = mh[row] * kLog2e;             // stored in natural-log units
-      float l_old = lh[row];
-      float m_new = fmaxf(m_old2, m2[rb]);
-      float fa = fast_exp2(m_old2 - m_new);        // weight of the stored state
-      float fb = fast_exp2(m2[rb] - m_new);        // weight of this chunk
-      float* orow = Oh + (size_t)row * 128;
+    const int row = q0 + rb * 32 + lr;
+    const float l_all = sum_both_halves(lsum[rb]);
+    if (row >= a.Nq) continue;
+    const size_t srow = (size_t)head * a.Nq + row;
+    // a row whose reference has not moved keeps its m bit for bit
+    float m_st = a.fresh ? BURST_NEG_INF : a.m[srow];
+    if (m2[rb] != reference_of(m_st)) m_st = m2[rb] * kLn2;
+    asm volatile("" : "+v"(m_st));                 // (m as the next launch would load it)
+    if (a.fresh || m2[rb] != BURST_NEG_INF) {      // rows that never saw a key keep their state
+      float* const orow = a.O_acc + srow * 128;
 #pragma unroll
       for (int db = 0; db < 4; db++)
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) {
-          float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
-          f32x4 old = *reinterpret_cast<f32x4*>(ptr);
-          f32x4 nw;
+          f32x4 v;
 #pragma unroll
-          for (int b = 0; b < 4; b++) {
-            float keep = (fa == 0.f) ? 0.f : old[b] * fa;   // a fresh state may hold anything
-            nw[b] = keep + fb * o[rb][db][4 * q4 + b];
-          }
-          *reinterpret_cast<f32x4*>(ptr) = nw;
+          for (int b = 0; b < 4; b++) v[b] = o[rb][db][4 * q4 + b];
+          *reinterpret_cast<f32x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
         }
-      if (h == 0) {
-        mh[row] = m_new * kLn2;
-        lh[row] = ((fa == 0.f) ? 0.f : fa * l_old) + fb * l_chunk;
-      }
+      if (h == 0) { a.m[srow] = m_st; a.l[srow] = l_all; }
+    }
+    if (a.O_out != nullptr) {
+      const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
+      bf16* const out = a.O_out + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
+#pragma unroll
+      for (int db = 0; db < 4; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          bf16x4 v;
+#pragma unroll
+          for (int b = 0; b < 4; b++) v[b] = (bf16)(l_all > 0.f ? o[rb][db][4 * q4 + b] * inv : 0.f);
+          *reinterpret_cast<bf16x4*>(out + db * 32 + 8 * q4 + 4 * h) = v;
+        }
+      if (h == 0) a.lse[srow] = l_all > 0.f ? m_st + __logf(l_all) : BURST_NEG_INF;
     }
   }
 }
 
-int launch_fwd_mfma(const KParams& p, const void* Q, const void* K, const void* V,
-                    float* O_acc, float* m, float* l, hipStream_t stream) {
+// n chunks of one row pitch (with block flags: one chunk).
+int launch_fwd_mfma(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   FwdArgs a;
-  a.Q = (const bf16*)Q; a.K = (const bf16*)K; a.V = (const bf16*)V;
-  a.O_acc = O_acc; a.m = m; a.l = l;
-  a.Nq = p.Nq; a.Nc = p.Nc; a.H = p.B * p.H;
-  a.causal = p.causal;
+  a.Q = (const bf16*)io.Q;
+  a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = (bf16*)io.O_out; a.lse = io.lse;
+  a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
+  a.causal = p.causal; a.fresh = io.fresh;
   a.c = p.scale * kLog2e;
-  a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
+  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.q_blocks = (p.Nq + FWD_BR - 1) / FWD_BR;
-  a.bmask = p.bmask; a.bsize = p.bsize; a.bpitch = p.bpitch; a.bhstride = p.bhstride; a.group = p.group;
-  a.lay = p.lay;
-  int heads8 = ((a.H + 7) / 8) * 8;                // pad the head count to a multiple of 8 ids
-  long long nblocks = (long long)heads8 * a.q_blocks;
+  a.n = n; a.lay = p.lay;
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
+  const long long nblocks = grid_blocks(a.H, a.q_blocks);
   if (nblocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
@@ -560,8 +640,8 @@ int launch_fwd_mfma(const KParams& p, const void* Q, const void* K, const void* 
                                2 * FWD_NBUF * FWD_TILE_BYTES + FWD_LIST_BYTES) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
-  if (a.bmask != nullptr) {
-    if ((p.Nc + FWD_BC - 1) / FWD_BC > FWD_MAX_LIST) return BURST_ERR_SHAPE;
+  if (a.ch[0].bmask != nullptr) {
+    if (n != 1 || (ch[0].Nc + FWD_BC - 1) / FWD_BC > FWD_MAX_LIST) return BURST_ERR_SHAPE;
     BURST_LAUNCH(burst_fwd_mfma_kernel<true>, dim3((unsigned)nblocks), dim3(256),
                        2 * FWD_NBUF * FWD_TILE_BYTES + FWD_LIST_BYTES, stream, a);
   } else {
