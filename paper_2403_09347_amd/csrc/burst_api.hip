@@ -16,8 +16,7 @@ int launch_bwd_prepare(const KParams&, int, const void*, const void*, float*, hi
 int launch_zero_fill(float*, long long, hipStream_t);
 int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_fwd_generic(const KParams&, int, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
-int launch_bwd_dq_mfma(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                       const float*, float*, int, hipStream_t);
+int launch_bwd_dq_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dkv_mfma(const KParams&, const void*, const void*, const void*, const void*, const float*,
                         const float*, float*, float*, int, hipStream_t, int key_waves);
 int launch_bwd_dq_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
@@ -277,16 +276,11 @@ struct Kernels {
   int takes;                                       // most chunks of one launch
   bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves && takes == o.takes; }
 };
-Kernels fwd_kernels(const burst_params* p, const KParams& k) {
+Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the same choice
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
   if (use_plain128(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
   return {nullptr, hand, 0, hand && p->block_mask == nullptr ? burst::kMaxChunks : 1};
-}
-Kernels dq_kernels(const burst_params* p, const KParams& k) {
-  Kernels f = fwd_kernels(p, k);
-  if (f.hand) f.takes = 1;
-  return f;
 }
 Kernels dkv_kernels(const burst_params* p, const KParams& k) {
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
@@ -301,7 +295,7 @@ int fwd_launch(const Kernels& f, const KParams& k, int dtype, const FwdIo& io, c
 }
 int dq_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->bwd_dq(k, io, c, n, s);
-  if (f.hand) return burst::launch_bwd_dq_mfma(k, io.Q, c->K, c->V, io.dO, io.lse, io.D, io.dQ, io.acc_dq, s);
+  if (f.hand) return burst::launch_bwd_dq_mfma(k, io, c, n, s);
   return burst::launch_bwd_dq_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, io.dQ, io.acc_dq, s);
 }
 int dkv_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
@@ -584,7 +578,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
     return BURST_OK;
   }
   // The kernels of this call: D (when it is not given), then the dQ half, then the dK/dV half.
-  const Kernels fq = dq_kernels(p, k), fk = dkv_kernels(p, k);
+  const Kernels fq = fwd_kernels(p, k), fk = dkv_kernels(p, k);
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
@@ -729,7 +723,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, (float*)workspace, splits};
-    e = for_each_run(w, dq_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
+    e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       io.acc_dq = accumulate_dq != 0 || !first;
       return dq_launch(f, kc, p->dtype, io, c, n, s);
     });

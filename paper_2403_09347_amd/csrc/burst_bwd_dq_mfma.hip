@@ -21,6 +21,11 @@
 //   3: dQ^T products of tile t-1 (its dS^T fragments were finished a step ago) + dS^T of tile t
 // Only the 16-register dS^T fragment sets exist twice; everything fits the register file
 // without shuttling accumulators through AGPRs.
+//
+// A launch takes several chunks (see the forward kernel): dQ stays in its accumulators from chunk to
+// chunk.  8 chunks of 4096 keys, 32 heads x 4096 rows: 2.74 ms with a launch and a load-add-store of
+// dQ per chunk, 2.45 ms in one launch (1.35 PFLOP/s of its own contractions).
+#include <cmath>
 #include "burst_bwd_common.h"
 
 namespace burst {
@@ -86,103 +91,127 @@ __device__ __forceinline__ void mfma_vgpr_fence(f32x16 (&acc)[2]) {
   asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[1]));
 }
 
-// MODE 0 compiles the sliding-window code away: this kernel uses every register of the file, and
-// the few values the window logic keeps alive would otherwise push others to scratch.  MODE 1
-// has it.  MODE 2 (the call carries block flags, paper Sec. 2.6) has it too and walks a list of
-// the key tiles that at least one wavefront of the workgroup can see, built in LDS at the start
+struct DqArgs {
+  const bf16* Q; const bf16* dO;
+  const float* lse; const float* D;
+  float* dQ;
+  int Nq, H, group;      // H counts batch x heads; query heads per key/value head
+  int causal, acc_dq;
+  float c, log2_scale;   // scale * log2(e), log2(scale)
+  long long q_off;
+  long long window;      // 0 = none; else keys at positions <= query position - window are hidden
+  int blocks_per_head;
+  int bsize;             // block flags: edge, a multiple of 64
+  int n;                 // chunks (with block flags: one)
+  Layout lay;            // strides of Q and dO
+  Chunk ch[kMaxChunks];  // with one row pitch
+};
+
+// The visible key tiles of all chunks of the launch form one sequence, as in the forward kernel; the
+// positions of the tile being computed and of the one being fetched, three further on, are kept.
+struct DqPos { int chunk, tile, left; };           // left: tiles of the chunk from this one on
+
+// SPARSE: the call carries block flags (paper Sec. 2.6; one chunk per launch).  The workgroup walks a
+// list of the key tiles that at least one of its wavefronts can see, built in LDS at the start
 // (tile index plus one bit per wavefront); a wavefront whose bit is clear hides the whole tile
 // in the masking path.  Entries past the end name a tile beyond the chunk: its DMA reads zeros
 // and the ragged-tail mask hides it.
-template <int MODE>
+template <bool SPARSE>
 __global__ void __launch_bounds__(256, 1)
-burst_bwd_dq_kernel(BwdArgs a) {
+burst_bwd_dq_kernel(DqArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr bool WINDOW = MODE != 0, SPARSE = MODE == 2;
-  const long long window = WINDOW ? a.window : 0;
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   int head, qb;
-  {
-    int bid = blockIdx.x;
-    int xcd = bid & 7, idx = bid >> 3;
-    int hx = idx / a.blocks_per_head;
-    qb = idx - hx * a.blocks_per_head;
-    if (a.causal) qb = a.blocks_per_head - 1 - qb;   // longest blocks of a head first (see the forward kernel)
-    head = hx * 8 + xcd;
-    if (head >= a.H) return;
-  }
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head, head, qb)) return;
+  if (a.causal) qb = a.blocks_per_head - 1 - qb;   // longest blocks of a head first (see the forward kernel)
+  const int kvhead = head / a.group;
   const int q0 = qb * DQ_BR + w * 64;
   const bf16* Qh = a.Q + a.lay.q_base(head);
   const bf16* Gh = a.dO + a.lay.q_base(head);
-  const bf16* Kh = a.K + a.lay.kv_base(head / a.group);
-  const bf16* Vh = a.V + a.lay.kv_base(head / a.group);
-  const unsigned kpitch = (unsigned)a.lay.ks_r * 2u;             // bytes between key rows
+  const unsigned kpitch = (unsigned)a.ch[0].ks_r * 2u;           // bytes between key rows
   const unsigned ktile = kpitch * DQ_BC;                         // ... between key tiles
   const float* lseh = a.lse + (size_t)head * a.Nq;
   const float* Dh = a.D + (size_t)head * a.Nq;
   float* dQh = a.dQ + (size_t)head * a.Nq * 128;
 
-  // Sliding window: key tiles before the first one that the workgroup's first row can see are
-  // skipped by moving the start of the chunk (pointers, length, global offset) forward by whole
-  // tiles; everything below works on that shortened chunk.
-  int Nc = a.Nc;
-  long long k_off = a.k_off;
-  int t_lo = 0;                                    // SPARSE: first tile of the list (the chunk is not shifted)
-  bool nothing = false;
-  if (window > 0) {
-    long long lo = a.q_off + (long long)qb * DQ_BR - window + 1 - a.k_off;   // first visible key index
-    if (lo >= a.Nc) nothing = true;                // nothing visible: contribution 0
-    else if (lo > 0) {
-      const int skip = (int)(lo / DQ_BC) * DQ_BC;
-      if constexpr (SPARSE) {
-        t_lo = skip / DQ_BC;
-      } else {
-        Kh += (size_t)skip * a.lay.ks_r; Vh += (size_t)skip * a.lay.ks_r;
-        Nc -= skip; k_off += skip;
-      }
+  auto tiles_of = [&](int c, int& lo, int& hi) {   // key tiles of chunk c that some row of the workgroup sees: [lo, hi)
+    const int Nc = a.ch[c].Nc;
+    const long long k_off = a.ch[c].k_off;
+    lo = 0; hi = (Nc + DQ_BC - 1) / DQ_BC;
+    if (a.window > 0) {
+      const long long first = a.q_off + (long long)qb * DQ_BR - a.window + 1 - k_off;
+      if (first >= Nc) lo = hi;
+      else if (first > 0) lo = (int)(first / DQ_BC);
     }
-  }
-  int ntiles = nothing ? 0 : (Nc + DQ_BC - 1) / DQ_BC;
-  if (a.causal) {
-    long long lim = a.q_off + min(qb * DQ_BR + DQ_BR, a.Nq) - 1 - k_off;
-    long long t = lim < 0 ? 0 : lim / DQ_BC + 1;
-    if (t < ntiles) ntiles = (int)t;
-  }
+    if (a.causal) {
+      const long long last = a.q_off + min(qb * DQ_BR + DQ_BR, a.Nq) - 1 - k_off;
+      if (last < 0) hi = lo;
+      else if (last / DQ_BC + 1 < hi) hi = (int)(last / DQ_BC) + 1;
+    }
+    if (hi < lo) hi = lo;
+  };
+  auto next_chunk = [&](DqPos& p) {                // to the first tile of the next chunk that has one
+    int lo = 0, hi = 0;
+    while (lo == hi && ++p.chunk < a.n) tiles_of(p.chunk, lo, hi);
+    p.tile = lo;
+    p.left = hi > lo ? hi - lo : 0x7fffffff;       // past the last chunk: stays there
+  };
+  auto kv_rsrc = [&](const DqPos& p, bool v) {     // past the last chunk: everything reads as zero
+    if (p.chunk >= a.n) return make_rsrc(nullptr, 0);
+    const Chunk& C = a.ch[p.chunk];
+    return make_rsrc((const bf16*)(v ? C.V : C.K) + C.kv_base(kvhead, a.lay.kv_heads), (unsigned)(C.Nc - 1) * kpitch + 256u);
+  };
+  DqPos at = {-1, 0, 0};
+  next_chunk(at);
   // SPARSE: the list of visible tiles, built by wavefront 0 (64 candidate tiles per round).
   // list[0] = number of entries, list[1 + j] = tile | (wavefront bits << 20), then 6 end entries.
   int* const list = reinterpret_cast<int*>(smem + DQ_LDS_BYTES);
+  int entries = 0;
   if constexpr (SPARSE) {
-    const int end_tile = (Nc + DQ_BC - 1) / DQ_BC;               // a tile past the chunk
-    if (w == 0) {
-      const uint8_t* const bm = a.bmask + (size_t)head * a.bhstride;
-      int n = 0;
-      for (int base = t_lo; base < ntiles; base += 64) {
-        const int kt = base + lane;
-        int bits = 0;
-        if (kt < ntiles) {
-          const int col = (kt * DQ_BC) / a.bsize;
+    if (at.chunk < a.n) {
+      const Chunk& C = a.ch[0];
+      const int end_tile = (C.Nc + DQ_BC - 1) / DQ_BC;           // a tile past the chunk
+      if (w == 0) {
+        const uint8_t* const bm = C.bmask + (size_t)head * C.bhstride;
+        int n = 0;
+        for (int base = at.tile; base < at.tile + at.left; base += 64) {
+          const int kt = base + lane;
+          int bits = 0;
+          if (kt < at.tile + at.left) {
+            const int col = (kt * DQ_BC) / a.bsize;
 #pragma unroll
-          for (int ww = 0; ww < 4; ww++) {
-            const int row0 = qb * DQ_BR + ww * 64;
-            if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * a.bpitch + col] != 0) bits |= 1 << ww;
+            for (int ww = 0; ww < 4; ww++) {
+              const int row0 = qb * DQ_BR + ww * 64;
+              if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + col] != 0) bits |= 1 << ww;
+            }
           }
+          const unsigned long long bal = __builtin_amdgcn_ballot_w64(bits != 0);
+          if (bits != 0) {
+            const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+            list[1 + pos] = kt | (bits << 20);
+          }
+          n += __builtin_popcountll(bal);
         }
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(bits != 0);
-        if (bits != 0) {
-          const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-          list[1 + pos] = kt | (bits << 20);
-        }
-        n += __builtin_popcountll(bal);
+        if (lane < 6) list[1 + n + lane] = end_tile;
+        if (lane == 0) list[0] = n;
       }
-      if (lane < 6) list[1 + n + lane] = end_tile;
-      if (lane == 0) list[0] = n;
+      __syncthreads();
+      entries = __builtin_amdgcn_readfirstlane(list[0]);
     }
-    __syncthreads();
-    ntiles = __builtin_amdgcn_readfirstlane(list[0]);            // from here on: number of list entries
   }
-  auto tile_at = [&](int j) __attribute__((always_inline)) {      // tile index of list entry j
-    if constexpr (SPARSE) return __builtin_amdgcn_readfirstlane(list[1 + j]) & 0xfffff;
-    else return j;
+  const bool any = SPARSE ? entries > 0 : at.chunk < a.n;
+  if (!any) {                                      // nothing visible: the contribution is zero
+    if (a.acc_dq) return;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    for (int i = tid; i < DQ_BR * 32; i += 256) {
+      const int row = qb * DQ_BR + (i >> 5);
+      if (row < a.Nq) *reinterpret_cast<f32x4*>(dQh + (size_t)row * 128 + (i & 31) * 4) = z;
+    }
+    return;
+  }
+  auto tile_at = [&](int j) __attribute__((always_inline)) {      // SPARSE: tile index of list entry j
+    return __builtin_amdgcn_readfirstlane(list[1 + j]) & 0xfffff;
   };
 
   f32x16 dq[2][4];         // dQ^T accumulators [row block][32-wide d block], pinned in AGPRs
@@ -192,8 +221,27 @@ burst_bwd_dq_kernel(BwdArgs a) {
     for (int db = 0; db < 4; db++)
 #pragma unroll
       for (int r = 0; r < 16; r++) dq[rb][db][r] = 0.f;
+  // The accumulators start at the dQ that is there: scale is folded into the exponents (dS^T comes out
+  // as scale * dS^T), so they hold dQ itself, and a walk gives the same bits whether its chunks come in
+  // one launch or one by one.
+  if (a.acc_dq) {
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++) {
+      const int row = q0 + rb * 32 + lr;
+      if (row < a.Nq) {
+#pragma unroll
+        for (int db = 0; db < 4; db++)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; q4++) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(dQh + (size_t)row * 128 + db * 32 + 8 * q4 + 4 * h);
+#pragma unroll
+            for (int b = 0; b < 4; b++) dq[rb][db][4 * q4 + b] = v[b];
+          }
+      }
+    }
+  }
 
-  if (ntiles > 0) {
+  {
     bf16x8 qf[2][8];       // Q fragments of the wavefront's rows (B operand of S^T), VGPRs
     bf16x8 gfr[2][8];      // dO fragments of the same rows (B operand of dP^T), AGPRs
     float nlse2[2];
@@ -204,7 +252,8 @@ burst_bwd_dq_kernel(BwdArgs a) {
       int row = q0 + rb * 32 + lr;
       bool ok = row < a.Nq;
       float lv = ok ? lseh[row] : BURST_NEG_INF;
-      nlse2[rb] = (lv == BURST_NEG_INF) ? BURST_NEG_INF : -lv * kLog2e;   // -inf => P = exp2(-inf) = 0
+      // exponent offset: P scaled by `scale`; -inf => P = exp2(-inf) = 0
+      nlse2[rb] = (lv == BURST_NEG_INF) ? BURST_NEG_INF : __builtin_fmaf(-lv, kLog2e, a.log2_scale);
       {
         const float nd = ok ? -Dh[row] : 0.f;
 #pragma unroll
@@ -232,9 +281,8 @@ burst_bwd_dq_kernel(BwdArgs a) {
           taddr[db][sx] = tile_off(8 * sx + 4 * h + (j16 >> 2), db * 4 + 2 * dh + ((j16 & 3) >> 1)) + (j16 & 1) * 8;
     }
     // DMA: a 32-key tile is 8 wave-loads of 4 rows; wavefront w issues loads 2w and 2w + 1
-    const unsigned kbytes = Nc > 0 ? (unsigned)(Nc - 1) * kpitch + 256u : 0u;   // up to the end of the last row
-    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, kbytes);
-    const __amdgpu_buffer_rsrc_t vrs = make_rsrc(Vh, kbytes);
+    DqPos kf = at;                                 // next tile to fetch
+    __amdgpu_buffer_rsrc_t krs = kv_rsrc(kf, false), vrs = kv_rsrc(kf, true);
     const int wu = __builtin_amdgcn_readfirstlane(w);
     const unsigned lds0 = lds_addr(smem);
     int goff[2];
@@ -249,11 +297,15 @@ burst_bwd_dq_kernel(BwdArgs a) {
     constexpr int VBASE = DQ_KSLOTS * DQ_TILE_BYTES;
 #pragma unroll
     for (int t = 0; t < 3; t++) {
-      const int src = tile_at(t);
+      if constexpr (SPARSE) kf.tile = tile_at(t);
 #pragma unroll
       for (int il = 0; il < 2; il++) {
-        dma_tile(krs, lds0 + t * DQ_TILE_BYTES, il, src);
-        dma_tile(vrs, lds0 + VBASE + t * DQ_TILE_BYTES, il, src);
+        dma_tile(krs, lds0 + t * DQ_TILE_BYTES, il, kf.tile);
+        dma_tile(vrs, lds0 + VBASE + t * DQ_TILE_BYTES, il, kf.tile);
+      }
+      if constexpr (!SPARSE) {
+        kf.tile++;
+        if (--kf.left == 0) { next_chunk(kf); krs = kv_rsrc(kf, false); vrs = kv_rsrc(kf, true); }
       }
     }
     {
@@ -265,7 +317,28 @@ burst_bwd_dq_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0): this wavefront's DMA and stores are done
     __builtin_amdgcn_s_barrier();
 
-    const long long wave_first_q = a.q_off + q0;
+    const long long wave_first_q = a.q_off + qb * DQ_BR + wu * 64;   // (scalar, as everything the masks' test needs)
+    // Of the chunk being computed: length, offset, and the tiles without any mask, [plain_lo, plain_hi)
+    // (before the diagonal and the ragged tail, behind the far edge of the window).  Past the last
+    // chunk: no tile is.
+    int Nc = 0, plain_lo = 0, plain_hi = 0;
+    long long k_off = 0;
+    auto enter_chunk = [&]() {
+      plain_lo = 0; plain_hi = 0; Nc = 0;
+      if (at.chunk >= a.n) return;
+      Nc = a.ch[at.chunk].Nc; k_off = a.ch[at.chunk].k_off;
+      plain_hi = Nc / DQ_BC;
+      if (a.causal) {                              // last key of the tile <= first row of the wavefront
+        const long long t = (wave_first_q - k_off + 1) >> 5;
+        if (t < plain_hi) plain_hi = t < 0 ? 0 : (int)t;
+      }
+      if (a.window > 0) {                          // first key of the tile > last row of the wavefront - window
+        const long long t = (wave_first_q + 63 - a.window + 1 - k_off + 31) >> 5;
+        if (t > 0) plain_lo = t > 0x7fffffff ? 0x7fffffff : (int)t;
+      }
+    };
+    static_assert(DQ_BC == 32, "the shifts above");
+    enter_chunk();
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     f32x16 s[2], dp[2];      // S^T (then P^T, in place) and dP^T of the current tile: [row block], 32 keys x 32 rows
     bf16x8 kfq[3];           // K fragments (A of S^T), read two k-steps ahead; the first two of a tile
@@ -300,15 +373,15 @@ burst_bwd_dq_kernel(BwdArgs a) {
     // One step = tile kt: S^T(kt), then dP^T(kt) with the exponentials riding along, then the
     // dQ^T products of tile kt - 1 (whose dS^T fragments `dsp` were finished one step ago) with the
     // dS of tile kt riding along into `dsc`.  kslot / vslot: ring slots of tile kt.
-    // jt = position of the tile in the walk (dense: jt = kt).
+    // SPARSE: jt = position of the tile in the list.
     auto step = [&](const bf16x8 (&dsp)[2][2], bf16x8 (&dsc)[2][2], int jt, int kslot, int vslot) __attribute__((always_inline)) {
-      int kt = jt, kt3 = jt + 3;                   // this tile, and the tile whose K / V are fetched now
+      int kt = at.tile;
       bool mine = true;                            // SPARSE: this wavefront's rows can see the tile
       if constexpr (SPARSE) {
         const int e = __builtin_amdgcn_readfirstlane(list[1 + jt]);
         kt = e & 0xfffff;
         mine = ((e >> (20 + wu)) & 1) != 0;
-        kt3 = tile_at(jt + 3);
+        kf.tile = tile_at(jt + 3);
       }
       const char* kl = smem + kslot * DQ_TILE_BYTES;
       const int kprev = (kslot == 0) ? DQ_KSLOTS - 1 : kslot - 1;
@@ -338,10 +411,7 @@ burst_bwd_dq_kernel(BwdArgs a) {
       asm volatile("s_nop 3" : "+v"(s[0]), "+v"(s[1]));
       // ---- masking (diagonal tiles, window edge, ragged key tail): rare.  A masked score becomes
       // -inf, its P and dS become 0.
-      const long long tile_first_k = k_off + (long long)kt * DQ_BC;
-      const bool need_mask = (a.causal && tile_first_k + DQ_BC - 1 > wave_first_q) ||
-                             (window > 0 && tile_first_k < wave_first_q + 63 - window + 1) ||
-                             ((kt + 1) * DQ_BC > Nc) || !mine;
+      const bool need_mask = kt >= plain_hi || kt < plain_lo || !mine;
       if (need_mask) {
 #pragma unroll
         for (int rb = 0; rb < 2; rb++) {
@@ -356,8 +426,8 @@ burst_bwd_dq_kernel(BwdArgs a) {
           int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : 64;
           lim = lim < tail ? lim : tail;
           if (!mine) lim = -1;
-          const long long dl = dd - window + 1;
-          const int lim_lo = window > 0 ? (int)(dl < -1 ? -1 : (dl > 64 ? 64 : dl)) : -1;
+          const long long dl = dd - a.window + 1;
+          const int lim_lo = a.window > 0 ? (int)(dl < -1 ? -1 : (dl > 64 ? 64 : dl)) : -1;
 #pragma unroll
           for (int r = 0; r < 16; r++) {
             const int cpart = 8 * (r >> 2) + (r & 3);
@@ -396,8 +466,8 @@ burst_bwd_dq_kernel(BwdArgs a) {
         dsc[prb][kg][t] = pk[0]; dsc[prb][kg][t + 1] = pk[1];
         if ((i & 3) == 1) {
           const int j = i >> 2;                    // 0, 1 -> K of tile kt + 3; 2, 3 -> V of tile kt + 3
-          if (j < 2) dma_tile(krs, k_dst, j, kt3);
-          else dma_tile(vrs, v_dst, j - 2, kt3);
+          if (j < 2) dma_tile(krs, k_dst, j, kf.tile);
+          else dma_tile(vrs, v_dst, j - 2, kf.tile);
         }
         if (i == 14) kfq[0] = lds_read_b128(kl_next, abase);
         if (i == 15) kfq[1] = lds_read_b128(kl_next, abase ^ (1 << 5));
@@ -415,17 +485,32 @@ burst_bwd_dq_kernel(BwdArgs a) {
       for (int kg = 0; kg < 2; kg++)
 #pragma unroll
         for (int t = 0; t < 8; t++) { dsA[rb][kg][t] = (bf16)0.0f; dsB[rb][kg][t] = (bf16)0.0f; }
-    // tiles are taken in pairs; an odd count is rounded up (the extra tile lies past the end of the
-    // chunk: its K / V read as zeros and every score of it is masked)
-    const int ntiles2 = (ntiles + 1) & ~1;
+    // After each tile the two positions move on.  False: that was the last tile.
+    int jt = 0, run = min(at.left, kf.left);       // run: tiles until one of the two reaches its chunk's end
+    auto moved_on = [&]() __attribute__((always_inline)) {
+      jt++;
+      if constexpr (SPARSE) return jt < entries;
+      at.tile++; kf.tile++;
+      if (--run != 0) return true;                 // (past the last chunk: the caller has seen false before)
+      const int gone = min(at.left, kf.left);
+      at.left -= gone; kf.left -= gone;
+      if (kf.left == 0) { next_chunk(kf); krs = kv_rsrc(kf, false); vrs = kv_rsrc(kf, true); }
+      if (at.left == 0) { next_chunk(at); enter_chunk(); }
+      run = min(at.left, kf.left);
+      return at.chunk < a.n;
+    };
+    // tiles are taken in pairs; an odd count is rounded up (the extra tile lies past the end: its K / V
+    // read as zeros and every score of it is masked)
     int kslot = 0, vslot = 0;
-    for (int kt = 0; kt < ntiles2; kt += 2) {
-      step(dsB, dsA, kt, kslot, vslot);
+    for (bool more = true; more;) {
+      step(dsB, dsA, jt, kslot, vslot);
       kslot = (kslot == DQ_KSLOTS - 1) ? 0 : kslot + 1;
       vslot = (vslot + 1) & 3;
-      step(dsA, dsB, kt + 1, kslot, vslot);
+      more = moved_on();
+      step(dsA, dsB, jt, kslot, vslot);
       kslot = (kslot == DQ_KSLOTS - 1) ? 0 : kslot + 1;
       vslot = (vslot + 1) & 3;
+      if (more) more = moved_on();
     }
     // the dQ^T products of the last tile
     {
@@ -435,9 +520,6 @@ burst_bwd_dq_kernel(BwdArgs a) {
       });
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): no DMA may outlive the loop
-    // The fence stands here, inside the block, on purpose: behind the join with the path that
-    // skipped the loop the compiler may move the accumulators to other registers, and those moves
-    // are vector instructions that would read them while the last MFMAs are still in flight.
     mfma_acc_fence(dq);
   }
   // epilogue: dQ rows are owned by this wavefront alone
@@ -450,43 +532,42 @@ burst_bwd_dq_kernel(BwdArgs a) {
       for (int db = 0; db < 4; db++)
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) {
-          float* ptr = orow + db * 32 + 8 * q4 + 4 * h;
-          f32x4 v = {0.f, 0.f, 0.f, 0.f};
-          if (a.acc_dq) v = *reinterpret_cast<f32x4*>(ptr);
+          f32x4 v;
 #pragma unroll
-          for (int b = 0; b < 4; b++) v[b] += a.scale * dq[rb][db][4 * q4 + b];
-          *reinterpret_cast<f32x4*>(ptr) = v;
+          for (int b = 0; b < 4; b++) v[b] = dq[rb][db][4 * q4 + b];
+          *reinterpret_cast<f32x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
         }
     }
   }
 }
 
-int launch_bwd_dq_mfma(const KParams& p, const void* Q, const void* K, const void* V,
-                       const void* dO, const float* lse, const float* D, float* dQ, int acc_dq,
-                       hipStream_t stream) {
+// n chunks of one row pitch (with block flags: one chunk).
+int launch_bwd_dq_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   if (p.Nq <= 0) return BURST_OK;
-  BwdArgs a = make_bwd_args(p, Q, K, V, dO, lse, D, dQ, nullptr, nullptr, acc_dq, 0);
-  int heads8 = ((a.H + 7) / 8) * 8;
+  DqArgs a;
+  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ;
+  a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
+  a.causal = p.causal; a.acc_dq = io.acc_dq;
+  a.c = p.scale * kLog2e; a.log2_scale = log2f(p.scale);
+  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.blocks_per_head = (p.Nq + DQ_BR - 1) / DQ_BR;
-  long long nb = (long long)heads8 * a.blocks_per_head;
+  a.n = n; a.lay = p.lay;
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
+  const long long nb = grid_blocks(a.H, a.blocks_per_head);
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
-    return hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                DQ_LDS_BYTES) == hipSuccess &&
-           hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               DQ_LDS_BYTES) == hipSuccess &&
-           hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+           hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                DQ_LDS_BYTES + DQ_LIST_BYTES) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
-  if (a.bmask != nullptr) {
-    if ((p.Nc + DQ_BC - 1) / DQ_BC > DQ_MAX_LIST) return BURST_ERR_SHAPE;
-    BURST_LAUNCH(burst_bwd_dq_kernel<2>, dim3((unsigned)nb), dim3(256), DQ_LDS_BYTES + DQ_LIST_BYTES, stream, a);
-  } else if (a.window > 0) {
-    BURST_LAUNCH(burst_bwd_dq_kernel<1>, dim3((unsigned)nb), dim3(256), DQ_LDS_BYTES, stream, a);
+  if (a.ch[0].bmask != nullptr) {
+    if (n != 1 || (ch[0].Nc + DQ_BC - 1) / DQ_BC > DQ_MAX_LIST) return BURST_ERR_SHAPE;
+    BURST_LAUNCH(burst_bwd_dq_kernel<true>, dim3((unsigned)nb), dim3(256), DQ_LDS_BYTES + DQ_LIST_BYTES, stream, a);
   } else {
-    BURST_LAUNCH(burst_bwd_dq_kernel<0>, dim3((unsigned)nb), dim3(256), DQ_LDS_BYTES, stream, a);
+    BURST_LAUNCH(burst_bwd_dq_kernel<false>, dim3((unsigned)nb), dim3(256), DQ_LDS_BYTES, stream, a);
   }
   return launch_status();
 }
