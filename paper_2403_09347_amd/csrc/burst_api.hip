@@ -17,8 +17,7 @@ int launch_zero_fill(float*, long long, hipStream_t);
 int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_fwd_generic(const KParams&, int, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
 int launch_bwd_dq_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);
-int launch_bwd_dkv_mfma(const KParams&, const void*, const void*, const void*, const void*, const float*,
-                        const float*, float*, float*, int, hipStream_t, int key_waves);
+int launch_bwd_dkv_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t, int key_waves);
 int launch_bwd_dq_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
                           const float*, float*, int, hipStream_t);
 int launch_bwd_dkv_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
@@ -286,7 +285,7 @@ Kernels dkv_kernels(const burst_params* p, const KParams& k) {
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
   if (use_plain128_dkv(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && dkv_mfma_ok(p, k);
-  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, 1};
+  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, hand ? burst::kMaxChunks : 1};
 }
 int fwd_launch(const Kernels& f, const KParams& k, int dtype, const FwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->fwd(k, io, c, n, s);
@@ -300,9 +299,8 @@ int dq_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, co
 }
 int dkv_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->bwd_dkv(k, io, c, n, s);
-  float* const dK = (float*)c->dK; float* const dV = (float*)c->dV;
-  if (f.hand) return burst::launch_bwd_dkv_mfma(k, io.Q, c->K, c->V, io.dO, io.lse, io.D, dK, dV, io.acc_dkv, s, f.key_waves);
-  return burst::launch_bwd_dkv_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, dK, dV, io.acc_dkv, s);
+  if (f.hand) return burst::launch_bwd_dkv_mfma(k, io, c, n, s, f.key_waves);
+  return burst::launch_bwd_dkv_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, (float*)c->dK, (float*)c->dV, io.acc_dkv, s);
 }
 
 // A walk over several chunks: the chunks (without the empty ones), each with its own parameter block.

@@ -18,6 +18,9 @@
 //   1: S, dP of block 0            2: S, dP of block 1   + P, dS of block 0
 //   3: dV, dK of block 0 + P, dS of block 1              4: dV, dK of block 1 + DMA of tile t+2
 // No atomics: every key row is owned by one wavefront, results are bitwise reproducible.
+// A launch takes several chunks: their workgroups form one grid, chunk after chunk, so that short or
+// mostly hidden chunks fill the chip together (16 chunks of 512 keys, 32 heads x 512 causal rows,
+// backward: 575 us with a launch per chunk, 338 us; long chunks take the same time either way).
 //
 // A second shape of the same kernel has 2 wavefronts = 64 keys per workgroup and two workgroups
 // per CU (NW = 2), for block flags 64 keys wide (paper Sec. 2.6): a workgroup's tile list then
@@ -49,6 +52,20 @@ struct DkvShape {
   static constexpr int LIST_BYTES = (MAX_LIST + 8) * 4;
 };
 
+struct DkvArgs {
+  const bf16* Q; const bf16* dO;
+  const float* lse; const float* D;
+  int Nq, H, group;      // H counts batch x key/value heads; query heads per key/value head
+  int causal, acc_dkv;
+  float c, scale;        // c = scale * log2(e)
+  long long q_off;
+  long long window;      // 0 = none; else keys at positions <= query position - window are hidden
+  int bsize;             // block flags: edge, a multiple of 64
+  int n;                 // chunks, all with block flags or none
+  Layout lay;            // strides of Q and dO
+  Chunk ch[kMaxChunks];
+};
+
 // SPARSE: the call carries block flags (paper Sec. 2.6) or several query heads share a key/value
 // head (a.group > 1: the tiles of all heads of the group are walked, `head` is then the key/value
 // head; an entry also names the head of its tile, whose rows have buffer descriptors of their own,
@@ -59,7 +76,7 @@ struct DkvShape {
 // beyond the slice: its Q, dO and statistics read as zeros and contribute nothing.
 template <bool SPARSE, int NW>
 __global__ void __launch_bounds__(64 * NW, 1)
-burst_bwd_dkv_kernel(BwdArgs a) {
+burst_bwd_dkv_kernel(DkvArgs a) {
   using Shape = DkvShape<NW>;
   constexpr int DKV_BC = Shape::BC, DKV_SLOTS = Shape::SLOTS, LPW = Shape::LPW;
   constexpr int DKV_LDS_Q = Shape::LDS_Q, DKV_LDS_G = Shape::LDS_G, DKV_LDS_L = Shape::LDS_L, DKV_LDS_D = Shape::LDS_D;
@@ -67,23 +84,22 @@ burst_bwd_dkv_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
+  // the workgroups of all chunks, chunk after chunk
+  int ci = 0;
+  while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
+  const Chunk& C = a.ch[ci];
   int head, kblk;
-  {
-    int bid = blockIdx.x;
-    int xcd = bid & 7, idx = bid >> 3;
-    int hx = idx / a.blocks_per_head;
-    kblk = idx - hx * a.blocks_per_head;
-    head = hx * 8 + xcd;
-    if (head >= a.H) return;
-  }
+  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + DKV_BC - 1) / DKV_BC, head, kblk)) return;
+  const int Nc = C.Nc;
+  const long long k_off = C.k_off;
   const int key_wg = kblk * DKV_BC;
   const int key0 = key_wg + w * 32;                // first key of this wavefront
   const int group = SPARSE ? a.group : 1;          // query heads that share this key/value head
   const int q_rows = group * a.Nq;                 // rows of the group's Q / dO / lse / D
   const bf16* Qh = a.Q + a.lay.q_base(head * group);    // first query head of the group
   const bf16* Gh = a.dO + a.lay.q_base(head * group);
-  const bf16* Kh = a.K + a.lay.kv_base(head);
-  const bf16* Vh = a.V + a.lay.kv_base(head);
+  const bf16* Kh = (const bf16*)C.K + C.kv_base(head, a.lay.kv_heads);
+  const bf16* Vh = (const bf16*)C.V + C.kv_base(head, a.lay.kv_heads);
   const unsigned qpitch = (unsigned)a.lay.qs_r * 2u;             // bytes between query rows
   const unsigned qtile = qpitch * DKV_BR;                        // ... between query tiles
   const float* lseh = a.lse + (size_t)head * q_rows;
@@ -93,12 +109,12 @@ burst_bwd_dkv_kernel(BwdArgs a) {
   int ntiles_all = (a.Nq + DKV_BR - 1) / DKV_BR;
   int t_begin = 0;
   if (a.causal) {
-    long long first_row = a.k_off + key_wg - a.q_off;      // first row index that sees key_wg
+    long long first_row = k_off + key_wg - a.q_off;      // first row index that sees key_wg
     if (first_row > 0) t_begin = (int)min((long long)ntiles_all, first_row / DKV_BR);
   }
   if (a.window > 0) {
     // sliding window: rows at positions >= key position + window no longer see the key
-    long long last_row = a.k_off + min(key_wg + DKV_BC, a.Nc) - 1 + a.window - 1 - a.q_off;
+    long long last_row = k_off + min(key_wg + DKV_BC, Nc) - 1 + a.window - 1 - a.q_off;
     ntiles_all = last_row < 0 ? 0 : (int)min((long long)ntiles_all, last_row / DKV_BR + 1);
   }
 
@@ -118,8 +134,8 @@ burst_bwd_dkv_kernel(BwdArgs a) {
       bf16x8 z;
 #pragma unroll
       for (int t = 0; t < 8; t++) z[t] = (bf16)0.0f;
-      kf[ks] = key < a.Nc ? *reinterpret_cast<const bf16x8*>(Kh + (size_t)key * a.lay.ks_r + ks * 16 + h * 8) : z;
-      vf[ks] = key < a.Nc ? *reinterpret_cast<const bf16x8*>(Vh + (size_t)key * a.lay.ks_r + ks * 16 + h * 8) : z;
+      kf[ks] = key < Nc ? *reinterpret_cast<const bf16x8*>(Kh + (size_t)key * C.ks_r + ks * 16 + h * 8) : z;
+      vf[ks] = key < Nc ? *reinterpret_cast<const bf16x8*>(Vh + (size_t)key * C.ks_r + ks * 16 + h * 8) : z;
     }
   }
   int nwalk = ntiles_all - t_begin;                // tiles to walk
@@ -135,14 +151,14 @@ burst_bwd_dkv_kernel(BwdArgs a) {
           const int t = base + lane;
           int bits = 0;
           if (t < ntiles_all) {
-            if (a.bmask == nullptr) {
+            if (C.bmask == nullptr) {
               bits = (1 << NW) - 1;
             } else {
-              const uint8_t* mrow = a.bmask + (size_t)(head * group + g) * a.bhstride + (size_t)((t * DKV_BR) / a.bsize) * a.bpitch;
+              const uint8_t* mrow = C.bmask + (size_t)(head * group + g) * C.bhstride + (size_t)((t * DKV_BR) / a.bsize) * C.bpitch;
 #pragma unroll
               for (int ww = 0; ww < NW; ww++) {
                 const int k0 = key_wg + ww * 32;
-                if (k0 < a.Nc && mrow[k0 / a.bsize] != 0) bits |= 1 << ww;
+                if (k0 < Nc && mrow[k0 / a.bsize] != 0) bits |= 1 << ww;
               }
             }
           }
@@ -266,7 +282,7 @@ burst_bwd_dkv_kernel(BwdArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0070);
     __builtin_amdgcn_s_barrier();
 
-    const long long wave_first_k = a.k_off + key0;
+    const long long wave_first_k = k_off + key0;
     const long long wave_last_k = wave_first_k + 31;
     const long long kpos = wave_first_k + lr;
     constexpr int LEAD = 6, RING = LEAD + 2;       // A-operand reads run LEAD slices ahead
@@ -447,12 +463,12 @@ burst_bwd_dkv_kernel(BwdArgs a) {
                    "+a"(dv[0]), "+a"(dv[1]), "+a"(dv[2]), "+a"(dv[3]));
   }
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
-  float* dKh = a.dK + (size_t)head * a.Nc * 128;
-  float* dVh = a.dV + (size_t)head * a.Nc * 128;
+  float* dKh = (float*)C.dK + (size_t)head * Nc * 128;
+  float* dVh = (float*)C.dV + (size_t)head * Nc * 128;
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-    if (key < a.Nc) {
+    if (key < Nc) {
 #pragma unroll
       for (int db = 0; db < 4; db++) {
         size_t off = (size_t)key * 128 + db * 32 + lr;
@@ -465,11 +481,9 @@ burst_bwd_dkv_kernel(BwdArgs a) {
   }
 }
 
-// key_waves: 4 (128-key workgroups) or 2 (64-key workgroups, calls with block flags only).
-int launch_bwd_dkv_mfma(const KParams& p, const void* Q, const void* K, const void* V,
-                        const void* dO, const float* lse, const float* D, float* dK, float* dV,
-                        int acc_dkv, hipStream_t stream, int key_waves) {
-  if (p.Nc <= 0) return BURST_OK;
+// n chunks, all with block flags or none.  key_waves: 4 (128-key workgroups) or 2 (64-key workgroups, calls
+// with block flags only).
+int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream, int key_waves) {
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
     return hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -480,15 +494,24 @@ int launch_bwd_dkv_mfma(const KParams& p, const void* Q, const void* K, const vo
                                DkvShape<2>::LDS_BYTES + DkvShape<2>::LIST_BYTES) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
-  BwdArgs a = make_bwd_args(p, Q, K, V, dO, lse, D, nullptr, dK, dV, 0, acc_dkv);
-  a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
-  int heads8 = ((a.H + 7) / 8) * 8;
-  const bool listed = a.bmask != nullptr || a.group > 1;
+  DkvArgs a;
+  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D;
+  a.Nq = p.Nq; a.H = p.B * p.H / p.group; a.group = p.group;     // workgroups are laid out over key/value heads
+  a.causal = p.causal; a.acc_dkv = io.acc_dkv;
+  a.c = p.scale * kLog2e; a.scale = p.scale;
+  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
+  a.n = n; a.lay = p.lay;
+  const bool listed = ch[0].bmask != nullptr || p.group > 1;
   if (key_waves != 4 && !(key_waves == 2 && listed)) return BURST_ERR_SHAPE;
   const int bc = 32 * key_waves;
-  a.blocks_per_head = (p.Nc + bc - 1) / bc;
-  long long nb = (long long)heads8 * a.blocks_per_head;
-  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  long long nb = 0;
+  for (int i = 0; i < n; i++) {
+    a.ch[i] = ch[i];
+    a.ch[i].first_block = (int)nb;
+    nb += grid_blocks(a.H, (ch[i].Nc + bc - 1) / bc);
+    if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  }
+  if (nb == 0) return BURST_OK;
   if (listed) {
     const int max_list = key_waves == 4 ? DkvShape<4>::MAX_LIST : DkvShape<2>::MAX_LIST;
     if ((long long)a.group * ((p.Nq + DKV_BR - 1) / DKV_BR) > max_list) return BURST_ERR_SHAPE;
