@@ -15,13 +15,11 @@ int launch_merge_state(const KParams&, float*, float*, float*, const float*, con
 int launch_bwd_prepare(const KParams&, int, const void*, const void*, float*, hipStream_t);
 int launch_zero_fill(float*, long long, hipStream_t);
 int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);
-int launch_fwd_generic(const KParams&, int, const void*, const void*, const void*, float*, float*, float*, hipStream_t);
+int launch_fwd_generic(const KParams&, int, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dq_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dkv_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t, int key_waves);
-int launch_bwd_dq_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
-                          const float*, float*, int, hipStream_t);
-int launch_bwd_dkv_generic(const KParams&, int, const void*, const void*, const void*, const void*, const float*,
-                           const float*, float*, float*, int, hipStream_t);
+int launch_bwd_dq_generic(const KParams&, int, const BwdIo&, const Chunk*, int, hipStream_t);
+int launch_bwd_dkv_generic(const KParams&, int, const BwdIo&, const Chunk*, int, hipStream_t);
 // the plainly written kernels of burst_plain_mfma.h, one namespace per build
 #define BURST_DECLARE_PLAIN(ns)                                                            \
   namespace ns {                                                                           \
@@ -272,35 +270,35 @@ struct Kernels {
   const PlainFamily* plain;
   bool hand;
   int key_waves;                                   // hand-scheduled dK/dV
-  int takes;                                       // most chunks of one launch
+  int takes;                                       // most chunks of one launch (hand-scheduled: of one row pitch)
   bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves && takes == o.takes; }
 };
 Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the same choice
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
   if (use_plain128(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
-  return {nullptr, hand, 0, hand && p->block_mask == nullptr ? burst::kMaxChunks : 1};
+  return {nullptr, hand, 0, hand && p->block_mask != nullptr ? 1 : burst::kMaxChunks};
 }
 Kernels dkv_kernels(const burst_params* p, const KParams& k) {
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
   if (use_plain128_dkv(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && dkv_mfma_ok(p, k);
-  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, hand ? burst::kMaxChunks : 1};
+  return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, burst::kMaxChunks};
 }
 int fwd_launch(const Kernels& f, const KParams& k, int dtype, const FwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->fwd(k, io, c, n, s);
   if (f.hand) return burst::launch_fwd_mfma(k, io, c, n, s);
-  return burst::launch_fwd_generic(k, dtype, io.Q, c->K, c->V, io.O_acc, io.m, io.l, s);
+  return burst::launch_fwd_generic(k, dtype, io, c, n, s);
 }
 int dq_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->bwd_dq(k, io, c, n, s);
   if (f.hand) return burst::launch_bwd_dq_mfma(k, io, c, n, s);
-  return burst::launch_bwd_dq_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, io.dQ, io.acc_dq, s);
+  return burst::launch_bwd_dq_generic(k, dtype, io, c, n, s);
 }
 int dkv_launch(const Kernels& f, const KParams& k, int dtype, const BwdIo& io, const Chunk* c, int n, hipStream_t s) {
   if (f.plain != nullptr) return f.plain->bwd_dkv(k, io, c, n, s);
   if (f.hand) return burst::launch_bwd_dkv_mfma(k, io, c, n, s, f.key_waves);
-  return burst::launch_bwd_dkv_generic(k, dtype, io.Q, c->K, c->V, io.dO, io.lse, io.D, (float*)c->dK, (float*)c->dV, io.acc_dkv, s);
+  return burst::launch_bwd_dkv_generic(k, dtype, io, c, n, s);
 }
 
 // A walk over several chunks: the chunks (without the empty ones), each with its own parameter block.
@@ -667,12 +665,7 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
     bool fresh = true, final = false;
     const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
       FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, fresh, nullptr, 1};
-      if (f.plain != nullptr || f.hand) {          // (the generic kernels want the state and leave it in memory)
-        if (last) { io.O_out = O_out; io.lse = lse; final = true; }
-      } else if (fresh) {
-        io.fresh = 0;
-        if (const int i = burst::launch_state_init(k, O_acc, m, l, s); i != BURST_OK) return i;
-      }
+      if (last) { io.O_out = O_out; io.lse = lse; final = true; }
       fresh = false;
       return fwd_launch(f, kc, p->dtype, io, c, n, s);
     });

@@ -29,21 +29,23 @@
 namespace burst {
 
 struct GenArgs {
-  const void* Q; const void* K; const void* V; const void* dO;
+  const void* Q; const void* dO;
   float* O_acc; float* m; float* l;               // forward state
+  void* O_out; float* lse_out;                    // O_out != nullptr: the state is final after this launch
   const float* lse; const float* D;               // backward inputs
-  float* dQ; float* dK; float* dV;
-  int Nq, Nc, d, BH;
-  int causal;
+  float* dQ;
+  int Nq, d, BH;
+  int causal, fresh;                              // fresh: the state before the launch is the initial one
   float scale, c;                                 // c = scale * log2(e)
-  long long q_off, k_off;
+  long long q_off;
   long long window;
-  const uint8_t* bmask; int bsize, bpitch;        // block mask (nullptr = none); bsize a multiple of 64
-  long long bhstride;                             // bytes between heads' flag matrices (0 = shared)
-  Layout lay;                                     // strides of Q, dO and of K, V
+  int bsize;                                      // edge of block flags, a multiple of 64
+  Layout lay;                                     // strides of Q, dO, O_out
   int group;                                      // query heads per key/value head
   int acc_dq, acc_dkv;
-  int blocks;                                     // 32-row (32-key) blocks per head
+  int blocks;                                     // forward, dQ: 32-row blocks per head
+  int n;                                          // chunks
+  Chunk ch[kMaxChunks];
 };
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
@@ -94,39 +96,62 @@ struct Rows {
   }
 };
 
-// Key tiles (32 keys) of the chunk that rows [row0, row0 + 32) of the slice can see: [lo, hi).
-__device__ __forceinline__ void key_tiles(const GenArgs& a, int row0, int& lo, int& hi) {
-  lo = 0; hi = (a.Nc + 31) >> 5;
-  if (a.causal) {
-    const long long last = a.q_off + min(row0 + 31, a.Nq - 1) - a.k_off;   // last visible key
-    if (last < 0) hi = 0;
-    else if ((last >> 5) + 1 < hi) hi = (int)(last >> 5) + 1;
-  }
-  if (a.window > 0) {
-    const long long first = a.q_off + row0 - a.window + 1 - a.k_off;
-    if (first >= a.Nc) lo = hi;
-    else if (first > 0) lo = (int)(first >> 5);
-  }
-}
-// Query tiles (32 rows) that see keys [key0, key0 + 32).
-__device__ __forceinline__ void row_tiles(const GenArgs& a, int key0, int& lo, int& hi) {
+// Query tiles (32 rows) that see keys [key0, key0 + 32) of the chunk.
+__device__ __forceinline__ void row_tiles(const GenArgs& a, const Chunk& C, int key0, int& lo, int& hi) {
   lo = 0; hi = (a.Nq + 31) >> 5;
   if (a.causal) {
-    const long long first = a.k_off + key0 - a.q_off;
+    const long long first = C.k_off + key0 - a.q_off;
     if (first >= a.Nq) lo = hi;
     else if (first > 0) lo = (int)(first >> 5);
   }
   if (a.window > 0) {
-    const long long last = a.k_off + min(key0 + 31, a.Nc - 1) + a.window - 1 - a.q_off;
+    const long long last = C.k_off + min(key0 + 31, C.Nc - 1) + a.window - 1 - a.q_off;
     if (last < 0) hi = 0;
     else if ((last >> 5) + 1 < hi) hi = (int)(last >> 5) + 1;
   }
 }
 // A 32 x 32 tile lies in one block of the flags (their edge is a multiple of 64).
-__device__ __forceinline__ bool tile_flag(const GenArgs& a, int head, int row0, int key0) {
-  if (a.bmask == nullptr) return true;
-  return a.bmask[(size_t)head * a.bhstride + (size_t)(row0 / a.bsize) * a.bpitch + key0 / a.bsize] != 0;
+__device__ __forceinline__ bool tile_flag(const GenArgs& a, const Chunk& C, int head, int row0, int key0) {
+  if (C.bmask == nullptr) return true;
+  return C.bmask[(size_t)head * C.bhstride + (size_t)(row0 / a.bsize) * C.bpitch + key0 / a.bsize] != 0;
 }
+// The key tiles that rows [row0, row0 + 32) see, chunk after chunk, every W-th of them: the share of one
+// wavefront.
+template <typename T, int W>
+struct KeyWalk {
+  int c, t, lo, hi;                               // chunk, tile, its chunk's visible range
+  const T* K; const T* V;                         // of the chunk, this head
+  long long ks_r, k_off;
+  int Nc;
+  __device__ __forceinline__ bool to(const GenArgs& a, int head, int row0, int step) {
+    t += step;
+    for (;;) {
+      while (t >= hi) {
+        const int past = t - hi;
+        if (++c >= a.n) return false;
+        const Chunk& C = a.ch[c];
+        Nc = C.Nc; k_off = C.k_off; ks_r = C.ks_r;
+        lo = 0; hi = (Nc + 31) >> 5;
+        if (a.causal) {
+          const long long last = a.q_off + min(row0 + 31, a.Nq - 1) - k_off;   // last visible key
+          if (last < 0) hi = 0;
+          else if ((last >> 5) + 1 < hi) hi = (int)(last >> 5) + 1;
+        }
+        if (a.window > 0) {
+          const long long first = a.q_off + row0 - a.window + 1 - k_off;
+          if (first >= Nc) lo = hi;
+          else if (first > 0) lo = (int)(first >> 5);
+        }
+        hi = max(hi, lo);
+        const size_t base = C.kv_base(head / a.group, a.lay.kv_heads);
+        K = (const T*)C.K + base; V = (const T*)C.V + base;
+        t = lo + past;
+      }
+      if (tile_flag(a, a.ch[c], head, row0, t * 32)) return true;
+      t += W;
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------- forward
 template <typename T, int D, bool VEC, int W>
@@ -140,14 +165,6 @@ fwd_generic_kernel(GenArgs a) {
   int head, blk;
   if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
   const int row0 = blk * 32, row = row0 + lr;
-  const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
-  const T* Vh = (const T*)a.V + a.lay.kv_base(head / a.group);
-  int lo, hi;
-  key_tiles(a, row0, lo, hi);
-  auto seek = [&](int t) {                        // first tile from t on, in steps of W, that the flags leave
-    while (t < hi && !tile_flag(a, head, row0, t * 32)) t += W;
-    return t;
-  };
 
   f32x16 o[NB];
 #pragma unroll
@@ -156,25 +173,31 @@ fwd_generic_kernel(GenArgs a) {
     for (int r = 0; r < 16; r++) o[db][r] = 0.f;
   float m2 = BURST_NEG_INF, lsum = 0.f;           // reference max (log2 units), sum over this lane's keys
 
-  int t = seek(lo + w);
-  if (t < hi) {
+  KeyWalk<T, W> at;
+  at.c = -1; at.t = at.lo = at.hi = 0;
+  bool more = at.to(a, head, row0, w);
+  if (more) {
     f32x4 qf[NK], kf[NK];
     const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
 #pragma unroll
     for (int ks = 0; ks < NK; ks++) qf[ks] = R::fixed(Qr, 8 * ks + 4 * h, a.d, row < a.Nq);
-    auto load_k = [&](int tile) __attribute__((always_inline)) {
-      const T* kr = Kh + (size_t)min(tile * 32 + lr, a.Nc - 1) * a.lay.ks_r;
+    auto load_k = [&]() __attribute__((always_inline)) {
+      const T* kr = at.K + (size_t)min(at.t * 32 + lr, at.Nc - 1) * at.ks_r;
 #pragma unroll
       for (int ks = 0; ks < NK; ks++) kf[ks] = R::piece(kr, 8 * ks + 4 * h, a.d);
     };
-    load_k(t);
-    while (t < hi) {
-      const int key0 = t * 32, tn = seek(t + W);
+    load_k();
+    while (more) {
+      const int key0 = at.t * 32, Nc = at.Nc;
+      const long long k_off = at.k_off, ks_r = at.ks_r;
+      const T* const Kh = at.K;
+      const T* const Vh = at.V;
+      more = at.to(a, head, row0, W);
       float vf[16][NB];
       auto load_v = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = r0; r < r0 + 8; r++)
-          R::spread(Vh + (size_t)min(key0 + reg_row(r, h), a.Nc - 1) * a.lay.ks_r, lr, a.d, vf[r]);
+          R::spread(Vh + (size_t)min(key0 + reg_row(r, h), Nc - 1) * ks_r, lr, a.d, vf[r]);
       };
       load_v(0);
       __builtin_amdgcn_sched_barrier(0);
@@ -188,8 +211,8 @@ fwd_generic_kernel(GenArgs a) {
       __builtin_amdgcn_sched_barrier(0);
       load_v(8);
       // masks: register r holds key key0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
-      const long long dd = (a.q_off - a.k_off) + row - ((long long)key0 + 4 * h);
-      int lim = min(64, a.Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      const long long dd = (a.q_off - k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
       if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
       if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
       float v = BURST_NEG_INF;
@@ -216,12 +239,11 @@ fwd_generic_kernel(GenArgs a) {
 #pragma unroll
         for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[r][db], s[r], o[db]);
       __builtin_amdgcn_sched_barrier(0);
-      if (tn < hi) load_k(tn);
+      if (more) load_k();
 #pragma unroll
       for (int r = 8; r < 16; r++)
 #pragma unroll
         for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[r][db], s[r], o[db]);
-      t = tn;
     }
   }
   // the wavefronts' partial results meet in LDS
@@ -241,31 +263,36 @@ fwd_generic_kernel(GenArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = o[db][r] * own;
   __syncthreads();
-  if (row >= a.Nq || mg == BURST_NEG_INF) return;  // rows that saw no key keep their state
+  const bool saw = mg != BURST_NEG_INF;
+  if (row >= a.Nq || (!saw && !a.fresh && a.O_out == nullptr)) return;   // rows that saw no key keep their state
   const size_t sr = (size_t)head * a.Nq + row;
-  const float m_old = a.m[sr] * kLog2e, l_old = a.l[sr];
-  const float m_new = fmaxf(m_old, mg);
-  const float fa = fast_exp2(m_old - m_new), fb = fast_exp2(mg - m_new);
+  const float m_old = a.fresh ? BURST_NEG_INF : a.m[sr] * kLog2e, l_old = a.fresh ? 0.f : a.l[sr];
+  const float m_new = fmaxf(m_old, mg), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
+  const float fa = fast_exp2(m_old - ref), fb = fast_exp2(mg - ref);
+  const float l_new = (fa == 0.f ? 0.f : fa * l_old) + fb * lg;
+  const float m_st = saw || a.fresh ? m_new * kLn2 : a.m[sr];
   __syncthreads();                                 // every wavefront has read the row's old m and l
   if (w == 0 && h == 0) {
-    a.m[sr] = m_new * kLn2;
-    a.l[sr] = (fa == 0.f ? 0.f : fa * l_old) + fb * lg;
+    if (saw || a.fresh) { a.m[sr] = m_st; a.l[sr] = l_new; }
+    if (a.O_out != nullptr) a.lse_out[sr] = l_new > 0.f ? m_st + __logf(l_new) : BURST_NEG_INF;
   }
+  const float inv = l_new > 0.f ? 1.0f / l_new : 0.f;
   float* const orow = a.O_acc + sr * a.d;
+  T* const out = a.O_out == nullptr ? nullptr : (T*)a.O_out + a.lay.q_base(head) + (size_t)row * a.lay.qs_r;
 #pragma unroll
   for (int rr = 0; rr < 16 / W; rr++) {
     const int r = w * (16 / W) + rr, mrow = reg_row(r, h);
-    float v[NB];
 #pragma unroll
     for (int db = 0; db < NB; db++) {
-      v[db] = 0.f;
+      float v = 0.f;
 #pragma unroll
-      for (int i = 0; i < W; i++) v[db] += gsh[((i * NB + db) * 16 + r) * 64 + lane];
-    }
-#pragma unroll
-    for (int db = 0; db < NB; db++) {
+      for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
       const int col = R::col_of(db, mrow);
-      if (col < a.d) orow[col] = (fa == 0.f ? 0.f : fa * orow[col]) + fb * v[db];
+      if (col < a.d) {
+        const float x = (fa == 0.f ? 0.f : fa * orow[col]) + fb * v;
+        if (saw || a.fresh) orow[col] = x;
+        if (out != nullptr) out[col] = (T)(l_new > 0.f ? x * inv : 0.f);
+      }
     }
   }
 }
@@ -283,23 +310,17 @@ bwd_dq_generic_kernel(GenArgs a) {
   if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
   const int row0 = blk * 32, row = row0 + lr;
   const bool ok = row < a.Nq;
-  const T* Kh = (const T*)a.K + a.lay.kv_base(head / a.group);
-  const T* Vh = (const T*)a.V + a.lay.kv_base(head / a.group);
   const size_t sr = (size_t)head * a.Nq + min(row, a.Nq - 1);
-  int lo, hi;
-  key_tiles(a, row0, lo, hi);
-  auto seek = [&](int t) {
-    while (t < hi && !tile_flag(a, head, row0, t * 32)) t += W;
-    return t;
-  };
 
   f32x16 dq[NB];
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
-  int t = seek(lo + w);
-  if (t < hi) {
+  KeyWalk<T, W> at;
+  at.c = -1; at.t = at.lo = at.hi = 0;
+  bool more = at.to(a, head, row0, w);
+  if (more) {
     f32x4 qf[NK], gf[NK], kf[NK];
     const size_t qrow = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
 #pragma unroll
@@ -310,16 +331,20 @@ bwd_dq_generic_kernel(GenArgs a) {
     const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
     const float nlse2 = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv * kLog2e;   // -inf: P = 0
     const float nD = ok ? -a.D[sr] : 0.f;
-    auto load_k = [&](int tile) __attribute__((always_inline)) {
-      const T* kr = Kh + (size_t)min(tile * 32 + lr, a.Nc - 1) * a.lay.ks_r;
+    auto load_k = [&]() __attribute__((always_inline)) {
+      const T* kr = at.K + (size_t)min(at.t * 32 + lr, at.Nc - 1) * at.ks_r;
 #pragma unroll
       for (int ks = 0; ks < NK; ks++) kf[ks] = R::piece(kr, 8 * ks + 4 * h, a.d);
     };
-    load_k(t);
-    while (t < hi) {
-      const int key0 = t * 32, tn = seek(t + W);
+    load_k();
+    while (more) {
+      const int key0 = at.t * 32, Nc = at.Nc;
+      const long long k_off = at.k_off, ks_r = at.ks_r;
+      const T* const Kh = at.K;
+      const T* const Vh = at.V;
+      more = at.to(a, head, row0, W);
       f32x4 vf[NK];
-      const T* vr = Vh + (size_t)min(key0 + lr, a.Nc - 1) * a.lay.ks_r;
+      const T* vr = Vh + (size_t)min(key0 + lr, Nc - 1) * ks_r;
 #pragma unroll
       for (int ks = 0; ks < NK; ks++) vf[ks] = R::piece(vr, 8 * ks + 4 * h, a.d);
       f32x16 s, dp;
@@ -334,7 +359,7 @@ bwd_dq_generic_kernel(GenArgs a) {
       auto load_kt = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = r0; r < r0 + 8; r++)
-          R::spread(Kh + (size_t)min(key0 + reg_row(r, h), a.Nc - 1) * a.lay.ks_r, lr, a.d, kt[r]);
+          R::spread(Kh + (size_t)min(key0 + reg_row(r, h), Nc - 1) * ks_r, lr, a.d, kt[r]);
         __builtin_amdgcn_sched_barrier(0);
       };
       load_kt(0);
@@ -344,8 +369,8 @@ bwd_dq_generic_kernel(GenArgs a) {
         for (int j = 0; j < 4; j++) dp = mfma_f32(vf[ks][j], gf[ks][j], dp);
       __builtin_amdgcn_sched_barrier(0);
       load_kt(8);
-      const long long dd = (a.q_off - a.k_off) + row - ((long long)key0 + 4 * h);
-      int lim = min(64, a.Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      const long long dd = (a.q_off - k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
       if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
       if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
 #pragma unroll
@@ -360,13 +385,12 @@ bwd_dq_generic_kernel(GenArgs a) {
 #pragma unroll
         for (int db = 0; db < NB; db++) dq[db] = mfma_f32(kt[r][db], dp[r], dq[db]);
       __builtin_amdgcn_sched_barrier(0);
-      if (tn < hi) load_k(tn);
+      if (more) load_k();
 #pragma unroll
       for (int r = 8; r < 16; r++)
 #pragma unroll
         for (int db = 0; db < NB; db++) dq[db] = mfma_f32(kt[r][db], dp[r], dq[db]);
       __builtin_amdgcn_sched_barrier(0);
-      t = tn;
     }
   }
 #pragma unroll
@@ -400,11 +424,15 @@ bwd_dkv_generic_kernel(GenArgs a) {
   extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dK, then dV
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int ci = 0;                                      // the workgroups of all chunks, chunk after chunk
+  while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
+  const Chunk& C = a.ch[ci];
+  const int Nc = C.Nc;
   int kvhead, blk;
-  if (!locate_block(blockIdx.x, a.BH / a.group, a.blocks, kvhead, blk)) return;
+  if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk)) return;
   const int key0 = blk * 32, key = key0 + lr;
   int lo, hi;
-  row_tiles(a, key0, lo, hi);
+  row_tiles(a, C, key0, lo, hi);
   const int per_head = hi - lo, total = max(per_head, 0) * a.group;   // walk positions: the tiles of all heads of the group
   auto place = [&](int n, int& head, int& tile) __attribute__((always_inline)) {
     const int g = n / per_head;
@@ -415,7 +443,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
     while (n < total) {
       int head, tile;
       place(n, head, tile);
-      if (tile_flag(a, head, tile * 32, key0)) break;
+      if (tile_flag(a, C, head, tile * 32, key0)) break;
       n += W;
     }
     return n;
@@ -429,11 +457,11 @@ bwd_dkv_generic_kernel(GenArgs a) {
   int n = seek(w);
   if (n < total) {
     f32x4 kf[NK], vf[NK];
-    const size_t krow = a.lay.kv_base(kvhead) + (size_t)min(key, a.Nc - 1) * a.lay.ks_r;
+    const size_t krow = C.kv_base(kvhead, a.lay.kv_heads) + (size_t)min(key, Nc - 1) * C.ks_r;
 #pragma unroll
     for (int ks = 0; ks < NK; ks++) {
-      kf[ks] = R::fixed((const T*)a.K + krow, 8 * ks + 4 * h, a.d, key < a.Nc);
-      vf[ks] = R::fixed((const T*)a.V + krow, 8 * ks + 4 * h, a.d, key < a.Nc);
+      kf[ks] = R::fixed((const T*)C.K + krow, 8 * ks + 4 * h, a.d, key < Nc);
+      vf[ks] = R::fixed((const T*)C.V + krow, 8 * ks + 4 * h, a.d, key < Nc);
     }
     // A tile is eight groups of MFMAs (S, dP, dV, dK, two halves each); every group's operands are
     // requested one group ahead, which is all that fits beside the resident operands and
@@ -495,7 +523,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
       over_d(dp, pb, vf, 1);
       rows8(rb, Gh, row0, 1);
       // masks: register r holds row row0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
-      const long long dd = (a.k_off - a.q_off) + key - ((long long)row0 + 4 * h);   // key position - row position at cpart 0
+      const long long dd = (C.k_off - a.q_off) + key - ((long long)row0 + 4 * h);   // key position - row position at cpart 0
       int lim = min(64, a.Nq - 1 - (row0 + 4 * h)), lim_lo = -1;
       if (a.causal) lim_lo = (int)(dd < -1 ? -1 : dd > 64 ? 64 : dd);
       if (a.window > 0) { const long long dl = dd + a.window - 1; lim = (int)min((long long)lim, dl < -1 ? -1LL : dl); }
@@ -531,13 +559,13 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
     __syncthreads();
-    float* const base = which ? a.dV : a.dK;
+    float* const base = (float*)(which ? C.dV : C.dK);
     const float f = which ? 1.f : a.scale;
 #pragma unroll
     for (int rr = 0; rr < 16 / W; rr++) {
       const int r = w * (16 / W) + rr, k = key0 + reg_row(r, h);
-      if (k >= a.Nc) continue;
-      float* const out = base + ((size_t)kvhead * a.Nc + k) * a.d;
+      if (k >= Nc) continue;
+      float* const out = base + ((size_t)kvhead * Nc + k) * a.d;
 #pragma unroll
       for (int db = 0; db < NB; db++) {
         float v = 0.f;
@@ -551,23 +579,18 @@ bwd_dkv_generic_kernel(GenArgs a) {
 }
 
 // ---------------------------------------------------------------------------- launchers
-static GenArgs make_args(const KParams& p) {
-  GenArgs a = {};
-  a.Nq = p.Nq; a.Nc = p.Nc; a.d = p.d; a.BH = p.B * p.H;
-  a.causal = p.causal; a.scale = p.scale; a.c = p.scale * kLog2e; a.q_off = p.q_off; a.k_off = p.k_off; a.window = p.window;
-  a.bmask = p.bmask; a.bsize = p.bsize; a.bpitch = p.bpitch; a.bhstride = p.bhstride; a.group = p.group;
-  a.lay = p.lay;
-  return a;
+static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
+  a.Nq = p.Nq; a.d = p.d; a.BH = p.B * p.H;
+  a.causal = p.causal; a.scale = p.scale; a.c = p.scale * kLog2e; a.q_off = p.q_off; a.window = p.window;
+  a.bsize = p.bsize; a.group = p.group; a.lay = p.lay;
+  a.n = n;
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
 }
 
 enum { GEN_FWD, GEN_DQ, GEN_DKV };
 template <int KIND, typename T, int D, bool VEC, int W>
-static int gen_launch(GenArgs a, hipStream_t s) {
-  const long long heads = KIND == GEN_DKV ? a.BH / a.group : a.BH;
-  a.blocks = (int)(((long long)(KIND == GEN_DKV ? a.Nc : a.Nq) + 31) / 32);
-  if (heads * a.blocks > 0x7fffff00LL) return BURST_ERR_SHAPE;
+static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
   const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : 0)) * 4;
-  const dim3 grid((unsigned)grid_blocks(heads, a.blocks)), wg(64 * W);
   void (*kernel)(GenArgs);
   if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W>;
   else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W>;
@@ -577,48 +600,57 @@ static int gen_launch(GenArgs a, hipStream_t s) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
-  BURST_LAUNCH(kernel, grid, wg, lds, s, a);
+  BURST_LAUNCH(kernel, dim3((unsigned)grid), dim3(64 * W), lds, s, a);
   return launch_status();
 }
 // Padded head dimension: the next multiple of 32.  With eight wavefronts per workgroup (two per
 // SIMD; the registers allow it up to 64) a row block's tiles are walked in half the time; that pays
 // while there are fewer row blocks than CUs.
 template <int KIND>
-static int gen_dispatch(const GenArgs& a, int dtype, hipStream_t s) {
-  const long long n = KIND == GEN_DKV ? (long long)(a.BH / a.group) * ((a.Nc + 31) / 32) : (long long)a.BH * ((a.Nq + 31) / 32);
-  const bool few = n <= 256;
-  if (dtype == BURST_F32 && a.d % 4 == 0) {
-    if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, s) : gen_launch<KIND, float, 32, true, 4>(a, s);
-    if (a.d <= 64) return few ? gen_launch<KIND, float, 64, true, 8>(a, s) : gen_launch<KIND, float, 64, true, 4>(a, s);
-    if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, s);
-    return gen_launch<KIND, float, 128, true, 4>(a, s);
+static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
+  long long grid = 0;
+  if (KIND == GEN_DKV) {
+    for (int i = 0; i < a.n; i++) {
+      a.ch[i].first_block = (int)grid;
+      grid += grid_blocks(a.BH / a.group, ((long long)a.ch[i].Nc + 31) / 32);
+      if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
+    }
+  } else {
+    a.blocks = (int)(((long long)a.Nq + 31) / 32);
+    grid = grid_blocks(a.BH, a.blocks);
   }
-  if (dtype == BURST_F32) return a.d <= 64 ? gen_launch<KIND, float, 64, false, 4>(a, s) : gen_launch<KIND, float, 128, false, 4>(a, s);
-  return a.d <= 64 ? gen_launch<KIND, bf16, 64, false, 4>(a, s) : gen_launch<KIND, bf16, 128, false, 4>(a, s);
+  if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
+  if (grid == 0) return BURST_OK;
+  const bool few = grid <= 256;
+  if (dtype == BURST_F32 && a.d % 4 == 0) {
+    if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, grid, s) : gen_launch<KIND, float, 32, true, 4>(a, grid, s);
+    if (a.d <= 64) return few ? gen_launch<KIND, float, 64, true, 8>(a, grid, s) : gen_launch<KIND, float, 64, true, 4>(a, grid, s);
+    if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, grid, s);
+    return gen_launch<KIND, float, 128, true, 4>(a, grid, s);
+  }
+  if (dtype == BURST_F32) return a.d <= 64 ? gen_launch<KIND, float, 64, false, 4>(a, grid, s) : gen_launch<KIND, float, 128, false, 4>(a, grid, s);
+  return a.d <= 64 ? gen_launch<KIND, bf16, 64, false, 4>(a, grid, s) : gen_launch<KIND, bf16, 128, false, 4>(a, grid, s);
 }
 
-int launch_fwd_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
-                       float* O_acc, float* m, float* l, hipStream_t s) {
-  if ((long long)p.B * p.H * p.Nq == 0 || p.Nc == 0) return BURST_OK;
-  GenArgs a = make_args(p);
-  a.Q = Q; a.K = K; a.V = V; a.O_acc = O_acc; a.m = m; a.l = l;
+// n <= kMaxChunks chunks.
+int launch_fwd_generic(const KParams& p, int dtype, const FwdIo& io, const Chunk* ch, int n, hipStream_t s) {
+  GenArgs a = {};
+  make_args(a, p, ch, n);
+  a.Q = io.Q; a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = io.O_out; a.lse_out = io.lse; a.fresh = io.fresh;
   return gen_dispatch<GEN_FWD>(a, dtype, s);
 }
-
-int launch_bwd_dq_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
-                          const void* dO, const float* lse, const float* D, float* dQ, int acc_dq, hipStream_t s) {
-  if ((long long)p.B * p.H * p.Nq == 0) return BURST_OK;
-  GenArgs a = make_args(p);
-  a.Q = Q; a.K = K; a.V = V; a.dO = dO; a.lse = lse; a.D = D; a.dQ = dQ; a.acc_dq = acc_dq;
+static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
+  make_args(a, p, ch, n);
+  a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
+}
+int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
+  GenArgs a = {};
+  bwd_args(a, p, io, ch, n);
   return gen_dispatch<GEN_DQ>(a, dtype, s);
 }
-
-int launch_bwd_dkv_generic(const KParams& p, int dtype, const void* Q, const void* K, const void* V,
-                           const void* dO, const float* lse, const float* D, float* dK, float* dV,
-                           int acc_dkv, hipStream_t s) {
-  if ((long long)p.B * p.H / p.group * p.Nc == 0) return BURST_OK;
-  GenArgs a = make_args(p);
-  a.Q = Q; a.K = K; a.V = V; a.dO = dO; a.lse = lse; a.D = D; a.dK = dK; a.dV = dV; a.acc_dkv = acc_dkv;
+int launch_bwd_dkv_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
+  GenArgs a = {};
+  bwd_args(a, p, io, ch, n);
   return gen_dispatch<GEN_DKV>(a, dtype, s);
 }
 
