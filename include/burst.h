@@ -203,7 +203,7 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
  * instead of storing and reloading it between launches. */
 typedef struct burst_chunk {
   const void* K; const void* V;      /* [B, kv_heads, Nc, d] of `dtype` */
-  float* dK; float* dV;              /* burst_walk_bwd: the same shapes, fp32; ignored by burst_walk_fwd */
+  void* dK; void* dV;                /* burst_walk_bwd: the same shapes, dense; ignored by burst_walk_fwd */
   const uint8_t* block_mask;         /* as in burst_params, for this chunk (edge: burst_params.block) */
   int64_t block_mask_stride;
   int64_t k_off;                     /* global position of row 0 */
@@ -214,7 +214,7 @@ typedef struct burst_chunk {
 /* burst_state_init, burst_local_fwd for each of the n_chunks chunks in order, burst_finalize: the same
  * O, lse and final state.  `p` gives everything but Nc, k_off, block_mask, block_mask_stride and
  * kv_strides, which are taken from the chunks.  workspace: device memory of at least
- * burst_walk_workspace_bytes(...) bytes, 16-byte aligned, contents undefined before and after, or NULL;
+ * burst_walk_workspace_bytes(..., 0) bytes, 16-byte aligned, contents undefined before and after, or NULL;
  * with it a slice of few rows is spread over the chip by splitting the keys into ranges whose partial
  * states are merged at the end (the sums then come in another order). */
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
@@ -222,13 +222,16 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
                    const burst_params* p, void* stream);
 /* burst_bwd_prepare (when O is given; D is then written, else read), then burst_local_bwd for each
  * chunk in order, with the dK and dV of the chunk.  accumulate_dq = 0: dQ is overwritten with the
- * contribution of all chunks; accumulate_dkv applies to every chunk's dK and dV. */
+ * contribution of all chunks; accumulate_dkv applies to every chunk's dK and dV.  dQ and the chunks' dK,
+ * dV are fp32 or, with half_grads, of `dtype` (each value is the fp32 sum rounded once); half_grads
+ * excludes both accumulate flags, and needs the workspace where burst_walk_workspace_bytes(..., 1) asks
+ * for more than (..., 0) does (BURST_ERR_SHAPE otherwise). */
 int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
-                   const float* lse, float* D, float* dQ, int accumulate_dq, int accumulate_dkv,
+                   const float* lse, float* D, void* dQ, int accumulate_dq, int accumulate_dkv, int half_grads,
                    void* workspace, size_t workspace_bytes, const burst_params* p, void* stream);
-/* Bytes of workspace either of the two can use for these arguments (0: none); an upper bound that
- * depends on the shapes only.  Host logic, no device call. */
-size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p);
+/* Bytes of workspace that either of the two (with these half_grads) can use for these arguments; 0: none.
+ * Host logic, no device call. */
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int half_grads);
 
 /* Alg. 1, body of the loop for one chunk exactly as printed, WITHOUT the tiling of
  * Sec. 2.4 (the "w/o LAO" variant of the paper's ablation, Tables 2-3): the whole

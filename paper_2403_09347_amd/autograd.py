@@ -40,15 +40,16 @@ class _BurstAttention(torch.autograd.Function):
         O, lse = walk.forward(ks, vs, k_offs, masks=masks)
         ctx.walk, ctx.ks, ctx.vs, ctx.k_offs, ctx.masks = walk, ks, vs, k_offs, masks
         ctx.mark_non_differentiable(lse)
+        ctx.set_materialize_grads(False)             # (no zeros for the gradient of lse)
         return O, lse
 
     @staticmethod
     def backward(ctx, dO, _dlse):
+        if dO is None:
+            return (None,) * (9 + 2 * len(ctx.ks))
         walk = ctx.walk
-        dQ, dKs, dVs = walk.backward(ctx.ks, ctx.vs, ctx.k_offs, dO.to(walk.Q.dtype), masks=ctx.masks)
-        dt = walk.Q.dtype
-        return (dQ.to(dt), None, None, None, None, None, None, None, None,
-                *[g.to(dt) for g in dKs], *[g.to(dt) for g in dVs])
+        dQ, dKs, dVs = walk.backward_in_dtype(ctx.ks, ctx.vs, ctx.k_offs, dO.to(walk.Q.dtype), masks=ctx.masks)
+        return (dQ, None, None, None, None, None, None, None, None, *dKs, *dVs)
 
 
 def burst_attention(q, k_chunks, v_chunks, scale=None, causal=False, q_off=0, window=0, block_masks=None, block=0):

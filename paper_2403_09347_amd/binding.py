@@ -88,11 +88,11 @@ def load():
                  "burst_bwd_prepare", "burst_local_bwd", "burst_event_record", "burst_version"):
         getattr(lib, name).restype = ctypes.c_int
     cp, sz, ci = ctypes.POINTER(BurstChunk), ctypes.c_size_t, ctypes.c_int
-    lib.burst_walk_workspace_bytes.argtypes = [cp, ci, pp]
+    lib.burst_walk_workspace_bytes.argtypes = [cp, ci, pp, ci]
     lib.burst_walk_workspace_bytes.restype = sz
     lib.burst_walk_fwd.argtypes = [vp, cp, ci, fp, fp, fp, vp, fp, vp, sz, pp, vp]
     lib.burst_walk_fwd.restype = ctypes.c_int
-    lib.burst_walk_bwd.argtypes = [vp, cp, ci, vp, vp, fp, fp, fp, ci, ci, vp, sz, pp, vp]
+    lib.burst_walk_bwd.argtypes = [vp, cp, ci, vp, vp, fp, fp, vp, ci, ci, ci, vp, sz, pp, vp]
     lib.burst_walk_bwd.restype = ctypes.c_int
     lib.burst_event_create.argtypes = []
     lib.burst_event_create.restype = vp
@@ -344,12 +344,15 @@ def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None):
         if masks is not None and masks[j] is not None:
             c.block_mask, c.block_mask_stride = _mask(masks[j], p.block, p.B, p.H, p.Nq, c.Nc)
         if dKs is not None:
-            c.dK, c.dV = _f32(dKs[j]).value, _f32(dVs[j]).value
+            dK, dV = dKs[j], dVs[j]
+            if dK.dtype != dKs[0].dtype or dV.dtype != dKs[0].dtype:
+                raise ValueError("one type for all gradients expected")
+            c.dK, c.dV = _ptr(dK).value, _ptr(dV).value
     return arr
 
 
-def burst_walk_workspace_bytes(chunks, p):
-    return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p)))
+def burst_walk_workspace_bytes(chunks, p, half_grads=False):
+    return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p), 1 if half_grads else 0))
 
 
 def _bytes(ws):
@@ -363,9 +366,13 @@ def burst_walk_fwd(Q, chunks, O_acc, m, l, O_out, lse, p, workspace=None):
 
 
 def burst_walk_bwd(Q, chunks, O, dO, lse, D, dQ, p, accumulate_dq=True, accumulate_dkv=False, workspace=None):
-    """O given: D = rowsum(dO o O) is computed first and written; O = None: D is read."""
-    _check(load().burst_walk_bwd(_q(Q, p), chunks, len(chunks), _q(O, p), _q(dO, p), _f32(lse), _f32(D), _f32(dQ),
-                                 1 if accumulate_dq else 0, 1 if accumulate_dkv else 0,
+    """O given: D = rowsum(dO o O) is computed first and written; O = None: D is read.  dQ and the chunks'
+    dK, dV: all fp32, or all of Q's type (then nothing accumulates)."""
+    half = dQ.dtype != torch.float32
+    if half and dQ.dtype != Q.dtype:
+        raise ValueError("gradients: float32 or the type of Q expected")
+    _check(load().burst_walk_bwd(_q(Q, p), chunks, len(chunks), _q(O, p), _q(dO, p), _f32(lse), _f32(D), _ptr(dQ),
+                                 1 if accumulate_dq else 0, 1 if accumulate_dkv else 0, 1 if half else 0,
                                  _ptr(workspace), _bytes(workspace), ctypes.byref(p), _stream()), "burst_walk_bwd")
 
 

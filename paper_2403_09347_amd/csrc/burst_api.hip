@@ -13,7 +13,7 @@ int launch_state_init(const KParams&, float*, float*, float*, hipStream_t);
 int launch_finalize(const KParams&, int, const float*, const float*, const float*, void*, float*, hipStream_t);
 int launch_merge_state(const KParams&, float*, float*, float*, const float*, const float*, const float*, hipStream_t);
 int launch_bwd_prepare(const KParams&, int, const void*, const void*, float*, hipStream_t);
-int launch_zero_fill(float*, long long, hipStream_t);
+int launch_zero_fill(float*, long long, bool half, hipStream_t);
 int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_fwd_generic(const KParams&, int, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dq_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);
@@ -389,6 +389,11 @@ int walk_splits(const std::vector<WalkChunk>& w) {
   const long long s = std::min(512 / blocks, tiles / 8);
   return s < 2 || tiles < 20 ? 1 : (int)s;
 }
+int dq_launches(const std::vector<WalkChunk>& w) {
+  int n = 0;
+  for_each_run(w, fwd_kernels, [&](const Kernels&, const KParams&, const Chunk*, int, bool, bool) { n++; return (int)BURST_OK; });
+  return n;
+}
 size_t split_bytes(const KParams& k, int splits) {
   return splits > 1 ? (size_t)splits * k.B * k.H * k.Nq * ((size_t)k.d + 2) * sizeof(float) : 0;
 }
@@ -490,10 +495,10 @@ int burst_local_bwd_materialized(const void* Q, const void* K_chunk, const void*
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   if (!have_q || !have_k) {                        // nothing to contract over: the contribution is zero
-    if (have_q && !accumulate_dq && (st = burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s)) != BURST_OK) return st;
+    if (have_q && !accumulate_dq && (st = burst::launch_zero_fill(dQ, bh * k.Nq * k.d, false, s)) != BURST_OK) return st;
     if (have_k && !accumulate_dkv) {
-      if ((st = burst::launch_zero_fill(dK_chunk, bh / k.group * k.Nc * k.d, s)) != BURST_OK) return st;
-      if ((st = burst::launch_zero_fill(dV_chunk, bh / k.group * k.Nc * k.d, s)) != BURST_OK) return st;
+      if ((st = burst::launch_zero_fill(dK_chunk, bh / k.group * k.Nc * k.d, false, s)) != BURST_OK) return st;
+      if ((st = burst::launch_zero_fill(dV_chunk, bh / k.group * k.Nc * k.d, false, s)) != BURST_OK) return st;
     }
     return BURST_OK;
   }
@@ -566,10 +571,10 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   // Degenerate sides: nothing to contract over, the contribution is zero.
   if (!have_q || !have_k) {
     if (want_dq && have_q && !accumulate_dq &&
-        (st = burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s)) != BURST_OK) return st;
+        (st = burst::launch_zero_fill(dQ, bh * k.Nq * k.d, false, s)) != BURST_OK) return st;
     if (want_dkv && have_k && !accumulate_dkv) {
-      if ((st = burst::launch_zero_fill(dK_chunk, bh / k.group * k.Nc * k.d, s)) != BURST_OK) return st;
-      if ((st = burst::launch_zero_fill(dV_chunk, bh / k.group * k.Nc * k.d, s)) != BURST_OK) return st;
+      if ((st = burst::launch_zero_fill(dK_chunk, bh / k.group * k.Nc * k.d, false, s)) != BURST_OK) return st;
+      if ((st = burst::launch_zero_fill(dV_chunk, bh / k.group * k.Nc * k.d, false, s)) != BURST_OK) return st;
     }
     return BURST_OK;
   }
@@ -578,7 +583,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, nullptr, 1};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -626,10 +631,13 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
                         0, accumulate_dkv, p, stream);
 }
 
-size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p) {
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int half_grads) {
   std::vector<WalkChunk> w;
   if (walk_chunks(chunks, n_chunks, p, false, w) != BURST_OK || w.empty()) return 0;
-  return split_bytes(w[0].k, walk_splits(w));
+  const KParams& k = w[0].k;
+  const size_t split = split_bytes(k, walk_splits(w));
+  if (!half_grads || dq_launches(w) == 1) return split;
+  return std::max(split, (size_t)k.B * k.H * k.Nq * k.d * sizeof(float));   // dQ in fp32 between the launches
 }
 
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
@@ -677,7 +685,7 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
 }
 
 int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
-                   const float* lse, float* D, float* dQ, int accumulate_dq, int accumulate_dkv,
+                   const float* lse, float* D, void* dQ, int accumulate_dq, int accumulate_dkv, int half_grads,
                    void* workspace, size_t workspace_bytes, const burst_params* p, void* stream) {
   KParams k;
   burst_params base;
@@ -689,6 +697,8 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   if (st != BURST_OK) return st;
   std::vector<WalkChunk> w;
   if ((st = walk_chunks(chunks, n_chunks, p, true, w)) != BURST_OK) return st;
+  if (half_grads && (accumulate_dq || accumulate_dkv)) return BURST_ERR_SHAPE;
+  const bool half = half_grads && p->dtype == BURST_BF16;
   const long long bh = (long long)k.B * k.H;
   const bool have_q = bh * k.Nq > 0;
   if (!have_q && w.empty()) return BURST_OK;
@@ -701,25 +711,31 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   hipStream_t s = (hipStream_t)stream;
   int splits = walk_splits(w);
   if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
+  auto zero = [&](void* ptr, long long n) { return burst::launch_zero_fill((float*)ptr, n, half, s); };
+  // dQ as bf16 by several launches: fp32 in the workspace between them
+  const bool staged = half && have_q && splits == 1 && !w.empty() && dq_launches(w) > 1;
+  if (staged && (workspace == nullptr || workspace_bytes < (size_t)bh * k.Nq * k.d * sizeof(float))) return BURST_ERR_SHAPE;
   return validated([&]() -> int {
     int e = BURST_OK;
     if (!have_q) {                                 // no rows: dK and dV are zero
       for (const WalkChunk& x : w) {
         if (accumulate_dkv) break;
-        if ((e = burst::launch_zero_fill((float*)x.c.dK, bh / k.group * x.c.Nc * k.d, s)) != BURST_OK) return e;
-        if ((e = burst::launch_zero_fill((float*)x.c.dV, bh / k.group * x.c.Nc * k.d, s)) != BURST_OK) return e;
+        if ((e = zero(x.c.dK, bh / k.group * x.c.Nc * k.d)) != BURST_OK) return e;
+        if ((e = zero(x.c.dV, bh / k.group * x.c.Nc * k.d)) != BURST_OK) return e;
       }
       return BURST_OK;
     }
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
-    if (w.empty()) return accumulate_dq ? (int)BURST_OK : burst::launch_zero_fill(dQ, bh * k.Nq * k.d, s);
-    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, (float*)workspace, splits};
+    if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
+    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
-      io.acc_dq = accumulate_dq != 0 || !first;
-      return dq_launch(f, kc, p->dtype, io, c, n, s);
+      BwdIo one = io;
+      one.acc_dq = accumulate_dq != 0 || !first;
+      if (staged) { one.dQ = workspace; one.half = 0; }
+      return dq_launch(f, kc, p->dtype, one, c, n, s);
     });
     if (e != BURST_OK) return e;
-    if (splits > 1 && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
+    if ((splits > 1 || staged) && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
     return for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
       return dkv_launch(f, kc, p->dtype, io, c, n, s);
     });

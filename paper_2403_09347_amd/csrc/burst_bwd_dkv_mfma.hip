@@ -57,6 +57,7 @@ struct DkvArgs {
   const float* lse; const float* D;
   int Nq, H, group;      // H counts batch x key/value heads; query heads per key/value head
   int causal, acc_dkv;
+  int half;              // dK, dV are bf16
   float c, scale;        // c = scale * log2(e)
   long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
@@ -463,6 +464,23 @@ burst_bwd_dkv_kernel(DkvArgs a) {
                    "+a"(dv[0]), "+a"(dv[1]), "+a"(dv[2]), "+a"(dv[3]));
   }
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
+  if (a.half) {
+    bf16* const dK16 = (bf16*)C.dK + (size_t)head * Nc * 128;
+    bf16* const dV16 = (bf16*)C.dV + (size_t)head * Nc * 128;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (key < Nc) {
+#pragma unroll
+        for (int db = 0; db < 4; db++) {
+          const size_t off = (size_t)key * 128 + db * 32;
+          store_pair_bf16(dK16 + off, dK16 + off + 128, lr, a.scale * dk[db][r], a.scale * dk[db][r + 1], key + 1 < Nc);
+          store_pair_bf16(dV16 + off, dV16 + off + 128, lr, dv[db][r], dv[db][r + 1], key + 1 < Nc);
+        }
+      }
+    }
+    return;
+  }
   float* dKh = (float*)C.dK + (size_t)head * Nc * 128;
   float* dVh = (float*)C.dV + (size_t)head * Nc * 128;
 #pragma unroll
@@ -497,7 +515,7 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
   DkvArgs a;
   a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D;
   a.Nq = p.Nq; a.H = p.B * p.H / p.group; a.group = p.group;     // workgroups are laid out over key/value heads
-  a.causal = p.causal; a.acc_dkv = io.acc_dkv;
+  a.causal = p.causal; a.acc_dkv = io.acc_dkv; a.half = io.half;
   a.c = p.scale * kLog2e; a.scale = p.scale;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.n = n; a.lay = p.lay;

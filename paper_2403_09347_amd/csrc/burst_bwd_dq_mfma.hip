@@ -94,7 +94,8 @@ __device__ __forceinline__ void mfma_vgpr_fence(f32x16 (&acc)[2]) {
 struct DqArgs {
   const bf16* Q; const bf16* dO;
   const float* lse; const float* D;
-  float* dQ;
+  void* dQ;              // fp32, or bf16 (half)
+  int half;
   int Nq, H, group;      // H counts batch x heads; query heads per key/value head
   int causal, acc_dq;
   float c, log2_scale;   // scale * log2(e), log2(scale)
@@ -133,7 +134,8 @@ burst_bwd_dq_kernel(DqArgs a) {
   const unsigned ktile = kpitch * DQ_BC;                         // ... between key tiles
   const float* lseh = a.lse + (size_t)head * a.Nq;
   const float* Dh = a.D + (size_t)head * a.Nq;
-  float* dQh = a.dQ + (size_t)head * a.Nq * 128;
+  float* const dQh = (float*)a.dQ + (size_t)head * a.Nq * 128;
+  bf16* const dQh16 = (bf16*)a.dQ + (size_t)head * a.Nq * 128;
 
   auto tiles_of = [&](int c, int& lo, int& hi) {   // key tiles of chunk c that some row of the workgroup sees: [lo, hi)
     const int Nc = a.ch[c].Nc;
@@ -206,7 +208,9 @@ burst_bwd_dq_kernel(DqArgs a) {
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
     for (int i = tid; i < DQ_BR * 32; i += 256) {
       const int row = qb * DQ_BR + (i >> 5);
-      if (row < a.Nq) *reinterpret_cast<f32x4*>(dQh + (size_t)row * 128 + (i & 31) * 4) = z;
+      if (row >= a.Nq) break;
+      if (a.half) *reinterpret_cast<unsigned long long*>(dQh16 + (size_t)row * 128 + (i & 31) * 4) = 0;
+      else *reinterpret_cast<f32x4*>(dQh + (size_t)row * 128 + (i & 31) * 4) = z;
     }
     return;
   }
@@ -526,7 +530,17 @@ burst_bwd_dq_kernel(DqArgs a) {
 #pragma unroll
   for (int rb = 0; rb < 2; rb++) {
     int row = q0 + rb * 32 + lr;
-    if (row < a.Nq) {
+    if (row < a.Nq && a.half) {
+#pragma unroll
+      for (int db = 0; db < 4; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) {
+          bf16x4 v;
+#pragma unroll
+          for (int b = 0; b < 4; b++) v[b] = (bf16)dq[rb][db][4 * q4 + b];
+          *reinterpret_cast<bf16x4*>(dQh16 + (size_t)row * 128 + db * 32 + 8 * q4 + 4 * h) = v;
+        }
+    } else if (row < a.Nq) {
       float* orow = dQh + (size_t)row * 128;
 #pragma unroll
       for (int db = 0; db < 4; db++)
@@ -545,7 +559,7 @@ burst_bwd_dq_kernel(DqArgs a) {
 int launch_bwd_dq_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   if (p.Nq <= 0) return BURST_OK;
   DqArgs a;
-  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ;
+  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half;
   a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
   a.causal = p.causal; a.acc_dq = io.acc_dq;
   a.c = p.scale * kLog2e; a.log2_scale = log2f(p.scale);

@@ -105,8 +105,9 @@ struct FwdIo {
 };
 struct BwdIo {
   const void* Q; const void* dO; const float* lse; const float* D;
-  float* dQ;
+  void* dQ;
   int acc_dq, acc_dkv;               // add to what the gradient buffers hold
+  int half;                          // dQ, dK, dV are bf16 tensors (the inputs' type) instead of fp32; nothing accumulates then
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
 };
 

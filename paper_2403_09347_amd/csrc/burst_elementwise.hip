@@ -104,67 +104,46 @@ merge_state_row_kernel(float* __restrict__ O_a, float* __restrict__ m_a, float* 
   }
 }
 
-// D = rowsum(dO o O): the threads of a row are `per_row` consecutive lanes (a power of two
-// <= 64 for the vector path), reduced with lane shuffles.
-template <typename T>
+// D = rowsum(dO o O).  L lanes per row (a power of two), each with 16 bytes of either tensor per step;
+// HBM bound.  65536 rows of d = 64: 10.1 us with one wavefront per row (of which 16 lanes had work), 4.6 us
+// with 8 lanes a row.
+template <typename T, int L>
 __global__ void __launch_bounds__(256)
 bwd_prepare_kernel(const T* __restrict__ O, const T* __restrict__ dO, float* __restrict__ D,
                    long long n_rows, int d, QRows qr) {
-  // one wavefront per row, lanes stride over the row in chunks of 4 elements when possible
-  const int lane = threadIdx.x & 63;
-  long long wave = ((long long)blockIdx.x * 256 + threadIdx.x) >> 6;
-  long long nwaves = ((long long)gridDim.x * 256) >> 6;
-  const bool vec = (d % 4) == 0;
-  for (long long row = wave; row < n_rows; row += nwaves) {
-    const T* o = O + qr.off(row);
-    const T* g = dO + qr.off(row);
+  constexpr int E = 16 / sizeof(T);
+  typedef __attribute__((ext_vector_type(E))) T vec;
+  const int part = threadIdx.x % L;
+  const long long stride = (long long)gridDim.x * (256 / L);
+  // (every lane stays in the loop as long as one of its wavefront has a row: the shuffles need them)
+  for (long long row = (long long)blockIdx.x * (256 / L) + threadIdx.x / L; row - (threadIdx.x & 63) / L < n_rows; row += stride) {
     float acc = 0.f;
-    if (vec) {
-      for (int c = lane * 4; c < d; c += 256) {
-        if (sizeof(T) == 4) {
-          f32x4 a = *reinterpret_cast<const f32x4*>(o + c);
-          f32x4 b = *reinterpret_cast<const f32x4*>(g + c);
-          for (int t = 0; t < 4; t++) acc += a[t] * b[t];
-        } else {
-          bf16x4 a = *reinterpret_cast<const bf16x4*>(o + c);
-          bf16x4 b = *reinterpret_cast<const bf16x4*>(g + c);
-          for (int t = 0; t < 4; t++) acc += (float)a[t] * (float)b[t];
-        }
+    if (row < n_rows) {
+      const size_t base = qr.off(row);
+      for (int c = part * E; c < d; c += L * E) {
+        const vec x = *reinterpret_cast<const vec*>(O + base + c), y = *reinterpret_cast<const vec*>(dO + base + c);
+#pragma unroll
+        for (int t = 0; t < E; t++) acc = __builtin_fmaf((float)x[t], (float)y[t], acc);
       }
-    } else {
-      for (int c = lane; c < d; c += 64) acc += (float)o[c] * (float)g[c];
     }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) D[row] = acc;
+#pragma unroll
+    for (int off = L / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (row < n_rows && part == 0) D[row] = acc;
   }
 }
-
-// Row-packed variant for d = 128 (32 lanes x 4 elements per row, two rows per wavefront):
-// fully coalesced 8-byte (bf16) or 16-byte (fp32) loads.
+// rows that do not start on 16 bytes: one wavefront per row
 template <typename T>
 __global__ void __launch_bounds__(256)
-bwd_prepare_d128_kernel(const T* __restrict__ O, const T* __restrict__ dO, float* __restrict__ D,
-                        long long n_rows, QRows qr) {
-  long long stride = (long long)gridDim.x * 256;
-  long long total = n_rows * 32;
-  long long total_pad = (total + 63) & ~63LL;      // keep whole wavefronts in the loop for the shuffles
-  for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < total_pad; k += stride) {
+bwd_prepare_row_kernel(const T* __restrict__ O, const T* __restrict__ dO, float* __restrict__ D,
+                       long long n_rows, int d, QRows qr) {
+  const int lane = threadIdx.x & 63;
+  const long long nwaves = ((long long)gridDim.x * 256) >> 6;
+  for (long long row = ((long long)blockIdx.x * 256 + threadIdx.x) >> 6; row < n_rows; row += nwaves) {
+    const size_t base = qr.off(row);
     float acc = 0.f;
-    long long row = k >> 5;
-    if (k < total) {
-      const size_t c = qr.off(row) + (size_t)(k & 31) * 4;
-      if (sizeof(T) == 4) {
-        f32x4 a = *reinterpret_cast<const f32x4*>(O + c);
-        f32x4 b = *reinterpret_cast<const f32x4*>(dO + c);
-        for (int t = 0; t < 4; t++) acc += a[t] * b[t];
-      } else {
-        bf16x4 a = *reinterpret_cast<const bf16x4*>(O + c);
-        bf16x4 b = *reinterpret_cast<const bf16x4*>(dO + c);
-        for (int t = 0; t < 4; t++) acc += (float)a[t] * (float)b[t];
-      }
-    }
-    for (int off = 16; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (k < total && (k & 31) == 0) D[row] = acc;
+    for (int c = lane; c < d; c += 64) acc += (float)O[base + c] * (float)dO[base + c];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) D[row] = acc;
   }
 }
 
@@ -233,9 +212,9 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
   }
 }
 
-// dQ = (acc ? dQ : 0) + the sum of `splits` partial dQ [splits][n], in that order.
+// dQ = (acc ? dQ : 0) + the sum of `splits` partial dQ [splits][n], in that order; half: dQ is bf16.
 __global__ void __launch_bounds__(256)
-sum_splits_kernel(const float* __restrict__ part, int splits, float* __restrict__ dQ, int acc, long long n4) {
+sum_splits_kernel(const float* __restrict__ part, int splits, void* __restrict__ dQ, int acc, int half, long long n4) {
   const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
   if (k >= n4) return;
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -244,8 +223,16 @@ sum_splits_kernel(const float* __restrict__ part, int splits, float* __restrict_
     const f32x4 x = reinterpret_cast<const f32x4*>(part)[(size_t)i * n4 + k];
     for (int t = 0; t < 4; t++) v[t] += x[t];
   }
-  reinterpret_cast<f32x4*>(dQ)[k] = v;
+  if (half) {
+    bf16x4 r;
+    for (int t = 0; t < 4; t++) r[t] = (bf16)v[t];
+    reinterpret_cast<bf16x4*>(dQ)[k] = r;
+  } else {
+    reinterpret_cast<f32x4*>(dQ)[k] = v;
+  }
 }
+
+__global__ void zero_tail_kernel(unsigned short* p) { *p = 0; }
 
 static inline unsigned grid_for(long long work_items, int per_block = 256, unsigned cap = 256 * 16) {
   long long b = (work_items + per_block - 1) / per_block;
@@ -299,7 +286,8 @@ int launch_sum_splits(const KParams& p, const BwdIo& io, hipStream_t s) {
   const long long n4 = (long long)p.B * p.H * p.Nq * p.d / 4, blocks = (n4 + 255) / 256;
   if (n4 == 0) return BURST_OK;
   if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  BURST_LAUNCH(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.dQ, io.acc_dq, n4);
+  BURST_LAUNCH(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.dQ, io.acc_dq,
+               io.half, n4);
   return launch_status();
 }
 
@@ -317,23 +305,36 @@ int launch_merge_state(const KParams& p, float* O_a, float* m_a, float* l_a,
   return launch_status();
 }
 
-int launch_bwd_prepare(const KParams& p, int dtype, const void* O, const void* dO, float* D, hipStream_t s) {
-  long long rows = (long long)p.B * p.H * p.Nq;
-  if (rows == 0) return BURST_OK;
-  if (p.d == 128) {
-    unsigned g = grid_for(rows * 32);
-    if (dtype == BURST_BF16) BURST_LAUNCH((bwd_prepare_d128_kernel<bf16>), dim3(g), dim3(256), 0, s, (const bf16*)O, (const bf16*)dO, D, rows, p.q_rows());
-    else BURST_LAUNCH((bwd_prepare_d128_kernel<float>), dim3(g), dim3(256), 0, s, (const float*)O, (const float*)dO, D, rows, p.q_rows());
-  } else {
-    unsigned g = grid_for(rows * 64);
-    if (dtype == BURST_BF16) BURST_LAUNCH((bwd_prepare_kernel<bf16>), dim3(g), dim3(256), 0, s, (const bf16*)O, (const bf16*)dO, D, rows, p.d, p.q_rows());
-    else BURST_LAUNCH((bwd_prepare_kernel<float>), dim3(g), dim3(256), 0, s, (const float*)O, (const float*)dO, D, rows, p.d, p.q_rows());
+template <typename T>
+static int prepare_for(const KParams& p, const T* O, const T* dO, float* D, long long rows, hipStream_t s) {
+  constexpr int E = 16 / sizeof(T);
+  if (p.d % E != 0) {
+    BURST_LAUNCH((bwd_prepare_row_kernel<T>), dim3(grid_for(rows * 64)), dim3(256), 0, s, O, dO, D, rows, p.d, p.q_rows());
+    return launch_status();
   }
+  const int pieces = p.d / E;                      // 16-byte pieces of a row
+  if (pieces > 8) BURST_LAUNCH((bwd_prepare_kernel<T, 16>), dim3(grid_for(rows * 16)), dim3(256), 0, s, O, dO, D, rows, p.d, p.q_rows());
+  else if (pieces > 4) BURST_LAUNCH((bwd_prepare_kernel<T, 8>), dim3(grid_for(rows * 8)), dim3(256), 0, s, O, dO, D, rows, p.d, p.q_rows());
+  else BURST_LAUNCH((bwd_prepare_kernel<T, 4>), dim3(grid_for(rows * 4)), dim3(256), 0, s, O, dO, D, rows, p.d, p.q_rows());
   return launch_status();
 }
 
-int launch_zero_fill(float* ptr, long long n, hipStream_t s) {
-  if (n <= 0) return BURST_OK;
+int launch_bwd_prepare(const KParams& p, int dtype, const void* O, const void* dO, float* D, hipStream_t s) {
+  const long long rows = (long long)p.B * p.H * p.Nq;
+  if (rows == 0) return BURST_OK;
+  return dtype == BURST_BF16 ? prepare_for(p, (const bf16*)O, (const bf16*)dO, D, rows, s)
+                             : prepare_for(p, (const float*)O, (const float*)dO, D, rows, s);
+}
+
+// n elements, fp32 or (half) bf16
+int launch_zero_fill(float* ptr, long long n, bool half, hipStream_t s) {
+  if (half) {
+    if (n % 2 != 0) {                              // an odd tail of two bytes
+      BURST_LAUNCH(zero_tail_kernel, dim3(1), dim3(1), 0, s, (unsigned short*)ptr + n - 1);
+    }
+    n /= 2;
+  }
+  if (n <= 0) return launch_status();
   BURST_LAUNCH(zero_fill_kernel, dim3(grid_for(n / 4 + 1)), dim3(256), 0, s, ptr, n);
   return launch_status();
 }

@@ -33,7 +33,8 @@ struct GenArgs {
   float* O_acc; float* m; float* l;               // forward state
   void* O_out; float* lse_out;                    // O_out != nullptr: the state is final after this launch
   const float* lse; const float* D;               // backward inputs
-  float* dQ;
+  void* dQ;                                       // fp32, or T (half), as dK and dV
+  int half;
   int Nq, d, BH;
   int causal, fresh;                              // fresh: the state before the launch is the initial one
   float scale, c;                                 // c = scale * log2(e)
@@ -399,7 +400,8 @@ bwd_dq_generic_kernel(GenArgs a) {
     for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = dq[db][r];
   __syncthreads();
   if (!ok) return;
-  float* const out = a.dQ + sr * a.d;
+  float* const out = (float*)a.dQ + sr * a.d;
+  T* const out16 = (T*)a.dQ + sr * a.d;
 #pragma unroll
   for (int rr = 0; rr < 16 / W; rr++) {
     const int r = w * (16 / W) + rr, mrow = reg_row(r, h);
@@ -409,7 +411,9 @@ bwd_dq_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
       const int col = R::col_of(db, mrow);
-      if (col < a.d) out[col] = (a.acc_dq ? out[col] : 0.f) + a.scale * v;
+      if (col >= a.d) continue;
+      if (a.half) out16[col] = (T)(a.scale * v);
+      else out[col] = (a.acc_dq ? out[col] : 0.f) + a.scale * v;
     }
   }
 }
@@ -559,20 +563,23 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
     __syncthreads();
-    float* const base = (float*)(which ? C.dV : C.dK);
+    void* const base = which ? C.dV : C.dK;
     const float f = which ? 1.f : a.scale;
 #pragma unroll
     for (int rr = 0; rr < 16 / W; rr++) {
       const int r = w * (16 / W) + rr, k = key0 + reg_row(r, h);
       if (k >= Nc) continue;
-      float* const out = base + ((size_t)kvhead * Nc + k) * a.d;
+      float* const out = (float*)base + ((size_t)kvhead * Nc + k) * a.d;
+      T* const out16 = (T*)base + ((size_t)kvhead * Nc + k) * a.d;
 #pragma unroll
       for (int db = 0; db < NB; db++) {
         float v = 0.f;
 #pragma unroll
         for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
         const int col = R::col_of(db, lr);
-        if (col < a.d) out[col] = (a.acc_dkv ? out[col] : 0.f) + f * v;
+        if (col >= a.d) continue;
+        if (a.half) out16[col] = (T)(f * v);
+        else out[col] = (a.acc_dkv ? out[col] : 0.f) + f * v;
       }
     }
   }
@@ -641,7 +648,7 @@ int launch_fwd_generic(const KParams& p, int dtype, const FwdIo& io, const Chunk
 }
 static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
   make_args(a, p, ch, n);
-  a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
+  a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
 }
 int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};

@@ -69,7 +69,8 @@ struct FwdArgsLite {
 struct BwdArgsLite {
   const bf16* Q; const bf16* dO;
   const float* lse; const float* D;
-  float* dQ;
+  void* dQ;                                      // fp32, or bf16 (half), as dK and dV
+  int half;
   float* part;                                   // partial dQ (splits > 1)
   int Nq, H, group;                              // H counts batch x heads (dQ: query heads, dK/dV: key/value heads)
   int causal, acc_dq, acc_dkv;
@@ -531,7 +532,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
   if (a.acc_dq && a.splits == 1 && ok) {
-    const float* const orow = a.dQ + srow * d;
+    const float* const orow = (const float*)a.dQ + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
@@ -617,8 +618,20 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
-  if (ok) {
-    float* const orow = a.splits > 1 ? a.part + ((size_t)split * a.H * a.Nq + srow) * d : a.dQ + srow * d;
+  if (ok && a.half && a.splits == 1) {
+    bf16* const orow = (bf16*)a.dQ + srow * d;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        if (S_PAD && db * 32 + 8 * q4 >= d) continue;
+        bf16x4 v;
+#pragma unroll
+        for (int b = 0; b < 4; b++) v[b] = (bf16)dq[db][4 * q4 + b];
+        *reinterpret_cast<bf16x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
+      }
+  } else if (ok) {
+    float* const orow = a.splits > 1 ? a.part + ((size_t)split * a.H * a.Nq + srow) * d : (float*)a.dQ + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
 #pragma unroll
@@ -866,6 +879,24 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   // lane = d column, registers = keys
+  if (a.half) {
+    bf16* const dK16 = (bf16*)C.dK + (size_t)kvhead * Nc * d;
+    bf16* const dV16 = (bf16*)C.dV + (size_t)kvhead * Nc * d;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (key < Nc) {
+#pragma unroll
+        for (int db = 0; db < S_DB; db++) {
+          if (S_PAD && db * 32 + lr >= d) continue;   // (d is even: both lanes of a pair take the same way)
+          const size_t off = (size_t)key * d + db * 32;
+          store_pair_bf16(dK16 + off, dK16 + off + d, lr, a.scale * dk[db][r], a.scale * dk[db][r + 1], key + 1 < Nc);
+          store_pair_bf16(dV16 + off, dV16 + off + d, lr, dv[db][r], dv[db][r + 1], key + 1 < Nc);
+        }
+      }
+    }
+    return;
+  }
   float* dKh = (float*)C.dK + (size_t)kvhead * Nc * d;
   float* dVh = (float*)C.dV + (size_t)kvhead * Nc * d;
 #pragma unroll
@@ -931,7 +962,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
 }
 
 static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
-  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ;
+  a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half;
   a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
   a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
   a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale; a.log2_scale = log2f(p.scale);

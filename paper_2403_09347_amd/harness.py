@@ -65,9 +65,9 @@ class RingWalk:
         p.block = self.block
         return p
 
-    def _scratch(self, chunks, p):
+    def _scratch(self, chunks, p, half_grads=False):
         """Workspace of a walk, kept by the walk (None: these sizes use none)."""
-        need = B.burst_walk_workspace_bytes(chunks, p)
+        need = B.burst_walk_workspace_bytes(chunks, p, half_grads)
         if need == 0:
             return None
         if self._workspace is None or self._workspace.numel() < need:
@@ -80,26 +80,44 @@ class RingWalk:
 
     def backward(self, Ks, Vs, k_offs, dO, dQ=None, dKs=None, dVs=None, use_D=True, masks=None):
         """dQ given: the gradient is added to it.  use_D = False: every chunk's call computes D for itself."""
+        if use_D:
+            accumulate = dQ is not None
+            if dQ is None:
+                dQ = torch.empty((self.Bt, self.H, self.Nq, self.d), device=self.Q.device, dtype=torch.float32)
+            return self._backward(Ks, Vs, k_offs, dO, dQ, dKs, dVs, masks, accumulate)
         dev = self.Q.device
-        accumulate = dQ is not None
         if dQ is None:
-            dQ = (torch.empty if use_D else torch.zeros)((self.Bt, self.H, self.Nq, self.d), device=dev, dtype=torch.float32)
+            dQ = torch.zeros((self.Bt, self.H, self.Nq, self.d), device=dev, dtype=torch.float32)
         if dKs is None:
             dKs = [torch.empty(K.shape, device=dev, dtype=torch.float32) for K in Ks]
             dVs = [torch.empty(V.shape, device=dev, dtype=torch.float32) for V in Vs]
-        if dO.stride() != self.Q.stride():         # dO and O lie in memory like Q
-            dO = torch.empty_strided(self.Q.shape, self.Q.stride(), device=dev, dtype=self.Q.dtype).copy_(dO)
-        if use_D:
-            p = self._walk_params()
-            chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs)
-            B.burst_walk_bwd(self.Q, chunks, self.O, dO, self.lse, self.D, dQ, p, accumulate_dq=accumulate,
-                             accumulate_dkv=False, workspace=self._scratch(chunks, p))
-            return dQ, dKs, dVs
+        dO = self._like_q(dO)
         for j in range(len(Ks)):
             B.burst_local_bwd(self.Q, Ks[j], Vs[j], self.O, dO, self.lse, None, dQ, dKs[j], dVs[j],
                               self.params(Ks[j].shape[2], k_offs[j], None if masks is None else masks[j], Ks[j]),
                               accumulate_dq=True, accumulate_dkv=False)
         return dQ, dKs, dVs
+
+    def backward_in_dtype(self, Ks, Vs, k_offs, dO, masks=None):
+        """The backward walk with all gradients in the type of Q (each the fp32 sum, rounded once)."""
+        dQ = torch.empty((self.Bt, self.H, self.Nq, self.d), device=self.Q.device, dtype=self.Q.dtype)
+        return self._backward(Ks, Vs, k_offs, dO, dQ, None, None, masks, False)
+
+    def _backward(self, Ks, Vs, k_offs, dO, dQ, dKs, dVs, masks, accumulate):
+        if dKs is None:
+            new = lambda x: torch.empty(x.shape, device=dQ.device, dtype=dQ.dtype)
+            dKs, dVs = [new(K) for K in Ks], [new(V) for V in Vs]
+        p = self._walk_params()
+        chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs)
+        B.burst_walk_bwd(self.Q, chunks, self.O, self._like_q(dO), self.lse, self.D, dQ, p, accumulate_dq=accumulate,
+                         accumulate_dkv=False, workspace=self._scratch(chunks, p, dQ.dtype != torch.float32))
+        return dQ, dKs, dVs
+
+    def _like_q(self, dO):
+        """dO and O lie in memory like Q."""
+        if dO.stride() == self.Q.stride():
+            return dO
+        return torch.empty_strided(self.Q.shape, self.Q.stride(), device=self.Q.device, dtype=self.Q.dtype).copy_(dO)
 
 
 class MaterializedWalk(RingWalk):
