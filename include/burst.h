@@ -216,7 +216,8 @@ typedef struct burst_chunk {
  * kv_strides, which are taken from the chunks.  workspace: device memory of at least
  * burst_walk_workspace_bytes(..., 0) bytes, 16-byte aligned, contents undefined before and after, or NULL;
  * with it a slice of few rows is spread over the chip by splitting the keys into ranges whose partial
- * states are merged at the end (the sums then come in another order). */
+ * states are merged at the end (the sums then come in another order).  O_acc, m, l may all be NULL: the
+ * state is then not kept (workspace: burst_walk_workspace_bytes(..., BURST_WALK_NO_STATE)). */
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
                    void* O_out, float* lse, void* workspace, size_t workspace_bytes,
                    const burst_params* p, void* stream);
@@ -224,14 +225,16 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
  * chunk in order, with the dK and dV of the chunk.  accumulate_dq = 0: dQ is overwritten with the
  * contribution of all chunks; accumulate_dkv applies to every chunk's dK and dV.  dQ and the chunks' dK,
  * dV are fp32 or, with half_grads, of `dtype` (each value is the fp32 sum rounded once); half_grads
- * excludes both accumulate flags, and needs the workspace where burst_walk_workspace_bytes(..., 1) asks
- * for more than (..., 0) does (BURST_ERR_SHAPE otherwise). */
+ * excludes both accumulate flags, and needs the workspace that burst_walk_workspace_bytes(...,
+ * BURST_WALK_HALF_GRADS) asks for (BURST_ERR_SHAPE if a part of it that it cannot do without is missing). */
 int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
                    const float* lse, float* D, void* dQ, int accumulate_dq, int accumulate_dkv, int half_grads,
                    void* workspace, size_t workspace_bytes, const burst_params* p, void* stream);
-/* Bytes of workspace that either of the two (with these half_grads) can use for these arguments; 0: none.
- * Host logic, no device call. */
-size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int half_grads);
+/* Bytes of workspace that either of the two can use (or, under these flags, needs) for these arguments;
+ * 0: none.  Host logic, no device call. */
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int flags);
+#define BURST_WALK_HALF_GRADS 1   /* for burst_walk_bwd with half_grads */
+#define BURST_WALK_NO_STATE 2     /* for burst_walk_fwd without O_acc, m, l */
 
 /* Alg. 1, body of the loop for one chunk exactly as printed, WITHOUT the tiling of
  * Sec. 2.4 (the "w/o LAO" variant of the paper's ablation, Tables 2-3): the whole

@@ -5,7 +5,9 @@ PyTorch tensors are used as device buffers; kernels are enqueued on torch's curr
 stream.  There is no fallback: if the library is missing, loading raises.
 """
 import ctypes
+import importlib.util
 import os
+import re
 
 import torch
 
@@ -50,7 +52,29 @@ class BurstError(RuntimeError):
         super().__init__(f"{where}: {strerror(code)} (status {code})")
 
 
-_lib = None
+def from_native(e):
+    """The exception of a failed library call inside the torch module as a BurstError (others as they are)."""
+    m = re.match(r"(burst_\w+): .* \(status (-\d+)\)", str(e))
+    return BurstError(int(m.group(2)), m.group(1)) if m else e
+
+
+_lib, _torch_module = None, None
+TORCH_LIB_PATH = os.path.join(_HERE, "_burst_torch.so")
+
+
+def load_torch_module():
+    """Loads the torch module of the differentiable call (once).  Raises if it has not been built."""
+    global _torch_module
+    if _torch_module is None:
+        if not os.path.exists(TORCH_LIB_PATH):
+            raise FileNotFoundError(
+                f"{TORCH_LIB_PATH} not found: build it first (python -c 'import __graft_entry__ as g; g.build()')")
+        load()
+        spec = importlib.util.spec_from_file_location("_burst_torch", TORCH_LIB_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _torch_module = module
+    return _torch_module
 
 
 def load():
@@ -351,8 +375,11 @@ def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None):
     return arr
 
 
-def burst_walk_workspace_bytes(chunks, p, half_grads=False):
-    return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p), 1 if half_grads else 0))
+BURST_WALK_HALF_GRADS, BURST_WALK_NO_STATE = 1, 2
+
+
+def burst_walk_workspace_bytes(chunks, p, flags=0):
+    return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p), int(flags)))
 
 
 def _bytes(ws):
@@ -360,7 +387,7 @@ def _bytes(ws):
 
 
 def burst_walk_fwd(Q, chunks, O_acc, m, l, O_out, lse, p, workspace=None):
-    """chunks: see chunk_array.  workspace: None or a contiguous device tensor."""
+    """chunks: see chunk_array.  workspace: None or a contiguous device tensor.  O_acc, m, l: None = not kept."""
     _check(load().burst_walk_fwd(_q(Q, p), chunks, len(chunks), _f32(O_acc), _f32(m), _f32(l), _q(O_out, p), _f32(lse),
                                  _ptr(workspace), _bytes(workspace), ctypes.byref(p), _stream()), "burst_walk_fwd")
 

@@ -28,6 +28,7 @@ int launch_bwd_dkv_generic(const KParams&, int, const BwdIo&, const Chunk*, int,
   int launch_bwd_dkv(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);        \
   }
 int launch_merge_splits(const KParams&, const FwdIo&, hipStream_t);
+int launch_fill_unseen(const KParams&, int, void*, float*, hipStream_t);
 int launch_sum_splits(const KParams&, const BwdIo&, hipStream_t);
 BURST_DECLARE_PLAIN(d64)
 BURST_DECLARE_PLAIN(d128p)
@@ -631,13 +632,17 @@ int burst_local_bwd_dkv(const void* Q, const void* K_chunk, const void* V_chunk,
                         0, accumulate_dkv, p, stream);
 }
 
-size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int half_grads) {
+size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int flags) {
   std::vector<WalkChunk> w;
   if (walk_chunks(chunks, n_chunks, p, false, w) != BURST_OK || w.empty()) return 0;
   const KParams& k = w[0].k;
-  const size_t split = split_bytes(k, walk_splits(w));
-  if (!half_grads || dq_launches(w) == 1) return split;
-  return std::max(split, (size_t)k.B * k.H * k.Nq * k.d * sizeof(float));   // dQ in fp32 between the launches
+  const size_t rows = (size_t)k.B * k.H * k.Nq;
+  size_t need = split_bytes(k, walk_splits(w));
+  if (flags != 0 && dq_launches(w) > 1) {          // between the launches: dQ in fp32, the state
+    if (flags & BURST_WALK_HALF_GRADS) need = std::max(need, rows * k.d * sizeof(float));
+    if (flags & BURST_WALK_NO_STATE) need = std::max(need, rows * ((size_t)k.d + 8) * sizeof(float));
+  }
+  return need;
 }
 
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
@@ -654,10 +659,18 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
   std::vector<WalkChunk> w;
   if ((st = walk_chunks(chunks, n_chunks, p, false, w)) != BURST_OK) return st;
   if ((long long)k.B * k.H * k.Nq == 0) return BURST_OK;
-  REQUIRE_PTR(Q); REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l); REQUIRE_PTR(O_out); REQUIRE_PTR(lse);
+  REQUIRE_PTR(Q); REQUIRE_PTR(O_out); REQUIRE_PTR(lse);
+  const bool keep = O_acc != nullptr || m != nullptr || l != nullptr;
+  if (keep) { REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l); }
   if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  if (!keep && (w.empty() || dq_launches(w) > 1)) {   // (as many launches as dQ takes)
+    const size_t rows = (size_t)k.B * k.H * k.Nq;
+    if (w.empty()) return burst::launch_fill_unseen(k, p->dtype, O_out, lse, s);
+    if (workspace == nullptr || workspace_bytes < rows * ((size_t)k.d + 8) * sizeof(float)) return BURST_ERR_SHAPE;
+    O_acc = (float*)workspace; m = O_acc + rows * k.d; l = m + (rows + 3) / 4 * 4;
+  }
   int splits = walk_splits(w);
   if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
   if (splits > 1) {

@@ -98,7 +98,7 @@ inline Chunk chunk_of(const KParams& p, const void* K, const void* V, void* dK, 
 // What a forward (backward) launch reads and writes beside its chunks.
 struct FwdIo {
   const void* Q;
-  float* O_acc; float* m; float* l;  // running state
+  float* O_acc; float* m; float* l;  // running state (nullptr: not kept; `fresh` and O_out only)
   void* O_out; float* lse;           // O_out != nullptr: the state is final after this launch, write these too
   int fresh;                         // the state before the launch is the initial one, whatever the buffers hold
   float* part; int splits;           // splits > 1: partial states of that many key ranges go to `part` instead

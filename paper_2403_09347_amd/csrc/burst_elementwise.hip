@@ -199,7 +199,7 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
   }
   __syncthreads();
   if (!live) return;
-  if (fresh || mg != BURST_NEG_INF) {
+  if (O_acc != nullptr && (fresh || mg != BURST_NEG_INF)) {
     *state = o;
     if (c == 0) { m[row] = m_st; l[row] = lsum; }
   }
@@ -229,6 +229,18 @@ sum_splits_kernel(const float* __restrict__ part, int splits, void* __restrict__
     reinterpret_cast<bf16x4*>(dQ)[k] = r;
   } else {
     reinterpret_cast<f32x4*>(dQ)[k] = v;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+fill_unseen_kernel(T* __restrict__ O_out, float* __restrict__ lse, long long n_rows, int d, QRows qr) {
+  const long long stride = (long long)gridDim.x * 256;
+  for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < n_rows * d; k += stride) {
+    const long long row = k / d;
+    const int c = (int)(k - row * d);
+    O_out[qr.off(row) + c] = (T)0.f;
+    if (c == 0) lse[row] = BURST_NEG_INF;
   }
 }
 
@@ -268,6 +280,16 @@ int launch_finalize(const KParams& p, int dtype, const float* O_acc, const float
     if (vec) BURST_LAUNCH((finalize_kernel<float, 4>), dim3(g), dim3(256), 0, s, O_acc, m, l, (float*)O_out, lse, rows, p.d, p.q_rows());
     else BURST_LAUNCH((finalize_kernel<float, 1>), dim3(g), dim3(256), 0, s, O_acc, m, l, (float*)O_out, lse, rows, p.d, p.q_rows());
   }
+  return launch_status();
+}
+
+// O = 0, lse = -inf: the output of a walk without any key
+int launch_fill_unseen(const KParams& p, int dtype, void* O_out, float* lse, hipStream_t s) {
+  const long long rows = (long long)p.B * p.H * p.Nq;
+  if (rows == 0) return BURST_OK;
+  const unsigned g = grid_for(rows * p.d);
+  if (dtype == BURST_BF16) BURST_LAUNCH(fill_unseen_kernel<bf16>, dim3(g), dim3(256), 0, s, (bf16*)O_out, lse, rows, p.d, p.q_rows());
+  else BURST_LAUNCH(fill_unseen_kernel<float>, dim3(g), dim3(256), 0, s, (float*)O_out, lse, rows, p.d, p.q_rows());
   return launch_status();
 }
 

@@ -588,7 +588,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     float m_st = a.fresh ? BURST_NEG_INF : a.m[srow];
     if (m2[rb] != reference_of(m_st)) m_st = m2[rb] * kLn2;
     asm volatile("" : "+v"(m_st));                 // (m as the next launch would load it)
-    if (a.fresh || m2[rb] != BURST_NEG_INF) {      // rows that never saw a key keep their state
+    if (a.O_acc != nullptr && (a.fresh || m2[rb] != BURST_NEG_INF)) {   // rows that never saw a key keep their state
       float* const orow = a.O_acc + srow * 128;
 #pragma unroll
       for (int db = 0; db < 4; db++)

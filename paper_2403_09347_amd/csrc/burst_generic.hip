@@ -274,7 +274,7 @@ fwd_generic_kernel(GenArgs a) {
   const float m_st = saw || a.fresh ? m_new * kLn2 : a.m[sr];
   __syncthreads();                                 // every wavefront has read the row's old m and l
   if (w == 0 && h == 0) {
-    if (saw || a.fresh) { a.m[sr] = m_st; a.l[sr] = l_new; }
+    if (a.O_acc != nullptr && (saw || a.fresh)) { a.m[sr] = m_st; a.l[sr] = l_new; }
     if (a.O_out != nullptr) a.lse_out[sr] = l_new > 0.f ? m_st + __logf(l_new) : BURST_NEG_INF;
   }
   const float inv = l_new > 0.f ? 1.0f / l_new : 0.f;
@@ -291,7 +291,7 @@ fwd_generic_kernel(GenArgs a) {
       const int col = R::col_of(db, mrow);
       if (col < a.d) {
         const float x = (fa == 0.f ? 0.f : fa * orow[col]) + fb * v;
-        if (saw || a.fresh) orow[col] = x;
+        if (a.O_acc != nullptr && (saw || a.fresh)) orow[col] = x;
         if (out != nullptr) out[col] = (T)(l_new > 0.f ? x * inv : 0.f);
       }
     }

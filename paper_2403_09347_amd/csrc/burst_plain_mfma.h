@@ -398,7 +398,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     }
     return;
   }
-  if (a.fresh || m2 != BURST_NEG_INF) {            // rows that never saw a key keep their state
+  if (a.O_acc != nullptr && (a.fresh || m2 != BURST_NEG_INF)) {   // rows that never saw a key keep their state
     float* const orow = a.O_acc + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)

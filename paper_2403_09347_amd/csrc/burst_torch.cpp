@@ -1,0 +1,173 @@
+// The differentiable call behind autograd.burst_attention: attention of a query slice against key/value
+// chunks as one torch autograd node, in C++.  Argument marshalling and buffers only; every arithmetic
+// step is a call into libburst.so (paper Alg. 1 forward, Alg. 2 backward).
+// Why native: in Python the two halves of a call ran on two threads (autograd's backward thread is another
+// one) and cost 200 us of host time at any size, several times the GPU time of a short sequence.
+#include <torch/extension.h>
+#include <c10/hip/HIPStream.h>
+
+#include <cmath>
+#include <string>
+#include <vector>
+
+#include "../../include/burst.h"
+
+namespace {
+
+using torch::Tensor;
+using torch::autograd::AutogradContext;
+using torch::autograd::variable_list;
+
+void check(int status, const char* where) {
+  TORCH_CHECK(status == BURST_OK, where, ": ", burst_strerror(status), " (status ", status, ")");
+}
+
+// Whether the library can read a [B, H, rows, d] tensor where it lies: last dimension contiguous, the
+// other strides and the base address multiples of 16 bytes, rows not overlapping.
+bool addressable(const Tensor& t) {
+  if (t.dim() != 4 || (t.size(3) != 1 && t.stride(3) != 1)) return false;
+  if (reinterpret_cast<uintptr_t>(t.data_ptr()) % 16 != 0) return false;
+  const int64_t unit = 16 / (int64_t)t.element_size();
+  for (int i = 0; i < 3; i++)
+    if (t.size(i) != 1 && (t.stride(i) <= 0 || t.stride(i) % unit != 0)) return false;
+  return t.size(2) == 1 || t.stride(2) >= t.size(3);
+}
+
+// Strides for the parameter block; all zero for a contiguous tensor.  Dimensions of size 1 (whose stride
+// addresses nothing) get the row length.
+void set_strides(int64_t (&out)[3], const Tensor& t) {
+  const bool dense = t.is_contiguous();
+  for (int i = 0; i < 3; i++) out[i] = dense ? 0 : t.size(i) > 1 ? t.stride(i) : t.size(3);
+}
+
+struct Call {                        // what forward and backward have in common
+  burst_params p{};
+  std::vector<burst_chunk> chunks;
+};
+
+Call describe(const Tensor& q, const variable_list& ks, const variable_list& vs, const variable_list& masks, double scale,
+              bool causal, int64_t q_off, int64_t window, int64_t block) {
+  Call c;
+  burst_params& p = c.p;
+  p.B = (int32_t)q.size(0); p.H = (int32_t)q.size(1); p.Nq = (int32_t)q.size(2); p.d = (int32_t)q.size(3);
+  p.dtype = q.scalar_type() == torch::kBFloat16 ? BURST_BF16 : BURST_F32;
+  p.causal = causal; p.scale = (float)scale; p.q_off = q_off; p.window = window; p.block = (int32_t)block;
+  p.kv_heads = ks[0].size(1) != q.size(1) ? (int32_t)ks[0].size(1) : 0;
+  set_strides(p.q_strides, q);
+  int64_t at = 0;
+  c.chunks.resize(ks.size());
+  for (size_t i = 0; i < ks.size(); i++) {
+    burst_chunk& k = c.chunks[i];
+    k = burst_chunk{};
+    k.K = ks[i].data_ptr(); k.V = vs[i].data_ptr();
+    k.Nc = (int32_t)ks[i].size(2);
+    k.k_off = at;
+    at += ks[i].size(2);
+    set_strides(k.kv_strides, ks[i]);
+    if (!masks.empty()) {
+      const Tensor& m = masks[i];
+      const int64_t rows = (q.size(2) + block - 1) / block, cols = (ks[i].size(2) + block - 1) / block;
+      const bool one = m.dim() == 2 && m.size(0) == rows && m.size(1) == cols;
+      const bool each = m.dim() == 4 && m.size(0) == q.size(0) && m.size(1) == q.size(1) && m.size(2) == rows && m.size(3) == cols;
+      TORCH_CHECK_VALUE(m.scalar_type() == torch::kByte && m.is_cuda() && m.is_contiguous(),
+                        "block_mask: contiguous uint8 device tensor expected");
+      TORCH_CHECK_VALUE(one || each, "block_mask: shape must be [ceil(Nq/block), ceil(Nc/block)], alone or after [B, H]");
+      k.block_mask = m.data_ptr<uint8_t>();
+      k.block_mask_stride = each ? rows * cols : 0;
+    }
+  }
+  return c;
+}
+
+Tensor scratch(const Call& c, int flags, const Tensor& like) {
+  const size_t need = burst_walk_workspace_bytes(c.chunks.data(), (int)c.chunks.size(), &c.p, flags);
+  return need ? torch::empty({(int64_t)need}, like.options().dtype(torch::kByte)) : Tensor();
+}
+void* ptr(const Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
+size_t bytes(const Tensor& t) { return t.defined() ? (size_t)t.nbytes() : 0; }
+void* stream_of(const Tensor& t) { return (void*)c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+class Attention : public torch::autograd::Function<Attention> {
+ public:
+  // kvm: the chunks' keys, then their values, then (n_masks of them) their block flags
+  static variable_list forward(AutogradContext* ctx, const Tensor& q_in, at::TensorList kvm, int64_t n_masks, double scale,
+                               bool causal, int64_t q_off, int64_t window, int64_t block) {
+    const size_t n = (kvm.size() - (size_t)n_masks) / 2;
+    const Tensor q = addressable(q_in) ? q_in : q_in.contiguous();
+    variable_list ks(kvm.begin(), kvm.begin() + n), vs(kvm.begin() + n, kvm.begin() + 2 * n), masks(kvm.begin() + 2 * n, kvm.end());
+    for (size_t i = 0; i < n; i++) {              // K and V as they are if one set of strides addresses both, else copies
+      Tensor &k = ks[i], &v = vs[i];
+      bool same = addressable(k) && addressable(v) && k.is_contiguous() == v.is_contiguous() && k.sizes() == v.sizes();
+      for (int j = 0; j < 3 && same; j++) same = k.size(j) == 1 || k.stride(j) == v.stride(j);
+      if (!same) { k = k.contiguous(); v = v.contiguous(); }
+    }
+    const Call c = describe(q, ks, vs, masks, scale, causal, q_off, window, block);
+    Tensor O = torch::empty_strided(q.sizes(), q.strides(), q.options());   // O lies in memory like Q
+    Tensor lse = torch::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(torch::kFloat));
+    const Tensor ws = scratch(c, BURST_WALK_NO_STATE, q);
+    check(burst_walk_fwd(q.data_ptr(), c.chunks.data(), (int)n, nullptr, nullptr, nullptr, O.data_ptr(), lse.data_ptr<float>(),
+                         ptr(ws), bytes(ws), &c.p, stream_of(q)), "burst_walk_fwd");
+    variable_list saved = {q, O, lse};
+    for (auto* l : {&ks, &vs, &masks}) saved.insert(saved.end(), l->begin(), l->end());
+    ctx->save_for_backward(saved);
+    ctx->saved_data["n"] = (int64_t)n;
+    ctx->saved_data["scale"] = scale;
+    ctx->saved_data["causal"] = causal;
+    ctx->saved_data["q_off"] = q_off;
+    ctx->saved_data["window"] = window;
+    ctx->saved_data["block"] = block;
+    ctx->mark_non_differentiable({lse});
+    ctx->set_materialize_grads(false);            // (no zeros for the gradient of lse)
+    return {O, lse};
+  }
+
+  static variable_list backward(AutogradContext* ctx, variable_list grads) {
+    const variable_list s = ctx->get_saved_variables();
+    const size_t n = (size_t)ctx->saved_data["n"].toInt();
+    variable_list out(1 + (s.size() - 3) + 6);    // q, kvm, and six arguments that are no tensors
+    if (!grads[0].defined()) return out;
+    const Tensor &q = s[0], &O = s[1], &lse = s[2];
+    const variable_list ks(s.begin() + 3, s.begin() + 3 + n), vs(s.begin() + 3 + n, s.begin() + 3 + 2 * n),
+        masks(s.begin() + 3 + 2 * n, s.end());
+    Call c = describe(q, ks, vs, masks, ctx->saved_data["scale"].toDouble(), ctx->saved_data["causal"].toBool(),
+                      ctx->saved_data["q_off"].toInt(), ctx->saved_data["window"].toInt(), ctx->saved_data["block"].toInt());
+    Tensor g = grads[0].to(q.scalar_type());
+    if (g.strides() != q.strides()) g = torch::empty_strided(q.sizes(), q.strides(), q.options()).copy_(g);   // dO lies in memory like Q
+    Tensor D = torch::empty_like(lse), dQ = torch::empty(q.sizes(), q.options());
+    out[0] = dQ;
+    for (size_t i = 0; i < n; i++) {
+      out[1 + i] = torch::empty(ks[i].sizes(), ks[i].options());
+      out[1 + n + i] = torch::empty(vs[i].sizes(), vs[i].options());
+      c.chunks[i].dK = out[1 + i].data_ptr();
+      c.chunks[i].dV = out[1 + n + i].data_ptr();
+    }
+    const Tensor ws = scratch(c, BURST_WALK_HALF_GRADS, q);
+    check(burst_walk_bwd(q.data_ptr(), c.chunks.data(), (int)n, O.data_ptr(), g.data_ptr(), lse.data_ptr<float>(),
+                         D.data_ptr<float>(), dQ.data_ptr(), 0, 0, 1, ptr(ws), bytes(ws), &c.p, stream_of(q)), "burst_walk_bwd");
+    return out;
+  }
+};
+
+std::vector<Tensor> attention(const Tensor& q, const std::vector<Tensor>& ks, const std::vector<Tensor>& vs,
+                              const std::vector<Tensor>& masks, double scale, bool causal, int64_t q_off, int64_t window,
+                              int64_t block) {
+  TORCH_CHECK_VALUE(!ks.empty() && ks.size() == vs.size(), "one key and one value tensor per chunk, at least one chunk, expected");
+  TORCH_CHECK_VALUE(masks.empty() || masks.size() == ks.size(), "one block mask per chunk expected");
+  TORCH_CHECK_VALUE(q.dim() == 4 && (q.scalar_type() == torch::kBFloat16 || q.scalar_type() == torch::kFloat),
+                    "q: [B, H, Nq, d] of bfloat16 or float32 expected");
+  variable_list kvm(ks);
+  kvm.insert(kvm.end(), vs.begin(), vs.end());
+  for (const Tensor& t : kvm) {
+    TORCH_CHECK_VALUE(t.dim() == 4 && t.scalar_type() == q.scalar_type() && t.size(0) == q.size(0) && t.size(1) == ks[0].size(1) &&
+                      t.size(3) == q.size(3), "keys and values: [B, Hkv, Nc, d] of the type of q expected");
+    TORCH_CHECK_VALUE(t.is_cuda() && t.device() == q.device(), "tensors on one device expected");
+  }
+  kvm.insert(kvm.end(), masks.begin(), masks.end());
+  return Attention::apply(q, at::TensorList(kvm), (int64_t)masks.size(), scale, causal, q_off, window, block);
+}
+
+}  // namespace
+
+PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
+  m.def("attention", &attention, pybind11::call_guard<pybind11::gil_scoped_release>());
+}

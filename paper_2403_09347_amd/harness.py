@@ -65,9 +65,9 @@ class RingWalk:
         p.block = self.block
         return p
 
-    def _scratch(self, chunks, p, half_grads=False):
+    def _scratch(self, chunks, p, flags=0):
         """Workspace of a walk, kept by the walk (None: these sizes use none)."""
-        need = B.burst_walk_workspace_bytes(chunks, p, half_grads)
+        need = B.burst_walk_workspace_bytes(chunks, p, flags)
         if need == 0:
             return None
         if self._workspace is None or self._workspace.numel() < need:
@@ -110,7 +110,7 @@ class RingWalk:
         p = self._walk_params()
         chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs)
         B.burst_walk_bwd(self.Q, chunks, self.O, self._like_q(dO), self.lse, self.D, dQ, p, accumulate_dq=accumulate,
-                         accumulate_dkv=False, workspace=self._scratch(chunks, p, dQ.dtype != torch.float32))
+                         accumulate_dkv=False, workspace=self._scratch(chunks, p, B.BURST_WALK_HALF_GRADS if dQ.dtype != torch.float32 else 0))
         return dQ, dKs, dVs
 
     def _like_q(self, dO):

@@ -93,3 +93,36 @@ def test_walk_calls_without_a_visible_or_any_chunk():
         assert torch.all(O == 0) and torch.all(torch.isneginf(lse)) and torch.all(walk.O_acc == 0)
         assert torch.all(walk.l == 0) and torch.all(torch.isneginf(walk.m)) and torch.all(dQ == 0) and torch.all(kept == 2.0)
         assert all(torch.all(g == 0) for g in dKs + dVs)
+
+
+def test_differentiable_call_partial_gradients_and_errors():
+    """The native autograd node: gradients for some inputs only, no gradient at all, views it cannot read in
+    place, and the exceptions of bad arguments."""
+    from paper_2403_09347_amd.autograd import burst_attention
+    case = workloads.make_case(B=1, H=4, kv_heads=2, d=64, Nq=70, chunk_rows=[64, 33], dtype="bf16", seed=5, device=DEV,
+                               causal=True, q_off=27)
+    q, ks, vs = case["Q"], case["K"], case["V"]
+    ref = [t.clone().requires_grad_(True) for t in [q, *ks, *vs]]
+    O, lse = burst_attention(ref[0], ref[1:3], ref[3:5], causal=True, q_off=27)
+    full = torch.autograd.grad(O, ref, case["dO"])
+    for wanted in ([0], [2], [1, 4]):
+        some = [t.clone() for t in [q, *ks, *vs]]
+        for i in wanted:
+            some[i].requires_grad_(True)
+        O1, lse1 = burst_attention(some[0], some[1:3], some[3:5], causal=True, q_off=27)
+        assert torch.equal(O1, O) and torch.equal(lse1, lse) and not lse1.requires_grad
+        for i, g in zip(wanted, torch.autograd.grad(O1, [some[i] for i in wanted], case["dO"])):
+            assert torch.equal(g, full[i])
+    with torch.no_grad():
+        assert not burst_attention(ref[0], ref[1:3], ref[3:5], causal=True, q_off=27)[0].requires_grad
+    # rows 130 elements apart start off the 16-byte grid: copied, same results
+    wide = torch.zeros((1, 4, 70, 130), device=DEV, dtype=torch.bfloat16)
+    wide[..., :64] = q
+    O2, _ = burst_attention(wide[..., :64], ks, vs, causal=True, q_off=27)
+    assert torch.equal(O2, O)
+    with pytest.raises(B.BurstError):
+        burst_attention(q, ks, vs, scale=-1.0)
+    with pytest.raises(ValueError):
+        burst_attention(q, ks, vs, block_masks=[torch.ones((1, 1), device=DEV)] * 2, block=64)
+    with pytest.raises(ValueError):
+        burst_attention(q, [k.float() for k in ks], vs)
