@@ -4,18 +4,83 @@
 
 namespace burst {
 
-// Store of two neighbouring keys' values of one column per lane (lane = column lr, odd and even columns on
-// neighbouring lanes) as bf16: even lanes store the first key's pair of columns, odd lanes the
-// second key's, four bytes each.
-__device__ __forceinline__ void store_pair_bf16(bf16* first, bf16* second, int lr, float a, float b, bool has_second) {
-  const bool odd = (lr & 1) != 0;
-  const float give = odd ? a : b;
-  const float got = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
-  bf16x2 v;
-  v[0] = (bf16)(odd ? got : a);
-  v[1] = (bf16)(odd ? b : got);
-  bf16* const p = odd ? second + (lr - 1) : first + lr;
-  if (!odd || has_second) *reinterpret_cast<bf16x2*>(p) = v;
+// Stores a wavefront's 32 keys of dK (times `scale`) and dV.  Layout of the accumulators: lane = column
+// db*32 + lr, register r = key key0 + 8*(r/4) + 4h + r%4.  `dK`, `dV`: key 0 of the head, rows of d values,
+// fp32 or, `half`, bf16.  Keys past Nc and (PAD) columns past d lie outside the buffers' range (at most
+// 4 Mi rows x 512 bytes), so there is not one branch or 64-bit address in here.
+// Bound by the stores, which must follow each other without a wait: with the loads of `acc` on a way of
+// their own.  (As one loop, old = acc ? load : 0, the compiler waited for every store before the next: a
+// workgroup of 128 keys then took 13.7 us on its 128 KB.)
+// bf16: a lane holds one column of two neighbouring keys; neighbouring lanes exchange, so that even lanes
+// store the first key's pair of columns and odd lanes the second key's, four bytes each.
+template <int DB, bool PAD>
+__device__ __forceinline__ void store_dkv(const f32x16 (&dk)[DB], const f32x16 (&dv)[DB], void* dK, void* dV, int Nc, int d,
+                                          int key0, int lr, int h, float scale, int half, int acc) {
+  const unsigned pitch = (unsigned)d * (half ? 2u : 4u);
+  const unsigned bytes = (unsigned)Nc * pitch;
+  const __amdgpu_buffer_rsrc_t krs = make_rsrc(dK, bytes), vrs = make_rsrc(dV, bytes);
+  const unsigned row0 = (unsigned)(key0 + 4 * h) * pitch;
+  auto key_of = [](int r) { return 8 * (r >> 2) + (r & 3); };
+  if (half) {
+    const bool odd = (lr & 1) != 0;
+    const unsigned base = row0 + (odd ? pitch + (lr - 1) * 2u : lr * 2u);
+    auto pair = [&](__amdgpu_buffer_rsrc_t rs, unsigned off, float x, float y) __attribute__((always_inline)) {
+      const float give = odd ? x : y;
+      const float got = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
+      bf16x2 v;
+      v[0] = (bf16)(odd ? got : x);
+      v[1] = (bf16)(odd ? y : got);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, off, 0, 0);
+    };
+#pragma unroll
+    for (int db = 0; db < DB; db++) {
+      const unsigned col = PAD && db * 32 + lr >= d ? 0x80000000u : base + db * 64u;   // (d is even: both lanes of a pair agree)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        pair(krs, col + key_of(r) * pitch, scale * dk[db][r], scale * dk[db][r + 1]);
+        pair(vrs, col + key_of(r) * pitch, dv[db][r], dv[db][r + 1]);
+      }
+    }
+    return;
+  }
+  const unsigned base = row0 + lr * 4u;
+  unsigned col[DB];
+#pragma unroll
+  for (int db = 0; db < DB; db++) col[db] = PAD && db * 32 + lr >= d ? 0x80000000u : base + db * 128u;
+  auto put = [](__amdgpu_buffer_rsrc_t rs, unsigned off, float x) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), rs, off, 0, 0);
+  };
+  if (acc) {
+    auto get = [](__amdgpu_buffer_rsrc_t rs, unsigned off) __attribute__((always_inline)) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+    };
+#pragma unroll
+    for (int q4 = 0; q4 < 4; q4++) {
+      float k_old[4][DB], v_old[4][DB];
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+#pragma unroll
+        for (int db = 0; db < DB; db++) {
+          k_old[j][db] = get(krs, col[db] + (8 * q4 + j) * pitch);
+          v_old[j][db] = get(vrs, col[db] + (8 * q4 + j) * pitch);
+        }
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+#pragma unroll
+        for (int db = 0; db < DB; db++) {
+          put(krs, col[db] + (8 * q4 + j) * pitch, k_old[j][db] + scale * dk[db][4 * q4 + j]);
+          put(vrs, col[db] + (8 * q4 + j) * pitch, v_old[j][db] + dv[db][4 * q4 + j]);
+        }
+    }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; r++)
+#pragma unroll
+    for (int db = 0; db < DB; db++) {
+      put(krs, col[db] + key_of(r) * pitch, scale * dk[db][r]);
+      put(vrs, col[db] + key_of(r) * pitch, dv[db][r]);
+    }
 }
 
 __device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {

@@ -62,7 +62,7 @@ struct DkvArgs {
   long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
   int bsize;             // block flags: edge, a multiple of 64
-  int n;                 // chunks, all with block flags or none
+  int n, per;            // chunks, all with block flags or none; workgroups of each (chunk_at)
   Layout lay;            // strides of Q and dO
   Chunk ch[kMaxChunks];
 };
@@ -86,9 +86,7 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   // the workgroups of all chunks, chunk after chunk
-  int ci = 0;
-  while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
-  const Chunk& C = a.ch[ci];
+  const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
   int head, kblk;
   if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + DKV_BC - 1) / DKV_BC, head, kblk)) return;
   const int Nc = C.Nc;
@@ -125,20 +123,20 @@ burst_bwd_dkv_kernel(DkvArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
 
-  // K, V fragments (B operands: lane = key lr, 8 consecutive d), requested before the tile list is
-  // built so that the two latencies overlap
+  // K, V fragments (B operands: lane = key lr, 8 consecutive d; keys past Nc: outside the buffers, zero).
+  // With a list they are requested before it is built, so that the two latencies overlap.
   bf16x8 kf[8], vf[8];
-  {
-    const int key = key0 + lr;
+  auto load_kv = [&]() __attribute__((always_inline)) {
+    const unsigned kpitch = (unsigned)C.ks_r * 2u, bytes = (unsigned)(Nc - 1) * kpitch + 256u;
+    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, bytes), vrs = make_rsrc(Vh, bytes);
+    const unsigned off = (unsigned)(key0 + lr) * kpitch + h * 16u;
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) {
-      bf16x8 z;
-#pragma unroll
-      for (int t = 0; t < 8; t++) z[t] = (bf16)0.0f;
-      kf[ks] = key < Nc ? *reinterpret_cast<const bf16x8*>(Kh + (size_t)key * C.ks_r + ks * 16 + h * 8) : z;
-      vf[ks] = key < Nc ? *reinterpret_cast<const bf16x8*>(Vh + (size_t)key * C.ks_r + ks * 16 + h * 8) : z;
+      kf[ks] = __builtin_bit_cast(bf16x8, buffer_load_b128(krs, (int)(off + ks * 32u)));
+      vf[ks] = __builtin_bit_cast(bf16x8, buffer_load_b128(vrs, (int)(off + ks * 32u)));
     }
-  }
+  };
+  if constexpr (SPARSE) load_kv();
   int nwalk = ntiles_all - t_begin;                // tiles to walk
   // SPARSE: the list of visible tiles, built by wavefront 0 (64 candidate tiles per round).
   // list[0] = number of entries, list[1 + j] = tile | (wavefront bits << 16), then 4 end entries.
@@ -188,6 +186,7 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   };
 
   if (nwalk > 0) {
+    if constexpr (!SPARSE) load_kv();
     // LDS addressing inside a 64-row tile.  A operands (128-bit): row rb*32 + lr, granule
     // 2*ks + h -> rb*8192 + (abase ^ (ks << 5)).  B operands through transposing reads:
     // rows = query rows rb*32 + u*16 + ..., cols = d.
@@ -464,39 +463,8 @@ burst_bwd_dkv_kernel(DkvArgs a) {
                    "+a"(dv[0]), "+a"(dv[1]), "+a"(dv[2]), "+a"(dv[3]));
   }
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
-  if (a.half) {
-    bf16* const dK16 = (bf16*)C.dK + (size_t)head * Nc * 128;
-    bf16* const dV16 = (bf16*)C.dV + (size_t)head * Nc * 128;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (key < Nc) {
-#pragma unroll
-        for (int db = 0; db < 4; db++) {
-          const size_t off = (size_t)key * 128 + db * 32;
-          store_pair_bf16(dK16 + off, dK16 + off + 128, lr, a.scale * dk[db][r], a.scale * dk[db][r + 1], key + 1 < Nc);
-          store_pair_bf16(dV16 + off, dV16 + off + 128, lr, dv[db][r], dv[db][r + 1], key + 1 < Nc);
-        }
-      }
-    }
-    return;
-  }
-  float* dKh = (float*)C.dK + (size_t)head * Nc * 128;
-  float* dVh = (float*)C.dV + (size_t)head * Nc * 128;
-#pragma unroll
-  for (int r = 0; r < 16; r++) {
-    int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-    if (key < Nc) {
-#pragma unroll
-      for (int db = 0; db < 4; db++) {
-        size_t off = (size_t)key * 128 + db * 32 + lr;
-        float k_old = 0.f, v_old = 0.f;
-        if (a.acc_dkv) { k_old = dKh[off]; v_old = dVh[off]; }
-        dKh[off] = k_old + a.scale * dk[db][r];
-        dVh[off] = v_old + dv[db][r];
-      }
-    }
-  }
+  const size_t first = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
+  store_dkv<4, false>(dk, dv, (char*)C.dK + first, (char*)C.dV + first, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
 }
 
 // n chunks, all with block flags or none.  key_waves: 4 (128-key workgroups) or 2 (64-key workgroups, calls
@@ -522,13 +490,9 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
   const bool listed = ch[0].bmask != nullptr || p.group > 1;
   if (key_waves != 4 && !(key_waves == 2 && listed)) return BURST_ERR_SHAPE;
   const int bc = 32 * key_waves;
-  long long nb = 0;
-  for (int i = 0; i < n; i++) {
-    a.ch[i] = ch[i];
-    a.ch[i].first_block = (int)nb;
-    nb += grid_blocks(a.H, (ch[i].Nc + bc - 1) / bc);
-    if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  }
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
+  const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per);
+  if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
   if (nb == 0) return BURST_OK;
   if (listed) {
     const int max_list = key_waves == 4 ? DkvShape<4>::MAX_LIST : DkvShape<2>::MAX_LIST;

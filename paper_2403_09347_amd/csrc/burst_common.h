@@ -134,7 +134,28 @@ __device__ __forceinline__ bool locate_block(int bid, int heads, int blocks, int
   blk = lin - head * blocks;
   return true;
 }
+// dK/dV grids hold the workgroups of all chunks, chunk after chunk.  per > 0: every chunk has that many (the
+// rule; looking through up to 31 chunks costs a scalar load's latency each).
+__device__ __forceinline__ int chunk_at(int bid, const Chunk* ch, int n, int per) {
+  if (per > 0) return bid / per;
+  int c = 0;
+  while (c + 1 < n && bid >= ch[c + 1].first_block) c++;
+  return c;
+}
 inline long long grid_blocks(long long heads, long long blocks) { return (heads * blocks + 7) / 8 * 8; }
+// Lays the chunks' workgroups (`block` keys each) out; returns their number, `per` as chunk_at wants it.
+inline long long chunk_grid(Chunk* ch, int n, long long heads, int block, int& per) {
+  long long nb = 0;
+  per = n > 0 ? (int)grid_blocks(heads, (ch[0].Nc + block - 1) / block) : 0;
+  for (int i = 0; i < n; i++) {
+    const long long here = grid_blocks(heads, (ch[i].Nc + block - 1) / block);
+    if (here != per) per = 0;
+    ch[i].first_block = (int)nb;
+    nb += here;
+    if (nb > 0x7fffffffLL) break;                  // (the launchers refuse it)
+  }
+  return nb;
+}
 
 // The opt-in to more than 64 KB of dynamic LDS is a per-device function attribute: launchers
 // set it once per device (index = current device, or -1 if it cannot be determined), whichever

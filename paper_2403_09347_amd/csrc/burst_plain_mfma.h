@@ -79,6 +79,7 @@ struct BwdArgsLite {
   int bsize;
   int blocks_per_head, splits;
   int d, n;
+  int per;                                       // dK/dV: workgroups of every chunk (chunk_at)
   Layout lay;
   Chunk ch[kMaxChunks];
 };
@@ -668,9 +669,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   // the workgroups of all chunks, chunk after chunk
-  int ci = 0;
-  while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
-  const Chunk& C = a.ch[ci];
+  const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
   int kvhead, kblk;
   if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + SK_BC - 1) / SK_BC, kvhead, kblk)) return;   // a.H counts key/value heads here
   const int Nc = C.Nc;
@@ -878,45 +877,9 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
-  // lane = d column, registers = keys
-  if (a.half) {
-    bf16* const dK16 = (bf16*)C.dK + (size_t)kvhead * Nc * d;
-    bf16* const dV16 = (bf16*)C.dV + (size_t)kvhead * Nc * d;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (key < Nc) {
-#pragma unroll
-        for (int db = 0; db < S_DB; db++) {
-          if (S_PAD && db * 32 + lr >= d) continue;   // (d is even: both lanes of a pair take the same way)
-          const size_t off = (size_t)key * d + db * 32;
-          store_pair_bf16(dK16 + off, dK16 + off + d, lr, a.scale * dk[db][r], a.scale * dk[db][r + 1], key + 1 < Nc);
-          store_pair_bf16(dV16 + off, dV16 + off + d, lr, dv[db][r], dv[db][r + 1], key + 1 < Nc);
-        }
-      }
-    }
-    return;
-  }
-  float* dKh = (float*)C.dK + (size_t)kvhead * Nc * d;
-  float* dVh = (float*)C.dV + (size_t)kvhead * Nc * d;
-#pragma unroll
-  for (int r = 0; r < 16; r++) {
-    const int key = key0 + 8 * (r >> 2) + 4 * h + (r & 3);
-    if (key < Nc) {
-#pragma unroll
-      for (int db = 0; db < S_DB; db++) {
-        if (S_PAD && db * 32 + lr >= d) continue;
-        const size_t off = (size_t)key * d + db * 32 + lr;
-        float k_old = 0.f, v_old = 0.f;
-        if (a.acc_dkv) { k_old = dKh[off]; v_old = dVh[off]; }
-        dKh[off] = k_old + a.scale * dk[db][r];
-        dVh[off] = v_old + dv[db][r];
-      }
-    }
-  }
+  const size_t first = (size_t)kvhead * Nc * d * (a.half ? 2 : 4);
+  store_dkv<S_DB, S_PAD>(dk, dv, (char*)C.dK + first, (char*)C.dV + first, Nc, d, key0, lr, h, a.scale, a.half, a.acc_dkv);
 }
-
-
 
 // ------------------------------------------------------------------------------- launchers
 // Tile lists are dynamic LDS behind up to 64 KB of static tiles: the kernels that take one opt
@@ -987,12 +950,7 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
-  long long nb = 0;
-  for (int i = 0; i < n; i++) {
-    a.ch[i].first_block = (int)nb;
-    nb += grid_blocks(a.H, (ch[i].Nc + SK_BC - 1) / SK_BC);
-    if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
-  }
+  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per);
   static DeviceOnce done;
   return launch_plain(burst_bwd_dkv_d64_kernel<false>, burst_bwd_dkv_d64_kernel<true>, done, a, nb,
                       (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
