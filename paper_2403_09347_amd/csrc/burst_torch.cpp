@@ -40,6 +40,18 @@ void set_strides(int64_t (&out)[3], const Tensor& t) {
   for (int i = 0; i < 3; i++) out[i] = dense ? 0 : t.size(i) > 1 ? t.stride(i) : t.size(3);
 }
 
+// K and V of a chunk as they are if one set of strides addresses both, else contiguous copies.
+void pair_in_place(Tensor& k, Tensor& v) {
+  bool same = addressable(k) && addressable(v) && k.is_contiguous() == v.is_contiguous() && k.sizes() == v.sizes();
+  for (int j = 0; j < 3 && same; j++) same = k.size(j) == 1 || k.stride(j) == v.stride(j);
+  if (!same) { k = k.contiguous(); v = v.contiguous(); }
+}
+
+// t if it lies in memory like q, else a copy that does.
+Tensor lying_like(const Tensor& t, const Tensor& q) {
+  return t.strides() == q.strides() ? t : torch::empty_strided(q.sizes(), q.strides(), q.options()).copy_(t);
+}
+
 struct Call {                        // what forward and backward have in common
   burst_params p{};
   std::vector<burst_chunk> chunks;
@@ -95,12 +107,7 @@ class Attention : public torch::autograd::Function<Attention> {
     const size_t n = (kvm.size() - (size_t)n_masks) / 2;
     const Tensor q = addressable(q_in) ? q_in : q_in.contiguous();
     variable_list ks(kvm.begin(), kvm.begin() + n), vs(kvm.begin() + n, kvm.begin() + 2 * n), masks(kvm.begin() + 2 * n, kvm.end());
-    for (size_t i = 0; i < n; i++) {              // K and V as they are if one set of strides addresses both, else copies
-      Tensor &k = ks[i], &v = vs[i];
-      bool same = addressable(k) && addressable(v) && k.is_contiguous() == v.is_contiguous() && k.sizes() == v.sizes();
-      for (int j = 0; j < 3 && same; j++) same = k.size(j) == 1 || k.stride(j) == v.stride(j);
-      if (!same) { k = k.contiguous(); v = v.contiguous(); }
-    }
+    for (size_t i = 0; i < n; i++) pair_in_place(ks[i], vs[i]);
     const Call c = describe(q, ks, vs, masks, scale, causal, q_off, window, block);
     Tensor O = torch::empty_strided(q.sizes(), q.strides(), q.options());   // O lies in memory like Q
     Tensor lse = torch::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(torch::kFloat));
@@ -126,14 +133,14 @@ class Attention : public torch::autograd::Function<Attention> {
     const size_t n = (size_t)ctx->saved_data["n"].toInt();
     variable_list out(1 + (s.size() - 3) + 6);    // q, kvm, and six arguments that are no tensors
     if (!grads[0].defined()) return out;
-    const Tensor &q = s[0], &O = s[1], &lse = s[2];
-    const variable_list ks(s.begin() + 3, s.begin() + 3 + n), vs(s.begin() + 3 + n, s.begin() + 3 + 2 * n),
-        masks(s.begin() + 3 + 2 * n, s.end());
+    // Hooks on saved tensors may have returned each of them in another layout than it was saved in.
+    const Tensor q = addressable(s[0]) ? s[0] : s[0].contiguous(), O = lying_like(s[1], q), lse = s[2].contiguous();
+    variable_list ks(s.begin() + 3, s.begin() + 3 + n), vs(s.begin() + 3 + n, s.begin() + 3 + 2 * n), masks(s.begin() + 3 + 2 * n, s.end());
+    for (size_t i = 0; i < n; i++) pair_in_place(ks[i], vs[i]);
     Call c = describe(q, ks, vs, masks, ctx->saved_data["scale"].toDouble(), ctx->saved_data["causal"].toBool(),
                       ctx->saved_data["q_off"].toInt(), ctx->saved_data["window"].toInt(), ctx->saved_data["block"].toInt());
-    Tensor g = grads[0].to(q.scalar_type());
-    if (g.strides() != q.strides()) g = torch::empty_strided(q.sizes(), q.strides(), q.options()).copy_(g);   // dO lies in memory like Q
-    Tensor D = torch::empty_like(lse), dQ = torch::empty(q.sizes(), q.options());
+    const Tensor g = lying_like(grads[0].to(q.scalar_type()), q);
+    Tensor D = torch::empty(lse.sizes(), lse.options()), dQ = torch::empty(q.sizes(), q.options());
     out[0] = dQ;
     for (size_t i = 0; i < n; i++) {
       out[1 + i] = torch::empty(ks[i].sizes(), ks[i].options());

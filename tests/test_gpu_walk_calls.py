@@ -126,3 +126,26 @@ def test_differentiable_call_partial_gradients_and_errors():
         burst_attention(q, ks, vs, block_masks=[torch.ones((1, 1), device=DEV)] * 2, block=64)
     with pytest.raises(ValueError):
         burst_attention(q, [k.float() for k in ks], vs)
+
+
+@pytest.mark.parametrize("moved", [{0}, {1, 2}, {3}, {4, 5}])
+def test_saved_tensors_come_back_in_another_layout(moved):
+    """Hooks on saved tensors may give back dense copies of some of the sequence-major tensors (here by position:
+    Q, O, lse, keys, values): the gradients are the same bits."""
+    from paper_2403_09347_amd.autograd import burst_attention
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    draw = lambda n, h: torch.randn((2, n, h, 64), device=DEV, generator=gen).bfloat16().transpose(1, 2).requires_grad_(True)
+    q, ks, vs, dO = draw(70, 4), [draw(64, 2), draw(33, 2)], [draw(64, 2), draw(33, 2)], draw(70, 4).detach()
+    O, _ = burst_attention(q, ks, vs, causal=True, q_off=27)
+    want = torch.autograd.grad(O, [q, *ks, *vs], dO)
+    packed = []
+
+    def pack(t):
+        packed.append(t)
+        return t.detach().contiguous() if len(packed) - 1 in moved else t.detach()
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+        O, _ = burst_attention(q, ks, vs, causal=True, q_off=27)
+    assert len(packed) >= 7
+    for a, b in zip(torch.autograd.grad(O, [q, *ks, *vs], dO), want):
+        assert torch.equal(a, b)
