@@ -66,10 +66,13 @@ class RingWalk:
         return p
 
     def _scratch(self, chunks, p, flags=0):
-        """Workspace of a walk, kept by the walk (None: these sizes use none)."""
+        """Workspace of a walk, kept by the walk (None: these sizes use none).  Under capture the graph's pool
+        owns it: a graph must not hold the address of one that a longer walk replaces."""
         need = B.burst_walk_workspace_bytes(chunks, p, flags)
         if need == 0:
             return None
+        if torch.cuda.is_current_stream_capturing():
+            return torch.empty(need, device=self.Q.device, dtype=torch.uint8)
         if self._workspace is None or self._workspace.numel() < need:
             self._workspace = torch.empty(need, device=self.Q.device, dtype=torch.uint8)
         return self._workspace

@@ -149,3 +149,35 @@ def test_saved_tensors_come_back_in_another_layout(moved):
     assert len(packed) >= 7
     for a, b in zip(torch.autograd.grad(O, [q, *ks, *vs], dO), want):
         assert torch.equal(a, b)
+
+
+def test_captured_walk_outlives_the_workspace_of_a_longer_one():
+    """A captured walk that splits its keys, replayed after the same object has walked more chunks eagerly
+    (a larger workspace): every replay equals the eager walk and writes nothing that others own."""
+    case = workloads.make_case(B=1, H=2, d=64, Nq=40, chunk_rows=[1024] * 6, dtype="bf16", seed=9, device=DEV)
+    walk = RingWalk(case["Q"], case["scale"])
+    args = case["K"][:2], case["V"][:2], case["k_offs"][:2]
+
+    def both():
+        O, lse = walk.forward(*args)
+        return [O, lse, *walk.backward(*args, case["dO"])[:1]]
+
+    want = [t.clone() for t in both()]
+    held = walk._workspace.numel()
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        both()
+    torch.cuda.current_stream().wait_stream(stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = both()
+    for _ in range(3):
+        walk.forward(case["K"], case["V"], case["k_offs"])
+        assert walk._workspace.numel() > held
+        others = [torch.full((held,), 7, device=DEV, dtype=torch.uint8) for _ in range(4)]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        assert all(bool((t == 7).all()) for t in others)
