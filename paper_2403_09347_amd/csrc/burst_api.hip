@@ -4,6 +4,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <vector>
 #include "burst_common.h"
@@ -308,7 +309,7 @@ int walk_chunks(const burst_chunk* chunks, int n, const burst_params* p, bool ba
   if (n < 0) return BURST_ERR_SHAPE;
   if (n > 0 && chunks == nullptr) return BURST_ERR_NULL;
   if (p == nullptr) return BURST_ERR_NULL;
-  out.reserve((size_t)n);
+  try { out.reserve((size_t)n); } catch (const std::exception&) { return BURST_ERR_ALLOC; }   // (nothing is thrown through the C ABI)
   for (int i = 0; i < n; i++) {
     const burst_chunk& in = chunks[i];
     WalkChunk w;
