@@ -60,7 +60,7 @@ struct FwdArgsLite {
   float c;                                       // scale * log2(e)
   long long q_off, window;
   int bsize;
-  int blocks_per_head, splits;
+  int blocks_per_head, splits, mirror;           // mirror: see mirrored()
   int d;                                         // head dimension (S_D unless S_PAD)
   int n;                                         // chunks
   Layout lay;                                    // strides of Q and O_out
@@ -77,7 +77,7 @@ struct BwdArgsLite {
   float c, scale, log2_scale;
   long long q_off, window;
   int bsize;
-  int blocks_per_head, splits;
+  int blocks_per_head, splits, mirror;
   int d, n;
   int per;                                       // dK/dV: workgroups of every chunk (chunk_at)
   Layout lay;
@@ -158,7 +158,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   int head, qb, split = 0;
-  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb)) return;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.mirror)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
   const int q0 = qb * SF_BR + w * 32, row = q0 + lr;
@@ -443,7 +443,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   int head, qb, split = 0;
-  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb)) return;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.mirror)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
   const int q0 = qb * SQ_BR + w * 32;
@@ -671,7 +671,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   // the workgroups of all chunks, chunk after chunk
   const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
   int kvhead, kblk;
-  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + SK_BC - 1) / SK_BC, kvhead, kblk)) return;   // a.H counts key/value heads here
+  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + SK_BC - 1) / SK_BC, kvhead, kblk, a.mirror)) return;   // a.H counts key/value heads here
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
   const int key_wg = kblk * SK_BC, key0 = key_wg + w * 32;
@@ -917,6 +917,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
   a.blocks_per_head = (p.Nq + SF_BR - 1) / SF_BR;
+  a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;
   for (int i = 0; i < n; i++) { a.ch[i] = ch[i]; if (ch[i].Nc > longest) longest = ch[i].Nc; }
   static DeviceOnce done;
@@ -939,6 +940,7 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.blocks_per_head = (p.Nq + SQ_BR - 1) / SQ_BR;
+  a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;
   for (int i = 0; i < n; i++) if (ch[i].Nc > longest) longest = ch[i].Nc;
   static DeviceOnce done;
@@ -951,6 +953,7 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
   const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per);
+  a.mirror = n == 1 && mirrored(nb, a.causal);
   static DeviceOnce done;
   return launch_plain(burst_bwd_dkv_d64_kernel<false>, burst_bwd_dkv_d64_kernel<true>, done, a, nb,
                       (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
