@@ -375,7 +375,7 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
 // (2: 106, 8: 108); 8 x 100 x 4K, d = 64, 63 / 24 in 8 (4: 28, 16: 22); 8 x 1024 x 4K 85 / 38 in 8
 // (4: 39, 16: 52); backward (dQ) 32 x 512 x 8K 664 / 585, 8 x 1024 x 4K 257 / 191.
 int walk_splits(const std::vector<WalkChunk>& w) {
-  if (w.empty() || w.size() > (size_t)burst::kMaxChunks) return 1;
+  if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return 1;
   const Kernels f = fwd_kernels(&w[0].p, w[0].k);
   if (f.plain == nullptr) return 1;
   const KParams& k = w[0].k;
