@@ -352,14 +352,18 @@ def burst_local_bwd_dkv(Q, K_chunk, V_chunk, dO, lse, D, dK_chunk, dV_chunk, p, 
                                       ctypes.byref(p), _stream()), "burst_local_bwd_dkv")
 
 
-def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None):
+def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None, grad_dtype=None):
     """The chunks of a walk as the C array burst_walk_fwd / burst_walk_bwd take.  `p`: the walk's parameter
-    block (its `block` is the edge of the masks' blocks)."""
+    block (its `block` is the edge of the masks' blocks).  grad_dtype: the type of dQ, which dKs and dVs must have."""
     arr = (BurstChunk * len(Ks))()
+    dtype = torch.bfloat16 if p.dtype == BURST_BF16 else torch.float32
     for j, (K, V) in enumerate(zip(Ks, Vs)):
         c = arr[j]
         if not K.is_cuda or not V.is_cuda:
             raise ValueError("device tensor expected")
+        if K.dtype != dtype or V.dtype != dtype or K.shape != V.shape or \
+                tuple(K.shape) != (p.B, p.kv_heads or p.H, K.shape[2], p.d):
+            raise ValueError("K, V: [B, kv_heads, Nc, d] of the type of Q expected")
         if not (K.is_contiguous() and V.is_contiguous()):
             s = strides_of(K) or (0, 0, 0)
             _strided(V, s)
@@ -369,8 +373,10 @@ def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None):
             c.block_mask, c.block_mask_stride = _mask(masks[j], p.block, p.B, p.H, p.Nq, c.Nc)
         if dKs is not None:
             dK, dV = dKs[j], dVs[j]
-            if dK.dtype != dKs[0].dtype or dV.dtype != dKs[0].dtype:
-                raise ValueError("one type for all gradients expected")
+            if dK.dtype != grad_dtype or dV.dtype != grad_dtype:
+                raise ValueError("dK, dV: the type of dQ expected")
+            if dK.numel() < K.numel() or dV.numel() < V.numel():
+                raise ValueError("dK, dV: the sizes of K and V expected")
             c.dK, c.dV = _ptr(dK).value, _ptr(dV).value
     return arr
 

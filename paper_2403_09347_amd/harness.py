@@ -111,7 +111,7 @@ class RingWalk:
             new = lambda x: torch.empty(x.shape, device=dQ.device, dtype=dQ.dtype)
             dKs, dVs = [new(K) for K in Ks], [new(V) for V in Vs]
         p = self._walk_params()
-        chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs)
+        chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs, dQ.dtype)
         B.burst_walk_bwd(self.Q, chunks, self.O, self._like_q(dO), self.lse, self.D, dQ, p, accumulate_dq=accumulate,
                          accumulate_dkv=False, workspace=self._scratch(chunks, p, B.BURST_WALK_HALF_GRADS if dQ.dtype != torch.float32 else 0))
         return dQ, dKs, dVs

@@ -135,3 +135,31 @@ def test_binding_rejects_host_masks_and_wrong_shapes():
     from paper_2403_09347_amd import binding
     with pytest.raises(ValueError):
         binding.params(1, 1, 128, 128, 128, "bf16", 0.1, block_mask=torch.ones((2, 2), dtype=torch.uint8), block=64)
+
+
+def test_walk_calls_reject_buffers_the_kernels_would_overrun():
+    """Gradient buffers of another type or size than the kernels write, keys and values of other types or sizes
+    than they read: refused before any address leaves Python, as the chunk-by-chunk calls refuse the types."""
+    import torch
+    from paper_2403_09347_amd.harness import RingWalk
+
+    class OnDevice(torch.Tensor):                  # a host tensor that says it is a device tensor; nothing reads it
+        is_cuda = property(lambda self: True)
+
+    new = lambda dtype, rows=64, heads=2, d=64: torch.zeros((1, heads, rows, d), dtype=dtype).as_subclass(OnDevice)
+    bf16, f32 = torch.bfloat16, torch.float32
+    walk = RingWalk(new(bf16), 0.125)
+    K, dO = [new(bf16), new(bf16)], new(bf16)
+    back = lambda **grads: walk.backward(K, K, [0, 64], dO, **grads)
+    for dKs, dVs in (([new(bf16)] * 2, [new(bf16)] * 2), ([new(f32)] * 2, [new(bf16)] * 2), ([new(f32), new(bf16)], [new(f32)] * 2)):
+        with pytest.raises(ValueError, match="type of dQ"):
+            back(dKs=dKs, dVs=dVs)
+    with pytest.raises(ValueError, match="type of dQ"):
+        back(dQ=new(bf16), dKs=[new(f32)] * 2, dVs=[new(f32)] * 2)
+    for dKs, dVs in (([new(f32, 63)] * 2, [new(f32)] * 2), ([new(f32)] * 2, [new(f32), new(f32, d=32)])):
+        with pytest.raises(ValueError, match="sizes of K and V"):
+            back(dKs=dKs, dVs=dVs)
+    for k, v in ((new(f32), new(f32)), (new(bf16), new(f32)), (new(bf16), new(bf16, 63)), (new(bf16, heads=1), new(bf16, heads=1)),
+                 (new(bf16, d=32), new(bf16, d=32))):
+        with pytest.raises(ValueError, match="of the type of Q"):
+            walk.forward([new(bf16), k], [new(bf16), v], [0, 64])
