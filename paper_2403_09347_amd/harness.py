@@ -53,6 +53,7 @@ class RingWalk:
                 self.step(Ks[j], Vs[j], k_offs[j], None if masks is None else masks[j])
             return self.finalize()
         if order is not None:
+            order = list(order)                      # (it may be an iterator, and is walked once per list)
             pick = lambda x: None if x is None else [x[j] for j in order]
             Ks, Vs, k_offs, masks = pick(Ks), pick(Vs), pick(k_offs), pick(masks)
         p = self._walk_params()

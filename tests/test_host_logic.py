@@ -137,15 +137,22 @@ def test_binding_rejects_host_masks_and_wrong_shapes():
         binding.params(1, 1, 128, 128, 128, "bf16", 0.1, block_mask=torch.ones((2, 2), dtype=torch.uint8), block=64)
 
 
+def _device_stand_in():
+    import torch
+
+    class OnDevice(torch.Tensor):                  # a host tensor that says it is a device tensor; nothing reads it
+        is_cuda = property(lambda self: True)
+
+    return OnDevice
+
+
 def test_walk_calls_reject_buffers_the_kernels_would_overrun():
     """Gradient buffers of another type or size than the kernels write, keys and values of other types or sizes
     than they read: refused before any address leaves Python, as the chunk-by-chunk calls refuse the types."""
     import torch
     from paper_2403_09347_amd.harness import RingWalk
 
-    class OnDevice(torch.Tensor):                  # a host tensor that says it is a device tensor; nothing reads it
-        is_cuda = property(lambda self: True)
-
+    OnDevice = _device_stand_in()
     new = lambda dtype, rows=64, heads=2, d=64: torch.zeros((1, heads, rows, d), dtype=dtype).as_subclass(OnDevice)
     bf16, f32 = torch.bfloat16, torch.float32
     walk = RingWalk(new(bf16), 0.125)
@@ -163,3 +170,22 @@ def test_walk_calls_reject_buffers_the_kernels_would_overrun():
                  (new(bf16, d=32), new(bf16, d=32))):
         with pytest.raises(ValueError, match="of the type of Q"):
             walk.forward([new(bf16), k], [new(bf16), v], [0, 64])
+
+
+def test_walk_takes_chunks_in_any_kind_of_order(monkeypatch):
+    """`order` as a list, a range or an iterator hands the same chunks to the library."""
+    import torch
+    from paper_2403_09347_amd import binding, harness
+    seen = []
+    monkeypatch.setattr(binding, "burst_walk_fwd", lambda Q, chunks, *rest: seen.append([(c.K, c.V, c.k_off, c.Nc) for c in chunks]))
+    monkeypatch.setattr(harness.RingWalk, "_scratch", lambda self, chunks, p, flags=0: None)
+    OnDevice = _device_stand_in()
+    new = lambda rows: torch.zeros((1, 2, rows, 64), dtype=torch.bfloat16).as_subclass(OnDevice)
+    walk = harness.RingWalk(new(8), 0.125)
+    Ks, Vs, offs = [new(r) for r in (8, 16, 24)], [new(r) for r in (8, 16, 24)], [0, 8, 24]
+    for order in ([2, 0, 1], iter([2, 0, 1]), (j for j in (2, 0, 1))):
+        walk.forward(Ks, Vs, offs, order=order)
+    want = [(Ks[j].data_ptr(), Vs[j].data_ptr(), offs[j], Ks[j].shape[2]) for j in (2, 0, 1)]
+    assert seen == [want] * 3
+    walk.forward(Ks, Vs, offs, order=range(2))
+    assert seen[-1] == [(Ks[j].data_ptr(), Vs[j].data_ptr(), offs[j], Ks[j].shape[2]) for j in (0, 1)]
