@@ -357,8 +357,8 @@ def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None, grad_dtype=None):
     block (its `block` is the edge of the masks' blocks).  grad_dtype: the type of dQ, which dKs and dVs must have."""
     arr = (BurstChunk * len(Ks))()
     dtype = torch.bfloat16 if p.dtype == BURST_BF16 else torch.float32
-    for j, (K, V) in enumerate(zip(Ks, Vs)):
-        c = arr[j]
+    for j in range(len(Ks)):                         # (by index: a list of values that is too short is an IndexError)
+        K, V, c = Ks[j], Vs[j], arr[j]
         if not K.is_cuda or not V.is_cuda:
             raise ValueError("device tensor expected")
         if K.dtype != dtype or V.dtype != dtype or K.shape != V.shape or \

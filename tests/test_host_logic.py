@@ -189,3 +189,16 @@ def test_walk_takes_chunks_in_any_kind_of_order(monkeypatch):
     assert seen == [want] * 3
     walk.forward(Ks, Vs, offs, order=range(2))
     assert seen[-1] == [(Ks[j].data_ptr(), Vs[j].data_ptr(), offs[j], Ks[j].shape[2]) for j in (0, 1)]
+
+
+def test_walk_refuses_lists_shorter_than_the_keys():
+    """A list of values or offsets shorter than the keys is an IndexError, not a walk over fewer chunks."""
+    import torch
+    from paper_2403_09347_amd import harness
+    OnDevice = _device_stand_in()
+    new = lambda rows: torch.zeros((1, 2, rows, 64), dtype=torch.bfloat16).as_subclass(OnDevice)
+    walk = harness.RingWalk(new(8), 0.125)
+    Ks, Vs, offs = [new(8), new(16)], [new(8), new(16)], [0, 8]
+    for args in ((Ks, Vs[:1], offs), (Ks, Vs, offs[:1])):
+        with pytest.raises(IndexError):
+            walk.forward(*args)
