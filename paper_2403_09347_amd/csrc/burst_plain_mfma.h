@@ -117,6 +117,34 @@ __device__ __forceinline__ bf16x8 s_load8(const bf16* p, bool ok) {
   for (int t = 0; t < 8; t++) z[t] = (bf16)0.0f;
   return ok ? *reinterpret_cast<const bf16x8*>(p) : z;
 }
+// A pair of probabilities (or dS) as bf16 operands of the second products: S_TERMS terms that add up to
+// the fp32 values, in elements t and t + 1 of the fragments.  One term where the inputs' 8 bits are the measure of a
+// probability as well (d = 64, 128, as in the hand-scheduled kernels).  The padded builds serve calls that had
+// fp32 probabilities in the generic kernels and keep all 24 bits: three terms, each remainder exact, three
+// MFMAs.  32 heads of 777 causal rows, d = 96, call with gradients: 80 us with one term, 114 us with three (1375 us
+// on the generic kernels); a walk's dV differs from 64 bits by 1.6e-3 with one term, 5.7e-7 with three (5.8e-7
+// on the generic kernels).
+constexpr int S_TERMS = S_PAD ? 3 : 1;
+__device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, float y) {
+#pragma unroll
+  for (int i = 0; i < S_TERMS; i++) {
+    bf16x2 pk;
+    pk[0] = (bf16)x; pk[1] = (bf16)y;
+    out[i][t] = pk[0]; out[i][t + 1] = pk[1];
+    x -= (float)pk[0]; y -= (float)pk[1];
+  }
+}
+// acc += a x (the sum of b's terms) and acc += (the sum of a's terms) x b, the smallest terms first
+__device__ __forceinline__ f32x16 s_mfma_terms_b(bf16x8 a, const bf16x8 (&b)[S_TERMS], f32x16 acc) {
+#pragma unroll
+  for (int i = S_TERMS - 1; i >= 0; i--) acc = mfma32(a, b[i], acc);
+  return acc;
+}
+__device__ __forceinline__ f32x16 s_mfma_terms_a(const bf16x8 (&a)[S_TERMS], bf16x8 b, f32x16 acc) {
+#pragma unroll
+  for (int i = S_TERMS - 1; i >= 0; i--) acc = mfma32(a[i], b, acc);
+  return acc;
+}
 // Calls with block flags (paper Sec. 2.6) run the SPARSE instantiations: wavefront 0 first writes
 // the list of tiles that at least one wavefront of the workgroup can see into LDS (tile index plus
 // one bit per wavefront, list[0] = count), the loop then walks that list, and a wavefront whose bit
@@ -350,17 +378,21 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         for (int r = 0; r < 16; r++) o[db][r] *= alpha;
     }
     const float nref = (m2 == BURST_NEG_INF) ? 0.f : -m2;
-    bf16x8 pf[4];                                  // P^T fragments per 16-key group
+    bf16x8 pf[4][S_TERMS];                         // P^T fragments per 16-key group
 #pragma unroll
     for (int kg = 0; kg < 4; kg++)
 #pragma unroll
       for (int t = 0; t < 8; t += 2) {
         const int kb = kg >> 1, r = 8 * (kg & 1) + t;
-        bf16x2 pk;
-        pk[0] = (bf16)fast_exp2(__builtin_fmaf(s[kb][r], a.c, nref));
-        pk[1] = (bf16)fast_exp2(__builtin_fmaf(s[kb][r + 1], a.c, nref));
-        lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);   // sums what the MFMA multiplies
-        pf[kg][t] = pk[0]; pf[kg][t + 1] = pk[1];
+        const float p0 = fast_exp2(__builtin_fmaf(s[kb][r], a.c, nref)), p1 = fast_exp2(__builtin_fmaf(s[kb][r + 1], a.c, nref));
+        s_terms(pf[kg], t, p0, p1);
+        if constexpr (S_TERMS == 1) {                // sums what the MFMA multiplies
+          bf16x2 pk;
+          pk[0] = pf[kg][0][t]; pk[1] = pf[kg][0][t + 1];
+          lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);
+        } else {
+          lsum += p0 + p1;
+        }
       }
     // O^T += V^T P^T
 #pragma unroll
@@ -369,7 +401,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       for (int db = 0; db < S_DB; db++) {
         const bf16x4 va = lds_read_tr(vl, kg * 16 * S_ROWB + taddr[db][0]);
         const bf16x4 vb = lds_read_tr(vl, kg * 16 * S_ROWB + taddr[db][1]);
-        o[db] = mfma32(cat4(va, vb), pf[kg], o[db]);
+        o[db] = s_mfma_terms_b(cat4(va, vb), pf[kg], o[db]);
       }
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -601,11 +633,11 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
           if (!(cpart <= lim && cpart >= lim_lo)) s[r] = BURST_NEG_INF;
         }
       }
-      bf16x8 dsf[2];                               // dS^T fragments per 16-key group
+      bf16x8 dsf[2][S_TERMS];                      // dS^T fragments per 16-key group
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const float p = fast_exp2(__builtin_fmaf(s[r], a.c, nlse2));
-        dsf[r >> 3][r & 7] = (bf16)(p * (dp[r] - Dv));
+      for (int r = 0; r < 16; r += 2) {
+        const float p0 = fast_exp2(__builtin_fmaf(s[r], a.c, nlse2)), p1 = fast_exp2(__builtin_fmaf(s[r + 1], a.c, nlse2));
+        s_terms(dsf[r >> 3], r & 7, p0 * (dp[r] - Dv), p1 * (dp[r + 1] - Dv));
       }
       // dQ^T += K^T dS^T
 #pragma unroll
@@ -614,7 +646,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
         for (int db = 0; db < S_DB; db++) {
           const bf16x4 ta = lds_read_tr(kl, kg * 16 * S_ROWB + taddr[db][0]);
           const bf16x4 tb = lds_read_tr(kl, kg * 16 * S_ROWB + taddr[db][1]);
-          dq[db] = mfma32(cat4(ta, tb), dsf[kg], dq[db]);
+          dq[db] = s_mfma_terms_b(cat4(ta, tb), dsf[kg], dq[db]);
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -843,17 +875,17 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
               }
           __builtin_amdgcn_sched_barrier(0);
         }
-        bf16x8 pf[2], dsf[2];                        // per 16-row group: A operands of dV, dK
+        bf16x8 pf[2][S_TERMS], dsf[2][S_TERMS];      // per 16-row group: A operands of dV, dK
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) {
           const f32x4 nl = *reinterpret_cast<const f32x4*>(stat + buf * 64 + 8 * q4 + 4 * h);
           const f32x4 dr = *reinterpret_cast<const f32x4*>(stat + buf * 64 + 32 + 8 * q4 + 4 * h);
 #pragma unroll
-          for (int j = 0; j < 4; j++) {
+          for (int j = 0; j < 4; j += 2) {
             const int r = 4 * q4 + j;
-            const float p = fast_exp2(__builtin_fmaf(s[r], a.c, nl[j]));
-            pf[r >> 3][r & 7] = (bf16)p;
-            dsf[r >> 3][r & 7] = (bf16)(p * (dp[r] - dr[j]));
+            const float p0 = fast_exp2(__builtin_fmaf(s[r], a.c, nl[j])), p1 = fast_exp2(__builtin_fmaf(s[r + 1], a.c, nl[j + 1]));
+            s_terms(pf[r >> 3], r & 7, p0, p1);
+            s_terms(dsf[r >> 3], r & 7, p0 * (dp[r] - dr[j]), p1 * (dp[r + 1] - dr[j + 1]));
           }
         }
         // dV += P^T dO, dK += dS^T Q (dO and Q through transposing reads)
@@ -869,8 +901,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
               bg = cat4(lds_read_tr(gl, u * 16 * S_ROWB + taddr[db][0]), lds_read_tr(gl, u * 16 * S_ROWB + taddr[db][1]));
               bq = cat4(lds_read_tr(ql, u * 16 * S_ROWB + taddr[db][0]), lds_read_tr(ql, u * 16 * S_ROWB + taddr[db][1]));
             }
-            dv[db] = mfma32(pf[u], bg, dv[db]);
-            dk[db] = mfma32(dsf[u], bq, dk[db]);
+            dv[db] = s_mfma_terms_a(pf[u], bg, dv[db]);
+            dk[db] = s_mfma_terms_a(dsf[u], bq, dk[db]);
           }
       }
       if (n + 1 < nwalk) stat_commit((n + 1) & 1);
