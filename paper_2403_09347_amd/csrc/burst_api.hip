@@ -229,13 +229,18 @@ bool use_plain128(const burst_params* p, const KParams& k) {
   const long long last = wgs % 256;                // workgroups of the last round (0 = full)
   return last != 0 && last <= 128 && wgs <= 1536;
 }
-// The dK/dV MFMA kernel walks the query tiles of all heads of a group as one list of at most 8192
-// tiles, the last one of each head partial where Nq is no multiple of 64; longer groups take the generic
-// kernel.  (32 heads over 8, 3001 causal rows, call with gradients: 646 us here, 10.3 ms with the generic
-// dK/dV kernel.)
+// The hand-scheduled dK/dV kernel walks the query tiles of all heads of a group as one list of at most 8192
+// tiles; longer groups take the generic kernel.  Groups whose slice is no multiple of its 64-row tiles go to the
+// plain kernel padded to 128 columns, whose P and dS have 24 bits as in the generic kernel that had these calls (see
+// s_terms).  (Call with gradients, 32 heads over 8, 3001 causal rows: 1020 us so, 560 us with the hand-scheduled
+// kernel and its 8-bit P and dS (a walk's dV then 1.7e-3 off 64 bits instead of 7.6e-5), 10.3 ms with the generic one.)
 bool dkv_mfma_ok(const burst_params* p, const KParams& k) {
-  if (k.group > 1) return (long long)k.group * ((p->Nq + 63) / 64) <= 8192 && k.group <= 256;
+  if (k.group > 1) return p->Nq % 64 == 0 && (long long)k.group * (p->Nq / 64) <= 8192 && k.group <= 256;
   return p->block_mask == nullptr || p->Nq <= kMaxMaskedRows;
+}
+bool use_padded128_dkv(const burst_params* p, const KParams& k) {
+  if (!use_mfma(p, k) || k.group == 1 || p->Nq % 64 == 0) return false;
+  return p->block_mask == nullptr || (long long)k.group * ((p->Nq + 31) / 32) <= 4096;   // (its tile list)
 }
 
 // Entry points that enqueue several kernels: one pass over the launchers in validate-only mode
@@ -285,6 +290,7 @@ Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the s
 Kernels dkv_kernels(const burst_params* p, const KParams& k) {
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
   if (use_plain128_dkv(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
+  if (use_padded128_dkv(p, k)) return {&kD128x, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && dkv_mfma_ok(p, k);
   return {nullptr, hand, hand ? dkv_key_waves(p, k) : 0, burst::kMaxChunks};
 }

@@ -7,7 +7,7 @@
 //   burst_d128_plain.hip  d = 128, namespace burst::d128p, all three kernels, the dK/dV one with
 //                         two wavefronts (64 keys) per workgroup (BURST_SMALL_DKV_WAVES = 2)
 //   burst_d{32,64,96,128}_pad.hip   every other multiple of 8 below 128, padded to the next of these
-//                         widths (BURST_SMALL_PAD), namespaces burst::d32x .. d128x
+//                         widths (BURST_SMALL_PAD), namespaces burst::d32x .. d128x; P and dS with 24 bits
 //
 // Same mathematics, operand orientations and register layouts as the hand-scheduled d = 128
 // kernels (S^T = K Q^T with one query row per lane for the forward and dQ side, S = Q K^T with one
