@@ -111,16 +111,30 @@ struct BwdIo {
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
 };
 
-// The forward kernels choose their reference maximum (log2 units) on a grid of 16: rows of ordinary
-// inputs then get the same reference whatever the order of the chunks and however the keys are split,
-// and with it the same bf16 rounding of P.  (P is at most 2^16 smaller than with the maximum itself,
-// which changes the precision of nothing: bf16 and fp32 are floating point.)  A stored m (natural log)
-// of such a reference comes back exactly: r ln2 log2e differs from r by at most 4 x 2^-24 of it.  Any
-// other m is taken as it is.
-__device__ __forceinline__ float reference_for(float row_max) { return 16.f * __builtin_ceilf(row_max * 0.0625f); }
-__device__ __forceinline__ float reference_of(float m) {
-  const float x = m * kLog2e, r = __builtin_rintf(x);
-  return fabsf(x - r) <= 3e-7f * fabsf(r) ? r : x;
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The reference maximum of a row in the forward kernels.  Every chunk chooses it anew: the row's maximum in the first
+// tile of the chunk in which it sees a key, so that the largest probability there is 1, exact in bf16 (a row that
+// sees one key has O = V and lse = its score), and raised to the row's maximum in a later tile that exceeds it by more than
+// 2^8.  The bf16 rounding of a chunk's P then depends on that chunk alone, not on the order of the chunks or on
+// where the keys are split.  The state in registers is brought to the new reference; where that is lower, only so far
+// that the row sum stays below 2^24 (what a chunk that far below the state adds, its rounding cannot change).
+// m_st: the reference as it is stored (natural log); log2 units are always m_st x log2 e, so a store and a load in between
+// change nothing.  cm: the chunk's reference (log2 units), -inf until the row has seen a key of the chunk.  mx: the row's
+// maximum in this tile; l: its sum so far.  Returns the factor of the row's O and l.
+// (References on a fixed grid of 16 did as much for the order, but rounded the largest P too: lse of a causal row that
+// sees one key was up to 3.8e-3 off, the lse of 4 x 16 heads of 1024 causal rows, d = 64, 3.2e-5 of its norm instead of 2.4e-5.)
+__device__ __forceinline__ float raise_reference(float& m_st, float& cm, float mx, float l) {
+  float m2 = m_st * kLog2e;
+  float to = fmaxf(mx, m2);
+  if (cm == BURST_NEG_INF)
+    to = mx == BURST_NEG_INF ? m2 : fmaxf(mx, m2 - fminf(fmaxf(24.f - __builtin_amdgcn_logf(l), 0.f), 64.f));
+  if (to != m2) m_st = to * kLn2;
+  asm volatile("" : "+v"(m_st));                   // (each product rounded by itself, and an unchanged one gives 1)
+  float now = m_st * kLog2e;
+  asm volatile("" : "+v"(m2), "+v"(now));
+  if (mx != BURST_NEG_INF || cm != BURST_NEG_INF) cm = now;
+  return fast_exp2(m2 - (now == BURST_NEG_INF ? 0.f : now));       // exp2(-inf) = 0 for a fresh row
 }
 
 // Workgroup id -> (head, block of the head).  Ids go round-robin to the 8 XCDs; each XCD gets one
@@ -201,8 +215,6 @@ inline int launch_status() {
   if (t_validate_only) return BURST_OK;
   return hipGetLastError() == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
 }
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Cross-half exchange.  v_permlane32_swap exchanges the upper 32 lanes of its first operand
 // with the lower 32 lanes of its second; fed the same value twice, every lane ends up with

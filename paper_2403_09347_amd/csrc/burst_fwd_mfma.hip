@@ -14,8 +14,9 @@
 // and vector instructions do not execute concurrently, the gain is in the absent stalls).  K and
 // V tiles are DMA-ed from HBM straight into LDS (buffer loads with the LDS modifier, no staging
 // registers) into two rings of three tiles each, two tiles ahead of their use (one barrier per
-// tile).  The running max is only raised when a row's new maximum exceeds it by more than 2^8
-// (P stays <= 2^8, exact in fp32/bf16 range), so the O rescale is rare.
+// tile).  A chunk's reference maximum is the one of its first tile, raised only when a row's new maximum exceeds it
+// by more than 2^8 (P stays <= 2^8, exact in fp32/bf16 range), so the O rescale is rare: once a chunk (see
+// raise_reference).
 // A launch takes several chunks: the state (O, m, l) is loaded once, stays in registers from chunk to
 // chunk and is stored once, and at the end of a walk the output is written with it.  With a launch per
 // chunk every workgroup drained its pipeline and moved its 128 KB of state both ways each time, all of
@@ -229,10 +230,10 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     }
   }
 
-  // The state: O^T accumulators [row block][32-wide d block], reference maximum (log2 units, see
-  // reference_of) and row sum over this lane's keys.
+  // The state: O^T accumulators [row block][32-wide d block], reference maximum (m_st as it is stored, cm the
+  // chunk's: see raise_reference) and row sum over this lane's keys.
   f32x16 o[2][4];
-  float m2[2] = {BURST_NEG_INF, BURST_NEG_INF};
+  float m_st[2] = {BURST_NEG_INF, BURST_NEG_INF}, cm[2] = {BURST_NEG_INF, BURST_NEG_INF};
   float lsum[2] = {0.f, 0.f};
 #pragma unroll
   for (int rb = 0; rb < 2; rb++)
@@ -245,7 +246,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     for (int rb = 0; rb < 2; rb++) {
       const int row = q0 + rb * 32 + lr;
       const size_t srow = (size_t)head * a.Nq + row;
-      if (row < a.Nq && (m2[rb] = reference_of(a.m[srow])) != BURST_NEG_INF) {   // (a row that has seen nothing may hold anything)
+      if (row < a.Nq && (m_st[rb] = a.m[srow]) != BURST_NEG_INF) {   // (a row that has seen nothing may hold anything)
         if (h == 0) lsum[rb] = a.l[srow];
 #pragma unroll
         for (int db = 0; db < 4; db++)
@@ -319,7 +320,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) v = fmaxf(v, sA[kb][rb][r]);
     mx[rb] = max_both_halves(v) * a.c;
-    raise = raise || (mx[rb] > m2[rb] + FWD_LAZY);
+    raise = raise || (mx[rb] > cm[rb] + FWD_LAZY);
   }
   __builtin_amdgcn_s_barrier();   // K tile 0 is consumed by every wavefront before its slot is refilled
 
@@ -398,18 +399,15 @@ burst_fwd_mfma_kernel(FwdArgs a) {
             v = fmaxf(v, x);
           }
         mx[rb] = max_both_halves(v) * a.c;
-        raise = raise || (mx[rb] > m2[rb] + FWD_LAZY);
+        raise = raise || (mx[rb] > cm[rb] + FWD_LAZY);
       }
     }
-    // ---- raise the reference max only when it is exceeded by 2^LAZY
-    if (__builtin_amdgcn_ballot_w64(raise) != 0) {             // wave-uniform, rare after the first tiles
+    // ---- a chunk's first reference max; after that, raised only when it is exceeded by 2^LAZY
+    if (__builtin_amdgcn_ballot_w64(raise) != 0) {             // wave-uniform, rare after the first tile of a chunk
       mfma_acc_fence(o);
 #pragma unroll
       for (int rb = 0; rb < 2; rb++) {
-        float m_new = mx[rb] > m2[rb] ? reference_for(mx[rb]) : m2[rb];
-        float ref = (m_new == BURST_NEG_INF) ? 0.f : m_new;
-        float alpha = fast_exp2(m2[rb] - ref);                 // exp2(-inf) = 0 for a fresh row
-        m2[rb] = m_new;
+        const float alpha = raise_reference(m_st[rb], cm[rb], mx[rb], sum_both_halves(lsum[rb]));
         lsum[rb] *= alpha;
 #pragma unroll
         for (int db = 0; db < 4; db++)
@@ -420,7 +418,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     }
     float nref[2];
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++) nref[rb] = (m2[rb] == BURST_NEG_INF) ? 0.f : -m2[rb];
+    for (int rb = 0; rb < 2; rb++) nref[rb] = (m_st[rb] == BURST_NEG_INF) ? 0.f : -(m_st[rb] * kLog2e);
 
     // The 64 MFMAs of a tile (32 for S^T of the next tile, then 32 for O^T += V^T P^T) are
     // hand-interleaved with the vector work, one MFMA per slice, scheduling barriers between
@@ -528,7 +526,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
       }
       if (i == 28) mx[0] = max_both_halves(nmax0) * a.c;
       if (i == 29) mx[1] = max_both_halves(nmax1) * a.c;
-      if (i == 30) raise = (mx[0] > m2[0] + FWD_LAZY) || (mx[1] > m2[1] + FWD_LAZY);
+      if (i == 30) raise = (mx[0] > cm[0] + FWD_LAZY) || (mx[1] > cm[1] + FWD_LAZY);
       __builtin_amdgcn_sched_barrier(0);
     }
     // The 8 DMA loads just issued may stay in flight; everything older (the tiles the next
@@ -559,7 +557,9 @@ burst_fwd_mfma_kernel(FwdArgs a) {
       for (int rb = 0; rb < 2; rb++) {
         const float both = sum_both_halves(lsum[rb]);
         lsum[rb] = h == 0 ? both : 0.f;
+        cm[rb] = BURST_NEG_INF;
       }
+      raise = true;
     }
     run = min(at.left, min(kf.left, vf.left));
     return true;
@@ -584,11 +584,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
     const float l_all = sum_both_halves(lsum[rb]);
     if (row >= a.Nq) continue;
     const size_t srow = (size_t)head * a.Nq + row;
-    // a row whose reference has not moved keeps its m bit for bit
-    float m_st = a.fresh ? BURST_NEG_INF : a.m[srow];
-    if (m2[rb] != reference_of(m_st)) m_st = m2[rb] * kLn2;
-    asm volatile("" : "+v"(m_st));                 // (m as the next launch would load it)
-    if (a.O_acc != nullptr && (a.fresh || m2[rb] != BURST_NEG_INF)) {   // rows that never saw a key keep their state
+    if (a.O_acc != nullptr && (a.fresh || m_st[rb] != BURST_NEG_INF)) {   // rows that never saw a key keep their state
       float* const orow = a.O_acc + srow * 128;
 #pragma unroll
       for (int db = 0; db < 4; db++)
@@ -599,7 +595,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
           for (int b = 0; b < 4; b++) v[b] = o[rb][db][4 * q4 + b];
           *reinterpret_cast<f32x4*>(orow + db * 32 + 8 * q4 + 4 * h) = v;
         }
-      if (h == 0) { a.m[srow] = m_st; a.l[srow] = l_all; }
+      if (h == 0) { a.m[srow] = m_st[rb]; a.l[srow] = l_all; }
     }
     if (a.O_out != nullptr) {
       const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
@@ -613,7 +609,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
           for (int b = 0; b < 4; b++) v[b] = (bf16)(l_all > 0.f ? o[rb][db][4 * q4 + b] * inv : 0.f);
           *reinterpret_cast<bf16x4*>(out + db * 32 + 8 * q4 + 4 * h) = v;
         }
-      if (h == 0) a.lse[srow] = l_all > 0.f ? m_st + __logf(l_all) : BURST_NEG_INF;
+      if (h == 0) a.lse[srow] = l_all > 0.f ? m_st[rb] + __logf(l_all) : BURST_NEG_INF;
     }
   }
 }

@@ -194,10 +194,36 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   const int wu = __builtin_amdgcn_readfirstlane(w);
   const unsigned lds0 = lds_addr(smem);
 
-  // The chunks' visible tiles (or list entries) form one sequence; this workgroup takes every
-  // `splits`-th of it, tile after tile, with the next one in flight across the chunk boundaries.
+  // The chunks' visible tiles (or list entries) form one sequence, walked with the next tile in flight across the
+  // chunk boundaries.  splits > 1: this workgroup takes one of that many runs of it, of equal length.
   constexpr int NL = SF_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
-  int c = -1, ft = split, lo = 0, hi = 0;         // chunk, position in it, first and end position
+  auto tiles_of = [&](const Chunk& C, int& lo, int& hi) __attribute__((always_inline)) {   // that some row of the workgroup sees
+    lo = 0; hi = (C.Nc + SF_BC - 1) / SF_BC;
+    if (a.window > 0) {                            // keys before the window of the first row
+      const long long first = a.q_off + (long long)qb * SF_BR - a.window + 1 - C.k_off;
+      if (first >= C.Nc) lo = hi;
+      else if (first > 0) lo = (int)(first / SF_BC);
+    }
+    if (a.causal) {                                // keys after the last row
+      const long long last = a.q_off + min(qb * SF_BR + SF_BR, a.Nq) - 1 - C.k_off;
+      if (last < 0) hi = lo;
+      else if (last / SF_BC + 1 < hi) hi = (int)(last / SF_BC) + 1;
+    }
+    hi = max(hi, lo);
+  };
+  int c = -1, ft = 0, lo = 0, hi = 0;             // chunk, position in it, first and end position
+  int left = 0x7fffffff;                          // tiles of the run from the one that `advance` finds next
+  if constexpr (!SPARSE)
+    if (a.splits > 1) {
+      int all = 0;
+      for (int i = 0; i < a.n; i++) {
+        tiles_of(a.ch[i], lo, hi);
+        all += hi - lo;
+      }
+      lo = hi = 0;
+      ft = all * split / a.splits;                 // (at most 512 runs of 32 x 2^16 tiles)
+      left = all * (split + 1) / a.splits - ft;
+    }
   int f_tile = 0, f_bits = 0xf, f_Nc = 0;         // the tile that was fetched last
   long long f_koff = 0;
   bool f_first = false;                           // ... is the first one of its chunk
@@ -205,24 +231,14 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   int goff[NL];
   __amdgpu_buffer_rsrc_t krs = make_rsrc(nullptr, 0), vrs = krs;
   auto advance = [&](int step) __attribute__((always_inline)) {
+    if (--left < 0) return false;
     ft += step;
-    f_first = false;
     while (ft >= hi) {
       const int past = ft - hi;
       if (++c >= a.n) return false;
       const Chunk& C = a.ch[c];
       f_Nc = C.Nc; f_koff = C.k_off;
-      lo = 0; hi = (f_Nc + SF_BC - 1) / SF_BC;
-      if (a.window > 0) {                          // keys before the window of the first row
-        const long long first = a.q_off + (long long)qb * SF_BR - a.window + 1 - f_koff;
-        if (first >= f_Nc) lo = hi;
-        else if (first > 0) lo = (int)(first / SF_BC);
-      }
-      if (a.causal) {                              // keys after the last row
-        const long long last = a.q_off + min(qb * SF_BR + SF_BR, a.Nq) - 1 - f_koff;
-        if (last < 0) hi = lo;
-        else if (last / SF_BC + 1 < hi) hi = (int)(last / SF_BC) + 1;
-      }
+      tiles_of(C, lo, hi);
       if (hi > lo) {
         const unsigned kpitch = (unsigned)C.ks_r * 2u;           // bytes between key rows
         const size_t base = C.kv_base(kvhead, a.lay.kv_heads);
@@ -245,10 +261,9 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
           lo = 0;
         }
       }
-      hi = max(hi, lo);
       ft = lo + past;
-      f_first = true;
     }
+    f_first = ft == lo;
     f_tile = ft;
     if constexpr (SPARSE) {
       const int e = __builtin_amdgcn_readfirstlane(s_list[1 + ft]);
@@ -273,16 +288,15 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   const bf16* Qh = a.Q + a.lay.q_base(head);
 #pragma unroll
   for (int ks = 0; ks < S_KS; ks++) qf[ks] = s_load8(Qh + (size_t)row * a.lay.qs_r + ks * 16 + h * 8, row < a.Nq && (!S_PAD || ks * 16 + h * 8 < d));
-  // The state in registers: O^T accumulators, reference maximum m2 (log2 units, see reference_of), and
-  // the row sum over this lane's keys.  m_st is m as it is stored (natural log); a row whose reference
-  // has not moved keeps it bit for bit.
+  // The state in registers: O^T accumulators, reference maximum (m_st as it is stored, cm the chunk's: see
+  // raise_reference), and the row sum over this lane's keys.
   const size_t srow = (size_t)head * a.Nq + (row < a.Nq ? row : 0);
   f32x16 o[S_DB];
 #pragma unroll
   for (int db = 0; db < S_DB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) o[db][r] = 0.f;
-  float m_st = BURST_NEG_INF, lsum = 0.f;
+  float m_st = BURST_NEG_INF, cm = BURST_NEG_INF, lsum = 0.f;
   if (!a.fresh && row < a.Nq) {
     m_st = a.m[srow];
     if (m_st != BURST_NEG_INF) {                   // (a row that has seen nothing may hold anything)
@@ -299,39 +313,25 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         }
     }
   }
-  float m2 = reference_of(m_st);
-  const float m_in = m2;
-  // What a store of the state and a load by the next launch do to it (to the row sum; m2 comes back as
-  // it was): a walk gives the same bits whether its chunks come in one launch or one by one.
+  // A new chunk: what a store of the state and a load by the next launch do to it (to the row sum; m_st comes back
+  // as it was), so that a walk gives the same bits whether its chunks come in one launch or one by one.
   auto settle = [&]() __attribute__((always_inline)) {
     const float both = sum_both_halves(lsum);
     lsum = h == 0 ? both : 0.f;
+    cm = BURST_NEG_INF;
   };
 
   int kaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
   for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
   s_taddr(lane, taddr);
-  const long long wave_first_q = a.q_off + q0, wave_last_q = wave_first_q + 31;
+  const long long wave_first_q = a.q_off + qb * SF_BR + wu * 32, wave_last_q = wave_first_q + 31;   // (scalar)
   bf16x2 ones;
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
 
-  bool begun = false;
-  for (int buf = 0; have; buf ^= 1) {
-    const int kt = f_tile, Nc = f_Nc;
-    const long long k_off = f_koff;
-    const bool mine = ((f_bits >> wu) & 1) != 0, first = f_first;
-    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0): the tile landed, reads of the one before are done
-    __builtin_amdgcn_s_barrier();
-    have = advance(a.splits);
-    if (have) fetch(buf ^ 1);
-    if (first && begun) settle();
-    begun = true;
-    if (!mine) continue;                           // block flags hide the tile from this wavefront's rows
-    const char* kl = smem + buf * SF_TILE;
-    const char* vl = smem + (2 + buf) * SF_TILE;
+  // The scores of a tile, masked, and the row's maximum of them (log2 units).
+  auto scores = [&](const char* kl, int kt, int Nc, long long k_off, f32x16 (&s)[2]) __attribute__((always_inline)) {
     // S^T = K Q^T: register r of key block kb = key kt*64 + kb*32 + 8*(r/4) + 4h + r%4
-    f32x16 s[2];
 #pragma unroll
     for (int kb = 0; kb < 2; kb++)
 #pragma unroll
@@ -365,19 +365,45 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     for (int kb = 0; kb < 2; kb++)
 #pragma unroll
       for (int r = 0; r < 16; r++) v = fmaxf(v, s[kb][r]);
-    const float mx = max_both_halves(v) * a.c;
-    if (__builtin_amdgcn_ballot_w64(mx > m2 + S_LAZY) != 0) {   // raise the reference max (rare after the first tiles)
-      const float m_new = mx > m2 ? reference_for(mx) : m2;
-      const float ref = (m_new == BURST_NEG_INF) ? 0.f : m_new;
-      const float alpha = fast_exp2(m2 - ref);
-      m2 = m_new;
+    return max_both_halves(v) * a.c;
+  };
+  bool begun = false;
+  // A run that begins inside a chunk takes the chunk's references from its first tile like every other run (one more
+  // K tile and its scores per run).
+  if constexpr (!SPARSE)
+    if (have && !f_first) {
+#pragma unroll
+      for (int il = 0; il < NL; il++)
+        dma_b128_to_lds(krs, lds0 + SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)lo * ktile) + goff[il]);
+      __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0), lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      f32x16 s[2];
+      raise_reference(m_st, cm, scores(smem + SF_TILE, lo, f_Nc, f_koff, s), 0.f);
+    }
+  for (int buf = 0; have; buf ^= 1) {
+    const int kt = f_tile, Nc = f_Nc;
+    const long long k_off = f_koff;
+    const bool mine = ((f_bits >> wu) & 1) != 0, first = f_first;
+    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0): the tile landed, reads of the one before are done
+    __builtin_amdgcn_s_barrier();
+    have = advance(1);
+    if (have) fetch(buf ^ 1);
+    if (first && begun) settle();
+    begun = true;
+    if (!mine) continue;                           // block flags hide the tile from this wavefront's rows
+    const char* kl = smem + buf * SF_TILE;
+    const char* vl = smem + (2 + buf) * SF_TILE;
+    f32x16 s[2];
+    const float mx = scores(kl, kt, Nc, k_off, s);
+    if (__builtin_amdgcn_ballot_w64(mx > cm + S_LAZY) != 0) {   // a chunk's first reference, or raised (rare)
+      const float alpha = raise_reference(m_st, cm, mx, sum_both_halves(lsum));
       lsum *= alpha;
 #pragma unroll
       for (int db = 0; db < S_DB; db++)
 #pragma unroll
         for (int r = 0; r < 16; r++) o[db][r] *= alpha;
     }
-    const float nref = (m2 == BURST_NEG_INF) ? 0.f : -m2;
+    const float nref = (m_st == BURST_NEG_INF) ? 0.f : -(m_st * kLog2e);
     bf16x8 pf[4][S_TERMS];                         // P^T fragments per 16-key group
 #pragma unroll
     for (int kg = 0; kg < 4; kg++)
@@ -407,8 +433,6 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
   const float l_all = sum_both_halves(lsum);
-  if (m2 != m_in) m_st = m2 * kLn2;
-  asm volatile("" : "+v"(m_st));                   // (m as the next launch would load it)
   if (row >= a.Nq) return;
   // lane (lr, h) holds row lr, columns db*32 + 8*q4 + 4h + (0..3)
   if (a.splits > 1) {                              // a partial state: [split][rows][d] O, then m (log2 units) and l
@@ -426,12 +450,12 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       }
     if (h == 0) {
       float* const ml = a.part + (size_t)a.splits * rows * d;
-      ml[pr] = m2;
+      ml[pr] = m_st * kLog2e;
       ml[(size_t)a.splits * rows + pr] = l_all;
     }
     return;
   }
-  if (a.O_acc != nullptr && (a.fresh || m2 != BURST_NEG_INF)) {   // rows that never saw a key keep their state
+  if (a.O_acc != nullptr && (a.fresh || m_st != BURST_NEG_INF)) {   // rows that never saw a key keep their state
     float* const orow = a.O_acc + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
