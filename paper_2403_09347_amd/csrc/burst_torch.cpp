@@ -7,6 +7,7 @@
 #include <c10/hip/HIPStream.h>
 
 #include <cmath>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -57,8 +58,9 @@ struct Call {                        // what forward and backward have in common
   std::vector<burst_chunk> chunks;
 };
 
-Call describe(const Tensor& q, const variable_list& ks, const variable_list& vs, const variable_list& masks, double scale,
-              bool causal, int64_t q_off, int64_t window, int64_t block) {
+// mask_of: for each chunk the place of its block flags in `masks`, -1 = none (empty: no chunk has any).
+Call describe(const Tensor& q, const variable_list& ks, const variable_list& vs, const variable_list& masks,
+              const std::vector<int64_t>& mask_of, double scale, bool causal, int64_t q_off, int64_t window, int64_t block) {
   Call c;
   burst_params& p = c.p;
   p.B = (int32_t)q.size(0); p.H = (int32_t)q.size(1); p.Nq = (int32_t)q.size(2); p.d = (int32_t)q.size(3);
@@ -76,8 +78,8 @@ Call describe(const Tensor& q, const variable_list& ks, const variable_list& vs,
     k.k_off = at;
     at += ks[i].size(2);
     set_strides(k.kv_strides, ks[i]);
-    if (!masks.empty()) {
-      const Tensor& m = masks[i];
+    if (!mask_of.empty() && mask_of[i] >= 0) {
+      const Tensor& m = masks[mask_of[i]];
       const int64_t rows = (q.size(2) + block - 1) / block, cols = (ks[i].size(2) + block - 1) / block;
       const bool one = m.dim() == 2 && m.size(0) == rows && m.size(1) == cols;
       const bool each = m.dim() == 4 && m.size(0) == q.size(0) && m.size(1) == q.size(1) && m.size(2) == rows && m.size(3) == cols;
@@ -101,14 +103,15 @@ void* stream_of(const Tensor& t) { return (void*)c10::hip::getCurrentHIPStream(t
 
 class Attention : public torch::autograd::Function<Attention> {
  public:
-  // kvm: the chunks' keys, then their values, then (n_masks of them) their block flags
-  static variable_list forward(AutogradContext* ctx, const Tensor& q_in, at::TensorList kvm, int64_t n_masks, double scale,
-                               bool causal, int64_t q_off, int64_t window, int64_t block) {
-    const size_t n = (kvm.size() - (size_t)n_masks) / 2;
+  // kvm: the keys of n chunks, then their values, then the block flags of those that have some (mask_of)
+  static variable_list forward(AutogradContext* ctx, const Tensor& q_in, at::TensorList kvm, int64_t n_chunks,
+                               const std::vector<int64_t>& mask_of, double scale, bool causal, int64_t q_off, int64_t window,
+                               int64_t block) {
+    const size_t n = (size_t)n_chunks;
     const Tensor q = addressable(q_in) ? q_in : q_in.contiguous();
     variable_list ks(kvm.begin(), kvm.begin() + n), vs(kvm.begin() + n, kvm.begin() + 2 * n), masks(kvm.begin() + 2 * n, kvm.end());
     for (size_t i = 0; i < n; i++) pair_in_place(ks[i], vs[i]);
-    const Call c = describe(q, ks, vs, masks, scale, causal, q_off, window, block);
+    const Call c = describe(q, ks, vs, masks, mask_of, scale, causal, q_off, window, block);
     Tensor O = torch::empty_strided(q.sizes(), q.strides(), q.options());   // O lies in memory like Q
     Tensor lse = torch::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(torch::kFloat));
     const Tensor ws = scratch(c, BURST_WALK_NO_STATE, q);
@@ -118,6 +121,7 @@ class Attention : public torch::autograd::Function<Attention> {
     for (auto* l : {&ks, &vs, &masks}) saved.insert(saved.end(), l->begin(), l->end());
     ctx->save_for_backward(saved);
     ctx->saved_data["n"] = (int64_t)n;
+    ctx->saved_data["mask_of"] = mask_of;
     ctx->saved_data["scale"] = scale;
     ctx->saved_data["causal"] = causal;
     ctx->saved_data["q_off"] = q_off;
@@ -131,14 +135,15 @@ class Attention : public torch::autograd::Function<Attention> {
   static variable_list backward(AutogradContext* ctx, variable_list grads) {
     const variable_list s = ctx->get_saved_variables();
     const size_t n = (size_t)ctx->saved_data["n"].toInt();
-    variable_list out(1 + (s.size() - 3) + 6);    // q, kvm, and six arguments that are no tensors
+    variable_list out(1 + (s.size() - 3) + 7);    // q, kvm, and seven arguments that are no tensors
     if (!grads[0].defined()) return out;
     // Hooks on saved tensors may have returned each of them in another layout than it was saved in.
     const Tensor q = addressable(s[0]) ? s[0] : s[0].contiguous(), O = lying_like(s[1], q), lse = s[2].contiguous();
     variable_list ks(s.begin() + 3, s.begin() + 3 + n), vs(s.begin() + 3 + n, s.begin() + 3 + 2 * n), masks(s.begin() + 3 + 2 * n, s.end());
     for (size_t i = 0; i < n; i++) pair_in_place(ks[i], vs[i]);
-    Call c = describe(q, ks, vs, masks, ctx->saved_data["scale"].toDouble(), ctx->saved_data["causal"].toBool(),
-                      ctx->saved_data["q_off"].toInt(), ctx->saved_data["window"].toInt(), ctx->saved_data["block"].toInt());
+    Call c = describe(q, ks, vs, masks, ctx->saved_data["mask_of"].toIntVector(), ctx->saved_data["scale"].toDouble(),
+                      ctx->saved_data["causal"].toBool(), ctx->saved_data["q_off"].toInt(), ctx->saved_data["window"].toInt(),
+                      ctx->saved_data["block"].toInt());
     const Tensor g = lying_like(grads[0].to(q.scalar_type()), q);
     Tensor D = torch::empty(lse.sizes(), lse.options()), dQ = torch::empty(q.sizes(), q.options());
     out[0] = dQ;
@@ -156,8 +161,8 @@ class Attention : public torch::autograd::Function<Attention> {
 };
 
 std::vector<Tensor> attention(const Tensor& q, const std::vector<Tensor>& ks, const std::vector<Tensor>& vs,
-                              const std::vector<Tensor>& masks, double scale, bool causal, int64_t q_off, int64_t window,
-                              int64_t block) {
+                              const std::vector<std::optional<Tensor>>& masks, double scale, bool causal, int64_t q_off,
+                              int64_t window, int64_t block) {
   TORCH_CHECK_VALUE(!ks.empty() && ks.size() == vs.size(), "one key and one value tensor per chunk, at least one chunk, expected");
   TORCH_CHECK_VALUE(masks.empty() || masks.size() == ks.size(), "one block mask per chunk expected");
   TORCH_CHECK_VALUE(q.dim() == 4 && (q.scalar_type() == torch::kBFloat16 || q.scalar_type() == torch::kFloat),
@@ -169,8 +174,12 @@ std::vector<Tensor> attention(const Tensor& q, const std::vector<Tensor>& ks, co
                       t.size(3) == q.size(3), "keys and values: [B, Hkv, Nc, d] of the type of q expected");
     TORCH_CHECK_VALUE(t.is_cuda() && t.device() == q.device(), "tensors on one device expected");
   }
-  kvm.insert(kvm.end(), masks.begin(), masks.end());
-  return Attention::apply(q, at::TensorList(kvm), (int64_t)masks.size(), scale, causal, q_off, window, block);
+  std::vector<int64_t> mask_of;
+  for (const auto& m : masks) {
+    mask_of.push_back(m.has_value() ? (int64_t)(kvm.size() - 2 * ks.size()) : -1);
+    if (m.has_value()) kvm.push_back(*m);
+  }
+  return Attention::apply(q, at::TensorList(kvm), (int64_t)ks.size(), mask_of, scale, causal, q_off, window, block);
 }
 
 }  // namespace

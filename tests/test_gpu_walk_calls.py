@@ -181,3 +181,19 @@ def test_captured_walk_outlives_the_workspace_of_a_longer_one():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want))
         assert all(bool((t == 7).all()) for t in others)
+
+
+def test_differentiable_call_with_flags_for_some_chunks_only():
+    """block_masks may hold None for a chunk without flags: the same O, lse and gradients as the walk gives."""
+    from paper_2403_09347_amd.autograd import burst_attention
+    case = workloads.make_case(B=1, H=2, d=64, Nq=100, chunk_rows=[90, 70, 64], dtype="bf16", seed=13, device=DEV, block=64,
+                               pattern="random", density=0.5)
+    for masks in ([case["masks"][0], None, case["masks"][2]], [None, case["masks"][1], None], [None] * 3):
+        walk = RingWalk(case["Q"], case["scale"], block=64)
+        O0, lse0 = walk.forward(case["K"], case["V"], case["k_offs"], masks=masks)
+        dQ, dKs, dVs = walk.backward_in_dtype(case["K"], case["V"], case["k_offs"], case["dO"], masks=masks)
+        leaves = [t.clone().requires_grad_(True) for t in [case["Q"], *case["K"], *case["V"]]]
+        O, lse = burst_attention(leaves[0], leaves[1:4], leaves[4:], block_masks=masks, block=64)
+        assert torch.equal(O, O0) and torch.equal(lse, lse0)
+        for a, b in zip(torch.autograd.grad(O, leaves, case["dO"]), [dQ, *dKs, *dVs]):
+            assert torch.equal(a, b)

@@ -202,3 +202,12 @@ def test_walk_refuses_lists_shorter_than_the_keys():
     for args in ((Ks, Vs[:1], offs), (Ks, Vs, offs[:1])):
         with pytest.raises(IndexError):
             walk.forward(*args)
+
+
+def test_differentiable_call_takes_none_for_a_chunk_without_flags():
+    """None among the block masks reaches the check of the tensors (here: host tensors) instead of a TypeError."""
+    import torch
+    from paper_2403_09347_amd.autograd import burst_attention
+    q = torch.zeros((1, 2, 64, 64), dtype=torch.bfloat16)
+    with pytest.raises(ValueError, match="tensors on one device expected"):
+        burst_attention(q, [q, q], [q, q], block_masks=[torch.ones((1, 1), dtype=torch.uint8), None], block=64)
