@@ -169,6 +169,8 @@ std::vector<Tensor> attention(const Tensor& q, const std::vector<Tensor>& ks, co
                     "q: [B, H, Nq, d] of bfloat16 or float32 expected");
   variable_list kvm(ks);
   kvm.insert(kvm.end(), vs.begin(), vs.end());
+  for (size_t i = 0; i < ks.size(); i++)
+    TORCH_CHECK_VALUE(ks[i].dim() == 4 && ks[i].sizes() == vs[i].sizes(), "the keys and values of a chunk: the same sizes expected");
   for (const Tensor& t : kvm) {
     TORCH_CHECK_VALUE(t.dim() == 4 && t.scalar_type() == q.scalar_type() && t.size(0) == q.size(0) && t.size(1) == ks[0].size(1) &&
                       t.size(3) == q.size(3), "keys and values: [B, Hkv, Nc, d] of the type of q expected");

@@ -211,3 +211,13 @@ def test_differentiable_call_takes_none_for_a_chunk_without_flags():
     q = torch.zeros((1, 2, 64, 64), dtype=torch.bfloat16)
     with pytest.raises(ValueError, match="tensors on one device expected"):
         burst_attention(q, [q, q], [q, q], block_masks=[torch.ones((1, 1), dtype=torch.uint8), None], block=64)
+
+
+def test_differentiable_call_refuses_values_of_other_sizes_than_their_keys():
+    """The library reads as many rows of V as K has."""
+    import torch
+    from paper_2403_09347_amd.autograd import burst_attention
+    new = lambda rows: torch.zeros((1, 2, rows, 64), dtype=torch.bfloat16)
+    for k, v in ((new(64), new(63)), (new(64), new(65))):
+        with pytest.raises(ValueError, match="same sizes"):
+            burst_attention(new(8), [new(64), k], [new(64), v])
