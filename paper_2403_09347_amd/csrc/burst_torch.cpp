@@ -4,6 +4,7 @@
 // Why native: in Python the two halves of a call ran on two threads (autograd's backward thread is another
 // one) and cost 200 us of host time at any size, several times the GPU time of a short sequence.
 #include <torch/extension.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
 
 #include <cmath>
@@ -107,6 +108,7 @@ class Attention : public torch::autograd::Function<Attention> {
   static variable_list forward(AutogradContext* ctx, const Tensor& q_in, at::TensorList kvm, int64_t n_chunks,
                                const std::vector<int64_t>& mask_of, double scale, bool causal, int64_t q_off, int64_t window,
                                int64_t block) {
+    const c10::DeviceGuard on(q_in.device());     // the library launches on the current device
     const size_t n = (size_t)n_chunks;
     const Tensor q = addressable(q_in) ? q_in : q_in.contiguous();
     variable_list ks(kvm.begin(), kvm.begin() + n), vs(kvm.begin() + n, kvm.begin() + 2 * n), masks(kvm.begin() + 2 * n, kvm.end());
@@ -137,6 +139,7 @@ class Attention : public torch::autograd::Function<Attention> {
     const size_t n = (size_t)ctx->saved_data["n"].toInt();
     variable_list out(1 + (s.size() - 3) + 7);    // q, kvm, and seven arguments that are no tensors
     if (!grads[0].defined()) return out;
+    const c10::DeviceGuard on(s[0].device());
     // Hooks on saved tensors may have returned each of them in another layout than it was saved in.
     const Tensor q = addressable(s[0]) ? s[0] : s[0].contiguous(), O = lying_like(s[1], q), lse = s[2].contiguous();
     variable_list ks(s.begin() + 3, s.begin() + 3 + n), vs(s.begin() + 3 + n, s.begin() + 3 + 2 * n), masks(s.begin() + 3 + 2 * n, s.end());
