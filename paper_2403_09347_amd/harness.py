@@ -26,7 +26,7 @@ class RingWalk:
         self.O = torch.empty_strided(Q.shape, Q.stride(), device=dev, dtype=Q.dtype)   # O and dO lie in memory like Q
         self.lse = torch.empty_like(self.m)
         self.D = torch.empty_like(self.m)
-        self._workspace = None
+        self._workspace, self._workspace_stream = None, None
 
     def params(self, Nc, k_off, mask=None, K_c=None):
         """K_c: the chunk the call is about (its strides go into the parameter block; Q's always do)."""
@@ -68,14 +68,17 @@ class RingWalk:
 
     def _scratch(self, chunks, p, flags=0):
         """Workspace of a walk, kept by the walk (None: these sizes use none).  Under capture the graph's pool
-        owns it: a graph must not hold the address of one that a longer walk replaces."""
+        owns it: a graph must not hold the address of one that a longer walk replaces.  A walk on another stream
+        takes a new one: the allocator gives a block that is replaced to the next one that asks on the stream it was
+        allocated on, which waits for the kernels of that stream only."""
         need = B.burst_walk_workspace_bytes(chunks, p, flags)
         if need == 0:
             return None
         if torch.cuda.is_current_stream_capturing():
             return torch.empty(need, device=self.Q.device, dtype=torch.uint8)
-        if self._workspace is None or self._workspace.numel() < need:
-            self._workspace = torch.empty(need, device=self.Q.device, dtype=torch.uint8)
+        stream = torch.cuda.current_stream(self.Q.device)
+        if self._workspace is None or self._workspace.numel() < need or self._workspace_stream != stream:
+            self._workspace, self._workspace_stream = torch.empty(need, device=self.Q.device, dtype=torch.uint8), stream
         return self._workspace
 
     # ---- backward (Alg. 2), query slice pinned, chunks walked

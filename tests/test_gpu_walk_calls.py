@@ -197,3 +197,29 @@ def test_differentiable_call_with_flags_for_some_chunks_only():
         assert torch.equal(O, O0) and torch.equal(lse, lse0)
         for a, b in zip(torch.autograd.grad(O, leaves, case["dO"]), [dQ, *dKs, *dVs]):
             assert torch.equal(a, b)
+
+
+def test_workspace_belongs_to_the_stream_that_uses_it(monkeypatch):
+    """One walk object on two streams in turn, shorter and longer walks: every workspace handed to the library was
+    allocated on the stream of that call, so that the allocator cannot give it away while the call's kernels run."""
+    case = workloads.make_case(B=1, H=2, d=64, Nq=40, chunk_rows=[1024] * 6, dtype="bf16", seed=9, device=DEV)
+    walk = RingWalk(case["Q"], case["scale"])
+    used, real = [], B.burst_walk_fwd
+
+    def spy(*args):
+        ws = args[-1]
+        at = [s["stream"] for s in torch.cuda.memory_snapshot() if s["address"] <= ws.data_ptr() < s["address"] + s["total_size"]]
+        used.append((at, torch.cuda.current_stream().cuda_stream))
+        real(*args)
+
+    monkeypatch.setattr(B, "burst_walk_fwd", spy)
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    outs = []
+    for stream, n in ((main, 2), (side, 2), (side, 4), (main, 6), (side, 6)):
+        stream.wait_stream(main if stream is side else side)
+        with torch.cuda.stream(stream):
+            outs.append([t.clone() for t in walk.forward(case["K"][:n], case["V"][:n], case["k_offs"][:n])])
+    torch.cuda.synchronize()
+    assert len(used) == 5 and all(at == [now] for at, now in used)
+    for i, j in ((0, 1), (3, 4)):
+        assert all(torch.equal(a, b) for a, b in zip(outs[i], outs[j]))
