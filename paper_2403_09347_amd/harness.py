@@ -47,7 +47,7 @@ class RingWalk:
 
     def forward(self, Ks, Vs, k_offs, order=None, masks=None):
         """masks: optional list of per-chunk block masks (uint8 device tensors, see binding.params)."""
-        if type(self).step is not RingWalk.step:     # a subclass with a chunk step of its own
+        if any(self._own(name) for name in ("init", "step", "finalize")):
             self.init()
             for j in (range(len(Ks)) if order is None else order):
                 self.step(Ks[j], Vs[j], k_offs[j], None if masks is None else masks[j])
@@ -60,6 +60,10 @@ class RingWalk:
         chunks = B.chunk_array(Ks, Vs, k_offs, masks, p)
         B.burst_walk_fwd(self.Q, chunks, self.O_acc, self.m, self.l, self.O, self.lse, p, self._scratch(chunks, p))
         return self.O, self.lse
+
+    def _own(self, name):
+        """Whether a subclass (or the object) has a part of the walk of its own, which the whole-walk calls would pass by."""
+        return getattr(getattr(self, name), "__func__", None) is not getattr(RingWalk, name)
 
     def _walk_params(self):
         p = self.params(0, 0)
@@ -116,7 +120,11 @@ class RingWalk:
             dKs, dVs = [new(K) for K in Ks], [new(V) for V in Vs]
         p = self._walk_params()
         chunks = B.chunk_array(Ks, Vs, k_offs, masks, p, dKs, dVs, dQ.dtype)
-        B.burst_walk_bwd(self.Q, chunks, self.O, self._like_q(dO), self.lse, self.D, dQ, p, accumulate_dq=accumulate,
+        dO, O = self._like_q(dO), self.O
+        if self._own("prepare"):
+            self.prepare(dO)
+            O = None                                 # (D is there)
+        B.burst_walk_bwd(self.Q, chunks, O, dO, self.lse, self.D, dQ, p, accumulate_dq=accumulate,
                          accumulate_dkv=False, workspace=self._scratch(chunks, p, B.BURST_WALK_HALF_GRADS if dQ.dtype != torch.float32 else 0))
         return dQ, dKs, dVs
 

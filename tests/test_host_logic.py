@@ -1,4 +1,6 @@
-"""Host-side logic that needs no GPU: workload table, FLOP accounting, bench argument handling."""
+"""Host-side logic that needs no GPU: workload table, FLOP accounting, bench argument handling,
+checks of the calls' arguments."""
+import ctypes
 import json
 import math
 import os
@@ -221,3 +223,30 @@ def test_differentiable_call_refuses_values_of_other_sizes_than_their_keys():
     for k, v in ((new(64), new(63)), (new(64), new(65))):
         with pytest.raises(ValueError, match="same sizes"):
             burst_attention(new(8), [new(64), k], [new(64), v])
+
+
+def test_walk_calls_the_parts_that_a_subclass_has_of_its_own(monkeypatch):
+    """A subclass (or an object) with an init, step, finalize or prepare of its own has it called."""
+    import torch
+    from paper_2403_09347_amd import binding, harness
+    calls = []
+    for name in ("burst_state_init", "burst_local_fwd", "burst_finalize", "burst_bwd_prepare", "burst_walk_fwd"):
+        monkeypatch.setattr(binding, name, lambda *a, name=name, **k: calls.append(name))
+    monkeypatch.setattr(binding, "burst_walk_bwd", lambda Q, chunks, O, *a, **k: calls.append("burst_walk_bwd" if O is not None else "burst_walk_bwd, D given"))
+    monkeypatch.setattr(harness.RingWalk, "_scratch", lambda self, chunks, p, flags=0: None)
+    monkeypatch.setattr(binding, "_ptr", lambda t: ctypes.c_void_p(t.data_ptr()))
+    OnDevice = _device_stand_in()
+    new = lambda: torch.zeros((1, 2, 8, 64), dtype=torch.bfloat16).as_subclass(OnDevice)
+    chunks = [new(), new()], [new(), new()], [0, 8]
+    walk = lambda cls: (calls.clear(), w := cls(new(), 0.125), w.forward(*chunks), w.backward(*chunks, new()))[1] and list(calls)
+    assert walk(harness.RingWalk) == ["burst_walk_fwd", "burst_walk_bwd"]
+    for part in ("init", "step", "finalize", "prepare"):
+        def own(self, *args, part=part):
+            calls.append("own " + part)
+            return getattr(harness.RingWalk, part)(self, *args)
+        got = walk(type("Own", (harness.RingWalk,), {part: own}))
+        assert got.count("own " + part) == (2 if part == "step" else 1)
+        if part == "prepare":
+            assert got == ["burst_walk_fwd", "own prepare", "burst_bwd_prepare", "burst_walk_bwd, D given"]
+        else:
+            assert [c for c in got if c[:3] != "own"] == ["burst_state_init", "burst_local_fwd", "burst_local_fwd", "burst_finalize", "burst_walk_bwd"]
