@@ -137,6 +137,25 @@ __device__ __forceinline__ float raise_reference(float& m_st, float& cm, float m
   return fast_exp2(m2 - (now == BURST_NEG_INF ? 0.f : now));       // exp2(-inf) = 0 for a fresh row
 }
 
+// s x scale, rounded: the opaque move keeps the compiler from contracting it with a following difference into one fma.
+__device__ __forceinline__ float product(float s, float scale) {
+  float x = s * scale;
+  asm("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ float above(float s, float scale, float ref) { return product(s, scale) - ref; }
+
+// The same with everything in natural units (m_st, cm and mx): no product between a score, its maximum and what is stored.
+__device__ __forceinline__ float raise_reference_natural(float& m_st, float& cm, float mx, float l) {
+  const float was = m_st;
+  float to = fmaxf(mx, was);
+  if (cm == BURST_NEG_INF)
+    to = mx == BURST_NEG_INF ? was : fmaxf(mx, was - fminf(fmaxf(24.f - __builtin_amdgcn_logf(l), 0.f), 64.f) * kLn2);
+  m_st = to;
+  if (mx != BURST_NEG_INF || cm != BURST_NEG_INF) cm = to;
+  return fast_exp2((was - (to == BURST_NEG_INF ? 0.f : to)) * kLog2e);
+}
+
 // Workgroup id -> (head, block of the head).  Ids go round-robin to the 8 XCDs; each XCD gets one
 // run of consecutive blocks, so that a head's tensors stay in one L2 and all XCDs get the same number
 // of workgroups whatever the number of heads.  False: nothing to do (the grid is rounded up to 8).

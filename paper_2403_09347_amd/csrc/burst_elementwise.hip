@@ -157,7 +157,7 @@ zero_fill_kernel(float* __restrict__ p, long long n) {
   for (long long k = (n4 << 2) + (long long)blockIdx.x * 256 + threadIdx.x; k < n; k += stride) p[k] = 0.f;
 }
 
-// Partial states of `splits` key ranges (O [splits][rows][d], then m in log2 units and l, each
+// Partial states of `splits` key ranges (O [splits][rows][d], then m, in log2 units or natural, and l, each
 // [splits][rows]) -> one, merged with the stored state unless that is the initial one; with O_out also
 // finalized (Alg. 1 merge step and last two steps).  HBM bound: every partial is read once.  d a
 // multiple of 8; d / 4 threads per row, whole rows per workgroup, so that a barrier separates the
@@ -165,7 +165,8 @@ zero_fill_kernel(float* __restrict__ p, long long n) {
 __global__ void __launch_bounds__(256)
 merge_splits_kernel(const float* __restrict__ part, int splits, float* __restrict__ O_acc, float* __restrict__ m,
                     float* __restrict__ l, bf16* __restrict__ O_out, float* __restrict__ lse, int fresh,
-                    long long n_rows, int d, QRows qr) {
+                    int natural, long long n_rows, int d, QRows qr) {
+  const float to_log2 = natural ? kLog2e : 1.f, to_units = natural ? 1.f : kLog2e, to_stored = natural ? 1.f : kLn2;
   const int per_row = d >> 2;
   const float* const pm = part + (size_t)splits * n_rows * d;
   const float* const pl = pm + (size_t)splits * n_rows;
@@ -179,20 +180,20 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
   f32x4* const state = reinterpret_cast<f32x4*>(O_acc + row * d + c * 4);
   if (mg != BURST_NEG_INF) {
-    const float m_old2 = m_old * kLog2e, mn = fmaxf(mg, m_old2);
-    const float fa = fast_exp2(m_old2 - mn);
+    const float m_old_u = m_old * to_units, mn = fmaxf(mg, m_old_u);
+    const float fa = fast_exp2((m_old_u - mn) * to_log2);
     if (fa != 0.f) {
       const f32x4 old = *state;
       for (int t = 0; t < 4; t++) o[t] = fa * old[t];
       lsum = fa * l_old;
     }
     for (int i = 0; i < splits; i++) {
-      const float f = fast_exp2(pm[i * n_rows + row] - mn);
+      const float f = fast_exp2((pm[i * n_rows + row] - mn) * to_log2);
       const f32x4 v = *reinterpret_cast<const f32x4*>(part + ((size_t)i * n_rows + row) * d + c * 4);
       for (int t = 0; t < 4; t++) o[t] += f * v[t];
       lsum += f * pl[i * n_rows + row];
     }
-    m_st = mn * kLn2;
+    m_st = mn * to_stored;
   } else if (m_old != BURST_NEG_INF) {             // no range saw a key: the state stays
     o = *state;
     lsum = l_old;
@@ -300,7 +301,7 @@ int launch_merge_splits(const KParams& p, const FwdIo& io, hipStream_t s) {
   if (rows == 0) return BURST_OK;
   if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
   BURST_LAUNCH(merge_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.O_acc, io.m, io.l,
-               (bf16*)io.O_out, io.lse, io.fresh, rows, p.d, p.q_rows());
+               (bf16*)io.O_out, io.lse, io.fresh, p.d != 64 && p.d != 128, rows, p.d, p.q_rows());   // (natural: the padded builds)
   return launch_status();
 }
 

@@ -37,7 +37,7 @@ struct GenArgs {
   int half;
   int Nq, d, BH;
   int causal, fresh;                              // fresh: the state before the launch is the initial one
-  float scale, c;                                 // c = scale * log2(e)
+  float scale;
   long long q_off;
   long long window;
   int bsize;                                      // edge of block flags, a multiple of 64
@@ -172,7 +172,7 @@ fwd_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) o[db][r] = 0.f;
-  float m2 = BURST_NEG_INF, lsum = 0.f;           // reference max (log2 units), sum over this lane's keys
+  float m_run = BURST_NEG_INF, lsum = 0.f;        // reference max, sum over this lane's keys
 
   KeyWalk<T, W> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
@@ -220,20 +220,19 @@ fwd_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) {
         const int cpart = 8 * (r >> 2) + (r & 3);
-        s[r] = (cpart <= lim && cpart >= lim_lo) ? s[r] : BURST_NEG_INF;
+        s[r] = (cpart <= lim && cpart >= lim_lo) ? product(s[r], a.scale) : BURST_NEG_INF;
         v = fmaxf(v, s[r]);
       }
-      const float mx = max_both_halves(v) * a.c;
-      const float m_new = fmaxf(m2, mx), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
-      const float alpha = fast_exp2(m2 - ref);
-      m2 = m_new;
+      const float m_new = fmaxf(m_run, max_both_halves(v)), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
+      const float alpha = fast_exp2((m_run - ref) * kLog2e);
+      m_run = m_new;
       lsum *= alpha;
 #pragma unroll
       for (int db = 0; db < NB; db++)
 #pragma unroll
         for (int r = 0; r < 16; r++) o[db][r] *= alpha;
 #pragma unroll
-      for (int r = 0; r < 16; r++) { s[r] = fast_exp2(__builtin_fmaf(s[r], a.c, -ref)); lsum += s[r]; }
+      for (int r = 0; r < 16; r++) { s[r] = fast_exp2((s[r] - ref) * kLog2e); lsum += s[r]; }
       // O^T += V^T P^T
 #pragma unroll
       for (int r = 0; r < 8; r++)
@@ -250,15 +249,15 @@ fwd_generic_kernel(GenArgs a) {
   // the wavefronts' partial results meet in LDS
   float* const ml = gsh + W * NB * 1024;
   const float l_half = sum_both_halves(lsum);
-  if (h == 0) { ml[w * 64 + lr] = m2; ml[w * 64 + 32 + lr] = l_half; }
+  if (h == 0) { ml[w * 64 + lr] = m_run; ml[w * 64 + 32 + lr] = l_half; }
   __syncthreads();
   float mg = BURST_NEG_INF, lg = 0.f;
 #pragma unroll
   for (int i = 0; i < W; i++) mg = fmaxf(mg, ml[i * 64 + lr]);
   const float mref = mg == BURST_NEG_INF ? 0.f : mg;
 #pragma unroll
-  for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2(ml[i * 64 + lr] - mref);
-  const float own = fast_exp2(m2 - mref);
+  for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2((ml[i * 64 + lr] - mref) * kLog2e);
+  const float own = fast_exp2((m_run - mref) * kLog2e);
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
@@ -267,15 +266,14 @@ fwd_generic_kernel(GenArgs a) {
   const bool saw = mg != BURST_NEG_INF;
   if (row >= a.Nq || (!saw && !a.fresh && a.O_out == nullptr)) return;   // rows that saw no key keep their state
   const size_t sr = (size_t)head * a.Nq + row;
-  const float m_old = a.fresh ? BURST_NEG_INF : a.m[sr] * kLog2e, l_old = a.fresh ? 0.f : a.l[sr];
+  const float m_old = a.fresh ? BURST_NEG_INF : a.m[sr], l_old = a.fresh ? 0.f : a.l[sr];
   const float m_new = fmaxf(m_old, mg), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
-  const float fa = fast_exp2(m_old - ref), fb = fast_exp2(mg - ref);
+  const float fa = fast_exp2((m_old - ref) * kLog2e), fb = fast_exp2((mg - ref) * kLog2e);
   const float l_new = (fa == 0.f ? 0.f : fa * l_old) + fb * lg;
-  const float m_st = saw || a.fresh ? m_new * kLn2 : a.m[sr];
   __syncthreads();                                 // every wavefront has read the row's old m and l
   if (w == 0 && h == 0) {
-    if (a.O_acc != nullptr && (saw || a.fresh)) { a.m[sr] = m_st; a.l[sr] = l_new; }
-    if (a.O_out != nullptr) a.lse_out[sr] = l_new > 0.f ? m_st + __logf(l_new) : BURST_NEG_INF;
+    if (a.O_acc != nullptr && (saw || a.fresh)) { a.m[sr] = m_new; a.l[sr] = l_new; }
+    if (a.O_out != nullptr) a.lse_out[sr] = l_new > 0.f ? m_new + __logf(l_new) : BURST_NEG_INF;
   }
   const float inv = l_new > 0.f ? 1.0f / l_new : 0.f;
   float* const orow = a.O_acc + sr * a.d;
@@ -300,7 +298,7 @@ fwd_generic_kernel(GenArgs a) {
 
 // ---------------------------------------------------------------------------- backward, dQ
 template <typename T, int D, bool VEC, int W>
-__global__ void __launch_bounds__(64 * W, W / 4)
+__global__ void __launch_bounds__(64 * W, VEC && D <= 64 ? 2 : 1)   // (256 registers do at d = 64: two wavefronts per SIMD)
 bwd_dq_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
   constexpr int NB = R::NB, NK = R::NK;
@@ -330,7 +328,7 @@ bwd_dq_generic_kernel(GenArgs a) {
       gf[ks] = R::fixed((const T*)a.dO + qrow, 8 * ks + 4 * h, a.d, ok);
     }
     const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
-    const float nlse2 = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv * kLog2e;   // -inf: P = 0
+    const float nlse = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv;   // -inf: P = 0
     const float nD = ok ? -a.D[sr] : 0.f;
     auto load_k = [&]() __attribute__((always_inline)) {
       const T* kr = at.K + (size_t)min(at.t * 32 + lr, at.Nc - 1) * at.ks_r;
@@ -377,7 +375,7 @@ bwd_dq_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) {
         const int cpart = 8 * (r >> 2) + (r & 3);
-        const float p = fast_exp2(__builtin_fmaf(s[r], a.c, nlse2));
+        const float p = fast_exp2(above(s[r], a.scale, -nlse) * kLog2e);
         dp[r] = (cpart <= lim && cpart >= lim_lo) ? p * dp[r] : 0.f;   // dS^T
       }
       // dQ^T += K^T dS^T
@@ -535,7 +533,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
       for (int r = 0; r < 16; r++) {
         const int cpart = 8 * (r >> 2) + (r & 3);
         const bool vis = cpart <= lim && cpart >= lim_lo && lrow[r] != BURST_NEG_INF;
-        const float p = fast_exp2(__builtin_fmaf(s[r], a.c, -lrow[r] * kLog2e));
+        const float p = fast_exp2(above(s[r], a.scale, lrow[r]) * kLog2e);
         dp[r] = vis ? p * (dp[r] - drow[r]) : 0.f;
         s[r] = vis ? p : 0.f;
       }
@@ -588,7 +586,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
 // ---------------------------------------------------------------------------- launchers
 static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
   a.Nq = p.Nq; a.d = p.d; a.BH = p.B * p.H;
-  a.causal = p.causal; a.scale = p.scale; a.c = p.scale * kLog2e; a.q_off = p.q_off; a.window = p.window;
+  a.causal = p.causal; a.scale = p.scale; a.q_off = p.q_off; a.window = p.window;
   a.bsize = p.bsize; a.group = p.group; a.lay = p.lay;
   a.n = n;
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];

@@ -1,6 +1,6 @@
 // Plainly written MFMA kernels for the forward chunk step (paper Alg. 1 loop body, tiled as in
 // Sec. 2.4) and the two halves of the backward block pair (Alg. 2 loop body), bf16, with the head
-// dimension a compile-time constant.  This header is the source of two kernel families; each is
+// dimension a compile-time constant.  This header is the source of six kernel families; each is
 // built by a small translation unit that defines BURST_SMALL_D (head dimension), BURST_SMALL_NS
 // (namespace) and, optionally, BURST_SMALL_DKV_WAVES before including it:
 //   burst_d64_mfma.hip    d = 64, namespace burst::d64, all three kernels
@@ -48,7 +48,7 @@ constexpr int S_KS = S_D / 16;                    // k-steps of a contraction ov
 constexpr int S_DB = S_D / 32;                    // 32-wide blocks of d
 constexpr int S_RPL = 1024 / S_ROWB;              // tile rows per wave-wide DMA load
 constexpr int S_GPR = S_ROWB / 16;                // granules per row
-constexpr float S_LAZY = 8.0f;                    // log2 of the largest P allowed before the max is raised
+constexpr float S_LAZY = S_PAD ? 8.0f * kLn2 : 8.0f;   // largest P allowed before the max is raised: 2^8
 
 struct FwdArgsLite {
   const bf16* Q;
@@ -57,7 +57,7 @@ struct FwdArgsLite {
   float* part;                                   // partial states (splits > 1)
   int Nq, H, group;                              // H counts batch x heads
   int causal, fresh;
-  float c;                                       // scale * log2(e)
+  float c, scale;                                // c = scale * log2(e)
   long long q_off, window;
   int bsize;
   int blocks_per_head, splits, mirror;           // mirror: see mirrored()
@@ -125,6 +125,17 @@ __device__ __forceinline__ bf16x8 s_load8(const bf16* p, bool ok) {
 // on the generic kernels); a walk's dV differs from 64 bits by 1.6e-3 with one term, 5.7e-7 with three (5.8e-7
 // on the generic kernels).
 constexpr int S_TERMS = S_PAD ? 3 : 1;
+// Units of scores, maxima and lse: log2 (one fma per exponent), or natural in the padded builds, where s x scale is rounded
+// before the maximum or lse is taken from it, as in the forward that made them: a row's largest key has exponent 0 exactly,
+// however large its score.  (In log2 units the product with log2 e rounds once more: at scores of 2^20 a
+// probability of 1 is up to 4 % off, and from 2^31 on it comes out as 0 or infinity.)
+__device__ __forceinline__ float s_units(float s, float scale, float c) { return S_PAD ? product(s, scale) : s * c; }
+__device__ __forceinline__ float s_exp(float s, float scale, float c, float nref) {   // nref: minus the reference in these units
+  return S_PAD ? fast_exp2(above(s, scale, -nref) * kLog2e) : fast_exp2(__builtin_fmaf(s, c, nref));
+}
+__device__ __forceinline__ float s_raise(float& m_st, float& cm, float mx, float l) {
+  return S_PAD ? raise_reference_natural(m_st, cm, mx, l) : raise_reference(m_st, cm, mx, l);
+}
 __device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, float y) {
 #pragma unroll
   for (int i = 0; i < S_TERMS; i++) {
@@ -329,7 +340,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   bf16x2 ones;
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
 
-  // The scores of a tile, masked, and the row's maximum of them (log2 units).
+  // The scores of a tile, masked, and the row's maximum of them (see s_units).
   auto scores = [&](const char* kl, int kt, int Nc, long long k_off, f32x16 (&s)[2]) __attribute__((always_inline)) {
     // S^T = K Q^T: register r of key block kb = key kt*64 + kb*32 + 8*(r/4) + 4h + r%4
 #pragma unroll
@@ -365,7 +376,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     for (int kb = 0; kb < 2; kb++)
 #pragma unroll
       for (int r = 0; r < 16; r++) v = fmaxf(v, s[kb][r]);
-    return max_both_halves(v) * a.c;
+    return s_units(max_both_halves(v), a.scale, a.c);
   };
   bool begun = false;
   // A run that begins inside a chunk takes the chunk's references from its first tile like every other run (one more
@@ -378,7 +389,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0), lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
       f32x16 s[2];
-      raise_reference(m_st, cm, scores(smem + SF_TILE, lo, f_Nc, f_koff, s), 0.f);
+      s_raise(m_st, cm, scores(smem + SF_TILE, lo, f_Nc, f_koff, s), 0.f);
     }
   for (int buf = 0; have; buf ^= 1) {
     const int kt = f_tile, Nc = f_Nc;
@@ -396,21 +407,21 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     f32x16 s[2];
     const float mx = scores(kl, kt, Nc, k_off, s);
     if (__builtin_amdgcn_ballot_w64(mx > cm + S_LAZY) != 0) {   // a chunk's first reference, or raised (rare)
-      const float alpha = raise_reference(m_st, cm, mx, sum_both_halves(lsum));
+      const float alpha = s_raise(m_st, cm, mx, sum_both_halves(lsum));
       lsum *= alpha;
 #pragma unroll
       for (int db = 0; db < S_DB; db++)
 #pragma unroll
         for (int r = 0; r < 16; r++) o[db][r] *= alpha;
     }
-    const float nref = (m_st == BURST_NEG_INF) ? 0.f : -(m_st * kLog2e);
+    const float nref = (m_st == BURST_NEG_INF) ? 0.f : S_PAD ? -m_st : -(m_st * kLog2e);
     bf16x8 pf[4][S_TERMS];                         // P^T fragments per 16-key group
 #pragma unroll
     for (int kg = 0; kg < 4; kg++)
 #pragma unroll
       for (int t = 0; t < 8; t += 2) {
         const int kb = kg >> 1, r = 8 * (kg & 1) + t;
-        const float p0 = fast_exp2(__builtin_fmaf(s[kb][r], a.c, nref)), p1 = fast_exp2(__builtin_fmaf(s[kb][r + 1], a.c, nref));
+        const float p0 = s_exp(s[kb][r], a.scale, a.c, nref), p1 = s_exp(s[kb][r + 1], a.scale, a.c, nref);
         s_terms(pf[kg], t, p0, p1);
         if constexpr (S_TERMS == 1) {                // sums what the MFMA multiplies
           bf16x2 pk;
@@ -435,7 +446,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   const float l_all = sum_both_halves(lsum);
   if (row >= a.Nq) return;
   // lane (lr, h) holds row lr, columns db*32 + 8*q4 + 4h + (0..3)
-  if (a.splits > 1) {                              // a partial state: [split][rows][d] O, then m (log2 units) and l
+  if (a.splits > 1) {                              // a partial state: [split][rows][d] O, then m (units: s_units) and l
     const size_t rows = (size_t)a.H * a.Nq, pr = (size_t)split * rows + srow;
     float* const prow = a.part + pr * d;
 #pragma unroll
@@ -450,7 +461,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       }
     if (h == 0) {
       float* const ml = a.part + (size_t)a.splits * rows * d;
-      ml[pr] = m_st * kLog2e;
+      ml[pr] = S_PAD ? m_st : m_st * kLog2e;
       ml[(size_t)a.splits * rows + pr] = l_all;
     }
     return;
@@ -512,6 +523,20 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
 
   // The chunks' visible tiles (or list entries) form one sequence, as in the forward kernel.
   constexpr int NL = SQ_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
+  auto tiles_of = [&](const Chunk& C, int& lo, int& hi) __attribute__((always_inline)) {   // that some row of the workgroup sees
+    lo = 0; hi = (C.Nc + SQ_BC - 1) / SQ_BC;
+    if (a.window > 0) {
+      const long long first = a.q_off + (long long)qb * SQ_BR - a.window + 1 - C.k_off;
+      if (first >= C.Nc) lo = hi;
+      else if (first > 0) lo = (int)(first / SQ_BC);
+    }
+    if (a.causal) {
+      const long long last = a.q_off + min(qb * SQ_BR + SQ_BR, a.Nq) - 1 - C.k_off;
+      if (last < 0) hi = lo;
+      else if (last / SQ_BC + 1 < hi) hi = (int)(last / SQ_BC) + 1;
+    }
+    hi = max(hi, lo);
+  };
   int c = -1, ft = split, lo = 0, hi = 0;         // chunk, position in it, first and end position
   int f_tile = 0, f_bits = 0xf, f_Nc = 0;         // the tile that was fetched last
   long long f_koff = 0;
@@ -525,17 +550,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
       if (++c >= a.n) return false;
       const Chunk& C = a.ch[c];
       f_Nc = C.Nc; f_koff = C.k_off;
-      lo = 0; hi = (f_Nc + SQ_BC - 1) / SQ_BC;
-      if (a.window > 0) {
-        const long long first = a.q_off + (long long)qb * SQ_BR - a.window + 1 - f_koff;
-        if (first >= f_Nc) lo = hi;
-        else if (first > 0) lo = (int)(first / SQ_BC);
-      }
-      if (a.causal) {
-        const long long last = a.q_off + min(qb * SQ_BR + SQ_BR, a.Nq) - 1 - f_koff;
-        if (last < 0) hi = lo;
-        else if (last / SQ_BC + 1 < hi) hi = (int)(last / SQ_BC) + 1;
-      }
+      tiles_of(C, lo, hi);
       if (hi > lo) {
         const unsigned kpitch = (unsigned)C.ks_r * 2u;           // bytes between key rows
         const size_t base = C.kv_base(kvhead, a.lay.kv_heads);
@@ -558,7 +573,6 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
           lo = 0;
         }
       }
-      hi = max(hi, lo);
       ft = lo + past;
     }
     f_tile = ft;
@@ -612,7 +626,10 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
     const float lv = ok ? a.lse[srow] : BURST_NEG_INF;
     // exponent offset: P scaled by `scale`; -inf: P = 0
-    const float nlse2 = (lv == BURST_NEG_INF) ? BURST_NEG_INF : __builtin_fmaf(-lv, kLog2e, a.log2_scale);
+    const float nlse2 = (lv == BURST_NEG_INF) ? BURST_NEG_INF : S_PAD ? -lv : __builtin_fmaf(-lv, kLog2e, a.log2_scale);
+    auto scaled_p = [&](float x) __attribute__((always_inline)) {
+      return S_PAD ? fast_exp2(__builtin_fmaf(above(x, a.scale, -nlse2), kLog2e, a.log2_scale)) : fast_exp2(__builtin_fmaf(x, a.c, nlse2));
+    };
     const float Dv = ok ? a.D[srow] : 0.f;
     int kaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
@@ -660,7 +677,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
       bf16x8 dsf[2][S_TERMS];                      // dS^T fragments per 16-key group
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
-        const float p0 = fast_exp2(__builtin_fmaf(s[r], a.c, nlse2)), p1 = fast_exp2(__builtin_fmaf(s[r + 1], a.c, nlse2));
+        const float p0 = scaled_p(s[r]), p1 = scaled_p(s[r + 1]);
         s_terms(dsf[r >> 3], r & 7, p0 * (dp[r] - Dv), p1 * (dp[r + 1] - Dv));
       }
       // dQ^T += K^T dS^T
@@ -715,7 +732,7 @@ constexpr int SK_WAVES = BURST_SMALL_DKV_WAVES;
 constexpr int SK_BC = 32 * SK_WAVES;              // keys per workgroup
 constexpr int SK_BR = 32;                         // query rows per tile
 constexpr int SK_TILE = SK_BR * S_ROWB;
-constexpr int SK_STAT = 4 * SK_TILE;              // per buffer: 32 x (-lse log2 e), 32 x D
+constexpr int SK_STAT = 4 * SK_TILE;              // per buffer: 32 x (-lse, see s_units), 32 x D
 
 template <bool SPARSE>
 __global__ void __launch_bounds__(64 * SK_WAVES, SK_WAVES == 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
@@ -829,7 +846,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       }
     };
     auto stat_commit = [&](int buf) __attribute__((always_inline)) {
-      if (tid < 32) stat[buf * 64 + tid] = (stat_x == BURST_NEG_INF) ? BURST_NEG_INF : -stat_x * kLog2e;   // -inf: P = 0
+      if (tid < 32) stat[buf * 64 + tid] = (stat_x == BURST_NEG_INF) ? BURST_NEG_INF : S_PAD ? -stat_x : -stat_x * kLog2e;   // -inf: P = 0
       else if (tid < 64) stat[buf * 64 + tid] = stat_x;
     };
     const long long wave_first_k = k_off + key0, wave_last_k = wave_first_k + 31;
@@ -907,7 +924,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 #pragma unroll
           for (int j = 0; j < 4; j += 2) {
             const int r = 4 * q4 + j;
-            const float p0 = fast_exp2(__builtin_fmaf(s[r], a.c, nl[j])), p1 = fast_exp2(__builtin_fmaf(s[r + 1], a.c, nl[j + 1]));
+            const float p0 = s_exp(s[r], a.scale, a.c, nl[j]), p1 = s_exp(s[r + 1], a.scale, a.c, nl[j + 1]);
             s_terms(pf[r >> 3], r & 7, p0, p1);
             s_terms(dsf[r >> 3], r & 7, p0 * (dp[r] - dr[j]), p1 * (dp[r + 1] - dr[j + 1]));
           }
@@ -969,7 +986,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
   a.fresh = io.fresh || a.splits > 1;
   a.Nq = p.Nq; a.H = p.B * p.H; a.group = p.group;
-  a.causal = p.causal; a.c = p.scale * kLog2e;
+  a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
   a.blocks_per_head = (p.Nq + SF_BR - 1) / SF_BR;
