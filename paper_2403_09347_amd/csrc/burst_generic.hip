@@ -24,7 +24,7 @@
 //    it stands: its two keys (rows), of h = 0 and h = 1, are the two k of that MFMA.
 //  - The other operand of the second product is a row of V, K, dO or Q spread over lr: block db of
 //    lane lr is column col_of(db, lr).
-#include "burst_common.h"
+#include "burst_rows.h"
 
 namespace burst {
 
@@ -154,6 +154,19 @@ struct KeyWalk {
   }
 };
 
+// Barrier of the workgroup; whether `odd` holds in a lane of any of its wavefronts (flags: W words of LDS).
+template <int W>
+__device__ __forceinline__ bool any_wave_odd(float* flags, int w, int lane, bool odd) {
+  int* const f = reinterpret_cast<int*>(flags);
+  const int mine = __builtin_amdgcn_ballot_w64(odd) != 0;
+  if (lane == 0) f[w] = mine;
+  __syncthreads();
+  int any = 0;
+#pragma unroll
+  for (int i = 0; i < W; i++) any |= f[i];
+  return __builtin_amdgcn_readfirstlane(any) != 0;
+}
+
 // ---------------------------------------------------------------------------- forward
 template <typename T, int D, bool VEC, int W>
 __global__ void __launch_bounds__(64 * W, W / 4)
@@ -248,7 +261,13 @@ fwd_generic_kernel(GenArgs a) {
   }
   // the wavefronts' partial results meet in LDS
   float* const ml = gsh + W * NB * 1024;
-  const float l_half = sum_both_halves(lsum);
+  unsigned most = larger_of(0, lsum);              // a wavefront with an infinity or NaN says so by its row sums
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) most = larger_of(most, o[db][r]);
+  const bool odd = __builtin_amdgcn_ballot_w64(row < a.Nq && most >= kInfBits) != 0;
+  const float l_half = odd ? -BURST_NEG_INF : sum_both_halves(lsum);
   if (h == 0) { ml[w * 64 + lr] = m_run; ml[w * 64 + 32 + lr] = l_half; }
   __syncthreads();
   float mg = BURST_NEG_INF, lg = 0.f;
@@ -257,6 +276,17 @@ fwd_generic_kernel(GenArgs a) {
   const float mref = mg == BURST_NEG_INF ? 0.f : mg;
 #pragma unroll
   for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2((ml[i * 64 + lr] - mref) * kLog2e);
+  if (__builtin_amdgcn_ballot_w64(row < a.Nq && larger_of(0, lg) >= kInfBits) != 0) {   // (alike in all wavefronts) the block's rows one by one, see burst_rows.h
+#pragma unroll 1
+    for (int one = row0 + w, end = min(row0 + 32, a.Nq); one < end; one += W) {
+      const size_t sr = (size_t)head * a.Nq + one;
+      RowState st = row_state(a.fresh, a.O_acc, a.m, a.l, sr, a.d, lane);
+      row_forward<T>(st, a, head, one, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 0x7fffffff);
+      row_store<T>(st, a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : (T*)a.O_out + a.lay.q_base(head) + (size_t)one * a.lay.qs_r,
+                   a.lse_out, sr, a.d, lane);
+    }
+    return;
+  }
   const float own = fast_exp2((m_run - mref) * kLog2e);
 #pragma unroll
   for (int db = 0; db < NB; db++)
@@ -302,7 +332,7 @@ __global__ void __launch_bounds__(64 * W, VEC && D <= 64 ? 2 : 1)   // (256 regi
 bwd_dq_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
   constexpr int NB = R::NB, NK = R::NK;
-  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dQ^T
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dQ^T, then [W] flags
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk;
@@ -396,7 +426,20 @@ bwd_dq_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = dq[db][r];
-  __syncthreads();
+  unsigned most = 0;
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits)) {   // the block's rows one by one, see burst_rows.h
+#pragma unroll 1
+    for (int one = row0 + w, end = min(row0 + 32, a.Nq); one < end; one += W) {
+      float g[2];
+      row_dq<T, 64>(g, a, head, one, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 1);
+      row_gradient<T>(a.dQ, ((size_t)head * a.Nq + one) * a.d, g, a.scale, a.half, a.acc_dq, lane, a.d);
+    }
+    return;
+  }
   if (!ok) return;
   float* const out = (float*)a.dQ + sr * a.d;
   T* const out16 = (T*)a.dQ + sr * a.d;
@@ -423,7 +466,7 @@ __global__ void __launch_bounds__(64 * W, W / 4)
 bwd_dkv_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
   constexpr int NB = R::NB, NK = R::NK;
-  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dK, then dV
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dK, then dV; [W] flags
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int ci = 0;                                      // the workgroups of all chunks, chunk after chunk
@@ -552,6 +595,22 @@ bwd_dkv_generic_kernel(GenArgs a) {
       n = nn;
     }
   }
+  unsigned most = 0;
+#pragma unroll
+  for (int db = 0; db < NB; db++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits)) {   // the block's keys one by one, see burst_rows.h
+#pragma unroll 1
+    for (int one = key0 + w, end = min(key0 + 32, Nc); one < end; one += W) {
+      const size_t at = ((size_t)kvhead * Nc + one) * a.d;
+      float gk[2], gv[2];
+      key_dkv<T>(gk, gv, a, C, kvhead, one, lane);
+      row_gradient<T>(C.dK, at, gk, a.scale, a.half, a.acc_dkv, lane, a.d);
+      row_gradient<T>(C.dV, at, gv, 1.f, a.half, a.acc_dkv, lane, a.d);
+    }
+    return;
+  }
   // lane = column, registers = keys; the two sums use the same LDS one after the other
 #pragma unroll
   for (int which = 0; which < 2; which++) {
@@ -595,7 +654,7 @@ static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
 enum { GEN_FWD, GEN_DQ, GEN_DKV };
 template <int KIND, typename T, int D, bool VEC, int W>
 static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
-  const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : 0)) * 4;
+  const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : W)) * 4;
   void (*kernel)(GenArgs);
   if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W>;
   else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W>;

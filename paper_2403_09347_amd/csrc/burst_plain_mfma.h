@@ -28,6 +28,7 @@
 #endif
 #include <cmath>
 #include "burst_bwd_common.h"
+#include "burst_rows.h"
 
 namespace burst {
 namespace BURST_SMALL_NS {
@@ -444,6 +445,43 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
   const float l_all = sum_both_halves(lsum);
+  if constexpr (S_PAD) {                           // rows with an infinity or NaN, one by one (see burst_rows.h)
+    unsigned most = larger_of(0, l_all);
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) most = larger_of(most, o[db][r]);
+    const unsigned long long bal = __builtin_amdgcn_ballot_w64(row < a.Nq && most >= kInfBits);
+    const unsigned redo = (unsigned)bal | (unsigned)(bal >> 32);
+    if (redo != 0) {
+      int first = 0, last = 0x7fffffff;
+      if (a.splits > 1) {
+        int all = 0;
+        for (int i = 0; i < a.n; i++) {
+          tiles_of(a.ch[i], lo, hi);
+          all += hi - lo;
+        }
+        first = all * split / a.splits;
+        last = all * (split + 1) / a.splits;
+      }
+      for (unsigned rows = redo; rows != 0; rows &= rows - 1) {
+        const int one = qb * SF_BR + wu * 32 + __builtin_ctz(rows);
+        const size_t sr = (size_t)head * a.Nq + one;
+        RowState st = row_state(a.fresh, a.O_acc, a.m, a.l, sr, d, lane);
+        row_forward<bf16>(st, a, head, one, lane, tiles_of, first, last);
+        if (a.splits > 1) {
+          const size_t n_rows = (size_t)a.H * a.Nq, pr = (size_t)split * n_rows + sr;
+          float* const ml = a.part + (size_t)a.splits * n_rows * d;
+          row_gradient<bf16>(a.part, pr * d, st.o, 1.f, 0, 0, lane, d);
+          if (lane == 0) { ml[pr] = st.m; ml[(size_t)a.splits * n_rows + pr] = st.l; }
+        } else {
+          row_store<bf16>(st, a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : a.O_out + a.lay.q_base(head) + (size_t)one * a.lay.qs_r,
+                          a.lse, sr, d, lane);
+        }
+      }
+      if ((redo >> lr) & 1) return;
+    }
+  }
   if (row >= a.Nq) return;
   // lane (lr, h) holds row lr, columns db*32 + 8*q4 + 4h + (0..3)
   if (a.splits > 1) {                              // a partial state: [split][rows][d] O, then m (units: s_units) and l
@@ -692,6 +730,24 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
+  if constexpr (S_PAD) {                           // rows with an infinity or NaN, one by one (see burst_rows.h)
+    unsigned most = 0;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
+    const unsigned long long bal = __builtin_amdgcn_ballot_w64(ok && most >= kInfBits);
+    const unsigned redo = (unsigned)bal | (unsigned)(bal >> 32);
+    for (unsigned rows = redo; rows != 0; rows &= rows - 1) {
+      const int one = qb * SQ_BR + wu * 32 + __builtin_ctz(rows);
+      const size_t at = ((size_t)head * a.Nq + one) * d;
+      float g[2];
+      row_dq<bf16, SQ_BC>(g, a, head, one, lane, tiles_of, split, a.splits);
+      if (a.splits > 1) row_gradient<bf16>(a.part, (size_t)split * a.H * a.Nq * d + at, g, a.scale, 0, 0, lane, d);
+      else row_gradient<bf16>(a.dQ, at, g, a.scale, a.half, a.acc_dq, lane, d);
+    }
+    if ((redo >> lr) & 1) return;
+  }
   if (ok && a.half && a.splits == 1) {
     bf16* const orow = (bf16*)a.dQ + srow * d;
 #pragma unroll
@@ -887,14 +943,16 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
         }
         const long long tile_first_q = a.q_off + (long long)t * SK_BR;
         const bool need_mask = (a.causal && wave_last_k > tile_first_q) ||
-                               (a.window > 0 && tile_first_q + SK_BR - 1 >= wave_first_k + a.window);
+                               (a.window > 0 && tile_first_q + SK_BR - 1 >= wave_first_k + a.window) ||
+                               (S_PAD && (t + 1) * SK_BR > a.Nq);   // (rows of zeros, whose product with an infinite key is NaN)
         if (need_mask) {
           // visible iff key position <= row position (constant part >= lim) and row position <
           // key position + window (constant part <= lim2)
           const long long dd = kpos - (tile_first_q + 4 * h);
           const int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : -1;
           const long long d2 = dd + a.window - 1;
-          const int lim2 = a.window > 0 ? (int)(d2 < -1 ? -1 : (d2 > 64 ? 64 : d2)) : 64;
+          int lim2 = a.window > 0 ? (int)(d2 < -1 ? -1 : (d2 > 64 ? 64 : d2)) : 64;
+          if (S_PAD) lim2 = min(lim2, a.Nq - 1 - (t * SK_BR + 4 * h));
 #pragma unroll
           for (int r = 0; r < 16; r++) {
             const int cpart = 8 * (r >> 2) + (r & 3);
@@ -949,6 +1007,24 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       if (n + 1 < nwalk) stat_commit((n + 1) & 1);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
+  }
+  if constexpr (S_PAD) {                           // keys with an infinity or NaN, and their neighbours (see burst_rows.h)
+    unsigned most = 0;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
+    if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
+#pragma unroll 1
+      for (int one = key_wg + __builtin_amdgcn_readfirstlane(w) * 32, end = min(one + 32, Nc); one < end; one++) {
+        const size_t at = ((size_t)kvhead * Nc + one) * d;
+        float gk[2], gv[2];
+        key_dkv<bf16>(gk, gv, a, C, kvhead, one, lane);
+        row_gradient<bf16>(C.dK, at, gk, a.scale, a.half, a.acc_dkv, lane, d);
+        row_gradient<bf16>(C.dV, at, gv, 1.f, a.half, a.acc_dkv, lane, d);
+      }
+      return;
+    }
   }
   const size_t first = (size_t)kvhead * Nc * d * (a.half ? 2 : 4);
   store_dkv<S_DB, S_PAD>(dk, dv, (char*)C.dK + first, (char*)C.dV + first, Nc, d, key0, lr, h, a.scale, a.half, a.acc_dkv);
