@@ -213,11 +213,19 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
   }
 }
 
-// dQ = (acc ? dQ : 0) + the sum of `splits` partial dQ [splits][n], in that order; half: dQ is bf16.
+// dQ = (acc ? dQ : 0) + the sum of `splits` partial dQ [splits][n], in that order; half: dQ is bf16.  More than one part
+// only with n a multiple of 4; else (odd head dimensions) one thread takes the last elements.
 __global__ void __launch_bounds__(256)
-sum_splits_kernel(const float* __restrict__ part, int splits, void* __restrict__ dQ, int acc, int half, long long n4) {
-  const long long k = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (k >= n4) return;
+sum_splits_kernel(const float* __restrict__ part, int splits, void* __restrict__ dQ, int acc, int half, long long n) {
+  const long long k = (long long)blockIdx.x * 256 + threadIdx.x, n4 = n >> 2;
+  if (k > n4) return;
+  if (k == n4) {
+    for (long long e = n4 << 2; e < n; e++) {
+      if (half) reinterpret_cast<bf16*>(dQ)[e] = (bf16)part[e];
+      else reinterpret_cast<float*>(dQ)[e] = (acc ? reinterpret_cast<const float*>(dQ)[e] : 0.f) + part[e];
+    }
+    return;
+  }
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if (acc) v = reinterpret_cast<const f32x4*>(dQ)[k];
   for (int i = 0; i < splits; i++) {
@@ -306,11 +314,11 @@ int launch_merge_splits(const KParams& p, const FwdIo& io, hipStream_t s) {
 }
 
 int launch_sum_splits(const KParams& p, const BwdIo& io, hipStream_t s) {
-  const long long n4 = (long long)p.B * p.H * p.Nq * p.d / 4, blocks = (n4 + 255) / 256;
-  if (n4 == 0) return BURST_OK;
+  const long long n = (long long)p.B * p.H * p.Nq * p.d, blocks = (n / 4 + 256) / 256;
+  if (n == 0) return BURST_OK;
   if (blocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
   BURST_LAUNCH(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, s, io.part, io.splits, io.dQ, io.acc_dq,
-               io.half, n4);
+               io.half, n);
   return launch_status();
 }
 

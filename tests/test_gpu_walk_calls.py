@@ -112,22 +112,27 @@ def test_chunks_of_different_pitch_in_one_walk(family):
 @pytest.mark.parametrize("spec,family", [
     (dict(d=64, Nq=70, chunk_rows=[20] * 37, causal=True, q_off=700), 0),
     (dict(d=20, Nq=70, chunk_rows=[20] * 37, causal=True, q_off=700), 0),
+    (dict(d=127, Nq=37, chunk_rows=[20] * 37, causal=True, q_off=700), 0),      # dQ: a multiple of 4 elements and two more
+    (dict(H=1, d=3, Nq=1, chunk_rows=[20] * 37), 0),                            # three elements
+    (dict(H=1, d=1, Nq=69, chunk_rows=[20] * 37), 0),                           # one more
     (dict(d=128, Nq=300, chunk_rows=[256, 70], block=256, pattern="random", density=0.5), 1),
-], ids=["d64-37-chunks", "d20-37-chunks", "d128-flags"])
+], ids=["d64-37-chunks", "d20-37-chunks", "d127-37-chunks", "d3-one-row", "d1-37-chunks", "d128-flags"])
 def test_differentiable_call_of_several_launches(spec, family):
     """The state between the launches lies in the workspace, as dQ does: the same bits as a walk that keeps it."""
     from paper_2403_09347_amd.autograd import burst_attention
     B.burst_set_kernel_family(family)
     try:
-        case = workloads.make_case(B=1, H=2, dtype="bf16", seed=103, device=DEV, **spec)
+        case = workloads.make_case(B=1, dtype="bf16", seed=103, device=DEV, **dict(dict(H=2), **spec))
         walk = RingWalk(case["Q"], case["scale"], case["causal"], case["q_off"], block=case.get("block", 0))
         p = walk._walk_params()
         chunks = B.chunk_array(case["K"], case["V"], case["k_offs"], case.get("masks"), p)
         for flag, floats in ((B.BURST_WALK_NO_STATE, spec["d"] + 2), (B.BURST_WALK_HALF_GRADS, spec["d"])):   # several launches
-            assert B.burst_walk_workspace_bytes(chunks, p, flag) >= 2 * spec["Nq"] * floats * 4
+            assert B.burst_walk_workspace_bytes(chunks, p, flag) >= spec.get("H", 2) * spec["Nq"] * floats * 4
         args = case["K"], case["V"], case["k_offs"]
         O0, lse0 = walk.forward(*args, masks=case.get("masks"))
         dQ, dKs, dVs = walk.backward_in_dtype(*args, case["dO"], masks=case.get("masks"))
+        full = walk.backward(*args, case["dO"], masks=case.get("masks"))[0]   # fp32
+        assert torch.equal(dQ, full.to(dQ.dtype))
         n = len(case["K"])
         leaves = [t.clone().requires_grad_(True) for t in [case["Q"], *case["K"], *case["V"]]]
         O, lse = burst_attention(leaves[0], leaves[1:n + 1], leaves[n + 1:], causal=case["causal"], q_off=case["q_off"],
