@@ -19,7 +19,8 @@
  *     kv_strides say otherwise.  K, V, dK, dV may have fewer heads than Q
  *     (burst_params.kv_heads; not in the paper).
  *   - Q, K, V, O, dO have element type `dtype` (bf16 or fp32).  The running
- *     state, lse, D and all gradients are fp32.
+ *     state, lse, D and all gradients are fp32 (burst_walk_bwd with half_grads writes
+ *     gradients of type `dtype`).
  *   - Scores are S = scale * Q K^T (Eq. 1 has scale = 1/sqrt(d); Alg. 1/2 omit
  *     it, here it is always applied).  scale must be finite and > 0.
  *   - Masking (not in the paper): with causal != 0 the key at global position
@@ -44,9 +45,15 @@
  *     attributes (once per device, whichever thread comes first); that call cannot be
  *     recorded into a HIP graph, so run each entry point once eagerly on a device
  *     before capturing it.
- *   - Supported shapes: B, H >= 1; Nq, Nc >= 0 (0 = nothing to do); 1 <= d <= 128
- *     for the generic kernels; the bf16 MFMA kernels are used when dtype = bf16
- *     and d = 128.  Any Nq, Nc (ragged tails) are accepted.
+ *   - Supported shapes: B, H >= 1; Nq, Nc >= 0 (0 = nothing to do); 1 <= d <= 128.
+ *     Any Nq, Nc (ragged tails) are accepted.  bf16 with d a multiple of 8 runs on the
+ *     bf16 matrix instructions, everything else (and slices, chunks or strides beyond
+ *     32-bit byte offsets) on the fp32 one.  Probabilities and dS enter the second
+ *     products rounded to bf16 at d = 64 and d = 128, with all their 24 bits otherwise
+ *     (d = 128 as well: dK and dV of grouped heads with Nq no multiple of 64).
+ *   - Infinities and NaN: at d = 64 and d = 128 (bf16) a hidden pair may be multiplied as
+ *     zero, so that an infinite or NaN value can make NaN of rows (keys) that share a
+ *     tile with one that sees it.  The other calls keep to the visible pairs.
  */
 #ifndef BURST_H
 #define BURST_H

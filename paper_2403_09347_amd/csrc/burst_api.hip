@@ -167,8 +167,9 @@ int check_params(const burst_params* p, KParams* k) {
   } while (0)
 
 // The MFMA kernels address a head's rows through 32-bit byte offsets (plus a few tiles of
-// prefetch past the end; dK/dV: the rows of all query heads of a group, from the first head's
-// row 0); longer or wider-strided slices or chunks take the generic kernels.
+// prefetch past the end); longer or wider-strided slices or chunks take the generic kernels.  So do
+// groups whose heads together span more than 4 GiB: no kernel needs that limit since dK/dV has a
+// descriptor per head, but these calls have the 24-bit probabilities of the generic kernels and keep them.
 constexpr int kMaxMfmaRows = 4 * 1024 * 1024;
 bool spans_fit(const burst_params* p, const KParams& k) {
   const long long q = ((long long)p->Nq + 1024) * k.lay.qs_r * 2 + (long long)(k.group - 1) * k.lay.qs_h * 2;
@@ -185,7 +186,7 @@ bool use_mfma(const burst_params* p, const KParams& k) {
 // every other multiple of 8, at the next of the padded widths 32, 64, 96, 128 (their DMA descriptors
 // must span less than 2 GiB, see s_dma_off).  Null where the generic kernels have to do it: rows that
 // do not start on 16 bytes, sizes beyond the 32-bit addressing.  (d = 96, 32 heads of 777 causal rows,
-// differentiable call with its gradients: 1375 us on the generic kernels, 114 us padded, with the same fp32
+// differentiable call with its gradients: 1375 us on the generic kernels, 121 us padded, with the same fp32
 // probabilities, see s_terms.)
 struct PlainFamily {
   decltype(&burst::d64::launch_fwd) fwd;
@@ -232,7 +233,7 @@ bool use_plain128(const burst_params* p, const KParams& k) {
 // The hand-scheduled dK/dV kernel walks the query tiles of all heads of a group as one list of at most 8192
 // tiles; longer groups take the generic kernel.  Groups whose slice is no multiple of its 64-row tiles go to the
 // plain kernel padded to 128 columns, whose P and dS have 24 bits as in the generic kernel that had these calls (see
-// s_terms).  (Call with gradients, 32 heads over 8, 3001 causal rows: 1020 us so, 560 us with the hand-scheduled
+// s_terms).  (Call with gradients, 32 heads over 8, 3001 causal rows: 1054 us so, 560 us with the hand-scheduled
 // kernel and its 8-bit P and dS (a walk's dV then 1.7e-3 off 64 bits instead of 7.6e-5), 10.3 ms with the generic one.)
 bool dkv_mfma_ok(const burst_params* p, const KParams& k) {
   if (k.group > 1) return p->Nq % 64 == 0 && (long long)k.group * (p->Nq / 64) <= 8192 && k.group <= 256;
@@ -374,11 +375,12 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
 }
 
 // Into how many key ranges a walk of the plain kernels is split (1: not at all).  Their workgroups hold
-// 128 rows and two share a CU: fewer than 512 leave the chip idle, fewer than 257 leave a second
-// workgroup's place on every CU.  Ranges shorter than 8 tiles would spend their time on the partial
-// states, and up to 20 tiles in all there is little to win (8 x 384 rows, forward: 512 keys 19.5 / 20.1 in
-// 2; 1024 keys 28 / 21; 1536 keys 36 / 22 in 3) and a walk keeps the bits it has chunk by chunk.  Forward, us, without / with the split this rule picks, in brackets one half or twice as many:
-// 32 heads x 40 rows x 32K keys 597 / 116 in 16 (8: 120, 24: 134); 32 x 512 x 8K causal 168 / 95 in 4
+// 128 rows and two share a CU: 512 fill every place on the chip, and with 256 or fewer two ranges or more have places
+// of their own.  Ranges shorter than 8 tiles would spend their time on the partial states.  Walks of fewer than
+// 20 tiles are not split, so that short ones keep the bits they have chunk by chunk: that gives up a quarter of the time just
+// below the line (8 x 384 rows, forward, without / with a split: 512 keys 19.5 / 20.1 us in 2; 1024 keys 28 / 21; 1536 keys,
+// 24 tiles, split by the rule, 36 / 22 in 3).  Forward, us, without / with the split this rule picks, in brackets one half or
+// twice as many: 32 heads x 40 rows x 32K keys 597 / 116 in 16 (8: 120, 24: 134); 32 x 512 x 8K causal 168 / 95 in 4
 // (2: 106, 8: 108); 8 x 100 x 4K, d = 64, 63 / 24 in 8 (4: 28, 16: 22); 8 x 1024 x 4K 85 / 38 in 8
 // (4: 39, 16: 52); backward (dQ) 32 x 512 x 8K 664 / 585, 8 x 1024 x 4K 257 / 191.
 int walk_splits(const std::vector<WalkChunk>& w) {

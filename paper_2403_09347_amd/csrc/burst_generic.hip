@@ -3,7 +3,7 @@
 // kernels.  Same mathematics (paper Alg. 1 loop body + merge, Alg. 2 block pair), all of it in fp32
 // on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 products, fp32 accumulation).
 //
-// What bounds them: the fp32 matrix rate (157 TFLOP/s nominal, 130 measured for a large product), 64
+// What they are built around: the fp32 matrix rate (157 TFLOP/s nominal, 153 measured for a large product), 64
 // cycles per MFMA, so that operand traffic is small beside it.  Hence no LDS tiles and no barriers
 // in the loops: a wavefront owns 32 query rows (or 32 keys), keeps their operands and accumulators in
 // registers and reads the other side's 32-row tiles straight from memory, each operand while the
@@ -11,10 +11,12 @@
 // tiles in turn (their partial results meet in LDS at the end, in a fixed order): a slice of 256
 // rows would otherwise keep 8 of the chip's 1024 SIMDs busy.
 // Measured per launch, forward / dQ / dK+dV, against one wavefront per row with scalar FMAs (the form
-// these kernels replace): fp32, 8 heads of 700 x 700, d = 128: 448 / 522 / 1927 -> 41 / 63 / 84 us
-// (half of the fp32 matrix rate; what is left is the address arithmetic and register moves of one
-// wavefront per SIMD); fp32, one head of 256 x 256, d = 64: 48 / 46 / 93 -> 13 / 18 / 26 us; bf16,
-// d = 96, 32 heads of 777 x 777: 1208 / 1070 / 4308 -> 272 / 480 / 587 us.
+// these kernels replace): fp32, 8 heads of 700 x 700 without a mask, d = 128: 448 / 522 / 1927 -> 48 / 64 / 91 us
+// (42 / 47 / 44 TFLOP/s, less than a third of the fp32 matrix rate: 176 row blocks for 256 CUs, one wavefront per SIMD, and
+// operands whose 32 rows are as many cache lines per load); fp32, one head of 256 x 256, d = 64: 48 / 46 / 93 ->
+// 15 / 18 / 27 us; bf16, d = 96, 32 heads of 777 x 777, before these calls went to the padded kernels of
+// burst_plain_mfma.h: 1208 / 1070 / 4308 -> 272 / 480 / 587 us.
+// Accumulators that come out infinite or NaN: see burst_rows.h.
 //
 // Operand layouts of v_mfma_f32_32x32x2_f32 (lane = 32 h + lr): A holds [m = lr][k = h], B holds
 // [k = h][n = lr], one value each; D register r holds [m = 8 (r / 4) + 4 h + r % 4][n = lr].

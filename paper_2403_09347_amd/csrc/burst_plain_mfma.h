@@ -122,8 +122,8 @@ __device__ __forceinline__ bf16x8 s_load8(const bf16* p, bool ok) {
 // the fp32 values, in elements t and t + 1 of the fragments.  One term where the inputs' 8 bits are the measure of a
 // probability as well (d = 64, 128, as in the hand-scheduled kernels).  The padded builds serve calls that had
 // fp32 probabilities in the generic kernels and keep all 24 bits: three terms, each remainder exact, three
-// MFMAs.  32 heads of 777 causal rows, d = 96, call with gradients: 80 us with one term, 114 us with three (1375 us
-// on the generic kernels); a walk's dV differs from 64 bits by 1.6e-3 with one term, 5.7e-7 with three (5.8e-7
+// MFMAs.  32 heads of 777 causal rows, d = 96, call with gradients: 80 us with one term, 114 us with three (121 us with
+// s_units and the check of burst_rows.h; 1375 us on the generic kernels); a walk's dV differs from 64 bits by 1.6e-3 with one term, 5.7e-7 with three (5.8e-7
 // on the generic kernels).
 constexpr int S_TERMS = S_PAD ? 3 : 1;
 // Units of scores, maxima and lse: log2 (one fma per exponent), or natural in the padded builds, where s x scale is rounded

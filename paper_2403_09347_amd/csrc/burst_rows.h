@@ -7,7 +7,7 @@
 // Finite accumulators need no second look: inf and NaN do not go away in a sum, nor when it is scaled.
 // Cost: nothing but the test at the end of a workgroup; with it, the time these calls took before they ran on the matrix
 // cores (rows at some 9 G pairs/s: 8 heads of 700 x 700, d = 128, all of them NaN: 0.45 / 0.5 / 1.9 ms for the three
-// kernels instead of 41 / 63 / 84 us).
+// kernels instead of 48 / 64 / 91 us).
 #pragma once
 #include "burst_common.h"
 

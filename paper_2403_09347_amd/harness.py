@@ -1,6 +1,6 @@
-"""Single-GPU harness: walks G key/value chunks, one library call per chunk, in the order a
-device of the ring would receive them (paper Alg. 1 / Alg. 2 loops with the ring step replaced
-by taking the next chunk).  Two walks: chunks already resident (plain), and chunks fetched from
+"""Single-GPU harness: walks G key/value chunks in the order a device of the ring would receive them
+(paper Alg. 1 / Alg. 2 loops with the ring step replaced by taking the next chunk).  Two walks: chunks
+already resident (plain: one library call for all of them), and, one library call per chunk, chunks fetched from
 a source pool through two receive buffers on a second stream while the previous chunk is being
 computed (the double buffer of paper Sec. 2.5 / Alg. 3, with a copy standing in for the ring
 transfer).  Host-side orchestration only: every arithmetic step is a library call."""
@@ -306,7 +306,7 @@ class GraphedStep:
     the kernels, set the pace.  The graph reads and writes the tensors it was recorded on: new
     inputs are copied INTO `walk.Q`, the chunk tensors and `dO`, results are read from
     `walk.O`, `walk.lse`, `dQ`, `dKs`, `dVs`.  Every node is a kernel (the gradient buffer is
-    cleared by a fill kernel, nothing is allocated or memset while recording)."""
+    cleared by a fill kernel, nothing is memset while recording, and a workspace comes from the graph's pool)."""
 
     def __init__(self, walk, Ks, Vs, k_offs, dO, masks=None):
         assert type(walk) is RingWalk
@@ -343,8 +343,8 @@ class SpanWalk:
     """A device whose query rows are several contiguous spans of the sequence, each its own tensor
     with its own global offset -- e.g. the two stripes of a load-balanced ("zig-zag") causal
     assignment (workloads.zigzag_spans).  Every span keeps its own running state; dK / dV of a
-    chunk accumulate over the spans.  Chunks a span cannot see cost a kernel launch that returns
-    at once (whole-chunk skipping, paper Sec. 2.6)."""
+    chunk accumulate over the spans.  Chunks a span cannot see are skipped as a whole (paper
+    Sec. 2.6): passed over inside the forward's launch, a backward launch that returns at once."""
 
     def __init__(self, Q_spans, q_offs, scale, causal=True, window=0):
         self.walks = [RingWalk(Q, scale, causal, off, window) for Q, off in zip(Q_spans, q_offs)]
