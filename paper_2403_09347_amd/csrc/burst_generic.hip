@@ -169,6 +169,10 @@ __device__ __forceinline__ bool any_wave_odd(float* flags, int w, int lane, bool
   return __builtin_amdgcn_readfirstlane(any) != 0;
 }
 
+// The share of wavefront w of a block's 32 rows or keys.
+template <int W>
+__device__ __forceinline__ unsigned share(int w) { return ((1u << (32 / W)) - 1u) << (w * (32 / W)); }
+
 // ---------------------------------------------------------------------------- forward
 template <typename T, int D, bool VEC, int W>
 __global__ void __launch_bounds__(64 * W, W / 4)
@@ -278,14 +282,19 @@ fwd_generic_kernel(GenArgs a) {
   const float mref = mg == BURST_NEG_INF ? 0.f : mg;
 #pragma unroll
   for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2((ml[i * 64 + lr] - mref) * kLog2e);
-  if (__builtin_amdgcn_ballot_w64(row < a.Nq && larger_of(0, lg) >= kInfBits) != 0) {   // (alike in all wavefronts) the block's rows one by one, see burst_rows.h
-#pragma unroll 1
-    for (int one = row0 + w, end = min(row0 + 32, a.Nq); one < end; one += W) {
-      const size_t sr = (size_t)head * a.Nq + one;
-      RowState st = row_state(a.fresh, a.O_acc, a.m, a.l, sr, a.d, lane);
-      row_forward<T>(st, a, head, one, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 0x7fffffff);
-      row_store<T>(st, a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : (T*)a.O_out + a.lay.q_base(head) + (size_t)one * a.lay.qs_r,
-                   a.lse_out, sr, a.d, lane);
+  if (__builtin_amdgcn_ballot_w64(row < a.Nq && larger_of(0, lg) >= kInfBits) != 0) {   // (alike in all wavefronts) the block's rows by themselves, see burst_rows.h
+    for (unsigned left = first_bits(a.Nq - row0) & share<W>(w); left != 0;) {
+      int rows[kRows];
+      const int n = next_rows(left, row0, rows);
+      RowState st[kRows];
+#pragma unroll
+      for (int r = 0; r < kRows; r++) st[r] = row_state(a.fresh, a.O_acc, a.m, a.l, (size_t)head * a.Nq + rows[r], a.d, lane);
+      rows_forward<T, VEC>(st, args_again<GenArgs>(), head, rows, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 0x7fffffff);
+#pragma unroll
+      for (int r = 0; r < kRows; r++)
+        if (r < n)
+          row_store<T>(st[r], a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : (T*)a.O_out + a.lay.q_base(head) + (size_t)rows[r] * a.lay.qs_r,
+                       a.lse_out, (size_t)head * a.Nq + rows[r], a.d, lane);
     }
     return;
   }
@@ -433,12 +442,15 @@ bwd_dq_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits)) {   // the block's rows one by one, see burst_rows.h
-#pragma unroll 1
-    for (int one = row0 + w, end = min(row0 + 32, a.Nq); one < end; one += W) {
-      float g[2];
-      row_dq<T, 64>(g, a, head, one, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 1);
-      row_gradient<T>(a.dQ, ((size_t)head * a.Nq + one) * a.d, g, a.scale, a.half, a.acc_dq, lane, a.d);
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits)) {   // the block's rows by themselves, see burst_rows.h
+    for (unsigned left = first_bits(a.Nq - row0) & share<W>(w); left != 0;) {
+      int rows[kRows];
+      const int n = next_rows(left, row0, rows);
+      float g[kRows][2];
+      rows_dq<T, VEC, 64>(g, args_again<GenArgs>(), head, rows, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 1);
+#pragma unroll
+      for (int r = 0; r < kRows; r++)
+        if (r < n) row_gradient<T>(a.dQ, ((size_t)head * a.Nq + rows[r]) * a.d, g[r], a.scale, a.half, a.acc_dq, lane, a.d);
     }
     return;
   }
@@ -602,14 +614,19 @@ bwd_dkv_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits)) {   // the block's keys one by one, see burst_rows.h
-#pragma unroll 1
-    for (int one = key0 + w, end = min(key0 + 32, Nc); one < end; one += W) {
-      const size_t at = ((size_t)kvhead * Nc + one) * a.d;
-      float gk[2], gv[2];
-      key_dkv<T>(gk, gv, a, C, kvhead, one, lane);
-      row_gradient<T>(C.dK, at, gk, a.scale, a.half, a.acc_dkv, lane, a.d);
-      row_gradient<T>(C.dV, at, gv, 1.f, a.half, a.acc_dkv, lane, a.d);
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits)) {   // the block's keys by themselves, see burst_rows.h
+    for (unsigned left = first_bits(Nc - key0) & share<W>(w); left != 0;) {
+      int keys[kRows];
+      const int n = next_rows(left, key0, keys);
+      float gk[kRows][2], gv[kRows][2];
+      keys_dkv<T, VEC>(gk, gv, args_again<GenArgs>(), C, kvhead, keys, lane);
+#pragma unroll
+      for (int r = 0; r < kRows; r++) {
+        if (r >= n) continue;
+        const size_t at = ((size_t)kvhead * Nc + keys[r]) * a.d;
+        row_gradient<T>(C.dK, at, gk[r], a.scale, a.half, a.acc_dkv, lane, a.d);
+        row_gradient<T>(C.dV, at, gv[r], 1.f, a.half, a.acc_dkv, lane, a.d);
+      }
     }
     return;
   }

@@ -445,7 +445,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
   const float l_all = sum_both_halves(lsum);
-  if constexpr (S_PAD) {                           // rows with an infinity or NaN, one by one (see burst_rows.h)
+  if constexpr (S_PAD) {                           // rows with an infinity or NaN, by themselves (see burst_rows.h)
     unsigned most = larger_of(0, l_all);
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
@@ -464,19 +464,26 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         first = all * split / a.splits;
         last = all * (split + 1) / a.splits;
       }
-      for (unsigned rows = redo; rows != 0; rows &= rows - 1) {
-        const int one = qb * SF_BR + wu * 32 + __builtin_ctz(rows);
-        const size_t sr = (size_t)head * a.Nq + one;
-        RowState st = row_state(a.fresh, a.O_acc, a.m, a.l, sr, d, lane);
-        row_forward<bf16>(st, a, head, one, lane, tiles_of, first, last);
-        if (a.splits > 1) {
-          const size_t n_rows = (size_t)a.H * a.Nq, pr = (size_t)split * n_rows + sr;
-          float* const ml = a.part + (size_t)a.splits * n_rows * d;
-          row_gradient<bf16>(a.part, pr * d, st.o, 1.f, 0, 0, lane, d);
-          if (lane == 0) { ml[pr] = st.m; ml[(size_t)a.splits * n_rows + pr] = st.l; }
-        } else {
-          row_store<bf16>(st, a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : a.O_out + a.lay.q_base(head) + (size_t)one * a.lay.qs_r,
-                          a.lse, sr, d, lane);
+      for (unsigned left = redo; left != 0;) {
+        int rows[kRows];
+        const int n = next_rows(left, qb * SF_BR + wu * 32, rows);
+        RowState st[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; r++) st[r] = row_state(a.fresh, a.O_acc, a.m, a.l, (size_t)head * a.Nq + rows[r], d, lane);
+        rows_forward<bf16, true>(st, args_again<FwdArgsLite>(), head, rows, lane, tiles_of, first, last);
+#pragma unroll
+        for (int r = 0; r < kRows; r++) {
+          if (r >= n) continue;
+          const size_t sr = (size_t)head * a.Nq + rows[r];
+          if (a.splits > 1) {
+            const size_t n_rows = (size_t)a.H * a.Nq, pr = (size_t)split * n_rows + sr;
+            float* const ml = a.part + (size_t)a.splits * n_rows * d;
+            row_gradient<bf16>(a.part, pr * d, st[r].o, 1.f, 0, 0, lane, d);
+            if (lane == 0) { ml[pr] = st[r].m; ml[(size_t)a.splits * n_rows + pr] = st[r].l; }
+          } else {
+            row_store<bf16>(st[r], a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : a.O_out + a.lay.q_base(head) + (size_t)rows[r] * a.lay.qs_r,
+                            a.lse, sr, d, lane);
+          }
         }
       }
       if ((redo >> lr) & 1) return;
@@ -730,7 +737,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
-  if constexpr (S_PAD) {                           // rows with an infinity or NaN, one by one (see burst_rows.h)
+  if constexpr (S_PAD) {                           // rows with an infinity or NaN, by themselves (see burst_rows.h)
     unsigned most = 0;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
@@ -738,13 +745,18 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
       for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
     const unsigned long long bal = __builtin_amdgcn_ballot_w64(ok && most >= kInfBits);
     const unsigned redo = (unsigned)bal | (unsigned)(bal >> 32);
-    for (unsigned rows = redo; rows != 0; rows &= rows - 1) {
-      const int one = qb * SQ_BR + wu * 32 + __builtin_ctz(rows);
-      const size_t at = ((size_t)head * a.Nq + one) * d;
-      float g[2];
-      row_dq<bf16, SQ_BC>(g, a, head, one, lane, tiles_of, split, a.splits);
-      if (a.splits > 1) row_gradient<bf16>(a.part, (size_t)split * a.H * a.Nq * d + at, g, a.scale, 0, 0, lane, d);
-      else row_gradient<bf16>(a.dQ, at, g, a.scale, a.half, a.acc_dq, lane, d);
+    for (unsigned left = redo; left != 0;) {
+      int rows[kRows];
+      const int n = next_rows(left, qb * SQ_BR + wu * 32, rows);
+      float g[kRows][2];
+      rows_dq<bf16, true, SQ_BC>(g, args_again<BwdArgsLite>(), head, rows, lane, tiles_of, split, a.splits);
+#pragma unroll
+      for (int r = 0; r < kRows; r++) {
+        if (r >= n) continue;
+        const size_t at = ((size_t)head * a.Nq + rows[r]) * d;
+        if (a.splits > 1) row_gradient<bf16>(a.part, (size_t)split * a.H * a.Nq * d + at, g[r], a.scale, 0, 0, lane, d);
+        else row_gradient<bf16>(a.dQ, at, g[r], a.scale, a.half, a.acc_dq, lane, d);
+      }
     }
     if ((redo >> lr) & 1) return;
   }
@@ -1015,13 +1027,19 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
     if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
-#pragma unroll 1
-      for (int one = key_wg + __builtin_amdgcn_readfirstlane(w) * 32, end = min(one + 32, Nc); one < end; one++) {
-        const size_t at = ((size_t)kvhead * Nc + one) * d;
-        float gk[2], gv[2];
-        key_dkv<bf16>(gk, gv, a, C, kvhead, one, lane);
-        row_gradient<bf16>(C.dK, at, gk, a.scale, a.half, a.acc_dkv, lane, d);
-        row_gradient<bf16>(C.dV, at, gv, 1.f, a.half, a.acc_dkv, lane, d);
+      const int base = key_wg + __builtin_amdgcn_readfirstlane(w) * 32;
+      for (unsigned left = first_bits(Nc - base); left != 0;) {
+        int keys[kRows];
+        const int n = next_rows(left, base, keys);
+        float gk[kRows][2], gv[kRows][2];
+        keys_dkv<bf16, true>(gk, gv, args_again<BwdArgsLite>(), C, kvhead, keys, lane);
+#pragma unroll
+        for (int r = 0; r < kRows; r++) {
+          if (r >= n) continue;
+          const size_t at = ((size_t)kvhead * Nc + keys[r]) * d;
+          row_gradient<bf16>(C.dK, at, gk[r], a.scale, a.half, a.acc_dkv, lane, d);
+          row_gradient<bf16>(C.dV, at, gv[r], 1.f, a.half, a.acc_dkv, lane, d);
+        }
       }
       return;
     }

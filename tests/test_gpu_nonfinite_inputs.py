@@ -136,3 +136,30 @@ def test_infinities_and_nan_stay_where_the_formula_puts_them(dtype, spec, what):
 def test_grouped_dkv_with_partial_last_tiles(what):
     """(O and lse come from kernels that multiply hidden pairs too: only their outputs go into the reference.)"""
     check(*GROUPED, what, forward=False)
+
+
+@pytest.mark.parametrize("dtype,spec", [("bf16", dict(H=2, d=96, Nq=33, chunk_rows=[70, 1, 129])), ("f32", dict(H=2, d=40, Nq=33, chunk_rows=[70, 1, 129])),
+                                        ("bf16", dict(H=4, kv_heads=2, d=128, Nq=33, chunk_rows=[70, 1, 129]))],
+                         ids=["padded", "f32", "grouped"])
+def test_nothing_is_written_past_the_gradients(dtype, spec):
+    """Wavefronts past the last key or row see NaN too (padding x infinity) and have nothing to write."""
+    case = workloads.make_case(B=1, dtype=dtype, seed=149, device="cuda:0", **spec)
+    case["dO"].fill_(NAN)
+    walk = RingWalk(case["Q"], case["scale"], kv_heads=case.get("kv_heads", 0))
+    walk.forward(case["K"], case["V"], case["k_offs"])
+    guard = 16384
+    flat = {}
+
+    def inside(name, shape):
+        n = int(np.prod(shape))
+        flat[name] = torch.full((n + 2 * guard,), 7.0, device="cuda:0")
+        return flat[name][guard:guard + n].view(shape)
+
+    dQ = inside("dQ", tuple(case["Q"].shape))
+    dKs = [inside(f"dK{j}", tuple(k.shape)) for j, k in enumerate(case["K"])]
+    dVs = [inside(f"dV{j}", tuple(k.shape)) for j, k in enumerate(case["K"])]
+    walk.backward(case["K"], case["V"], case["k_offs"], case["dO"], dQ, dKs, dVs)
+    torch.cuda.synchronize()
+    for name, t in flat.items():
+        assert bool((t[:guard] == 7.0).all()) and bool((t[-guard:] == 7.0).all()), name
+        assert bool(torch.isnan(t[guard:-guard]).all()), name
