@@ -14,7 +14,9 @@ def burst_attention(q, k_chunks, v_chunks, scale=None, causal=False, q_off=0, wi
     to q and to every chunk (rounded to the input dtype).  Views with a contiguous last dimension
     (sequence-major tensors, slices of a packed projection) are read in place, without a copy.
     block_masks: one uint8 device tensor of block flags per chunk (see binding.params) with blocks
-    of `block` rows / keys, or None for a chunk without flags; or None."""
+    of `block` rows / keys, or None for a chunk without flags; or None.
+    The node saves its inputs, O and lse as torch's own operations do: a tensor changed in place before the backward is
+    an error, and a second backward needs retain_graph."""
     if isinstance(k_chunks, torch.Tensor):
         k_chunks, v_chunks = [k_chunks], [v_chunks]
     assert len(k_chunks) == len(v_chunks) and len(k_chunks) > 0
