@@ -547,8 +547,10 @@ constexpr int SQ_BR = 128;                        // query rows per workgroup
 constexpr int SQ_BC = 32;                         // keys per tile
 constexpr int SQ_TILE = SQ_BC * S_ROWB;
 
+// (d = 64 fits four wavefronts per SIMD; left alone, the compiler takes 136 registers with block flags, which leaves three:
+// 32 heads of 4096 x 4096 rows, 64-wide flags at density 0.5: 164 us instead of 147)
 template <bool SPARSE>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, S_D == 64 && !S_PAD ? 4 : 2)
 burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SQ_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
