@@ -27,6 +27,7 @@ int launch_bwd_dkv_generic(const KParams&, int, const BwdIo&, const Chunk*, int,
   int launch_fwd(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t);            \
   int launch_bwd_dq(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);         \
   int launch_bwd_dkv(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);        \
+  int dkv_keys();                                                                          \
   }
 int launch_merge_splits(const KParams&, const FwdIo&, hipStream_t);
 int launch_fill_unseen(const KParams&, int, void*, float*, hipStream_t);
@@ -192,8 +193,9 @@ struct PlainFamily {
   decltype(&burst::d64::launch_fwd) fwd;
   decltype(&burst::d64::launch_bwd_dq) bwd_dq;
   decltype(&burst::d64::launch_bwd_dkv) bwd_dkv;
+  decltype(&burst::d64::dkv_keys) dkv_keys;
 };
-#define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv}
+#define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv, burst::ns::dkv_keys}
 const PlainFamily kD64 = BURST_PLAIN(d64), kD128p = BURST_PLAIN(d128p), kD32x = BURST_PLAIN(d32x), kD64x = BURST_PLAIN(d64x), kD96x = BURST_PLAIN(d96x),
                   kD128x = BURST_PLAIN(d128x);
 #undef BURST_PLAIN
@@ -405,6 +407,47 @@ int dq_launches(const std::vector<WalkChunk>& w) {
   for_each_run(w, fwd_kernels, [&](const Kernels&, const KParams&, const Chunk*, int, bool, bool) { n++; return (int)BURST_OK; });
   return n;
 }
+// How the dK/dV launch of a walk is cut (RowParts; splits = 1: not at all).  Few or unequal walks leave most of the chip idle:
+// under a causal mask the longest is twice the average, and with grouped heads there are few blocks of keys.  A block's walk
+// is therefore cut into about as many parts as the longest walk exceeds the work of one place on the chip (two workgroups
+// of the plain kernels share a CU), of at least 256 (hand-scheduled: 1024) rows, below which the partial results cost what
+// the balance gains.  Equal parts for short and long blocks (down to 8 tiles) do better than parts of equal length, because
+// the launch then ends with small ones.  Below a ratio of 1.9 a launch that fills the chip loses.  Walks of fewer than 24
+// tiles (hand-scheduled: 32) keep the bits they have chunk by chunk.  Causal calls with gradients, us, whole / by the rule, in
+// brackets one part less and more: 32 heads over 8 x 3001 rows 1055 / 633 in 3 (690, 636), x 3008 564 / 440 in 3 (448, 445);
+// 32 over 8 x 2048, d = 64, 354 / 156 in 8 (153 in 6, 167 in 12); 8 over 2 x 1000 332 / 98 in 16 (101 in 12); 8 x 3000, d = 64,
+// 174 / 124 in 5 (123, 124); 32 x 777, d = 96, 123 / 107 in 3 (111, 117); 8 x 8000, d = 64, 511 / 443 in 2 (447 in 3); not
+// cut: 64 x 1024, d = 64, 98 (in 2: 112), 16 x 3000 279 (301), 16 x 4096 403 (440).
+struct DkvParts { int splits, tiles; long long rows; };
+constexpr DkvParts kWhole = {1, 1, 0};
+DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
+  if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return kWhole;
+  const Kernels f = dkv_kernels(&w[0].p, w[0].k);
+  if (f.plain == nullptr && !f.hand) return kWhole;
+  const KParams& k = w[0].k;
+  const int bc = f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.plain != nullptr ? 32 : 64;
+  const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;
+  long long total = 0, most = 0, rows = 0, blocks = 0;
+  for (const WalkChunk& x : w) {
+    if (x.p.block_mask != nullptr || !(dkv_kernels(&x.p, x.k) == f) || (f.hand && x.c.ks_r != w[0].c.ks_r)) return kWhole;
+    rows += heads * x.c.Nc;
+    blocks += heads * ((x.c.Nc + bc - 1) / bc);
+    if (blocks > 2 * slots) return kWhole;         // (no walk is 1.9 times the average place's then)
+    for (int key0 = 0; key0 < x.c.Nc; key0 += bc) {
+      const burst::RowRange r = burst::row_range(k.Nq, k.causal, k.window, k.q_off, x.c.k_off, x.c.Nc, key0, bc, br);
+      const long long walk = (long long)(r.hi - r.lo) * k.group;
+      total += walk * heads;
+      most = std::max(most, walk);
+    }
+  }
+  if (most < 24 || most > 0x7fffffffLL || 10 * most * slots < 19 * total) return kWhole;
+  const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on
+  const long long splits = std::min({16LL, ratio, most / (f.plain != nullptr ? 8 : 16)});
+  return splits < 2 ? kWhole : DkvParts{(int)splits, 8, rows};
+}
+size_t dkv_bytes(const KParams& k, const DkvParts& p) {
+  return p.splits > 1 ? (size_t)p.splits * 2 * p.rows * k.d * sizeof(float) : 0;
+}
 size_t split_bytes(const KParams& k, int splits) {
   return splits > 1 ? (size_t)splits * k.B * k.H * k.Nq * ((size_t)k.d + 2) * sizeof(float) : 0;
 }
@@ -594,7 +637,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -648,6 +691,7 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
   const KParams& k = w[0].k;
   const size_t rows = (size_t)k.B * k.H * k.Nq;
   size_t need = split_bytes(k, walk_splits(w));
+  if (!(flags & BURST_WALK_NO_STATE)) need = std::max(need, dkv_bytes(k, dkv_parts(w)));   // (that flag: a forward walk)
   if (flags != 0 && dq_launches(w) > 1) {          // between the launches: dQ in fp32, the state
     if (flags & BURST_WALK_HALF_GRADS) need = std::max(need, rows * k.d * sizeof(float));
     if (flags & BURST_WALK_NO_STATE) need = std::max(need, rows * ((size_t)k.d + 8) * sizeof(float));
@@ -734,6 +778,8 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   hipStream_t s = (hipStream_t)stream;
   int splits = walk_splits(w);
   if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
+  DkvParts parts = dkv_parts(w);
+  if (workspace == nullptr || workspace_bytes < dkv_bytes(k, parts)) parts = kWhole;
   auto zero = [&](void* ptr, long long n) { return burst::launch_zero_fill((float*)ptr, n, half, s); };
   // dQ as bf16 by several launches: fp32 in the workspace between them
   const bool staged = half && have_q && splits == 1 && !w.empty() && dq_launches(w) > 1;
@@ -750,7 +796,8 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     }
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
-    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits};
+    BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,
+                (float*)workspace, parts.splits, parts.tiles};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       BwdIo one = io;
       one.acc_dq = accumulate_dq != 0 || !first;

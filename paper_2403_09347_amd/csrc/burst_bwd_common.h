@@ -1,6 +1,6 @@
 // Shared by the backward kernels (paper Alg. 2 loop body, bf16).
 #pragma once
-#include "burst_common.h"
+#include "burst_rows.h"
 
 namespace burst {
 
@@ -81,6 +81,79 @@ __device__ __forceinline__ void store_dkv(const f32x16 (&dk)[DB], const f32x16 (
       put(krs, col[db] + key_of(r) * pitch, scale * dk[db][r]);
       put(vrs, col[db] + key_of(r) * pitch, dv[db][r]);
     }
+}
+
+// Adds the partial dK, dV of a split launch (see RowParts) in the order of the parts: one wavefront per key.  Bound by
+// its reads, which lie in the last-level cache.  PAD: keys whose sum is infinite or NaN are computed by themselves
+// (see burst_rows.h).
+template <int D, int BC, int BR, bool PAD, typename A>
+__global__ void __launch_bounds__(256)
+merge_dkv_kernel(A a) {
+  const int lane = threadIdx.x & 63;
+  const int row = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= a.parts.rows) return;
+  int c = 0;
+  while (c + 1 < a.n && row >= a.ch[c + 1].first_row) c++;
+  const Chunk& C = a.ch[c];
+  const int kvhead = (row - C.first_row) / C.Nc, key = row - C.first_row - kvhead * C.Nc;
+  const RowRange range = row_range(a.Nq, a.causal, a.window, a.q_off, C.k_off, C.Nc, key / BC * BC, BC, BR);
+  const int parts = a.parts.of((range.hi - range.lo) * a.group);
+  if (parts == 1) return;                          // written by its workgroup
+  int d = D;
+  if constexpr (PAD) d = a.d;
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  f32x2 k = {0.f, 0.f}, v = {0.f, 0.f};
+  const int col = 2 * lane < d ? 2 * lane : 0;
+  const size_t plane = (size_t)a.parts.rows * d;
+  const float* from = a.parts.part + (size_t)row * d + col;
+#pragma unroll 4
+  for (int i = 0; i < parts; i++, from += 2 * plane) {
+    const f32x2 x = *reinterpret_cast<const f32x2*>(from), y = *reinterpret_cast<const f32x2*>(from + plane);
+    k[0] += x[0]; k[1] += x[1];
+    v[0] += y[0]; v[1] += y[1];
+  }
+  const size_t at = ((size_t)kvhead * C.Nc + key) * d;
+  if constexpr (PAD) {
+    const unsigned most = larger_of(larger_of(larger_of(larger_of(0, k[0]), k[1]), v[0]), v[1]);
+    if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
+      const int keys[kRows] = {key, key, key};
+      float gk[kRows][2], gv[kRows][2];
+      keys_dkv<bf16, true>(gk, gv, a, C, kvhead, keys, lane);
+      row_gradient<bf16>(C.dK, at, gk[0], a.scale, a.half, a.acc_dkv, lane, d);
+      row_gradient<bf16>(C.dV, at, gv[0], 1.f, a.half, a.acc_dkv, lane, d);
+      return;
+    }
+  }
+  if (2 * lane >= d) return;
+  if (a.half) {
+    bf16x2 x, y;
+    x[0] = (bf16)k[0]; x[1] = (bf16)k[1];
+    y[0] = (bf16)v[0]; y[1] = (bf16)v[1];
+    *reinterpret_cast<bf16x2*>((bf16*)C.dK + at + col) = x;
+    *reinterpret_cast<bf16x2*>((bf16*)C.dV + at + col) = y;
+  } else {
+    f32x2* const dk = reinterpret_cast<f32x2*>((float*)C.dK + at + col);
+    f32x2* const dv = reinterpret_cast<f32x2*>((float*)C.dV + at + col);
+    if (a.acc_dkv) {
+      const f32x2 x = *dk, y = *dv;
+      k[0] += x[0]; k[1] += x[1];
+      v[0] += y[0]; v[1] += y[1];
+    }
+    *dk = k;
+    *dv = v;
+  }
+}
+template <int D, int BC, int BR, bool PAD, typename A>
+static int launch_merge_dkv(const A& a, hipStream_t stream) {
+  BURST_LAUNCH((merge_dkv_kernel<D, BC, BR, PAD, A>), dim3((unsigned)((a.parts.rows + 3) / 4)), dim3(256), 0, stream, a);
+  return launch_status();
+}
+inline RowParts row_parts(const BwdIo& io, const Chunk* ch, int n, long long heads) {
+  RowParts p = {io.kv_part, io.kv_splits > 1 ? io.kv_splits : 1, io.kv_tiles > 0 ? io.kv_tiles : 1, 0};
+  long long rows = 0;
+  for (int i = 0; i < n; i++) rows += heads * ch[i].Nc;
+  p.rows = p.splits > 1 ? (int)rows : 0;
+  return p;
 }
 
 __device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {

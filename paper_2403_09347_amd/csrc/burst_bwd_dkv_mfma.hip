@@ -65,6 +65,7 @@ struct DkvArgs {
   int n, per;            // chunks, all with block flags or none; workgroups of each (chunk_at)
   Layout lay;            // strides of Q and dO
   Chunk ch[kMaxChunks];
+  RowParts parts;
 };
 
 // SPARSE: the call carries block flags (paper Sec. 2.6) or several query heads share a key/value
@@ -75,7 +76,8 @@ struct DkvArgs {
 // wavefront) into LDS and then walks that list instead of t_begin, t_begin + 1, ...; a wavefront
 // whose bit is clear hides the whole tile in the masking path.  Entries past the end name a tile
 // beyond the slice: its Q, dO and statistics read as zeros and contribute nothing.
-template <bool SPARSE, int NW>
+// PARTS: the walks are cut (RowParts; calls without flags only).
+template <bool SPARSE, int NW, bool PARTS>
 __global__ void __launch_bounds__(64 * NW, 1)
 burst_bwd_dkv_kernel(DkvArgs a) {
   using Shape = DkvShape<NW>;
@@ -87,8 +89,13 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   // the workgroups of all chunks, chunk after chunk
   const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
-  int head, kblk;
-  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + DKV_BC - 1) / DKV_BC, head, kblk)) return;
+  int head, kblk, part = 0;
+  const int bid = (int)blockIdx.x - C.first_block, blocks = (C.Nc + DKV_BC - 1) / DKV_BC;
+  if constexpr (PARTS) {
+    if (!locate_part(bid, a.H, blocks, a.parts.splits, head, kblk, part)) return;
+  } else {
+    if (!locate_block(bid, a.H, blocks, head, kblk)) return;
+  }
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
   const int key_wg = kblk * DKV_BC;
@@ -104,17 +111,16 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   const float* lseh = a.lse + (size_t)head * q_rows;
   const float* Dh = a.D + (size_t)head * q_rows;
 
-  // query tiles to visit: causal rows before the first key of the workgroup see none of it
-  int ntiles_all = (a.Nq + DKV_BR - 1) / DKV_BR;
-  int t_begin = 0;
-  if (a.causal) {
-    long long first_row = k_off + key_wg - a.q_off;      // first row index that sees key_wg
-    if (first_row > 0) t_begin = (int)min((long long)ntiles_all, first_row / DKV_BR);
-  }
-  if (a.window > 0) {
-    // sliding window: rows at positions >= key position + window no longer see the key
-    long long last_row = k_off + min(key_wg + DKV_BC, Nc) - 1 + a.window - 1 - a.q_off;
-    ntiles_all = last_row < 0 ? 0 : (int)min((long long)ntiles_all, last_row / DKV_BR + 1);
+  // query tiles of a head to visit; of the walk over all of them, this workgroup's part
+  const RowRange range = row_range(a.Nq, a.causal, a.window, a.q_off, k_off, Nc, key_wg, DKV_BC, DKV_BR);
+  const int ntiles_all = range.hi;
+  int t_begin = range.lo, first = 0, nwalk = ntiles_all - t_begin, parts = 1;   // (tiles to walk)
+  if constexpr (PARTS) {
+    nwalk *= group;
+    parts = a.parts.of(nwalk);
+    if (part >= parts) return;
+    first = (int)((long long)nwalk * part / parts);
+    nwalk = (int)((long long)nwalk * (part + 1) / parts) - first;
   }
 
   f32x16 dk[4], dv[4];     // [32-wide d block]: rows = the wavefront's 32 keys; pinned in AGPRs
@@ -137,10 +143,9 @@ burst_bwd_dkv_kernel(DkvArgs a) {
     }
   };
   if constexpr (SPARSE) load_kv();
-  int nwalk = ntiles_all - t_begin;                // tiles to walk
   // SPARSE: the list of visible tiles, built by wavefront 0 (64 candidate tiles per round).
   // list[0] = number of entries, list[1 + j] = tile | (wavefront bits << 16), then 4 end entries.
-  int* const list = reinterpret_cast<int*>(smem + DKV_LDS_BYTES);
+  int* list = reinterpret_cast<int*>(smem + DKV_LDS_BYTES);
   if constexpr (SPARSE) {
     const int end_tile = (a.Nq + DKV_BR - 1) / DKV_BR;          // a tile past the rows of the group's first head
     if (w == 0) {
@@ -172,7 +177,10 @@ burst_bwd_dkv_kernel(DkvArgs a) {
       if (lane == 0) list[0] = n;
     }
     __syncthreads();
-    nwalk = __builtin_amdgcn_readfirstlane(list[0]);
+    if constexpr (PARTS) list += first;            // (the list holds the whole walk)
+    else nwalk = __builtin_amdgcn_readfirstlane(list[0]);
+  } else {
+    t_begin += first;
   }
   // walk position j -> its entry: the tile of its head in the low 16 bits and, SPARSE, the wavefront
   // bits (16..19) and the head of the group (20..27)
@@ -305,6 +313,9 @@ burst_bwd_dkv_kernel(DkvArgs a) {
     };
     load_init(0, reinterpret_cast<const float*>(smem + DKV_LDS_L), reinterpret_cast<const float*>(smem + DKV_LDS_D));
 
+    // lgkmcnt(0).  With a scalar load possibly still on its way at the loop's entry the compiler waits, in every step, for
+    // all six operand reads before the first MFMA instead of for one (1 % of long walks, 2 % of short ones).
+    __builtin_amdgcn_s_waitcnt(0xC07F);
     int slot = 0;
     for (int n = 0; n < nwalk; n++) {                  // n = walk position; statistic slot n & 3 holds its tile
       // this tile, the entries of the tile whose rows are fetched now and of the one whose statistics are
@@ -463,23 +474,37 @@ burst_bwd_dkv_kernel(DkvArgs a) {
                    "+a"(dv[0]), "+a"(dv[1]), "+a"(dv[2]), "+a"(dv[3]));
   }
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
-  const size_t first = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
-  store_dkv<4, false>(dk, dv, (char*)C.dK + first, (char*)C.dV + first, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
+  if constexpr (PARTS) {
+    void *dk_at, *dv_at;
+    if (parts > 1) {
+      float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + C.first_row + (size_t)head * Nc) * 128;
+      dk_at = to; dv_at = to + (size_t)a.parts.rows * 128;
+    } else {
+      const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
+      dk_at = (char*)C.dK + at; dv_at = (char*)C.dV + at;
+    }
+    store_dkv<4, false>(dk, dv, dk_at, dv_at, Nc, 128, key0, lr, h, a.scale, parts > 1 ? 0 : a.half, parts > 1 ? 0 : a.acc_dkv);
+  } else {
+    const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
+    store_dkv<4, false>(dk, dv, (char*)C.dK + at, (char*)C.dV + at, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
+  }
 }
 
 // n chunks, all with block flags or none.  key_waves: 4 (128-key workgroups) or 2 (64-key workgroups, calls
 // with block flags only).
-int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream, int key_waves) {
+template <bool SPARSE, int NW, bool PARTS>
+static int launch_shape(const DkvArgs& a, long long nb, hipStream_t stream) {
+  constexpr unsigned lds = DkvShape<NW>::LDS_BYTES + (SPARSE ? DkvShape<NW>::LIST_BYTES : 0);
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
-    return hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<false, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               DkvShape<4>::LDS_BYTES) == hipSuccess &&
-           hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<true, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               DkvShape<4>::LDS_BYTES + DkvShape<4>::LIST_BYTES) == hipSuccess &&
-           hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<true, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               DkvShape<2>::LDS_BYTES + DkvShape<2>::LIST_BYTES) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
+    return hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<SPARSE, NW, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               lds) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
+  BURST_LAUNCH((burst_bwd_dkv_kernel<SPARSE, NW, PARTS>), dim3((unsigned)nb), dim3(64 * NW), lds, stream, a);
+  return launch_status();
+}
+int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream, int key_waves) {
   DkvArgs a;
   a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D;
   a.Nq = p.Nq; a.H = p.B * p.H / p.group; a.group = p.group;     // workgroups are laid out over key/value heads
@@ -491,22 +516,21 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
   if (key_waves != 4 && !(key_waves == 2 && listed)) return BURST_ERR_SHAPE;
   const int bc = 32 * key_waves;
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
-  const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per);
+  const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, key_waves == 4 ? io.kv_splits : 1);
+  a.parts = row_parts(io, ch, n, a.H);
+  if (a.parts.splits > 1 && (key_waves != 4 || ch[0].bmask != nullptr)) return BURST_ERR_SHAPE;
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
   if (nb == 0) return BURST_OK;
   if (listed) {
     const int max_list = key_waves == 4 ? DkvShape<4>::MAX_LIST : DkvShape<2>::MAX_LIST;
     if ((long long)a.group * ((p.Nq + DKV_BR - 1) / DKV_BR) > max_list) return BURST_ERR_SHAPE;
-    if (key_waves == 4)
-      BURST_LAUNCH((burst_bwd_dkv_kernel<true, 4>), dim3((unsigned)nb), dim3(256),
-                   DkvShape<4>::LDS_BYTES + DkvShape<4>::LIST_BYTES, stream, a);
-    else
-      BURST_LAUNCH((burst_bwd_dkv_kernel<true, 2>), dim3((unsigned)nb), dim3(128),
-                   DkvShape<2>::LDS_BYTES + DkvShape<2>::LIST_BYTES, stream, a);
-  } else {
-    BURST_LAUNCH((burst_bwd_dkv_kernel<false, 4>), dim3((unsigned)nb), dim3(256), DkvShape<4>::LDS_BYTES, stream, a);
   }
-  return launch_status();
+  if (a.parts.splits > 1) {
+    const int st = listed ? launch_shape<true, 4, true>(a, nb, stream) : launch_shape<false, 4, true>(a, nb, stream);
+    return st != BURST_OK ? st : launch_merge_dkv<128, DkvShape<4>::BC, DKV_BR, false>(a, stream);
+  }
+  if (!listed) return launch_shape<false, 4, false>(a, nb, stream);
+  return key_waves == 4 ? launch_shape<true, 4, false>(a, nb, stream) : launch_shape<true, 2, false>(a, nb, stream);
 }
 
 }  // namespace burst

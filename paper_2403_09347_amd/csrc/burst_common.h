@@ -80,6 +80,7 @@ struct Chunk {
   long long ks_b, ks_h, ks_r;        // element strides of K and V: batch, head, row
   int Nc, bpitch;
   int first_block;                   // dK/dV kernels: workgroups of the chunks before this one
+  int first_row;                     // split dK/dV walks: keys (of all heads) of the chunks before this one
   // element offset of row 0 of key/value head `kvhead`, which counts batch x heads
   __host__ __device__ size_t kv_base(int kvhead, int kv_heads) const {
     const int b = kvhead / kv_heads;
@@ -109,7 +110,40 @@ struct BwdIo {
   int acc_dq, acc_dkv;               // add to what the gradient buffers hold
   int half;                          // dQ, dK, dV are bf16 tensors (the inputs' type) instead of fp32; nothing accumulates then
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
+  float* kv_part; int kv_splits, kv_tiles;   // kv_splits > 1: see RowParts
 };
+
+// How a dK/dV launch deals out its work.  A workgroup's walk are the query tiles its keys are visible to, of all heads of
+// the group: very unequal under a causal mask, and few workgroups where there are few keys.  splits > 1: the
+// walk of a block of keys is cut into parts of at most about `tiles` tiles, each a workgroup of its own that leaves fp32
+// partial dK, dV in `part` ([part][dK, dV][keys of all chunks and heads][d]); another launch adds them in a fixed order.
+// Blocks with one part write their gradients themselves.
+struct RowParts {
+  float* part;
+  int splits, tiles;                 // most parts of a block; tiles of a part
+  int rows;                          // keys of all chunks and heads
+  __host__ __device__ int of(int walk) const {
+    const int n = (walk + tiles - 1) / tiles;
+    return n < 1 ? 1 : n < splits ? n : splits;
+  }
+};
+// The query tiles (BR rows) of one head that see a key of the block [key0, key0 + BC) of a chunk: [lo, hi).
+struct RowRange { int lo, hi; };
+__host__ __device__ inline RowRange row_range(int Nq, int causal, long long window, long long q_off, long long k_off, int Nc,
+                                              int key0, int BC, int BR) {
+  RowRange r = {0, (Nq + BR - 1) / BR};
+  if (causal) {                      // rows before the first key see nothing
+    const long long first = k_off + key0 - q_off;
+    if (first > 0) r.lo = first / BR < r.hi ? (int)(first / BR) : r.hi;
+  }
+  if (window > 0) {                  // rows too far behind the last key neither
+    const long long last = k_off + (key0 + BC < Nc ? key0 + BC : Nc) - 1 + window - 1 - q_off;
+    if (last < 0) r.hi = 0;
+    else if (last / BR + 1 < r.hi) r.hi = (int)(last / BR) + 1;
+  }
+  if (r.hi < r.lo) r.hi = r.lo;
+  return r;
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -187,14 +221,33 @@ __device__ __forceinline__ int chunk_at(int bid, const Chunk* ch, int n, int per
 // d = 80, 24 x 2500 (480) 239 / 210; d = 64, 8 x 4500 (288) 297 / 298.
 inline int mirrored(long long blocks, int causal) { return causal && blocks > 256 && blocks <= 512; }
 inline long long grid_blocks(long long heads, long long blocks) { return (heads * blocks + 7) / 8 * 8; }
+// Workgroup id of a split dK/dV launch -> (head, block of keys, part).  An XCD gets whole (head, part) columns, longest
+// block first; which part a column holds turns with the block, so that the XCDs with the high columns are not idle where
+// blocks have few parts.  False: nothing to do.
+__device__ __forceinline__ bool locate_part(int bid, int heads, int blocks, int splits, int& head, int& blk, int& part) {
+  const int cols = heads * splits, per = (cols + 7) >> 3, at = bid >> 3;
+  blk = at / per;
+  const int col = (bid & 7) * per + at - blk * per;
+  if (col >= cols || blk >= blocks) return false;
+  head = col / splits;
+  part = (col - head * splits + blk) % splits;
+  return true;
+}
+inline long long part_grid(long long heads, long long blocks, int splits) { return (heads * splits + 7) / 8 * 8 * blocks; }
 // Lays the chunks' workgroups (`block` keys each) out; returns their number, `per` as chunk_at wants it.
-inline long long chunk_grid(Chunk* ch, int n, long long heads, int block, int& per) {
-  long long nb = 0;
-  per = n > 0 ? (int)grid_blocks(heads, (ch[0].Nc + block - 1) / block) : 0;
+inline long long chunk_grid(Chunk* ch, int n, long long heads, int block, int& per, int splits = 1) {
+  auto count = [&](int i) {
+    const long long blocks = (ch[i].Nc + block - 1) / block;
+    return splits > 1 ? part_grid(heads, blocks, splits) : grid_blocks(heads, blocks);
+  };
+  long long nb = 0, rows = 0;
+  per = n > 0 ? (int)count(0) : 0;
   for (int i = 0; i < n; i++) {
-    const long long here = grid_blocks(heads, (ch[i].Nc + block - 1) / block);
+    const long long here = count(i);
     if (here != per) per = 0;
     ch[i].first_block = (int)nb;
+    ch[i].first_row = (int)rows;                   // (used by split launches only, which are small)
+    rows += heads * ch[i].Nc;
     nb += here;
     if (nb > 0x7fffffffLL) break;                  // (the launchers refuse it)
   }

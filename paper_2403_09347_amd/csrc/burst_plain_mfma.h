@@ -81,6 +81,7 @@ struct BwdArgsLite {
   int blocks_per_head, splits, mirror;
   int d, n;
   int per;                                       // dK/dV: workgroups of every chunk (chunk_at)
+  RowParts parts;                                // dK/dV
   Layout lay;
   Chunk ch[kMaxChunks];
 };
@@ -804,7 +805,8 @@ constexpr int SK_BR = 32;                         // query rows per tile
 constexpr int SK_TILE = SK_BR * S_ROWB;
 constexpr int SK_STAT = 4 * SK_TILE;              // per buffer: 32 x (-lse, see s_units), 32 x D
 
-template <bool SPARSE>
+// PARTS: the walks are cut (RowParts), in an instantiation of its own: as a branch of the ordinary one it cost short walks 1 to 2 %.
+template <bool SPARSE, bool PARTS>
 __global__ void __launch_bounds__(64 * SK_WAVES, SK_WAVES == 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
 burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   __shared__ __attribute__((aligned(16))) char smem[4 * SK_TILE + 2 * 64 * 4];   // Q[2], dO[2], statistics[2]
@@ -813,8 +815,13 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   const int d = S_PAD ? a.d : S_D;
   // the workgroups of all chunks, chunk after chunk
   const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
-  int kvhead, kblk;
-  if (!locate_block((int)blockIdx.x - C.first_block, a.H, (C.Nc + SK_BC - 1) / SK_BC, kvhead, kblk, a.mirror)) return;   // a.H counts key/value heads here
+  int kvhead, kblk, part = 0;                      // a.H counts key/value heads here
+  const int bid = (int)blockIdx.x - C.first_block, blocks = (C.Nc + SK_BC - 1) / SK_BC;
+  if constexpr (PARTS) {
+    if (!locate_part(bid, a.H, blocks, a.parts.splits, kvhead, kblk, part)) return;
+  } else {
+    if (!locate_block(bid, a.H, blocks, kvhead, kblk, a.mirror)) return;
+  }
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
   const int key_wg = kblk * SK_BC, key0 = key_wg + w * 32;
@@ -822,19 +829,16 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   const bf16* Vh = (const bf16*)C.V + C.kv_base(kvhead, a.lay.kv_heads);
   const unsigned qpitch = (unsigned)a.lay.qs_r * 2u;             // bytes between query rows
 
-  // query tiles of one head to visit (causal: rows before the first key see nothing; window:
-  // rows too far behind the last key neither), then the same range for every head of the group
-  int t_end = (a.Nq + SK_BR - 1) / SK_BR, t_begin = 0;
-  if (a.causal) {
-    long long first_row = k_off + key_wg - a.q_off;
-    if (first_row > 0) t_begin = (int)min((long long)t_end, first_row / SK_BR);
+  // query tiles of one head to visit, then the same range for every head of the group
+  const RowRange range = row_range(a.Nq, a.causal, a.window, a.q_off, k_off, Nc, key_wg, SK_BC, SK_BR);
+  const int t_begin = range.lo, per_head = range.hi - range.lo;
+  int nwalk = per_head * a.group, first = 0, parts = 1;   // this workgroup's tiles begin at position `first` of the walk
+  if constexpr (PARTS) {
+    parts = a.parts.of(nwalk);
+    if (part >= parts) return;
+    first = (int)((long long)nwalk * part / parts);
+    nwalk = (int)((long long)nwalk * (part + 1) / parts) - first;
   }
-  if (a.window > 0) {
-    long long last_row = k_off + min(key_wg + SK_BC, Nc) - 1 + a.window - 1 - a.q_off;
-    t_end = last_row < 0 ? 0 : (int)min((long long)t_end, last_row / SK_BR + 1);
-  }
-  const int per_head = t_end > t_begin ? t_end - t_begin : 0;
-  int nwalk = per_head * a.group;
   if constexpr (SPARSE) {                          // entries count tiles over all heads of the group
     nwalk = s_build_list(s_list, w, lane, 0, nwalk, [&](int n) {
       const int g = n / (per_head > 0 ? per_head : 1);
@@ -851,7 +855,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   }
   // walk position -> (query head of the group, tile, this wavefront's bit)
   auto locate = [&](int j, int& g, int& t) __attribute__((always_inline)) {
-    int n = j, bits = 0xf;
+    int n = first + j, bits = 0xf;
     if constexpr (SPARSE) {
       const int e = __builtin_amdgcn_readfirstlane(s_list[1 + j]);
       n = e & 0xfffff; bits = e >> 20;
@@ -1022,6 +1026,11 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
+  if (PARTS && parts > 1) {                        // (infinities and NaN: merge_dkv_kernel sees to them)
+    float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + C.first_row + (size_t)kvhead * Nc) * d;
+    store_dkv<S_DB, S_PAD>(dk, dv, to, to + (size_t)a.parts.rows * d, Nc, d, key0, lr, h, a.scale, 0, 0);
+    return;
+  }
   if constexpr (S_PAD) {                           // keys with an infinity or NaN, and their neighbours (see burst_rows.h)
     unsigned most = 0;
 #pragma unroll
@@ -1046,8 +1055,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       return;
     }
   }
-  const size_t first = (size_t)kvhead * Nc * d * (a.half ? 2 : 4);
-  store_dkv<S_DB, S_PAD>(dk, dv, (char*)C.dK + first, (char*)C.dV + first, Nc, d, key0, lr, h, a.scale, a.half, a.acc_dkv);
+  const size_t at = (size_t)kvhead * Nc * d * (a.half ? 2 : 4);
+  store_dkv<S_DB, S_PAD>(dk, dv, (char*)C.dK + at, (char*)C.dV + at, Nc, d, key0, lr, h, a.scale, a.half, a.acc_dkv);
 }
 
 // ------------------------------------------------------------------------------- launchers
@@ -1117,15 +1126,22 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
                       grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SQ_BC - 1) / SQ_BC, 256, stream);
 }
 
+// Keys of a dK/dV workgroup, for the host's rule of splitting (two workgroups share a CU in every build).
+int dkv_keys() { return SK_BC; }
+
 int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
-  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per);
-  a.mirror = n == 1 && mirrored(nb, a.causal);
+  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per, io.kv_splits);
+  a.parts = row_parts(io, ch, n, a.H);
+  if (a.parts.splits > 1 && ch[0].bmask != nullptr) return BURST_ERR_SHAPE;
+  a.mirror = n == 1 && a.parts.splits == 1 && mirrored(nb, a.causal);
   static DeviceOnce done;
-  return launch_plain(burst_bwd_dkv_d64_kernel<false>, burst_bwd_dkv_d64_kernel<true>, done, a, nb,
-                      (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
+  const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true> : burst_bwd_dkv_d64_kernel<false, false>,
+                              burst_bwd_dkv_d64_kernel<true, false>, done, a, nb,
+                              (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
+  return st != BURST_OK || a.parts.splits == 1 ? st : launch_merge_dkv<S_D, SK_BC, SK_BR, S_PAD>(a, stream);
 }
 
 }  // namespace BURST_SMALL_NS
