@@ -423,7 +423,7 @@ constexpr DkvParts kWhole = {1, 1, 0};
 DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
   if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return kWhole;
   const Kernels f = dkv_kernels(&w[0].p, w[0].k);
-  if (f.plain == nullptr && !f.hand) return kWhole;
+  if ((f.plain == nullptr && !f.hand) || f.plain == &kD128p) return kWhole;   // (the latter runs only when its family is forced)
   const KParams& k = w[0].k;
   const int bc = f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.plain != nullptr ? 32 : 64;
   const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;
