@@ -27,6 +27,7 @@
 // holds what its own 64 keys need and nothing else, which the 128-key shape cannot offer (a tile
 // that half of its keys need costs the full time).  Two workgroups share the CU's LDS, so the
 // tile ring has two slots instead of three and a tile is fetched one step ahead instead of two.
+#include <algorithm>
 #include "burst_bwd_common.h"
 
 namespace burst {
@@ -66,6 +67,7 @@ struct DkvArgs {
   Layout lay;            // strides of Q and dO
   Chunk ch[kMaxChunks];
   RowParts parts;
+  int items, turn;       // CHAIN: workgroups that the launch stands for; the order in which they are taken (see next_item)
 };
 
 // SPARSE: the call carries block flags (paper Sec. 2.6) or several query heads share a key/value
@@ -77,7 +79,11 @@ struct DkvArgs {
 // whose bit is clear hides the whole tile in the masking path.  Entries past the end name a tile
 // beyond the slice: its Q, dO and statistics read as zeros and contribute nothing.
 // PARTS: the walks are cut (RowParts; calls without flags only).
-template <bool SPARSE, int NW, bool PARTS>
+// CHAIN: 256 workgroups, one per CU, compute the work of a.items ones each, every 256th (calls without flags or groups).
+// While a block's last two tiles are computed, the K and V rows of the workgroup's next block are fetched into the
+// tile slots that become free (they look like two more tiles: rows of Q and of K must lie the same distance
+// apart), and the first tiles of the next block are requested before the results of this one are stored.
+template <bool SPARSE, int NW, bool PARTS, bool CHAIN>
 __global__ void __launch_bounds__(64 * NW, 1)
 burst_bwd_dkv_kernel(DkvArgs a) {
   using Shape = DkvShape<NW>;
@@ -88,31 +94,81 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   // the workgroups of all chunks, chunk after chunk
-  const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
-  int head, kblk, part = 0;
-  const int bid = (int)blockIdx.x - C.first_block, blocks = (C.Nc + DKV_BC - 1) / DKV_BC;
-  if constexpr (PARTS) {
-    if (!locate_part(bid, a.H, blocks, a.parts.splits, head, kblk, part)) return;
+  int chunk, head, kblk, part = 0;
+  RowRange range;
+  // CHAIN: the next block of keys of this workgroup that some row sees; those that none sees, before it, become zero.
+  // a.turn = n > 1: the workgroups of an XCD begin at n places of their list (whole chunks apart, so that they share the
+  // query tiles of one head), and hidden chunks, which are nothing but stores, are spread over the launch.  0: every
+  // second round is dealt in reverse.
+  int round = 0;
+  auto next_item = [&](int& c, int& hd, int& kb, RowRange& r) __attribute__((always_inline)) {
+    const int rounds = (a.items + 255) >> 8;
+    const int rot = a.turn > 1 ? (int)(blockIdx.x >> 3) * a.turn / 32 * (rounds / a.turn) : 0;
+    while (round < rounds) {
+      int at = round + rot;
+      if (at >= rounds) at -= rounds;
+      const int id = 256 * at + (a.turn == 0 && (at & 1) ? (int)(blockIdx.x ^ 248) : (int)blockIdx.x);
+      round++;
+      if (id >= a.items) continue;
+      c = chunk_at(id, a.ch, a.n, a.per);
+      const Chunk& X = a.ch[c];
+      if (!locate_block(id - X.first_block, a.H, (X.Nc + DKV_BC - 1) / DKV_BC, hd, kb)) continue;
+      r = row_range(a.Nq, a.causal, a.window, a.q_off, X.k_off, X.Nc, kb * DKV_BC, DKV_BC, DKV_BR);
+      if (r.lo + 1 == r.hi) r.hi++;                // (two tiles at least, for K and V behind them; no row past the range sees the keys)
+      if (r.hi > r.lo) {
+        c = __builtin_amdgcn_readfirstlane(c); hd = __builtin_amdgcn_readfirstlane(hd); kb = __builtin_amdgcn_readfirstlane(kb);
+        r.lo = __builtin_amdgcn_readfirstlane(r.lo); r.hi = __builtin_amdgcn_readfirstlane(r.hi);
+        return true;
+      }
+      if (!a.acc_dkv) {                            // rows of keys are contiguous in the gradients
+        const size_t from = ((size_t)hd * X.Nc + (size_t)kb * DKV_BC) * (a.half ? 256 : 512);
+        const unsigned bytes = (unsigned)min(DKV_BC, X.Nc - kb * DKV_BC) * (a.half ? 256u : 512u);
+        const __amdgpu_buffer_rsrc_t k0 = make_rsrc((const char*)X.dK + from, bytes), v0 = make_rsrc((const char*)X.dV + from, bytes);
+        typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+        const u32x4 z = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 16; i++) {             // (past the end: not stored)
+          __builtin_amdgcn_raw_buffer_store_b128(z, k0, tid * 16 + i * 4096, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(z, v0, tid * 16 + i * 4096, 0, 0);
+        }
+      }
+    }
+    return false;
+  };
+  if constexpr (CHAIN) {
+    if (!next_item(chunk, head, kblk, range)) return;
   } else {
-    if (!locate_block(bid, a.H, blocks, head, kblk)) return;
+    chunk = chunk_at((int)blockIdx.x, a.ch, a.n, a.per);
+    const int bid = (int)blockIdx.x - a.ch[chunk].first_block, blocks = (a.ch[chunk].Nc + DKV_BC - 1) / DKV_BC;
+    if constexpr (PARTS) {
+      if (!locate_part(bid, a.H, blocks, a.parts.splits, head, kblk, part)) return;
+    } else {
+      if (!locate_block(bid, a.H, blocks, head, kblk)) return;
+    }
   }
-  const int Nc = C.Nc;
-  const long long k_off = C.k_off;
-  const int key_wg = kblk * DKV_BC;
-  const int key0 = key_wg + w * 32;                // first key of this wavefront
   const int group = SPARSE ? a.group : 1;          // query heads that share this key/value head
   const int q_rows = group * a.Nq;                 // rows of the group's Q / dO / lse / D
-  const bf16* Qh = a.Q + a.lay.q_base(head * group);    // first query head of the group
-  const bf16* Gh = a.dO + a.lay.q_base(head * group);
-  const bf16* Kh = (const bf16*)C.K + C.kv_base(head, a.lay.kv_heads);
-  const bf16* Vh = (const bf16*)C.V + C.kv_base(head, a.lay.kv_heads);
   const unsigned qpitch = (unsigned)a.lay.qs_r * 2u;             // bytes between query rows
   const unsigned qtile = qpitch * DKV_BR;                        // ... between query tiles
-  const float* lseh = a.lse + (size_t)head * q_rows;
-  const float* Dh = a.D + (size_t)head * q_rows;
+
+  // (a.ch[chunk] throughout: through a pointer that changes the compiler copies the arguments to scratch memory)
+  int Nc = a.ch[chunk].Nc, key_wg = kblk * DKV_BC, key0 = key_wg + w * 32;   // key0: first key of this wavefront
+  long long k_off = a.ch[chunk].k_off;
+  const bf16 *Qh, *Gh;                             // first query head of the group
+  const float *lseh, *Dh;
+  auto of_head = [&]() __attribute__((always_inline)) {
+    Qh = a.Q + a.lay.q_base(head * group);
+    Gh = a.dO + a.lay.q_base(head * group);
+    lseh = a.lse + (size_t)head * q_rows;
+    Dh = a.D + (size_t)head * q_rows;
+  };
+  of_head();
+  auto keys_rsrc = [&](const Chunk& X, int hd, bool v) __attribute__((always_inline)) {   // keys past Nc: outside
+    return make_rsrc((const bf16*)(v ? X.V : X.K) + X.kv_base(hd, a.lay.kv_heads), (unsigned)(X.Nc - 1) * (unsigned)X.ks_r * 2u + 256u);
+  };
 
   // query tiles of a head to visit; of the walk over all of them, this workgroup's part
-  const RowRange range = row_range(a.Nq, a.causal, a.window, a.q_off, k_off, Nc, key_wg, DKV_BC, DKV_BR);
+  if constexpr (!CHAIN) range = row_range(a.Nq, a.causal, a.window, a.q_off, k_off, Nc, key_wg, DKV_BC, DKV_BR);
   const int ntiles_all = range.hi;
   int t_begin = range.lo, first = 0, nwalk = ntiles_all - t_begin, parts = 1;   // (tiles to walk)
   if constexpr (PARTS) {
@@ -133,8 +189,8 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   // With a list they are requested before it is built, so that the two latencies overlap.
   bf16x8 kf[8], vf[8];
   auto load_kv = [&]() __attribute__((always_inline)) {
-    const unsigned kpitch = (unsigned)C.ks_r * 2u, bytes = (unsigned)(Nc - 1) * kpitch + 256u;
-    const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, bytes), vrs = make_rsrc(Vh, bytes);
+    const unsigned kpitch = (unsigned)a.ch[chunk].ks_r * 2u;
+    const __amdgpu_buffer_rsrc_t krs = keys_rsrc(a.ch[chunk], head, false), vrs = keys_rsrc(a.ch[chunk], head, true);
     const unsigned off = (unsigned)(key0 + lr) * kpitch + h * 16u;
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) {
@@ -155,10 +211,10 @@ burst_bwd_dkv_kernel(DkvArgs a) {
           const int t = base + lane;
           int bits = 0;
           if (t < ntiles_all) {
-            if (C.bmask == nullptr) {
+            if (a.ch[chunk].bmask == nullptr) {
               bits = (1 << NW) - 1;
             } else {
-              const uint8_t* mrow = C.bmask + (size_t)(head * group + g) * C.bhstride + (size_t)((t * DKV_BR) / a.bsize) * C.bpitch;
+              const uint8_t* mrow = a.ch[chunk].bmask + (size_t)(head * group + g) * a.ch[chunk].bhstride + (size_t)((t * DKV_BR) / a.bsize) * a.ch[chunk].bpitch;
 #pragma unroll
               for (int ww = 0; ww < NW; ww++) {
                 const int k0 = key_wg + ww * 32;
@@ -222,9 +278,9 @@ burst_bwd_dkv_kernel(DkvArgs a) {
       int row = 4 * LPW * w + 4 * il + (lane >> 4);
       goff[il] = (int)(row * qpitch + (((lane & 15) ^ row_code(row)) << 4));
     }
-    // `e`: an entry (see entry_at)
-    auto dma_tile = [&](__amdgpu_buffer_rsrc_t rs, unsigned lds_tile, int il, int e) __attribute__((always_inline)) {
-      dma_b128_to_lds(rs, lds_tile + (unsigned)(wu * LPW + il) * 1024u, (int)((unsigned)tile_of(e) * qtile) + goff[il]);
+    // base: byte offset of the tile's first row
+    auto dma_tile = [&](__amdgpu_buffer_rsrc_t rs, unsigned lds_tile, int il, unsigned base) __attribute__((always_inline)) {
+      dma_b128_to_lds(rs, lds_tile + (unsigned)(wu * LPW + il) * 1024u, (int)base + goff[il]);
     };
     // Per-row statistics of a tile travel like the tiles: wavefront 0 DMAs the 64 lse values,
     // wavefront 1 the 64 D values (rows past Nq read as 0; their Q and dO rows are 0 too, so they
@@ -269,20 +325,51 @@ burst_bwd_dkv_kernel(DkvArgs a) {
       }
     };
 
+    // CHAIN: the next block of keys.  Its K and V rows follow the tiles of the walk as two more.
+    int c_next = 0, head_next = 0, blk_next = 0;
+    RowRange range_next = {0, 0};
+    bool more = false;
+    const bf16 *K_next = nullptr, *V_next = nullptr;
+    unsigned bytes_next = 0;
+    // What is fetched at walk position m (entry e): Q or K rows, dO or V rows, the offset of the first one.
+    auto first_rsrc = [&](int m, int e) __attribute__((always_inline)) {
+      if constexpr (CHAIN) return make_rsrc(m < nwalk ? Qh : K_next, m < nwalk ? qbytes : bytes_next);
+      else return q_rsrc(e);
+    };
+    auto second_rsrc = [&](int m, int e) __attribute__((always_inline)) {
+      if constexpr (CHAIN) return make_rsrc(m < nwalk ? Gh : V_next, m < nwalk ? qbytes : bytes_next);
+      else return g_rsrc(e);
+    };
+    auto first_row_at = [&](int m, int e) __attribute__((always_inline)) {
+      if constexpr (CHAIN) return (unsigned)(m < nwalk ? t_begin + m : 2 * blk_next + m - nwalk) * qtile;
+      else return (unsigned)tile_of(e) * qtile;
+    };
     // ---- prologue: tiles t_begin, t_begin + 1 into tile slots 0, 1 (two slots: the first tile
     // alone); the statistics of tiles t_begin .. t_begin + 2 into statistic slots 0 .. 2, the
-    // first two scaled right away
+    // first two scaled when they are there
+    auto start_tiles = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < DKV_SLOTS - 1; t++) {
-      const int src = entry_at(t);
+      for (int t = 0; t < DKV_SLOTS - 1; t++) {
+        const int e = entry_at(t);
+        const unsigned base = (unsigned)tile_of(e) * qtile;
 #pragma unroll
-      for (int il = 0; il < LPW; il++) {
-        dma_tile(q_rsrc(src), lds0 + DKV_LDS_Q + t * DKV_TILE_BYTES, il, src);
-        dma_tile(g_rsrc(src), lds0 + DKV_LDS_G + t * DKV_TILE_BYTES, il, src);
+        for (int il = 0; il < LPW; il++) {
+          dma_tile(q_rsrc(e), lds0 + DKV_LDS_Q + t * DKV_TILE_BYTES, il, base);
+          dma_tile(g_rsrc(e), lds0 + DKV_LDS_G + t * DKV_TILE_BYTES, il, base);
+        }
       }
-    }
 #pragma unroll
-    for (int t = 0; t < 3; t++) dma_rowstat(entry_at(t), t);
+      for (int t = 0; t < 3; t++) dma_rowstat(entry_at(t), t);
+    };
+    start_tiles();
+    for (;;) {                                     // (CHAIN: the blocks of this workgroup; else once)
+    if constexpr (CHAIN) {
+      more = next_item(c_next, head_next, blk_next, range_next);
+      const size_t at = a.ch[c_next].kv_base(head_next, a.lay.kv_heads);
+      K_next = (const bf16*)a.ch[c_next].K + at;
+      V_next = (const bf16*)a.ch[c_next].V + at;
+      bytes_next = more ? (unsigned)(a.ch[c_next].Nc - 1) * qpitch + 256u : 0u;
+    }
     __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0), lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     scale_rowstat(0);
@@ -315,20 +402,27 @@ burst_bwd_dkv_kernel(DkvArgs a) {
 
     // lgkmcnt(0).  With a scalar load possibly still on its way at the loop's entry the compiler waits, in every step, for
     // all six operand reads before the first MFMA instead of for one (1 % of long walks, 2 % of short ones).
+    int ahead[4];                                    // SPARSE: the entries of this tile and the next three
+    if constexpr (SPARSE) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) ahead[j] = entry_at(j);
+    }
     __builtin_amdgcn_s_waitcnt(0xC07F);
     int slot = 0;
     for (int n = 0; n < nwalk; n++) {                  // n = walk position; statistic slot n & 3 holds its tile
       // this tile, the entries of the tile whose rows are fetched now and of the one whose statistics are
       int t = t_begin + n, t2 = t + DKV_SLOTS - 1, t3 = t + 3;
       bool mine = true;                                // SPARSE: this wavefront's keys are visible to the tile
+      int entry4 = 0;
       if constexpr (SPARSE) {
-        const int e = __builtin_amdgcn_readfirstlane(list[1 + n]);
-        t = e & 0xffff;
-        mine = ((e >> (16 + wu)) & 1) != 0;
-        t2 = entry_at(n + DKV_SLOTS - 1);
-        t3 = entry_at(n + 3);
+        entry4 = list[1 + n + 4];                    // (used at the end of the step)
+        t = ahead[0] & 0xffff;
+        mine = ((ahead[0] >> (16 + wu)) & 1) != 0;
+        t2 = ahead[DKV_SLOTS - 1];
+        t3 = ahead[3];
       }
-      const __amdgpu_buffer_rsrc_t qrs = q_rsrc(t2), grs = g_rsrc(t2);
+      const __amdgpu_buffer_rsrc_t qrs = first_rsrc(n + DKV_SLOTS - 1, t2), grs = second_rsrc(n + DKV_SLOTS - 1, t2);
+      const unsigned base2 = first_row_at(n + DKV_SLOTS - 1, t2);
       const int slot1 = (slot == DKV_SLOTS - 1) ? 0 : slot + 1;
       // where the tile fetched in this step goes: the slot after the next tile's, or (two slots) the next tile's
       const int slot2 = DKV_SLOTS == 2 ? slot1 : (slot1 == DKV_SLOTS - 1) ? 0 : slot1 + 1;
@@ -420,8 +514,8 @@ burst_bwd_dkv_kernel(DkvArgs a) {
             // statistics of tile t + 3 are requested here and awaited at the end of the step
             if (i == 0) dma_rowstat(t3, (n + 3) & 3);
             if (i < 2 * LPW) {
-              if (i & 1) dma_tile(grs, lds0 + DKV_LDS_G + slot2 * DKV_TILE_BYTES, i >> 1, t2);
-              else dma_tile(qrs, lds0 + DKV_LDS_Q + slot2 * DKV_TILE_BYTES, i >> 1, t2);
+              if (i & 1) dma_tile(grs, lds0 + DKV_LDS_G + slot2 * DKV_TILE_BYTES, i >> 1, base2);
+              else dma_tile(qrs, lds0 + DKV_LDS_Q + slot2 * DKV_TILE_BYTES, i >> 1, base2);
             }
           }
           if (isg) dp[rb] = mfma32(fq[i % RING], vf[ks], dp[rb]);
@@ -448,8 +542,8 @@ burst_bwd_dkv_kernel(DkvArgs a) {
           if (DKV_SLOTS == 3 && i == 16) dma_rowstat(t3, (n + 3) & 3);
           if (DKV_SLOTS == 3 && i > 16 && (i & 1)) {
             const int j = (i - 17) >> 1;                  // 0..7: Q rows, then dO rows
-            if (j < 4) dma_tile(qrs, lds0 + DKV_LDS_Q + slot2 * DKV_TILE_BYTES, j, t2);
-            else dma_tile(grs, lds0 + DKV_LDS_G + slot2 * DKV_TILE_BYTES, j - 4, t2);
+            if (j < 4) dma_tile(qrs, lds0 + DKV_LDS_Q + slot2 * DKV_TILE_BYTES, j, base2);
+            else dma_tile(grs, lds0 + DKV_LDS_G + slot2 * DKV_TILE_BYTES, j - 4, base2);
           }
           const bf16x8 bt = cat4(tq[i % TRING][0], tq[i % TRING][1]);
           if (isk) mfma32_acc(dk[db], dsf[rb][u], bt);
@@ -462,6 +556,10 @@ burst_bwd_dkv_kernel(DkvArgs a) {
       // loads, issued most of a step ago, must have landed.  The LDS stores of the rewritten
       // statistics must be done.
       slot = slot1;
+      if constexpr (SPARSE) {
+        ahead[0] = ahead[1]; ahead[1] = ahead[2]; ahead[2] = ahead[3];
+        ahead[3] = __builtin_amdgcn_readfirstlane(entry4);
+      }
       if constexpr (DKV_SLOTS == 3) __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0)
       else __builtin_amdgcn_s_waitcnt(0x0070);                                   // vmcnt(0), lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
@@ -472,37 +570,117 @@ burst_bwd_dkv_kernel(DkvArgs a) {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
                  : "+a"(dk[0]), "+a"(dk[1]), "+a"(dk[2]), "+a"(dk[3]),
                    "+a"(dv[0]), "+a"(dv[1]), "+a"(dv[2]), "+a"(dv[3]));
+    if constexpr (!CHAIN) break;
+    else {
+      const int P_chunk = chunk, P_Nc = Nc, P_key0 = key0;   // the block that is done
+      const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
+      if (more) {
+        // its last tile lay in the slot before `slot`; `slot` and the one after it hold the next block's keys
+        __builtin_amdgcn_s_barrier();              // everyone's K and V rows have landed
+        const int from = w < 2 ? slot : (slot == DKV_SLOTS - 1) ? 0 : slot + 1;
+        const char* const kl = smem + DKV_LDS_Q + from * DKV_TILE_BYTES + (w & 1) * 32 * 256;
+        const char* const vl = smem + DKV_LDS_G + from * DKV_TILE_BYTES + (w & 1) * 32 * 256;
+#pragma unroll
+        for (int ks = 0; ks < 8; ks++) {
+          kf[ks] = lds_read_b128(kl, abase ^ (ks << 5));
+          vf[ks] = lds_read_b128(vl, abase ^ (ks << 5));
+        }
+        chunk = c_next; head = head_next; kblk = blk_next; range = range_next;
+        Nc = a.ch[chunk].Nc; key_wg = kblk * DKV_BC; key0 = key_wg + w * 32; k_off = a.ch[chunk].k_off;
+        t_begin = range.lo; nwalk = range.hi - range.lo;
+        of_head();
+        __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();              // ... and have been read: the slots are free
+        start_tiles();
+      }
+      store_dkv<4, false>(dk, dv, (char*)a.ch[P_chunk].dK + at, (char*)a.ch[P_chunk].dV + at, P_Nc, 128, P_key0, lr, h, a.scale, a.half, a.acc_dkv);
+      if (!more) return;
+#pragma unroll
+      for (int db = 0; db < 4; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
+    }
+    }
   }
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
   if constexpr (PARTS) {
     void *dk_at, *dv_at;
     if (parts > 1) {
-      float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + C.first_row + (size_t)head * Nc) * 128;
+      float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + a.ch[chunk].first_row + (size_t)head * Nc) * 128;
       dk_at = to; dv_at = to + (size_t)a.parts.rows * 128;
     } else {
       const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
-      dk_at = (char*)C.dK + at; dv_at = (char*)C.dV + at;
+      dk_at = (char*)a.ch[chunk].dK + at; dv_at = (char*)a.ch[chunk].dV + at;
     }
     store_dkv<4, false>(dk, dv, dk_at, dv_at, Nc, 128, key0, lr, h, a.scale, parts > 1 ? 0 : a.half, parts > 1 ? 0 : a.acc_dkv);
-  } else {
+  } else if constexpr (!CHAIN) {
     const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
-    store_dkv<4, false>(dk, dv, (char*)C.dK + at, (char*)C.dV + at, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
+    store_dkv<4, false>(dk, dv, (char*)a.ch[chunk].dK + at, (char*)a.ch[chunk].dV + at, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
   }
 }
 
 // n chunks, all with block flags or none.  key_waves: 4 (128-key workgroups) or 2 (64-key workgroups, calls
 // with block flags only).
-template <bool SPARSE, int NW, bool PARTS>
+template <bool SPARSE, int NW, bool PARTS, bool CHAIN = false>
 static int launch_shape(const DkvArgs& a, long long nb, hipStream_t stream) {
   constexpr unsigned lds = DkvShape<NW>::LDS_BYTES + (SPARSE ? DkvShape<NW>::LIST_BYTES : 0);
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
-    return hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<SPARSE, NW, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void*)burst_bwd_dkv_kernel<SPARSE, NW, PARTS, CHAIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                lds) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
   });
   if (st != BURST_OK) return st;
-  BURST_LAUNCH((burst_bwd_dkv_kernel<SPARSE, NW, PARTS>), dim3((unsigned)nb), dim3(64 * NW), lds, stream, a);
+  BURST_LAUNCH((burst_bwd_dkv_kernel<SPARSE, NW, PARTS, CHAIN>), dim3((unsigned)nb), dim3(64 * NW), lds, stream, a);
   return launch_status();
+}
+// Whether the launch's nb workgroups are computed by 256 (CHAIN), and in which order (a.items, a.turn).
+// The chain saves what a workgroup does before its first tile (arguments, K and V from HBM, first tiles: 5 us) and the gap to
+// the next one (2 us), of 13 us beside 1.8 us a tile, and lets the zeros of hidden chunks be written while others compute.
+// It is not used where
+//  - walks are long (average above 36 tiles): those launches are bound by socket power, and a CU that waits gives its share to
+//    the others (32 heads x 4096 rows, 64 tiles: 3834 us as workgroups, 3855 chained; 32 tiles: 1031 / 1022; 24: 606 / 595; 16:
+//    318 / 302; 8: 107 / 98);
+//  - the 256 shares are unequal: the largest more than 1.08 of the average (causal 32 x 3000 rows, 1.48: 166 / 195 us; chunks
+//    of 2048 on both sides of the diagonal, 1.12: 497 / 510; 1.07: 232 / 219).  One causal chunk is dealt in alternating
+//    direction (a.turn = 0), long blocks with short ones: 32 x 2048 rows 100 / 76 us, 128 x 1024 117 / 92, 64 x 2048 171 / 146.
+// Causal walk of 16 chunks of 512 keys (32 heads) 209 / 188 us; window of 4096 over 8 chunks of 4096, five of them hidden,
+// 710 / 612 (656 with all workgroups beginning at the same chunk).
+static bool chained(DkvArgs& a, long long nb) {
+  constexpr int BC = DkvShape<4>::BC;
+  if (nb <= 256 || nb > 16384 || a.group > 1) return false;
+  a.items = (int)nb;
+  a.turn = a.n == 1 && a.causal ? 0 : a.n > 1 && a.per > 0 && a.per % 256 == 0 ? a.n : 1;
+  const int tiles = (a.Nq + DKV_BR - 1) / DKV_BR;
+  int most_blocks = 0;
+  long long all = 0;
+  for (int c = 0; c < a.n; c++) most_blocks = std::max(most_blocks, (a.ch[c].Nc + BC - 1) / BC);
+  int walk[kMaxChunks][256];                       // tiles of a block
+  if (most_blocks > 256) return false;
+  for (int c = 0; c < a.n; c++) {
+    if (a.ch[c].ks_r != a.lay.qs_r) return false;
+    for (int b = 0; b * BC < a.ch[c].Nc; b++) {
+      const RowRange r = row_range(a.Nq, a.causal, a.window, a.q_off, a.ch[c].k_off, a.ch[c].Nc, b * BC, BC, DKV_BR);
+      walk[c][b] = r.hi - r.lo;
+      all += (long long)walk[c][b] * a.H;
+      // (one tile is walked as two: only where the rows of the second one, past Nq, are zeros that the first one has too)
+      if (walk[c][b] == 1 && (r.hi != tiles || a.Nq % DKV_BR == 0)) return false;
+    }
+  }
+  if (all > 36 * nb) return false;
+  int share[256] = {};                             // in fifths of a tile: 5 a tile, 15 a block, 6 a hidden block (turns change the order only)
+  for (int c = 0; c < a.n; c++) {
+    const int blocks = (a.ch[c].Nc + BC - 1) / BC, total = a.H * blocks, per = (total + 7) / 8;
+    for (int x = 0; x < 8; x++)
+      for (int at = 0, b = x * per % blocks; at < per && x * per + at < total; at++, b = b + 1 == blocks ? 0 : b + 1) {
+        const int id = a.ch[c].first_block + 8 * at + x, round = id >> 8;
+        const int wg = a.turn == 0 && (round & 1) ? (id & 255) ^ 248 : id & 255;
+        share[wg] += walk[c][b] ? 5 * walk[c][b] + 15 : 6;
+      }
+  }
+  long long sum = 0;
+  int most = 0;
+  for (int i = 0; i < 256; i++) { sum += share[i]; most = std::max(most, share[i]); }
+  return 100LL * 256 * most <= 108 * sum;
 }
 int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream, int key_waves) {
   DkvArgs a;
@@ -529,6 +707,7 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
     const int st = listed ? launch_shape<true, 4, true>(a, nb, stream) : launch_shape<false, 4, true>(a, nb, stream);
     return st != BURST_OK ? st : launch_merge_dkv<128, DkvShape<4>::BC, DKV_BR, false>(a, stream);
   }
+  if (!listed && chained(a, nb)) return launch_shape<false, 4, false, true>(a, 256, stream);
   if (!listed) return launch_shape<false, 4, false>(a, nb, stream);
   return key_waves == 4 ? launch_shape<true, 4, false>(a, nb, stream) : launch_shape<true, 2, false>(a, nb, stream);
 }
