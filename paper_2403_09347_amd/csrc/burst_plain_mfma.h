@@ -187,13 +187,16 @@ __device__ __forceinline__ int s_build_list(int* list, int w, int lane, int t_lo
 }
 
 // ------------------------------------------------------------------------------- forward
-constexpr int SF_BR = 128;                        // query rows per workgroup (4 wavefronts x 32)
-constexpr int SF_BC = 64;                         // keys per tile
-constexpr int SF_TILE = SF_BC * S_ROWB;
-
-template <bool SPARSE>
-__global__ void __launch_bounds__(256, 2)
+// NW wavefronts of 32 query rows per workgroup.  Four; two for block flags 64 wide (SPARSE), whose lists of visible tiles
+// then hold what the workgroup's 64 rows see and nothing else, so that no wavefront waits for another's tiles.  Such a
+// workgroup takes 32 keys a tile instead of 64, so that as many wavefronts share a CU's LDS.
+constexpr int sf_keys(int NW) { return NW == 2 ? 32 : 64; }
+template <bool SPARSE, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)     // (second figure: wavefronts per SIMD)
 burst_fwd_d64_kernel(FwdArgsLite a) {
+  constexpr int SF_BR = 32 * NW;                  // query rows per workgroup
+  constexpr int SF_BC = sf_keys(NW), SF_TILE = SF_BC * S_ROWB;   // keys per tile
+  constexpr int KB = SF_BC / 32;                  // 32-key blocks of a tile
   __shared__ __attribute__((aligned(16))) char smem[4 * SF_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
@@ -209,7 +212,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 
   // The chunks' visible tiles (or list entries) form one sequence, walked with the next tile in flight across the
   // chunk boundaries.  splits > 1: this workgroup takes one of that many runs of it, of equal length.
-  constexpr int NL = SF_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
+  constexpr int NL = SF_BC / S_RPL / NW;          // wave-wide loads per wavefront and tile
   auto tiles_of = [&](const Chunk& C, int& lo, int& hi) __attribute__((always_inline)) {   // that some row of the workgroup sees
     lo = 0; hi = (C.Nc + SF_BC - 1) / SF_BC;
     if (a.window > 0) {                            // keys before the window of the first row
@@ -265,7 +268,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
           hi = s_build_list(s_list, w, lane, lo, hi, [&](int t) {
             int bits = 0;
 #pragma unroll
-            for (int ww = 0; ww < 4; ww++) {
+            for (int ww = 0; ww < NW; ww++) {
               const int row0 = qb * SF_BR + ww * 32;
               if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + (t * SF_BC) / a.bsize] != 0) bits |= 1 << ww;
             }
@@ -343,16 +346,16 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
 
   // The scores of a tile, masked, and the row's maximum of them (see s_units).
-  auto scores = [&](const char* kl, int kt, int Nc, long long k_off, f32x16 (&s)[2]) __attribute__((always_inline)) {
+  auto scores = [&](const char* kl, int kt, int Nc, long long k_off, f32x16 (&s)[KB]) __attribute__((always_inline)) {
     // S^T = K Q^T: register r of key block kb = key kt*64 + kb*32 + 8*(r/4) + 4h + r%4
 #pragma unroll
-    for (int kb = 0; kb < 2; kb++)
+    for (int kb = 0; kb < KB; kb++)
 #pragma unroll
       for (int r = 0; r < 16; r++) s[kb][r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++)
 #pragma unroll
-      for (int kb = 0; kb < 2; kb++)
+      for (int kb = 0; kb < KB; kb++)
         s[kb] = mfma32(lds_read_b128(kl, kb * 32 * S_ROWB + kaddr[ks]), qf[ks], s[kb]);
     const long long tile_first_k = k_off + (long long)kt * SF_BC;
     const bool need_mask = (a.causal && tile_first_k + SF_BC - 1 > wave_first_q) ||
@@ -366,7 +369,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       const long long dl = dd - a.window + 1;
       const int lim_lo = a.window > 0 ? (int)(dl < -1 ? -1 : (dl > 64 ? 64 : dl)) : -1;
 #pragma unroll
-      for (int kb = 0; kb < 2; kb++)
+      for (int kb = 0; kb < KB; kb++)
 #pragma unroll
         for (int r = 0; r < 16; r++) {
           const int cpart = kb * 32 + 8 * (r >> 2) + (r & 3);
@@ -375,7 +378,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     }
     float v = s[0][0];
 #pragma unroll
-    for (int kb = 0; kb < 2; kb++)
+    for (int kb = 0; kb < KB; kb++)
 #pragma unroll
       for (int r = 0; r < 16; r++) v = fmaxf(v, s[kb][r]);
     return s_units(max_both_halves(v), a.scale, a.c);
@@ -390,7 +393,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         dma_b128_to_lds(krs, lds0 + SF_TILE + (unsigned)(wu * NL + il) * 1024u, (int)((unsigned)lo * ktile) + goff[il]);
       __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0), lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
-      f32x16 s[2];
+      f32x16 s[KB];
       s_raise(m_st, cm, scores(smem + SF_TILE, lo, f_Nc, f_koff, s), 0.f);
     }
   for (int buf = 0; have; buf ^= 1) {
@@ -406,7 +409,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     if (!mine) continue;                           // block flags hide the tile from this wavefront's rows
     const char* kl = smem + buf * SF_TILE;
     const char* vl = smem + (2 + buf) * SF_TILE;
-    f32x16 s[2];
+    f32x16 s[KB];
     const float mx = scores(kl, kt, Nc, k_off, s);
     if (__builtin_amdgcn_ballot_w64(mx > cm + S_LAZY) != 0) {   // a chunk's first reference, or raised (rare)
       const float alpha = s_raise(m_st, cm, mx, sum_both_halves(lsum));
@@ -417,9 +420,9 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         for (int r = 0; r < 16; r++) o[db][r] *= alpha;
     }
     const float nref = (m_st == BURST_NEG_INF) ? 0.f : S_PAD ? -m_st : -(m_st * kLog2e);
-    bf16x8 pf[4][S_TERMS];                         // P^T fragments per 16-key group
+    bf16x8 pf[2 * KB][S_TERMS];                       // P^T fragments per 16-key group
 #pragma unroll
-    for (int kg = 0; kg < 4; kg++)
+    for (int kg = 0; kg < 2 * KB; kg++)
 #pragma unroll
       for (int t = 0; t < 8; t += 2) {
         const int kb = kg >> 1, r = 8 * (kg & 1) + t;
@@ -435,7 +438,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       }
     // O^T += V^T P^T
 #pragma unroll
-    for (int kg = 0; kg < 4; kg++)
+    for (int kg = 0; kg < 2 * KB; kg++)
 #pragma unroll
       for (int db = 0; db < S_DB; db++) {
         const bf16x4 va = lds_read_tr(vl, kg * 16 * S_ROWB + taddr[db][0]);
@@ -471,7 +474,8 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
         RowState st[kRows];
 #pragma unroll
         for (int r = 0; r < kRows; r++) st[r] = row_state(a.fresh, a.O_acc, a.m, a.l, (size_t)head * a.Nq + rows[r], d, lane);
-        rows_forward<bf16, true>(st, args_again<FwdArgsLite>(), head, rows, lane, tiles_of, first, last);
+        if constexpr (SF_BC == 64) rows_forward<bf16, true>(st, args_again<FwdArgsLite>(), head, rows, lane, tiles_of, first, last);
+        else rows_forward<bf16, true>(st, args_again<FwdArgsLite>(), head, rows, lane, [](const Chunk& C, int& l, int& h) { l = 0; h = (C.Nc + 63) >> 6; }, 0, 0x7fffffff);
 #pragma unroll
         for (int r = 0; r < kRows; r++) {
           if (r >= n) continue;
@@ -544,15 +548,16 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 }
 
 // ------------------------------------------------------------------------------- backward, dQ
-constexpr int SQ_BR = 128;                        // query rows per workgroup
 constexpr int SQ_BC = 32;                         // keys per tile
 constexpr int SQ_TILE = SQ_BC * S_ROWB;
 
 // (d = 64 fits four wavefronts per SIMD; left alone, the compiler takes 136 registers with block flags, which leaves three:
 // 32 heads of 4096 x 4096 rows, 64-wide flags at density 0.5: 164 us instead of 147)
-template <bool SPARSE>
-__global__ void __launch_bounds__(256, S_D == 64 && !S_PAD ? 4 : 2)
+// (NW: as in the forward kernel)
+template <bool SPARSE, int NW>
+__global__ void __launch_bounds__(64 * NW, S_D == 64 && !S_PAD ? 4 : 2)
 burst_bwd_dq_d64_kernel(BwdArgsLite a) {
+  constexpr int SQ_BR = 32 * NW;                  // query rows per workgroup
   __shared__ __attribute__((aligned(16))) char smem[4 * SQ_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
@@ -570,7 +575,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   const unsigned lds0 = lds_addr(smem);
 
   // The chunks' visible tiles (or list entries) form one sequence, as in the forward kernel.
-  constexpr int NL = SQ_BC / S_RPL / 4;           // wave-wide loads per wavefront and tile
+  constexpr int NL = SQ_BC / S_RPL / NW;          // wave-wide loads per wavefront and tile
   auto tiles_of = [&](const Chunk& C, int& lo, int& hi) __attribute__((always_inline)) {   // that some row of the workgroup sees
     lo = 0; hi = (C.Nc + SQ_BC - 1) / SQ_BC;
     if (a.window > 0) {
@@ -612,7 +617,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
           hi = s_build_list(s_list, w, lane, lo, hi, [&](int t) {
             int bits = 0;
 #pragma unroll
-            for (int ww = 0; ww < 4; ww++) {
+            for (int ww = 0; ww < NW; ww++) {
               const int row0 = qb * SQ_BR + ww * 32;
               if (row0 < a.Nq && bm[(size_t)(row0 / a.bsize) * C.bpitch + (t * SQ_BC) / a.bsize] != 0) bits |= 1 << ww;
             }
@@ -1083,6 +1088,16 @@ static int launch_plain(K dense, K sparse, DeviceOnce& once, A& a, long long nb,
   return launch_status();
 }
 
+// Wavefronts of a forward or dQ workgroup: two where the flags are 64 wide (see the forward kernel).  32 heads x 4096 rows x
+// 8192 keys, four / two, us: dQ, d = 128, density 0.1 166 / 134, 0.25 351 / 280, 0.5 496 / 470; d = 64 171 / 149, 270 / 253
+// (0.25, 0.5); forward, d = 64, 141 / 130, 216 / 215.  In the forward at d = 128 the smaller tiles take back what the exact
+// lists give (134 / 132, 274 / 266, 389 / 408): two only while all workgroups are resident at once (8 heads x 1000 rows x
+// 3000 keys 44 / 35).
+static int row_waves(const KParams& p, const Chunk* ch, bool forward) {
+  if (ch[0].bmask == nullptr || p.bsize >= 128) return 4;
+  return !forward || S_D <= 64 || (long long)p.B * p.H * ((p.Nq + 63) / 64) <= 1024 ? 2 : 4;
+}
+
 // n <= kMaxChunks chunks, all of them with block flags or none.
 int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   FwdArgsLite a;
@@ -1094,13 +1109,14 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
-  a.blocks_per_head = (p.Nq + SF_BR - 1) / SF_BR;
+  const int nw = row_waves(p, ch, true);
+  a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
   a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;
   for (int i = 0; i < n; i++) { a.ch[i] = ch[i]; if (ch[i].Nc > longest) longest = ch[i].Nc; }
-  static DeviceOnce done;
-  return launch_plain(burst_fwd_d64_kernel<false>, burst_fwd_d64_kernel<true>, done, a,
-                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SF_BC - 1) / SF_BC, 256, stream);
+  static DeviceOnce done, done2;
+  return launch_plain(burst_fwd_d64_kernel<false, 4>, nw == 2 ? burst_fwd_d64_kernel<true, 2> : burst_fwd_d64_kernel<true, 4>, nw == 2 ? done2 : done, a,
+                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + sf_keys(nw) - 1) / sf_keys(nw), 64 * nw, stream);
 }
 
 static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
@@ -1117,13 +1133,14 @@ static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Ch
 int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
-  a.blocks_per_head = (p.Nq + SQ_BR - 1) / SQ_BR;
+  const int nw = row_waves(p, ch, false);
+  a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
   a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;
   for (int i = 0; i < n; i++) if (ch[i].Nc > longest) longest = ch[i].Nc;
-  static DeviceOnce done;
-  return launch_plain(burst_bwd_dq_d64_kernel<false>, burst_bwd_dq_d64_kernel<true>, done, a,
-                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SQ_BC - 1) / SQ_BC, 256, stream);
+  static DeviceOnce done, done2;
+  return launch_plain(burst_bwd_dq_d64_kernel<false, 4>, nw == 2 ? burst_bwd_dq_d64_kernel<true, 2> : burst_bwd_dq_d64_kernel<true, 4>, nw == 2 ? done2 : done, a,
+                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SQ_BC - 1) / SQ_BC, 64 * nw, stream);
 }
 
 // Keys of a dK/dV workgroup, for the host's rule of splitting (two workgroups share a CU in every build).
