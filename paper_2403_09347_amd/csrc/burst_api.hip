@@ -376,6 +376,35 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
   return BURST_OK;
 }
 
+// Walks of the generic kernels that can be split: fp32, d a multiple of 4, no flags.
+bool generic_splittable(const std::vector<WalkChunk>& w) {
+  if (w[0].p.dtype != BURST_F32 || w[0].p.d % 4 != 0) return false;
+  for (const WalkChunk& x : w) if (x.p.block_mask != nullptr) return false;
+  return true;
+}
+// Into how many workgroups the tiles of a block of 32 rows are dealt: as many as there are CUs for (they run at the fp32
+// matrix rate with one wavefront per SIMD, so that more gain nothing), with a tile for each of their four wavefronts.
+// us a launch with its merge, whole / by the rule, forward and dQ: 256 rows x 1024 keys, one head, d = 64, 32 / 15 and 40 / 16
+// in 8; 4 x 1000 x 3000, d = 64, 82 / 53 and 111 / 63 in 2 (3: 66, 85; 4: 56, 72); 4 x 700 x 1400, d = 128, 70 / 48 and 102 / 68
+// in 2 (3: 57, 79); 8 x 300 x 600 causal, d = 80, 30 / 21 and 38 / 26 in 3 (4: 31, 32); not split: 8 x 700 x 1400 causal 71 and
+// 103 (2: 69, 97; 3: 73, 101), 8 x 1000 x 4000, d = 32, 67 and 82 (2: 72, 84).
+int generic_splits(const std::vector<WalkChunk>& w) {
+  const KParams& k = w[0].k;
+  const long long heads = (long long)k.B * k.H, blocks = (k.Nq + 31) / 32;
+  if (heads * blocks > 128 || !generic_splittable(w)) return 1;
+  long long most = 0;                              // key tiles that a block sees
+  for (long long row0 = 0; row0 < k.Nq; row0 += 32) {
+    long long walk = 0;
+    for (const WalkChunk& x : w) {
+      long long lo = 0, hi = x.c.Nc;
+      if (k.causal) hi = std::min(hi, k.q_off + std::min<long long>(row0 + 32, k.Nq) - x.c.k_off);
+      if (k.window > 0) lo = std::max(lo, k.q_off + row0 - k.window + 1 - x.c.k_off);
+      if (hi > lo) walk += (hi + 31) / 32 - lo / 32;
+    }
+    most = std::max(most, walk);
+  }
+  return (int)std::max<long long>(1, std::min({256 / (heads * blocks), most / 4, 64LL}));
+}
 // Into how many key ranges a walk of the plain kernels is split (1: not at all).  Their workgroups hold
 // 128 rows and two share a CU: 512 fill every place on the chip, and with 256 or fewer two ranges or more have places
 // of their own.  Ranges shorter than 8 tiles would spend their time on the partial states.  Walks of fewer than
@@ -388,7 +417,7 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
 int walk_splits(const std::vector<WalkChunk>& w) {
   if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return 1;
   const Kernels f = fwd_kernels(&w[0].p, w[0].k);
-  if (f.plain == nullptr) return 1;
+  if (f.plain == nullptr) return generic_splits(w);
   const KParams& k = w[0].k;
   const long long blocks = (long long)k.B * k.H * ((k.Nq + 127) / 128);
   long long tiles = 0;                             // of 64 keys, that the last rows see
@@ -418,15 +447,23 @@ int dq_launches(const std::vector<WalkChunk>& w) {
 // 32 over 8 x 2048, d = 64, 354 / 156 in 8 (153 in 6, 167 in 12); 8 over 2 x 1000 332 / 98 in 16 (101 in 12); 8 x 3000, d = 64,
 // 174 / 124 in 5 (123, 124); 32 x 777, d = 96, 123 / 107 in 3 (111, 117); 8 x 8000, d = 64, 511 / 443 in 2 (447 in 3); not
 // cut: 64 x 1024, d = 64, 98 (in 2: 112), 16 x 3000 279 (301), 16 x 4096 403 (440).
-struct DkvParts { int splits, tiles; long long rows; };
-constexpr DkvParts kWhole = {1, 1, 0};
+struct DkvParts { int splits, most, tiles; long long rows; };
+constexpr DkvParts kWhole = {1, 1, 1, 0};
+// Workgroups per block for at most `most` parts: whole (head, part) columns go to the 8 XCDs, so their number should be a
+// multiple of 8 (workgroups without a part end at once).
+int part_columns(long long heads, long long most) {
+  for (long long s = most; s < most + 8; s++) if (heads * s % 8 == 0) return (int)s;
+  return (int)most;
+}
 DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
   if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return kWhole;
   const Kernels f = dkv_kernels(&w[0].p, w[0].k);
-  if ((f.plain == nullptr && !f.hand) || f.plain == &kD128p) return kWhole;   // (the latter runs only when its family is forced)
+  if (f.plain == &kD128p) return kWhole;           // (it runs only when its family is forced)
   const KParams& k = w[0].k;
-  const int bc = f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.plain != nullptr ? 32 : 64;
-  const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;
+  const bool generic = f.plain == nullptr && !f.hand;
+  if (generic && !generic_splittable(w)) return kWhole;
+  const int bc = generic ? 32 : f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.hand ? 64 : 32;
+  const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;   // (generic: the CUs)
   long long total = 0, most = 0, rows = 0, blocks = 0;
   for (const WalkChunk& x : w) {
     if (x.p.block_mask != nullptr || !(dkv_kernels(&x.p, x.k) == f) || (f.hand && x.c.ks_r != w[0].c.ks_r)) return kWhole;
@@ -440,13 +477,21 @@ DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
       most = std::max(most, walk);
     }
   }
+  if (generic) {
+    // as many as there are CUs for, four tiles each at least; two also where a causal launch fits the CUs once.
+    // us a launch, whole / by the rule: 1024 keys x 256 rows, one head, d = 64, 28 / 19 in 2; 500 x 500, d = 128, 64 / 30 in 4 (2: 41);
+    // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).
+    long long parts = std::min({256 / blocks, most / 4, 16LL});
+    if (parts < 2 && blocks <= 256 && most >= 16 && 10 * most * slots >= 18 * total) parts = 2;
+    return parts < 2 || most > 0x7fffffffLL ? kWhole : DkvParts{part_columns(heads, parts), (int)parts, (int)((most + parts - 1) / parts), rows};
+  }
   if (most < 24 || most > 0x7fffffffLL || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on
   const long long splits = std::min({16LL, ratio, most / (f.plain != nullptr ? 8 : 16)});
-  return splits < 2 ? kWhole : DkvParts{(int)splits, 8, rows};
+  return splits < 2 ? kWhole : DkvParts{part_columns(heads, splits), (int)splits, 8, rows};
 }
 size_t dkv_bytes(const KParams& k, const DkvParts& p) {
-  return p.splits > 1 ? (size_t)p.splits * 2 * p.rows * k.d * sizeof(float) : 0;
+  return p.splits > 1 ? (size_t)p.most * 2 * p.rows * k.d * sizeof(float) : 0;
 }
 size_t split_bytes(const KParams& k, int splits) {
   return splits > 1 ? (size_t)splits * k.B * k.H * k.Nq * ((size_t)k.d + 2) * sizeof(float) : 0;
@@ -637,7 +682,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1, 1};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -733,7 +778,7 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
       const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
         return fwd_launch(f, kc, p->dtype, io, c, n, s);
       });
-      return e != BURST_OK ? e : burst::launch_merge_splits(k, io, s);
+      return e != BURST_OK || fwd_kernels(&w[0].p, w[0].k).plain == nullptr ? e : burst::launch_merge_splits(k, io, s);   // (the generic launcher merges by itself)
     });
   }
   return validated([&] {
@@ -797,7 +842,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,
-                (float*)workspace, parts.splits, parts.tiles};
+                (float*)workspace, parts.splits, parts.most, parts.tiles};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       BwdIo one = io;
       one.acc_dq = accumulate_dq != 0 || !first;
@@ -805,7 +850,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
       return dq_launch(f, kc, p->dtype, one, c, n, s);
     });
     if (e != BURST_OK) return e;
-    if ((splits > 1 || staged) && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
+    if (((splits > 1 && fwd_kernels(&w[0].p, w[0].k).plain != nullptr) || staged) && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
     return for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
       return dkv_launch(f, kc, p->dtype, io, c, n, s);
     });

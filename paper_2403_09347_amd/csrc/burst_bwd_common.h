@@ -149,7 +149,7 @@ static int launch_merge_dkv(const A& a, hipStream_t stream) {
   return launch_status();
 }
 inline RowParts row_parts(const BwdIo& io, const Chunk* ch, int n, long long heads) {
-  RowParts p = {io.kv_part, io.kv_splits > 1 ? io.kv_splits : 1, io.kv_tiles > 0 ? io.kv_tiles : 1, 0};
+  RowParts p = {io.kv_part, io.kv_splits > 1 ? io.kv_splits : 1, io.kv_most, io.kv_tiles > 0 ? io.kv_tiles : 1, 0};
   long long rows = 0;
   for (int i = 0; i < n; i++) rows += heads * ch[i].Nc;
   p.rows = p.splits > 1 ? (int)rows : 0;

@@ -110,7 +110,7 @@ struct BwdIo {
   int acc_dq, acc_dkv;               // add to what the gradient buffers hold
   int half;                          // dQ, dK, dV are bf16 tensors (the inputs' type) instead of fp32; nothing accumulates then
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
-  float* kv_part; int kv_splits, kv_tiles;   // kv_splits > 1: see RowParts
+  float* kv_part; int kv_splits, kv_most, kv_tiles;   // kv_splits > 1: see RowParts
 };
 
 // How a dK/dV launch deals out its work.  A workgroup's walk are the query tiles its keys are visible to, of all heads of
@@ -120,11 +120,12 @@ struct BwdIo {
 // Blocks with one part write their gradients themselves.
 struct RowParts {
   float* part;
-  int splits, tiles;                 // most parts of a block; tiles of a part
+  int splits;                        // workgroups per block of keys
+  int most, tiles;                   // most parts of a block (<= splits); tiles of a part
   int rows;                          // keys of all chunks and heads
   __host__ __device__ int of(int walk) const {
     const int n = (walk + tiles - 1) / tiles;
-    return n < 1 ? 1 : n < splits ? n : splits;
+    return n < 1 ? 1 : n < most ? n : most;
   }
 };
 // The query tiles (BR rows) of one head that see a key of the block [key0, key0 + BC) of a chunk: [lo, hi).

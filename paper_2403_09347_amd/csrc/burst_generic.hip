@@ -26,7 +26,7 @@
 //    it stands: its two keys (rows), of h = 0 and h = 1, are the two k of that MFMA.
 //  - The other operand of the second product is a row of V, K, dO or Q spread over lr: block db of
 //    lane lr is column col_of(db, lr).
-#include "burst_rows.h"
+#include "burst_bwd_common.h"
 
 namespace burst {
 
@@ -49,6 +49,9 @@ struct GenArgs {
   int blocks;                                     // forward, dQ: 32-row blocks per head
   int n;                                          // chunks
   Chunk ch[kMaxChunks];
+  // SPLIT: a block's tiles are shared by the wavefronts of several workgroups, whose partial results another launch merges
+  float* part; int splits;                        // forward: [split][rows][d] O, then m and l, each [split][rows]; dQ: [split][rows][d]
+  RowParts parts;                                 // dK/dV
 };
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
@@ -118,15 +121,15 @@ __device__ __forceinline__ bool tile_flag(const GenArgs& a, const Chunk& C, int 
   if (C.bmask == nullptr) return true;
   return C.bmask[(size_t)head * C.bhstride + (size_t)(row0 / a.bsize) * C.bpitch + key0 / a.bsize] != 0;
 }
-// The key tiles that rows [row0, row0 + 32) see, chunk after chunk, every W-th of them: the share of one
+// The key tiles that rows [row0, row0 + 32) see, chunk after chunk, every `every`-th of them: the share of one
 // wavefront.
-template <typename T, int W>
+template <typename T>
 struct KeyWalk {
   int c, t, lo, hi;                               // chunk, tile, its chunk's visible range
   const T* K; const T* V;                         // of the chunk, this head
   long long ks_r, k_off;
   int Nc;
-  __device__ __forceinline__ bool to(const GenArgs& a, int head, int row0, int step) {
+  __device__ __forceinline__ bool to(const GenArgs& a, int head, int row0, int step, int every) {
     t += step;
     for (;;) {
       while (t >= hi) {
@@ -151,7 +154,7 @@ struct KeyWalk {
         t = lo + past;
       }
       if (tile_flag(a, a.ch[c], head, row0, t * 32)) return true;
-      t += W;
+      t += every;
     }
   }
 };
@@ -174,7 +177,7 @@ template <int W>
 __device__ __forceinline__ unsigned share(int w) { return ((1u << (32 / W)) - 1u) << (w * (32 / W)); }
 
 // ---------------------------------------------------------------------------- forward
-template <typename T, int D, bool VEC, int W>
+template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, W / 4)
 fwd_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
@@ -182,8 +185,13 @@ fwd_generic_kernel(GenArgs a) {
   extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial O^T, then [W][32] m, l
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int head, blk;
-  if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  int head, blk, split = 0;
+  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk)) return;
+  if constexpr (SPLIT) {
+    split = blk % a.splits; blk /= a.splits;
+  }
+  if (a.causal) blk = a.blocks - 1 - blk;          // later blocks see more keys: the long ones start first
+  const int every = SPLIT ? W * a.splits : W;      // wavefronts that share the block
   const int row0 = blk * 32, row = row0 + lr;
 
   f32x16 o[NB];
@@ -193,9 +201,9 @@ fwd_generic_kernel(GenArgs a) {
     for (int r = 0; r < 16; r++) o[db][r] = 0.f;
   float m_run = BURST_NEG_INF, lsum = 0.f;        // reference max, sum over this lane's keys
 
-  KeyWalk<T, W> at;
+  KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
-  bool more = at.to(a, head, row0, w);
+  bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
   if (more) {
     f32x4 qf[NK], kf[NK];
     const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
@@ -212,7 +220,7 @@ fwd_generic_kernel(GenArgs a) {
       const long long k_off = at.k_off, ks_r = at.ks_r;
       const T* const Kh = at.K;
       const T* const Vh = at.V;
-      more = at.to(a, head, row0, W);
+      more = at.to(a, head, row0, every, every);
       float vf[16][NB];
       auto load_v = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
@@ -282,7 +290,7 @@ fwd_generic_kernel(GenArgs a) {
   const float mref = mg == BURST_NEG_INF ? 0.f : mg;
 #pragma unroll
   for (int i = 0; i < W; i++) lg += ml[i * 64 + 32 + lr] * fast_exp2((ml[i * 64 + lr] - mref) * kLog2e);
-  if (__builtin_amdgcn_ballot_w64(row < a.Nq && larger_of(0, lg) >= kInfBits) != 0) {   // (alike in all wavefronts) the block's rows by themselves, see burst_rows.h
+  if (!SPLIT && __builtin_amdgcn_ballot_w64(row < a.Nq && larger_of(0, lg) >= kInfBits) != 0) {   // (alike in all wavefronts) the block's rows by themselves, see burst_rows.h
     for (unsigned left = first_bits(a.Nq - row0) & share<W>(w); left != 0;) {
       int rows[kRows];
       const int n = next_rows(left, row0, rows);
@@ -304,6 +312,28 @@ fwd_generic_kernel(GenArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = o[db][r] * own;
   __syncthreads();
+  if constexpr (SPLIT) {                           // the partial state (an l that is no finite number: see merge_fwd_generic_kernel)
+    if (row >= a.Nq) return;
+    const size_t rows = (size_t)a.BH * a.Nq, pr = (size_t)split * rows + (size_t)head * a.Nq + row;
+    if (w == 0 && h == 0) {
+      float* const pm = a.part + (size_t)a.splits * rows * a.d;
+      pm[pr] = mg;
+      pm[(size_t)a.splits * rows + pr] = lg;
+    }
+#pragma unroll
+    for (int rr = 0; rr < 16 / W; rr++) {
+      const int r = w * (16 / W) + rr, mrow = reg_row(r, h);
+#pragma unroll
+      for (int db = 0; db < NB; db++) {
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+        const int col = R::col_of(db, mrow);
+        if (col < a.d) a.part[pr * a.d + col] = v;
+      }
+    }
+    return;
+  }
   const bool saw = mg != BURST_NEG_INF;
   if (row >= a.Nq || (!saw && !a.fresh && a.O_out == nullptr)) return;   // rows that saw no key keep their state
   const size_t sr = (size_t)head * a.Nq + row;
@@ -338,7 +368,7 @@ fwd_generic_kernel(GenArgs a) {
 }
 
 // ---------------------------------------------------------------------------- backward, dQ
-template <typename T, int D, bool VEC, int W>
+template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, VEC && D <= 64 ? 2 : 1)   // (256 registers do at d = 64: two wavefronts per SIMD)
 bwd_dq_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
@@ -346,8 +376,13 @@ bwd_dq_generic_kernel(GenArgs a) {
   extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dQ^T, then [W] flags
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int head, blk;
-  if (!locate_block(blockIdx.x, a.BH, a.blocks, head, blk)) return;
+  int head, blk, split = 0;
+  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk)) return;
+  if constexpr (SPLIT) {
+    split = blk % a.splits; blk /= a.splits;
+  }
+  if (a.causal) blk = a.blocks - 1 - blk;          // later blocks see more keys: the long ones start first
+  const int every = SPLIT ? W * a.splits : W;      // wavefronts that share the block
   const int row0 = blk * 32, row = row0 + lr;
   const bool ok = row < a.Nq;
   const size_t sr = (size_t)head * a.Nq + min(row, a.Nq - 1);
@@ -357,9 +392,9 @@ bwd_dq_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
-  KeyWalk<T, W> at;
+  KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
-  bool more = at.to(a, head, row0, w);
+  bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
   if (more) {
     f32x4 qf[NK], gf[NK], kf[NK];
     const size_t qrow = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
@@ -382,7 +417,7 @@ bwd_dq_generic_kernel(GenArgs a) {
       const long long k_off = at.k_off, ks_r = at.ks_r;
       const T* const Kh = at.K;
       const T* const Vh = at.V;
-      more = at.to(a, head, row0, W);
+      more = at.to(a, head, row0, every, every);
       f32x4 vf[NK];
       const T* vr = Vh + (size_t)min(key0 + lr, Nc - 1) * ks_r;
 #pragma unroll
@@ -442,7 +477,7 @@ bwd_dq_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits)) {   // the block's rows by themselves, see burst_rows.h
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits) && !SPLIT) {   // the block's rows by themselves, see burst_rows.h
     for (unsigned left = first_bits(a.Nq - row0) & share<W>(w); left != 0;) {
       int rows[kRows];
       const int n = next_rows(left, row0, rows);
@@ -467,7 +502,8 @@ bwd_dq_generic_kernel(GenArgs a) {
       for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
       const int col = R::col_of(db, mrow);
       if (col >= a.d) continue;
-      if (a.half) out16[col] = (T)(a.scale * v);
+      if constexpr (SPLIT) a.part[((size_t)split * a.BH * a.Nq + sr) * a.d + col] = a.scale * v;
+      else if (a.half) out16[col] = (T)(a.scale * v);
       else out[col] = (a.acc_dq ? out[col] : 0.f) + a.scale * v;
     }
   }
@@ -475,7 +511,7 @@ bwd_dq_generic_kernel(GenArgs a) {
 
 // ---------------------------------------------------------------------------- backward, dK dV
 // Lane = key; score register r = query row reg_row(r, h) of the tile.
-template <typename T, int D, bool VEC, int W>
+template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, W / 4)
 bwd_dkv_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
@@ -487,12 +523,21 @@ bwd_dkv_generic_kernel(GenArgs a) {
   while (ci + 1 < a.n && (int)blockIdx.x >= a.ch[ci + 1].first_block) ci++;
   const Chunk& C = a.ch[ci];
   const int Nc = C.Nc;
-  int kvhead, blk;
-  if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk)) return;
+  int kvhead, blk, part = 0, parts = 1;
+  if constexpr (SPLIT) {
+    if (!locate_part((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, a.parts.splits, kvhead, blk, part)) return;
+  } else {
+    if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk)) return;
+  }
   const int key0 = blk * 32, key = key0 + lr;
   int lo, hi;
   row_tiles(a, C, key0, lo, hi);
   const int per_head = hi - lo, total = max(per_head, 0) * a.group;   // walk positions: the tiles of all heads of the group
+  if constexpr (SPLIT) {
+    parts = a.parts.of(total);
+    if (part >= parts) return;
+  }
+  const int every = SPLIT ? W * parts : W;         // wavefronts that share the walk
   auto place = [&](int n, int& head, int& tile) __attribute__((always_inline)) {
     const int g = n / per_head;
     head = kvhead * a.group + g;
@@ -503,7 +548,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
       int head, tile;
       place(n, head, tile);
       if (tile_flag(a, C, head, tile * 32, key0)) break;
-      n += W;
+      n += every;
     }
     return n;
   };
@@ -513,7 +558,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
-  int n = seek(w);
+  int n = seek(SPLIT ? part * W + w : w);
   if (n < total) {
     f32x4 kf[NK], vf[NK];
     const size_t krow = C.kv_base(kvhead, a.lay.kv_heads) + (size_t)min(key, Nc - 1) * C.ks_r;
@@ -558,7 +603,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
     const T* qrow = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(tile * 32 + lr, a.Nq - 1) * a.lay.qs_r;
     pieces(pa, qrow, 0);
     while (n < total) {
-      const int nn = seek(n + W), row0 = tile * 32;
+      const int nn = seek(n + every), row0 = tile * 32;
       const T* Qh = (const T*)a.Q + a.lay.q_base(head);
       const T* Gh = (const T*)a.dO + a.lay.q_base(head);
       const T* grow = Gh + (size_t)min(row0 + lr, a.Nq - 1) * a.lay.qs_r;
@@ -614,7 +659,8 @@ bwd_dkv_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits)) {   // the block's keys by themselves, see burst_rows.h
+  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits) && parts == 1) {   // (parts: the merging launch sees to it)
+      // the block's keys by themselves, see burst_rows.h
     for (unsigned left = first_bits(Nc - key0) & share<W>(w); left != 0;) {
       int keys[kRows];
       const int n = next_rows(left, key0, keys);
@@ -639,8 +685,10 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
     __syncthreads();
-    void* const base = which ? C.dV : C.dK;
+    float* const to = SPLIT ? a.parts.part + ((size_t)(2 * part + which) * a.parts.rows + C.first_row) * a.d : nullptr;
+    void* const base = parts > 1 ? (void*)to : which ? C.dV : C.dK;
     const float f = which ? 1.f : a.scale;
+    const int half = parts > 1 ? 0 : a.half, acc = parts > 1 ? 0 : a.acc_dkv;
 #pragma unroll
     for (int rr = 0; rr < 16 / W; rr++) {
       const int r = w * (16 / W) + rr, k = key0 + reg_row(r, h);
@@ -654,11 +702,110 @@ bwd_dkv_generic_kernel(GenArgs a) {
         for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
         const int col = R::col_of(db, lr);
         if (col >= a.d) continue;
-        if (a.half) out16[col] = (T)(f * v);
-        else out[col] = (a.acc_dkv ? out[col] : 0.f) + f * v;
+        if (half) out16[col] = (T)(f * v);
+        else out[col] = (acc ? out[col] : 0.f) + f * v;
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------- merging (SPLIT): one wavefront per row
+// Rows whose sum is infinite or NaN are computed by themselves (see burst_rows.h).
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256)
+merge_fwd_generic_kernel(GenArgs a) {
+  const int lane = threadIdx.x & 63;
+  const long long row = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = (long long)a.BH * a.Nq;
+  if (row >= rows) return;
+  const int head = (int)(row / a.Nq), at = (int)(row - (long long)head * a.Nq);
+  const float* const pm = a.part + (size_t)a.splits * rows * a.d;
+  const float* const pl = pm + (size_t)a.splits * rows;
+  const int mine = min(lane, a.splits - 1);        // (at most 64 splits)
+  const float m_part = pm[(size_t)mine * rows + row], l_part = pl[(size_t)mine * rows + row];
+  const float m = wave_max(m_part), ref = m == BURST_NEG_INF ? 0.f : m;
+  const float f = fast_exp2((m_part - ref) * kLog2e);
+  float o[2] = {0.f, 0.f}, l = 0.f;
+#pragma unroll 4
+  for (int i = 0; i < a.splits; i++) {
+    float x[2];
+    row_load(x, a.part + ((size_t)i * rows + row) * a.d, lane, a.d);
+    const float fi = lane_value(f, i);
+    o[0] = __builtin_fmaf(fi, x[0], o[0]);
+    o[1] = __builtin_fmaf(fi, x[1], o[1]);
+    l = __builtin_fmaf(fi, lane_value(l_part, i), l);
+  }
+  RowState st[kRows];
+  st[0] = row_state(a.fresh, a.O_acc, a.m, a.l, row, a.d, lane);
+  const unsigned most = larger_of(larger_of(larger_of(0, l), o[0]), o[1]);
+  if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
+    const int again[kRows] = {at, at, at};
+    st[1] = st[2] = st[0];
+    rows_forward<T, VEC>(st, a, head, again, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 0x7fffffff);
+  } else if (m != BURST_NEG_INF) {                 // Alg. 1 merge step
+    const float m_new = fmaxf(st[0].m, m);
+    const float fa = fast_exp2((st[0].m - m_new) * kLog2e), fb = fast_exp2((m - m_new) * kLog2e);
+#pragma unroll
+    for (int j = 0; j < 2; j++) st[0].o[j] = (fa == 0.f ? 0.f : fa * st[0].o[j]) + fb * o[j];
+    st[0].l = (fa == 0.f ? 0.f : fa * st[0].l) + fb * l;
+    st[0].m = m_new;
+  }
+  row_store<T>(st[0], a.fresh, a.O_acc, a.m, a.l, a.O_out == nullptr ? nullptr : (T*)a.O_out + a.lay.q_base(head) + (size_t)at * a.lay.qs_r,
+               a.lse_out, row, a.d, lane);
+}
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256)
+merge_dq_generic_kernel(GenArgs a) {
+  const int lane = threadIdx.x & 63;
+  const long long row = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = (long long)a.BH * a.Nq;
+  if (row >= rows) return;
+  float g[kRows][2] = {}, scale = 1.f;
+#pragma unroll 4
+  for (int i = 0; i < a.splits; i++) {
+    float x[2];
+    row_load(x, a.part + ((size_t)i * rows + row) * a.d, lane, a.d);
+    g[0][0] += x[0];
+    g[0][1] += x[1];
+  }
+  if (__builtin_amdgcn_ballot_w64(larger_of(larger_of(0, g[0][0]), g[0][1]) >= kInfBits) != 0) {
+    const int head = (int)(row / a.Nq), at = (int)(row - (long long)head * a.Nq);
+    const int again[kRows] = {at, at, at};
+    rows_dq<T, VEC, 64>(g, a, head, again, lane, [](const Chunk& C, int& lo, int& hi) { lo = 0; hi = (C.Nc + 63) >> 6; }, 0, 1);
+    scale = a.scale;
+  }
+  row_gradient<T>(a.dQ, row * a.d, g[0], scale, a.half, a.acc_dq, lane, a.d);
+}
+template <typename T, bool VEC>
+__global__ void __launch_bounds__(256)
+merge_dkv_generic_kernel(GenArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int row = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= a.parts.rows) return;
+  int c = 0;
+  while (c + 1 < a.n && row >= a.ch[c + 1].first_row) c++;
+  const Chunk& C = a.ch[c];
+  const int kvhead = (row - C.first_row) / C.Nc, key = row - C.first_row - kvhead * C.Nc;
+  int lo, hi;
+  row_tiles(a, C, key & ~31, lo, hi);
+  const int parts = a.parts.of(max(hi - lo, 0) * a.group);
+  if (parts == 1) return;                          // written by its workgroup
+  float gk[kRows][2] = {}, gv[kRows][2] = {}, scale = 1.f;
+#pragma unroll 4
+  for (int i = 0; i < parts; i++) {
+    float x[2], y[2];
+    row_load(x, a.parts.part + ((size_t)(2 * i) * a.parts.rows + row) * a.d, lane, a.d);
+    row_load(y, a.parts.part + ((size_t)(2 * i + 1) * a.parts.rows + row) * a.d, lane, a.d);
+#pragma unroll
+    for (int j = 0; j < 2; j++) { gk[0][j] += x[j]; gv[0][j] += y[j]; }
+  }
+  const unsigned most = larger_of(larger_of(larger_of(larger_of(0, gk[0][0]), gk[0][1]), gv[0][0]), gv[0][1]);
+  if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
+    const int again[kRows] = {key, key, key};
+    keys_dkv<T, VEC>(gk, gv, a, C, kvhead, again, lane);
+    scale = a.scale;
+  }
+  const size_t at = ((size_t)kvhead * C.Nc + key) * a.d;
+  row_gradient<T>(C.dK, at, gk[0], scale, a.half, a.acc_dkv, lane, a.d);
+  row_gradient<T>(C.dV, at, gv[0], 1.f, a.half, a.acc_dkv, lane, a.d);
 }
 
 // ---------------------------------------------------------------------------- launchers
@@ -671,13 +818,13 @@ static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
 }
 
 enum { GEN_FWD, GEN_DQ, GEN_DKV };
-template <int KIND, typename T, int D, bool VEC, int W>
+template <int KIND, typename T, int D, bool VEC, int W, bool SPLIT = false>
 static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
   const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : W)) * 4;
   void (*kernel)(GenArgs);
-  if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W>;
-  else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W>;
-  else kernel = bwd_dkv_generic_kernel<T, D, VEC, W>;
+  if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W, SPLIT>;
+  else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W, SPLIT>;
+  else kernel = bwd_dkv_generic_kernel<T, D, VEC, W, SPLIT>;
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([&] {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess ? BURST_OK : BURST_ERR_LAUNCH;
@@ -690,20 +837,40 @@ static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
 // SIMD; the registers allow it up to 64) a row block's tiles are walked in half the time; that pays
 // while there are fewer row blocks than CUs.
 template <int KIND>
+static int gen_split(GenArgs& a, long long grid, hipStream_t s) {      // (fp32, d a multiple of 4)
+  const int st = a.d <= 32 ? gen_launch<KIND, float, 32, true, 4, true>(a, grid, s) : a.d <= 64 ? gen_launch<KIND, float, 64, true, 4, true>(a, grid, s)
+               : a.d <= 96 ? gen_launch<KIND, float, 96, true, 4, true>(a, grid, s) : gen_launch<KIND, float, 128, true, 4, true>(a, grid, s);
+  if (st != BURST_OK) return st;
+  const long long rows = KIND == GEN_DKV ? a.parts.rows : (long long)a.BH * a.Nq;
+  void (*merge)(GenArgs);
+  if constexpr (KIND == GEN_FWD) merge = merge_fwd_generic_kernel<float, true>;
+  else if constexpr (KIND == GEN_DQ) merge = merge_dq_generic_kernel<float, true>;
+  else merge = merge_dkv_generic_kernel<float, true>;
+  BURST_LAUNCH(merge, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, a);
+  return launch_status();
+}
+template <int KIND>
 static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
-  long long grid = 0;
+  long long grid = 0, rows = 0;
   if (KIND == GEN_DKV) {
     for (int i = 0; i < a.n; i++) {
+      const long long blocks = ((long long)a.ch[i].Nc + 31) / 32;
       a.ch[i].first_block = (int)grid;
-      grid += grid_blocks(a.BH / a.group, ((long long)a.ch[i].Nc + 31) / 32);
+      a.ch[i].first_row = (int)rows;               // (used by split launches only, which are small)
+      rows += (long long)(a.BH / a.group) * a.ch[i].Nc;
+      grid += a.parts.splits > 1 ? part_grid(a.BH / a.group, blocks, a.parts.splits) : grid_blocks(a.BH / a.group, blocks);
       if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
     }
   } else {
     a.blocks = (int)(((long long)a.Nq + 31) / 32);
-    grid = grid_blocks(a.BH, a.blocks);
+    grid = grid_blocks(a.BH, (long long)a.blocks * a.splits);
   }
   if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
   if (grid == 0) return BURST_OK;
+  if (KIND == GEN_DKV ? a.parts.splits > 1 : a.splits > 1) {
+    if (dtype != BURST_F32 || a.d % 4 != 0 || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;
+    return gen_split<KIND>(a, grid, s);
+  }
   const bool few = grid <= 256;
   if (dtype == BURST_F32 && a.d % 4 == 0) {
     if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, grid, s) : gen_launch<KIND, float, 32, true, 4>(a, grid, s);
@@ -719,12 +886,16 @@ static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
 int launch_fwd_generic(const KParams& p, int dtype, const FwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};
   make_args(a, p, ch, n);
-  a.Q = io.Q; a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = io.O_out; a.lse_out = io.lse; a.fresh = io.fresh;
+  a.Q = io.Q; a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = io.O_out; a.lse_out = io.lse;
+  a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
+  a.fresh = io.fresh;
   return gen_dispatch<GEN_FWD>(a, dtype, s);
 }
 static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
   make_args(a, p, ch, n);
   a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
+  a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
+  a.parts = row_parts(io, ch, n, a.BH / a.group);
 }
 int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};
