@@ -428,8 +428,12 @@ int walk_splits(const std::vector<WalkChunk>& w) {
     if (k.window > 0) lo = std::max(lo, k.q_off + k.Nq - 128 - k.window + 1 - x.c.k_off);
     if (hi > lo) tiles += (hi - lo + 63) / 64;
   }
-  const long long s = std::min(512 / blocks, tiles / 8);
-  return s < 2 || tiles < 20 ? 1 : (int)s;
+  // The padded kernels' tiles take twice the time: 6 of them are a range where the blocks have a CU each, and walks of 12 are
+  // split (8 x 900 causal rows, d = 96, forward and dQ 33 + 35 us, in 2 26 + 27 with the merges; 16 x 850, 33 + 36, 28 + 29;
+  // 32 x 777, 224 blocks, 32 + 34, 36 + 36).
+  const bool pad = f.plain != &kD64 && f.plain != &kD128p && blocks <= 160;
+  const long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
+  return s < 2 || tiles < (pad ? 12 : 20) ? 1 : (int)s;
 }
 int dq_launches(const std::vector<WalkChunk>& w) {
   int n = 0;

@@ -173,8 +173,16 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
   const int rows_here = 256 / per_row, r_in = threadIdx.x / per_row, c = threadIdx.x - r_in * per_row;
   const bool live = r_in < rows_here && (long long)blockIdx.x * rows_here + r_in < n_rows;
   const long long row = live ? (long long)blockIdx.x * rows_here + r_in : 0;
+  // (8 and 4 ranges at a time, their loads requested together: 32 heads x
+  // 40 rows, 16 ranges, 11.6 us one after the other, 9.3 so)
   float mg = BURST_NEG_INF;
-  for (int i = 0; i < splits; i++) mg = fmaxf(mg, pm[i * n_rows + row]);
+  for (int i = 0; i < splits; i += 8) {
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) x[j] = pm[min(i + j, splits - 1) * n_rows + row];
+#pragma unroll
+    for (int j = 0; j < 8; j++) mg = fmaxf(mg, x[j]);
+  }
   const float m_old = fresh ? BURST_NEG_INF : m[row], l_old = fresh ? 0.f : l[row];
   float m_st = m_old, lsum = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
@@ -187,11 +195,23 @@ merge_splits_kernel(const float* __restrict__ part, int splits, float* __restric
       for (int t = 0; t < 4; t++) o[t] = fa * old[t];
       lsum = fa * l_old;
     }
-    for (int i = 0; i < splits; i++) {
-      const float f = fast_exp2((pm[i * n_rows + row] - mn) * to_log2);
-      const f32x4 v = *reinterpret_cast<const f32x4*>(part + ((size_t)i * n_rows + row) * d + c * 4);
-      for (int t = 0; t < 4; t++) o[t] += f * v[t];
-      lsum += f * pl[i * n_rows + row];
+    for (int i = 0; i < splits; i += 4) {
+      f32x4 v[4];
+      float x[4], l4[4];
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int k = min(i + j, splits - 1);
+        v[j] = *reinterpret_cast<const f32x4*>(part + ((size_t)k * n_rows + row) * d + c * 4);
+        x[j] = pm[k * n_rows + row];
+        l4[j] = pl[k * n_rows + row];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        if (i + j >= splits) break;
+        const float f = fast_exp2((x[j] - mn) * to_log2);
+        for (int t = 0; t < 4; t++) o[t] += f * v[j][t];
+        lsum += f * l4[j];
+      }
     }
     m_st = mn * to_stored;
   } else if (m_old != BURST_NEG_INF) {             // no range saw a key: the state stays
@@ -228,9 +248,14 @@ sum_splits_kernel(const float* __restrict__ part, int splits, void* __restrict__
   }
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if (acc) v = reinterpret_cast<const f32x4*>(dQ)[k];
-  for (int i = 0; i < splits; i++) {
-    const f32x4 x = reinterpret_cast<const f32x4*>(part)[(size_t)i * n4 + k];
-    for (int t = 0; t < 4; t++) v[t] += x[t];
+  for (int i = 0; i < splits; i += 4) {            // (four parts' loads together)
+    f32x4 x[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) x[j] = reinterpret_cast<const f32x4*>(part)[(size_t)min(i + j, splits - 1) * n4 + k];
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      if (i + j < splits)
+        for (int t = 0; t < 4; t++) v[t] += x[j][t];
   }
   if (half) {
     bf16x4 r;
