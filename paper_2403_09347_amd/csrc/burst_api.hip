@@ -376,10 +376,10 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
   return BURST_OK;
 }
 
-// Walks of the generic kernels that can be split: fp32, d a multiple of 4, no flags.
+// Walks of the generic kernels that can be split: fp32 through LDS, no flags.
 bool generic_splittable(const std::vector<WalkChunk>& w) {
-  if (w[0].p.dtype != BURST_F32 || w[0].p.d % 4 != 0) return false;
-  for (const WalkChunk& x : w) if (x.p.block_mask != nullptr) return false;
+  if (w[0].p.dtype != BURST_F32) return false;
+  for (const WalkChunk& x : w) if (x.p.block_mask != nullptr || !burst::fp32_tiles(x.k.d, x.k.lay, &x.c, 1)) return false;
   return true;
 }
 // Into how many workgroups the tiles of a block of 32 rows are dealt: as many as there are CUs for (they run at the fp32

@@ -88,6 +88,12 @@ struct Chunk {
   }
 };
 constexpr int kMaxChunks = 32;
+// fp32 rows that the generic kernels can bring to LDS: whole 16-byte granules, and 32 rows within a descriptor's 2 GiB.
+inline bool fp32_tiles(int d, const Layout& lay, const Chunk* ch, int n) {
+  bool ok = d % 4 == 0 && lay.qs_r < (1 << 24);
+  for (int i = 0; i < n; i++) ok = ok && ch[i].ks_r < (1 << 24);
+  return ok;
+}
 inline Chunk chunk_of(const KParams& p, const void* K, const void* V, void* dK, void* dV) {
   Chunk c = {};
   c.K = K; c.V = V; c.dK = dK; c.dV = dV;

@@ -4,18 +4,16 @@
 // on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 products, fp32 accumulation).
 //
 // What they are built around: the fp32 matrix rate (157 TFLOP/s nominal, 153 measured for a large product), 64
-// cycles per MFMA, so that operand traffic is small beside it.  Hence no LDS tiles and no barriers
-// in the loops: a wavefront owns 32 query rows (or 32 keys), keeps their operands and accumulators in
-// registers and reads the other side's 32-row tiles straight from memory, each operand while the
-// MFMAs of the one before it run.  The wavefronts of a workgroup share one row block and take its
-// tiles in turn (their partial results meet in LDS at the end, in a fixed order): a slice of 256
-// rows would otherwise keep 8 of the chip's 1024 SIMDs busy.
-// Measured per launch, forward / dQ / dK+dV, against one wavefront per row with scalar FMAs (the form
-// these kernels replace): fp32, 8 heads of 700 x 700 without a mask, d = 128: 448 / 522 / 1927 -> 48 / 64 / 91 us
-// (42 / 47 / 44 TFLOP/s, less than a third of the fp32 matrix rate: 176 row blocks for 256 CUs, one wavefront per SIMD, and
-// operands whose 32 rows are as many cache lines per load); fp32, one head of 256 x 256, d = 64: 48 / 46 / 93 ->
-// 15 / 18 / 27 us; bf16, d = 96, 32 heads of 777 x 777, before these calls went to the padded kernels of
-// burst_plain_mfma.h: 1208 / 1070 / 4308 -> 272 / 480 / 587 us.
+// cycles per MFMA, so that operand traffic is small beside it.  A wavefront owns 32 query rows (or 32 keys), keeps their
+// operands and accumulators in registers and walks the other side in 32-row tiles: fp32 through LDS of its own, without
+// barriers (LdsTile); other types and strides straight from memory, each operand while the MFMAs of the one before it
+// run.  The wavefronts of a workgroup share one row block and take its tiles in turn (their partial results meet in LDS at
+// the end, in a fixed order): a slice of 256 rows would otherwise keep 8 of the chip's 1024 SIMDs busy.  Where that is not
+// enough several workgroups share a block (SPLIT).
+// Measured per launch, forward / dQ / dK+dV, fp32, with operands from memory / through LDS: 8 heads of 700 rows x 1400 causal keys,
+// d = 128, 71 / 104 / 121 -> 68 / 89 / 100 us; 4 x 1000 x 3000, d = 64, 53 / 63 / 112 -> 51 / 60 / 85; 8 x 1000 x 4000, d = 32,
+// 67 / 82 / 134 -> 61 / 71 / 100.  What is left at 700 rows: 176 row blocks for 256 CUs, of unequal length, one wavefront
+// per SIMD, and about 12 us a workgroup before and after its tiles.
 // Accumulators that come out infinite or NaN: see burst_rows.h.
 //
 // Operand layouts of v_mfma_f32_32x32x2_f32 (lane = 32 h + lr): A holds [m = lr][k = h], B holds
@@ -59,12 +57,12 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
 }
 __device__ __forceinline__ int reg_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
-// How one call shape reads its rows.  VEC: fp32 with d a multiple of 4 (rows then start on 16 bytes).
+// How one call shape reads its rows.  VEC: fp32 with d a multiple of 4 (see fp32_tiles), whose tiles come through LDS.
 template <typename T, int D, bool VEC>
 struct Rows {
   static constexpr int NK = D / 8;                // four-wide operand pieces of a row
   static constexpr int NB = D / 32;               // 32-wide blocks of d
-  static constexpr bool PACKED = VEC && D != 96;  // columns NB lr .. NB lr + NB - 1 in one load
+  static constexpr bool PACKED = VEC && D != 96;  // columns NB lr .. NB lr + NB - 1 in one LDS read
   static __device__ __forceinline__ int col_of(int db, int lr) { return PACKED ? NB * lr + db : 32 * db + lr; }
   // columns 8 ks + 4 h .. + 3.  Past d: whatever the row's last columns hold (the other operand, `fixed`
   // below, is zero there).
@@ -87,20 +85,64 @@ struct Rows {
   }
   // block columns of lane lr (past d: anything, such columns are never stored)
   static __device__ __forceinline__ void spread(const T* row, int lr, int d, float (&v)[NB]) {
-    if constexpr (PACKED) {
+#pragma unroll
+    for (int db = 0; db < NB; db++) v[db] = (float)row[min(32 * db + lr, d - 1)];
+  }
+};
+
+// VEC: a wavefront's tiles of the other side, 32 rows of D floats, come by DMA into LDS of its own (no barriers): read from
+// memory directly, the four-wide pieces of 32 rows are as many cache lines per load, each fetched again for the next piece.
+// Two tiles per wavefront (K and V, or Q and dO); each is refilled as soon as the last product that reads it has been issued, a
+// phase or more ahead of its next use.  Granule g (four floats) of row r sits at slot g ^ (r & 15) (D = 32, 96: & 7), so that
+// reads of one granule of 16 rows use all banks (D = 96: two rows each).  Rows and columns that do not exist are zero.
+template <int D>
+struct LdsTile {
+  static constexpr int G = D / 4, LOADS = D / 8, BYTES = 32 * D * 4;   // wave-wide loads of a tile
+  static __device__ __forceinline__ int off(int row, int g) { return (row * G + (g ^ (row & (G % 16 == 0 ? 15 : 7)))) * 16; }
+  // byte offsets of the lane's granules in a tensor (outside any tile for columns past d)
+  static __device__ __forceinline__ void sources(int (&at)[LOADS], int lane, unsigned pitch, int d) {
+#pragma unroll
+    for (int il = 0; il < LOADS; il++) {
+      const int flat = il * 64 + lane, row = flat / G, g = (flat % G) ^ (row & (G % 16 == 0 ? 15 : 7));
+      at[il] = 4 * g < d ? (int)(row * pitch) + g * 16 : (int)0x80000000u;
+    }
+  }
+  // rows: how many of the 32 exist
+  static __device__ __forceinline__ void fetch(unsigned lds, const float* first, int rows, unsigned pitch, int d, const int (&at)[LOADS]) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(first, (unsigned)(min(rows, 32) - 1) * pitch + 4u * d);
+#pragma unroll
+    for (int il = 0; il < LOADS; il++) dma_b128_to_lds(rs, lds + il * 1024u, at[il]);
+  }
+  static __device__ __forceinline__ f32x4 piece(const char* t, int row, int g) { return *reinterpret_cast<const f32x4*>(t + off(row, g)); }
+  // block columns of lane lr (Rows::col_of)
+  static __device__ __forceinline__ void spread(const char* t, int row, int lr, float (&v)[D / 32]) {
+    constexpr int NB = D / 32;
+    if constexpr (D == 96) {
+#pragma unroll
+      for (int db = 0; db < NB; db++) v[db] = *reinterpret_cast<const float*>(t + off(row, 8 * db + (lr >> 2)) + (lr & 3) * 4);
+    } else {
       typedef __attribute__((ext_vector_type(NB))) float vec;
-      if constexpr (NB == 1) v[0] = row[min(lr, d - 1)];
+      const char* const p = t + off(row, NB * lr >> 2) + (NB * lr & 3) * 4;
+      if constexpr (NB == 1) v[0] = *reinterpret_cast<const float*>(p);
       else {
-        const vec x = *reinterpret_cast<const vec*>(row + min(NB * lr, d - NB));
+        const vec x = *reinterpret_cast<const vec*>(p);
 #pragma unroll
         for (int db = 0; db < NB; db++) v[db] = x[db];
       }
-    } else {
-#pragma unroll
-      for (int db = 0; db < NB; db++) v[db] = (float)row[min(32 * db + lr, d - 1)];
     }
   }
 };
+// at most N loads outstanding; LDS reads below stay below
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+// the LDS reads above have been answered
+__device__ __forceinline__ void wait_reads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
+}
 
 // Query tiles (32 rows) that see keys [key0, key0 + 32) of the chunk.
 __device__ __forceinline__ void row_tiles(const GenArgs& a, const Chunk& C, int key0, int& lo, int& hi) {
@@ -176,13 +218,17 @@ __device__ __forceinline__ bool any_wave_odd(float* flags, int w, int lane, bool
 template <int W>
 __device__ __forceinline__ unsigned share(int w) { return ((1u << (32 / W)) - 1u) << (w * (32 / W)); }
 
+// Floats of LDS per wavefront: its two tiles, and at the end its partial results.
+template <int D, bool VEC>
+constexpr int wave_floats() { return VEC ? 64 * D : 32 * D; }
+
 // ---------------------------------------------------------------------------- forward
 template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, W / 4)
 fwd_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
-  constexpr int NB = R::NB, NK = R::NK;
-  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial O^T, then [W][32] m, l
+  constexpr int NB = R::NB, NK = R::NK, WS = wave_floats<D, VEC>();
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // per wavefront: tiles, then [NB][16][64] partial O^T; [W][32] m, l
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk, split = 0;
@@ -204,7 +250,83 @@ fwd_generic_kernel(GenArgs a) {
   KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
   bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
-  if (more) {
+  if (VEC && more) {
+    if constexpr (VEC) {
+    using L = LdsTile<D>;
+    char* const kl = reinterpret_cast<char*>(gsh) + w * 2 * L::BYTES;
+    char* const vl = kl + L::BYTES;
+    const unsigned kd = lds_addr(kl), vd = lds_addr(vl);
+    f32x4 qf[NK];
+    const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) qf[ks] = R::fixed(Qr, 8 * ks + 4 * h, a.d, row < a.Nq);
+    wait_loads<0>();                               // (no load of the compiler's own in the loop: it would wait for the DMA too)
+    int src[L::LOADS];
+    unsigned pitch = (unsigned)at.ks_r * 4u;
+    L::sources(src, lane, pitch, a.d);
+    auto fetch = [&](unsigned to, const T* base) __attribute__((always_inline)) {
+      if (pitch != (unsigned)at.ks_r * 4u) {       // (chunks of another pitch)
+        pitch = (unsigned)at.ks_r * 4u;
+        L::sources(src, lane, pitch, a.d);
+      }
+      L::fetch(to, base + (size_t)at.t * 32 * at.ks_r, at.Nc - at.t * 32, pitch, a.d, src);
+    };
+    fetch(kd, at.K);
+    fetch(vd, at.V);
+    while (more) {
+      const int key0 = at.t * 32, Nc = at.Nc;
+      const long long k_off = at.k_off;
+      more = at.to(a, head, row0, every, every);
+      wait_loads<L::LOADS>();                      // K; V may be on its way
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; r++) s[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) {
+        const f32x4 kf = L::piece(kl, lr, 2 * ks + h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) s = mfma_f32(kf[j], qf[ks][j], s);
+      }
+      wait_reads();
+      if (more) fetch(kd, at.K);
+      // masks: register r holds key key0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
+      const long long dd = (a.q_off - k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
+      if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
+      float v = BURST_NEG_INF;
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        s[r] = (cpart <= lim && cpart >= lim_lo) ? product(s[r], a.scale) : BURST_NEG_INF;
+        v = fmaxf(v, s[r]);
+      }
+      const float m_new = fmaxf(m_run, max_both_halves(v)), ref = m_new == BURST_NEG_INF ? 0.f : m_new;
+      const float alpha = fast_exp2((m_run - ref) * kLog2e);
+      m_run = m_new;
+      lsum *= alpha;
+#pragma unroll
+      for (int db = 0; db < NB; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) o[db][r] *= alpha;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = fast_exp2((s[r] - ref) * kLog2e); lsum += s[r]; }
+      if (more) wait_loads<L::LOADS>();            // V; the next K may be on its way
+      else wait_loads<0>();
+      // O^T += V^T P^T
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        float vf[NB];
+        L::spread(vl, reg_row(r, h), lr, vf);
+#pragma unroll
+        for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[db], s[r], o[db]);
+      }
+      wait_reads();
+      if (more) fetch(vd, at.V);
+    }
+    }
+  } else if (more) {
+    if constexpr (!VEC) {
     f32x4 qf[NK], kf[NK];
     const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
 #pragma unroll
@@ -273,8 +395,9 @@ fwd_generic_kernel(GenArgs a) {
         for (int db = 0; db < NB; db++) o[db] = mfma_f32(vf[r][db], s[r], o[db]);
     }
   }
+  }
   // the wavefronts' partial results meet in LDS
-  float* const ml = gsh + W * NB * 1024;
+  float* const ml = gsh + W * WS;
   unsigned most = larger_of(0, lsum);              // a wavefront with an infinity or NaN says so by its row sums
 #pragma unroll
   for (int db = 0; db < NB; db++)
@@ -310,7 +433,7 @@ fwd_generic_kernel(GenArgs a) {
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = o[db][r] * own;
+    for (int r = 0; r < 16; r++) gsh[w * WS + (db * 16 + r) * 64 + lane] = o[db][r] * own;
   __syncthreads();
   if constexpr (SPLIT) {                           // the partial state (an l that is no finite number: see merge_fwd_generic_kernel)
     if (row >= a.Nq) return;
@@ -327,7 +450,7 @@ fwd_generic_kernel(GenArgs a) {
       for (int db = 0; db < NB; db++) {
         float v = 0.f;
 #pragma unroll
-        for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+        for (int i = 0; i < W; i++) v += gsh[i * WS + (db * 16 + r) * 64 + lane];
         const int col = R::col_of(db, mrow);
         if (col < a.d) a.part[pr * a.d + col] = v;
       }
@@ -356,7 +479,7 @@ fwd_generic_kernel(GenArgs a) {
     for (int db = 0; db < NB; db++) {
       float v = 0.f;
 #pragma unroll
-      for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+      for (int i = 0; i < W; i++) v += gsh[i * WS + (db * 16 + r) * 64 + lane];
       const int col = R::col_of(db, mrow);
       if (col < a.d) {
         const float x = (fa == 0.f ? 0.f : fa * orow[col]) + fb * v;
@@ -372,8 +495,8 @@ template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, VEC && D <= 64 ? 2 : 1)   // (256 registers do at d = 64: two wavefronts per SIMD)
 bwd_dq_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
-  constexpr int NB = R::NB, NK = R::NK;
-  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dQ^T, then [W] flags
+  constexpr int NB = R::NB, NK = R::NK, WS = wave_floats<D, VEC>();
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // per wavefront: tiles, then [NB][16][64] partial dQ^T; [W] flags
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk, split = 0;
@@ -395,7 +518,86 @@ bwd_dq_generic_kernel(GenArgs a) {
   KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
   bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
-  if (more) {
+  if (VEC && more) {
+    if constexpr (VEC) {
+    using L = LdsTile<D>;
+    char* const kl = reinterpret_cast<char*>(gsh) + w * 2 * L::BYTES;
+    char* const vl = kl + L::BYTES;
+    const unsigned kd = lds_addr(kl), vd = lds_addr(vl);
+    f32x4 qf[NK], gf[NK];
+    const size_t qrow = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) {
+      qf[ks] = R::fixed((const T*)a.Q + qrow, 8 * ks + 4 * h, a.d, ok);
+      gf[ks] = R::fixed((const T*)a.dO + qrow, 8 * ks + 4 * h, a.d, ok);
+    }
+    const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
+    const float nlse = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv;   // -inf: P = 0
+    const float nD = ok ? -a.D[sr] : 0.f;
+    wait_loads<0>();
+    int src[L::LOADS];
+    unsigned pitch = (unsigned)at.ks_r * 4u;
+    L::sources(src, lane, pitch, a.d);
+    auto fetch = [&](unsigned to, const T* base) __attribute__((always_inline)) {
+      if (pitch != (unsigned)at.ks_r * 4u) {       // (chunks of another pitch)
+        pitch = (unsigned)at.ks_r * 4u;
+        L::sources(src, lane, pitch, a.d);
+      }
+      L::fetch(to, base + (size_t)at.t * 32 * at.ks_r, at.Nc - at.t * 32, pitch, a.d, src);
+    };
+    fetch(vd, at.V);
+    fetch(kd, at.K);
+    while (more) {                                 // V's product first: K, which is read last, has that long to arrive
+      const int key0 = at.t * 32, Nc = at.Nc;
+      const long long k_off = at.k_off;
+      more = at.to(a, head, row0, every, every);
+      wait_loads<L::LOADS>();
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = nD; }
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) {
+        const f32x4 vf = L::piece(vl, lr, 2 * ks + h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) dp = mfma_f32(vf[j], gf[ks][j], dp);
+      }
+      wait_reads();
+      if (more) {
+        fetch(vd, at.V);
+        wait_loads<L::LOADS>();
+      } else {
+        wait_loads<0>();
+      }
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) {
+        const f32x4 kf = L::piece(kl, lr, 2 * ks + h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) s = mfma_f32(kf[j], qf[ks][j], s);
+      }
+      const long long dd = (a.q_off - k_off) + row - ((long long)key0 + 4 * h);
+      int lim = min(64, Nc - 1 - (key0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim = (int)min((long long)lim, dd < -1 ? -1LL : dd);
+      if (a.window > 0) { const long long dl = dd - a.window + 1; lim_lo = (int)(dl < -1 ? -1 : dl > 64 ? 64 : dl); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        const float p = fast_exp2(above(s[r], a.scale, -nlse) * kLog2e);
+        dp[r] = (cpart <= lim && cpart >= lim_lo) ? p * dp[r] : 0.f;   // dS^T
+      }
+      // dQ^T += K^T dS^T
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        float kt[NB];
+        L::spread(kl, reg_row(r, h), lr, kt);
+#pragma unroll
+        for (int db = 0; db < NB; db++) dq[db] = mfma_f32(kt[db], dp[r], dq[db]);
+      }
+      wait_reads();
+      if (more) fetch(kd, at.K);
+    }
+    }
+  } else if (more) {
+    if constexpr (!VEC) {
     f32x4 qf[NK], gf[NK], kf[NK];
     const size_t qrow = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
 #pragma unroll
@@ -468,16 +670,17 @@ bwd_dq_generic_kernel(GenArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  }
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
-    for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = dq[db][r];
+    for (int r = 0; r < 16; r++) gsh[w * WS + (db * 16 + r) * 64 + lane] = dq[db][r];
   unsigned most = 0;
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(most, dq[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, ok && most >= kInfBits) && !SPLIT) {   // the block's rows by themselves, see burst_rows.h
+  if (any_wave_odd<W>(gsh + W * WS, w, lane, ok && most >= kInfBits) && !SPLIT) {   // the block's rows by themselves, see burst_rows.h
     for (unsigned left = first_bits(a.Nq - row0) & share<W>(w); left != 0;) {
       int rows[kRows];
       const int n = next_rows(left, row0, rows);
@@ -499,7 +702,7 @@ bwd_dq_generic_kernel(GenArgs a) {
     for (int db = 0; db < NB; db++) {
       float v = 0.f;
 #pragma unroll
-      for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+      for (int i = 0; i < W; i++) v += gsh[i * WS + (db * 16 + r) * 64 + lane];
       const int col = R::col_of(db, mrow);
       if (col >= a.d) continue;
       if constexpr (SPLIT) a.part[((size_t)split * a.BH * a.Nq + sr) * a.d + col] = a.scale * v;
@@ -515,8 +718,8 @@ template <typename T, int D, bool VEC, int W, bool SPLIT>
 __global__ void __launch_bounds__(64 * W, W / 4)
 bwd_dkv_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
-  constexpr int NB = R::NB, NK = R::NK;
-  extern __shared__ __attribute__((aligned(16))) float gsh[];          // [W][NB][16][64] partial dK, then dV; [W] flags
+  constexpr int NB = R::NB, NK = R::NK, WS = wave_floats<D, VEC>();
+  extern __shared__ __attribute__((aligned(16))) float gsh[];          // per wavefront: tiles, then [NB][16][64] partial dK, then dV; statistics, then flags
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int ci = 0;                                      // the workgroups of all chunks, chunk after chunk
@@ -559,7 +762,104 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) { dk[db][r] = 0.f; dv[db][r] = 0.f; }
   int n = seek(SPLIT ? part * W + w : w);
-  if (n < total) {
+  if (VEC && n < total) {
+    if constexpr (VEC) {
+    f32x4 kf[NK], vf[NK];
+    const size_t krow = C.kv_base(kvhead, a.lay.kv_heads) + (size_t)min(key, Nc - 1) * C.ks_r;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) {
+      kf[ks] = R::fixed((const T*)C.K + krow, 8 * ks + 4 * h, a.d, key < Nc);
+      vf[ks] = R::fixed((const T*)C.V + krow, 8 * ks + 4 * h, a.d, key < Nc);
+    }
+    using L = LdsTile<D>;
+    char* const ql = reinterpret_cast<char*>(gsh) + w * 2 * L::BYTES;
+    char* const gl = ql + L::BYTES;
+    const float* const stat = reinterpret_cast<const float*>(reinterpret_cast<const char*>(gsh) + W * 2 * L::BYTES + w * 512);   // lse, then D, of the tile's rows
+    const unsigned qd = lds_addr(ql), gd = lds_addr(gl), sd = lds_addr(stat);
+    wait_loads<0>();
+    int src[L::LOADS];
+    const unsigned pitch = (unsigned)a.lay.qs_r * 4u;
+    L::sources(src, lane, pitch, a.d);
+    int head, tile;
+    place(n, head, tile);
+    auto fetch = [&](unsigned to, const void* x) __attribute__((always_inline)) {
+      L::fetch(to, (const T*)x + a.lay.q_base(head) + (size_t)tile * 32 * a.lay.qs_r, a.Nq - tile * 32, pitch, a.d, src);
+    };
+    auto fetch_g = [&]() __attribute__((always_inline)) {
+      fetch(gd, a.dO);
+      const size_t sr = (size_t)head * a.Nq + tile * 32;
+      const unsigned bytes = 4u * min(32, a.Nq - tile * 32);
+      dma_b32_to_lds(make_rsrc(a.lse + sr, bytes), sd, lr * 4);
+      dma_b32_to_lds(make_rsrc(a.D + sr, bytes), sd + 256, lr * 4);
+    };
+    fetch_g();
+    fetch(qd, a.Q);
+    while (n < total) {                            // dO's product first: Q, which is read last, has that long to arrive
+      const int row0 = tile * 32;
+      const int nn = seek(n + every);
+      const bool more = nn < total;
+      if (more) place(nn, head, tile);
+      wait_loads<L::LOADS>();
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) {
+        const f32x4 x = L::piece(gl, lr, 2 * ks + h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) dp = mfma_f32(x[j], vf[ks][j], dp);
+      }
+      wait_loads<0>();
+#pragma unroll
+      for (int ks = 0; ks < NK; ks++) {
+        const f32x4 x = L::piece(ql, lr, 2 * ks + h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) s = mfma_f32(x[j], kf[ks][j], s);
+      }
+      float lrow[16], drow[16];
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(stat + 8 * q4 + 4 * h), d4 = *reinterpret_cast<const f32x4*>(stat + 64 + 8 * q4 + 4 * h);
+#pragma unroll
+        for (int j = 0; j < 4; j++) { lrow[4 * q4 + j] = l4[j]; drow[4 * q4 + j] = d4[j]; }
+      }
+      // masks: register r holds row row0 + 4 h + cpart; visible iff cpart in [lim_lo, lim]
+      const long long dd = (C.k_off - a.q_off) + key - ((long long)row0 + 4 * h);   // key position - row position at cpart 0
+      int lim = min(64, a.Nq - 1 - (row0 + 4 * h)), lim_lo = -1;
+      if (a.causal) lim_lo = (int)(dd < -1 ? -1 : dd > 64 ? 64 : dd);
+      if (a.window > 0) { const long long dl = dd + a.window - 1; lim = (int)min((long long)lim, dl < -1 ? -1LL : dl); }
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int cpart = 8 * (r >> 2) + (r & 3);
+        const bool vis = cpart <= lim && cpart >= lim_lo && lrow[r] != BURST_NEG_INF;
+        const float p = fast_exp2(above(s[r], a.scale, lrow[r]) * kLog2e);
+        dp[r] = vis ? p * (dp[r] - drow[r]) : 0.f;
+        s[r] = vis ? p : 0.f;
+      }
+      // dV += P^T dO, dK += dS^T Q
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        float x[NB];
+        L::spread(gl, reg_row(r, h), lr, x);
+#pragma unroll
+        for (int db = 0; db < NB; db++) dv[db] = mfma_f32(s[r], x[db], dv[db]);
+      }
+      wait_reads();
+      if (more) fetch_g();
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        float x[NB];
+        L::spread(ql, reg_row(r, h), lr, x);
+#pragma unroll
+        for (int db = 0; db < NB; db++) dk[db] = mfma_f32(dp[r], x[db], dk[db]);
+      }
+      wait_reads();
+      if (more) fetch(qd, a.Q);
+      n = nn;
+    }
+    }
+  } else if (n < total) {
+    if constexpr (!VEC) {
     f32x4 kf[NK], vf[NK];
     const size_t krow = C.kv_base(kvhead, a.lay.kv_heads) + (size_t)min(key, Nc - 1) * C.ks_r;
 #pragma unroll
@@ -654,12 +954,13 @@ bwd_dkv_generic_kernel(GenArgs a) {
       n = nn;
     }
   }
+  }
   unsigned most = 0;
 #pragma unroll
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
-  if (any_wave_odd<W>(gsh + W * NB * 1024, w, lane, most >= kInfBits) && parts == 1) {   // (parts: the merging launch sees to it)
+  if (any_wave_odd<W>(gsh + W * WS + (VEC ? 128 * W : 0), w, lane, most >= kInfBits) && parts == 1) {   // (parts: the merging launch sees to it)
       // the block's keys by themselves, see burst_rows.h
     for (unsigned left = first_bits(Nc - key0) & share<W>(w); left != 0;) {
       int keys[kRows];
@@ -683,7 +984,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
     for (int db = 0; db < NB; db++)
 #pragma unroll
-      for (int r = 0; r < 16; r++) gsh[((w * NB + db) * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
+      for (int r = 0; r < 16; r++) gsh[w * WS + (db * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
     __syncthreads();
     float* const to = SPLIT ? a.parts.part + ((size_t)(2 * part + which) * a.parts.rows + C.first_row) * a.d : nullptr;
     void* const base = parts > 1 ? (void*)to : which ? C.dV : C.dK;
@@ -699,7 +1000,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
       for (int db = 0; db < NB; db++) {
         float v = 0.f;
 #pragma unroll
-        for (int i = 0; i < W; i++) v += gsh[((i * NB + db) * 16 + r) * 64 + lane];
+        for (int i = 0; i < W; i++) v += gsh[i * WS + (db * 16 + r) * 64 + lane];
         const int col = R::col_of(db, lr);
         if (col >= a.d) continue;
         if (half) out16[col] = (T)(f * v);
@@ -820,7 +1121,7 @@ static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
 enum { GEN_FWD, GEN_DQ, GEN_DKV };
 template <int KIND, typename T, int D, bool VEC, int W, bool SPLIT = false>
 static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
-  const unsigned lds = (W * (D / 32) * 1024 + (KIND == GEN_FWD ? W * 64 : W)) * 4;
+  const unsigned lds = (W * wave_floats<D, VEC>() + (KIND == GEN_FWD ? W * 64 : KIND == GEN_DKV && VEC ? W * 129 : W)) * 4;
   void (*kernel)(GenArgs);
   if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W, SPLIT>;
   else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W, SPLIT>;
@@ -868,11 +1169,11 @@ static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
   if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
   if (grid == 0) return BURST_OK;
   if (KIND == GEN_DKV ? a.parts.splits > 1 : a.splits > 1) {
-    if (dtype != BURST_F32 || a.d % 4 != 0 || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;
+    if (dtype != BURST_F32 || !fp32_tiles(a.d, a.lay, a.ch, a.n) || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;
     return gen_split<KIND>(a, grid, s);
   }
   const bool few = grid <= 256;
-  if (dtype == BURST_F32 && a.d % 4 == 0) {
+  if (dtype == BURST_F32 && fp32_tiles(a.d, a.lay, a.ch, a.n)) {
     if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, grid, s) : gen_launch<KIND, float, 32, true, 4>(a, grid, s);
     if (a.d <= 64) return few ? gen_launch<KIND, float, 64, true, 8>(a, grid, s) : gen_launch<KIND, float, 64, true, 4>(a, grid, s);
     if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, grid, s);
