@@ -686,7 +686,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1, 1};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1, 1, nullptr};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -843,13 +843,20 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
       }
       return BURST_OK;
     }
-    if (O != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
+    // D by the first dQ launch itself where that is shorter than a launch of its own (4.5 us): walk of 256 rows x 1024 keys, fp32,
+    // 82 / 77 us, call with gradients of 64 heads x 1024 rows, d = 64, 93.6 / 91.2 (dQ 30.7 / 32.6).  The d = 128 kernels lose as much
+    // (32 over 8 heads x 3001 rows: dQ 153 / 163, the launch 9), and ranges of keys would each compute it (dQ 116 / 125).
+    const PlainFamily* const first_plain = w.empty() ? nullptr : fwd_kernels(&w[0].p, w[0].k).plain;
+    const bool fused = O != nullptr && !w.empty() && !fwd_kernels(&w[0].p, w[0].k).hand && first_plain != &kD128p &&
+                       (first_plain == nullptr || splits == 1);
+    if (O != nullptr && !fused && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,
-                (float*)workspace, parts.splits, parts.most, parts.tiles};
+                (float*)workspace, parts.splits, parts.most, parts.tiles, nullptr};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       BwdIo one = io;
       one.acc_dq = accumulate_dq != 0 || !first;
+      one.O = fused && first ? O : nullptr;
       if (staged) { one.dQ = workspace; one.half = 0; }
       return dq_launch(f, kc, p->dtype, one, c, n, s);
     });

@@ -117,6 +117,7 @@ struct BwdIo {
   int half;                          // dQ, dK, dV are bf16 tensors (the inputs' type) instead of fp32; nothing accumulates then
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
   float* kv_part; int kv_splits, kv_most, kv_tiles;   // kv_splits > 1: see RowParts
+  const void* O;                     // dQ, plain and generic kernels: D = rowsum(dO o O) is computed and written first (nullptr: it is there)
 };
 
 // How a dK/dV launch deals out its work.  A workgroup's walk are the query tiles its keys are visible to, of all heads of
@@ -186,7 +187,19 @@ __device__ __forceinline__ float product(float s, float scale) {
 }
 __device__ __forceinline__ float above(float s, float scale, float ref) { return product(s, scale) - ref; }
 
-// The same with everything in natural units (m_st, cm and mx): no product between a score, its maximum and what is stored.
+// Sums whose order the compiler must not change (D has the same bits wherever it is computed).
+__device__ __forceinline__ float fma_in_order(float x, float y, float acc) {
+  acc = __builtin_fmaf(x, y, acc);
+  asm("" : "+v"(acc));
+  return acc;
+}
+__device__ __forceinline__ float add_in_order(float x, float y) {
+  x += y;
+  asm("" : "+v"(x));
+  return x;
+}
+
+// raise_reference with everything in natural units (m_st, cm and mx): no product between a score, its maximum and what is stored.
 __device__ __forceinline__ float raise_reference_natural(float& m_st, float& cm, float mx, float l) {
   const float was = m_st;
   float to = fmaxf(mx, was);

@@ -123,7 +123,7 @@ bwd_prepare_kernel(const T* __restrict__ O, const T* __restrict__ dO, float* __r
       for (int c = part * E; c < d; c += L * E) {
         const vec x = *reinterpret_cast<const vec*>(O + base + c), y = *reinterpret_cast<const vec*>(dO + base + c);
 #pragma unroll
-        for (int t = 0; t < E; t++) acc = __builtin_fmaf((float)x[t], (float)y[t], acc);
+        for (int t = 0; t < E; t++) acc = fma_in_order((float)x[t], (float)y[t], acc);
       }
     }
 #pragma unroll

@@ -48,6 +48,7 @@ struct GenArgs {
   int n;                                          // chunks
   Chunk ch[kMaxChunks];
   // SPLIT: a block's tiles are shared by the wavefronts of several workgroups, whose partial results another launch merges
+  const void* O;                                  // dQ: D is computed from it and written (nullptr: D is there)
   float* part; int splits;                        // forward: [split][rows][d] O, then m and l, each [split][rows]; dQ: [split][rows][d]
   RowParts parts;                                 // dK/dV
 };
@@ -515,6 +516,22 @@ bwd_dq_generic_kernel(GenArgs a) {
   for (int db = 0; db < NB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
+  float nD = 0.f;                                  // minus D
+  if (a.O != nullptr) {                            // (every wavefront for itself)
+    const size_t from = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
+    float x = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NK; ks++) {
+      const f32x4 g = R::fixed((const T*)a.dO + from, 8 * ks + 4 * h, a.d, ok), o = R::fixed((const T*)a.O + from, 8 * ks + 4 * h, a.d, ok);
+#pragma unroll
+      for (int j = 0; j < 4; j++) x = __builtin_fmaf(o[j], g[j], x);
+    }
+    x = sum_both_halves(x);
+    nD = -x;
+    if (ok && h == 0 && w == 0) const_cast<float*>(a.D)[sr] = x;
+  } else if (ok) {
+    nD = -a.D[sr];
+  }
   KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
   bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
@@ -533,7 +550,6 @@ bwd_dq_generic_kernel(GenArgs a) {
     }
     const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
     const float nlse = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv;   // -inf: P = 0
-    const float nD = ok ? -a.D[sr] : 0.f;
     wait_loads<0>();
     int src[L::LOADS];
     unsigned pitch = (unsigned)at.ks_r * 4u;
@@ -607,7 +623,6 @@ bwd_dq_generic_kernel(GenArgs a) {
     }
     const float lv = ok ? a.lse[sr] : BURST_NEG_INF;
     const float nlse = lv == BURST_NEG_INF ? BURST_NEG_INF : -lv;   // -inf: P = 0
-    const float nD = ok ? -a.D[sr] : 0.f;
     auto load_k = [&]() __attribute__((always_inline)) {
       const T* kr = at.K + (size_t)min(at.t * 32 + lr, at.Nc - 1) * at.ks_r;
 #pragma unroll
@@ -1194,7 +1209,7 @@ int launch_fwd_generic(const KParams& p, int dtype, const FwdIo& io, const Chunk
 }
 static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
   make_args(a, p, ch, n);
-  a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
+  a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv; a.O = io.O;
   a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
   a.parts = row_parts(io, ch, n, a.BH / a.group);
 }

@@ -84,6 +84,7 @@ struct BwdArgsLite {
   RowParts parts;                                // dK/dV
   Layout lay;
   Chunk ch[kMaxChunks];
+  const bf16* O;                                 // dQ: D is computed from it and written (nullptr: D is there)
 };
 
 __device__ __forceinline__ int s_swz(int row) { return S_ROWB == 128 ? ((row >> 1) & 7) : row_code(row); }
@@ -644,8 +645,33 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
   };
   bool have = advance(0);
-  if (!have && a.acc_dq && a.splits == 1) return;  // nothing visible: nothing to add
+  if (!have && a.acc_dq && a.splits == 1 && a.O == nullptr) return;  // nothing visible: nothing to add
   if (have) fetch(0);
+  // D of the workgroup's rows, in the order of bwd_prepare_kernel's sums: the same bits.  (Its own launch took 4.5 us of a
+  // call with gradients of 64 heads x 1024 rows, d = 64.)
+  float Dv = 0.f;
+  if (a.O != nullptr) {
+    constexpr int L2 = S_D <= 32 ? 2 : S_D <= 64 ? 4 : 8;   // pairs of 16-byte pieces that bwd_prepare_kernel has lanes for
+    const size_t at = a.lay.q_base(head) + (size_t)(ok ? row : 0) * a.lay.qs_r;
+    float x[L2];
+#pragma unroll
+    for (int ks = 0; ks < L2; ks++) {
+      x[ks] = 0.f;
+      if (ks >= S_KS) continue;
+      const bool there = ok && (!S_PAD || ks * 16 + h * 8 < d);
+      const bf16x8 g = s_load8(a.dO + at + ks * 16 + h * 8, there), o = s_load8(a.O + at + ks * 16 + h * 8, there);
+#pragma unroll
+      for (int t = 0; t < 8; t++) x[ks] = fma_in_order((float)o[t], (float)g[t], x[ks]);
+    }
+#pragma unroll
+    for (int off = L2 / 2; off > 0; off >>= 1)
+#pragma unroll
+      for (int ks = 0; ks < off; ks++) x[ks] = add_in_order(x[ks], x[ks + off]);
+    Dv = sum_both_halves(x[0]);
+    if (ok && h == 0) const_cast<float*>(a.D)[srow] = Dv;   // (every key range writes it: the fall-back below reads it again)
+  } else if (ok) {
+    Dv = a.D[srow];
+  }
 
   // The accumulators start at the dQ that is there: scale is folded into the exponent below
   // (dS^T comes out as scale * dS^T), so they hold dQ itself and a walk gives the same bits whether its
@@ -683,7 +709,6 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     auto scaled_p = [&](float x) __attribute__((always_inline)) {
       return S_PAD ? fast_exp2(__builtin_fmaf(above(x, a.scale, -nlse2), kLog2e, a.log2_scale)) : fast_exp2(__builtin_fmaf(x, a.c, nlse2));
     };
-    const float Dv = ok ? a.D[srow] : 0.f;
     int kaddr[S_KS], taddr[S_DB][2];
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
@@ -1126,7 +1151,7 @@ static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Ch
   a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale; a.log2_scale = log2f(p.scale);
   a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
-  a.lay = p.lay; a.d = p.d; a.n = n;
+  a.lay = p.lay; a.d = p.d; a.n = n; a.O = (const bf16*)io.O;
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
 }
 
