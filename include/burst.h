@@ -233,7 +233,9 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
  * contribution of all chunks; accumulate_dkv applies to every chunk's dK and dV.  dQ and the chunks' dK,
  * dV are fp32 or, with half_grads, of `dtype` (each value is the fp32 sum rounded once); half_grads
  * excludes both accumulate flags, and needs the workspace that burst_walk_workspace_bytes(...,
- * BURST_WALK_HALF_GRADS) asks for (BURST_ERR_SHAPE if a part of it that it cannot do without is missing). */
+ * BURST_WALK_HALF_GRADS) asks for (BURST_ERR_SHAPE if a part of it that it cannot do without is missing).
+ * With the workspace few or unequal walks over query tiles (grouped heads, few keys, causal masks) are also cut
+ * into parts whose partial dK, dV are added at the end. */
 int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
                    const float* lse, float* D, void* dQ, int accumulate_dq, int accumulate_dkv, int half_grads,
                    void* workspace, size_t workspace_bytes, const burst_params* p, void* stream);

@@ -468,6 +468,7 @@ DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
   if (generic && !generic_splittable(w)) return kWhole;
   const int bc = generic ? 32 : f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.hand ? 64 : 32;
   const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;   // (generic: the CUs)
+  if ((long long)k.group * ((k.Nq + br - 1) / br) < (generic ? 8 : f.hand ? 32 : 24)) return kWhole;   // (no walk is long enough, see below)
   long long total = 0, most = 0, rows = 0, blocks = 0;
   for (const WalkChunk& x : w) {
     if (x.p.block_mask != nullptr || !(dkv_kernels(&x.p, x.k) == f) || (f.hand && x.c.ks_r != w[0].c.ks_r)) return kWhole;
