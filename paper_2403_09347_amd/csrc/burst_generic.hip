@@ -1041,14 +1041,18 @@ merge_fwd_generic_kernel(GenArgs a) {
   const float m = wave_max(m_part), ref = m == BURST_NEG_INF ? 0.f : m;
   const float f = fast_exp2((m_part - ref) * kLog2e);
   float o[2] = {0.f, 0.f}, l = 0.f;
-#pragma unroll 4
-  for (int i = 0; i < a.splits; i++) {
-    float x[2];
-    row_load(x, a.part + ((size_t)i * rows + row) * a.d, lane, a.d);
-    const float fi = lane_value(f, i);
-    o[0] = __builtin_fmaf(fi, x[0], o[0]);
-    o[1] = __builtin_fmaf(fi, x[1], o[1]);
-    l = __builtin_fmaf(fi, lane_value(l_part, i), l);
+  for (int i = 0; i < a.splits; i += 4) {          // (four splits' loads together)
+    float x[4][2];
+#pragma unroll
+    for (int j = 0; j < 4; j++) row_load(x[j], a.part + ((size_t)min(i + j, a.splits - 1) * rows + row) * a.d, lane, a.d);
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (i + j >= a.splits) break;
+      const float fi = lane_value(f, i + j);
+      o[0] = __builtin_fmaf(fi, x[j][0], o[0]);
+      o[1] = __builtin_fmaf(fi, x[j][1], o[1]);
+      l = __builtin_fmaf(fi, lane_value(l_part, i + j), l);
+    }
   }
   RowState st[kRows];
   st[0] = row_state(a.fresh, a.O_acc, a.m, a.l, row, a.d, lane);
