@@ -498,6 +498,23 @@ DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
 size_t dkv_bytes(const KParams& k, const DkvParts& p) {
   return p.splits > 1 ? (size_t)p.most * 2 * p.rows * k.d * sizeof(float) : 0;
 }
+// Whether the first dQ launch of a walk computes D (the same bits as a launch of its own).  The d = 64 and padded kernels do
+// where they are not split by keys (each range would compute it, dQ of 32 over 8 heads x 3001 rows, d = 128: 116 / 125 us):
+// the launch saved is worth more than the two rows read before the first tile at every size, backward pass, us, own launch /
+// by dQ: d = 64, 32 heads x 512 causal rows 36.9 / 35.9, 64 x 1024 69.5 / 67.2, 32 x 4096 396 / 394, 32 x 8192 1086 / 1081, 32 x
+// 65536 rows x 64 keys 475 / 476; d = 96, 64 x 1024 128 / 125, 32 x 32768 x 96 492 / 487.  The d = 128 kernels lose as much (dQ
+// 153 / 163, the launch 9).  fp32: every row block starts with reads
+// that nothing covers (32 x 8192 rows x 32 keys, d = 64, 220 / 249, 16 x 2000 x 32, d = 128, 112 / 119, 16 x 3000 x 1000, 758 / 767),
+// so only walks whose blocks of 32 rows have a CU each, where the two forms take the GPU the same time (8 x 1000 causal, d = 64,
+// 85.3 / 85.8; 4 x 500 32.4 / 31.5) and the launch saved is the host's (256 rows x 1024 keys, 82 / 77 a pass; 8 x 700 x 1400, 247.8 / 246.0).
+bool d_by_dq(const std::vector<WalkChunk>& w, int splits) {
+  if (w.empty()) return false;
+  const Kernels f = fwd_kernels(&w[0].p, w[0].k);
+  if (f.plain != nullptr) return f.plain != &kD128p && splits == 1;
+  if (f.hand || w[0].p.dtype != BURST_F32 || (long long)w[0].k.B * w[0].k.H * (((long long)w[0].k.Nq + 31) / 32) > 256) return false;
+  for (const WalkChunk& x : w) if (!burst::fp32_tiles(x.k.d, x.k.lay, &x.c, 1)) return false;
+  return true;
+}
 size_t split_bytes(const KParams& k, int splits) {
   return splits > 1 ? (size_t)splits * k.B * k.H * k.Nq * ((size_t)k.d + 2) * sizeof(float) : 0;
 }
@@ -844,12 +861,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
       }
       return BURST_OK;
     }
-    // D by the first dQ launch itself where that is shorter than a launch of its own (4.5 us): walk of 256 rows x 1024 keys, fp32,
-    // 82 / 77 us, call with gradients of 64 heads x 1024 rows, d = 64, 93.6 / 91.2 (dQ 30.7 / 32.6).  The d = 128 kernels lose as much
-    // (32 over 8 heads x 3001 rows: dQ 153 / 163, the launch 9), and ranges of keys would each compute it (dQ 116 / 125).
-    const PlainFamily* const first_plain = w.empty() ? nullptr : fwd_kernels(&w[0].p, w[0].k).plain;
-    const bool fused = O != nullptr && !w.empty() && !fwd_kernels(&w[0].p, w[0].k).hand && first_plain != &kD128p &&
-                       (first_plain == nullptr || splits == 1);
+    const bool fused = O != nullptr && d_by_dq(w, splits);
     if (O != nullptr && !fused && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,

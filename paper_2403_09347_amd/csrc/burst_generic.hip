@@ -48,7 +48,7 @@ struct GenArgs {
   int n;                                          // chunks
   Chunk ch[kMaxChunks];
   // SPLIT: a block's tiles are shared by the wavefronts of several workgroups, whose partial results another launch merges
-  const void* O;                                  // dQ: D is computed from it and written (nullptr: D is there)
+  const void* O;                                  // dQ, VEC: D is computed from it and written (nullptr: D is there)
   float* part; int splits;                        // forward: [split][rows][d] O, then m and l, each [split][rows]; dQ: [split][rows][d]
   RowParts parts;                                 // dK/dV
 };
@@ -517,18 +517,25 @@ bwd_dq_generic_kernel(GenArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
   float nD = 0.f;                                  // minus D
-  if (a.O != nullptr) {                            // (every wavefront for itself)
+  if (VEC && a.O != nullptr) {                     // (every wavefront for itself)
+    // in the order of bwd_prepare_kernel's sums, which is a tree over 16-byte pieces: the same bits.  (As two chains of
+    // d / 2 products the largest error of D against 64 bits was 2.3 times as large at d = 128.)
+    constexpr int L2 = D <= 32 ? 4 : 8;            // pairs of pieces that bwd_prepare_kernel has lanes for
     const size_t from = a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
-    float x = 0.f;
+    float x[L2] = {};
 #pragma unroll
     for (int ks = 0; ks < NK; ks++) {
       const f32x4 g = R::fixed((const T*)a.dO + from, 8 * ks + 4 * h, a.d, ok), o = R::fixed((const T*)a.O + from, 8 * ks + 4 * h, a.d, ok);
 #pragma unroll
-      for (int j = 0; j < 4; j++) x = __builtin_fmaf(o[j], g[j], x);
+      for (int j = 0; j < 4; j++) x[ks % L2] = fma_in_order(o[j], g[j], x[ks % L2]);
     }
-    x = sum_both_halves(x);
-    nD = -x;
-    if (ok && h == 0 && w == 0) const_cast<float*>(a.D)[sr] = x;
+#pragma unroll
+    for (int off = L2 / 2; off > 0; off >>= 1)
+#pragma unroll
+      for (int ks = 0; ks < off; ks++) x[ks] = add_in_order(x[ks], x[ks + off]);
+    const float sum = sum_both_halves(x[0]);
+    nD = -sum;
+    if (ok && h == 0 && w == 0) const_cast<float*>(a.D)[sr] = sum;
   } else if (ok) {
     nD = -a.D[sr];
   }
@@ -1198,6 +1205,7 @@ static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
     if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, grid, s);
     return gen_launch<KIND, float, 128, true, 4>(a, grid, s);
   }
+  if (a.O != nullptr) return BURST_ERR_SHAPE;      // (the kernels below leave D to bwd_prepare)
   if (dtype == BURST_F32) return a.d <= 64 ? gen_launch<KIND, float, 64, false, 4>(a, grid, s) : gen_launch<KIND, float, 128, false, 4>(a, grid, s);
   return a.d <= 64 ? gen_launch<KIND, bf16, 64, false, 4>(a, grid, s) : gen_launch<KIND, bf16, 128, false, 4>(a, grid, s);
 }
@@ -1225,6 +1233,7 @@ int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Ch
 int launch_bwd_dkv_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};
   bwd_args(a, p, io, ch, n);
+  a.O = nullptr;
   return gen_dispatch<GEN_DKV>(a, dtype, s);
 }
 

@@ -668,7 +668,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
 #pragma unroll
       for (int ks = 0; ks < off; ks++) x[ks] = add_in_order(x[ks], x[ks + off]);
     Dv = sum_both_halves(x[0]);
-    if (ok && h == 0) const_cast<float*>(a.D)[srow] = Dv;   // (every key range writes it: the fall-back below reads it again)
+    if (ok && h == 0) const_cast<float*>(a.D)[srow] = Dv;   // (the fall-back below reads it again)
   } else if (ok) {
     Dv = a.D[srow];
   }
