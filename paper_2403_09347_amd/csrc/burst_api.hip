@@ -428,12 +428,14 @@ int walk_splits(const std::vector<WalkChunk>& w) {
     if (k.window > 0) lo = std::max(lo, k.q_off + k.Nq - 128 - k.window + 1 - x.c.k_off);
     if (hi > lo) tiles += (hi - lo + 63) / 64;
   }
-  // The padded kernels' tiles take twice the time: 6 of them are a range where the blocks have a CU each, and walks of 12 are
-  // split (8 x 900 causal rows, d = 96, forward and dQ 33 + 35 us, in 2 26 + 27 with the merges; 16 x 850, 33 + 36, 28 + 29;
-  // 32 x 777, 224 blocks, 32 + 34, 36 + 36).
+  // The padded kernels' tiles take twice the time: up to 160 blocks 6 of them are a range.  Walks of 18 are split there (three
+  // ranges: 16 x 1216 causal rows, d = 96, 160 blocks, forward 39.9 / 36.8 us, backward pass 124 / 120; 15 x 1130, 135, 38.4 / 35.6,
+  // 120 / 113), walks of 12 while both ranges have a CU each, up to 128 blocks (16 x 900, 32.8 / 29.3, 99 / 95); past that some CUs
+  // have two workgroups of such a launch and others one (17 x 1024, 136, 35.0 / 36.4, 108 / 111; 18 x 900, 144, 33.0 / 34.6, 99 / 102; 20 x
+  // 1000, 160, 35.2 / 37.3, 109 / 112).  From 161 blocks on two ranges as elsewhere (24 x 1000, 192, 35.3 / 40.4, not split).
   const bool pad = f.plain != &kD64 && f.plain != &kD128p && blocks <= 160;
   const long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
-  return s < 2 || tiles < (pad ? 12 : 20) ? 1 : (int)s;
+  return s < 2 || tiles < (!pad ? 20 : blocks > 128 ? 18 : 12) ? 1 : (int)s;
 }
 int dq_launches(const std::vector<WalkChunk>& w) {
   int n = 0;
