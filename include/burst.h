@@ -242,6 +242,10 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
 /* Bytes of workspace that either of the two can use (or, under these flags, needs) for these arguments;
  * 0: none.  Host logic, no device call. */
 size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int flags);
+/* How burst_walk_bwd lays out its first dK/dV launch for these arguments: 0 = a workgroup per block of keys, 1 = the
+ * walks over query tiles cut into parts (with the workspace), 2 = one workgroup per CU that takes several blocks in
+ * turn; a negative burst_status for invalid arguments.  Host logic, no device call. */
+int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_params* p, int with_workspace);
 #define BURST_WALK_HALF_GRADS 1   /* for burst_walk_bwd with half_grads */
 #define BURST_WALK_NO_STATE 2     /* for burst_walk_fwd without O_acc, m, l */
 

@@ -23,7 +23,7 @@ EXPORTS = [
     "burst_materialized_workspace_bytes", "burst_local_fwd_materialized", "burst_workspace_bytes",
     "burst_materialized_bwd_workspace_bytes", "burst_local_bwd_materialized", "burst_set_kernel_family",
     "burst_kernel_family_for", "burst_local_bwd_static", "burst_probe_mfma", "burst_probe_atomic_dq",
-    "burst_walk_fwd", "burst_walk_bwd", "burst_walk_workspace_bytes",
+    "burst_walk_fwd", "burst_walk_bwd", "burst_walk_workspace_bytes", "burst_walk_dkv_form",
 ]
 
 
@@ -114,6 +114,8 @@ def load():
     cp, sz, ci = ctypes.POINTER(BurstChunk), ctypes.c_size_t, ctypes.c_int
     lib.burst_walk_workspace_bytes.argtypes = [cp, ci, pp, ci]
     lib.burst_walk_workspace_bytes.restype = sz
+    lib.burst_walk_dkv_form.argtypes = [cp, ci, pp, ci]
+    lib.burst_walk_dkv_form.restype = ci
     lib.burst_walk_fwd.argtypes = [vp, cp, ci, fp, fp, fp, vp, fp, vp, sz, pp, vp]
     lib.burst_walk_fwd.restype = ctypes.c_int
     lib.burst_walk_bwd.argtypes = [vp, cp, ci, vp, vp, fp, fp, vp, ci, ci, ci, vp, sz, pp, vp]
@@ -386,6 +388,15 @@ BURST_WALK_HALF_GRADS, BURST_WALK_NO_STATE = 1, 2
 
 def burst_walk_workspace_bytes(chunks, p, flags=0):
     return int(load().burst_walk_workspace_bytes(chunks, len(chunks), ctypes.byref(p), int(flags)))
+
+
+def burst_walk_dkv_form(chunks, p, with_workspace=True):
+    """How the backward walk's (first) dK/dV launch is laid out: 0 a workgroup per block of keys, 1 walks cut into parts,
+    2 one workgroup per CU that takes several blocks in turn."""
+    form = load().burst_walk_dkv_form(chunks, len(chunks), ctypes.byref(p), 1 if with_workspace else 0)
+    if form < 0:
+        _check(form, "burst_walk_dkv_form")
+    return form
 
 
 def _bytes(ws):

@@ -19,6 +19,7 @@ int launch_fwd_mfma(const KParams&, const FwdIo&, const Chunk*, int, hipStream_t
 int launch_fwd_generic(const KParams&, int, const FwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dq_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dkv_mfma(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t, int key_waves);
+bool dkv_chained(const KParams&, const Chunk*, int);
 int launch_bwd_dq_generic(const KParams&, int, const BwdIo&, const Chunk*, int, hipStream_t);
 int launch_bwd_dkv_generic(const KParams&, int, const BwdIo&, const Chunk*, int, hipStream_t);
 // the plainly written kernels of burst_plain_mfma.h, one namespace per build
@@ -768,6 +769,19 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
   return need;
 }
 
+int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_params* p, int with_workspace) {
+  std::vector<WalkChunk> w;
+  const int st = walk_chunks(chunks, n_chunks, p, false, w);
+  if (st != BURST_OK || w.empty() || w[0].k.Nq == 0) return st;
+  if (with_workspace && dkv_parts(w).splits > 1) return 1;
+  int form = -1;
+  for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
+    if (form < 0) form = f.hand && f.key_waves == 4 && burst::dkv_chained(kc, c, n) ? 2 : 0;
+    return (int)BURST_OK;
+  });
+  return form;
+}
+
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
                    void* O_out, float* lse, void* workspace, size_t workspace_bytes,
                    const burst_params* p, void* stream) {
@@ -916,6 +930,6 @@ const char* burst_strerror(int status) {
   }
 }
 
-int burst_version(void) { return 112; }
+int burst_version(void) { return 113; }
 
 }  // extern "C"

@@ -651,30 +651,31 @@ static bool chained(DkvArgs& a, long long nb) {
   a.items = (int)nb;
   a.turn = a.n == 1 && a.causal ? 0 : a.n > 1 && a.per > 0 && a.per % 256 == 0 ? a.n : 1;
   const int tiles = (a.Nq + DKV_BR - 1) / DKV_BR;
-  int most_blocks = 0;
+  auto blocks_of = [&](int c) { return (a.ch[c].Nc + BC - 1) / BC; };
+  auto range_of = [&](int c, int b) { return row_range(a.Nq, a.causal, a.window, a.q_off, a.ch[c].k_off, a.ch[c].Nc, b * BC, BC, DKV_BR); };
   long long all = 0;
-  for (int c = 0; c < a.n; c++) most_blocks = std::max(most_blocks, (a.ch[c].Nc + BC - 1) / BC);
-  int walk[kMaxChunks][256];                       // tiles of a block
-  if (most_blocks > 256) return false;
   for (int c = 0; c < a.n; c++) {
-    if (a.ch[c].ks_r != a.lay.qs_r) return false;
-    for (int b = 0; b * BC < a.ch[c].Nc; b++) {
-      const RowRange r = row_range(a.Nq, a.causal, a.window, a.q_off, a.ch[c].k_off, a.ch[c].Nc, b * BC, BC, DKV_BR);
-      walk[c][b] = r.hi - r.lo;
-      all += (long long)walk[c][b] * a.H;
+    if (blocks_of(c) > 256 || a.ch[c].ks_r != a.lay.qs_r) return false;
+    for (int b = 0; b < blocks_of(c); b++) {
+      const RowRange r = range_of(c, b);
+      all += (long long)(r.hi - r.lo) * a.H;
       // (one tile is walked as two: only where the rows of the second one, past Nq, are zeros that the first one has too)
-      if (walk[c][b] == 1 && (r.hi != tiles || a.Nq % DKV_BR == 0)) return false;
+      if (r.hi - r.lo == 1 && (r.hi != tiles || a.Nq % DKV_BR == 0)) return false;
     }
   }
   if (all > 36 * nb) return false;
   int share[256] = {};                             // in fifths of a tile: 5 a tile, 15 a block, 6 a hidden block (turns change the order only)
   for (int c = 0; c < a.n; c++) {
-    const int blocks = (a.ch[c].Nc + BC - 1) / BC, total = a.H * blocks, per = (total + 7) / 8;
+    const int blocks = blocks_of(c), total = a.H * blocks, per = (total + 7) / 8;
+    int cost[256];                                 // of a block
+    for (int b = 0; b < blocks; b++) {
+      const RowRange r = range_of(c, b);
+      cost[b] = r.hi > r.lo ? 5 * (r.hi - r.lo) + 15 : 6;
+    }
     for (int x = 0; x < 8; x++)
       for (int at = 0, b = x * per % blocks; at < per && x * per + at < total; at++, b = b + 1 == blocks ? 0 : b + 1) {
         const int id = a.ch[c].first_block + 8 * at + x, round = id >> 8;
-        const int wg = a.turn == 0 && (round & 1) ? (id & 255) ^ 248 : id & 255;
-        share[wg] += walk[c][b] ? 5 * walk[c][b] + 15 : 6;
+        share[a.turn == 0 && (round & 1) ? (id & 255) ^ 248 : id & 255] += cost[b];
       }
   }
   long long sum = 0;
@@ -682,19 +683,26 @@ static bool chained(DkvArgs& a, long long nb) {
   for (int i = 0; i < 256; i++) { sum += share[i]; most = std::max(most, share[i]); }
   return 100LL * 256 * most <= 108 * sum;
 }
+// Fills all but the pointers of a call; returns the number of its workgroups.
+static long long lay_out(DkvArgs& a, const KParams& p, const Chunk* ch, int n, int key_waves, int splits) {
+  a.Nq = p.Nq; a.H = p.B * p.H / p.group; a.group = p.group;     // workgroups are laid out over key/value heads
+  a.c = p.scale * kLog2e; a.scale = p.scale; a.causal = p.causal; a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
+  a.n = n; a.lay = p.lay;
+  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
+  return chunk_grid(a.ch, n, a.H, 32 * key_waves, a.per, key_waves == 4 ? splits : 1);
+}
+bool dkv_chained(const KParams& p, const Chunk* ch, int n) {
+  DkvArgs a;
+  const long long nb = lay_out(a, p, ch, n, 4, 1);
+  return ch[0].bmask == nullptr && chained(a, nb);
+}
 int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream, int key_waves) {
   DkvArgs a;
   a.Q = (const bf16*)io.Q; a.dO = (const bf16*)io.dO; a.lse = io.lse; a.D = io.D;
-  a.Nq = p.Nq; a.H = p.B * p.H / p.group; a.group = p.group;     // workgroups are laid out over key/value heads
-  a.causal = p.causal; a.acc_dkv = io.acc_dkv; a.half = io.half;
-  a.c = p.scale * kLog2e; a.scale = p.scale;
-  a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
-  a.n = n; a.lay = p.lay;
+  a.acc_dkv = io.acc_dkv; a.half = io.half;
   const bool listed = ch[0].bmask != nullptr || p.group > 1;
   if (key_waves != 4 && !(key_waves == 2 && listed)) return BURST_ERR_SHAPE;
-  const int bc = 32 * key_waves;
-  for (int i = 0; i < n; i++) a.ch[i] = ch[i];
-  const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, key_waves == 4 ? io.kv_splits : 1);
+  const long long nb = lay_out(a, p, ch, n, key_waves, io.kv_splits);
   a.parts = row_parts(io, ch, n, a.H);
   if (a.parts.splits > 1 && (key_waves != 4 || ch[0].bmask != nullptr)) return BURST_ERR_SHAPE;
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
@@ -707,8 +715,11 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
     const int st = listed ? launch_shape<true, 4, true>(a, nb, stream) : launch_shape<false, 4, true>(a, nb, stream);
     return st != BURST_OK ? st : launch_merge_dkv<128, DkvShape<4>::BC, DKV_BR, false>(a, stream);
   }
-  if (!listed && chained(a, nb)) return launch_shape<false, 4, false, true>(a, 256, stream);
-  if (!listed) return launch_shape<false, 4, false>(a, nb, stream);
+  if (!listed) {                                   // (the validating pass sees to the attributes of both forms; the rule is asked once)
+    if (t_validate_only || chained(a, nb))
+      if (const int st = launch_shape<false, 4, false, true>(a, 256, stream); st != BURST_OK || !t_validate_only) return st;
+    return launch_shape<false, 4, false>(a, nb, stream);
+  }
   return key_waves == 4 ? launch_shape<true, 4, false>(a, nb, stream) : launch_shape<true, 2, false>(a, nb, stream);
 }
 

@@ -23,3 +23,24 @@ def test_key_ranges_of_the_padded_kernels(H, N, ranges):
         p = B.params(1, H, N, 0, d, "bf16", 0.1, causal=True)
         want = 0 if ranges == 1 else ranges * H * N * (d + 2) * 4
         assert workspace(p, [N], flags=B.BURST_WALK_NO_STATE) == want
+
+
+def form(H, Nq, rows, workspace, **kw):
+    p = B.params(1, H, Nq, 0, 128, "bf16", 0.1, **kw)
+    chunks = (B.BurstChunk * len(rows))()
+    for i, c in enumerate(chunks):
+        c.K, c.V, c.Nc, c.k_off = 4096, 8192, rows[i], sum(rows[:i])
+    return B.burst_walk_dkv_form(chunks, p, workspace)
+
+
+def test_forms_of_dkv_launches():
+    for ws in (False, True):
+        assert form(32, 512, [512] * 16, ws, causal=True, q_off=15 * 512) == 2              # many short walks
+        assert form(32, 4096, [4096] * 8, ws) == 0                                          # 64 tiles each: long ones
+        assert form(32, 2048, [2048], ws, causal=True) == 2 and form(32, 3000, [3000], ws, causal=True) == 0   # equal shares or not
+        assert form(257, 64, [128], ws) == 0 and form(8, 512, [512], ws) == 0               # one whole tile; few workgroups
+        assert form(32, 512, [512] * 16, ws, q_strides=(512 * 4096, 128, 4096)) == 0        # rows of Q and K at different distances
+    assert form(32, 3008, [3008], True, causal=True, kv_heads=8) == 1 and form(32, 3008, [3008], False, causal=True, kv_heads=8) == 0
+    assert form(32, 0, [512], True) == 0 and form(32, 512, [0], True) == 0
+    with pytest.raises(B.BurstError):
+        form(32, 512, [512], True, kv_heads=5)
