@@ -454,15 +454,16 @@ int dq_launches(const std::vector<WalkChunk>& w) {
 // 32 over 8 x 2048, d = 64, 354 / 156 in 8 (153 in 6, 167 in 12); 8 over 2 x 1000 332 / 98 in 16 (101 in 12); 8 x 3000, d = 64,
 // 174 / 124 in 5 (123, 124); 32 x 777, d = 96, 123 / 107 in 3 (111, 117); 8 x 8000, d = 64, 511 / 443 in 2 (447 in 3); not
 // cut: 64 x 1024, d = 64, 98 (in 2: 112), 16 x 3000 279 (301), 16 x 4096 403 (440).
-struct DkvParts { int splits, most, tiles; long long rows; };
-constexpr DkvParts kWhole = {1, 1, 1, 0};
+// Partial gradients have room for the keys of a chunk from its first block with several parts to its last: hidden chunks and
+// the short ends of masked ones take none.
+constexpr burst::RowPlan kWhole = {{nullptr, 1, 1, 1, 0}, {}};
 // Workgroups per block for at most `most` parts: whole (head, part) columns go to the 8 XCDs, so their number should be a
 // multiple of 8 (workgroups without a part end at once).
 int part_columns(long long heads, long long most) {
   for (long long s = most; s < most + 8; s++) if (heads * s % 8 == 0) return (int)s;
   return (int)most;
 }
-DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
+burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
   if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return kWhole;
   const Kernels f = dkv_kernels(&w[0].p, w[0].k);
   if (f.plain == &kD128p) return kWhole;           // (it runs only when its family is forced)
@@ -472,33 +473,49 @@ DkvParts dkv_parts(const std::vector<WalkChunk>& w) {
   const int bc = generic ? 32 : f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.hand ? 64 : 32;
   const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;   // (generic: the CUs)
   if ((long long)k.group * ((k.Nq + br - 1) / br) < (generic ? 8 : f.hand ? 32 : 24)) return kWhole;   // (no walk is long enough, see below)
-  long long total = 0, most = 0, rows = 0, blocks = 0;
+  auto walk_of = [&](const WalkChunk& x, int key0) {   // tiles of a block of keys, of all heads of the group
+    const burst::RowRange r = burst::row_range(k.Nq, k.causal, k.window, k.q_off, x.c.k_off, x.c.Nc, key0, bc, br);
+    return (long long)(r.hi - r.lo) * k.group;
+  };
+  long long total = 0, most = 0, blocks = 0;
   for (const WalkChunk& x : w) {
     if (x.p.block_mask != nullptr || !(dkv_kernels(&x.p, x.k) == f) || (f.hand && x.c.ks_r != w[0].c.ks_r)) return kWhole;
-    rows += heads * x.c.Nc;
     blocks += heads * ((x.c.Nc + bc - 1) / bc);
     if (blocks > 2 * slots) return kWhole;         // (no walk is 1.9 times the average place's then)
     for (int key0 = 0; key0 < x.c.Nc; key0 += bc) {
-      const burst::RowRange r = burst::row_range(k.Nq, k.causal, k.window, k.q_off, x.c.k_off, x.c.Nc, key0, bc, br);
-      const long long walk = (long long)(r.hi - r.lo) * k.group;
+      const long long walk = walk_of(x, key0);
       total += walk * heads;
       most = std::max(most, walk);
     }
   }
+  auto cut = [&](long long parts, int tiles) {
+    burst::RowPlan plan = {{nullptr, part_columns(heads, parts), (int)parts, tiles, 0}, {}};
+    burst::RowParts& p = plan.parts;
+    for (size_t i = 0; i < w.size(); i++) {
+      int lo = -1, hi = 0;
+      for (int key0 = 0; key0 < w[i].c.Nc; key0 += bc)
+        if (p.of((int)walk_of(w[i], key0)) > 1) { lo = lo < 0 ? key0 : lo; hi = std::min(key0 + bc, w[i].c.Nc); }
+      plan.span[i] = {p.rows, std::max(lo, 0), hi - std::max(lo, 0)};
+      p.rows += (int)(heads * plan.span[i].keys);
+    }
+    return plan;
+  };
+  if (most > 0x7fffffffLL) return kWhole;
   if (generic) {
     // as many as there are CUs for, four tiles each at least; two also where a causal launch fits the CUs once.
     // us a launch, whole / by the rule: 1024 keys x 256 rows, one head, d = 64, 28 / 19 in 2; 500 x 500, d = 128, 64 / 30 in 4 (2: 41);
     // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).
     long long parts = std::min({256 / blocks, most / 4, 16LL});
     if (parts < 2 && blocks <= 256 && most >= 16 && 10 * most * slots >= 18 * total) parts = 2;
-    return parts < 2 || most > 0x7fffffffLL ? kWhole : DkvParts{part_columns(heads, parts), (int)parts, (int)((most + parts - 1) / parts), rows};
+    return parts < 2 ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
   }
-  if (most < 24 || most > 0x7fffffffLL || 10 * most * slots < 19 * total) return kWhole;
+  if (most < 24 || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on
   const long long splits = std::min({16LL, ratio, most / (f.plain != nullptr ? 8 : 16)});
-  return splits < 2 ? kWhole : DkvParts{part_columns(heads, splits), (int)splits, 8, rows};
+  return splits < 2 ? kWhole : cut(splits, 8);
 }
-size_t dkv_bytes(const KParams& k, const DkvParts& p) {
+size_t dkv_bytes(const KParams& k, const burst::RowPlan& plan) {
+  const burst::RowParts& p = plan.parts;
   return p.splits > 1 ? (size_t)p.most * 2 * p.rows * k.d * sizeof(float) : 0;
 }
 // Whether the first dQ launch of a walk computes D (the same bits as a launch of its own).  The d = 64 and padded kernels do
@@ -707,7 +724,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, 1, 1, 1, nullptr};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, nullptr};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -773,7 +790,7 @@ int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_par
   std::vector<WalkChunk> w;
   const int st = walk_chunks(chunks, n_chunks, p, false, w);
   if (st != BURST_OK || w.empty() || w[0].k.Nq == 0) return st;
-  if (with_workspace && dkv_parts(w).splits > 1) return 1;
+  if (with_workspace && dkv_parts(w).parts.splits > 1) return 1;
   int form = -1;
   for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
     if (form < 0) form = f.hand && f.key_waves == 4 && burst::dkv_chained(kc, c, n) ? 2 : 0;
@@ -861,8 +878,9 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   hipStream_t s = (hipStream_t)stream;
   int splits = walk_splits(w);
   if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
-  DkvParts parts = dkv_parts(w);
+  burst::RowPlan parts = dkv_parts(w);
   if (workspace == nullptr || workspace_bytes < dkv_bytes(k, parts)) parts = kWhole;
+  parts.parts.part = (float*)workspace;
   auto zero = [&](void* ptr, long long n) { return burst::launch_zero_fill((float*)ptr, n, half, s); };
   // dQ as bf16 by several launches: fp32 in the workspace between them
   const bool staged = half && have_q && splits == 1 && !w.empty() && dq_launches(w) > 1;
@@ -881,7 +899,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
     if (O != nullptr && !fused && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,
-                (float*)workspace, parts.splits, parts.most, parts.tiles, nullptr};
+                parts.parts.splits > 1 ? &parts : nullptr, nullptr};
     e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       BwdIo one = io;
       one.acc_dq = accumulate_dq != 0 || !first;

@@ -95,7 +95,7 @@ merge_dkv_kernel(A a) {
   int c = 0;
   while (c + 1 < a.n && row >= a.ch[c + 1].first_row) c++;
   const Chunk& C = a.ch[c];
-  const int kvhead = (row - C.first_row) / C.Nc, key = row - C.first_row - kvhead * C.Nc;
+  const int kvhead = (row - C.first_row) / C.span_keys, key = C.span_lo + row - C.first_row - kvhead * C.span_keys;
   const RowRange range = row_range(a.Nq, a.causal, a.window, a.q_off, C.k_off, C.Nc, key / BC * BC, BC, BR);
   const int parts = a.parts.of((range.hi - range.lo) * a.group);
   if (parts == 1) return;                          // written by its workgroup
@@ -148,12 +148,14 @@ static int launch_merge_dkv(const A& a, hipStream_t stream) {
   BURST_LAUNCH((merge_dkv_kernel<D, BC, BR, PAD, A>), dim3((unsigned)((a.parts.rows + 3) / 4)), dim3(256), 0, stream, a);
   return launch_status();
 }
-inline RowParts row_parts(const BwdIo& io, const Chunk* ch, int n, long long heads) {
-  RowParts p = {io.kv_part, io.kv_splits > 1 ? io.kv_splits : 1, io.kv_most, io.kv_tiles > 0 ? io.kv_tiles : 1, 0};
-  long long rows = 0;
-  for (int i = 0; i < n; i++) rows += heads * ch[i].Nc;
-  p.rows = p.splits > 1 ? (int)rows : 0;
-  return p;
+// (after the chunks; all chunks of the call without flags where its walks are cut)
+template <typename A>
+static void set_row_parts(A& a, const BwdIo& io) {
+  a.parts = io.parts != nullptr ? io.parts->parts : RowParts{nullptr, 1, 1, 1, 0};
+  for (int i = 0; i < a.n && io.parts != nullptr; i++) {
+    const RowSpan& s = io.parts->span[i];
+    a.ch[i].first_row = s.first; a.ch[i].span_lo = s.lo; a.ch[i].span_keys = s.keys;
+  }
 }
 
 __device__ __forceinline__ bf16x8 cat4(bf16x4 a, bf16x4 b) {

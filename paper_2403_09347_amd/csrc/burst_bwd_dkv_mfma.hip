@@ -605,14 +605,15 @@ burst_bwd_dkv_kernel(DkvArgs a) {
   // epilogue: keys are owned by this wavefront alone. C layout: lane = d column, regs = keys.
   if constexpr (PARTS) {
     void *dk_at, *dv_at;
+    int keys = Nc, k0 = key0;
     if (parts > 1) {
-      float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + a.ch[chunk].first_row + (size_t)head * Nc) * 128;
-      dk_at = to; dv_at = to + (size_t)a.parts.rows * 128;
+      dk_at = a.parts.at(part, false, a.ch[chunk], head, 128); dv_at = a.parts.at(part, true, a.ch[chunk], head, 128);
+      keys = a.ch[chunk].span_keys; k0 -= a.ch[chunk].span_lo;
     } else {
       const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
       dk_at = (char*)a.ch[chunk].dK + at; dv_at = (char*)a.ch[chunk].dV + at;
     }
-    store_dkv<4, false>(dk, dv, dk_at, dv_at, Nc, 128, key0, lr, h, a.scale, parts > 1 ? 0 : a.half, parts > 1 ? 0 : a.acc_dkv);
+    store_dkv<4, false>(dk, dv, dk_at, dv_at, keys, 128, k0, lr, h, a.scale, parts > 1 ? 0 : a.half, parts > 1 ? 0 : a.acc_dkv);
   } else if constexpr (!CHAIN) {
     const size_t at = (size_t)head * Nc * 128 * (a.half ? 2 : 4);
     store_dkv<4, false>(dk, dv, (char*)a.ch[chunk].dK + at, (char*)a.ch[chunk].dV + at, Nc, 128, key0, lr, h, a.scale, a.half, a.acc_dkv);
@@ -702,8 +703,8 @@ int launch_bwd_dkv_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int 
   a.acc_dkv = io.acc_dkv; a.half = io.half;
   const bool listed = ch[0].bmask != nullptr || p.group > 1;
   if (key_waves != 4 && !(key_waves == 2 && listed)) return BURST_ERR_SHAPE;
-  const long long nb = lay_out(a, p, ch, n, key_waves, io.kv_splits);
-  a.parts = row_parts(io, ch, n, a.H);
+  const long long nb = lay_out(a, p, ch, n, key_waves, io.parts != nullptr ? io.parts->parts.splits : 1);
+  set_row_parts(a, io);
   if (a.parts.splits > 1 && (key_waves != 4 || ch[0].bmask != nullptr)) return BURST_ERR_SHAPE;
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
   if (nb == 0) return BURST_OK;

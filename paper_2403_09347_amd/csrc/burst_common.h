@@ -75,12 +75,15 @@ struct Chunk {
   const void* K; const void* V;
   void* dK; void* dV;                // backward only
   const uint8_t* bmask;              // block flags of this chunk (nullptr = none), [ceil(Nq/bsize)][bpitch]
-  long long bhstride;                // bytes between the flag matrices of consecutive query heads (0 = shared)
+  union {
+    long long bhstride;              // bytes between the flag matrices of consecutive query heads (0 = shared)
+    struct { int span_lo, span_keys; };   // split dK/dV walks (which have no flags): see RowSpan
+  };
   long long k_off;                   // global position of key 0
   long long ks_b, ks_h, ks_r;        // element strides of K and V: batch, head, row
   int Nc, bpitch;
   int first_block;                   // dK/dV kernels: workgroups of the chunks before this one
-  int first_row;                     // split dK/dV walks: keys (of all heads) of the chunks before this one
+  int first_row;                     // split dK/dV walks: rows of partial gradients of the chunks before this one
   // element offset of row 0 of key/value head `kvhead`, which counts batch x heads
   __host__ __device__ size_t kv_base(int kvhead, int kv_heads) const {
     const int b = kvhead / kv_heads;
@@ -116,25 +119,32 @@ struct BwdIo {
   int acc_dq, acc_dkv;               // add to what the gradient buffers hold
   int half;                          // dQ, dK, dV are bf16 tensors (the inputs' type) instead of fp32; nothing accumulates then
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
-  float* kv_part; int kv_splits, kv_most, kv_tiles;   // kv_splits > 1: see RowParts
+  const struct RowPlan* parts;       // dK/dV: how the walks are cut (nullptr: not at all)
   const void* O;                     // dQ, plain and generic kernels: D = rowsum(dO o O) is computed and written first (nullptr: it is there)
 };
 
 // How a dK/dV launch deals out its work.  A workgroup's walk are the query tiles its keys are visible to, of all heads of
 // the group: very unequal under a causal mask, and few workgroups where there are few keys.  splits > 1: the
 // walk of a block of keys is cut into parts of at most about `tiles` tiles, each a workgroup of its own that leaves fp32
-// partial dK, dV in `part` ([part][dK, dV][keys of all chunks and heads][d]); another launch adds them in a fixed order.
-// Blocks with one part write their gradients themselves.
+// partial dK, dV in `part` ([part][dK, dV][rows][d]); another launch adds them in a fixed order.  Blocks with one part write
+// their gradients themselves: of each chunk the keys from the first to the last block with several have rows there, head
+// after head (RowSpan; the kernels have it in the Chunk, whose cache line is there when they need it).
+struct RowSpan { int first, lo, keys; };   // a chunk's first row; its keys that have some, of each head
 struct RowParts {
   float* part;
   int splits;                        // workgroups per block of keys
   int most, tiles;                   // most parts of a block (<= splits); tiles of a part
-  int rows;                          // keys of all chunks and heads
+  int rows;                          // keys that have rows, of all chunks and heads
   __host__ __device__ int of(int walk) const {
     const int n = (walk + tiles - 1) / tiles;
     return n < 1 ? 1 : n < most ? n : most;
   }
+  // where part `i` of key/value head `head` has the keys of a chunk's span
+  __device__ float* at(int i, bool dv, const Chunk& C, int head, int d) const {
+    return part + ((size_t)(2 * i + dv) * rows + C.first_row + (size_t)head * C.span_keys) * d;
+  }
 };
+struct RowPlan { RowParts parts; RowSpan span[kMaxChunks]; };
 // The query tiles (BR rows) of one head that see a key of the block [key0, key0 + BC) of a chunk: [lo, hi).
 struct RowRange { int lo, hi; };
 __host__ __device__ inline RowRange row_range(int Nq, int causal, long long window, long long q_off, long long k_off, int Nc,
@@ -260,14 +270,12 @@ inline long long chunk_grid(Chunk* ch, int n, long long heads, int block, int& p
     const long long blocks = (ch[i].Nc + block - 1) / block;
     return splits > 1 ? part_grid(heads, blocks, splits) : grid_blocks(heads, blocks);
   };
-  long long nb = 0, rows = 0;
+  long long nb = 0;
   per = n > 0 ? (int)count(0) : 0;
   for (int i = 0; i < n; i++) {
     const long long here = count(i);
     if (here != per) per = 0;
     ch[i].first_block = (int)nb;
-    ch[i].first_row = (int)rows;                   // (used by split launches only, which are small)
-    rows += heads * ch[i].Nc;
     nb += here;
     if (nb > 0x7fffffffLL) break;                  // (the launchers refuse it)
   }

@@ -1008,16 +1008,18 @@ bwd_dkv_generic_kernel(GenArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) gsh[w * WS + (db * 16 + r) * 64 + lane] = which ? dv[db][r] : dk[db][r];
     __syncthreads();
-    float* const to = SPLIT ? a.parts.part + ((size_t)(2 * part + which) * a.parts.rows + C.first_row) * a.d : nullptr;
-    void* const base = parts > 1 ? (void*)to : which ? C.dV : C.dK;
+    // the head's keys: partial ones of the chunk's span, or the chunk's own
+    void* base = which ? C.dV : C.dK;
+    size_t first = (size_t)kvhead * Nc;
+    if (SPLIT && parts > 1) { base = a.parts.at(part, which, C, kvhead, a.d); first = -(size_t)C.span_lo; }
     const float f = which ? 1.f : a.scale;
     const int half = parts > 1 ? 0 : a.half, acc = parts > 1 ? 0 : a.acc_dkv;
 #pragma unroll
     for (int rr = 0; rr < 16 / W; rr++) {
       const int r = w * (16 / W) + rr, k = key0 + reg_row(r, h);
       if (k >= Nc) continue;
-      float* const out = (float*)base + ((size_t)kvhead * Nc + k) * a.d;
-      T* const out16 = (T*)base + ((size_t)kvhead * Nc + k) * a.d;
+      float* const out = (float*)base + (first + k) * a.d;
+      T* const out16 = (T*)base + (first + k) * a.d;
 #pragma unroll
       for (int db = 0; db < NB; db++) {
         float v = 0.f;
@@ -1110,7 +1112,7 @@ merge_dkv_generic_kernel(GenArgs a) {
   int c = 0;
   while (c + 1 < a.n && row >= a.ch[c + 1].first_row) c++;
   const Chunk& C = a.ch[c];
-  const int kvhead = (row - C.first_row) / C.Nc, key = row - C.first_row - kvhead * C.Nc;
+  const int kvhead = (row - C.first_row) / C.span_keys, key = C.span_lo + row - C.first_row - kvhead * C.span_keys;
   int lo, hi;
   row_tiles(a, C, key & ~31, lo, hi);
   const int parts = a.parts.of(max(hi - lo, 0) * a.group);
@@ -1178,13 +1180,11 @@ static int gen_split(GenArgs& a, long long grid, hipStream_t s) {      // (fp32,
 }
 template <int KIND>
 static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
-  long long grid = 0, rows = 0;
+  long long grid = 0;
   if (KIND == GEN_DKV) {
     for (int i = 0; i < a.n; i++) {
       const long long blocks = ((long long)a.ch[i].Nc + 31) / 32;
       a.ch[i].first_block = (int)grid;
-      a.ch[i].first_row = (int)rows;               // (used by split launches only, which are small)
-      rows += (long long)(a.BH / a.group) * a.ch[i].Nc;
       grid += a.parts.splits > 1 ? part_grid(a.BH / a.group, blocks, a.parts.splits) : grid_blocks(a.BH / a.group, blocks);
       if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
     }
@@ -1223,7 +1223,7 @@ static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk*
   make_args(a, p, ch, n);
   a.Q = io.Q; a.dO = io.dO; a.lse = io.lse; a.D = io.D; a.dQ = io.dQ; a.half = io.half; a.acc_dq = io.acc_dq; a.acc_dkv = io.acc_dkv; a.O = io.O;
   a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
-  a.parts = row_parts(io, ch, n, a.BH / a.group);
+  set_row_parts(a, io);
 }
 int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};

@@ -844,7 +844,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   // the workgroups of all chunks, chunk after chunk
-  const Chunk& C = a.ch[chunk_at((int)blockIdx.x, a.ch, a.n, a.per)];
+  const int chunk = chunk_at((int)blockIdx.x, a.ch, a.n, a.per);
+  const Chunk& C = a.ch[chunk];
   int kvhead, kblk, part = 0;                      // a.H counts key/value heads here
   const int bid = (int)blockIdx.x - C.first_block, blocks = (C.Nc + SK_BC - 1) / SK_BC;
   if constexpr (PARTS) {
@@ -1057,8 +1058,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
   if (PARTS && parts > 1) {                        // (infinities and NaN: merge_dkv_kernel sees to them)
-    float* const to = a.parts.part + ((size_t)(2 * part) * a.parts.rows + C.first_row + (size_t)kvhead * Nc) * d;
-    store_dkv<S_DB, S_PAD>(dk, dv, to, to + (size_t)a.parts.rows * d, Nc, d, key0, lr, h, a.scale, 0, 0);
+    store_dkv<S_DB, S_PAD>(dk, dv, a.parts.at(part, false, C, kvhead, d), a.parts.at(part, true, C, kvhead, d),
+                           C.span_keys, d, key0 - C.span_lo, lr, h, a.scale, 0, 0);
     return;
   }
   if constexpr (S_PAD) {                           // keys with an infinity or NaN, and their neighbours (see burst_rows.h)
@@ -1175,8 +1176,8 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
-  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per, io.kv_splits);
-  a.parts = row_parts(io, ch, n, a.H);
+  set_row_parts(a, io);
+  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per, a.parts.splits);
   if (a.parts.splits > 1 && ch[0].bmask != nullptr) return BURST_ERR_SHAPE;
   a.mirror = n == 1 && a.parts.splits == 1 && mirrored(nb, a.causal);
   static DeviceOnce done;

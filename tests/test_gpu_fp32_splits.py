@@ -24,6 +24,8 @@ CASES = [
     dict(H=8, kv_heads=1, d=32, Nq=160, chunk_rows=[97]),
     dict(H=1, d=128, Nq=500, chunk_rows=[500]),
     dict(H=5, d=64, Nq=700, chunk_rows=[700], causal=True),
+    dict(H=2, d=128, Nq=600, chunk_rows=[300, 330, 600, 300], window=300, q_off=500, causal=True),     # hidden blocks before and after
+    dict(H=4, kv_heads=2, d=36, Nq=300, chunk_rows=[200, 330, 100, 300], window=200, q_off=500, causal=True),
 ]
 
 

@@ -25,6 +25,20 @@ def test_key_ranges_of_the_padded_kernels(H, N, ranges):
         assert workspace(p, [N], flags=B.BURST_WALK_NO_STATE) == want
 
 
+def test_partial_gradients_take_room_for_visible_keys_only():
+    gradients = lambda keys, d: 2 * keys * d * 4
+    # one head, 8192 rows, window of 4096 over 16 chunks of 4096: at most 8 parts of the two chunks (the first rows' window is empty
+    # before key 0) that rows see
+    p = B.params(1, 1, 8192, 0, 128, "bf16", 0.1, causal=True, window=4096)
+    assert 0 < workspace(p, [4096] * 16) <= 8 * gradients(2 * 4096, 128)
+    # 8 heads, 1024 rows that see the first of 16 chunks
+    p = B.params(1, 8, 1024, 0, 64, "bf16", 0.1, causal=True)
+    assert 0 < workspace(p, [1024] * 16) <= 4 * gradients(8 * 1024, 64) and workspace(p, [1024] * 16) == workspace(p, [1024])
+    # hidden keys of the only chunk: 1024 rows and a window of 1000 see 2023 keys, 17 blocks of 128
+    p = B.params(1, 1, 1024, 0, 64, "bf16", 0.1, causal=True, q_off=60000, window=1000)
+    assert 0 < workspace(p, [65536]) <= 4 * gradients(17 * 128, 64)
+
+
 def form(H, Nq, rows, workspace, **kw):
     p = B.params(1, H, Nq, 0, 128, "bf16", 0.1, **kw)
     chunks = (B.BurstChunk * len(rows))()
