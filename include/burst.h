@@ -221,7 +221,7 @@ typedef struct burst_chunk {
 /* burst_state_init, burst_local_fwd for each of the n_chunks chunks in order, burst_finalize: the same
  * O, lse and final state.  `p` gives everything but Nc, k_off, block_mask, block_mask_stride and
  * kv_strides, which are taken from the chunks.  workspace: device memory of at least
- * burst_walk_workspace_bytes(..., 0) bytes, 16-byte aligned, contents undefined before and after, or NULL;
+ * burst_walk_workspace_bytes(..., BURST_WALK_FORWARD) bytes, 16-byte aligned, contents undefined before and after, or NULL;
  * with it a slice of few rows is spread over the chip by splitting the keys into ranges whose partial
  * states are merged at the end (the sums then come in another order).  O_acc, m, l may all be NULL: the
  * state is then not kept (workspace: burst_walk_workspace_bytes(..., BURST_WALK_NO_STATE)). */
@@ -248,6 +248,7 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
 int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_params* p, int with_workspace);
 #define BURST_WALK_HALF_GRADS 1   /* for burst_walk_bwd with half_grads */
 #define BURST_WALK_NO_STATE 2     /* for burst_walk_fwd without O_acc, m, l */
+#define BURST_WALK_FORWARD 4      /* for burst_walk_fwd alone: not what only burst_walk_bwd uses */
 
 /* Alg. 1, body of the loop for one chunk exactly as printed, WITHOUT the tiling of
  * Sec. 2.4 (the "w/o LAO" variant of the paper's ablation, Tables 2-3): the whole

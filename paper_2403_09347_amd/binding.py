@@ -383,7 +383,7 @@ def chunk_array(Ks, Vs, k_offs, masks, p, dKs=None, dVs=None, grad_dtype=None):
     return arr
 
 
-BURST_WALK_HALF_GRADS, BURST_WALK_NO_STATE = 1, 2
+BURST_WALK_HALF_GRADS, BURST_WALK_NO_STATE, BURST_WALK_FORWARD = 1, 2, 4
 
 
 def burst_walk_workspace_bytes(chunks, p, flags=0):

@@ -778,8 +778,8 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
   const KParams& k = w[0].k;
   const size_t rows = (size_t)k.B * k.H * k.Nq;
   size_t need = split_bytes(k, walk_splits(w));
-  if (!(flags & BURST_WALK_NO_STATE)) need = std::max(need, dkv_bytes(k, dkv_parts(w)));   // (that flag: a forward walk)
-  if (flags != 0 && dq_launches(w) > 1) {          // between the launches: dQ in fp32, the state
+  if (!(flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD))) need = std::max(need, dkv_bytes(k, dkv_parts(w)));
+  if ((flags & (BURST_WALK_NO_STATE | BURST_WALK_HALF_GRADS)) && dq_launches(w) > 1) {          // between the launches: dQ in fp32, the state
     if (flags & BURST_WALK_HALF_GRADS) need = std::max(need, rows * k.d * sizeof(float));
     if (flags & BURST_WALK_NO_STATE) need = std::max(need, rows * ((size_t)k.d + 8) * sizeof(float));
   }

@@ -58,7 +58,7 @@ class RingWalk:
             Ks, Vs, k_offs, masks = pick(Ks), pick(Vs), pick(k_offs), pick(masks)
         p = self._walk_params()
         chunks = B.chunk_array(Ks, Vs, k_offs, masks, p)
-        B.burst_walk_fwd(self.Q, chunks, self.O_acc, self.m, self.l, self.O, self.lse, p, self._scratch(chunks, p))
+        B.burst_walk_fwd(self.Q, chunks, self.O_acc, self.m, self.l, self.O, self.lse, p, self._scratch(chunks, p, B.BURST_WALK_FORWARD))
         return self.O, self.lse
 
     def _own(self, name):

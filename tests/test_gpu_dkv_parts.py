@@ -36,6 +36,9 @@ def walk_of(spec):
     case = workloads.make_case(B=1, dtype="bf16", seed=211, device=DEV, **spec)
     walk = RingWalk(case["Q"], case["scale"], case["causal"], case["q_off"], case["window"], kv_heads=case.get("kv_heads", 0))
     walk.forward(case["K"], case["V"], case["k_offs"])
+    p = walk._walk_params()
+    held = 0 if walk._workspace is None else walk._workspace.numel()
+    assert held == B.burst_walk_workspace_bytes(B.chunk_array(case["K"], case["V"], case["k_offs"], None, p), p, B.BURST_WALK_FORWARD)
     return case, walk
 
 

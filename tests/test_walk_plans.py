@@ -39,6 +39,13 @@ def test_partial_gradients_take_room_for_visible_keys_only():
     assert 0 < workspace(p, [65536]) <= 4 * gradients(17 * 128, 64)
 
 
+def test_forward_walks_ask_for_no_partial_gradients():
+    p = B.params(1, 32, 3008, 0, 128, "bf16", 0.1, causal=True, kv_heads=8)
+    assert workspace(p, [3008]) > 0 and workspace(p, [3008], flags=B.BURST_WALK_FORWARD) == 0
+    p = B.params(1, 1, 256, 0, 64, "f32", 0.1)                                               # split by keys: the states of the ranges
+    assert workspace(p, [256] * 4, flags=B.BURST_WALK_FORWARD) == 8 * 256 * 66 * 4 <= workspace(p, [256] * 4)
+
+
 def form(H, Nq, rows, workspace, **kw):
     p = B.params(1, H, Nq, 0, 128, "bf16", 0.1, **kw)
     chunks = (B.BurstChunk * len(rows))()
