@@ -81,6 +81,16 @@ def test_walk_calls_equal_the_walk_chunk_by_chunk(dtype, spec, family):
         B.burst_set_kernel_family(0)
 
 
+def in_three_layouts(case):
+    """The chunks head-major, sequence-major, packed, packed and head-major."""
+    def lay(t, how):
+        rows = t.transpose(1, 2).contiguous()       # [B, rows, H, d]
+        return t if how == 0 else rows.transpose(1, 2) if how == 1 else torch.cat([rows, rows], 2)[:, :, :2].transpose(1, 2)
+
+    for name in ("K", "V"):
+        case[name] = [lay(t, how) for t, how in zip(case[name], (0, 1, 2, 2, 0))]
+
+
 @pytest.mark.parametrize("family", [1, 2])
 def test_chunks_of_different_pitch_in_one_walk(family):
     """Head-major, sequence-major and packed chunks in turn, d = 128: the hand-scheduled kernels take one row pitch a launch."""
@@ -89,12 +99,7 @@ def test_chunks_of_different_pitch_in_one_walk(family):
         case = workloads.make_case(B=2, H=2, d=128, Nq=257, chunk_rows=[100, 64, 190, 128, 65], dtype="bf16", seed=101, device=DEV,
                                    causal=True, q_off=290)
 
-        def lay(t, how):
-            rows = t.transpose(1, 2).contiguous()   # [B, rows, H, d]
-            return t if how == 0 else rows.transpose(1, 2) if how == 1 else torch.cat([rows, rows], 2)[:, :, :2].transpose(1, 2)
-
-        for name in ("K", "V"):
-            case[name] = [lay(t, how) for t, how in zip(case[name], (0, 1, 2, 2, 0))]
+        in_three_layouts(case)
         assert len({k.stride(2) for k in case["K"]}) == 3
         mk = lambda: RingWalk(case["Q"], case["scale"], case["causal"], case["q_off"])
         want, dKs0, dVs0 = chunk_by_chunk(case, mk())
@@ -107,6 +112,34 @@ def test_chunks_of_different_pitch_in_one_walk(family):
         compare_all_heads(case, "bf16", O, lse, dQ, dKs, dVs)
     finally:
         B.burst_set_kernel_family(0)
+
+
+@pytest.mark.parametrize("d", [4, 32, 64, 96, 128])
+@pytest.mark.parametrize("rows", [100, 257])
+def test_fp32_chunks_of_different_pitch_in_one_walk(d, rows):
+    """The same in fp32, whose kernels go from one pitch to the next inside a launch: dealt to several workgroups per block
+    (with a workspace) and not; fp32 sums in another order than chunk by chunk, 1e-5 of the norm."""
+    case = workloads.make_case(B=2, H=2, d=d, Nq=rows, chunk_rows=[100, 64, 190, 128, 65], dtype="f32", seed=107, device=DEV,
+                               causal=True, q_off=290)
+    in_three_layouts(case)
+    assert len({k.stride(2) for k in case["K"]}) == 3
+    walk = RingWalk(case["Q"], case["scale"], case["causal"], case["q_off"])
+    want, dKs0, dVs0 = chunk_by_chunk(case, walk)
+    p = walk._walk_params()
+    for split in (True, False):
+        dQ = torch.full(tuple(walk.Q.shape), float("nan"), device=DEV)
+        dKs, dVs = [[torch.full(tuple(k.shape), float("nan"), device=DEV) for k in case["K"]] for _ in range(2)]
+        chunks = B.chunk_array(case["K"], case["V"], case["k_offs"], None, p, dKs, dVs, torch.float32)
+        need = B.burst_walk_workspace_bytes(chunks, p)
+        assert need > 0
+        ws = torch.empty(need, device=DEV, dtype=torch.uint8) if split else None
+        B.burst_walk_fwd(walk.Q, chunks, walk.O_acc, walk.m, walk.l, walk.O, walk.lse, p, ws)
+        B.burst_walk_bwd(walk.Q, chunks, walk.O, case["dO"], walk.lse, walk.D, dQ, p, accumulate_dq=False, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.allclose(walk.lse, want[1], rtol=0, atol=1e-5)
+        for a, b in zip([walk.O, dQ, *dKs, *dVs], [want[0], want[5], *dKs0, *dVs0]):
+            assert float((a - b).norm()) <= 1e-5 * float(b.norm())
+        compare_all_heads(case, "f32", walk.O, walk.lse, dQ, dKs, dVs)
 
 
 @pytest.mark.parametrize("spec,family", [
