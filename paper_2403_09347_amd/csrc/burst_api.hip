@@ -429,14 +429,17 @@ int walk_splits(const std::vector<WalkChunk>& w) {
     if (k.window > 0) lo = std::max(lo, k.q_off + k.Nq - 128 - k.window + 1 - x.c.k_off);
     if (hi > lo) tiles += (hi - lo + 63) / 64;
   }
-  // The padded kernels' tiles take twice the time: up to 160 blocks 6 of them are a range.  Walks of 18 are split there (three
-  // ranges: 16 x 1216 causal rows, d = 96, 160 blocks, forward 39.9 / 36.8 us, backward pass 124 / 120; 15 x 1130, 135, 38.4 / 35.6,
-  // 120 / 113), walks of 12 while both ranges have a CU each, up to 128 blocks (16 x 900, 32.8 / 29.3, 99 / 95); past that some CUs
-  // have two workgroups of such a launch and others one (17 x 1024, 136, 35.0 / 36.4, 108 / 111; 18 x 900, 144, 33.0 / 34.6, 99 / 102; 20 x
-  // 1000, 160, 35.2 / 37.3, 109 / 112).  From 161 blocks on two ranges as elsewhere (24 x 1000, 192, 35.3 / 40.4, not split).
+  // The padded kernels' tiles take twice the time: up to 160 blocks 6 of them are a range, and walks of 12 are split (d = 96, causal,
+  // whole / split, forward and backward pass, us: 16 x 900, 128 blocks, in 2 32.8 / 29.3, 99 / 95; 16 x 1216, 160, in 3 39.9 / 36.8,
+  // 124 / 120; 15 x 1130, 135, in 3 38.4 / 35.6, 120 / 113).  A few workgroups more than CUs cost as much as another round of them
+  // (forward, d = 96, in 2 / 3: 100 x 100 rows x 1200 keys, 300, 31.7 / 33.6; 12 x 1200 x 1200, 360, 35.8 / 39.0; 3840 causal rows
+  // in 8 / 10 (300) 30.0 / 33.9; whole / in 2: 17 x 1024, 272, 35.0 / 36.4; 20 x 1000, 320, 35.2 / 37.3): then as many ranges as
+  // there are CUs for.  Halfway to two a CU it pays again (8 x 1500, in 2 / 4, 384, 37.2 / 32.1).  From 161 blocks on as elsewhere
+  // (24 x 1000, 192, in 2: 35.3 / 40.4, not split).
   const bool pad = f.plain != &kD64 && f.plain != &kD128p && blocks <= 160;
-  const long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
-  return s < 2 || tiles < (!pad ? 20 : blocks > 128 ? 18 : 12) ? 1 : (int)s;
+  long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
+  if (pad && s * blocks > 256 && s * blocks <= 360) s = 256 / blocks;
+  return s < 2 || tiles < (pad ? 12 : 20) ? 1 : (int)s;
 }
 int dq_launches(const std::vector<WalkChunk>& w) {
   int n = 0;

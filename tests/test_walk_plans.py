@@ -14,10 +14,11 @@ def workspace(p, rows, k_offs=None, flags=0):
     return B.burst_walk_workspace_bytes(chunks, p, flags)
 
 
-@pytest.mark.parametrize("H,N,ranges", [(16, 900, 2), (16, 1024, 2), (8, 2040, 4),             # 128 blocks of 128 rows
-                                        (17, 1024, 1), (18, 900, 1), (20, 1000, 1),           # 136, 144, 160: two short ranges do not pay
-                                        (16, 1216, 3), (15, 1130, 3), (14, 1400, 3),          # 160, 135, 154: three do
-                                        (24, 1000, 1), (32, 777, 1), (16, 1500, 2)])          # 192, 224, 192
+@pytest.mark.parametrize("H,N,ranges", [(16, 900, 2), (16, 1024, 2), (8, 2040, 4),             # 128 blocks of 128 rows: 256 or 512 workgroups
+                                        (17, 1024, 1), (18, 900, 1), (20, 1000, 1), (12, 1200, 2),   # not 272, 288, 320 or 360
+                                        (1, 3840, 8), (2, 2816, 5), (8, 1536, 4),             # not 300 or 308, but 384
+                                        (16, 1216, 3), (15, 1130, 3), (14, 1400, 3),          # 480, 405, 462
+                                        (24, 1000, 1), (32, 777, 1), (16, 1500, 2)])          # more than 160 blocks
 def test_key_ranges_of_the_padded_kernels(H, N, ranges):
     for d in (40, 96, 120):
         p = B.params(1, H, N, 0, d, "bf16", 0.1, causal=True)
