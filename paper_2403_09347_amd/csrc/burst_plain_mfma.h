@@ -549,6 +549,9 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 }
 
 // ------------------------------------------------------------------------------- backward, dQ
+// Builds whose dQ kernel can compute D.  (At d = 128 the host never asks for it, and the branch alone cost 3 % of walks of few
+// rows: 52 rows x 6656 keys, window 1074, 34.3 / 35.2 us.)
+constexpr bool S_SUMS = S_PAD || S_D == 64;
 constexpr int SQ_BC = 32;                         // keys per tile
 constexpr int SQ_TILE = SQ_BC * S_ROWB;
 
@@ -645,12 +648,12 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
   };
   bool have = advance(0);
-  if (!have && a.acc_dq && a.splits == 1 && a.O == nullptr) return;  // nothing visible: nothing to add
+  if (!have && a.acc_dq && a.splits == 1 && !(S_SUMS && a.O != nullptr)) return;  // nothing visible: nothing to add
   if (have) fetch(0);
   // D of the workgroup's rows, in the order of bwd_prepare_kernel's sums: the same bits.  (Its own launch took 4.5 us of a
   // call with gradients of 64 heads x 1024 rows, d = 64.)
   float Dv = 0.f;
-  if (a.O != nullptr) {
+  if (S_SUMS && a.O != nullptr) {
     constexpr int L2 = S_D <= 32 ? 2 : S_D <= 64 ? 4 : 8;   // pairs of 16-byte pieces that bwd_prepare_kernel has lanes for
     const size_t at = a.lay.q_base(head) + (size_t)(ok ? row : 0) * a.lay.qs_r;
     float x[L2];
@@ -1159,6 +1162,7 @@ static void bwd_args(BwdArgsLite& a, const KParams& p, const BwdIo& io, const Ch
 int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
+  if (io.O != nullptr && !S_SUMS) return BURST_ERR_SHAPE;
   const int nw = row_waves(p, ch, false);
   a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
   a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
