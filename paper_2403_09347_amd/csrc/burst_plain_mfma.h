@@ -1121,10 +1121,19 @@ static int launch_plain(K dense, K sparse, DeviceOnce& once, A& a, long long nb,
 // 8192 keys, four / two, us: dQ, d = 128, density 0.1 166 / 134, 0.25 351 / 280, 0.5 496 / 470; d = 64 171 / 149, 270 / 253
 // (0.25, 0.5); forward, d = 64, 141 / 130, 216 / 215.  In the forward at d = 128 the smaller tiles take back what the exact
 // lists give (134 / 132, 274 / 266, 389 / 408): two only while all workgroups are resident at once (8 heads x 1000 rows x
-// 3000 keys 44 / 35).
-static int row_waves(const KParams& p, const Chunk* ch, bool forward) {
-  if (ch[0].bmask == nullptr || p.bsize >= 128) return 4;
-  return !forward || S_D <= 64 || (long long)p.B * p.H * ((p.Nq + 63) / 64) <= 1024 ? 2 : 4;
+// 3000 keys 44 / 35).  Four for at most 64 rows, where both have as many workgroups (8 x 64 rows x 4000 keys, forward, d = 64, 0.25, 18.0 /
+// 22.3, d = 120 36 / 40), and in the forward where workgroups of four wavefronts have a CU each and equal work, on the narrow padded builds
+// (d = 40, 24 x 900 x 1800, 0.1, 0.25 and 0.5 17.4 / 20.6, 29.1 / 34.8, 42.4 / 55.9) and with at most 2048 keys on the others (d = 64 13.9 / 15.6,
+// 21.8 / 23.1, 30.6 / 35.0, d = 128 20.0 / 20.9, 31.2 / 32.2, 43.9 / 49.0; 6000 keys 0.87, 0.98, 1.12 of the time).  Dense flags lose
+// whatever the sizes (0.9: forward 3 to 30 %, dQ up to 8 %); the host cannot see them.
+static int row_waves(const KParams& p, const Chunk* ch, int n, bool forward) {
+  if (ch[0].bmask == nullptr || p.bsize >= 128 || p.Nq <= 64) return 4;
+  if (!forward) return 2;
+  const long long heads = (long long)p.B * p.H, places = heads * ((p.Nq + 127) / 128);
+  long long keys = 0;
+  for (int i = 0; i < n; i++) keys += ch[i].Nc;
+  if (!p.causal && places > 128 && places <= 256 && ((S_PAD && S_D <= 64) || keys <= 2048)) return 4;
+  return S_D <= 64 || heads * ((p.Nq + 63) / 64) <= 1024 ? 2 : 4;
 }
 
 // n <= kMaxChunks chunks, all of them with block flags or none.
@@ -1138,7 +1147,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
-  const int nw = row_waves(p, ch, true);
+  const int nw = row_waves(p, ch, n, true);
   a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
   a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;
@@ -1163,7 +1172,7 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   if (io.O != nullptr && !S_SUMS) return BURST_ERR_SHAPE;
-  const int nw = row_waves(p, ch, false);
+  const int nw = row_waves(p, ch, n, false);
   a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
   a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
   int longest = 0;

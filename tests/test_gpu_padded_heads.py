@@ -22,6 +22,9 @@ CASES = [
     dict(B=1, H=3, d=80, Nq=128, chunk_rows=[129, 31], causal=True, q_off=32, layout="packed"),
     dict(B=1, H=4, kv_heads=1, d=96, Nq=161, chunk_rows=[161], causal=True, layout="seq"),
     dict(B=1, H=2, d=104, Nq=64, chunk_rows=[64]),
+    dict(B=1, H=2, d=40, Nq=64, chunk_rows=[130, 65], block=64, pattern="random", density=0.5),        # one wavefront's flags a row block
+    dict(B=1, H=2, d=40, Nq=65, chunk_rows=[130, 65], block=64, pattern="random", density=0.5),        # ... and two
+    dict(B=1, H=43, d=40, Nq=300, chunk_rows=[130, 65], block=64, pattern="random", density=0.5),      # 129 row blocks: four
     dict(B=1, H=2, d=120, Nq=200, chunk_rows=[90, 110], block=128, pattern="band_global", causal=True, q_off=0),
 ]
 
