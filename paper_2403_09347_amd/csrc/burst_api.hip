@@ -389,6 +389,9 @@ bool generic_splittable(const std::vector<WalkChunk>& w) {
 // in 8; 4 x 1000 x 3000, d = 64, 82 / 53 and 111 / 63 in 2 (3: 66, 85; 4: 56, 72); 4 x 700 x 1400, d = 128, 70 / 48 and 102 / 68
 // in 2 (3: 57, 79); 8 x 300 x 600 causal, d = 80, 30 / 21 and 38 / 26 in 3 (4: 31, 32); not split: 8 x 700 x 1400 causal 71 and
 // 103 (2: 69, 97; 3: 73, 101), 8 x 1000 x 4000, d = 32, 67 and 82 (2: 72, 84).
+// (tiles through registers then; through LDS, whole / split, forward: d = 24, 4 x 1000 causal, in 2 17.3 / 16.4; 8 x 128 x 500, in 4 11.2 /
+// 9.7.)  At 32 columns a tile takes 0.4 us and the merge 4, so 10 tiles or more have to be saved there (in 2: 8 x 277 x 277, 9 tiles,
+// forward 9.7 / 12.0, dQ +0.7; 16 x 256 x 600, 19, 12.6 / 14.5 and -0.1; at d = 64 15.2 / 15.6 and -3.1).
 int generic_splits(const std::vector<WalkChunk>& w) {
   const KParams& k = w[0].k;
   const long long heads = (long long)k.B * k.H, blocks = (k.Nq + 31) / 32;
@@ -404,7 +407,8 @@ int generic_splits(const std::vector<WalkChunk>& w) {
     }
     most = std::max(most, walk);
   }
-  return (int)std::max<long long>(1, std::min({256 / (heads * blocks), most / 4, 64LL}));
+  const long long s = std::min({256 / (heads * blocks), most / 4, 64LL});
+  return s < 2 || (k.d <= 32 && most - (most + s - 1) / s < 10) ? 1 : (int)s;
 }
 // Into how many key ranges a walk of the plain kernels is split (1: not at all).  Their workgroups hold
 // 128 rows and two share a CU: 512 fill every place on the chip, and with 256 or fewer two ranges or more have places
@@ -507,10 +511,11 @@ burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
   if (generic) {
     // as many as there are CUs for, four tiles each at least; two also where a causal launch fits the CUs once.
     // us a launch, whole / by the rule: 1024 keys x 256 rows, one head, d = 64, 28 / 19 in 2; 500 x 500, d = 128, 64 / 30 in 4 (2: 41);
-    // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).
+    // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).  At 32 columns 8 tiles or more
+    // have to be saved (backward pass, d = 24, in 2: 8 x 277 x 277, 9 tiles, 23.3 / 25.5; 4 x 300 causal, 10, 22.7 / 24.4; 8 x 500, 16, 28.2 / 28.1).
     long long parts = std::min({256 / blocks, most / 4, 16LL});
     if (parts < 2 && blocks <= 256 && most >= 16 && 10 * most * slots >= 18 * total) parts = 2;
-    return parts < 2 ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
+    return parts < 2 || (k.d <= 32 && most - most / parts < 8) ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
   }
   if (most < 24 || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on

@@ -16,7 +16,7 @@ DEV = "cuda:0"
 
 CASES = [
     dict(H=1, d=64, Nq=256, chunk_rows=[256] * 4),
-    dict(H=1, d=4, Nq=1, chunk_rows=[257]),
+    dict(H=1, d=4, Nq=1, chunk_rows=[513]),
     dict(H=2, d=128, Nq=33, chunk_rows=[500, 1, 310], causal=True, q_off=700),
     dict(H=3, d=36, Nq=300, chunk_rows=[300, 290], causal=True, q_off=-20),          # rows that see nothing
     dict(H=2, d=96, Nq=100, chunk_rows=[600], window=150, q_off=300, layout="seq"),

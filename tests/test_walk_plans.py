@@ -26,6 +26,16 @@ def test_key_ranges_of_the_padded_kernels(H, N, ranges):
         assert workspace(p, [N], flags=B.BURST_WALK_NO_STATE) == want
 
 
+def test_fp32_walks_that_are_split():
+    state = lambda s, H, N, d: 0 if s == 1 else s * H * N * (d + 2) * 4
+    for H, N, K, d, s in ((8, 277, 277, 24, 1), (8, 277, 277, 36, 2), (16, 256, 600, 32, 1), (16, 256, 600, 36, 2), (8, 128, 500, 24, 4), (4, 1000, 1000, 32, 2),
+                          (8, 700, 1400, 64, 1)):
+        p = B.params(1, H, N, 0, d, "f32", 0.1)
+        assert workspace(p, [K], flags=B.BURST_WALK_FORWARD) == state(s, H, N, d)
+    dkv = lambda H, N, K, d: form(H, N, [K], True, d=d, dtype="f32")
+    assert dkv(8, 277, 277, 24) == 0 and dkv(8, 277, 277, 36) == 1 and dkv(8, 500, 500, 32) == 1 and dkv(2, 1000, 300, 24) == 1
+
+
 def test_partial_gradients_take_room_for_visible_keys_only():
     gradients = lambda keys, d: 2 * keys * d * 4
     # one head, 8192 rows, window of 4096 over 16 chunks of 4096: at most 8 parts of the two chunks (the first rows' window is empty
@@ -47,8 +57,8 @@ def test_forward_walks_ask_for_no_partial_gradients():
     assert workspace(p, [256] * 4, flags=B.BURST_WALK_FORWARD) == 8 * 256 * 66 * 4 <= workspace(p, [256] * 4)
 
 
-def form(H, Nq, rows, workspace, **kw):
-    p = B.params(1, H, Nq, 0, 128, "bf16", 0.1, **kw)
+def form(H, Nq, rows, workspace, d=128, dtype="bf16", **kw):
+    p = B.params(1, H, Nq, 0, d, dtype, 0.1, **kw)
     chunks = (B.BurstChunk * len(rows))()
     for i, c in enumerate(chunks):
         c.K, c.V, c.Nc, c.k_off = 4096, 8192, rows[i], sum(rows[:i])
