@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d", [("bf16", 8), ("bf16", 24), ("bf16", 56), ("bf16", 64), ("bf16", 72), ("bf16", 96), ("bf16", 120), ("bf16", 128),
                                      ("bf16", 20), ("f32", 4), ("f32", 12), ("f32", 20), ("f32", 32), ("f32", 36), ("f32", 64), ("f32", 68), ("f32", 96),
                                      ("f32", 128), ("f32", 34)])
-@pytest.mark.parametrize("layout,k_off,Nq", [("head", 0, 131), ("seq", 60, 131), ("packed", 5000, 131), ("head", 0, 1400)])
+@pytest.mark.parametrize("layout,k_off,Nq", [("head", 0, 131), ("seq", 60, 131), ("packed", 5000, 131), ("head", 0, 1400), ("head", 0, 5500)])
 def test_row_sums_of_a_walk(dtype, d, layout, k_off, Nq):
     if layout != "head" and d * (2 if dtype == "bf16" else 4) % 16:
         pytest.skip("strided rows start on 16 bytes")
