@@ -520,7 +520,15 @@ burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
   if (most < 24 || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on
   const long long splits = std::min({16LL, ratio, most / (f.plain != nullptr ? 8 : 16)});
-  return splits < 2 ? kWhole : cut(splits, 8);
+  if (splits < 2) return kWhole;
+  // What the longest walk has above a CU's share has to be worth the merging launch: 16 tiles at d = 64, 6 on the padded kernels, whose
+  // tiles take three times as long.  Backward pass, whole / cut, us: d = 64, 32 x 1226 causal, 13 tiles above, 73.2 / 78.3, 2 x 3840 x
+  // 15360, 8, 177 / 202, 16 x 1984 x 1280, 15.5, 96.1 / 94.5, 16 x 919 causal, 21, 54.7 / 50.7; d = 96, 32 x 1024, 0, 113 / 119; d = 40, 16 x 851
+  // x 2099, window 71, 2, 91 / 100; d = 120, 8 x 2209, window 674, 11, 245 / 204.  Hand-scheduled (one workgroup a CU): the share and a
+  // part behind it have to be shorter than the longest walk (1 x 4736 x 18944, 148 equal blocks, in 2: 192 / 223; 4 x 3547, 112, in 3 143 / 139).
+  const long long share = total / 256;
+  if (f.hand ? share + (most + splits - 1) / splits >= most : most - share < (f.plain == &kD64 ? 16 : 6)) return kWhole;
+  return cut(splits, 8);
 }
 size_t dkv_bytes(const KParams& k, const burst::RowPlan& plan) {
   const burst::RowParts& p = plan.parts;

@@ -73,6 +73,11 @@ def test_forms_of_dkv_launches():
         assert form(257, 64, [128], ws) == 0 and form(8, 512, [512], ws) == 0               # one whole tile; few workgroups
         assert form(32, 512, [512] * 16, ws, q_strides=(512 * 4096, 128, 4096)) == 0        # rows of Q and K at different distances
     assert form(32, 3008, [3008], True, causal=True, kv_heads=8) == 1 and form(32, 3008, [3008], False, causal=True, kv_heads=8) == 0
+    # cut where the longest walk is far above a CU's share, in tiles of 32 rows: 13 at d = 64, 21; 0, 14 on padded kernels
+    cut = lambda H, N, d, rows=0, **kw: form(H, N, rows or [N], True, d=d, **kw)
+    assert cut(32, 1226, 64, causal=True) == 0 and cut(16, 919, 64, causal=True) == 1
+    assert cut(32, 1024, 96) == 0 and cut(32, 777, 96, causal=True) == 1
+    assert cut(1, 4736, 128, [4736] * 4, causal=True, q_off=3 * 4736) == 0 and cut(2, 2609, 128, causal=True) == 1   # 148 x 2 workgroups: two rounds
     assert form(32, 0, [512], True) == 0 and form(32, 512, [0], True) == 0
     with pytest.raises(B.BurstError):
         form(32, 512, [512], True, kv_heads=5)
