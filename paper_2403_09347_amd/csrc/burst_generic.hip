@@ -58,12 +58,13 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
 }
 __device__ __forceinline__ int reg_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
-// How one call shape reads its rows.  VEC: fp32 with d a multiple of 4 (see fp32_tiles), whose tiles come through LDS.
+// How one call shape reads its rows.  VEC: fp32 with d a multiple of 4 (see fp32_tiles), whose tiles come through LDS but where
+// gen_dispatch says otherwise.
 template <typename T, int D, bool VEC>
 struct Rows {
   static constexpr int NK = D / 8;                // four-wide operand pieces of a row
   static constexpr int NB = D / 32;               // 32-wide blocks of d
-  static constexpr bool PACKED = VEC && D != 96;  // columns NB lr .. NB lr + NB - 1 in one LDS read
+  static constexpr bool PACKED = VEC && D != 96;  // columns NB lr .. NB lr + NB - 1 in one read
   static __device__ __forceinline__ int col_of(int db, int lr) { return PACKED ? NB * lr + db : 32 * db + lr; }
   // columns 8 ks + 4 h .. + 3.  Past d: whatever the row's last columns hold (the other operand, `fixed`
   // below, is zero there).
@@ -86,8 +87,15 @@ struct Rows {
   }
   // block columns of lane lr (past d: anything, such columns are never stored)
   static __device__ __forceinline__ void spread(const T* row, int lr, int d, float (&v)[NB]) {
+    if constexpr (PACKED && NB > 1) {
+      typedef __attribute__((ext_vector_type(NB))) float vec;
+      const vec x = *reinterpret_cast<const vec*>(row + min(NB * lr, d - NB));
 #pragma unroll
-    for (int db = 0; db < NB; db++) v[db] = (float)row[min(32 * db + lr, d - 1)];
+      for (int db = 0; db < NB; db++) v[db] = x[db];
+    } else {
+#pragma unroll
+      for (int db = 0; db < NB; db++) v[db] = (float)row[min(32 * db + lr, d - 1)];
+    }
   }
 };
 
@@ -224,11 +232,12 @@ template <int D, bool VEC>
 constexpr int wave_floats() { return VEC ? 64 * D : 32 * D; }
 
 // ---------------------------------------------------------------------------- forward
-template <typename T, int D, bool VEC, int W, bool SPLIT>
+// LDS: tiles come through LDS (VEC).
+template <typename T, int D, bool VEC, int W, bool SPLIT, bool LDS>
 __global__ void __launch_bounds__(64 * W, W / 4)
 fwd_generic_kernel(GenArgs a) {
   using R = Rows<T, D, VEC>;
-  constexpr int NB = R::NB, NK = R::NK, WS = wave_floats<D, VEC>();
+  constexpr int NB = R::NB, NK = R::NK, WS = wave_floats<D, LDS>();
   extern __shared__ __attribute__((aligned(16))) float gsh[];          // per wavefront: tiles, then [NB][16][64] partial O^T; [W][32] m, l
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -251,8 +260,8 @@ fwd_generic_kernel(GenArgs a) {
   KeyWalk<T> at;
   at.c = -1; at.t = at.lo = at.hi = 0;
   bool more = at.to(a, head, row0, SPLIT ? split * W + w : w, every);
-  if (VEC && more) {
-    if constexpr (VEC) {
+  if (LDS && more) {
+    if constexpr (LDS) {
     using L = LdsTile<D>;
     char* const kl = reinterpret_cast<char*>(gsh) + w * 2 * L::BYTES;
     char* const vl = kl + L::BYTES;
@@ -327,7 +336,7 @@ fwd_generic_kernel(GenArgs a) {
     }
     }
   } else if (more) {
-    if constexpr (!VEC) {
+    if constexpr (!LDS) {
     f32x4 qf[NK], kf[NK];
     const T* Qr = (const T*)a.Q + a.lay.q_base(head) + (size_t)min(row, a.Nq - 1) * a.lay.qs_r;
 #pragma unroll
@@ -1147,11 +1156,11 @@ static void make_args(GenArgs& a, const KParams& p, const Chunk* ch, int n) {
 }
 
 enum { GEN_FWD, GEN_DQ, GEN_DKV };
-template <int KIND, typename T, int D, bool VEC, int W, bool SPLIT = false>
+template <int KIND, typename T, int D, bool VEC, int W, bool SPLIT = false, bool LDS = VEC>
 static int gen_launch(GenArgs& a, long long grid, hipStream_t s) {
-  const unsigned lds = (W * wave_floats<D, VEC>() + (KIND == GEN_FWD ? W * 64 : KIND == GEN_DKV && VEC ? W * 129 : W)) * 4;
+  const unsigned lds = (W * wave_floats<D, LDS>() + (KIND == GEN_FWD ? W * 64 : KIND == GEN_DKV && VEC ? W * 129 : W)) * 4;
   void (*kernel)(GenArgs);
-  if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W, SPLIT>;
+  if constexpr (KIND == GEN_FWD) kernel = fwd_generic_kernel<T, D, VEC, W, SPLIT, LDS>;
   else if constexpr (KIND == GEN_DQ) kernel = bwd_dq_generic_kernel<T, D, VEC, W, SPLIT>;
   else kernel = bwd_dkv_generic_kernel<T, D, VEC, W, SPLIT>;
   static DeviceOnce lds_opt_in;
@@ -1202,6 +1211,15 @@ static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
   if (dtype == BURST_F32 && fp32_tiles(a.d, a.lay, a.ch, a.n)) {
     if (a.d <= 32) return few ? gen_launch<KIND, float, 32, true, 8>(a, grid, s) : gen_launch<KIND, float, 32, true, 4>(a, grid, s);
     if (a.d <= 64) return few ? gen_launch<KIND, float, 64, true, 8>(a, grid, s) : gen_launch<KIND, float, 64, true, 4>(a, grid, s);
+    if constexpr (KIND == GEN_FWD) {
+      // One tile a wavefront at most: nothing is fetched ahead, and LDS for two tiles a wavefront leaves a CU one workgroup.  Through
+      // LDS / from memory, us, d = 128: 1 x 512 rows x 64 keys 14.4 / 13.4, 32 x 805 x 41 72.3 / 69.3; d = 96, 8 x 1213 x 100 26.0 / 25.1; at d = 64
+      // 14.5 / 15.9, and with 7 tiles, d = 128, 20.0 / 20.6.
+      long long tiles = 0;
+      for (int i = 0; i < a.n; i++) tiles += ((long long)a.ch[i].Nc + 31) / 32;
+      if (a.d > 64 && tiles <= 4)
+        return a.d <= 96 ? gen_launch<KIND, float, 96, true, 4, false, false>(a, grid, s) : gen_launch<KIND, float, 128, true, 4, false, false>(a, grid, s);
+    }
     if (a.d <= 96) return gen_launch<KIND, float, 96, true, 4>(a, grid, s);
     return gen_launch<KIND, float, 128, true, 4>(a, grid, s);
   }

@@ -20,6 +20,9 @@ CASES = [("f32", dict(B=1, H=2, d=d, Nq=nq, chunk_rows=rows, **kw))
              (128, 1, [290], {}), (128, 190, [1, 129], dict(block=64, pattern="random", density=0.5)),
              (127, 40, [70], {})]]
 CASES += [("f32", dict(B=1, H=8, d=64, Nq=n, chunk_rows=[n], causal=True, q_off=0)) for n in (1024, 1025)]
+CASES += [("f32", dict(B=1, H=2, d=d, Nq=70, chunk_rows=rows, **kw))            # at most four key tiles, d > 64: tiles from memory
+          for d, rows, kw in [(68, [128], {}), (72, [128, 1], {}), (96, [33, 31, 5], dict(causal=True, q_off=20)), (100, [1], {}),
+                              (124, [97], dict(window=30, q_off=40)), (128, [60, 64], dict(layout="seq")), (128, [128], dict(block=64, pattern="random", density=0.5))]]
 CASES += [("f32", dict(B=1, H=6, kv_heads=2, d=48, Nq=70, chunk_rows=[90], causal=True, q_off=20)),
           ("bf16", dict(B=1, H=2, d=70, Nq=70, chunk_rows=[90], causal=True, q_off=20)),
           ("bf16", dict(B=1, H=4, kv_heads=2, d=7, Nq=33, chunk_rows=[65]))]
