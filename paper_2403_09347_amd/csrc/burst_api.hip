@@ -438,11 +438,13 @@ int walk_splits(const std::vector<WalkChunk>& w) {
   // 124 / 120; 15 x 1130, 135, in 3 38.4 / 35.6, 120 / 113).  A few workgroups more than CUs cost as much as another round of them
   // (forward, d = 96, in 2 / 3: 100 x 100 rows x 1200 keys, 300, 31.7 / 33.6; 12 x 1200 x 1200, 360, 35.8 / 39.0; 3840 causal rows
   // in 8 / 10 (300) 30.0 / 33.9; whole / in 2: 17 x 1024, 272, 35.0 / 36.4; 20 x 1000, 320, 35.2 / 37.3): then as many ranges as
-  // there are CUs for.  Halfway to two a CU it pays again (8 x 1500, in 2 / 4, 384, 37.2 / 32.1).  From 161 blocks on as elsewhere
+  // there are CUs for.  Halfway to two a CU it pays again under a causal mask (8 x 1500, in 2 / 4, 384, 37.2 / 32.1) and where the
+  // alternative is one range (130 x 100 rows x 1200 keys, in 1 / 3, 42.0 / 34.6); walks of equal length later (d = 32, 8 x 958 x 2268, in 4 / 6,
+  // 24.5 / 27.6; d = 96, 8 x 1500 in 2 / 4 37.7 / 38.9).  From 161 blocks on as elsewhere
   // (24 x 1000, 192, in 2: 35.3 / 40.4, not split).
   const bool pad = f.plain != &kD64 && f.plain != &kD128p && blocks <= 160;
   long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
-  if (pad && s * blocks > 256 && s * blocks <= 360) s = 256 / blocks;
+  if (pad && s * blocks > 256 && s * blocks <= (k.causal || blocks > 128 ? 360 : 400)) s = 256 / blocks;
   return s < 2 || tiles < (pad ? 12 : 20) ? 1 : (int)s;
 }
 int dq_launches(const std::vector<WalkChunk>& w) {

@@ -26,6 +26,11 @@ def test_key_ranges_of_the_padded_kernels(H, N, ranges):
         assert workspace(p, [N], flags=B.BURST_WALK_NO_STATE) == want
 
 
+@pytest.mark.parametrize("H,N,K,ranges", [(8, 958, 2268, 4), (8, 1500, 1500, 2), (130, 100, 1200, 3), (60, 128, 3000, 7)])   # 384, 384, 390, 420 workgroups
+def test_key_ranges_of_walks_of_equal_length(H, N, K, ranges):
+    assert workspace(B.params(1, H, N, 0, 40, "bf16", 0.1), [K], flags=B.BURST_WALK_NO_STATE) == ranges * H * N * 42 * 4
+
+
 def test_fp32_walks_that_are_split():
     state = lambda s, H, N, d: 0 if s == 1 else s * H * N * (d + 2) * 4
     for H, N, K, d, s in ((8, 277, 277, 24, 1), (8, 277, 277, 36, 2), (16, 256, 600, 32, 1), (16, 256, 600, 36, 2), (8, 128, 500, 24, 4), (4, 1000, 1000, 32, 2),
