@@ -389,9 +389,11 @@ bool generic_splittable(const std::vector<WalkChunk>& w) {
 // in 8; 4 x 1000 x 3000, d = 64, 82 / 53 and 111 / 63 in 2 (3: 66, 85; 4: 56, 72); 4 x 700 x 1400, d = 128, 70 / 48 and 102 / 68
 // in 2 (3: 57, 79); 8 x 300 x 600 causal, d = 80, 30 / 21 and 38 / 26 in 3 (4: 31, 32); not split: 8 x 700 x 1400 causal 71 and
 // 103 (2: 69, 97; 3: 73, 101), 8 x 1000 x 4000, d = 32, 67 and 82 (2: 72, 84).
-// (tiles through registers then; through LDS, whole / split, forward: d = 24, 4 x 1000 causal, in 2 17.3 / 16.4; 8 x 128 x 500, in 4 11.2 /
-// 9.7.)  At 32 columns a tile takes 0.4 us and the merge 4, so 10 tiles or more have to be saved there (in 2: 8 x 277 x 277, 9 tiles,
-// forward 9.7 / 12.0, dQ +0.7; 16 x 256 x 600, 19, 12.6 / 14.5 and -0.1; at d = 64 15.2 / 15.6 and -3.1).
+// The merging launch takes 4 us of the GPU and 4 of the host, twice in a pass with gradients, whose host needs about 36 us and 6 a chunk
+// however short the walk is.  At up to 64 columns short walks are therefore whole (a workgroup then has eight wavefronts).  A pass
+// with gradients, whole / split, us: d = 32, one head, 450 x 450 (15 tiles) 46 / 57, 192 rows x 1130 keys (36) 54 / 53, 256 x 1300 (41)
+// 61 / 53; four chunks of 256 (32) 62 / 76, of 320 (40) 63 / 76, of 410 (52) 74 / 76, eight heads 83 / 79; d = 64, 300 x 300 (10) 60 / 61, three
+// chunks of 128 (12) 55 / 69, 416 x 416 (13) 67 / 58.
 int generic_splits(const std::vector<WalkChunk>& w) {
   const KParams& k = w[0].k;
   const long long heads = (long long)k.B * k.H, blocks = (k.Nq + 31) / 32;
@@ -408,7 +410,8 @@ int generic_splits(const std::vector<WalkChunk>& w) {
     most = std::max(most, walk);
   }
   const long long s = std::min({256 / (heads * blocks), most / 4, 64LL});
-  return s < 2 || (k.d <= 32 && most - (most + s - 1) / s < 10) ? 1 : (int)s;
+  const long long others = (long long)w.size() - 1;
+  return s < 2 || most < (k.d <= 32 ? 36 + 4 * others : k.d <= 64 ? 13 + 2 * others : 0) ? 1 : (int)s;
 }
 // Into how many key ranges a walk of the plain kernels is split (1: not at all).  Their workgroups hold
 // 128 rows and two share a CU: 512 fill every place on the chip, and with 256 or fewer two ranges or more have places
@@ -513,11 +516,12 @@ burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
   if (generic) {
     // as many as there are CUs for, four tiles each at least; two also where a causal launch fits the CUs once.
     // us a launch, whole / by the rule: 1024 keys x 256 rows, one head, d = 64, 28 / 19 in 2; 500 x 500, d = 128, 64 / 30 in 4 (2: 41);
-    // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).  At 32 columns 8 tiles or more
-    // have to be saved (backward pass, d = 24, in 2: 8 x 277 x 277, 9 tiles, 23.3 / 25.5; 4 x 300 causal, 10, 22.7 / 24.4; 8 x 500, 16, 28.2 / 28.1).
+    // 8 x 700 causal, d = 64, 56 / 44 in 2; not cut: 8 x 600 keys x 300 rows, causal, d = 80, 37 (2: 52).  Short walks of at most 64 columns
+    // are whole, as in generic_splits: a pass, whole / cut, us: d = 32, 600 rows x 256 keys
+    // (19 tiles) 42 / 48, 1400 x 128 (44) 51 / 48; d = 64, 300 x 300 (10) 60 / 60, without waiting 85 / 88, 384 x 384 (12) 60 / 57.
     long long parts = std::min({256 / blocks, most / 4, 16LL});
     if (parts < 2 && blocks <= 256 && most >= 16 && 10 * most * slots >= 18 * total) parts = 2;
-    return parts < 2 || (k.d <= 32 && most - most / parts < 8) ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
+    return parts < 2 || (k.d <= 32 ? most - most / parts < 16 : k.d <= 64 && most < 12) ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
   }
   if (most < 24 || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on

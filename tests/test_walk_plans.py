@@ -33,12 +33,14 @@ def test_key_ranges_of_walks_of_equal_length(H, N, K, ranges):
 
 def test_fp32_walks_that_are_split():
     state = lambda s, H, N, d: 0 if s == 1 else s * H * N * (d + 2) * 4
-    for H, N, K, d, s in ((8, 277, 277, 24, 1), (8, 277, 277, 36, 2), (16, 256, 600, 32, 1), (16, 256, 600, 36, 2), (8, 128, 500, 24, 4), (4, 1000, 1000, 32, 2),
-                          (8, 700, 1400, 64, 1)):
+    for H, N, K, d, s in ((8, 277, [277], 24, 1), (8, 384, [384], 36, 1), (8, 385, [385], 36, 2), (16, 256, [600], 36, 2), (8, 128, [1120], 32, 1),
+                          (8, 128, [1121], 32, 8), (1, 256, [256] * 4, 32, 1), (4, 410, [410] * 4, 32, 4), (1, 128, [128] * 3, 64, 1), (1, 160, [160] * 4, 64, 5),
+                          (8, 277, [277], 68, 2), (8, 700, [1400], 64, 1)):
         p = B.params(1, H, N, 0, d, "f32", 0.1)
-        assert workspace(p, [K], flags=B.BURST_WALK_FORWARD) == state(s, H, N, d)
+        assert workspace(p, K, flags=B.BURST_WALK_FORWARD) == state(s, H, N, d)
     dkv = lambda H, N, K, d: form(H, N, [K], True, d=d, dtype="f32")
-    assert dkv(8, 277, 277, 24) == 0 and dkv(8, 277, 277, 36) == 1 and dkv(8, 500, 500, 32) == 1 and dkv(2, 1000, 300, 24) == 1
+    assert dkv(8, 277, 277, 24) == 0 and dkv(8, 300, 300, 36) == 0 and dkv(8, 384, 384, 36) == 1 and dkv(8, 500, 500, 32) == 0 and dkv(2, 1000, 300, 24) == 1 \
+        and dkv(8, 277, 277, 68) == 1
 
 
 def test_partial_gradients_take_room_for_visible_keys_only():
