@@ -547,15 +547,16 @@ size_t dkv_bytes(const KParams& k, const burst::RowPlan& plan) {
 // 65536 rows x 64 keys 475 / 476; d = 96, 64 x 1024 128 / 125, 32 x 32768 x 96 492 / 487.  The d = 128 kernels lose as much (dQ
 // 153 / 163, the launch 9).  fp32: every row block starts with reads
 // that nothing covers (32 x 8192 rows x 32 keys, d = 64, 220 / 249, 16 x 2000 x 32, d = 128, 112 / 119, 16 x 3000 x 1000, 758 / 767),
-// so only walks whose blocks of 32 rows have a CU each, where the two forms take the GPU the same time (8 x 1000 causal, d = 64,
-// 85.3 / 85.8; 4 x 500 32.4 / 31.5) and the launch saved is the host's (256 rows x 1024 keys, 82 / 77 a pass; 8 x 700 x 1400, 247.8 / 246.0);
+// so only walks of at most two blocks of 32 rows a CU, where the two forms take the GPU about the same time (8 x 1000 causal, d = 64,
+// 85.3 / 85.8; 4 x 500 32.4 / 31.5; d = 128, 8 x 1423 causal, 360 blocks, 290.3 / 287.9, 16 x 1000 x 64, 512, 112.8 / 114.0; d = 96, 16 x 800 x 1600
+// causal 386.0 / 385.6) and the launch saved is the host's (256 rows x 1024 keys, 82 / 77 a pass; 8 x 700 x 1400, 247.8 / 246.0);
 // rows of at most 48 columns up to four a CU (d = 24, 32 x 805 x 41 29.5 / 28.3; d = 48, 16 x 1000 causal 135.0 / 133.8, 32 x 8192 x 32 205 / 216).
 bool d_by_dq(const std::vector<WalkChunk>& w, int splits) {
   if (w.empty()) return false;
   const Kernels f = fwd_kernels(&w[0].p, w[0].k);
   if (f.plain != nullptr) return f.plain != &kD128p && splits == 1;
   const long long blocks = (long long)w[0].k.B * w[0].k.H * (((long long)w[0].k.Nq + 31) / 32);
-  if (f.hand || w[0].p.dtype != BURST_F32 || blocks > (w[0].k.d <= 48 ? 1024 : 256)) return false;
+  if (f.hand || w[0].p.dtype != BURST_F32 || blocks > (w[0].k.d <= 48 ? 1024 : 512)) return false;
   for (const WalkChunk& x : w) if (!burst::fp32_tiles(x.k.d, x.k.lay, &x.c, 1)) return false;
   return true;
 }
