@@ -102,6 +102,7 @@ struct DqArgs {
   long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
   int blocks_per_head;
+  int order;             // see grid_order
   int bsize;             // block flags: edge, a multiple of 64
   int n;                 // chunks (with block flags: one)
   Layout lay;            // strides of Q and dO
@@ -124,7 +125,7 @@ burst_bwd_dq_kernel(DqArgs a) {
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   int head, qb;
-  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head, head, qb)) return;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head, head, qb, a.order)) return;
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // longest blocks of a head first (see the forward kernel)
   const int kvhead = head / a.group;
   const int q0 = qb * DQ_BR + w * 64;
@@ -569,6 +570,7 @@ int launch_bwd_dq_mfma(const KParams& p, const BwdIo& io, const Chunk* ch, int n
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
   const long long nb = grid_blocks(a.H, a.blocks_per_head);
   if (nb > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  a.order = grid_order(a.H, a.blocks_per_head, unequal_rows(p, ch, n, DQ_BR), 1);
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
     return hipFuncSetAttribute((const void*)burst_bwd_dq_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,

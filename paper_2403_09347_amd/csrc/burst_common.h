@@ -223,15 +223,30 @@ __device__ __forceinline__ float raise_reference_natural(float& m_st, float& cm,
 // Workgroup id -> (head, block of the head).  Ids go round-robin to the 8 XCDs; each XCD gets one
 // run of consecutive blocks, so that a head's tensors stay in one L2 and all XCDs get the same number
 // of workgroups whatever the number of heads.  False: nothing to do (the grid is rounded up to 8).
-// mirror: the second workgroups of an XCD's 32 CUs take their blocks from the end of the run.
-__device__ __forceinline__ bool locate_block(int bid, int heads, int blocks, int& head, int& blk, bool mirror = false) {
+// order (see grid_order): kByBlock: an XCD takes block 0 of all its heads, then block 1, ... (its heads are whole ones where
+// their number is a multiple of 8, else each is spread over several XCDs); kMirror: every other 32 workgroups of an XCD, one
+// for each of its CUs, take theirs in reverse.
+enum { kByBlock = 1, kMirror = 2 };
+__device__ __forceinline__ bool locate_block(int bid, int heads, int blocks, int& head, int& blk, int order = 0) {
   const int total = heads * blocks, per = (total + 7) >> 3;
   int at = bid >> 3;
-  if (mirror && at >= 32 && at < per) at = per + 31 - at;
-  const int lin = (bid & 7) * per + at;
-  if (at >= per || lin >= total) return false;
-  head = lin / blocks;
-  blk = lin - head * blocks;
+  if (at >= per) return false;
+  if (order == 0) {                                // (first: the launches for which 0.2 us count have it)
+    const int lin = (bid & 7) * per + at;
+    if (lin >= total) return false;
+    head = lin / blocks;
+    blk = lin - head * blocks;
+    return true;
+  }
+  if ((order & kMirror) && (at & 32)) {
+    const int from = at & ~31;
+    at = from + min(from + 32, per) - 1 - at;
+  }
+  const bool own = (heads & 7) == 0;
+  const int lin = own ? at : 8 * at + (bid & 7), of = own ? heads >> 3 : heads;
+  if (!own && lin >= total) return false;
+  blk = lin / of;
+  head = lin - blk * of + (own ? (bid & 7) * of : 0);
   return true;
 }
 // dK/dV grids hold the workgroups of all chunks, chunk after chunk.  per > 0: every chunk has that many (the
@@ -242,14 +257,42 @@ __device__ __forceinline__ int chunk_at(int bid, const Chunk* ch, int n, int per
   while (c + 1 < n && bid >= ch[c + 1].first_block) c++;
   return c;
 }
-// Whether a causal grid of kernels that run two workgroups per CU is mirrored: more than one and at most two
-// workgroups for every CU, all of them resident from the start.  In order of the blocks a CU's two workgroups are
-// 32 blocks of a run apart, of equal length where 32 is a multiple of a head's blocks; mirrored, the longest
-// shares a CU with the shortest.  Longer grids even out by themselves.  Causal calls with gradients, in order /
-// mirrored, us: d = 64, 64 heads x 1024 rows (512 workgroups) 108.6 / 94.6 (forward 29.9 / 25.6, dQ 36.5 / 32.0,
-// dK/dV 48.5 / 44.2), 32 x 2048 (512) 184 / 156, 32 x 1700 (448) 138 / 134; d = 96, 32 x 1300 (352) 147 / 125;
-// d = 80, 24 x 2500 (480) 239 / 210; d = 64, 8 x 4500 (288) 297 / 298.
-inline int mirrored(long long blocks, int causal) { return causal && blocks > 256 && blocks <= 512; }
+// Whether blocks of `br` query rows differ by more than a tenth in the keys they see; the same for blocks of `bc` keys of one chunk.
+inline bool unequal_rows(const KParams& p, const Chunk* ch, int n, int br) {
+  if (!p.causal) return false;
+  auto keys = [&](long long row0, long long row1) {
+    long long sum = 0;
+    for (int i = 0; i < n; i++) {
+      const long long hi = p.q_off + row1 - ch[i].k_off, lo = p.window > 0 ? p.q_off + row0 - p.window + 1 - ch[i].k_off : 0;
+      const long long from = lo > 0 ? lo : 0, to = hi < ch[i].Nc ? hi : ch[i].Nc;
+      if (to > from) sum += to - from;
+    }
+    return sum;
+  };
+  return 10 * keys(p.Nq > br ? p.Nq - br : 0, p.Nq) > 11 * keys(0, br < p.Nq ? br : p.Nq);
+}
+inline bool unequal_keys(const KParams& p, const Chunk& c, int bc, int br) {
+  if (!p.causal || c.Nc == 0) return false;
+  const RowRange a = row_range(p.Nq, 1, p.window, p.q_off, c.k_off, c.Nc, 0, bc, br);
+  const RowRange b = row_range(p.Nq, 1, p.window, p.q_off, c.k_off, c.Nc, (c.Nc - 1) / bc * bc, bc, br);
+  return 10 * (a.hi - a.lo) > 11 * (b.hi - b.lo);
+}
+// The order in which a grid of heads x blocks workgroups, `fit` to a CU, takes its blocks.  Equal ones go head by head (L2):
+// without a causal mask, few rows against many keys (walks of 512 rows x 8192 keys, 0.99 of the time), windows.  Unequal ones
+// are numbered longest first by the kernels, and are taken in that order over all heads of
+// an XCD: head by head, the second head's longest block starts behind the first one's shortest ones, and the launch ends with
+// the last head's long ones on a few CUs.  Causal calls with gradients, us a launch, head by head / by block: d = 64, 128 heads
+// x 1024 rows forward 43.5 / 31.0, dQ 57.9 / 44.2, dK/dV 81.9 / 56.2; 32 x 4096 144.7 / 97.0, 176 / 124, 230 / 174; d = 128,
+// hand-scheduled, 32 x 4096 forward 205 / 153, dQ 263 / 198, 31 x 3001 118 / 94, 156 / 126, dK/dV 196 / 172; 32 x 8192 (four rounds)
+// 559 / 539, 746 / 719.  Head by head also where nothing has to wait (31 x 1000, d = 96, 248 workgroups 36.0 / 37.5), and where a head
+// alone has two rounds of blocks for its XCD, so that its short ones end the launch (40 x 16384, 64 blocks, 2522 / 2606).
+// Grids of at most `fit` workgroups a CU, all resident from the start, are mirrored besides: in order, a CU's workgroups
+// would all be long or all be short.  (Two a CU, d = 64, 64 heads x 1024 rows, 512 workgroups: 108.6 us a call in order, 94.6
+// mirrored; d = 96, 32 x 1300, 352: 147 / 125.)
+inline int grid_order(long long heads, long long blocks, bool unequal, int fit) {
+  if (!unequal || heads * blocks <= 256 || (heads % 8 == 0 && blocks >= 64 * fit)) return 0;
+  return heads * blocks <= 256LL * fit ? kByBlock | kMirror : kByBlock;
+}
 inline long long grid_blocks(long long heads, long long blocks) { return (heads * blocks + 7) / 8 * 8; }
 // Workgroup id of a split dK/dV launch -> (head, block of keys, part).  An XCD gets whole (head, part) columns, longest
 // block first; which part a column holds turns with the block, so that the XCDs with the high columns are not idle where

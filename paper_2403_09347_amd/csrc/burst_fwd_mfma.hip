@@ -47,6 +47,7 @@ struct FwdArgs {
   long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
   int q_blocks;          // ceil(Nq / FWD_BR)
+  int order;             // see grid_order
   int bsize;             // block flags: edge, a multiple of 64, so a wavefront's 64 rows and a key tile lie in one block
   int n;                 // chunks (with block flags: one)
   Layout lay;            // strides of Q and O_out
@@ -129,7 +130,7 @@ burst_fwd_mfma_kernel(FwdArgs a) {
   const int w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
 
   int head, qb;
-  if (!locate_block(blockIdx.x, a.H, a.q_blocks, head, qb)) return;   // whole workgroup exits together
+  if (!locate_block(blockIdx.x, a.H, a.q_blocks, head, qb, a.order)) return;   // whole workgroup exits together
   // causal: the later a query block, the more key tiles it sees; the blocks of a head start
   // in descending order so that the long ones do not end up in the last round
   if (a.causal) qb = a.q_blocks - 1 - qb;
@@ -628,6 +629,7 @@ int launch_fwd_mfma(const KParams& p, const FwdIo& io, const Chunk* ch, int n, h
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
   const long long nblocks = grid_blocks(a.H, a.q_blocks);
   if (nblocks > 0x7fffffffLL) return BURST_ERR_SHAPE;
+  a.order = grid_order(a.H, a.q_blocks, unequal_rows(p, ch, n, FWD_BR), 1);
   static DeviceOnce lds_opt_in;
   const int st = lds_opt_in.run([] {
     return hipFuncSetAttribute((const void*)burst_fwd_mfma_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -45,6 +45,7 @@ struct GenArgs {
   int group;                                      // query heads per key/value head
   int acc_dq, acc_dkv;
   int blocks;                                     // forward, dQ: 32-row blocks per head
+  int order;                                      // see grid_order
   int n;                                          // chunks
   Chunk ch[kMaxChunks];
   // SPLIT: a block's tiles are shared by the wavefronts of several workgroups, whose partial results another launch merges
@@ -242,7 +243,7 @@ fwd_generic_kernel(GenArgs a) {
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk, split = 0;
-  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk)) return;
+  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk, a.order)) return;
   if constexpr (SPLIT) {
     split = blk % a.splits; blk /= a.splits;
   }
@@ -510,7 +511,7 @@ bwd_dq_generic_kernel(GenArgs a) {
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int head, blk, split = 0;
-  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk)) return;
+  if (!locate_block(blockIdx.x, a.BH, SPLIT ? a.blocks * a.splits : a.blocks, head, blk, a.order)) return;
   if constexpr (SPLIT) {
     split = blk % a.splits; blk /= a.splits;
   }
@@ -761,7 +762,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
   if constexpr (SPLIT) {
     if (!locate_part((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, a.parts.splits, kvhead, blk, part)) return;
   } else {
-    if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk)) return;
+    if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk, a.order)) return;
   }
   const int key0 = blk * 32, key = key0 + lr;
   int lo, hi;
@@ -1188,7 +1189,7 @@ static int gen_split(GenArgs& a, long long grid, hipStream_t s) {      // (fp32,
   return launch_status();
 }
 template <int KIND>
-static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
+static int gen_dispatch(GenArgs& a, const KParams& p, int dtype, hipStream_t s) {
   long long grid = 0;
   if (KIND == GEN_DKV) {
     for (int i = 0; i < a.n; i++) {
@@ -1203,6 +1204,8 @@ static int gen_dispatch(GenArgs& a, int dtype, hipStream_t s) {
   }
   if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
   if (grid == 0) return BURST_OK;
+  if (KIND == GEN_DKV) a.order = a.n == 1 && a.parts.splits == 1 ? grid_order(a.BH / a.group, (a.ch[0].Nc + 31) / 32, unequal_keys(p, a.ch[0], 32, 32), 1) : 0;
+  else a.order = grid_order(a.BH, (long long)a.blocks * a.splits, unequal_rows(p, a.ch, a.n, 32), 1);
   if (KIND == GEN_DKV ? a.parts.splits > 1 : a.splits > 1) {
     if (dtype != BURST_F32 || !fp32_tiles(a.d, a.lay, a.ch, a.n) || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;
     return gen_split<KIND>(a, grid, s);
@@ -1235,7 +1238,7 @@ int launch_fwd_generic(const KParams& p, int dtype, const FwdIo& io, const Chunk
   a.Q = io.Q; a.O_acc = io.O_acc; a.m = io.m; a.l = io.l; a.O_out = io.O_out; a.lse_out = io.lse;
   a.part = io.part; a.splits = io.splits > 1 ? io.splits : 1;
   a.fresh = io.fresh;
-  return gen_dispatch<GEN_FWD>(a, dtype, s);
+  return gen_dispatch<GEN_FWD>(a, p, dtype, s);
 }
 static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk* ch, int n) {
   make_args(a, p, ch, n);
@@ -1246,13 +1249,13 @@ static void bwd_args(GenArgs& a, const KParams& p, const BwdIo& io, const Chunk*
 int launch_bwd_dq_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};
   bwd_args(a, p, io, ch, n);
-  return gen_dispatch<GEN_DQ>(a, dtype, s);
+  return gen_dispatch<GEN_DQ>(a, p, dtype, s);
 }
 int launch_bwd_dkv_generic(const KParams& p, int dtype, const BwdIo& io, const Chunk* ch, int n, hipStream_t s) {
   GenArgs a = {};
   bwd_args(a, p, io, ch, n);
   a.O = nullptr;
-  return gen_dispatch<GEN_DKV>(a, dtype, s);
+  return gen_dispatch<GEN_DKV>(a, p, dtype, s);
 }
 
 }  // namespace burst

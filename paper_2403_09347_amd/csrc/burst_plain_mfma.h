@@ -61,7 +61,7 @@ struct FwdArgsLite {
   float c, scale;                                // c = scale * log2(e)
   long long q_off, window;
   int bsize;
-  int blocks_per_head, splits, mirror;           // mirror: see mirrored()
+  int blocks_per_head, splits, order;            // order: see grid_order
   int d;                                         // head dimension (S_D unless S_PAD)
   int n;                                         // chunks
   Layout lay;                                    // strides of Q and O_out
@@ -78,7 +78,7 @@ struct BwdArgsLite {
   float c, scale, log2_scale;
   long long q_off, window;
   int bsize;
-  int blocks_per_head, splits, mirror;
+  int blocks_per_head, splits, order;
   int d, n;
   int per;                                       // dK/dV: workgroups of every chunk (chunk_at)
   RowParts parts;                                // dK/dV
@@ -203,7 +203,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   int head, qb, split = 0;
-  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.mirror)) return;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.order)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
   const int q0 = qb * SF_BR + w * 32, row = q0 + lr;
@@ -567,7 +567,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
   int head, qb, split = 0;
-  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.mirror)) return;
+  if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.order)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
   const int q0 = qb * SQ_BR + w * 32;
@@ -854,7 +854,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   if constexpr (PARTS) {
     if (!locate_part(bid, a.H, blocks, a.parts.splits, kvhead, kblk, part)) return;
   } else {
-    if (!locate_block(bid, a.H, blocks, kvhead, kblk, a.mirror)) return;
+    if (!locate_block(bid, a.H, blocks, kvhead, kblk, a.order)) return;
   }
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
@@ -1149,7 +1149,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.lay = p.lay; a.d = p.d; a.n = n;
   const int nw = row_waves(p, ch, n, true);
   a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
-  a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
+  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, 32 * nw), 2);
   int longest = 0;
   for (int i = 0; i < n; i++) { a.ch[i] = ch[i]; if (ch[i].Nc > longest) longest = ch[i].Nc; }
   static DeviceOnce done, done2;
@@ -1174,7 +1174,7 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
   if (io.O != nullptr && !S_SUMS) return BURST_ERR_SHAPE;
   const int nw = row_waves(p, ch, n, false);
   a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
-  a.mirror = mirrored((long long)a.H * a.blocks_per_head * a.splits, a.causal && a.splits == 1);
+  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, 32 * nw), 2);
   int longest = 0;
   for (int i = 0; i < n; i++) if (ch[i].Nc > longest) longest = ch[i].Nc;
   static DeviceOnce done, done2;
@@ -1192,7 +1192,7 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   set_row_parts(a, io);
   const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per, a.parts.splits);
   if (a.parts.splits > 1 && ch[0].bmask != nullptr) return BURST_ERR_SHAPE;
-  a.mirror = n == 1 && a.parts.splits == 1 && mirrored(nb, a.causal);
+  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + SK_BC - 1) / SK_BC, unequal_keys(p, ch[0], SK_BC, SK_BR), 2) : 0;
   static DeviceOnce done;
   const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true> : burst_bwd_dkv_d64_kernel<false, false>,
                               burst_bwd_dkv_d64_kernel<true, false>, done, a, nb,
