@@ -220,7 +220,11 @@ const PlainFamily* plain_family(const burst_params* p, const KParams& k) {
 // and 1.1-1.25x (backward) at up to 128 workgroups, 15 % at 320, 3-6 % (forward) at 384 .. 1152;
 // they lose 3-6 % where the rounds are full, and the gain fades as the rounds grow in number.
 std::atomic<int> g_kernel_family{0};            // burst_set_kernel_family
-bool use_plain128(const burst_params* p, const KParams& k) {
+// A causal walk of one chunk (`whole`) has long and short workgroups besides, and the small ones are dealt out more evenly: us,
+// hand-scheduled / plain, forward and dQ, 64 x 777 rows (256 workgroups) 36 / 24 and 43 / 31, 64 x 1024 44 / 31, 52 / 40, 16 x 4096
+// 113 / 89, 146 / 117, 8 x 8192 206 / 165, 273 / 220; up to 512 workgroups 128 x 1024 71 / 55, 82 / 70, 64 x 2048 95 / 85, 116 / 115,
+// but 40 x 3001 117 / 110, 148 / 152, 32 x 4096 148 / 150, 194 / 207.
+bool use_plain128(const burst_params* p, const KParams& k, bool whole = false) {
   if (!use_mfma(p, k)) return false;
   const bool flags = p->block_mask != nullptr;
   if (flags && p->Nc > 4096 * 32) return false;    // their tile lists hold 4096 entries (32-key tiles in dQ)
@@ -230,6 +234,10 @@ bool use_plain128(const burst_params* p, const KParams& k) {
   // skip per wavefront (32 rows x 64 or 32 keys), which is what such patterns need.
   if (flags) return p->block < 256;
   const long long wgs = (long long)p->B * p->H * ((p->Nq + 255) / 256);
+  if (whole && wgs <= (p->Nq <= 2048 ? 512 : 256)) {
+    const Chunk c = burst::chunk_of(k, nullptr, nullptr, nullptr, nullptr);
+    if (burst::unequal_rows(k, &c, 1, 128)) return true;
+  }
   const long long last = wgs % 256;                // workgroups of the last round (0 = full)
   return last != 0 && last <= 128 && wgs <= 1536;
 }
@@ -285,9 +293,9 @@ struct Kernels {
   int takes;                                       // most chunks of one launch (hand-scheduled: of one row pitch)
   bool operator==(const Kernels& o) const { return plain == o.plain && hand == o.hand && key_waves == o.key_waves && takes == o.takes; }
 };
-Kernels fwd_kernels(const burst_params* p, const KParams& k) {      // dQ: the same choice
+Kernels fwd_kernels(const burst_params* p, const KParams& k, bool whole = false) {      // dQ: the same choice
   if (const PlainFamily* f = plain_family(p, k)) return {f, false, 0, burst::kMaxChunks};
-  if (use_plain128(p, k)) return {&kD128p, false, 0, burst::kMaxChunks};
+  if (use_plain128(p, k, whole)) return {&kD128p, false, 0, burst::kMaxChunks};
   const bool hand = use_mfma(p, k) && (p->block_mask == nullptr || p->Nc <= kMaxMaskedRows);
   return {nullptr, hand, 0, hand && p->block_mask != nullptr ? 1 : burst::kMaxChunks};
 }
@@ -377,6 +385,12 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
   return BURST_OK;
 }
 
+// The choice for a walk's forward and dQ launches.  `whole`: one chunk, and neither a state nor fp32 gradients that a caller could
+// go on with chunk by chunk, in which case a walk has the bits it has chunk by chunk.
+auto walk_choice(bool whole) {
+  return [whole](const burst_params* p, const KParams& k) { return fwd_kernels(p, k, whole); };
+}
+
 // Walks of the generic kernels that can be split: fp32 through LDS, no flags.
 bool generic_splittable(const std::vector<WalkChunk>& w) {
   if (w[0].p.dtype != BURST_F32) return false;
@@ -422,19 +436,52 @@ int generic_splits(const std::vector<WalkChunk>& w) {
 // twice as many: 32 heads x 40 rows x 32K keys 597 / 116 in 16 (8: 120, 24: 134); 32 x 512 x 8K causal 168 / 95 in 4
 // (2: 106, 8: 108); 8 x 100 x 4K, d = 64, 63 / 24 in 8 (4: 28, 16: 22); 8 x 1024 x 4K 85 / 38 in 8
 // (4: 39, 16: 52); backward (dQ) 32 x 512 x 8K 664 / 585, 8 x 1024 x 4K 257 / 191.
-int walk_splits(const std::vector<WalkChunk>& w) {
-  if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return 1;
-  const Kernels f = fwd_kernels(&w[0].p, w[0].k);
-  if (f.plain == nullptr) return generic_splits(w);
+//
+// Key groups: a workgroup's four wavefronts own 128 rows, or 64 rows and a half of every tile's keys each (`groups` = 2, see
+// burst_plain_mfma.h): twice the workgroups, half as long, for twice the traffic into LDS.  A `whole` walk (see walk_choice) that is not
+// split has two where its workgroups of 128 rows are few, or unequal and not too many (LDS rows of 128 bytes: four
+// of 64 rows share a CU, of 256 bytes: two).  Forward + dQ, us, one / two groups, causal: d = 64, 8 x 512 rows (32 workgroups of
+// 128) 31 / 23, 32 x 1000 (256) 49 / 37, 64 x 1024 (512) 56 / 46, 40 x 2048 (640) 96 / 92, 96 x 1024 (768) 64 / 67, 16 x 8192 (1024)
+// 407 / 396, 64 x 4096 (2048) 382 / 409; d = 40, 24 x 4096 (768) 293 / 251, 128 x 1024 (1024) 112 / 111; d = 96, 32 x 777 (224) 68 /
+// 51, 48 x 1024 (384) 84 / 76, 80 x 700 (480) 64 / 69, 16 x 4000 (512) 293 / 274, 128 x 1024 (1024) 157 / 169; d = 128, 32 x 1000
+// (256) 65 / 49, 24 x 2048 (384) 110 / 93, 64 x 1024 (512) 71 / 79, 16 x 4096 (512) 213 / 206; without a mask: d = 64, 20 x 2048
+// (320) 100 / 84, 48 x 1024 (384) 60 / 53, 64 x 1024 (512) 65 / 67; d = 96, 24 x 1024 (192) 79 / 69, 40 x 777 (280) 94 / 94; d =
+// 128, 32 x 1000 (256) 66 / 61.
+// Such a walk is split only where that is worth the merging launches: from 32 tiles on (24 on the padded kernels), as many
+// ranges as its workgroups have places for (forward + dQ with merging and D, us, whole / split: d = 64, 8 x 1500 42 / 40,
+// 8 x 2048 53 / 46, 16 x 2048 56 / 58, 8 x 4000 92 / 79; d = 96, 16 x 1000 54 / 54, 8 x 2048 89 / 71, 12 x 2048 91 / 89; d = 128,
+// 8 x 1500 58 / 58, 8 x 2048 74 / 65, 12 x 2048 75 / 82).
+// Split walks have two groups too where their workgroups of 128 rows are at most one a CU, or would hold 64 rows less
+// (forward, us: d = 64, 32 over 8 x 16 rows x 16K keys 40 / 31, 80 over 20 x 150 x 8K 76 / 64, 8 x 100 x 8K 26 / 22, 32 x 200 x 64K
+// 188 / 221 (one); d = 128, 32 over 2 x 5 x 64K 145 / 99, 80 over 20 x 150 x 8K 107 / 114 (one), 32 x 200 x 64K 309 / 413 (one)).
+struct RowsPlan { int splits, groups; };
+RowsPlan walk_rows(const std::vector<WalkChunk>& w, bool backward, bool whole) {
+  if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return {1, 1};
+  const Kernels f = fwd_kernels(&w[0].p, w[0].k, whole);
+  if (f.plain == nullptr) return {generic_splits(w), 1};
   const KParams& k = w[0].k;
+  const bool wide = f.plain == &kD96x || f.plain == &kD128x || f.plain == &kD128p;
+  const bool padded = f.plain != &kD64 && f.plain != &kD128p;
   const long long blocks = (long long)k.B * k.H * ((k.Nq + 127) / 128);
   long long tiles = 0;                             // of 64 keys, that the last rows see
   for (const WalkChunk& x : w) {
-    if (x.p.block_mask != nullptr || !(fwd_kernels(&x.p, x.k) == f)) return 1;
+    if (x.p.block_mask != nullptr || !(fwd_kernels(&x.p, x.k, whole) == f)) return {1, 1};
     long long lo = 0, hi = x.c.Nc;
     if (k.causal) hi = std::min(hi, k.q_off + k.Nq - x.c.k_off);
     if (k.window > 0) lo = std::max(lo, k.q_off + k.Nq - 128 - k.window + 1 - x.c.k_off);
     if (hi > lo) tiles += (hi - lo + 63) / 64;
+  }
+  const bool unequal = whole && burst::unequal_rows(k, &w[0].c, 1, 128);
+  auto unsplit = [&]() -> RowsPlan {
+    bool two;
+    if (!wide) two = blocks <= (!unequal ? 448 : padded ? 896 : k.Nq >= 4096 ? 1024 : 640);
+    else two = unequal ? blocks <= 352 || (blocks <= 448 && padded && k.Nq >= 1000) || (blocks <= 512 && k.Nq >= 2048) : blocks <= 224;
+    return {1, whole && two ? 2 : 1};
+  };
+  if (whole && blocks > 32 && (backward || !padded)) {
+    const long long s = std::min((wide ? 256 : 512) / blocks, tiles / 8);
+    if (s >= 2 && tiles >= (padded ? 24 : 32)) return {(int)s, unequal || blocks * s <= 256 ? 2 : 1};
+    return unsplit();
   }
   // The padded kernels' tiles take twice the time: up to 160 blocks 6 of them are a range, and walks of 12 are split (d = 96, causal,
   // whole / split, forward and backward pass, us: 16 x 900, 128 blocks, in 2 32.8 / 29.3, 99 / 95; 16 x 1216, 160, in 3 39.9 / 36.8,
@@ -445,14 +492,15 @@ int walk_splits(const std::vector<WalkChunk>& w) {
   // alternative is one range (130 x 100 rows x 1200 keys, in 1 / 3, 42.0 / 34.6); walks of equal length later (d = 32, 8 x 958 x 2268, in 4 / 6,
   // 24.5 / 27.6; d = 96, 8 x 1500 in 2 / 4 37.7 / 38.9).  From 161 blocks on as elsewhere
   // (24 x 1000, 192, in 2: 35.3 / 40.4, not split).
-  const bool pad = f.plain != &kD64 && f.plain != &kD128p && blocks <= 160;
+  const bool pad = padded && blocks <= 160;
   long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
   if (pad && s * blocks > 256 && s * blocks <= (k.causal || blocks > 128 ? 360 : 400)) s = 256 / blocks;
-  return s < 2 || tiles < (pad ? 12 : 20) ? 1 : (int)s;
+  if (s < 2 || tiles < (pad ? 12 : 20)) return unsplit();
+  return {(int)s, s * blocks <= 256 || k.Nq <= 64 || (!wide && (k.Nq - 1) % 128 < 64) ? 2 : 1};
 }
-int dq_launches(const std::vector<WalkChunk>& w) {
+int dq_launches(const std::vector<WalkChunk>& w, bool whole) {
   int n = 0;
-  for_each_run(w, fwd_kernels, [&](const Kernels&, const KParams&, const Chunk*, int, bool, bool) { n++; return (int)BURST_OK; });
+  for_each_run(w, walk_choice(whole), [&](const Kernels&, const KParams&, const Chunk*, int, bool, bool) { n++; return (int)BURST_OK; });
   return n;
 }
 // How the dK/dV launch of a walk is cut (RowParts; splits = 1: not at all).  Few or unequal walks leave most of the chip idle:
@@ -468,14 +516,21 @@ int dq_launches(const std::vector<WalkChunk>& w) {
 // cut: 64 x 1024, d = 64, 98 (in 2: 112), 16 x 3000 279 (301), 16 x 4096 403 (440).
 // Partial gradients have room for the keys of a chunk from its first block with several parts to its last: hidden chunks and
 // the short ends of masked ones take none.
-constexpr burst::RowPlan kWhole = {{nullptr, 1, 1, 1, 0}, {}};
+// Row groups: a whole walk (see walk_choice) on the plain kernels of four wavefronts may have workgroups of 64 keys instead, two halves of every
+// tile's rows each (see burst_plain_mfma.h).  They take the place of the parts, whose launch and traffic they save, where
+// there are blocks enough: us, whole or parts with their merge / row groups, causal: d = 64, 8 x 1000 (64 blocks of 128 keys) 20.5 / 19.5,
+// 8 x 2048 (128) 37 / 35, 8 x 4000 (256) 61 / 65 (parts), 32 x 1000 (256) 35 / 22, 64 x 1024 (512) 39 / 34, 24 x 4096 (768) 136 / 131,
+// 32 x 4096 (1024) 171 / 177; d = 96, 8 x 1000 (64) 31 / 36 (parts), 16 x 777 (112) 33 / 32, 8 x 2048 (128) 62 / 68 (parts), 32 x 777
+// (224) 43 / 35, 20 x 2048 (320) 103 / 82, 16 x 4000 (512) 257 / 219, 64 x 2048 (1024) 226 / 216; without a mask: d = 64, 8 x 4096
+// (256) 121 / 87, 48 x 1024 (384) 43 / 41, 64 x 1024 (512) 46 / 49; d = 96, 24 x 1024 (192) 72 / 53, 64 x 1024 (512) 106 / 111.
+constexpr burst::RowPlan kWhole = {{nullptr, 1, 1, 1, 0}, {}, 1};
 // Workgroups per block for at most `most` parts: whole (head, part) columns go to the 8 XCDs, so their number should be a
 // multiple of 8 (workgroups without a part end at once).
 int part_columns(long long heads, long long most) {
   for (long long s = most; s < most + 8; s++) if (heads * s % 8 == 0) return (int)s;
   return (int)most;
 }
-burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
+burst::RowPlan cut_walks(const std::vector<WalkChunk>& w) {
   if (w.empty() || w[0].k.Nq == 0 || w.size() > (size_t)burst::kMaxChunks) return kWhole;
   const Kernels f = dkv_kernels(&w[0].p, w[0].k);
   if (f.plain == &kD128p) return kWhole;           // (it runs only when its family is forced)
@@ -501,7 +556,7 @@ burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
     }
   }
   auto cut = [&](long long parts, int tiles) {
-    burst::RowPlan plan = {{nullptr, part_columns(heads, parts), (int)parts, tiles, 0}, {}};
+    burst::RowPlan plan = {{nullptr, part_columns(heads, parts), (int)parts, tiles, 0}, {}, 1};
     burst::RowParts& p = plan.parts;
     for (size_t i = 0; i < w.size(); i++) {
       int lo = -1, hi = 0;
@@ -536,6 +591,20 @@ burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w) {
   if (f.hand ? share + (most + splits - 1) / splits >= most : most - share < (f.plain == &kD64 ? 16 : 6)) return kWhole;
   return cut(splits, 8);
 }
+burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w, bool half) {
+  burst::RowPlan plan = cut_walks(w);
+  if (!half || w.size() != 1 || w[0].p.block_mask != nullptr || w[0].k.Nq == 0) return plan;
+  const Kernels f = dkv_kernels(&w[0].p, w[0].k);
+  if (f.plain == nullptr || f.plain->dkv_keys() != 128) return plan;
+  const KParams& k = w[0].k;
+  const long long blocks = (long long)k.B * k.H / k.group * ((w[0].c.Nc + 127) / 128), walk = (long long)k.group * ((k.Nq + 31) / 32);
+  const bool narrow = f.plain == &kD64;
+  if (plan.parts.splits > 1 && (blocks <= (narrow ? 48 : 64) || (blocks <= 128 && !narrow && walk >= 32) || (blocks <= 256 && walk >= 96))) return plan;
+  if (blocks > (!burst::unequal_keys(k, w[0].c, 128, 32) ? 448 : narrow ? 768 : 1024)) return plan;
+  plan = kWhole;
+  plan.groups = 2;
+  return plan;
+}
 size_t dkv_bytes(const KParams& k, const burst::RowPlan& plan) {
   const burst::RowParts& p = plan.parts;
   return p.splits > 1 ? (size_t)p.most * 2 * p.rows * k.d * sizeof(float) : 0;
@@ -551,9 +620,9 @@ size_t dkv_bytes(const KParams& k, const burst::RowPlan& plan) {
 // 85.3 / 85.8; 4 x 500 32.4 / 31.5; d = 128, 8 x 1423 causal, 360 blocks, 290.3 / 287.9, 16 x 1000 x 64, 512, 112.8 / 114.0; d = 96, 16 x 800 x 1600
 // causal 386.0 / 385.6) and the launch saved is the host's (256 rows x 1024 keys, 82 / 77 a pass; 8 x 700 x 1400, 247.8 / 246.0);
 // rows of at most 48 columns up to four a CU (d = 24, 32 x 805 x 41 29.5 / 28.3; d = 48, 16 x 1000 causal 135.0 / 133.8, 32 x 8192 x 32 205 / 216).
-bool d_by_dq(const std::vector<WalkChunk>& w, int splits) {
+bool d_by_dq(const std::vector<WalkChunk>& w, int splits, bool whole) {
   if (w.empty()) return false;
-  const Kernels f = fwd_kernels(&w[0].p, w[0].k);
+  const Kernels f = fwd_kernels(&w[0].p, w[0].k, whole);
   if (f.plain != nullptr) return f.plain != &kD128p && splits == 1;
   const long long blocks = (long long)w[0].k.B * w[0].k.H * (((long long)w[0].k.Nq + 31) / 32);
   if (f.hand || w[0].p.dtype != BURST_F32 || blocks > (w[0].k.d <= 48 ? 1024 : 512)) return false;
@@ -587,7 +656,7 @@ int burst_local_fwd(const void* Q, const void* K_chunk, const void* V_chunk,
   REQUIRE_PTR(Q); REQUIRE_PTR(K_chunk); REQUIRE_PTR(V_chunk);
   REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l);
   if ((st = check_arch()) != BURST_OK) return st;
-  const FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, 0, nullptr, 1};
+  const FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, 0, nullptr, 1, 1};
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, nullptr, nullptr);
   return fwd_launch(fwd_kernels(p, k), k, p->dtype, io, &c, 1, (hipStream_t)stream);
 }
@@ -749,7 +818,7 @@ static int local_bwd_impl(int which, const void* Q, const void* K_chunk, const v
   const Chunk c = burst::chunk_of(k, K_chunk, V_chunk, dK_chunk, dV_chunk);
   auto enqueue = [&](const float* Duse, float* Dwrite) -> int {
     int e;
-    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, nullptr};
+    const BwdIo io = {Q, dO, lse, Duse, dQ, accumulate_dq != 0, accumulate_dkv != 0, 0, nullptr, 1, nullptr, nullptr, 1};
     if (Dwrite != nullptr && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, Dwrite, s)) != BURST_OK) return e;
     if (want_dq && (e = dq_launch(fq, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
     if (want_dkv && (e = dkv_launch(fk, k, p->dtype, io, &c, 1, s)) != BURST_OK) return e;
@@ -802,9 +871,13 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
   if (walk_chunks(chunks, n_chunks, p, false, w) != BURST_OK || w.empty()) return 0;
   const KParams& k = w[0].k;
   const size_t rows = (size_t)k.B * k.H * k.Nq;
-  size_t need = split_bytes(k, walk_splits(w));
-  if (!(flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD))) need = std::max(need, dkv_bytes(k, dkv_parts(w)));
-  if ((flags & (BURST_WALK_NO_STATE | BURST_WALK_HALF_GRADS)) && dq_launches(w) > 1) {          // between the launches: dQ in fp32, the state
+  size_t need = 0;
+  const bool fwd = (flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD)) != 0, bwd = (flags & BURST_WALK_HALF_GRADS) != 0;   // (neither: both)
+  const bool whole_fwd = w.size() == 1 && (flags & BURST_WALK_NO_STATE), whole_bwd = w.size() == 1 && bwd;
+  if (fwd || !bwd) need = split_bytes(k, walk_rows(w, false, whole_fwd).splits);
+  if (bwd || !fwd) need = std::max(need, split_bytes(k, walk_rows(w, true, whole_bwd).splits));
+  if (!(flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD))) need = std::max(need, dkv_bytes(k, dkv_parts(w, (flags & BURST_WALK_HALF_GRADS) != 0)));
+  if ((flags & (BURST_WALK_NO_STATE | BURST_WALK_HALF_GRADS)) && dq_launches(w, w.size() == 1) > 1) {          // between the launches: dQ in fp32, the state
     if (flags & BURST_WALK_HALF_GRADS) need = std::max(need, rows * k.d * sizeof(float));
     if (flags & BURST_WALK_NO_STATE) need = std::max(need, rows * ((size_t)k.d + 8) * sizeof(float));
   }
@@ -815,7 +888,7 @@ int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_par
   std::vector<WalkChunk> w;
   const int st = walk_chunks(chunks, n_chunks, p, false, w);
   if (st != BURST_OK || w.empty() || w[0].k.Nq == 0) return st;
-  if (with_workspace && dkv_parts(w).parts.splits > 1) return 1;
+  if (with_workspace && dkv_parts(w, false).parts.splits > 1) return 1;
   int form = -1;
   for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
     if (form < 0) form = f.hand && f.key_waves == 4 && burst::dkv_chained(kc, c, n) ? 2 : 0;
@@ -839,32 +912,32 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
   if ((st = walk_chunks(chunks, n_chunks, p, false, w)) != BURST_OK) return st;
   if ((long long)k.B * k.H * k.Nq == 0) return BURST_OK;
   REQUIRE_PTR(Q); REQUIRE_PTR(O_out); REQUIRE_PTR(lse);
-  const bool keep = O_acc != nullptr || m != nullptr || l != nullptr;
+  const bool keep = O_acc != nullptr || m != nullptr || l != nullptr, whole = !keep && w.size() == 1;
   if (keep) { REQUIRE_PTR(O_acc); REQUIRE_PTR(m); REQUIRE_PTR(l); }
   if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  if (!keep && (w.empty() || dq_launches(w) > 1)) {   // (as many launches as dQ takes)
+  if (!keep && (w.empty() || dq_launches(w, whole) > 1)) {   // (as many launches as dQ takes)
     const size_t rows = (size_t)k.B * k.H * k.Nq;
     if (w.empty()) return burst::launch_fill_unseen(k, p->dtype, O_out, lse, s);
     if (workspace == nullptr || workspace_bytes < rows * ((size_t)k.d + 8) * sizeof(float)) return BURST_ERR_SHAPE;
     O_acc = (float*)workspace; m = O_acc + rows * k.d; l = m + (rows + 3) / 4 * 4;
   }
-  int splits = walk_splits(w);
-  if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
-  if (splits > 1) {
-    const FwdIo io = {Q, O_acc, m, l, O_out, lse, 1, (float*)workspace, splits};
+  RowsPlan rows = walk_rows(w, false, whole);
+  if (rows.splits > 1 && (workspace == nullptr || workspace_bytes < split_bytes(k, rows.splits))) rows = {1, 1};
+  if (rows.splits > 1) {
+    const FwdIo io = {Q, O_acc, m, l, O_out, lse, 1, (float*)workspace, rows.splits, rows.groups};
     return validated([&] {
-      const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
+      const int e = for_each_run(w, walk_choice(whole), [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
         return fwd_launch(f, kc, p->dtype, io, c, n, s);
       });
-      return e != BURST_OK || fwd_kernels(&w[0].p, w[0].k).plain == nullptr ? e : burst::launch_merge_splits(k, io, s);   // (the generic launcher merges by itself)
+      return e != BURST_OK || fwd_kernels(&w[0].p, w[0].k, whole).plain == nullptr ? e : burst::launch_merge_splits(k, io, s);   // (the generic launcher merges by itself)
     });
   }
   return validated([&] {
     bool fresh = true, final = false;
-    const int e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
-      FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, fresh, nullptr, 1};
+    const int e = for_each_run(w, walk_choice(whole), [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool last) {
+      FwdIo io = {Q, O_acc, m, l, nullptr, nullptr, fresh, nullptr, 1, rows.groups};
       if (last) { io.O_out = O_out; io.lse = lse; final = true; }
       fresh = false;
       return fwd_launch(f, kc, p->dtype, io, c, n, s);
@@ -901,14 +974,16 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
   if (workspace != nullptr && !aligned16(workspace)) return BURST_ERR_ALIGN;
   if ((st = check_arch()) != BURST_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  int splits = walk_splits(w);
-  if (workspace == nullptr || workspace_bytes < split_bytes(k, splits)) splits = 1;
-  burst::RowPlan parts = dkv_parts(w);
-  if (workspace == nullptr || workspace_bytes < dkv_bytes(k, parts)) parts = kWhole;
+  const bool whole = half && w.size() == 1;
+  RowsPlan rows = walk_rows(w, true, whole);
+  if (rows.splits > 1 && (workspace == nullptr || workspace_bytes < split_bytes(k, rows.splits))) rows = {1, 1};
+  const int splits = rows.splits;
+  burst::RowPlan parts = dkv_parts(w, half);
+  if (parts.parts.splits > 1 && (workspace == nullptr || workspace_bytes < dkv_bytes(k, parts))) parts = kWhole;
   parts.parts.part = (float*)workspace;
   auto zero = [&](void* ptr, long long n) { return burst::launch_zero_fill((float*)ptr, n, half, s); };
   // dQ as bf16 by several launches: fp32 in the workspace between them
-  const bool staged = half && have_q && splits == 1 && !w.empty() && dq_launches(w) > 1;
+  const bool staged = half && have_q && splits == 1 && !w.empty() && dq_launches(w, whole) > 1;
   if (staged && (workspace == nullptr || workspace_bytes < (size_t)bh * k.Nq * k.d * sizeof(float))) return BURST_ERR_SHAPE;
   return validated([&]() -> int {
     int e = BURST_OK;
@@ -920,12 +995,12 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
       }
       return BURST_OK;
     }
-    const bool fused = O != nullptr && d_by_dq(w, splits);
+    const bool fused = O != nullptr && d_by_dq(w, splits, whole);
     if (O != nullptr && !fused && (e = burst::launch_bwd_prepare(k, p->dtype, O, dO, D, s)) != BURST_OK) return e;
     if (w.empty()) return accumulate_dq ? (int)BURST_OK : zero(dQ, bh * k.Nq * k.d);
     BwdIo io = {Q, dO, lse, D, dQ, accumulate_dq != 0, accumulate_dkv != 0, half, (float*)workspace, splits,
-                parts.parts.splits > 1 ? &parts : nullptr, nullptr};
-    e = for_each_run(w, fwd_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
+                parts.parts.splits > 1 || parts.groups > 1 ? &parts : nullptr, nullptr, rows.groups};
+    e = for_each_run(w, walk_choice(whole), [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool first, bool) {
       BwdIo one = io;
       one.acc_dq = accumulate_dq != 0 || !first;
       one.O = fused && first ? O : nullptr;
@@ -933,7 +1008,7 @@ int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const
       return dq_launch(f, kc, p->dtype, one, c, n, s);
     });
     if (e != BURST_OK) return e;
-    if (((splits > 1 && fwd_kernels(&w[0].p, w[0].k).plain != nullptr) || staged) && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
+    if (((splits > 1 && fwd_kernels(&w[0].p, w[0].k, whole).plain != nullptr) || staged) && (e = burst::launch_sum_splits(k, io, s)) != BURST_OK) return e;
     return for_each_run(w, dkv_kernels, [&](const Kernels& f, const KParams& kc, const Chunk* c, int n, bool, bool) {
       return dkv_launch(f, kc, p->dtype, io, c, n, s);
     });

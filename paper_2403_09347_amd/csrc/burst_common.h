@@ -112,6 +112,7 @@ struct FwdIo {
   void* O_out; float* lse;           // O_out != nullptr: the state is final after this launch, write these too
   int fresh;                         // the state before the launch is the initial one, whatever the buffers hold
   float* part; int splits;           // splits > 1: partial states of that many key ranges go to `part` instead
+  int groups;                        // plain kernels: key groups of a workgroup (0 and 1: one)
 };
 struct BwdIo {
   const void* Q; const void* dO; const float* lse; const float* D;
@@ -121,6 +122,7 @@ struct BwdIo {
   float* part; int splits;           // splits > 1: dQ of that many key ranges goes to `part` instead
   const struct RowPlan* parts;       // dK/dV: how the walks are cut (nullptr: not at all)
   const void* O;                     // dQ, plain and generic kernels: D = rowsum(dO o O) is computed and written first (nullptr: it is there)
+  int groups;                        // dQ, plain kernels: as in FwdIo
 };
 
 // How a dK/dV launch deals out its work.  A workgroup's walk are the query tiles its keys are visible to, of all heads of
@@ -144,7 +146,7 @@ struct RowParts {
     return part + ((size_t)(2 * i + dv) * rows + C.first_row + (size_t)head * C.span_keys) * d;
   }
 };
-struct RowPlan { RowParts parts; RowSpan span[kMaxChunks]; };
+struct RowPlan { RowParts parts; RowSpan span[kMaxChunks]; int groups; };   // groups: row groups of a workgroup of the plain kernels, whole walks
 // The query tiles (BR rows) of one head that see a key of the block [key0, key0 + BC) of a chunk: [lo, hi).
 struct RowRange { int lo, hi; };
 __host__ __device__ inline RowRange row_range(int Nq, int causal, long long window, long long q_off, long long k_off, int Nc,

@@ -192,12 +192,16 @@ __device__ __forceinline__ int s_build_list(int* list, int w, int lane, int t_lo
 // then hold what the workgroup's 64 rows see and nothing else, so that no wavefront waits for another's tiles.  Such a
 // workgroup takes 32 keys a tile instead of 64, so that as many wavefronts share a CU's LDS.
 constexpr int sf_keys(int NW) { return NW == 2 ? 32 : 64; }
-template <bool SPARSE, int NW>
+// KG = 2: the four wavefronts are two row blocks times two halves of every tile's keys; the halves' states meet in LDS at the
+// end.  Half the rows a workgroup make twice the workgroups, and each wavefront walks half as many scores: a causal call that fits the
+// chip once is bound by its longest wavefronts, alone on their SIMDs, whose vector and matrix work do not overlap.  32 heads of
+// 777 causal rows, d = 96: 31 -> 23 us (dQ 37 -> 24); 32 of 1000, d = 64: 21 -> 15 (27 -> 18).  Rule and more sizes: walk_rows.
+template <bool SPARSE, int NW, int KG>
 __global__ void __launch_bounds__(64 * NW, 2)     // (second figure: wavefronts per SIMD)
 burst_fwd_d64_kernel(FwdArgsLite a) {
-  constexpr int SF_BR = 32 * NW;                  // query rows per workgroup
+  constexpr int RW = NW / KG, SF_BR = 32 * RW;    // row blocks, query rows per workgroup
   constexpr int SF_BC = sf_keys(NW), SF_TILE = SF_BC * S_ROWB;   // keys per tile
-  constexpr int KB = SF_BC / 32;                  // 32-key blocks of a tile
+  constexpr int KB = SF_BC / 32 / KG;             // 32-key blocks of a wavefront's share of a tile
   __shared__ __attribute__((aligned(16))) char smem[4 * SF_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
@@ -206,9 +210,10 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.order)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
-  const int q0 = qb * SF_BR + w * 32, row = q0 + lr;
-  const int kvhead = head / a.group;
   const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int rw = KG == 1 ? wu : wu % RW, koff = KG == 1 ? 0 : wu / RW * (32 * KB);   // row block; first key of the share
+  const int q0 = qb * SF_BR + (KG == 1 ? w : rw) * 32, row = q0 + lr;
+  const int kvhead = head / a.group;
   const unsigned lds0 = lds_addr(smem);
 
   // The chunks' visible tiles (or list entries) form one sequence, walked with the next tile in flight across the
@@ -342,13 +347,13 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 #pragma unroll
   for (int ks = 0; ks < S_KS; ks++) kaddr[ks] = s_off(lr, 2 * ks + h);
   s_taddr(lane, taddr);
-  const long long wave_first_q = a.q_off + qb * SF_BR + wu * 32, wave_last_q = wave_first_q + 31;   // (scalar)
+  const long long wave_first_q = a.q_off + qb * SF_BR + rw * 32, wave_last_q = wave_first_q + 31;   // (scalar)
   bf16x2 ones;
   ones[0] = (bf16)1.0f; ones[1] = (bf16)1.0f;
 
-  // The scores of a tile, masked, and the row's maximum of them (see s_units).
-  auto scores = [&](const char* kl, int kt, int Nc, long long k_off, f32x16 (&s)[KB]) __attribute__((always_inline)) {
-    // S^T = K Q^T: register r of key block kb = key kt*64 + kb*32 + 8*(r/4) + 4h + r%4
+  // The scores of a wavefront's share of a tile (from key `first` on), masked, and the row's maximum of them (see s_units).
+  auto scores = [&](const char* kl, int first, int Nc, long long k_off, f32x16 (&s)[KB]) __attribute__((always_inline)) {
+    // S^T = K Q^T: register r of key block kb = key first + kb*32 + 8*(r/4) + 4h + r%4
 #pragma unroll
     for (int kb = 0; kb < KB; kb++)
 #pragma unroll
@@ -358,13 +363,12 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 #pragma unroll
       for (int kb = 0; kb < KB; kb++)
         s[kb] = mfma32(lds_read_b128(kl, kb * 32 * S_ROWB + kaddr[ks]), qf[ks], s[kb]);
-    const long long tile_first_k = k_off + (long long)kt * SF_BC;
-    const bool need_mask = (a.causal && tile_first_k + SF_BC - 1 > wave_first_q) ||
-                           (a.window > 0 && tile_first_k < wave_last_q - a.window + 1) ||
-                           ((kt + 1) * SF_BC > Nc);
+    const long long tile_first_k = k_off + first;
+    const bool need_mask = ((a.causal != 0) & (tile_first_k + 32 * KB - 1 > wave_first_q)) |   // (no short circuits: one branch)
+                           ((a.window > 0) & (tile_first_k < wave_last_q - a.window + 1)) | (first + 32 * KB > Nc);
     if (need_mask) {
-      const long long dd = (a.q_off - k_off) + (q0 + lr) - ((long long)kt * SF_BC + 4 * h);
-      const int tail = Nc - 1 - (kt * SF_BC + 4 * h);
+      const long long dd = (a.q_off - k_off) + (q0 + lr) - ((long long)first + 4 * h);
+      const int tail = Nc - 1 - (first + 4 * h);
       int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : 64;
       lim = lim < tail ? lim : tail;
       const long long dl = dd - a.window + 1;
@@ -384,7 +388,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       for (int r = 0; r < 16; r++) v = fmaxf(v, s[kb][r]);
     return s_units(max_both_halves(v), a.scale, a.c);
   };
-  bool begun = false;
+  bool begun = false, unset = true;                // unset: some row has no reference in this chunk yet (KG > 1)
   // A run that begins inside a chunk takes the chunk's references from its first tile like every other run (one more
   // K tile and its scores per run).
   if constexpr (!SPARSE)
@@ -395,7 +399,10 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0), lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
       f32x16 s[KB];
-      s_raise(m_st, cm, scores(smem + SF_TILE, lo, f_Nc, f_koff, s), 0.f);
+      float mx = scores(smem + SF_TILE, lo * SF_BC, f_Nc, f_koff, s);
+      if constexpr (KG > 1) mx = fmaxf(mx, scores(smem + SF_TILE + 32 * KB * S_ROWB, lo * SF_BC + 32 * KB, f_Nc, f_koff, s));
+      s_raise(m_st, cm, mx, 0.f);
+      if constexpr (KG > 1) unset = __builtin_amdgcn_ballot_w64(row < a.Nq && cm == BURST_NEG_INF) != 0;
     }
   for (int buf = 0; have; buf ^= 1) {
     const int kt = f_tile, Nc = f_Nc;
@@ -405,13 +412,24 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     __builtin_amdgcn_s_barrier();
     have = advance(1);
     if (have) fetch(buf ^ 1);
-    if (first && begun) settle();
+    if (first && begun) {
+      settle();
+      unset = true;
+    }
     begun = true;
     if (!mine) continue;                           // block flags hide the tile from this wavefront's rows
-    const char* kl = smem + buf * SF_TILE;
-    const char* vl = smem + (2 + buf) * SF_TILE;
+    const char* kl = smem + buf * SF_TILE + koff * S_ROWB;
+    const char* vl = smem + (2 + buf) * SF_TILE + koff * S_ROWB;
     f32x16 s[KB];
-    const float mx = scores(kl, kt, Nc, k_off, s);
+    float mx = scores(kl, kt * SF_BC + koff, Nc, k_off, s);
+    // A row's first reference in a chunk is its maximum in the whole tile: its probabilities then do not depend on the groups.
+    if (KG > 1 && unset) {
+      const int other = koff ^ (32 * KB);
+      f32x16 t[KB];
+      const float m2 = scores(smem + buf * SF_TILE + other * S_ROWB, kt * SF_BC + other, Nc, k_off, t);
+      mx = cm == BURST_NEG_INF ? fmaxf(mx, m2) : mx;
+      unset = __builtin_amdgcn_ballot_w64(row < a.Nq && fmaxf(mx, cm) == BURST_NEG_INF) != 0;
+    }
     if (__builtin_amdgcn_ballot_w64(mx > cm + S_LAZY) != 0) {   // a chunk's first reference, or raised (rare)
       const float alpha = s_raise(m_st, cm, mx, sum_both_halves(lsum));
       lsum *= alpha;
@@ -449,7 +467,36 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
-  const float l_all = sum_both_halves(lsum);
+  float l_all = sum_both_halves(lsum);
+  if constexpr (KG > 1) {                          // [row block][db][q4][lane] O^T, then [row block][m, l][row]
+    static_assert(KG == 2 && RW * (128 * S_D + 256) <= 4 * SF_TILE, "the other half's state fits the tiles");
+    f32x4* const so = reinterpret_cast<f32x4*>(smem) + rw * S_DB * 4 * 64 + lane;
+    float* const ml = reinterpret_cast<float*>(smem) + RW * S_D * 32 + rw * 64 + lr;
+    __builtin_amdgcn_s_barrier();                  // (all have read the last tile)
+    if (koff != 0) {
+#pragma unroll
+      for (int db = 0; db < S_DB; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) so[(db * 4 + q4) * 64] = f32x4{o[db][4 * q4], o[db][4 * q4 + 1], o[db][4 * q4 + 2], o[db][4 * q4 + 3]};
+      if (h == 0) { ml[0] = m_st; ml[32] = l_all; }
+    }
+    __syncthreads();
+    if (koff != 0) return;
+    const float m1 = ml[0], l1 = ml[32], both = fmaxf(m_st, m1), ref = both == BURST_NEG_INF ? 0.f : both;
+    // (in the units of the probabilities, and 1 where a half's reference is the larger one)
+    const float f0 = fast_exp2(S_PAD ? (m_st - ref) * kLog2e : product(m_st, kLog2e) - product(ref, kLog2e));
+    const float f1 = fast_exp2(S_PAD ? (m1 - ref) * kLog2e : product(m1, kLog2e) - product(ref, kLog2e));
+    m_st = both;
+    l_all = l_all * f0 + l1 * f1;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        const f32x4 v = so[(db * 4 + q4) * 64];
+#pragma unroll
+        for (int b = 0; b < 4; b++) o[db][4 * q4 + b] = o[db][4 * q4 + b] * f0 + v[b] * f1;
+      }
+  }
   if constexpr (S_PAD) {                           // rows with an infinity or NaN, by themselves (see burst_rows.h)
     unsigned most = larger_of(0, l_all);
 #pragma unroll
@@ -471,7 +518,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       }
       for (unsigned left = redo; left != 0;) {
         int rows[kRows];
-        const int n = next_rows(left, qb * SF_BR + wu * 32, rows);
+        const int n = next_rows(left, qb * SF_BR + rw * 32, rows);
         RowState st[kRows];
 #pragma unroll
         for (int r = 0; r < kRows; r++) st[r] = row_state(a.fresh, a.O_acc, a.m, a.l, (size_t)head * a.Nq + rows[r], d, lane);
@@ -552,16 +599,14 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
 // Builds whose dQ kernel can compute D.  (At d = 128 the host never asks for it, and the branch alone cost 3 % of walks of few
 // rows: 52 rows x 6656 keys, window 1074, 34.3 / 35.2 us.)
 constexpr bool S_SUMS = S_PAD || S_D == 64;
-constexpr int SQ_BC = 32;                         // keys per tile
-constexpr int SQ_TILE = SQ_BC * S_ROWB;
-
 // (d = 64 fits four wavefronts per SIMD; left alone, the compiler takes 136 registers with block flags, which leaves three:
 // 32 heads of 4096 x 4096 rows, 64-wide flags at density 0.5: 164 us instead of 147)
 // (NW: as in the forward kernel)
-template <bool SPARSE, int NW>
+template <bool SPARSE, int NW, int KG>
 __global__ void __launch_bounds__(64 * NW, S_D == 64 && !S_PAD ? 4 : 2)
 burst_bwd_dq_d64_kernel(BwdArgsLite a) {
-  constexpr int SQ_BR = 32 * NW;                  // query rows per workgroup
+  constexpr int RW = NW / KG, SQ_BR = 32 * RW;    // row blocks, query rows per workgroup
+  constexpr int SQ_BC = 32 * KG, SQ_TILE = SQ_BC * S_ROWB;   // keys per tile, 32 a wavefront
   __shared__ __attribute__((aligned(16))) char smem[4 * SQ_TILE];   // K[2], V[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
@@ -570,12 +615,13 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   if (!locate_block(blockIdx.x, a.H, a.blocks_per_head * a.splits, head, qb, a.order)) return;
   if (a.splits > 1) { split = qb % a.splits; qb /= a.splits; }
   if (a.causal) qb = a.blocks_per_head - 1 - qb;   // later blocks see more keys: the long ones start first
-  const int q0 = qb * SQ_BR + w * 32;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int rw = KG == 1 ? wu : wu % RW, koff = KG == 1 ? 0 : wu / RW * 32;   // row block; first key of the share of a tile
+  const int q0 = qb * SQ_BR + (KG == 1 ? w : w % RW) * 32;
   const int row = q0 + lr;
   const bool ok = row < a.Nq;
   const size_t srow = (size_t)head * a.Nq + (ok ? row : 0);
   const int kvhead = head / a.group;
-  const int wu = __builtin_amdgcn_readfirstlane(w);
   const unsigned lds0 = lds_addr(smem);
 
   // The chunks' visible tiles (or list entries) form one sequence, as in the forward kernel.
@@ -671,7 +717,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
 #pragma unroll
       for (int ks = 0; ks < off; ks++) x[ks] = add_in_order(x[ks], x[ks + off]);
     Dv = sum_both_halves(x[0]);
-    if (ok && h == 0) const_cast<float*>(a.D)[srow] = Dv;   // (the fall-back below reads it again)
+    if (ok && h == 0 && koff == 0) const_cast<float*>(a.D)[srow] = Dv;   // (the fall-back below reads it again)
   } else if (ok) {
     Dv = a.D[srow];
   }
@@ -684,7 +730,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   for (int db = 0; db < S_DB; db++)
 #pragma unroll
     for (int r = 0; r < 16; r++) dq[db][r] = 0.f;
-  if (a.acc_dq && a.splits == 1 && ok) {
+  if (a.acc_dq && a.splits == 1 && ok && koff == 0) {
     const float* const orow = (const float*)a.dQ + srow * d;
 #pragma unroll
     for (int db = 0; db < S_DB; db++)
@@ -727,9 +773,10 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
       have = advance(a.splits);
       if (have) fetch(buf ^ 1);
       if (!mine) continue;                         // block flags hide the tile from this wavefront's rows
-      const char* kl = smem + buf * SQ_TILE;
-      const char* vl = smem + (2 + buf) * SQ_TILE;
-      // S^T = K Q^T, dP^T = V dO^T: register r = key kt*32 + 8*(r/4) + 4h + r%4
+      const char* kl = smem + buf * SQ_TILE + koff * S_ROWB;
+      const char* vl = smem + (2 + buf) * SQ_TILE + koff * S_ROWB;
+      const int first = kt * SQ_BC + koff;
+      // S^T = K Q^T, dP^T = V dO^T: register r = key first + 8*(r/4) + 4h + r%4
       f32x16 s, dp;
 #pragma unroll
       for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
@@ -738,13 +785,12 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
         s = mfma32(lds_read_b128(kl, kaddr[ks]), qf[ks], s);
         dp = mfma32(lds_read_b128(vl, kaddr[ks]), gf[ks], dp);
       }
-      const long long tile_first_k = k_off + (long long)kt * SQ_BC;
-      const bool need_mask = (a.causal && tile_first_k + SQ_BC - 1 > wave_first_q) ||
-                             (a.window > 0 && tile_first_k < wave_first_q + 31 - a.window + 1) ||
-                             ((kt + 1) * SQ_BC > Nc);
+      const long long tile_first_k = k_off + first;
+      const bool need_mask = ((a.causal != 0) & (tile_first_k + 31 > wave_first_q)) |
+                             ((a.window > 0) & (tile_first_k < wave_first_q + 31 - a.window + 1)) | (first + 32 > Nc);
       if (need_mask) {
-        const long long dd = (a.q_off - k_off) + (q0 + lr) - ((long long)kt * SQ_BC + 4 * h);
-        const int tail = Nc - 1 - (kt * SQ_BC + 4 * h);
+        const long long dd = (a.q_off - k_off) + (q0 + lr) - ((long long)first + 4 * h);
+        const int tail = Nc - 1 - (first + 4 * h);
         int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : 64;
         lim = lim < tail ? lim : tail;
         const long long dl = dd - a.window + 1;
@@ -773,6 +819,27 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
   }
+  if constexpr (KG > 1) {                          // the halves' sums meet, as in the forward kernel
+    static_assert(KG == 2 && RW * 128 * S_D <= 4 * SQ_TILE, "the other half's sums fit the tiles");
+    f32x4* const so = reinterpret_cast<f32x4*>(smem) + rw * S_DB * 4 * 64 + lane;
+    __builtin_amdgcn_s_barrier();                  // (all have read the last tile)
+    if (koff != 0) {
+#pragma unroll
+      for (int db = 0; db < S_DB; db++)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; q4++) so[(db * 4 + q4) * 64] = f32x4{dq[db][4 * q4], dq[db][4 * q4 + 1], dq[db][4 * q4 + 2], dq[db][4 * q4 + 3]};
+    }
+    __syncthreads();
+    if (koff != 0) return;
+#pragma unroll
+    for (int db = 0; db < S_DB; db++)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        const f32x4 v = so[(db * 4 + q4) * 64];
+#pragma unroll
+        for (int b = 0; b < 4; b++) dq[db][4 * q4 + b] += v[b];
+      }
+  }
   if constexpr (S_PAD) {                           // rows with an infinity or NaN, by themselves (see burst_rows.h)
     unsigned most = 0;
 #pragma unroll
@@ -783,7 +850,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
     const unsigned redo = (unsigned)bal | (unsigned)(bal >> 32);
     for (unsigned left = redo; left != 0;) {
       int rows[kRows];
-      const int n = next_rows(left, qb * SQ_BR + wu * 32, rows);
+      const int n = next_rows(left, qb * SQ_BR + rw * 32, rows);
       float g[kRows][2];
       rows_dq<bf16, true, SQ_BC>(g, args_again<BwdArgsLite>(), head, rows, lane, tiles_of, split, a.splits);
 #pragma unroll
@@ -833,16 +900,18 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
 #define BURST_SMALL_DKV_WAVES 4
 #endif
 constexpr int SK_WAVES = BURST_SMALL_DKV_WAVES;
-constexpr int SK_BC = 32 * SK_WAVES;              // keys per workgroup
-constexpr int SK_BR = 32;                         // query rows per tile
-constexpr int SK_TILE = SK_BR * S_ROWB;
-constexpr int SK_STAT = 4 * SK_TILE;              // per buffer: 32 x (-lse, see s_units), 32 x D
 
 // PARTS: the walks are cut (RowParts), in an instantiation of its own: as a branch of the ordinary one it cost short walks 1 to 2 %.
-template <bool SPARSE, bool PARTS>
+// QG = 2: the wavefronts are two key blocks times two halves of every tile's rows; the halves' sums meet in LDS at the end, for the
+// reasons of KG in the forward kernel (rule: dkv_parts; 32 heads of 777 causal rows, d = 96: 32 + 10 merging parts -> 34 us).
+constexpr int sk_keys(int QG) { return 32 * SK_WAVES / QG; }   // keys per workgroup
+constexpr int sk_rows(int QG) { return 32 * QG; }              // query rows per tile
+template <bool SPARSE, bool PARTS, int QG>
 __global__ void __launch_bounds__(64 * SK_WAVES, SK_WAVES == 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
 burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
-  __shared__ __attribute__((aligned(16))) char smem[4 * SK_TILE + 2 * 64 * 4];   // Q[2], dO[2], statistics[2]
+  constexpr int KW = SK_WAVES / QG, SK_BC = sk_keys(QG), SK_BR = sk_rows(QG), SK_TILE = SK_BR * S_ROWB;
+  constexpr int SK_STAT = 4 * SK_TILE;            // per buffer and row: -lse (see s_units), then D
+  __shared__ __attribute__((aligned(16))) char smem[SK_STAT + 2 * 2 * SK_BR * 4];   // Q[2], dO[2], statistics[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
@@ -858,7 +927,9 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   }
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
-  const int key_wg = kblk * SK_BC, key0 = key_wg + w * 32;
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int kw = QG == 1 ? wu : wu % KW, qoff = QG == 1 ? 0 : wu / KW * 32;   // key block; first row of the share of a tile
+  const int key_wg = kblk * SK_BC, key0 = key_wg + (QG == 1 ? w : w % KW) * 32;
   const bf16* Kh = (const bf16*)C.K + C.kv_base(kvhead, a.lay.kv_heads);
   const bf16* Vh = (const bf16*)C.V + C.kv_base(kvhead, a.lay.kv_heads);
   const unsigned qpitch = (unsigned)a.lay.qs_r * 2u;             // bytes between query rows
@@ -880,7 +951,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       const uint8_t* mrow = C.bmask + (size_t)(kvhead * a.group + g) * C.bhstride + (size_t)((t * SK_BR) / a.bsize) * C.bpitch;
       int bits = 0;
 #pragma unroll
-      for (int ww = 0; ww < SK_WAVES; ww++) {
+      for (int ww = 0; ww < KW; ww++) {
         const int k0 = key_wg + ww * 32;
         if (k0 < Nc && mrow[k0 / a.bsize] != 0) bits |= 1 << ww;
       }
@@ -922,7 +993,6 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) qaddr[ks] = s_off(lr, 2 * ks + h);
     s_taddr(lane, taddr);
-    const int wu = __builtin_amdgcn_readfirstlane(w);
     const unsigned lds0 = lds_addr(smem);
     constexpr int NL = SK_BR / S_RPL / SK_WAVES;  // wave-wide loads per wavefront and tile
     static_assert(NL >= 1 && NL * SK_WAVES * S_RPL == SK_BR, "a tile's rows must divide evenly among the wavefronts");
@@ -930,8 +1000,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 #pragma unroll
     for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, qpitch, d);
     float* const stat = reinterpret_cast<float*>(smem + SK_STAT);
-    // walk position n -> (query head, tile); every wavefront DMAs its 8 rows of Q and dO.  The
-    // first wavefront also fetches the 32 rows' statistics with plain loads issued BEFORE the
+    // walk position n -> (query head, tile); every wavefront DMAs its rows of Q and dO.  The
+    // first wavefronts also fetch the rows' statistics with plain loads issued BEFORE the
     // DMA (the wait the compiler places before their first use then does not cover the DMA) and
     // writes them to LDS at the end of the step (stat_commit).
     float stat_x = 0.f;
@@ -939,9 +1009,9 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       int g, t;
       locate(n, g, t);
       const size_t hrow = (size_t)(kvhead * a.group + g) * a.Nq;
-      if (tid < 64) {
-        const int r = t * SK_BR + (tid & 31);
-        if (tid < 32) stat_x = r < a.Nq ? a.lse[hrow + r] : BURST_NEG_INF;
+      if (tid < 2 * SK_BR) {
+        const int r = t * SK_BR + (tid & (SK_BR - 1));
+        if (tid < SK_BR) stat_x = r < a.Nq ? a.lse[hrow + r] : BURST_NEG_INF;
         else stat_x = r < a.Nq ? a.D[hrow + r] : 0.f;
       }
       const size_t hbase = a.lay.q_base(kvhead * a.group + g);
@@ -954,8 +1024,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       }
     };
     auto stat_commit = [&](int buf) __attribute__((always_inline)) {
-      if (tid < 32) stat[buf * 64 + tid] = (stat_x == BURST_NEG_INF) ? BURST_NEG_INF : S_PAD ? -stat_x : -stat_x * kLog2e;   // -inf: P = 0
-      else if (tid < 64) stat[buf * 64 + tid] = stat_x;
+      if (tid < SK_BR) stat[buf * 2 * SK_BR + tid] = (stat_x == BURST_NEG_INF) ? BURST_NEG_INF : S_PAD ? -stat_x : -stat_x * kLog2e;   // -inf: P = 0
+      else if (tid < 2 * SK_BR) stat[buf * 2 * SK_BR + tid] = stat_x;
     };
     const long long wave_first_k = k_off + key0, wave_last_k = wave_first_k + 31;
     const long long kpos = wave_first_k + lr;
@@ -967,12 +1037,13 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       __builtin_amdgcn_s_barrier();
       if (n + 1 < nwalk) fetch(n + 1, (n + 1) & 1);
       const int buf = n & 1;
-      const char* ql = smem + buf * SK_TILE;
-      const char* gl = smem + (2 + buf) * SK_TILE;
+      const char* ql = smem + buf * SK_TILE + qoff * S_ROWB;
+      const char* gl = smem + (2 + buf) * SK_TILE + qoff * S_ROWB;
       int g_unused, t;
       const bool mine = ((locate(n, g_unused, t) >> wu) & 1) != 0;
       if (mine) {                                  // (else: block flags hide this wavefront's keys from the tile)
-        // S = Q K^T, dP = dO V^T: lane = key lr, register r = row t*32 + 8*(r/4) + 4h + r%4
+        // S = Q K^T, dP = dO V^T: lane = key lr, register r = row first_row + 8*(r/4) + 4h + r%4
+        const int first_row = t * SK_BR + qoff;
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
@@ -993,10 +1064,10 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
             dp = mfma32(lds_read_b128(gl, qaddr[ks]), vf[ks], dp);
           }
         }
-        const long long tile_first_q = a.q_off + (long long)t * SK_BR;
-        const bool need_mask = (a.causal && wave_last_k > tile_first_q) ||
-                               (a.window > 0 && tile_first_q + SK_BR - 1 >= wave_first_k + a.window) ||
-                               (S_PAD && (t + 1) * SK_BR > a.Nq);   // (rows of zeros, whose product with an infinite key is NaN)
+        const long long tile_first_q = a.q_off + first_row;
+        const bool need_mask = ((a.causal != 0) & (wave_last_k > tile_first_q)) |
+                               ((a.window > 0) & (tile_first_q + 31 >= wave_first_k + a.window)) |
+                               (S_PAD & (first_row + 32 > a.Nq));   // (rows of zeros, whose product with an infinite key is NaN)
         if (need_mask) {
           // visible iff key position <= row position (constant part >= lim) and row position <
           // key position + window (constant part <= lim2)
@@ -1004,7 +1075,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
           const int lim = a.causal ? (int)(dd < -1 ? -1 : (dd > 64 ? 64 : dd)) : -1;
           const long long d2 = dd + a.window - 1;
           int lim2 = a.window > 0 ? (int)(d2 < -1 ? -1 : (d2 > 64 ? 64 : d2)) : 64;
-          if (S_PAD) lim2 = min(lim2, a.Nq - 1 - (t * SK_BR + 4 * h));
+          if (S_PAD) lim2 = min(lim2, a.Nq - 1 - (first_row + 4 * h));
 #pragma unroll
           for (int r = 0; r < 16; r++) {
             const int cpart = 8 * (r >> 2) + (r & 3);
@@ -1029,8 +1100,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
         bf16x8 pf[2][S_TERMS], dsf[2][S_TERMS];      // per 16-row group: A operands of dV, dK
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) {
-          const f32x4 nl = *reinterpret_cast<const f32x4*>(stat + buf * 64 + 8 * q4 + 4 * h);
-          const f32x4 dr = *reinterpret_cast<const f32x4*>(stat + buf * 64 + 32 + 8 * q4 + 4 * h);
+          const f32x4 nl = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + qoff + 8 * q4 + 4 * h);
+          const f32x4 dr = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + SK_BR + qoff + 8 * q4 + 4 * h);
 #pragma unroll
           for (int j = 0; j < 4; j += 2) {
             const int r = 4 * q4 + j;
@@ -1059,7 +1130,33 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       if (n + 1 < nwalk) stat_commit((n + 1) & 1);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
+    if constexpr (QG > 1) {                        // [key block][dK, dV][db][q4][lane]
+      static_assert(QG == 2 && KW * 256 * S_D <= SK_STAT, "the other half's sums fit the tiles");
+      f32x4* const so = reinterpret_cast<f32x4*>(smem) + kw * 2 * S_DB * 4 * 64 + lane;
+      __builtin_amdgcn_s_barrier();                // (all have read the last tile)
+      if (qoff != 0) {
+#pragma unroll
+        for (int db = 0; db < S_DB; db++)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; q4++) {
+            so[(db * 4 + q4) * 64] = f32x4{dk[db][4 * q4], dk[db][4 * q4 + 1], dk[db][4 * q4 + 2], dk[db][4 * q4 + 3]};
+            so[((S_DB + db) * 4 + q4) * 64] = f32x4{dv[db][4 * q4], dv[db][4 * q4 + 1], dv[db][4 * q4 + 2], dv[db][4 * q4 + 3]};
+          }
+      }
+      __syncthreads();
+      if (qoff == 0) {
+#pragma unroll
+        for (int db = 0; db < S_DB; db++)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; q4++) {
+            const f32x4 x = so[(db * 4 + q4) * 64], y = so[((S_DB + db) * 4 + q4) * 64];
+#pragma unroll
+            for (int b = 0; b < 4; b++) { dk[db][4 * q4 + b] += x[b]; dv[db][4 * q4 + b] += y[b]; }
+          }
+      }
+    }
   }
+  if (QG > 1 && qoff != 0) return;
   if (PARTS && parts > 1) {                        // (infinities and NaN: merge_dkv_kernel sees to them)
     store_dkv<S_DB, S_PAD>(dk, dv, a.parts.at(part, false, C, kvhead, d), a.parts.at(part, true, C, kvhead, d),
                            C.span_keys, d, key0 - C.span_lo, lr, h, a.scale, 0, 0);
@@ -1072,7 +1169,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 #pragma unroll
       for (int r = 0; r < 16; r++) most = larger_of(larger_of(most, dk[db][r]), dv[db][r]);
     if (__builtin_amdgcn_ballot_w64(most >= kInfBits) != 0) {
-      const int base = key_wg + __builtin_amdgcn_readfirstlane(w) * 32;
+      const int base = key_wg + kw * 32;
       for (unsigned left = first_bits(Nc - base); left != 0;) {
         int keys[kRows];
         const int n = next_rows(left, base, keys);
@@ -1147,13 +1244,14 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.causal = p.causal; a.c = p.scale * kLog2e; a.scale = p.scale;
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
-  const int nw = row_waves(p, ch, n, true);
-  a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
-  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, 32 * nw), 2);
+  const int nw = row_waves(p, ch, n, true), kg = io.groups == 2 && ch[0].bmask == nullptr ? 2 : 1, br = 32 * nw / kg;
+  a.blocks_per_head = (p.Nq + br - 1) / br;
+  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, br), kg == 2 && S_ROWB == 128 ? 4 : 2);
   int longest = 0;
   for (int i = 0; i < n; i++) { a.ch[i] = ch[i]; if (ch[i].Nc > longest) longest = ch[i].Nc; }
   static DeviceOnce done, done2;
-  return launch_plain(burst_fwd_d64_kernel<false, 4>, nw == 2 ? burst_fwd_d64_kernel<true, 2> : burst_fwd_d64_kernel<true, 4>, nw == 2 ? done2 : done, a,
+  return launch_plain(kg == 2 ? burst_fwd_d64_kernel<false, 4, 2> : burst_fwd_d64_kernel<false, 4, 1>,
+                      nw == 2 ? burst_fwd_d64_kernel<true, 2, 1> : burst_fwd_d64_kernel<true, 4, 1>, nw == 2 ? done2 : done, a,
                       grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + sf_keys(nw) - 1) / sf_keys(nw), 64 * nw, stream);
 }
 
@@ -1172,32 +1270,35 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   if (io.O != nullptr && !S_SUMS) return BURST_ERR_SHAPE;
-  const int nw = row_waves(p, ch, n, false);
-  a.blocks_per_head = (p.Nq + 32 * nw - 1) / (32 * nw);
-  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, 32 * nw), 2);
+  const int nw = row_waves(p, ch, n, false), kg = io.groups == 2 && ch[0].bmask == nullptr ? 2 : 1, br = 32 * nw / kg;
+  a.blocks_per_head = (p.Nq + br - 1) / br;
+  a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, br), kg == 2 && S_ROWB == 128 ? 4 : 2);
   int longest = 0;
   for (int i = 0; i < n; i++) if (ch[i].Nc > longest) longest = ch[i].Nc;
   static DeviceOnce done, done2;
-  return launch_plain(burst_bwd_dq_d64_kernel<false, 4>, nw == 2 ? burst_bwd_dq_d64_kernel<true, 2> : burst_bwd_dq_d64_kernel<true, 4>, nw == 2 ? done2 : done, a,
-                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + SQ_BC - 1) / SQ_BC, 64 * nw, stream);
+  return launch_plain(kg == 2 ? burst_bwd_dq_d64_kernel<false, 4, 2> : burst_bwd_dq_d64_kernel<false, 4, 1>,
+                      nw == 2 ? burst_bwd_dq_d64_kernel<true, 2, 1> : burst_bwd_dq_d64_kernel<true, 4, 1>, nw == 2 ? done2 : done, a,
+                      grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + 31) / 32, 64 * nw, stream);
 }
 
 // Keys of a dK/dV workgroup, for the host's rule of splitting (two workgroups share a CU in every build).
-int dkv_keys() { return SK_BC; }
+int dkv_keys() { return sk_keys(1); }
 
 int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
   set_row_parts(a, io);
-  const long long nb = chunk_grid(a.ch, n, a.H, SK_BC, a.per, a.parts.splits);
+  constexpr int G = SK_WAVES == 4 ? 2 : 1;
+  const int groups = io.parts != nullptr && io.parts->groups == 2 && a.parts.splits == 1 && ch[0].bmask == nullptr ? G : 1, bc = sk_keys(groups);
+  const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, a.parts.splits);
   if (a.parts.splits > 1 && ch[0].bmask != nullptr) return BURST_ERR_SHAPE;
-  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + SK_BC - 1) / SK_BC, unequal_keys(p, ch[0], SK_BC, SK_BR), 2) : 0;
+  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + bc - 1) / bc, unequal_keys(p, ch[0], bc, 32), 2) : 0;
   static DeviceOnce done;
-  const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true> : burst_bwd_dkv_d64_kernel<false, false>,
-                              burst_bwd_dkv_d64_kernel<true, false>, done, a, nb,
-                              (long long)p.group * ((p.Nq + SK_BR - 1) / SK_BR), 64 * SK_WAVES, stream);
-  return st != BURST_OK || a.parts.splits == 1 ? st : launch_merge_dkv<S_D, SK_BC, SK_BR, S_PAD>(a, stream);
+  const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true, 1> : groups > 1 ? burst_bwd_dkv_d64_kernel<false, false, G> : burst_bwd_dkv_d64_kernel<false, false, 1>,
+                              burst_bwd_dkv_d64_kernel<true, false, 1>, done, a, nb,
+                              (long long)p.group * ((p.Nq + 31) / 32), 64 * SK_WAVES, stream);
+  return st != BURST_OK || a.parts.splits == 1 ? st : launch_merge_dkv<S_D, sk_keys(1), sk_rows(1), S_PAD>(a, stream);
 }
 
 }  // namespace BURST_SMALL_NS
