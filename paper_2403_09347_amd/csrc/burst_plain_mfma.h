@@ -140,12 +140,18 @@ __device__ __forceinline__ float s_raise(float& m_st, float& cm, float mx, float
   return S_PAD ? raise_reference_natural(m_st, cm, mx, l) : raise_reference(m_st, cm, mx, l);
 }
 __device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, float y) {
+  unsigned c1 = 0x0000bf80u, c2 = 0xbf800000u;     // (-1, 0) and (0, -1), in registers: as an inline constant -1.0 has no packed meaning to rely on
+  asm("" : "+s"(c1), "+s"(c2));
+  const bf16x2 first = __builtin_bit_cast(bf16x2, c1), second = __builtin_bit_cast(bf16x2, c2);
 #pragma unroll
   for (int i = 0; i < S_TERMS; i++) {
     bf16x2 pk;
     pk[0] = (bf16)x; pk[1] = (bf16)y;
     out[i][t] = pk[0]; out[i][t + 1] = pk[1];
-    x -= (float)pk[0]; y -= (float)pk[1];
+    if (i + 1 < S_TERMS) {                         // x - pk[0], y - pk[1]: one instruction each
+      x = __builtin_amdgcn_fdot2_f32_bf16(pk, first, x, false);
+      y = __builtin_amdgcn_fdot2_f32_bf16(pk, second, y, false);
+    }
   }
 }
 // acc += a x (the sum of b's terms) and acc += (the sum of a's terms) x b, the smallest terms first
