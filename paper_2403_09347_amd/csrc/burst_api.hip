@@ -29,6 +29,7 @@ int launch_bwd_dkv_generic(const KParams&, int, const BwdIo&, const Chunk*, int,
   int launch_bwd_dq(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);         \
   int launch_bwd_dkv(const KParams&, const BwdIo&, const Chunk*, int, hipStream_t);        \
   int dkv_keys();                                                                          \
+  int dkv_rows();                                                                          \
   }
 int launch_merge_splits(const KParams&, const FwdIo&, hipStream_t);
 int launch_fill_unseen(const KParams&, int, void*, float*, hipStream_t);
@@ -194,9 +195,9 @@ struct PlainFamily {
   decltype(&burst::d64::launch_fwd) fwd;
   decltype(&burst::d64::launch_bwd_dq) bwd_dq;
   decltype(&burst::d64::launch_bwd_dkv) bwd_dkv;
-  decltype(&burst::d64::dkv_keys) dkv_keys;
+  decltype(&burst::d64::dkv_keys) dkv_keys, dkv_rows;
 };
-#define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv, burst::ns::dkv_keys}
+#define BURST_PLAIN(ns) {burst::ns::launch_fwd, burst::ns::launch_bwd_dq, burst::ns::launch_bwd_dkv, burst::ns::dkv_keys, burst::ns::dkv_rows}
 const PlainFamily kD64 = BURST_PLAIN(d64), kD128p = BURST_PLAIN(d128p), kD32x = BURST_PLAIN(d32x), kD64x = BURST_PLAIN(d64x), kD96x = BURST_PLAIN(d96x),
                   kD128x = BURST_PLAIN(d128x);
 #undef BURST_PLAIN
@@ -244,8 +245,8 @@ bool use_plain128(const burst_params* p, const KParams& k, bool whole = false) {
 // The hand-scheduled dK/dV kernel walks the query tiles of all heads of a group as one list of at most 8192
 // tiles; longer groups take the generic kernel.  Groups whose slice is no multiple of its 64-row tiles go to the
 // plain kernel padded to 128 columns, whose P and dS have 24 bits as in the generic kernel that had these calls (see
-// s_terms).  (Call with gradients, 32 heads over 8, 3001 causal rows: 1054 us so, 560 us with the hand-scheduled
-// kernel and its 8-bit P and dS (a walk's dV then 1.7e-3 off 64 bits instead of 7.6e-5), 10.3 ms with the generic one.)
+// s_terms).  (Call with gradients, 32 heads over 8, 3001 causal rows: 518 us, 1054 with
+// two wavefronts a workgroup, 10.3 ms with the generic kernel; with 8-bit P and dS a walk's dV is 1.7e-3 off 64 bits instead of 7.6e-5.)
 bool dkv_mfma_ok(const burst_params* p, const KParams& k) {
   if (k.group > 1) return p->Nq % 64 == 0 && (long long)k.group * (p->Nq / 64) <= 8192 && k.group <= 256;
   return p->block_mask == nullptr || p->Nq <= kMaxMaskedRows;
@@ -537,9 +538,10 @@ burst::RowPlan cut_walks(const std::vector<WalkChunk>& w) {
   const KParams& k = w[0].k;
   const bool generic = f.plain == nullptr && !f.hand;
   if (generic && !generic_splittable(w)) return kWhole;
-  const int bc = generic ? 32 : f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.hand ? 64 : 32;
-  const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr ? 512 : 256;   // (generic: the CUs)
-  if ((long long)k.group * ((k.Nq + br - 1) / br) < (generic ? 8 : f.hand ? 32 : 24)) return kWhole;   // (no walk is long enough, see below)
+  const int bc = generic ? 32 : f.plain != nullptr ? f.plain->dkv_keys() : 128, br = f.hand ? 64 : generic ? 32 : f.plain->dkv_rows();
+  const int unit = f.plain != nullptr ? br / 32 : 1;   // (the plain kernels' thresholds count tiles of 32 rows)
+  const long long heads = (long long)k.B * k.H / k.group, slots = f.plain != nullptr && br == 32 ? 512 : 256;   // (generic: the CUs)
+  if ((long long)k.group * ((k.Nq + br - 1) / br) * unit < (generic ? 8 : f.hand ? 32 : 24)) return kWhole;   // (no walk is long enough, see below)
   auto walk_of = [&](const WalkChunk& x, int key0) {   // tiles of a block of keys, of all heads of the group
     const burst::RowRange r = burst::row_range(k.Nq, k.causal, k.window, k.q_off, x.c.k_off, x.c.Nc, key0, bc, br);
     return (long long)(r.hi - r.lo) * k.group;
@@ -578,9 +580,9 @@ burst::RowPlan cut_walks(const std::vector<WalkChunk>& w) {
     if (parts < 2 && blocks <= 256 && most >= 16 && 10 * most * slots >= 18 * total) parts = 2;
     return parts < 2 || (k.d <= 32 ? most - most / parts < 16 : k.d <= 64 && most < 12) ? kWhole : cut(parts, (int)((most + parts - 1) / parts));
   }
-  if (most < 24 || 10 * most * slots < 19 * total) return kWhole;
+  if (most * unit < 24 || 10 * most * slots < 19 * total) return kWhole;
   const long long ratio = (4 * most * slots + 3 * total - 1) / (4 * total);   // the ratio rounded up from a quarter on
-  const long long splits = std::min({16LL, ratio, most / (f.plain != nullptr ? 8 : 16)});
+  const long long splits = std::min({16LL, ratio, most * unit / (f.plain != nullptr ? 8 : 16)});
   if (splits < 2) return kWhole;
   // What the longest walk has above a CU's share has to be worth the merging launch: 16 tiles at d = 64, 6 on the padded kernels, whose
   // tiles take three times as long.  Backward pass, whole / cut, us: d = 64, 32 x 1226 causal, 13 tiles above, 73.2 / 78.3, 2 x 3840 x
@@ -588,14 +590,14 @@ burst::RowPlan cut_walks(const std::vector<WalkChunk>& w) {
   // x 2099, window 71, 2, 91 / 100; d = 120, 8 x 2209, window 674, 11, 245 / 204.  Hand-scheduled (one workgroup a CU): the share and a
   // part behind it have to be shorter than the longest walk (1 x 4736 x 18944, 148 equal blocks, in 2: 192 / 223; 4 x 3547, 112, in 3 143 / 139).
   const long long share = total / 256;
-  if (f.hand ? share + (most + splits - 1) / splits >= most : most - share < (f.plain == &kD64 ? 16 : 6)) return kWhole;
-  return cut(splits, 8);
+  if (f.hand ? share + (most + splits - 1) / splits >= most : (most - share) * unit < (f.plain == &kD64 ? 16 : 6)) return kWhole;
+  return cut(splits, 8 / unit);
 }
 burst::RowPlan dkv_parts(const std::vector<WalkChunk>& w, bool half) {
   burst::RowPlan plan = cut_walks(w);
   if (!half || w.size() != 1 || w[0].p.block_mask != nullptr || w[0].k.Nq == 0) return plan;
   const Kernels f = dkv_kernels(&w[0].p, w[0].k);
-  if (f.plain == nullptr || f.plain->dkv_keys() != 128) return plan;
+  if (f.plain == nullptr || f.plain->dkv_keys() != 128 || f.plain->dkv_rows() != 32) return plan;
   const KParams& k = w[0].k;
   const long long blocks = (long long)k.B * k.H / k.group * ((w[0].c.Nc + 127) / 128), walk = (long long)k.group * ((k.Nq + 31) / 32);
   const bool narrow = f.plain == &kD64;

@@ -3,6 +3,6 @@
 #define BURST_SMALL_D 128
 #define BURST_SMALL_NS d128x
 #define BURST_SMALL_PAD
-// (two wavefronts per dK/dV workgroup, as in the d = 128 build: four would spill)
-#define BURST_SMALL_DKV_WAVES 2
+// (eight wavefronts per dK/dV workgroup, K and V in LDS: see burst_bwd_dkv_d64_kernel)
+#define BURST_SMALL_DKV_WAVES 8
 #include "burst_plain_mfma.h"

@@ -7,7 +7,8 @@
 //   burst_d128_plain.hip  d = 128, namespace burst::d128p, all three kernels, the dK/dV one with
 //                         two wavefronts (64 keys) per workgroup (BURST_SMALL_DKV_WAVES = 2)
 //   burst_d{32,64,96,128}_pad.hip   every other multiple of 8 below 128, padded to the next of these
-//                         widths (BURST_SMALL_PAD), namespaces burst::d32x .. d128x; P and dS with 24 bits
+//                         widths (BURST_SMALL_PAD), namespaces burst::d32x .. d128x; P and dS with 24 bits; at 128 the dK/dV kernel
+//                         with eight wavefronts (BURST_SMALL_DKV_WAVES = 8)
 //
 // Same mathematics, operand orientations and register layouts as the hand-scheduled d = 128
 // kernels (S^T = K Q^T with one query row per lane for the forward and dQ side, S = Q K^T with one
@@ -139,6 +140,9 @@ __device__ __forceinline__ float s_exp(float s, float scale, float c, float nref
 __device__ __forceinline__ float s_raise(float& m_st, float& cm, float mx, float l) {
   return S_PAD ? raise_reference_natural(m_st, cm, mx, l) : raise_reference(m_st, cm, mx, l);
 }
+// DOT: remainders by dot products instead of a shift or mask and a subtraction (all but the dense 128-wide forward, 86 / 89 us at 32 x 2048
+// causal rows: its vector unit is not what bounds it).
+template <bool DOT = true>
 __device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, float y) {
   unsigned c1 = 0x0000bf80u, c2 = 0xbf800000u;     // (-1, 0) and (0, -1), in registers: as an inline constant -1.0 has no packed meaning to rely on
   asm("" : "+s"(c1), "+s"(c2));
@@ -148,7 +152,9 @@ __device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, 
     bf16x2 pk;
     pk[0] = (bf16)x; pk[1] = (bf16)y;
     out[i][t] = pk[0]; out[i][t + 1] = pk[1];
-    if (i + 1 < S_TERMS) {                         // x - pk[0], y - pk[1]: one instruction each
+    if (!DOT) {
+      x -= (float)pk[0]; y -= (float)pk[1];
+    } else if (i + 1 < S_TERMS) {                  // x - pk[0], y - pk[1]: one instruction each
       x = __builtin_amdgcn_fdot2_f32_bf16(pk, first, x, false);
       y = __builtin_amdgcn_fdot2_f32_bf16(pk, second, y, false);
     }
@@ -452,7 +458,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
       for (int t = 0; t < 8; t += 2) {
         const int kb = kg >> 1, r = 8 * (kg & 1) + t;
         const float p0 = s_exp(s[kb][r], a.scale, a.c, nref), p1 = s_exp(s[kb][r + 1], a.scale, a.c, nref);
-        s_terms(pf[kg], t, p0, p1);
+        s_terms<SPARSE || S_D <= 96>(pf[kg], t, p0, p1);
         if constexpr (S_TERMS == 1) {                // sums what the MFMA multiplies
           bf16x2 pk;
           pk[0] = pf[kg][0][t]; pk[1] = pf[kg][0][t + 1];
@@ -478,7 +484,7 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     static_assert(KG == 2 && RW * (128 * S_D + 256) <= 4 * SF_TILE, "the other half's state fits the tiles");
     f32x4* const so = reinterpret_cast<f32x4*>(smem) + rw * S_DB * 4 * 64 + lane;
     float* const ml = reinterpret_cast<float*>(smem) + RW * S_D * 32 + rw * 64 + lr;
-    __builtin_amdgcn_s_barrier();                  // (all have read the last tile)
+    __syncthreads();                               // (all have read the last tile; a barrier that the writes below do not cross)
     if (koff != 0) {
 #pragma unroll
       for (int db = 0; db < S_DB; db++)
@@ -828,7 +834,7 @@ burst_bwd_dq_d64_kernel(BwdArgsLite a) {
   if constexpr (KG > 1) {                          // the halves' sums meet, as in the forward kernel
     static_assert(KG == 2 && RW * 128 * S_D <= 4 * SQ_TILE, "the other half's sums fit the tiles");
     f32x4* const so = reinterpret_cast<f32x4*>(smem) + rw * S_DB * 4 * 64 + lane;
-    __builtin_amdgcn_s_barrier();                  // (all have read the last tile)
+    __syncthreads();                               // (all have read the last tile; a barrier that the writes below do not cross)
     if (koff != 0) {
 #pragma unroll
       for (int db = 0; db < S_DB; db++)
@@ -910,14 +916,22 @@ constexpr int SK_WAVES = BURST_SMALL_DKV_WAVES;
 // PARTS: the walks are cut (RowParts), in an instantiation of its own: as a branch of the ordinary one it cost short walks 1 to 2 %.
 // QG = 2: the wavefronts are two key blocks times two halves of every tile's rows; the halves' sums meet in LDS at the end, for the
 // reasons of KG in the forward kernel (rule: dkv_parts; 32 heads of 777 causal rows, d = 96: 32 + 10 merging parts -> 34 us).
-constexpr int sk_keys(int QG) { return 32 * SK_WAVES / QG; }   // keys per workgroup
+// NW wavefronts.  Eight (the 128-wide padded build): two per SIMD, a CU's only workgroup, QG = 2.  K and V of its 128 keys lie in
+// LDS before the tiles: in registers they and the three terms of P and dS left room for one wavefront per SIMD (382 registers).
+// 32 over 8 heads x 3001 causal rows, dK/dV with merging: 422 us so, 363 with eight (five contractions' worth of terms at 0.85 PFLOP/s
+// executed); 8 x 2048, d = 120, 133 / 77.  Block flags 64 wide stay with two wavefronts of 64 keys, whose lists are exact (density 0.25, 32 over 8
+// x 1000 x 2000 60 / 71; 128 wide 125 / 119, 256 wide 74 / 58).
+constexpr int SK_GROUPS = SK_WAVES == 8 ? 2 : 1;  // the build's ordinary QG
+constexpr int sk_keys(int NW, int QG) { return 32 * NW / QG; }   // keys per workgroup
 constexpr int sk_rows(int QG) { return 32 * QG; }              // query rows per tile
-template <bool SPARSE, bool PARTS, int QG>
-__global__ void __launch_bounds__(64 * SK_WAVES, SK_WAVES == 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
+template <bool SPARSE, bool PARTS, int QG, int NW>
+__global__ void __launch_bounds__(64 * NW, NW >= 4 ? 2 : 1)   // (second figure: wavefronts per SIMD)
 burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
-  constexpr int KW = SK_WAVES / QG, SK_BC = sk_keys(QG), SK_BR = sk_rows(QG), SK_TILE = SK_BR * S_ROWB;
-  constexpr int SK_STAT = 4 * SK_TILE;            // per buffer and row: -lse (see s_units), then D
-  __shared__ __attribute__((aligned(16))) char smem[SK_STAT + 2 * 2 * SK_BR * 4];   // Q[2], dO[2], statistics[2]
+  constexpr bool S_KV_LDS = NW == 8;
+  constexpr int KW = NW / QG, SK_BC = sk_keys(NW, QG), SK_BR = sk_rows(QG), SK_TILE = SK_BR * S_ROWB;
+  constexpr int SK_Q = S_KV_LDS ? 2 * SK_BC * S_ROWB : 0;   // K, V; then the tiles
+  constexpr int SK_STAT = SK_Q + 4 * SK_TILE;     // per buffer and row: -lse (see s_units), then D
+  __shared__ __attribute__((aligned(16))) char smem[SK_STAT + 2 * 2 * SK_BR * 4];   // (K, V,) Q[2], dO[2], statistics[2]
   extern __shared__ int s_list[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, h = lane >> 5;
   const int d = S_PAD ? a.d : S_D;
@@ -989,6 +1003,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
 
   if (nwalk > 0) {
     bf16x8 kf[S_KS], vf[S_KS];
+    if constexpr (!S_KV_LDS)
 #pragma unroll
     for (int ks = 0; ks < S_KS; ks++) {
       const bool there = key0 + lr < Nc && (!S_PAD || ks * 16 + h * 8 < d);
@@ -1000,8 +1015,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     for (int ks = 0; ks < S_KS; ks++) qaddr[ks] = s_off(lr, 2 * ks + h);
     s_taddr(lane, taddr);
     const unsigned lds0 = lds_addr(smem);
-    constexpr int NL = SK_BR / S_RPL / SK_WAVES;  // wave-wide loads per wavefront and tile
-    static_assert(NL >= 1 && NL * SK_WAVES * S_RPL == SK_BR, "a tile's rows must divide evenly among the wavefronts");
+    constexpr int NL = SK_BR / S_RPL / NW;  // wave-wide loads per wavefront and tile
+    static_assert(NL >= 1 && NL * NW * S_RPL == SK_BR, "a tile's rows must divide evenly among the wavefronts");
     int goff[NL];
 #pragma unroll
     for (int il = 0; il < NL; il++) goff[il] = s_dma_off(w * NL + il, lane, qpitch, d);
@@ -1025,8 +1040,8 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       const __amdgpu_buffer_rsrc_t grs = make_rsrc(a.dO + hbase, s_span(a.Nq, qpitch, d));
 #pragma unroll
       for (int il = 0; il < NL; il++) {
-        dma_b128_to_lds(qrs, lds0 + buf * SK_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SK_BR * qpitch) + goff[il]);
-        dma_b128_to_lds(grs, lds0 + (2 + buf) * SK_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SK_BR * qpitch) + goff[il]);
+        dma_b128_to_lds(qrs, lds0 + SK_Q + buf * SK_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SK_BR * qpitch) + goff[il]);
+        dma_b128_to_lds(grs, lds0 + SK_Q + (2 + buf) * SK_TILE + (unsigned)(wu * NL + il) * 1024u, (int)(t * SK_BR * qpitch) + goff[il]);
       }
     };
     auto stat_commit = [&](int buf) __attribute__((always_inline)) {
@@ -1036,6 +1051,17 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     const long long wave_first_k = k_off + key0, wave_last_k = wave_first_k + 31;
     const long long kpos = wave_first_k + lr;
 
+    if constexpr (S_KV_LDS) {                      // (keys past Nc, columns past d: zero; awaited with the first tile)
+      constexpr int LOADS = SK_BC / S_RPL / NW;
+      const unsigned kpitch = (unsigned)C.ks_r * 2u;
+      const __amdgpu_buffer_rsrc_t krs = make_rsrc(Kh, s_span(Nc, kpitch, d)), vrs = make_rsrc(Vh, s_span(Nc, kpitch, d));
+#pragma unroll
+      for (int il = 0; il < LOADS; il++) {
+        const int off = s_dma_off(w * LOADS + il, lane, kpitch, d), at = S_PAD && off < 0 ? off : (int)((unsigned)key_wg * kpitch) + off;
+        dma_b128_to_lds(krs, lds0 + (unsigned)(wu * LOADS + il) * 1024u, at);
+        dma_b128_to_lds(vrs, lds0 + SK_BC * S_ROWB + (unsigned)(wu * LOADS + il) * 1024u, at);
+      }
+    }
     fetch(0, 0);
     stat_commit(0);
     for (int n = 0; n < nwalk; n++) {
@@ -1043,17 +1069,17 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
       __builtin_amdgcn_s_barrier();
       if (n + 1 < nwalk) fetch(n + 1, (n + 1) & 1);
       const int buf = n & 1;
-      const char* ql = smem + buf * SK_TILE + qoff * S_ROWB;
-      const char* gl = smem + (2 + buf) * SK_TILE + qoff * S_ROWB;
+      const char* ql = smem + SK_Q + buf * SK_TILE + qoff * S_ROWB;
+      const char* gl = smem + SK_Q + (2 + buf) * SK_TILE + qoff * S_ROWB;
       int g_unused, t;
-      const bool mine = ((locate(n, g_unused, t) >> wu) & 1) != 0;
+      const bool mine = ((locate(n, g_unused, t) >> kw) & 1) != 0;
       if (mine) {                                  // (else: block flags hide this wavefront's keys from the tile)
         // S = Q K^T, dP = dO V^T: lane = key lr, register r = row first_row + 8*(r/4) + 4h + r%4
         const int first_row = t * SK_BR + qoff;
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
-        if constexpr (SK_WAVES == 2) {
+        if constexpr (NW == 2) {
           // One wavefront per SIMD: nobody else hides an LDS read's latency, and left alone the
           // compiler reads one fragment, waits, multiplies, sixteen times over.  All sixteen
           // fragments are requested first (the registers are there), then the MFMAs run.
@@ -1063,6 +1089,13 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int ks = 0; ks < S_KS; ks++) { s = mfma32(qa[ks], kf[ks], s); dp = mfma32(ga[ks], vf[ks], dp); }
+        } else if constexpr (S_KV_LDS) {
+          const char* const kl = smem + kw * 32 * S_ROWB;
+#pragma unroll
+          for (int ks = 0; ks < S_KS; ks++) {
+            s = mfma32(lds_read_b128(ql, qaddr[ks]), lds_read_b128(kl, qaddr[ks]), s);
+            dp = mfma32(lds_read_b128(gl, qaddr[ks]), lds_read_b128(kl, SK_BC * S_ROWB + qaddr[ks]), dp);
+          }
         } else {
 #pragma unroll
           for (int ks = 0; ks < S_KS; ks++) {
@@ -1091,7 +1124,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
         // (two wavefronts per workgroup: the transposed dO and Q fragments of the last phase are
         // requested here, so that they arrive while the exponentials run)
         bf16x4 tg[2][S_DB][2], tq[2][S_DB][2];
-        if constexpr (SK_WAVES == 2) {
+        if constexpr (NW == 2) {
 #pragma unroll
           for (int u = 0; u < 2; u++)
 #pragma unroll
@@ -1104,25 +1137,26 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
           __builtin_amdgcn_sched_barrier(0);
         }
         bf16x8 pf[2][S_TERMS], dsf[2][S_TERMS];      // per 16-row group: A operands of dV, dK
+        auto terms = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q4 = 0; q4 < 4; q4++) {
-          const f32x4 nl = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + qoff + 8 * q4 + 4 * h);
-          const f32x4 dr = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + SK_BR + qoff + 8 * q4 + 4 * h);
+          for (int q4 = 2 * u; q4 < 2 * u + 2; q4++) {
+            const f32x4 nl = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + qoff + 8 * q4 + 4 * h);
+            const f32x4 dr = *reinterpret_cast<const f32x4*>(stat + buf * 2 * SK_BR + SK_BR + qoff + 8 * q4 + 4 * h);
 #pragma unroll
-          for (int j = 0; j < 4; j += 2) {
-            const int r = 4 * q4 + j;
-            const float p0 = s_exp(s[r], a.scale, a.c, nl[j]), p1 = s_exp(s[r + 1], a.scale, a.c, nl[j + 1]);
-            s_terms(pf[r >> 3], r & 7, p0, p1);
-            s_terms(dsf[r >> 3], r & 7, p0 * (dp[r] - dr[j]), p1 * (dp[r + 1] - dr[j + 1]));
+            for (int j = 0; j < 4; j += 2) {
+              const int r = 4 * q4 + j;
+              const float p0 = s_exp(s[r], a.scale, a.c, nl[j]), p1 = s_exp(s[r + 1], a.scale, a.c, nl[j + 1]);
+              s_terms(pf[u], r & 7, p0, p1);
+              s_terms(dsf[u], r & 7, p0 * (dp[r] - dr[j]), p1 * (dp[r + 1] - dr[j + 1]));
+            }
           }
-        }
+        };
         // dV += P^T dO, dK += dS^T Q (dO and Q through transposing reads)
-#pragma unroll
-        for (int u = 0; u < 2; u++)
+        auto products = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
           for (int db = 0; db < S_DB; db++) {
             bf16x8 bg, bq;
-            if constexpr (SK_WAVES == 2) {
+            if constexpr (NW == 2) {
               bg = cat4(tg[u][db][0], tg[u][db][1]);
               bq = cat4(tq[u][db][0], tq[u][db][1]);
             } else {
@@ -1132,6 +1166,11 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
             dv[db] = s_mfma_terms_a(pf[u], bg, dv[db]);
             dk[db] = s_mfma_terms_a(dsf[u], bq, dk[db]);
           }
+        };
+        terms(0);
+        if constexpr (S_KV_LDS) { products(0); terms(1); }           // (fewer registers)
+        else { terms(1); products(0); }
+        products(1);
       }
       if (n + 1 < nwalk) stat_commit((n + 1) & 1);
     }
@@ -1139,7 +1178,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
     if constexpr (QG > 1) {                        // [key block][dK, dV][db][q4][lane]
       static_assert(QG == 2 && KW * 256 * S_D <= SK_STAT, "the other half's sums fit the tiles");
       f32x4* const so = reinterpret_cast<f32x4*>(smem) + kw * 2 * S_DB * 4 * 64 + lane;
-      __builtin_amdgcn_s_barrier();                // (all have read the last tile)
+      __syncthreads();                             // (all have read the last tile; a barrier that the writes below do not cross)
       if (qoff != 0) {
 #pragma unroll
         for (int db = 0; db < S_DB; db++)
@@ -1287,24 +1326,28 @@ int launch_bwd_dq(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hip
                       grid_blocks(a.H, (long long)a.blocks_per_head * a.splits), (longest + 31) / 32, 64 * nw, stream);
 }
 
-// Keys of a dK/dV workgroup, for the host's rule of splitting (two workgroups share a CU in every build).
-int dkv_keys() { return sk_keys(1); }
+// Keys of a dK/dV workgroup, for the host's rule of splitting (two workgroups of 32-row tiles share a CU, one of 64-row tiles).
+int dkv_keys() { return sk_keys(SK_WAVES, SK_GROUPS); }
+int dkv_rows() { return sk_rows(SK_GROUPS); }      // rows of its tiles
 
 int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hipStream_t stream) {
   BwdArgsLite a;
   bwd_args(a, p, io, ch, n);
   a.H = p.B * p.H / p.group;                       // workgroups are laid out over key/value heads
   set_row_parts(a, io);
-  constexpr int G = SK_WAVES == 4 ? 2 : 1;
-  const int groups = io.parts != nullptr && io.parts->groups == 2 && a.parts.splits == 1 && ch[0].bmask == nullptr ? G : 1, bc = sk_keys(groups);
+  constexpr int G = SK_WAVES == 4 ? 2 : SK_GROUPS, FINE = SK_WAVES == 8 ? 2 : SK_WAVES;   // groups of whole walks; wavefronts for flags 64 wide
+  const bool flags = ch[0].bmask != nullptr, fine = flags && p.bsize < 128;
+  const int nw = fine ? FINE : SK_WAVES;
+  const int groups = nw == 2 ? 1 : io.parts != nullptr && io.parts->groups == 2 && a.parts.splits == 1 && !flags ? G : SK_GROUPS, bc = sk_keys(nw, groups);
   const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, a.parts.splits);
-  if (a.parts.splits > 1 && ch[0].bmask != nullptr) return BURST_ERR_SHAPE;
-  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + bc - 1) / bc, unequal_keys(p, ch[0], bc, 32), 2) : 0;
-  static DeviceOnce done;
-  const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true, 1> : groups > 1 ? burst_bwd_dkv_d64_kernel<false, false, G> : burst_bwd_dkv_d64_kernel<false, false, 1>,
-                              burst_bwd_dkv_d64_kernel<true, false, 1>, done, a, nb,
-                              (long long)p.group * ((p.Nq + 31) / 32), 64 * SK_WAVES, stream);
-  return st != BURST_OK || a.parts.splits == 1 ? st : launch_merge_dkv<S_D, sk_keys(1), sk_rows(1), S_PAD>(a, stream);
+  if (a.parts.splits > 1 && flags) return BURST_ERR_SHAPE;
+  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + bc - 1) / bc, unequal_keys(p, ch[0], bc, 32), nw == 8 ? 1 : 2) : 0;
+  static DeviceOnce done, done2;
+  const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true, SK_GROUPS, SK_WAVES>
+                              : groups == G ? burst_bwd_dkv_d64_kernel<false, false, G, SK_WAVES> : burst_bwd_dkv_d64_kernel<false, false, SK_GROUPS, SK_WAVES>,
+                              nw == SK_WAVES ? burst_bwd_dkv_d64_kernel<true, false, SK_GROUPS, SK_WAVES> : burst_bwd_dkv_d64_kernel<true, false, 1, FINE>,
+                              nw == SK_WAVES ? done : done2, a, nb, (long long)p.group * ((p.Nq + 31) / 32), 64 * nw, stream);
+  return st != BURST_OK || a.parts.splits == 1 ? st : launch_merge_dkv<S_D, sk_keys(SK_WAVES, SK_GROUPS), sk_rows(SK_GROUPS), S_PAD>(a, stream);
 }
 
 }  // namespace BURST_SMALL_NS
