@@ -5,6 +5,7 @@
 // one) and cost 200 us of host time at any size, several times the GPU time of a short sequence.
 #include <torch/extension.h>
 #include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 
 #include <cmath>
@@ -187,8 +188,89 @@ std::vector<Tensor> attention(const Tensor& q, const std::vector<Tensor>& ks, co
   return Attention::apply(q, at::TensorList(kvm), (int64_t)ks.size(), mask_of, scale, causal, q_off, window, block);
 }
 
+// harness.RingWalk's two calls for tensors as they usually are: chunks that lie densely, of the walk's type and sizes and without
+// block flags, state and statistics as the walk made them, a workspace that suffices, no capture.  kOther where something
+// is not so, with nothing enqueued: the caller's own marshalling then sees to it, and to its errors.  (A pass over four chunks of 256
+// rows spent more time in the interpreter than on the GPU: see RingWalk.)
+constexpr int kOther = 1;
+bool plain_f32(const Tensor& t, const Tensor& q) { return t.is_cuda() && t.device() == q.device() && t.scalar_type() == torch::kFloat && t.is_contiguous(); }
+bool like_q(const Tensor& t, const Tensor& q) {
+  return t.is_cuda() && t.device() == q.device() && t.scalar_type() == q.scalar_type() && t.sizes() == q.sizes() && t.strides() == q.strides();
+}
+bool usual(Call& c, const Tensor& q, const std::vector<Tensor>& ks, const std::vector<Tensor>& vs, const std::vector<int64_t>& k_offs, double scale,
+           bool causal, int64_t q_off, int64_t window, int64_t kv_heads) {
+  if (ks.empty() || vs.size() != ks.size() || k_offs.size() != ks.size() || q.dim() != 4 || !q.is_cuda() || q.numel() == 0) return false;
+  if (q.scalar_type() != torch::kBFloat16 && q.scalar_type() != torch::kFloat) return false;
+  if ((q.size(3) > 1 && q.stride(3) != 1) || q.device().index() != c10::hip::current_device()) return false;
+  if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) return false;
+  const int64_t heads = kv_heads != 0 ? kv_heads : q.size(1);
+  for (size_t i = 0; i < ks.size(); i++) {
+    const Tensor &k = ks[i], &v = vs[i];
+    if (!k.is_cuda() || !v.is_cuda() || k.device() != q.device() || v.device() != q.device() || k.scalar_type() != q.scalar_type() ||
+        v.scalar_type() != q.scalar_type() || k.dim() != 4 || k.sizes() != v.sizes() || !k.is_contiguous() || !v.is_contiguous()) return false;
+    if (k.size(0) != q.size(0) || k.size(1) != heads || k.size(3) != q.size(3) || k.size(2) > 0x7fffffff) return false;
+  }
+  c = describe(q, ks, vs, {}, {}, scale, causal, q_off, window, 0);
+  c.p.kv_heads = (int32_t)kv_heads;
+  for (size_t i = 0; i < ks.size(); i++) c.chunks[i].k_off = k_offs[i];
+  return true;
+}
+// The walk's workspace, if the call needs one: false where it is too small or belongs to another stream.
+bool suffices(const Call& c, int flags, const std::optional<Tensor>& ws, uint64_t ws_stream, void* stream, void*& at, size_t& bytes) {
+  const size_t need = burst_walk_workspace_bytes(c.chunks.data(), (int)c.chunks.size(), &c.p, flags);
+  at = nullptr; bytes = 0;
+  if (need == 0) return true;
+  if (!ws.has_value() || (size_t)ws->nbytes() < need || ws_stream != (uint64_t)stream) return false;
+  at = ws->data_ptr(); bytes = (size_t)ws->nbytes();
+  return true;
+}
+
+int walk_forward(const Tensor& q, const std::vector<Tensor>& ks, const std::vector<Tensor>& vs, const std::vector<int64_t>& k_offs, double scale,
+                 bool causal, int64_t q_off, int64_t window, int64_t kv_heads, const Tensor& O_acc, const Tensor& m, const Tensor& l,
+                 const Tensor& O, const Tensor& lse, const std::optional<Tensor>& ws, uint64_t ws_stream) {
+  Call c;
+  if (!usual(c, q, ks, vs, k_offs, scale, causal, q_off, window, kv_heads) || !like_q(O, q)) return kOther;
+  for (const Tensor* t : {&O_acc, &m, &l, &lse}) if (!plain_f32(*t, q)) return kOther;
+  void *at, *const stream = stream_of(q);
+  size_t bytes;
+  if (!suffices(c, BURST_WALK_FORWARD, ws, ws_stream, stream, at, bytes)) return kOther;
+  return burst_walk_fwd(q.data_ptr(), c.chunks.data(), (int)ks.size(), O_acc.data_ptr<float>(), m.data_ptr<float>(), l.data_ptr<float>(),
+                        O.data_ptr(), lse.data_ptr<float>(), at, bytes, &c.p, stream);
+}
+
+// dQ, dK, dV: new tensors, fp32.
+std::tuple<int, Tensor, std::vector<Tensor>, std::vector<Tensor>> walk_backward(
+    const Tensor& q, const std::vector<Tensor>& ks, const std::vector<Tensor>& vs, const std::vector<int64_t>& k_offs, double scale, bool causal,
+    int64_t q_off, int64_t window, int64_t kv_heads, const Tensor& O, const Tensor& dO, const Tensor& lse, const Tensor& D,
+    const std::optional<Tensor>& ws, uint64_t ws_stream) {
+  Call c;
+  Tensor dQ;
+  std::vector<Tensor> dK, dV;
+  void *at, *stream = nullptr;
+  size_t bytes;
+  if (!usual(c, q, ks, vs, k_offs, scale, causal, q_off, window, kv_heads) || !like_q(O, q) || !like_q(dO, q) || !plain_f32(lse, q) || !plain_f32(D, q) ||
+      !suffices(c, 0, ws, ws_stream, stream = stream_of(q), at, bytes)) return {kOther, dQ, dK, dV};
+  const auto f32 = q.options().dtype(torch::kFloat);
+  try {
+    dQ = torch::empty(q.sizes(), f32);
+    for (size_t i = 0; i < ks.size(); i++) {
+      dK.push_back(torch::empty(ks[i].sizes(), f32));
+      dV.push_back(torch::empty(vs[i].sizes(), f32));
+      c.chunks[i].dK = dK[i].data_ptr();
+      c.chunks[i].dV = dV[i].data_ptr();
+    }
+  } catch (const c10::OutOfMemoryError&) {         // (raised again, as torch's own, by the caller's allocations)
+    return {kOther, Tensor(), {}, {}};
+  }
+  const int st = burst_walk_bwd(q.data_ptr(), c.chunks.data(), (int)ks.size(), O.data_ptr(), dO.data_ptr(), lse.data_ptr<float>(), D.data_ptr<float>(),
+                                dQ.data_ptr(), 0, 0, 0, at, bytes, &c.p, stream);
+  return {st, dQ, dK, dV};
+}
+
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("attention", &attention, pybind11::call_guard<pybind11::gil_scoped_release>());
+  m.def("walk_forward", &walk_forward, pybind11::call_guard<pybind11::gil_scoped_release>());
+  m.def("walk_backward", &walk_backward, pybind11::call_guard<pybind11::gil_scoped_release>());
 }

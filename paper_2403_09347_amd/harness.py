@@ -56,6 +56,11 @@ class RingWalk:
             order = list(order)                      # (it may be an iterator, and is walked once per list)
             pick = lambda x: None if x is None else [x[j] for j in order]
             Ks, Vs, k_offs, masks = pick(Ks), pick(Vs), pick(k_offs), pick(masks)
+        if masks is None:
+            st = self._native("walk_forward", Ks, Vs, k_offs, self.O_acc, self.m, self.l, self.O, self.lse)
+            if st is not None:
+                B._check(st, "burst_walk_fwd")
+                return self.O, self.lse
         p = self._walk_params()
         chunks = B.chunk_array(Ks, Vs, k_offs, masks, p)
         B.burst_walk_fwd(self.Q, chunks, self.O_acc, self.m, self.l, self.O, self.lse, p, self._scratch(chunks, p, B.BURST_WALK_FORWARD))
@@ -64,6 +69,19 @@ class RingWalk:
     def _own(self, name):
         """Whether a subclass (or the object) has a part of the walk of its own, which the whole-walk calls would pass by."""
         return getattr(getattr(self, name), "__func__", None) is not getattr(RingWalk, name)
+
+    def _native(self, name, Ks, Vs, k_offs, *tensors):
+        """The whole call in native code where everything is as usual (see csrc/burst_torch.cpp), or None: marshalling four chunks
+        of 256 rows here takes longer than their kernels (us a pass with gradients, so / natively 73 / 49)."""
+        if type(self) is not RingWalk or type(Ks) is not list or type(Vs) is not list or type(k_offs) is not list:
+            return None
+        try:
+            r = getattr(B.load_torch_module(), name)(
+                self.Q, Ks, Vs, k_offs, self.scale, self.causal, self.q_off, self.window, self.kv_heads, *tensors, self._workspace,
+                0 if self._workspace_stream is None else self._workspace_stream.cuda_stream)
+        except TypeError:                            # (something that is no tensor or no whole number)
+            return None
+        return None if (r if isinstance(r, int) else r[0]) == 1 else r
 
     def _walk_params(self):
         p = self.params(0, 0)
@@ -92,6 +110,11 @@ class RingWalk:
     def backward(self, Ks, Vs, k_offs, dO, dQ=None, dKs=None, dVs=None, use_D=True, masks=None):
         """dQ given: the gradient is added to it.  use_D = False: every chunk's call computes D for itself."""
         if use_D:
+            if dQ is None and dKs is None and masks is None and not self._own("prepare"):
+                r = self._native("walk_backward", Ks, Vs, k_offs, self.O, dO, self.lse, self.D)
+                if r is not None:
+                    B._check(r[0], "burst_walk_bwd")
+                    return r[1:]
             accumulate = dQ is not None
             if dQ is None:
                 dQ = torch.empty((self.Bt, self.H, self.Nq, self.d), device=self.Q.device, dtype=torch.float32)
