@@ -63,7 +63,6 @@ struct DkvArgs {
   long long q_off;
   long long window;      // 0 = none; else keys at positions <= query position - window are hidden
   int bsize;             // block flags: edge, a multiple of 64
-  int order;             // not PARTS, CHAIN: see grid_order
   int n, per;            // chunks, all with block flags or none; workgroups of each (chunk_at)
   Layout lay;            // strides of Q and dO
   Chunk ch[kMaxChunks];
@@ -144,7 +143,7 @@ burst_bwd_dkv_kernel(DkvArgs a) {
     if constexpr (PARTS) {
       if (!locate_part(bid, a.H, blocks, a.parts.splits, head, kblk, part)) return;
     } else {
-      if (!locate_block(bid, a.H, blocks, head, kblk, a.order)) return;
+      if (!locate_block(bid, a.H, blocks, head, kblk, a.ch[chunk].order)) return;
     }
   }
   const int group = SPARSE ? a.group : 1;          // query heads that share this key/value head
@@ -691,7 +690,7 @@ static long long lay_out(DkvArgs& a, const KParams& p, const Chunk* ch, int n, i
   a.c = p.scale * kLog2e; a.scale = p.scale; a.causal = p.causal; a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.n = n; a.lay = p.lay;
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
-  a.order = n == 1 ? grid_order(a.H, (ch[0].Nc + 32 * key_waves - 1) / (32 * key_waves), unequal_keys(p, ch[0], 32 * key_waves, DKV_BR), key_waves == 4 ? 1 : 2) : 0;
+  for (int i = 0; i < n; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, 32 * key_waves, DKV_BR, key_waves == 4 ? 1 : 2);
   return chunk_grid(a.ch, n, a.H, 32 * key_waves, a.per, key_waves == 4 ? splits : 1);
 }
 bool dkv_chained(const KParams& p, const Chunk* ch, int n) {

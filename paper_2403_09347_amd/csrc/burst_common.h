@@ -84,6 +84,7 @@ struct Chunk {
   int Nc, bpitch;
   int first_block;                   // dK/dV kernels: workgroups of the chunks before this one
   int first_row;                     // split dK/dV walks: rows of partial gradients of the chunks before this one
+  int order;                         // dK/dV kernels, walks not cut: see grid_order
   // element offset of row 0 of key/value head `kvhead`, which counts batch x heads
   __host__ __device__ size_t kv_base(int kvhead, int kv_heads) const {
     const int b = kvhead / kv_heads;
@@ -294,6 +295,11 @@ inline bool unequal_keys(const KParams& p, const Chunk& c, int bc, int br) {
 inline int grid_order(long long heads, long long blocks, bool unequal, int fit) {
   if (!unequal || heads * blocks <= 256 || (heads % 8 == 0 && blocks >= 64 * fit)) return 0;
   return heads * blocks <= 256LL * fit ? kByBlock | kMirror : kByBlock;
+}
+// The order of a chunk's blocks of bc keys in a dK/dV grid of n chunks (each a run of workgroups, none of them mirrored where others follow).  In
+// a causal walk of several chunks it is the one on the diagonal that is taken by block.
+inline int keys_order(const KParams& p, const Chunk& c, int n, long long heads, int bc, int br, int fit) {
+  return grid_order(heads, (c.Nc + bc - 1) / bc, unequal_keys(p, c, bc, br), fit) & (n == 1 ? kByBlock | kMirror : kByBlock);
 }
 inline long long grid_blocks(long long heads, long long blocks) { return (heads * blocks + 7) / 8 * 8; }
 // Workgroup id of a split dK/dV launch -> (head, block of keys, part).  An XCD gets whole (head, part) columns, longest

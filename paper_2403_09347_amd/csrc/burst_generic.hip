@@ -762,7 +762,7 @@ bwd_dkv_generic_kernel(GenArgs a) {
   if constexpr (SPLIT) {
     if (!locate_part((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, a.parts.splits, kvhead, blk, part)) return;
   } else {
-    if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk, a.order)) return;
+    if (!locate_block((int)blockIdx.x - C.first_block, a.BH / a.group, (Nc + 31) >> 5, kvhead, blk, C.order)) return;
   }
   const int key0 = blk * 32, key = key0 + lr;
   int lo, hi;
@@ -1204,7 +1204,8 @@ static int gen_dispatch(GenArgs& a, const KParams& p, int dtype, hipStream_t s) 
   }
   if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
   if (grid == 0) return BURST_OK;
-  if (KIND == GEN_DKV) a.order = a.n == 1 && a.parts.splits == 1 ? grid_order(a.BH / a.group, (a.ch[0].Nc + 31) / 32, unequal_keys(p, a.ch[0], 32, 32), 1) : 0;
+  if (KIND == GEN_DKV)
+    for (int i = 0; i < a.n; i++) a.ch[i].order = keys_order(p, a.ch[i], a.n, a.BH / a.group, 32, 32, 1);
   else a.order = grid_order(a.BH, (long long)a.blocks * a.splits, unequal_rows(p, a.ch, a.n, 32), 1);
   if (KIND == GEN_DKV ? a.parts.splits > 1 : a.splits > 1) {
     if (dtype != BURST_F32 || !fp32_tiles(a.d, a.lay, a.ch, a.n) || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;

@@ -943,7 +943,7 @@ burst_bwd_dkv_d64_kernel(BwdArgsLite a) {
   if constexpr (PARTS) {
     if (!locate_part(bid, a.H, blocks, a.parts.splits, kvhead, kblk, part)) return;
   } else {
-    if (!locate_block(bid, a.H, blocks, kvhead, kblk, a.order)) return;
+    if (!locate_block(bid, a.H, blocks, kvhead, kblk, C.order)) return;
   }
   const int Nc = C.Nc;
   const long long k_off = C.k_off;
@@ -1341,7 +1341,7 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   const int groups = nw == 2 ? 1 : io.parts != nullptr && io.parts->groups == 2 && a.parts.splits == 1 && !flags ? G : SK_GROUPS, bc = sk_keys(nw, groups);
   const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, a.parts.splits);
   if (a.parts.splits > 1 && flags) return BURST_ERR_SHAPE;
-  a.order = n == 1 && a.parts.splits == 1 ? grid_order(a.H, (ch[0].Nc + bc - 1) / bc, unequal_keys(p, ch[0], bc, 32), nw == 8 ? 1 : 2) : 0;
+  for (int i = 0; i < n; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, bc, 32, nw == 8 ? 1 : 2);
   static DeviceOnce done, done2;
   const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true, SK_GROUPS, SK_WAVES>
                               : groups == G ? burst_bwd_dkv_d64_kernel<false, false, G, SK_WAVES> : burst_bwd_dkv_d64_kernel<false, false, SK_GROUPS, SK_WAVES>,
