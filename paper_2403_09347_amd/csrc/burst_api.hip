@@ -398,7 +398,7 @@ bool generic_splittable(const std::vector<WalkChunk>& w) {
   for (const WalkChunk& x : w) if (x.p.block_mask != nullptr || !burst::fp32_tiles(x.k.d, x.k.lay, &x.c, 1)) return false;
   return true;
 }
-// Into how many workgroups the tiles of a block of 32 rows are dealt: as many as there are CUs for (they run at the fp32
+// Into how many workgroups the tiles of a block of 32 rows are dealt.  Up to 128 blocks as many as there are CUs for (they run at the fp32
 // matrix rate with one wavefront per SIMD, so that more gain nothing), with a tile for each of their four wavefronts.
 // us a launch with its merge, whole / by the rule, forward and dQ: 256 rows x 1024 keys, one head, d = 64, 32 / 15 and 40 / 16
 // in 8; 4 x 1000 x 3000, d = 64, 82 / 53 and 111 / 63 in 2 (3: 66, 85; 4: 56, 72); 4 x 700 x 1400, d = 128, 70 / 48 and 102 / 68
@@ -412,8 +412,9 @@ bool generic_splittable(const std::vector<WalkChunk>& w) {
 int generic_splits(const std::vector<WalkChunk>& w) {
   const KParams& k = w[0].k;
   const long long heads = (long long)k.B * k.H, blocks = (k.Nq + 31) / 32;
-  if (heads * blocks > 128 || !generic_splittable(w)) return 1;
-  long long most = 0;                              // key tiles that a block sees
+  const bool many = heads * blocks > 128;
+  if (heads * blocks > (k.d <= 64 ? 128 : 1024) || !generic_splittable(w)) return 1;
+  long long most = 0, least = 0x7fffffff, sum = 0; // key tiles that a block sees
   for (long long row0 = 0; row0 < k.Nq; row0 += 32) {
     long long walk = 0;
     for (const WalkChunk& x : w) {
@@ -423,6 +424,23 @@ int generic_splits(const std::vector<WalkChunk>& w) {
       if (hi > lo) walk += (hi + 31) / 32 - lo / 32;
     }
     most = std::max(most, walk);
+    least = std::min(least, walk);
+    sum += walk;
+  }
+  // More than 128 blocks, above 64 columns (a workgroup a CU): in two where that ends sooner, counted in tiles of a wavefront, with 3
+  // a workgroup beside its tiles and 2 for the merge.  Unequal blocks fill the CUs but for half of a long one at the end, equal ones
+  // come in rounds.  us, forward and dQ with merging, whole / in 2, d = 128: 4 x 1400 x 2800 causal, 176 blocks, 283 / 244;
+  // 8 x 1500, third of three causal chunks, 376 blocks, 700 / 627; equal blocks: 8 x 1100 x 2200, 280 of them, 460 / 395, 8 x 1500 x
+  // 6000, 376, 1115 / 903.  Not split: 8 x 700 x 1400 causal 162 / 161, 8 x 1000 x 2000 causal 212 / 212, 8 x 1400 causal 153 / 196,
+  // 8 x 600 x 1200 141 / 174.
+  if (many) {
+    const double B = (double)(heads * blocks), all = (double)(sum * heads);
+    auto cost = [&](int s) {
+      const double longest = most / (4.0 * s);
+      if (10 * most <= 11 * least) return std::ceil(B * s / 256) * (longest + 3) + (s > 1 ? 2 : 0);
+      return std::max(longest + 3, all / 1024 + 3 * B * s / 256 + longest / 2) + (s > 1 ? 2 : 0);
+    };
+    return cost(2) < 0.97 * cost(1) ? 2 : 1;
   }
   const long long s = std::min({256 / (heads * blocks), most / 4, 64LL});
   const long long others = (long long)w.size() - 1;
