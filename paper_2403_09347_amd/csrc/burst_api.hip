@@ -470,7 +470,9 @@ int generic_splits(const std::vector<WalkChunk>& w) {
 // ranges as its workgroups have places for (forward + dQ with merging and D, us, whole / split: d = 64, 8 x 1500 42 / 40,
 // 8 x 2048 53 / 46, 16 x 2048 56 / 58, 8 x 4000 92 / 79; d = 96, 16 x 1000 54 / 54, 8 x 2048 89 / 71, 12 x 2048 91 / 89; d = 128,
 // 8 x 1500 58 / 58, 8 x 2048 74 / 65, 12 x 2048 75 / 82).
-// Split walks have two groups too where their workgroups of 128 rows are at most one a CU, or would hold 64 rows less
+// Split walks have two groups too where their workgroups of 128 rows are at most one a CU, or where 64 rows less a head are a good part
+// of it (passes of 4 x 1698 keys, us, one / two: d = 64, 80 x 162 rows 238 / 223, 48 x 290 213 / 199, 40 x 418 223 / 226, 16 x 1058 214 / 216;
+// d = 48, 80 x 162 331 / 294, 40 x 418 329 / 334, 16 x 1058 331 / 336).
 // (forward, us: d = 64, 32 over 8 x 16 rows x 16K keys 40 / 31, 80 over 20 x 150 x 8K 76 / 64, 8 x 100 x 8K 26 / 22, 32 x 200 x 64K
 // 188 / 221 (one); d = 128, 32 over 2 x 5 x 64K 145 / 99, 80 over 20 x 150 x 8K 107 / 114 (one), 32 x 200 x 64K 309 / 413 (one)).
 struct RowsPlan { int splits, groups; };
@@ -515,7 +517,7 @@ RowsPlan walk_rows(const std::vector<WalkChunk>& w, bool backward, bool whole) {
   long long s = std::min(512 / blocks, tiles / (pad ? 6 : 8));
   if (pad && s * blocks > 256 && s * blocks <= (k.causal || blocks > 128 ? 360 : 400)) s = 256 / blocks;
   if (s < 2 || tiles < (pad ? 12 : 20)) return unsplit();
-  return {(int)s, s * blocks <= 256 || k.Nq <= 64 || (!wide && (k.Nq - 1) % 128 < 64) ? 2 : 1};
+  return {(int)s, s * blocks <= 256 || k.Nq <= 64 || (!wide && k.Nq <= 320 && (k.Nq - 1) % 128 < 64) ? 2 : 1};
 }
 int dq_launches(const std::vector<WalkChunk>& w, bool whole) {
   int n = 0;
