@@ -13,7 +13,8 @@
 // Same mathematics, operand orientations and register layouts as the hand-scheduled d = 128
 // kernels (S^T = K Q^T with one query row per lane for the forward and dQ side, S = Q K^T with one
 // key per lane for the dK/dV side; P and dS leave the accumulators already in the layout the next
-// MFMA wants), but written plainly: one wavefront owns 32 rows (or keys), a step runs its phases
+// MFMA wants), but written plainly: one wavefront owns 32 rows (or keys), alone or halving every tile with another
+// wavefront (see walk_rows in burst_api.hip), a step runs its phases
 // one after the other with compiler-scheduled MFMAs in VGPR accumulators, tiles are
 // double-buffered in LDS by DMA with one barrier per tile, and two workgroups share a CU so that
 // one's vector work overlaps the other's matrix work.  At d = 64 a tile has half the matrix work
