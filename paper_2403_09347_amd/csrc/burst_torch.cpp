@@ -201,7 +201,8 @@ bool usual(Call& c, const Tensor& q, const std::vector<Tensor>& ks, const std::v
            bool causal, int64_t q_off, int64_t window, int64_t kv_heads) {
   if (ks.empty() || vs.size() != ks.size() || k_offs.size() != ks.size() || q.dim() != 4 || !q.is_cuda() || q.numel() == 0) return false;
   if (q.scalar_type() != torch::kBFloat16 && q.scalar_type() != torch::kFloat) return false;
-  if ((q.size(3) > 1 && q.stride(3) != 1) || q.device().index() != c10::hip::current_device()) return false;
+  // (not every stride of a view can go into the parameter block: all of them 0, as of an expanded row, means dense there)
+  if (!(q.is_contiguous() || addressable(q)) || q.device().index() != c10::hip::current_device()) return false;
   if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) return false;
   const int64_t heads = kv_heads != 0 ? kv_heads : q.size(1);
   for (size_t i = 0; i < ks.size(); i++) {

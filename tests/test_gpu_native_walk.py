@@ -73,3 +73,14 @@ def test_what_is_not_as_usual_is_marshalled_as_before(monkeypatch):
     with pytest.raises(B.BurstError):
         RingWalk(case["Q"], 0.0).forward(K, V, offs)
     assert count == [False, False, True, False, False, False, False, True]
+
+
+def test_a_row_expanded_to_a_slice_is_refused():
+    """Strides of 0 throughout mean a dense tensor in the parameter block: such a Q, which holds one row, is no slice to read."""
+    q = torch.randn(64, device=DEV).bfloat16().expand(2, 3, 100, 64)
+    K, V = ([torch.randn(2, 3, 70, 64, device=DEV).bfloat16()] for _ in range(2))
+    walk = RingWalk(q, 0.125)
+    with pytest.raises(ValueError):
+        walk.forward(K, V, [0])
+    with pytest.raises(ValueError):
+        walk.backward(K, V, [0], q)
