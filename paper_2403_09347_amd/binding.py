@@ -58,7 +58,7 @@ def from_native(e):
     return BurstError(int(m.group(2)), m.group(1)) if m else e
 
 
-_lib, _torch_module = None, None
+_lib, _torch_module, _walk_module = None, None, None
 TORCH_LIB_PATH = os.path.join(_HERE, "_burst_torch.so")
 
 
@@ -75,6 +75,18 @@ def load_torch_module():
         spec.loader.exec_module(module)
         _torch_module = module
     return _torch_module
+
+
+def walk_module():
+    """The torch module for RingWalk's native calls, or None where it is not built or does not load (looked for once): a walk
+    marshalled here needs libburst.so alone."""
+    global _walk_module
+    if _walk_module is None:
+        try:
+            _walk_module = load_torch_module()
+        except (ImportError, OSError):
+            _walk_module = False
+    return _walk_module or None
 
 
 def load():

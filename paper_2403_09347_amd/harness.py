@@ -75,8 +75,11 @@ class RingWalk:
         of 256 rows here takes longer than their kernels (us a pass with gradients, so / natively 73 / 49)."""
         if type(self) is not RingWalk or type(Ks) is not list or type(Vs) is not list or type(k_offs) is not list:
             return None
+        module = B.walk_module()
+        if module is None:
+            return None
         try:
-            r = getattr(B.load_torch_module(), name)(
+            r = getattr(module, name)(
                 self.Q, Ks, Vs, k_offs, self.scale, self.causal, self.q_off, self.window, self.kv_heads, *tensors, self._workspace,
                 0 if self._workspace_stream is None else self._workspace_stream.cuda_stream)
         except TypeError:                            # (something that is no tensor or no whole number)
