@@ -73,7 +73,7 @@ class RingWalk:
     def _native(self, name, Ks, Vs, k_offs, *tensors):
         """The whole call in native code where everything is as usual (see csrc/burst_torch.cpp), or None: marshalling four chunks
         of 256 rows here takes longer than their kernels (us a pass with gradients, so / natively 73 / 49)."""
-        if type(self) is not RingWalk or type(Ks) is not list or type(Vs) is not list or type(k_offs) is not list:
+        if type(self) is not RingWalk or self._own("params") or type(Ks) is not list or type(Vs) is not list or type(k_offs) is not list:
             return None
         module = B.walk_module()
         if module is None:

@@ -40,3 +40,21 @@ def test_the_module_takes_what_the_walk_hands_it():
     for ws in (None, torch.zeros(16, dtype=torch.uint8)):
         assert module.walk_forward(*common, walk.O_acc, walk.m, walk.l, walk.O, walk.lse, ws, 0) == 1
         assert module.walk_backward(*common, walk.O, dO, walk.lse, walk.D, ws, 0)[0] == 1
+
+
+def test_an_object_s_own_params_are_asked(monkeypatch):
+    walk, K, V, dO = host_walk()
+    asked = []
+
+    def params(*args, **kw):
+        asked.append(args)
+        return RingWalk.params(walk, *args, **kw)
+
+    monkeypatch.setattr(B, "load_torch_module", lambda: pytest.fail("marshalled natively"))
+    monkeypatch.setattr(B, "_walk_module", None)
+    walk.params = params
+    with pytest.raises(ValueError, match="device tensor expected"):
+        walk.forward(K, V, [0])
+    with pytest.raises(ValueError, match="device tensor expected"):
+        walk.backward(K, V, [0], dO)
+    assert asked
