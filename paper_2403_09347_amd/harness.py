@@ -72,9 +72,13 @@ class RingWalk:
 
     def _native(self, name, Ks, Vs, k_offs, *tensors):
         """The whole call in native code where everything is as usual (see csrc/burst_torch.cpp), or None: marshalling four chunks
-        of 256 rows here takes longer than their kernels (us a pass with gradients, so / natively 73 / 49)."""
+        of 256 rows here takes longer than their kernels (us a pass with gradients, so / natively 73 / 50).  A call refused there costs
+        2 to 3 us: captures, and the first call of a walk that needs a workspace or has changed streams.  Sequence-major chunks, each of whose calls
+        would be refused, are not offered (2 heads, four chunks of 256 rows, a pass 104 / 100)."""
         if type(self) is not RingWalk or self._own("params") or type(Ks) is not list or type(Vs) is not list or type(k_offs) is not list:
             return None
+        if not Ks or not isinstance(Ks[0], torch.Tensor) or not Ks[0].is_contiguous():
+            return None                              # (refused there too, after every tensor has been converted)
         module = B.walk_module()
         if module is None:
             return None

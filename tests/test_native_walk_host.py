@@ -58,3 +58,18 @@ def test_an_object_s_own_params_are_asked(monkeypatch):
     with pytest.raises(ValueError, match="device tensor expected"):
         walk.backward(K, V, [0], dO)
     assert asked
+
+
+def test_chunks_that_are_not_dense_are_not_offered(monkeypatch):
+    """Every call over sequence-major chunks would convert its tensors only to be refused."""
+    walk, K, V, dO = host_walk()
+    seq = [torch.zeros(1, 8, 2, 64, dtype=torch.bfloat16).transpose(1, 2)]
+    monkeypatch.setattr(B, "load_torch_module", lambda: pytest.fail("offered"))
+    monkeypatch.setattr(B, "_walk_module", None)
+    with pytest.raises(ValueError, match="device tensor expected"):
+        walk.forward(seq, seq, [0])
+    with pytest.raises(ValueError, match="device tensor expected"):
+        walk.backward(seq, seq, [0], dO)
+    monkeypatch.undo()
+    with pytest.raises(AttributeError):
+        walk.forward([None], [None], [0])
