@@ -893,11 +893,10 @@ size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const
   if (walk_chunks(chunks, n_chunks, p, false, w) != BURST_OK || w.empty()) return 0;
   const KParams& k = w[0].k;
   const size_t rows = (size_t)k.B * k.H * k.Nq;
-  size_t need = 0;
-  const bool fwd = (flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD)) != 0, bwd = (flags & BURST_WALK_HALF_GRADS) != 0;   // (neither: both)
-  const bool whole_fwd = w.size() == 1 && (flags & BURST_WALK_NO_STATE), whole_bwd = w.size() == 1 && bwd;
-  if (fwd || !bwd) need = split_bytes(k, walk_rows(w, false, whole_fwd).splits);
-  if (bwd || !fwd) need = std::max(need, split_bytes(k, walk_rows(w, true, whole_bwd).splits));
+  // (the two calls may plan differently: what is enough for either of them, unless it is for the forward alone)
+  size_t need = split_bytes(k, walk_rows(w, false, w.size() == 1 && (flags & BURST_WALK_NO_STATE)).splits);
+  if (!(flags & BURST_WALK_FORWARD))
+    need = std::max(need, split_bytes(k, walk_rows(w, true, w.size() == 1 && (flags & BURST_WALK_HALF_GRADS)).splits));
   if (!(flags & (BURST_WALK_NO_STATE | BURST_WALK_FORWARD))) need = std::max(need, dkv_bytes(k, dkv_parts(w, (flags & BURST_WALK_HALF_GRADS) != 0)));
   if ((flags & (BURST_WALK_NO_STATE | BURST_WALK_HALF_GRADS)) && dq_launches(w, w.size() == 1) > 1) {          // between the launches: dQ in fp32, the state
     if (flags & BURST_WALK_HALF_GRADS) need = std::max(need, rows * k.d * sizeof(float));

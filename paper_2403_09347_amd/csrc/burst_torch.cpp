@@ -117,7 +117,7 @@ class Attention : public torch::autograd::Function<Attention> {
     const Call c = describe(q, ks, vs, masks, mask_of, scale, causal, q_off, window, block);
     Tensor O = torch::empty_strided(q.sizes(), q.strides(), q.options());   // O lies in memory like Q
     Tensor lse = torch::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(torch::kFloat));
-    const Tensor ws = scratch(c, BURST_WALK_NO_STATE, q);
+    const Tensor ws = scratch(c, BURST_WALK_NO_STATE | BURST_WALK_FORWARD, q);
     check(burst_walk_fwd(q.data_ptr(), c.chunks.data(), (int)n, nullptr, nullptr, nullptr, O.data_ptr(), lse.data_ptr<float>(),
                          ptr(ws), bytes(ws), &c.p, stream_of(q)), "burst_walk_fwd");
     variable_list saved = {q, O, lse};

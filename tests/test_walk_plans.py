@@ -88,3 +88,20 @@ def test_forms_of_dkv_launches():
     assert form(32, 0, [512], True) == 0 and form(32, 512, [0], True) == 0
     with pytest.raises(B.BurstError):
         form(32, 512, [512], True, kv_heads=5)
+
+
+def test_without_the_forward_flag_the_size_is_enough_for_both_calls():
+    """The forward and the dQ launches of a walk may be split differently (gradients in the inputs' type, no state)."""
+    one = [(8, 2048, 128), (8, 2050, 128), (8, 2048, 64), (8, 1000, 96), (16, 1000, 128), (12, 1700, 64), (4, 2048, 80), (40, 300, 128)]
+    for H, N, d in one:
+        for causal in (False, True):
+            p = B.params(1, H, N, 0, d, "bf16", 0.1, causal=causal)
+            for rows in ([N], [N, N], [4 * N]):
+                state, no_state = (workspace(p, rows, flags=f | B.BURST_WALK_FORWARD) for f in (0, B.BURST_WALK_NO_STATE))
+                assert workspace(p, rows, flags=0) >= state and workspace(p, rows, flags=B.BURST_WALK_HALF_GRADS) >= state
+                assert workspace(p, rows, flags=B.BURST_WALK_NO_STATE) >= no_state
+                assert workspace(p, rows, flags=B.BURST_WALK_NO_STATE | B.BURST_WALK_HALF_GRADS) >= no_state
+    p = B.params(1, 8, 2048, 0, 128, "bf16", 0.1, causal=True)
+    state = lambda s: s * 8 * 2048 * 130 * 4
+    assert workspace(p, [2048], flags=B.BURST_WALK_FORWARD) == state(4) and workspace(p, [2048], flags=B.BURST_WALK_HALF_GRADS) == state(4)
+    assert workspace(p, [2048], flags=B.BURST_WALK_FORWARD | B.BURST_WALK_NO_STATE) == state(2)
