@@ -1291,6 +1291,7 @@ int launch_fwd(const KParams& p, const FwdIo& io, const Chunk* ch, int n, hipStr
   a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.lay = p.lay; a.d = p.d; a.n = n;
   const int nw = row_waves(p, ch, n, true), kg = io.groups == 2 && ch[0].bmask == nullptr ? 2 : 1, br = 32 * nw / kg;
+  if (kg == 2 && !a.fresh) return BURST_ERR_SHAPE;   // (both groups would start from the state and count it twice)
   a.blocks_per_head = (p.Nq + br - 1) / br;
   a.order = grid_order(a.H, (long long)a.blocks_per_head * a.splits, unequal_rows(p, ch, n, br), kg == 2 && S_ROWB == 128 ? 4 : 2);
   int longest = 0;
