@@ -222,9 +222,13 @@ typedef struct burst_chunk {
  * O, lse and final state.  `p` gives everything but Nc, k_off, block_mask, block_mask_stride and
  * kv_strides, which are taken from the chunks.  workspace: device memory of at least
  * burst_walk_workspace_bytes(..., BURST_WALK_FORWARD) bytes, 16-byte aligned, contents undefined before and after, or NULL;
- * with it a slice of few rows is spread over the chip by splitting the keys into ranges whose partial
- * states are merged at the end (the sums then come in another order).  O_acc, m, l may all be NULL: the
- * state is then not kept (workspace: burst_walk_workspace_bytes(..., BURST_WALK_NO_STATE)). */
+ * with it a walk that would leave much of the chip idle (few rows; fp32 also up to 1024 blocks of 32 rows above 64 columns) is
+ * spread over it by splitting the keys into ranges whose partial states are merged at the end, and the workgroups of such a
+ * walk may halve every tile between two groups of wavefronts (the sums then come in another order than chunk by chunk).
+ * O_acc, m, l may all be NULL: the state is then not kept (workspace: burst_walk_workspace_bytes(..., BURST_WALK_NO_STATE)),
+ * and a walk of one chunk may have two groups, or the other d = 128 kernels, with and without a workspace.
+ * Which of these a call has depends on its sizes alone, the number of heads among them: a call repeated gives the same bits, a
+ * head in a call of other sizes the same values up to rounding. */
 int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float* O_acc, float* m, float* l,
                    void* O_out, float* lse, void* workspace, size_t workspace_bytes,
                    const burst_params* p, void* stream);
@@ -235,16 +239,18 @@ int burst_walk_fwd(const void* Q, const burst_chunk* chunks, int n_chunks, float
  * excludes both accumulate flags, and needs the workspace that burst_walk_workspace_bytes(...,
  * BURST_WALK_HALF_GRADS) asks for (BURST_ERR_SHAPE if a part of it that it cannot do without is missing).
  * With the workspace few or unequal walks over query tiles (grouped heads, few keys, causal masks) are also cut
- * into parts whose partial dK, dV are added at the end. */
+ * into parts whose partial dK, dV are added at the end; key ranges, groups and the order of sums as in burst_walk_fwd
+ * (half_grads in the place of the state that is not kept). */
 int burst_walk_bwd(const void* Q, const burst_chunk* chunks, int n_chunks, const void* O, const void* dO,
                    const float* lse, float* D, void* dQ, int accumulate_dq, int accumulate_dkv, int half_grads,
                    void* workspace, size_t workspace_bytes, const burst_params* p, void* stream);
 /* Bytes of workspace that either of the two can use (or, under these flags, needs) for these arguments;
  * 0: none.  Host logic, no device call. */
 size_t burst_walk_workspace_bytes(const burst_chunk* chunks, int n_chunks, const burst_params* p, int flags);
-/* How burst_walk_bwd lays out its first dK/dV launch for these arguments: 0 = a workgroup per block of keys, 1 = the
- * walks over query tiles cut into parts (with the workspace), 2 = one workgroup per CU that takes several blocks in
- * turn; a negative burst_status for invalid arguments.  Host logic, no device call. */
+/* How burst_walk_bwd lays out its first dK/dV launch for these arguments and fp32 gradients: 0 = a workgroup per block of
+ * keys, 1 = the walks over query tiles cut into parts (with the workspace), 2 = one workgroup per CU that takes several
+ * blocks in turn; a negative burst_status for invalid arguments.  (With half_grads a walk of one chunk for which this is 1 may
+ * have a workgroup per 64 keys instead, not cut.)  Host logic, no device call. */
 int burst_walk_dkv_form(const burst_chunk* chunks, int n_chunks, const burst_params* p, int with_workspace);
 #define BURST_WALK_HALF_GRADS 1   /* for burst_walk_bwd with half_grads */
 #define BURST_WALK_NO_STATE 2     /* for burst_walk_fwd without O_acc, m, l */
@@ -295,8 +301,9 @@ int burst_local_bwd_materialized(const void* Q, const void* K_chunk, const void*
 int burst_set_kernel_family(int family);
 /* Which family would serve burst_local_fwd / the dQ half of burst_local_bwd for these parameters
  * under the current setting: 1 or 2 as above, 0 = neither (another head dimension or type, or a
- * shape only the generic kernels take); a negative burst_status for an invalid block.  Host
- * logic only, no device call. */
+ * shape only the generic kernels take); a negative burst_status for an invalid block.  Walks of several chunks
+ * choose likewise for each of them; a causal walk of one chunk without a state (with half_grads) may take family 2 where
+ * this is 1.  Host logic only, no device call. */
 int burst_kernel_family_for(const burst_params* p);
 
 /* Timing helper for harnesses that cannot create HIP events themselves:

@@ -15,6 +15,8 @@ def burst_attention(q, k_chunks, v_chunks, scale=None, causal=False, q_off=0, wi
     (sequence-major tensors, slices of a packed projection) are read in place, without a copy.
     block_masks: one uint8 device tensor of block flags per chunk (see binding.params) with blocks
     of `block` rows / keys, or None for a chunk without flags; or None.
+    Results are the same bits whenever a call is repeated; the order of the fp32 sums, and with it the last bits, depends on all
+    sizes of a call, the number of heads among them.
     The node saves its inputs, O and lse as torch's own operations do: a tensor changed in place before the backward is
     an error, and a second backward needs retain_graph."""
     if isinstance(k_chunks, torch.Tensor):

@@ -404,7 +404,7 @@ def burst_walk_workspace_bytes(chunks, p, flags=0):
 
 def burst_walk_dkv_form(chunks, p, with_workspace=True):
     """How the backward walk's (first) dK/dV launch is laid out: 0 a workgroup per block of keys, 1 walks cut into parts,
-    2 one workgroup per CU that takes several blocks in turn."""
+    2 one workgroup per CU that takes several blocks in turn.  For fp32 gradients (see burst.h)."""
     form = load().burst_walk_dkv_form(chunks, len(chunks), ctypes.byref(p), 1 if with_workspace else 0)
     if form < 0:
         _check(form, "burst_walk_dkv_form")

@@ -387,7 +387,7 @@ int get_d_scratch(hipStream_t stream, size_t elems, float** out) {
 }
 
 // The choice for a walk's forward and dQ launches.  `whole`: one chunk, and neither a state nor fp32 gradients that a caller could
-// go on with chunk by chunk, in which case a walk has the bits it has chunk by chunk.
+// go on with chunk by chunk.  Other walks have the bits that they have chunk by chunk where they are not split.
 auto walk_choice(bool whole) {
   return [whole](const burst_params* p, const KParams& k) { return fwd_kernels(p, k, whole); };
 }
