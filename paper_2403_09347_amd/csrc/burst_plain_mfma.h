@@ -155,7 +155,7 @@ __device__ __forceinline__ void s_terms(bf16x8 (&out)[S_TERMS], int t, float x, 
     out[i][t] = pk[0]; out[i][t + 1] = pk[1];
     if (!DOT) {
       x -= (float)pk[0]; y -= (float)pk[1];
-    } else if (i + 1 < S_TERMS) {                  // x - pk[0], y - pk[1]: one instruction each
+    } else if (i + 1 < S_TERMS) {                  // x - pk[0], y - pk[1]: one instruction each, exact (below 2^-126 nothing, as by subtraction)
       x = __builtin_amdgcn_fdot2_f32_bf16(pk, first, x, false);
       y = __builtin_amdgcn_fdot2_f32_bf16(pk, second, y, false);
     }
@@ -435,7 +435,8 @@ burst_fwd_d64_kernel(FwdArgsLite a) {
     const char* vl = smem + (2 + buf) * SF_TILE + koff * S_ROWB;
     f32x16 s[KB];
     float mx = scores(kl, kt * SF_BC + koff, Nc, k_off, s);
-    // A row's first reference in a chunk is its maximum in the whole tile: its probabilities then do not depend on the groups.
+    // A row's first reference in a chunk is its maximum in the whole tile: its probabilities then do not depend on the groups
+    // (under a window they do on the workgroup's rows, which its first tile follows).
     if (KG > 1 && unset) {
       const int other = koff ^ (32 * KB);
       f32x16 t[KB];

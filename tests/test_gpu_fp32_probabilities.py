@@ -111,3 +111,24 @@ def test_grouped_heads_with_partial_last_tiles_keep_fp32_probabilities_in_dkv(sp
         check_gradients(case, walk, grads, own_lse=True)
     finally:
         B.burst_set_kernel_family(0)
+
+
+@pytest.mark.parametrize("d", [40, 96, 120])
+def test_gradients_of_tiny_values(d):
+    """dO times 2^-60 and 2^-100: the same digits.  Smaller, dS and the two remainders it is split into leave the range of
+    normal numbers, where each counts as nothing: 2^-126 a pair for each at most, and as much for dP before."""
+    case = workloads.make_case(B=1, H=2, d=d, Nq=192, chunk_rows=[192], dtype="bf16", seed=113, device="cuda:0")
+    dO = case["dO"].float()
+    for e in (60, 100, 112, 118):
+        case["dO"] = (dO * 2.0 ** -e).bfloat16()
+        walk, _, _, grads = walk_of(case)
+        if e <= 100:
+            check_gradients(case, walk, grads)
+            continue
+        for h in range(2):
+            Q, K = f64(case["Q"][0, h]), f64(case["K"][0][0, h])
+            _, _, dQ, dK, dV = references(case, walk, 0, h)
+            lost = case["scale"] * 4 * 2.0 ** -126
+            assert np.all(np.abs(f64(grads[0][0, h]) - dQ) <= lost * np.abs(K).sum(0) + BAR * np.abs(dQ).max())
+            assert np.all(np.abs(f64(grads[1][0][0, h]) - dK) <= lost * np.abs(Q).sum(0) + BAR * np.abs(dK).max())
+            assert off(f64(grads[2][0][0, h]), dV) < BAR

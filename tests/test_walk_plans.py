@@ -105,3 +105,21 @@ def test_without_the_forward_flag_the_size_is_enough_for_both_calls():
     state = lambda s: s * 8 * 2048 * 130 * 4
     assert workspace(p, [2048], flags=B.BURST_WALK_FORWARD) == state(4) and workspace(p, [2048], flags=B.BURST_WALK_HALF_GRADS) == state(4)
     assert workspace(p, [2048], flags=B.BURST_WALK_FORWARD | B.BURST_WALK_NO_STATE) == state(2)
+
+
+@pytest.mark.parametrize("H,N,d,causal,state,no_state", [
+    (8, 2048, 64, True, 4, 4), (8, 2050, 64, True, 3, 3), (8, 1500, 64, True, 3, 0), (2, 2048, 64, True, 4, 4),     # 128, 136, 96, 32 blocks of 128 rows
+    (16, 2048, 64, False, 2, 2), (20, 2048, 64, False, 0, 0),                                                       # 256 and 320
+    (8, 2048, 128, True, 4, 2), (8, 2050, 128, True, 3, 0), (8, 2048, 128, False, 4, 2), (2, 2048, 128, True, 4, 4)])
+def test_key_ranges_of_walks_without_a_state(H, N, d, causal, state, no_state):
+    """One chunk: as many ranges as workgroups of 64 rows have places for, from 32 tiles on."""
+    p = B.params(1, H, N, 0, d, "bf16", 0.1, causal=causal)
+    size = lambda flags: workspace(p, [N], flags=flags | B.BURST_WALK_FORWARD) / (H * N * (d + 2) * 4)
+    assert size(0) == state and size(B.BURST_WALK_NO_STATE) == no_state
+
+
+def test_half_gradients_in_row_groups_ask_for_no_partial_ones():
+    for H, N, d in ((32, 777, 96), (16, 900, 64)):
+        p = B.params(1, H, N, 0, d, "bf16", 0.1, causal=True)
+        assert workspace(p, [N]) > 0 and workspace(p, [N], flags=B.BURST_WALK_HALF_GRADS) == 0
+        assert form(H, N, [N], True, d=d, causal=True) == 1                        # (with fp32 gradients)
