@@ -152,7 +152,7 @@ static int launch_merge_dkv(const A& a, hipStream_t stream) {
 template <typename A>
 static void set_row_parts(A& a, const BwdIo& io) {
   a.parts = io.parts != nullptr ? io.parts->parts : RowParts{nullptr, 1, 1, 1, 0};
-  for (int i = 0; i < a.n && io.parts != nullptr; i++) {
+  for (int i = 0; i < a.n && a.parts.splits > 1; i++) {
     const RowSpan& s = io.parts->span[i];
     a.ch[i].first_row = s.first; a.ch[i].span_lo = s.lo; a.ch[i].span_keys = s.keys;
   }

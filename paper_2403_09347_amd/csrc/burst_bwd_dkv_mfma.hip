@@ -690,7 +690,7 @@ static long long lay_out(DkvArgs& a, const KParams& p, const Chunk* ch, int n, i
   a.c = p.scale * kLog2e; a.scale = p.scale; a.causal = p.causal; a.q_off = p.q_off; a.window = p.window; a.bsize = p.bsize;
   a.n = n; a.lay = p.lay;
   for (int i = 0; i < n; i++) a.ch[i] = ch[i];
-  for (int i = 0; i < n; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, 32 * key_waves, DKV_BR, key_waves == 4 ? 1 : 2);
+  for (int i = 0; i < n && splits == 1; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, 32 * key_waves, DKV_BR, key_waves == 4 ? 1 : 2);
   return chunk_grid(a.ch, n, a.H, 32 * key_waves, a.per, key_waves == 4 ? splits : 1);
 }
 bool dkv_chained(const KParams& p, const Chunk* ch, int n) {

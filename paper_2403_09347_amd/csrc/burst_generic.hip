@@ -1205,7 +1205,7 @@ static int gen_dispatch(GenArgs& a, const KParams& p, int dtype, hipStream_t s) 
   if (grid > 0x7fffff00LL) return BURST_ERR_SHAPE;
   if (grid == 0) return BURST_OK;
   if (KIND == GEN_DKV)
-    for (int i = 0; i < a.n; i++) a.ch[i].order = keys_order(p, a.ch[i], a.n, a.BH / a.group, 32, 32, 1);
+    for (int i = 0; i < a.n && a.parts.splits == 1; i++) a.ch[i].order = keys_order(p, a.ch[i], a.n, a.BH / a.group, 32, 32, 1);
   else a.order = grid_order(a.BH, (long long)a.blocks * a.splits, unequal_rows(p, a.ch, a.n, 32), 1);
   if (KIND == GEN_DKV ? a.parts.splits > 1 : a.splits > 1) {
     if (dtype != BURST_F32 || !fp32_tiles(a.d, a.lay, a.ch, a.n) || a.ch[0].bmask != nullptr || a.splits > 64) return BURST_ERR_SHAPE;

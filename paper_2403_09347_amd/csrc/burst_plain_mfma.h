@@ -1344,7 +1344,7 @@ int launch_bwd_dkv(const KParams& p, const BwdIo& io, const Chunk* ch, int n, hi
   const int groups = nw == 2 ? 1 : io.parts != nullptr && io.parts->groups == 2 && a.parts.splits == 1 && !flags ? G : SK_GROUPS, bc = sk_keys(nw, groups);
   const long long nb = chunk_grid(a.ch, n, a.H, bc, a.per, a.parts.splits);
   if (a.parts.splits > 1 && flags) return BURST_ERR_SHAPE;
-  for (int i = 0; i < n; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, bc, 32, nw == 8 ? 1 : 2);
+  for (int i = 0; i < n && a.parts.splits == 1; i++) a.ch[i].order = keys_order(p, ch[i], n, a.H, bc, 32, nw == 8 ? 1 : 2);
   static DeviceOnce done, done2;
   const int st = launch_plain(a.parts.splits > 1 ? burst_bwd_dkv_d64_kernel<false, true, SK_GROUPS, SK_WAVES>
                               : groups == G ? burst_bwd_dkv_d64_kernel<false, false, G, SK_WAVES> : burst_bwd_dkv_d64_kernel<false, false, SK_GROUPS, SK_WAVES>,
